@@ -97,6 +97,7 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     S2Meta *meta;           // [nq]
     int32_t *kept_ids;      // [nq][S2_MAX_KEPT]
     float *T;               // [nq][S2_MAX_KEPT + 1][32]
+    int32_t *gain;          // [nq][S2_MAX_KEPT + 1]
     const int64_t *ivf_offsets;  // [C + 1] inverted-list offsets: slots are numbered by list length (null: by id)
     int32_t *qcount;        // [3] / [3][qlist_stride]: the queries by number of surviving centroids (none, 1..31, more),
     int32_t *qlist;         //   appended as their workgroups finish (null: not recorded).  Stage 2 runs one kernel per
@@ -128,6 +129,7 @@ __device__ __forceinline__ float scq_exact_entry(const float *__restrict__ crow,
     return (float)acc;
 }
 
+#define TX_STRIDE 33  // floats per row of the survivors' entries in LDS: walks along rows and along columns hit all banks
 // Survivor table of one query (runs in one workgroup, all of whose threads call it).  K = number of centroids
 // passing Eq. 5; when K <= S2_MAX_KEPT their ids are listed ascending, their rows copied to T (slot s at T[s],
 // s = 1..K), a collision-free hash shift is chosen for stage 2's table, and bin_hi / bin_scale are set from bounds
@@ -140,7 +142,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
                                       int64_t keep_words, const int32_t *top1, S2Meta *meta_q,
                                       int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq, int32_t *scan /*[waves]*/,
                                       int32_t *ids /*[S2_MAX_KEPT + 1]*/, uint32_t *trial /*[S2_NHASH][S2_HASH / 32]*/,
-                                      float *colmm /*[2][32]*/, int32_t *misc /*[2]*/, const float *__restrict__ Cm = nullptr,
+                                      float *colmm /*[3][32]*/, float *Tx /*[S2_MAX_KEPT][TX_STRIDE]*/, int32_t *gain_q, int32_t *misc /*[2]*/, const float *__restrict__ Cm = nullptr,
                                       const float *Qq = nullptr /* the query's rows, in LDS */,
                                       const int64_t *__restrict__ ivf_offsets = nullptr, int q = 0,
                                       int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0)
@@ -233,24 +235,58 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     }
     const int hash_shift = (K <= S2_MAX_KEPT) ? S2_SHIFT0 + (S2_NHASH - 1 - misc[1]) : 0;
     if (K <= S2_MAX_KEPT) {
-        for (int e = tid; e < K * QLEN; e += nthreads)
-            Tq[QLEN + e] = APPROX ? scq_exact_entry(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * DIM)
-                                  : Sq[(int64_t)ids[e >> 5] * QLEN + (e & 31)];
+        for (int e = tid; e < K * QLEN; e += nthreads) {
+            const float v = APPROX ? scq_exact_entry(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * DIM)
+                                   : Sq[(int64_t)ids[e >> 5] * QLEN + (e & 31)];
+            Tq[QLEN + e] = v;
+            Tx[(e >> 5) * TX_STRIDE + (e & 31)] = v;
+        }
         if (tid < K) kept_ids_q[tid] = ids[tid];
+        __syncthreads();
+        // Per query token: bounds of the rows for the bins, and the third largest entry as the base of the additive bound
+        // score(bag) <= sum_i base_i + sum over the members of sum_i max(0, row_i - base_i): true for any base, and tight
+        // for one that only a token's own centroid (and perhaps one more) exceeds.  With the third largest entry the
+        // passages whose bound reaches the ndocs-th best score are 1.5 to 5 times ndocs on the synthetic collections; the
+        // second largest leaves up to ten times as many at 262144 centroids, the fifth three times as many at 65536.
         if (tid < QLEN) {
-            float mx = -INFINITY, mn = INFINITY;
-            for (int s0 = 0; s0 < K; s0 += 8) {  // eight rows in flight
-                float v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = Sq[(int64_t)ids[s0 + u < K ? s0 + u : s0] * QLEN + tid];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    mx = fmaxf(mx, v[u]);
-                    mn = fminf(mn, v[u]);
-                }
+            float t0 = -INFINITY, t1 = -INFINITY, t2 = -INFINITY, mn = INFINITY;
+#pragma unroll 4
+            for (int s = 0; s < K; ++s) {
+                const float v = Tx[s * TX_STRIDE + tid];
+                const float a = fminf(t0, v);
+                t0 = fmaxf(t0, v);
+                const float b = fminf(t1, a);
+                t1 = fmaxf(t1, a);
+                t2 = fmaxf(t2, b);
+                mn = fminf(mn, v);
             }
-            colmm[tid] = mx;
+            colmm[tid] = t0;
             colmm[QLEN + tid] = mn;
+            colmm[2 * QLEN + tid] = K >= 3 ? t2 : mn;
+        }
+        __syncthreads();
+        if (tid < 64 && K > 0) {  // one wave, lane = slot
+            float g = 0.f, base = 0.f, scale = 0.f;
+            for (int i = 0; i < QLEN; ++i) {
+                const float b = colmm[2 * QLEN + i];
+                if (tid < K) g += fmaxf(Tx[tid * TX_STRIDE + i] - b, 0.f);
+                base += b;
+                scale += fmaxf(fabsf(colmm[i]), fabsf(colmm[QLEN + i]));
+            }
+            float total = g;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
+            // the rounding of these fp32 sums (at most 64 additions of values within `scale`) and of the scores themselves
+            const float slack = 2e-5f * scale;
+            const bool finite = total < INFINITY && scale < INFINITY;  // (false also when an entry is not a number)
+            const float unit = finite ? total * (1.0f / S2_UB_TOTAL) : 0.f;
+            int gq = 0;
+            if (unit > 0.f && g > 0.f) gq = (int)ceilf(g / unit * 1.00002f);
+            if (tid < K) gain_q[tid] = gq;
+            if (tid == 0) {
+                meta_q->ub_base = finite ? base + slack : INFINITY;  // infinity: nothing is ever pruned
+                meta_q->ub_unit = unit;
+            }
         }
     } else if (tid < QLEN) {
         // many survivors: the best centroid of each token bounds every row from above
@@ -265,13 +301,11 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
             u += (double)colmm[i];
             l += (double)colmm[QLEN + i];
         }
-        S2Meta m;
-        m.K = K;
-        m.bin_hi = (float)u;
+        meta_q->K = K;
+        meta_q->bin_hi = (float)u;
         const float range = (float)u - (float)l;
-        m.bin_scale = (K > 0 && range > 0.f && range < INFINITY) ? (float)SEL_BINS / range : 0.f;
-        m.hash_shift = hash_shift;
-        *meta_q = m;
+        meta_q->bin_scale = (K > 0 && range > 0.f && range < INFINITY) ? (float)SEL_BINS / range : 0.f;
+        meta_q->hash_shift = hash_shift;
         if (qlist) {
             const int cls = K == 0 ? 0 : (K <= 31 ? 1 : 2);
             const int at = atomicAdd(&qcount[cls], 1);
@@ -288,7 +322,8 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
     __shared__ int32_t scan[512];
     __shared__ int32_t ids[S2_MAX_KEPT + 1];
     __shared__ uint32_t trial[S2_NHASH * (S2_HASH / 32)];
-    __shared__ float colmm[2 * QLEN];
+    __shared__ float colmm[3 * QLEN];
+    __shared__ float Tx[S2_MAX_KEPT * TX_STRIDE];
     __shared__ int32_t misc[2];
     __shared__ int32_t top1[QLEN];
     const int q = blockIdx.x;
@@ -296,7 +331,7 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
     __syncthreads();
     stage1_survivor_table<false>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1, o.meta + q,
                                  o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, scan, ids,
-                                 trial, colmm, misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride);
+                                 trial, colmm, Tx, o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride);
 }
 
 // tilemax: [q][tile][32] column maxima of each tile (null: scores and pruning bits only).
@@ -696,7 +731,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
     __shared__ int32_t scan[TAIL_THREADS / 64 + 1];
     __shared__ int32_t ids[S2_MAX_KEPT + 1];
     __shared__ uint32_t trial[S2_NHASH * (S2_HASH / 32)];
-    __shared__ float colmm[2 * QLEN];
+    __shared__ float colmm[3 * QLEN];
+    __shared__ float Tx[S2_MAX_KEPT * TX_STRIDE];
     __shared__ int32_t misc[2];
     constexpr int TAIL_WAVES = TAIL_THREADS / 64;
     constexpr int TAIL_FLY = 8;                          // loads in flight per thread
@@ -972,7 +1008,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
     }
     stage1_survivor_table<APPROX>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1,
                                   o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT,
-                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, scan, ids, trial, colmm, misc, x.Cm, Qq,
+                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, scan, ids, trial, colmm, Tx,
+                                  o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, x.Cm, Qq,
                                   o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride);
 }
 
@@ -1058,6 +1095,7 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
     o.meta = s2.meta;
     o.kept_ids = s2.kept_ids;
     o.T = s2.T;
+    o.gain = s2.gain;
     o.ivf_offsets = s2.ivf_offsets;
     o.qcount = s2.qcount;
     o.qlist = s2.qlist;

@@ -87,15 +87,20 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_hist0_kernel(const uint64_t *
 }
 
 // Finds the boundary bin of a histogram: the smallest b with count(bins <= b) >= m_rem.  Every thread of
-// the block returns the same (bstar, before).  bstar = SEL_BINS when the whole list is taken.
+// the block returns the same (bstar, before).  bstar = SEL_BINS when the whole list is taken.  (BINS: the histogram's
+// size; bins past it count as empty.  COPIES of it, one after the other, are added up.)
+template <int BINS = SEL_BINS, int COPIES = 1>
 __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int32_t *scan /* [SEL_THREADS] */,
                               int32_t *res /* [2] */, int &bstar, int &before, int32_t m_cap = 0x7FFFFFFF)
 {
-    constexpr int PER = SEL_BINS / SEL_THREADS;
+    constexpr int PER = BINS > SEL_THREADS ? BINS / SEL_THREADS : 1;
     int32_t loc[PER];
     int32_t sum = 0;
     for (int j = 0; j < PER; ++j) {
-        loc[j] = gh[threadIdx.x * PER + j];
+        loc[j] = 0;
+        if ((int)threadIdx.x * PER + j < BINS)
+#pragma unroll
+            for (int c = 0; c < COPIES; ++c) loc[j] += gh[c * BINS + threadIdx.x * PER + j];
         sum += loc[j];
     }
     scan[threadIdx.x] = sum;
@@ -656,9 +661,9 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
 __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                   const uint32_t *__restrict__ candbits, int64_t cand_words,
                                                                   int64_t P, int32_t m, const S2Meta *__restrict__ meta,
-                                                                  const int32_t *__restrict__ hist, Sel2State *state,
-                                                                  uint64_t *__restrict__ out, int64_t out_stride,
-                                                                  uint64_t *__restrict__ blist, int64_t blist_stride)
+                                                                  const int32_t *__restrict__ hist, const int32_t *__restrict__ coarse,
+                                                                  Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
+                                                                  uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
 {
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
@@ -666,8 +671,16 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
     Sel2State *s = state + seg;
     const S2Meta mt = meta[seg];
     if (mt.K == 0) return;  // no surviving centroid: no valid key, the state stays zero and the fill takes over
+    constexpr int SEL2_GROUPS = 8;
+    const bool is_list = lists && mt.K <= S2_MAX_KEPT;
+    const int64_t n_items = is_list ? (int64_t)s->n_list : P;
+    // a list is short next to the passages the grid is sized for: most of its workgroups have nothing to read
+    if (blockIdx.x > 0 && (int64_t)blockIdx.x * SEL_THREADS * SEL2_GROUPS >= n_items) return;
     int bstar, before;
-    find_boundary(hist + (int64_t)seg * SEL_BINS, 0, scan, res, bstar, before, m);  // takes min(m, number of keys)
+    // takes min(m, number of keys); a list comes with the coarse histogram
+    if (is_list) find_boundary<S2_COARSE, S2_COPIES>(coarse + (int64_t)seg * S2_COPIES * S2_COARSE, 0, scan, res, bstar, before, m);
+    else find_boundary(hist + (int64_t)seg * SEL_BINS, 0, scan, res, bstar, before, m);
+    const int bin_shift = is_list ? S2_COARSE_SHIFT : 0;
     const int32_t n_keys = scan[SEL_THREADS - 1];
     if (blockIdx.x == 0 && threadIdx.x == 0) s->m_rem = (m < n_keys ? m : n_keys) - before;
     if (n_keys == 0) return;
@@ -678,36 +691,44 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
     const int lane = threadIdx.x & 63;
     // A wave takes SEL2_GROUPS x 64 consecutive slots per step and reserves its output positions with one pair of
     // counter updates per step (the updates return a value, so their round trip is the step's latency).
-    constexpr int SEL2_GROUPS = 8;
     const int64_t wave_id = (int64_t)blockIdx.x * (SEL_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t n_waves = (int64_t)gridDim.x * (SEL_THREADS / 64);
     unsigned long long o = 0, no = 0;
-    for (int64_t i0 = wave_id * (64 * SEL2_GROUPS); i0 < P; i0 += n_waves * (64 * SEL2_GROUPS)) {  // uniform per wave
+    for (int64_t i0 = wave_id * (64 * SEL2_GROUPS); i0 < n_items; i0 += n_waves * (64 * SEL2_GROUPS)) {  // uniform per wave
         uint64_t key[SEL2_GROUPS];
         int cls[SEL2_GROUPS];  // 0 = surely selected, 1 = boundary, 2 = dropped
         unsigned long long b0[SEL2_GROUPS], b1[SEL2_GROUPS];
         int n0 = 0, n1 = 0;
-        // word i is meaningful only when passage i is a candidate; it then holds its score word or "no score".  The
-        // candidate bits and the score words are requested together (a word that means nothing is read and dropped): one
-        // round trip to memory per step.
-        uint32_t cw[SEL2_GROUPS], sw[SEL2_GROUPS];
+        if (is_list) {  // uniform
+            const uint64_t *kl = keys + (int64_t)seg * key_stride;
 #pragma unroll
-        for (int u = 0; u < SEL2_GROUPS; ++u) {
-            const int64_t i = i0 + 64 * u + lane;
-            cw[u] = i < P ? cb[i >> 5] : 0u;
-            sw[u] = i < P ? k[i] : PLAID_S2_NO_SCORE;
-        }
+            for (int u = 0; u < SEL2_GROUPS; ++u) {
+                const int64_t i = i0 + 64 * u + lane;
+                key[u] = i < n_items ? kl[i] : PLAID_KEY_MAX;
+            }
+        } else {
+            // word i is meaningful only when passage i is a candidate; it then holds its score word or "no score".  The
+            // candidate bits and the score words are requested together (a word that means nothing is read and dropped):
+            // one round trip to memory per step.
+            uint32_t cw[SEL2_GROUPS], sw[SEL2_GROUPS];
 #pragma unroll
-        for (int u = 0; u < SEL2_GROUPS; ++u) {
-            const int64_t i = i0 + 64 * u + lane;
-            key[u] = PLAID_KEY_MAX;
-            if (((cw[u] >> (i & 31)) & 1u) && sw[u] != PLAID_S2_NO_SCORE) key[u] = ((uint64_t)sw[u] << 32) | (uint32_t)i;
+            for (int u = 0; u < SEL2_GROUPS; ++u) {
+                const int64_t i = i0 + 64 * u + lane;
+                cw[u] = i < P ? cb[i >> 5] : 0u;
+                sw[u] = i < P ? k[i] : PLAID_S2_NO_SCORE;
+            }
+#pragma unroll
+            for (int u = 0; u < SEL2_GROUPS; ++u) {
+                const int64_t i = i0 + 64 * u + lane;
+                key[u] = PLAID_KEY_MAX;
+                if (((cw[u] >> (i & 31)) & 1u) && sw[u] != PLAID_S2_NO_SCORE) key[u] = ((uint64_t)sw[u] << 32) | (uint32_t)i;
+            }
         }
 #pragma unroll
         for (int u = 0; u < SEL2_GROUPS; ++u) {
             cls[u] = 2;
             if (key[u] != PLAID_KEY_MAX) {
-                const int d = plaid_s2_bin(plaid_ord_to_score((uint32_t)(key[u] >> 32)), mt.bin_hi, mt.bin_scale);
+                const int d = plaid_s2_bin(plaid_ord_to_score((uint32_t)(key[u] >> 32)), mt.bin_hi, mt.bin_scale) >> bin_shift;
                 cls[u] = d < bstar ? 0 : (d == bstar ? 1 : 2);
             }
             b0[u] = __ballot(cls[u] == 0);
@@ -750,7 +771,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
 // serial step of the selection.  Two such passes can be chained (LEVEL 1 reads the bin filter's list, LEVEL 2 the list
 // LEVEL 1 leaves): when a few distinct scores are shared by very many passages, the first digit falls into the score
 // bits and leaves one whole tie group, the second falls into the passage-id bits and leaves 2^-11 of it.
-#define SEL2_DIGIT_MIN 1024
+#define SEL2_DIGIT_MIN 4096
 #define SEL2_SECOND_MIN_PASSAGES (1 << 19)  // indexes with more passages than this get the second digit pass
 template <int LEVEL>
 __device__ __forceinline__ int sel2_level_input(const Sel2State *s, int &m_rem)
@@ -875,8 +896,10 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
                                                                   int32_t *__restrict__ out_counts)
 {
     __shared__ uint64_t sk[SEL_SORT_CAP];
+    __shared__ int32_t dh[SEL_BINS];
     __shared__ int32_t h256[256];
     __shared__ int32_t sh[4];
+    constexpr int FIN_RANK = FIN_THREADS / 4;
     const int seg = blockIdx.x;
     const Sel2State *s = state + seg;
     // how many digit filters this query's boundary list went through (levels: how many were launched); the second one
@@ -892,11 +915,84 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
     int total = n_sure + m_rem;
 
     if (nb <= SEL_SORT_CAP) {
-        const int n2 = next_pow2(nb > 1 ? nb : 1);
-        for (int i = threadIdx.x; i < n2; i += FIN_THREADS) sk[i] = i < nb ? bl[i] : PLAID_KEY_MAX;
-        __syncthreads();
-        lds_bitonic_sort(sk, n2);
-        for (int i = threadIdx.x; i < m_rem; i += FIN_THREADS) o[n_sure + i] = sk[i];
+        int n = nb, take = m_rem, base = n_sure;
+        if (n > FIN_RANK) {
+            // One digit in LDS: the eleven bits from the highest in which the keys differ.  Keys below the boundary digit are
+            // taken, its own are left -- a handful, unless the keys tie in their scores' upper bits.
+            uint64_t key[SEL_SORT_CAP / FIN_THREADS];
+            const unsigned long long diff = done == 1 ? (s->b_or1 & s->b_nor1) : (done == 0 ? (s->b_or & s->b_nor) : 0ull);
+            const int high = diff ? 64 - __builtin_clzll(diff) : top_bit;  // keys agree at and above this bit
+            const int shift = high > SEL_RADIX_BITS ? high - SEL_RADIX_BITS : 0;
+            for (int i = threadIdx.x; i < SEL_BINS; i += FIN_THREADS) dh[i] = 0;
+            if (threadIdx.x == 0) sh[0] = sh[1] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
+                const int i = threadIdx.x + u * FIN_THREADS;
+                key[u] = i < n ? bl[i] : PLAID_KEY_MAX;
+                if (i < n) atomicAdd(&dh[(int)(key[u] >> shift) & (SEL_BINS - 1)], 1);
+            }
+            __syncthreads();
+            {
+                // thread t: bins 2 t and 2 t + 1; sums over the waves before it from the waves' totals
+                const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                const int c0 = dh[2 * threadIdx.x], c1 = dh[2 * threadIdx.x + 1];
+                int incl = c0 + c1;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int t = __shfl_up(incl, d);
+                    if (lane >= d) incl += t;
+                }
+                if (lane == 63) h256[wave] = incl;
+                __syncthreads();
+                int before = incl - c0 - c1;
+                for (int w = 0; w < wave; ++w) before += h256[w];
+                if (take > 0 && before < take && before + c0 + c1 >= take) {
+                    const bool second = before + c0 < take;
+                    sh[2] = 2 * threadIdx.x + (second ? 1 : 0);
+                    sh[3] = before + (second ? c0 : 0);
+                }
+                if (take <= 0 && threadIdx.x == 0) {
+                    sh[2] = -1;
+                    sh[3] = 0;
+                }
+                __syncthreads();
+            }
+            const int bd = sh[2], below = sh[3];
+#pragma unroll
+            for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
+                const int i = threadIdx.x + u * FIN_THREADS;
+                if (u * FIN_THREADS >= n) break;  // uniform
+                const int d = i < n ? (int)(key[u] >> shift) & (SEL_BINS - 1) : SEL_BINS;
+                if (d < bd) o[base + atomicAdd(&sh[0], 1)] = key[u];
+                if (d == bd) sk[atomicAdd(&sh[1], 1)] = key[u];
+            }
+            __syncthreads();
+            n = sh[1];
+            base += below;
+            take -= below;
+        } else {
+            if ((int)threadIdx.x < n) sk[threadIdx.x] = bl[threadIdx.x];
+            __syncthreads();
+        }
+        if (n <= FIN_RANK) {
+            // few keys: four threads count how many of them precede theirs
+            const int i = threadIdx.x >> 2;
+            if (i < n) {
+                const uint64_t key = sk[i];
+                int rank = 0;
+                for (int j = threadIdx.x & 3; j < n; j += 4) rank += sk[j] < key ? 1 : 0;
+                rank += __shfl_xor(rank, 1);
+                rank += __shfl_xor(rank, 2);
+                if ((threadIdx.x & 3) == 0 && rank < take) o[base + rank] = key;
+            }
+        } else {
+            const int n2 = next_pow2(n);
+            for (int i = n + threadIdx.x; i < n2; i += FIN_THREADS) sk[i] = PLAID_KEY_MAX;
+            __syncthreads();
+            lds_bitonic_sort(sk, n2);
+            for (int i = threadIdx.x; i < take; i += FIN_THREADS) o[base + i] = sk[i];
+        }
     } else {
         // still long (huge tie groups): radix selection over global memory by this one workgroup.  The keys of such a
         // list mostly share their digit (that is what made the list long), so a wave whose keys all have one digit
@@ -1009,11 +1105,11 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
 
 void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, const uint32_t *candbits, int nq, int64_t P,
                           int64_t cand_words, int32_t m, const Stage2Buffers &b, uint64_t *out, int64_t out_stride,
-                          int32_t *out_counts)
+                          int32_t *out_counts, int lists)
 {
     const int gx = blocks_for(P, nq);
     hipLaunchKernelGGL(sel2_filter_kernel, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P,
-                       m, b.meta, b.hist, b.state, out, out_stride, b.blist, P);
+                       m, b.meta, b.hist, b.coarse, b.state, out, out_stride, b.blist, P, lists);
     // Digit filters: only a boundary list longer than SEL2_DIGIT_MIN makes them do anything.  The second pair is worth its
     // two launches for large indexes (a tie group can be as long as the index) in launches of several queries; otherwise
     // the query's finishing workgroup handles a long remainder alone (same result).  keys2 serves as the first

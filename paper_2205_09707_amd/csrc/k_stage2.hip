@@ -34,9 +34,6 @@
 #define S2W_CAP (64 * 4 * S2_ITEMS - 32)  // tokens a wave stages per round (one byte each), whatever their alignment
 #define S2_LBWORDS ((S2_ITEMS + 3) / 4)   // words of the round's line bitmap (8 lines per item)
 #define S2_TSTRIDE 36    // floats per staged S_cq row (16-byte aligned, rows spread over the banks)
-// Inverted form: a workgroup owns 2^SHIFT consecutive passages, SHIFT = 11 (256 threads) for indexes whose range table
-// stays small at that granularity, 13 (1024 threads) for large ones; both are instances of one kernel template.
-#define IVR_THREADS(SHIFT) (256 << ((SHIFT) - 11))
 static_assert(S2_LBWORDS <= 64, "one lane clears one word of the line bitmap");
 
 // ------------------------------------------------------------------ gather form (K > S2_MAX_KEPT)
@@ -189,37 +186,50 @@ __device__ __forceinline__ float s2_score_members(uint64_t members, const float 
     return (float)d;
 }
 
-// The same score with all 32 running maxima in registers and two rows folded per step: one pass over the members.
-// For kernels with registers to spare; the additions are the same and in the same order as in s2_score_members.
-__device__ __forceinline__ float s2_score_members_wide(uint64_t members, const float *Tl, const float *rowsum)
+// The same score from rows of 32 floats without padding (slot s at row s - 1): the 16-byte pieces of row r are stored in the
+// order g ^ (r & 7), so that lanes that read one piece of different rows spread over the banks.  COLS query tokens at a
+// time and two rows per step; the additions are the same and in the same order as in s2_score_members.
+__device__ __forceinline__ int s2_row_piece(int r, int g) { return r * QLEN + 4 * (g ^ (r & 7)); }
+__device__ __forceinline__ int s2_first_bit(uint32_t v) { return __ffs((int)v) - 1; }
+__device__ __forceinline__ int s2_first_bit(unsigned long long v) { return __ffsll((long long)v) - 1; }
+// pairs (uniform): the lanes 2 j and 2 j + 1 share a bag and take half of the query tokens each, the odd lane continuing
+// the even lane's sum (half the steps where at most 32 passages are to be scored); the score is then the odd lane's.
+template <int COLS, typename SetT>
+__device__ __forceinline__ float s2_score_rows(SetT rows, const float *Tl, const float *rowsum, bool pairs, int lane)
 {
-    if ((members & (members - 1)) == 0) return rowsum[__ffsll((long long)members) - 1];
-    float acc[QLEN];
+    double d = 0.0;
+    const int g_first = pairs && (lane & 1) ? QLEN / 8 : 0, g_count = pairs ? QLEN / 8 : QLEN / 4;
+#pragma unroll 1
+    for (int g0 = 0; g0 < g_count; g0 += COLS / 4) {
+        float acc[COLS];
 #pragma unroll
-    for (int i = 0; i < QLEN; ++i) acc[i] = -INFINITY;
-    uint64_t rest = members;
-    while (rest) {
-        const int s0 = __ffsll((long long)rest) - 1;
-        rest &= rest - 1;
-        int s1 = 0;  // row 0 holds -infinity: a neutral second operand when the member count is odd
-        if (rest) {
-            s1 = __ffsll((long long)rest) - 1;
+        for (int i = 0; i < COLS; ++i) acc[i] = -INFINITY;
+        SetT rest = rows;
+        while (rest) {
+            const int r0 = s2_first_bit(rest);
             rest &= rest - 1;
-        }
-        const float4 *ra = reinterpret_cast<const float4 *>(Tl + s0 * S2_TSTRIDE);
-        const float4 *rb = reinterpret_cast<const float4 *>(Tl + s1 * S2_TSTRIDE);
+            int r1 = r0;  // (an odd member count folds its last row twice)
+            if (rest) {
+                r1 = s2_first_bit(rest);
+                rest &= rest - 1;
+            }
 #pragma unroll
-        for (int g = 0; g < QLEN / 4; ++g) {
-            const float4 a = ra[g], b = rb[g];
-            acc[4 * g] = fmaxf(acc[4 * g], fmaxf(a.x, b.x));
-            acc[4 * g + 1] = fmaxf(acc[4 * g + 1], fmaxf(a.y, b.y));
-            acc[4 * g + 2] = fmaxf(acc[4 * g + 2], fmaxf(a.z, b.z));
-            acc[4 * g + 3] = fmaxf(acc[4 * g + 3], fmaxf(a.w, b.w));
+            for (int g = 0; g < COLS / 4; ++g) {
+                const float4 a = *reinterpret_cast<const float4 *>(Tl + s2_row_piece(r0, g_first + g0 + g));
+                const float4 b = *reinterpret_cast<const float4 *>(Tl + s2_row_piece(r1, g_first + g0 + g));
+                acc[4 * g] = fmaxf(acc[4 * g], fmaxf(a.x, b.x));
+                acc[4 * g + 1] = fmaxf(acc[4 * g + 1], fmaxf(a.y, b.y));
+                acc[4 * g + 2] = fmaxf(acc[4 * g + 2], fmaxf(a.z, b.z));
+                acc[4 * g + 3] = fmaxf(acc[4 * g + 3], fmaxf(a.w, b.w));
+            }
+        }
+#pragma unroll 1
+        for (int t = pairs ? 0 : 1; t < 2; ++t) {
+#pragma unroll
+            for (int i = 0; i < COLS; ++i) d += (double)acc[i];
+            if (t == 0) d = __shfl_xor(d, 1);  // the odd lane goes on from the even lane's sum
         }
     }
-    double d = 0.0;
-#pragma unroll
-    for (int i = 0; i < QLEN; ++i) d += (double)acc[i];
     return (float)d;
 }
 
@@ -463,14 +473,10 @@ __global__ __launch_bounds__(S2_THREADS) void s2_stream_kernel(
 // centroid).  So the candidate set is the union of the probed centroids' lists, and the pruned bag of a passage
 // (Eq. 5) is the set of surviving centroids whose lists contain it: both follow from the inverted lists of at most
 // 32 nprobe + S2_MAX_KEPT centroids, far fewer bytes than the candidates' token codes whenever few centroids
-// survive.  A workgroup owns a range of 2^SHIFT consecutive passages: it ORs the lists' entries that fall into
-// its range into 64-bit words in LDS (bit 0 = candidate, bit s = surviving slot s), then scores, emits keys, the bin
-// histogram, the candidate words and the empty-bag words of the range exactly as the streaming form does.  Where a
-// list enters a range comes from a table built once per index: table[c][r] = position in list c of its first entry
-// with passage id >= r * 2^SHIFT.
+// survive.  Where a list enters a range of 2^SHIFT passages comes from a table built once per index: table[c][r] =
+// position in list c of its first entry with passage id >= r * 2^SHIFT.
 #define IVR_EMPTY 0xFFFFFFFFu
-#define IVR_LISTS 256  // lists handled per LDS round (brought by the first IVR_LISTS threads of the workgroup)
-#define IVR_SHORT 64   // a list with at most this many entries in the range joins the pooled pass
+#define IVR_LISTS 256  // lists per round of the wide union
 #define IVR_DENSE_DIV 16  // a list with at least P / 16 entries also gets a bitmap over the passages
 
 // table[c][r] for every non-empty (list, range) pair; the others keep IVR_EMPTY until ivr_fill_kernel.
@@ -556,104 +562,6 @@ void plaid_launch_ivf_dense_fill(hipStream_t st, const int64_t *ivf_offsets, con
 {
     hipLaunchKernelGGL(ivr_dense_fill_kernel, dim3((unsigned)(C < 8192 ? C : 8192)), dim3(256), 0, st, ivf_offsets, ivf_pids, C,
                        P, dense_id, bits, words);
-}
-
-// Exclusive prefix sum of one value per thread over the first IVR_LISTS threads of the workgroup, into
-// out[0 .. IVR_LISTS]; scratch: one int per wave of those threads.  All threads of the workgroup call this.
-__device__ __forceinline__ void ivr_block_scan(int v, int32_t *out, int32_t *wave_tot)
-{
-    const int tid = threadIdx.x, lane = tid & 63;
-    if (tid >= IVR_LISTS) {  // (whole waves) the other threads only keep the barriers company
-        __syncthreads();
-        __syncthreads();
-        return;
-    }
-    int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-    }
-    if (lane == 63) wave_tot[tid >> 6] = incl;
-    __syncthreads();
-    int base = 0;
-    for (int wv = 0; wv < (tid >> 6); ++wv) base += wave_tot[wv];
-    out[tid + 1] = base + incl;
-    if (tid == 0) out[0] = 0;
-    __syncthreads();
-}
-
-// LDS work arrays of ivr_apply_round.
-struct IvrLists {
-    int64_t long_start[IVR_LISTS];              // compacted lists with more than IVR_SHORT entries in the range
-    int32_t long_cnt[IVR_LISTS];
-    unsigned long long long_val[IVR_LISTS];
-    int64_t short_start[IVR_LISTS];             // per thread: its list when it has 1 .. IVR_SHORT entries in the range
-    unsigned long long short_val[IVR_LISTS];
-    int32_t pref[IVR_LISTS + 1];                // packed prefix sums: long-list count << 20 | short entries
-    int32_t wave_tot[IVR_LISTS / 64];
-    int32_t next;
-};
-
-// One round of list application: thread t < IVR_LISTS brings one list (cnt entries of ivf_pids from `first` on fall into
-// the range of `range` passages, cnt = 0: none; the other threads bring none) and the bits `val` to OR into the set words of those passages.  Lists with few entries are pooled into
-// one flat index range that all threads share (a lane finds its entry by binary search in the prefix sums), so that
-// fifty lists of two entries cost one memory round trip instead of fifty; a long list is walked by one wave, 512
-// entries per step with eight loads in flight, waves taking lists from a shared counter.  All threads call this.
-template <typename SetT>
-__device__ __forceinline__ void ivr_apply_round(int cnt, int64_t first, unsigned long long val,
-                                                const int32_t *__restrict__ ivf_pids, uint32_t r0, uint32_t range,
-                                                SetT *lsets, IvrLists &L)
-{
-    const int tid = threadIdx.x, lane = tid & 63;
-    const bool is_long = cnt > IVR_SHORT;
-    const int packed = is_long ? (1 << 20) : cnt;
-    if (tid == 0) L.next = 0;
-    ivr_block_scan(packed, L.pref, L.wave_tot);
-    if (is_long) {
-        const int at = L.pref[tid] >> 20;
-        L.long_start[at] = first;
-        L.long_cnt[at] = cnt;
-        L.long_val[at] = val;
-    } else if (cnt > 0) {
-        L.short_start[tid] = first;
-        L.short_val[tid] = val;
-    }
-    __syncthreads();
-    const int n_long = L.pref[IVR_LISTS] >> 20, n_short = L.pref[IVR_LISTS] & 0xFFFFF;
-    for (int w = tid; w < n_short; w += (int)blockDim.x) {
-        int lo = 0, hi = IVR_LISTS;  // largest lo whose short-entry prefix is <= w: the list that holds entry w
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if ((L.pref[mid] & 0xFFFFF) <= w) lo = mid;
-            else hi = mid;
-        }
-        const uint32_t loc = (uint32_t)ivf_pids[L.short_start[lo] + (w - (L.pref[lo] & 0xFFFFF))] - r0;
-        if (loc < range) atomicOr(&lsets[loc], (SetT)L.short_val[lo]);  // (false only if a list is not ascending)
-    }
-    for (;;) {
-        int l = 0;
-        if (lane == 0) l = atomicAdd(&L.next, 1);
-        l = s2_uniform(__shfl(l, 0));
-        if (l >= n_long) break;
-        const int n = s2_uniform(L.long_cnt[l]);
-        const int32_t *__restrict__ src = ivf_pids + L.long_start[l];
-        const SetT v = (SetT)L.long_val[l];
-        for (int e0 = 0; e0 < n; e0 += 512) {
-            uint32_t pid[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = e0 + 64 * u + lane;
-                pid[u] = e < n ? (uint32_t)src[e] : 0xFFFFFFFFu;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t loc = pid[u] - r0;
-                if (pid[u] != 0xFFFFFFFFu && loc < range) atomicOr(&lsets[loc], v);
-            }
-        }
-    }
-    __syncthreads();
 }
 
 // Queries none of whose centroids passes Eq. 5: every bag is empty, so stage 2 only has to produce the candidate set,
@@ -768,202 +676,519 @@ __global__ __launch_bounds__(UW_THREADS) void s2_union_wide_kernel(
     }
 }
 
-// Counting sort of a round's bags by size (LDS).
-#define S2_ORDER_ROUND 2048  // passages per round
-struct S2Order {
-    int32_t count[64];                // bags of each size (2..63 members)
-    int32_t start[64];                // running positions, largest size first
-    int32_t total;
-    uint16_t list[S2_ORDER_ROUND];    // round-local passages in that order
-};
-// The list-application arrays and the sort are never live together.
-union S2InvertScratch {
-    IvrLists lists;
-    S2Order order;
-};
+// The range kernel.  A WAVE owns 2^len passages at a time (2048 unless the launch is small).  Every surviving slot has a
+// bit plane over them: word w, bit b = the slot is in the bag of passage p0 + 32 w + b.  The planes of long lists are the
+// index's bitmaps, those of the other lists are filled entry by entry in the wave's own LDS area.  With lane = 32 passages:
+//   bound    every passage's additive bound (S2Meta::ub_base, gains) is summed bit-sliced: the gains are wave-uniform
+//            whole numbers, a ten-bit ripple-carry addition of "gain where the plane's bit is set" serves 32 passages
+//            per lane with three instructions per bit and slot.
+//   prune    the coarse histogram of the scores computed so far (by every wave of the query) tells a bin that at least m
+//            scores have reached or passed; a passage whose bound falls into a worse bin cannot be among the best m and
+//            is not scored.  Which passages are skipped depends on timing, the best m do not.
+//   score    the remaining passages, 64 at a time with lane = passage: the bag's slots are collected from the planes
+//            and scored exactly (s2_score_members_wide), the key appended to the query's list, the bin counted.
+// While the histogram does not prune yet (the first waves of a query), a wave scores the passages with the highest
+// bounds of its range, some dozens, and looks again: a thousand such waves know the final threshold almost exactly.
+//
+// Why: of cfg3's 400 000 candidates per query about one in a hundred is scored.  Scoring all of them (a set word per
+// passage built with LDS atomics, one lane per passage, sorted by bag size) took 3.5 ms per 512 queries, 25 ms per 150
+// queries of 8.8 M passages at C = 262144.
+#define IV_WAVES 4
+#define IV_LISTS 256    // probed-only lists a workgroup classifies; beyond (nprobe > 8) they are walked unclassified
 
-// SetT: the per-passage set word.  Queries with at most 31 surviving centroids fit 32-bit words (bit 0 = candidate,
-// bits 1..31 = slots), which halves the kernel's largest LDS array and lets two of the 1024-thread workgroups share a
-// compute unit; the 64-bit instance serves the other queries.  Both are launched; each leaves the other's queries alone.
+// Makes the compiler forget what it has derived from v.  Addresses and lane masks computed from the lane number would
+// otherwise be kept in registers across the range kernel's loops (25 registers past what four waves per SIMD leave).
+__device__ __forceinline__ void s2_opaque(int &v) { asm volatile("" : "+v"(v)); }
+
+// Sum over the lanes of a value below 64: one ballot per bit, no exchange between lanes.
+__device__ __forceinline__ int s2_wave_sum6(int v)
+{
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) n += __popcll(__ballot((v >> k) & 1)) << k;
+    return n;
+}
+// Inclusive prefix sum over the lanes: additions with data-parallel-primitive operands (shifts by 1, 2, 4, 8 within a row of
+// sixteen lanes, then the last lane of a row added to the rows that follow), no LDS exchange.  All lanes active.
+__device__ __forceinline__ int s2_wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
+// the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
+__device__ __forceinline__ int2 s2_coarse_load(const int32_t *coarse_q, int lane)
+{
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(coarse_q) + lane, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    return make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
+}
 template <int SHIFT, typename SetT>
-__global__ __launch_bounds__(IVR_THREADS(SHIFT)) void s2_invert_kernel(
+__global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4 : 3) void s2_invert_kernel(
     const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride,
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
     const int32_t *__restrict__ codes, const int64_t *__restrict__ doc_offsets, int64_t P, const S2Meta *__restrict__ meta,
-    const int32_t *__restrict__ kept_ids, const float *__restrict__ T, uint32_t *__restrict__ candbits, int64_t cand_words,
-    uint64_t *__restrict__ keys2, int64_t key_stride, int32_t *__restrict__ hist, uint32_t *__restrict__ emptybits,
-    int skip_k0, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride)
+    const int32_t *__restrict__ kept_ids, const float *__restrict__ T, const int32_t *__restrict__ gain,
+    uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
+    int32_t *__restrict__ hist, int32_t *__restrict__ coarse, Sel2State *__restrict__ state,
+    uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
+    int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
+    int steps, int32_t m, int first_batch)
 {
-    constexpr int RANGE = 1 << SHIFT, THREADS = IVR_THREADS(SHIFT);
-    __shared__ SetT lsets[RANGE];
-    __shared__ uint32_t lcand[RANGE / 32], lempty[RANGE / 32];
-    __shared__ uint32_t htab[S2_HASH];
-    __shared__ __align__(16) float Tl[(S2_MAX_KEPT + 1) * S2_TSTRIDE];
-    __shared__ float rowsum[S2_MAX_KEPT + 1];
-    __shared__ int32_t lhist[SEL_BINS];
-    __shared__ S2InvertScratch scratch;
-    __shared__ uint32_t slot_probed[2];  // bit s: surviving slot s is also a probed centroid
-    const int64_t r = blockIdx.x;
-    const uint32_t r0 = (uint32_t)(r << SHIFT);
+    constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
+    // Planes of 64 words that fit a wave's area: what lets four (32-bit sets, coarse tables) or three workgroups share a
+    // compute unit.  A query with more slots takes half or a quarter of the passages at a time.
+    constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 36 : 24);
+    static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
+    constexpr int SLOTS = KMAX + 1;
+    __shared__ uint32_t area_all[IV_WAVES][FULL_PLANES * 64];
+    __shared__ __align__(16) float Tl[KMAX * QLEN];
+    __shared__ float rowsum[SLOTS];
+    __shared__ int32_t kid[SLOTS], drow[SLOTS];  // slot - 1 -> centroid, row of its list's bitmap or -1
+    __shared__ uint8_t order[SLOTS];             // the slots (minus one) with a bitmap, from the back those without
+    __shared__ int32_t plist[IV_LISTS];    // probed lists of no surviving centroid: bitmap rows from the front, centroids from the back
+    __shared__ uint32_t probed_mask[2];    // bit s: slot s + 1 is also probed
+    __shared__ int32_t n_front, n_back, n_sparse;
+    // per wave; while lists are applied: start (low 32 bits), start (high bits) << 21 | entries << 7 | plane, candidate words;
+    // while passages are scored: 16-bit counts of the coarse bins, ranks of the words' first bits, selected words
+    __shared__ uint32_t lstart_all[IV_WAVES][64];
+    __shared__ uint32_t lcnt_all[IV_WAVES][64];
+    __shared__ uint32_t lcand_all[IV_WAVES][64];
+    static_assert(S2_COARSE == 128, "two 16-bit coarse counts per lane");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = s2_uniform(tid >> 6);
-    // This instance's queries: those with 1..31 (32-bit sets) or more (64-bit sets) surviving centroids, and with the
-    // 32-bit instance those without any unless s2_union_wide_kernel has produced their candidate and empty-bag words.
-    // Row y of the grid takes entries y, y + gridDim.y, ... of the lists the probe kernel made.
-    // skip_k0 bit 1 (64-bit instance only): this instance is the only one launched and takes every query (a launch of a
-    // few queries: one kernel less on the way of each).
+    uint32_t *area = area_all[wave];
+    uint32_t *lstart = lstart_all[wave];
+    uint32_t *lcnt = lcnt_all[wave];
+    uint32_t *lcand = lcand_all[wave];
+    // This instance's queries, from the lists the probe kernel made: class 1 (1..31 survivors) or 2 (more), and with the
+    // 32-bit instance class 0 (none) unless s2_union_wide_kernel has produced its candidate and empty-bag words (mode bit
+    // 0).  mode bit 1 (64-bit instance): the only instance launched, it takes every query.  Bit 3: see the launch.  Consecutive workgroups take
+    // consecutive queries of one passage range: all queries of a chunk advance together, so that each has a threshold to
+    // prune with after its first ranges, and the bitmap rows of the range are shared in the caches.
     const int cls = sizeof(SetT) == 4 ? 1 : 2;
-    const bool take_all = sizeof(SetT) == 8 && (skip_k0 & 2);
-    const bool skip_none = skip_k0 & 1;
-    const int n_first = take_all ? qcount[1] : qcount[cls];                      // entries of list 1 (or of this class)
-    const int n_second = take_all ? qcount[2] : 0;                               // then of list 2
-    const int n_none = ((cls == 1 || take_all) && !skip_none) ? qcount[0] : 0;   // then of list 0
+    const bool take_all = sizeof(SetT) == 8 && (mode & 2);
+    const bool single = take_all && (mode & 4);  // one query: number 0, whatever its class
+    const int n_first = single ? 1 : (take_all ? qcount[1] : qcount[cls]);
+    const int n_second = take_all && !single ? qcount[2] : 0;
+    const int n_none = ((cls == 1 || take_all) && !single && !(mode & 1)) ? qcount[0] : 0;
     const int n_all = n_first + n_second + n_none;
-    // Only the 2048-passage instance with 64-bit sets loops: its class is usually empty or nearly so, and a launch of
-    // nq rows of workgroups that all find nothing to do costs tens of microseconds.  The other instances are launched
-    // with one row per query and take one entry (a class that holds most of the chunk's queries runs faster that way).
-    constexpr bool LOOP = SHIFT == 11 && sizeof(SetT) == 8;
-    int qi = blockIdx.y;
-    if (qi >= n_all) return;  // uniform
-    do {
-    const int q = qi < n_first ? qlist[(int64_t)(take_all ? 1 : cls) * qlist_stride + qi]
-                               : (qi < n_first + n_second ? qlist[2ll * qlist_stride + qi - n_first]
-                                                          : qlist[qi - n_first - n_second]);
-    const int K = s2_uniform(meta[q].K);
-    if (!take_all && (K <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
-    const bool slots = K > 0 && K <= S2_MAX_KEPT;  // bags are kept as slot sets
-    const int hsh = s2_uniform(meta[q].hash_shift);
-    for (int e = tid; e < RANGE; e += THREADS) lsets[e] = (SetT)0;
-    for (int e = tid; e < SEL_BINS; e += THREADS) lhist[e] = 0;
-    if (tid < 2) slot_probed[tid] = 0u;
-    if (slots) s2_stage_tables(q, K, hsh, kept_ids, T, htab, Tl, rowsum);
-    else __syncthreads();
-
-    // The lists to apply, in one index space: the probed centroids' (candidate bit, plus the slot bit when the centroid
-    // also survives), then the surviving centroids' that were not probed (slot bit only).  A round takes IVR_LISTS of
-    // them: the centroid ids are fetched first, the slots of the probed ones marked in LDS, and only then -- one
-    // barrier later, which by then costs no memory round trip -- do all lists of the round look up their stretch of
-    // the range together.  (A surviving centroid's round comes after every probed centroid's mark.)
-    const int nu = n_uniq[q], ntot = nu + (slots ? K : 0);
-    for (int u0 = 0; u0 < ntot; u0 += IVR_LISTS) {
-        const int e = u0 + tid;
-        const bool mine = tid < IVR_LISTS && e < ntot, survivor = mine && e >= nu;
-        int32_t c = -1;
-        if (mine) c = survivor ? kept_ids[(int64_t)q * S2_MAX_KEPT + e - nu] : uniq[(int64_t)q * uniq_stride + e];
-        unsigned long long val = 0;
-        if (mine && !survivor) {
-            const uint32_t sl = slots ? s2_lookup(htab, (uint32_t)c, hsh) : 0u;
-            val = 1ull | (sl ? 1ull << sl : 0ull);
-            if (sl) atomicOr(&slot_probed[sl >> 5], 1u << (sl & 31));
+    const int rb = (int)(blockIdx.x / (unsigned)nqx);
+    for (int qi = (int)(blockIdx.x % (unsigned)nqx); qi < n_all; qi += nqx) {
+        const int q = single ? 0 : s2_uniform(qi < n_first ? qlist[(int64_t)(take_all ? 1 : cls) * qlist_stride + qi]
+                                              : (qi < n_first + n_second ? qlist[2ll * qlist_stride + qi - n_first]
+                                                                         : qlist[qi - n_first - n_second]));
+        // everything that does not depend on the number of survivors is requested at once (the tables have room for
+        // S2_MAX_KEPT survivors and uniq_stride probes; what lies past their ends is not used)
+        const S2Meta mt = meta[q];
+        const int kept_lane = tid < S2_MAX_KEPT ? kept_ids[(int64_t)q * S2_MAX_KEPT + tid] : 0;
+        const int gain_any = gain[(int64_t)q * (S2_MAX_KEPT + 1) + lane];
+        const int probed_c = tid < uniq_stride ? uniq[(int64_t)q * uniq_stride + tid] : 0;
+        const int K_all = s2_uniform(mt.K);
+        if (!take_all && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
+        const int K = K_all <= KMAX ? K_all : 0;  // slots kept as planes (0 also for the queries scored from token codes)
+        const int nu = n_uniq[q];
+        const bool classified = nu <= IV_LISTS;
+        const int32_t *uq = uniq + (int64_t)q * uniq_stride;
+        __syncthreads();  // the previous query's readers are done
+        if (tid < 64) {
+            int32_t c = -1, d = -1;
+            if (tid < K) {
+                c = kept_lane;
+                d = dense_id[c];
+                kid[tid] = c;
+                drow[tid] = d;
+            }
+            const unsigned long long below = (1ull << tid) - 1ull;
+            const unsigned long long sm = __ballot(tid < K && d < 0), dm = __ballot(tid < K && d >= 0);
+            if (tid < K) order[d >= 0 ? __popcll(dm & below) : SLOTS - 1 - __popcll(sm & below)] = (uint8_t)tid;
+            if (tid == 0) {
+                n_sparse = __popcll(sm);
+                n_front = n_back = 0;
+                probed_mask[0] = probed_mask[1] = 0u;
+            }
+        }
+        for (int e = tid; e < K * (QLEN / 4); e += 64 * IV_WAVES)
+            *reinterpret_cast<float4 *>(Tl + s2_row_piece(e >> 3, e & 7)) =
+                *reinterpret_cast<const float4 *>(T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN + QLEN + 4 * e);
+        const int gain_lane = lane < K ? gain_any : 0;
+        __syncthreads();
+        if (tid < K) {  // one survivor in the bag: its row, summed in the same order as in s2_score_rows
+            double d = 0.0;
+            for (int i = 0; i < QLEN; ++i) d += (double)Tl[s2_row_piece(tid, i >> 2) + (i & 3)];
+            rowsum[tid] = (float)d;
+        }
+        if (classified) {
+            static_assert(64 * IV_WAVES >= IV_LISTS, "one thread per probed list");
+            if (tid < nu) {
+                const int32_t c = probed_c;
+                const int32_t d = dense_id[c];
+                int slot = -1;
+                for (int s = 0; s < K; ++s) slot = kid[s] == c ? s : slot;
+                if (slot >= 0) atomicOr(&probed_mask[slot >> 5], 1u << (slot & 31));
+                else if (d >= 0) plist[atomicAdd(&n_front, 1)] = d;
+                else plist[IV_LISTS - 1 - atomicAdd(&n_back, 1)] = c;
+            }
         }
         __syncthreads();
-        if (survivor) {
-            const int sl = e - nu + 1;
-            val = 1ull << sl;
-            if ((slot_probed[sl >> 5] >> (sl & 31)) & 1u) c = -1;  // already applied with its probed list
-        }
-        int cnt = 0;
-        int64_t first = 0;
-        if (c >= 0) {
-            const uint32_t a = table[(int64_t)c * (nr + 1) + r], b = table[(int64_t)c * (nr + 1) + r + 1];
-            first = ivf_offsets[c] + a;
-            cnt = b > a ? (int)(b - a) : 0;
-        }
-        ivr_apply_round(cnt, first, val, ivf_pids, r0, (uint32_t)RANGE, lsets, scratch.lists);
-    }
-
-    const int64_t w_first = (int64_t)r0 >> 5;  // first bitmap word of the range
-    // emit the range: lane = passage, 64 passages per step
-    const float bin_hi = meta[q].bin_hi, bin_scale = meta[q].bin_scale;
-    uint32_t *keys_out = reinterpret_cast<uint32_t *>(keys2 + (int64_t)q * key_stride);  // slot p: passage p's score word
-    uint32_t *cbq = candbits + (int64_t)q * cand_words;
-    uint32_t *ebq = emptybits + (int64_t)q * cand_words;
-    // Pass 1, lane = passage in passage order: candidate and empty-bag words, the keys of empty bags and of bags with one
-    // member (a table look-up), and how many bags there are of each larger size.
-    // Pass 2, lane = bag with two members or more, in the order of their sizes (a counting sort of the passages of a
-    // round in LDS): the lanes of a wave then run about the same number of steps over their members, where in passage
-    // order each wave would run as long as its largest bag takes.
-    S2Order &ord = scratch.order;
-    for (int b0 = 0; b0 < RANGE; b0 += S2_ORDER_ROUND) {  // (the last list application ended with a barrier)
-        if (slots) {
-            for (int e = tid; e < 64; e += THREADS) ord.count[e] = 0;
-            __syncthreads();
-        }
-        for (int g = b0 / 64 + wave; g < (b0 + S2_ORDER_ROUND) / 64; g += THREADS / 64) {
-            const SetT vs = lsets[64 * g + lane];
-            const int64_t pid = (int64_t)r0 + 64 * g + lane;
-            const bool cand = (vs & (SetT)1) && pid < P;
-            const SetT members = vs & ~(SetT)1;
-            const unsigned long long cm = __ballot(cand);
-            bool empty = true;
-            if (slots) {
-                empty = members == 0;
-                const int size = sizeof(SetT) == 4 ? __popc((uint32_t)members) : __popcll((unsigned long long)members);
-                float score = -INFINITY;
-                if (cand && size == 1) score = rowsum[__ffsll((long long)(unsigned long long)members) - 1];
-                if (cand && size <= 1) keys_out[pid] = empty ? PLAID_S2_NO_SCORE : plaid_score_to_ord(score);
-                if (cand && size > 1) atomicAdd(&ord.count[size], 1);
-                if (cand && size == 1) atomicAdd(&lhist[plaid_s2_bin(score, bin_hi, bin_scale)], 1);
+        const uint32_t pm0 = s2_uniform((int)probed_mask[0]), pm1 = s2_uniform((int)probed_mask[1]);
+        const int n_rows = s2_uniform(n_front), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
+        const int n_sp = classified ? s2_uniform(n_back) : nu;
+        int my_log = len_log;
+        while ((n_ss << (my_log - 5)) > FULL_PLANES * 64) --my_log;
+        const int len = 1 << my_log, nw = len >> 5;
+        // lane i: the i-th slot with a bitmap and its row / the i-th slot without one and its centroid
+        const int dense_slot = lane < n_dense ? order[lane] : 0, dense_row = lane < n_dense ? drow[dense_slot] : 0;
+        const int list_slot = lane < n_ss ? order[SLOTS - 1 - lane] : 64, list_c = lane < n_ss ? kid[list_slot] : -1;
+        uint64_t *klist = keys2 + (int64_t)q * key_stride;
+        uint32_t *cbq = candbits + (int64_t)q * cand_words;
+        uint32_t *ebq = emptybits + (int64_t)q * cand_words;
+        int32_t *hist_q = hist + (int64_t)q * SEL_BINS;
+        int32_t *coarse_q = coarse + ((int64_t)q * S2_COPIES + ((mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0)) * S2_COARSE;
+        const int64_t first = ((int64_t)(rb * IV_WAVES + wave) * steps) << len_log;
+        const int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
+        const int lane0 = lane;
+        for (int64_t p0 = first; p0 < last; p0 += len) {  // uniform
+            int lane = lane0;
+            s2_opaque(lane);
+            const int64_t w0 = p0 >> 5;
+            const bool act = lane < nw && w0 + lane < cand_words;  // the lanes that hold a word of the range
+            uint32_t valid = 0u;
+            if (act) valid = P - (p0 + 32 * lane) >= 32 ? 0xFFFFFFFFu : (1u << (uint32_t)(P - (p0 + 32 * lane))) - 1u;
+            // what is known of the scores so far (used below, once the bounds are there)
+            const int2 known = s2_coarse_load(coarse_q, lane);
+            // where the surviving centroids' other lists enter the range (used further down)
+            const int64_t col = p0 >> SHIFT;
+            uint32_t list_a = 0u, list_b = 0u;
+            int64_t list_at = 0;
+            if (lane < n_ss) {
+                list_a = table[(int64_t)list_c * (nr + 1) + col];
+                list_b = table[(int64_t)list_c * (nr + 1) + col + 1];
+                list_at = ivf_offsets[list_c];
             }
-            const unsigned long long em = __ballot(cand && empty);
-            if (lane == 0) {
-                lcand[2 * g] = (uint32_t)cm;
-                lcand[2 * g + 1] = (uint32_t)(cm >> 32);
-                lempty[2 * g] = (uint32_t)em;
-                lempty[2 * g + 1] = (uint32_t)(em >> 32);
-            }
-        }
-        if (slots) {  // uniform
-            __syncthreads();
-            if (tid < 64) {  // exclusive prefix over the sizes, largest first: the long bags start the pass
-                const int c = ord.count[63 - lane];
-                int incl = c;
+            for (int i = 0; i < n_ss; ++i)
+                if (lane < nw) area[i * nw + lane] = 0u;
+            // bounds, bit-sliced; A[k] bit b = bit k of the gain sum of passage p0 + 32 lane + b.  A range shorter than 2048
+            // passages leaves lanes over: groups of nw lanes then take a slot each and add up their sums at the end.
+            uint32_t A[S2_UB_BITS];
 #pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int t = __shfl_up(incl, d);
-                    if (lane >= d) incl += t;
+            for (int k = 0; k < S2_UB_BITS; ++k) A[k] = 0u;
+            uint32_t any = 0u, cand = 0u;
+            auto add = [&](uint32_t b, int g) {
+                any |= b;
+                uint32_t carry = 0u;
+#pragma unroll
+                for (int k = 0; k < S2_UB_BITS; ++k) {
+                    const uint32_t x = b & (uint32_t)(((int32_t)((uint32_t)g << (31 - k))) >> 31);
+                    const uint32_t sum = A[k] ^ x ^ carry;
+                    carry = (A[k] & x) | (carry & (A[k] | x));
+                    A[k] = sum;
                 }
-                ord.start[63 - lane] = incl - c;
-                if (lane == 63) ord.total = incl;
+            };
+            const int groups = 64 / nw, grp = lane / nw, gl = lane % nw;
+            const bool gact = w0 + gl < cand_words;
+            if (groups == 1) {
+                for (int i0 = 0; i0 < n_dense; i0 += 8) {
+                    uint32_t v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        v[u] = 0u;
+                        if (i0 + u < n_dense && act)
+                            v[u] = dense_bits[(int64_t)__builtin_amdgcn_readlane(dense_row, i0 + u) * cand_words + w0 + lane];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (i0 + u < n_dense) {
+                            const int s = __builtin_amdgcn_readlane(dense_slot, i0 + u);
+                            if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= v[u];
+                            add(v[u], __builtin_amdgcn_readlane(gain_lane, s));
+                        }
+                }
+            } else {
+                for (int i0 = 0; i0 < n_dense; i0 += groups) {
+                    const int i = i0 + grp, s = __shfl(dense_slot, i & 63), row = __shfl(dense_row, i & 63);
+                    const int g = __shfl(gain_lane, s);
+                    const uint32_t v = i < n_dense && gact ? dense_bits[(int64_t)row * cand_words + w0 + gl] : 0u;
+                    if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= v;
+                    add(v, g);
+                }
+                for (int d = nw; d < 64; d <<= 1) cand |= __shfl_xor(cand, d);
             }
-            __syncthreads();
-            for (int p = b0 + tid; p < b0 + S2_ORDER_ROUND; p += THREADS) {
-                const SetT vs = lsets[p];
-                const SetT members = vs & ~(SetT)1;
-                if ((vs & (SetT)1) && (int64_t)r0 + p < P && (members & (members - 1)) != 0) {
-                    const int size = sizeof(SetT) == 4 ? __popc((uint32_t)members) : __popcll((unsigned long long)members);
-                    ord.list[atomicAdd(&ord.start[size], 1)] = (uint16_t)(p - b0);
+            for (int d0 = 0; d0 < n_rows; d0 += 8) {
+                uint32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = d0 + u < n_rows && act ? dense_bits[(int64_t)s2_uniform(plist[d0 + u]) * cand_words + w0 + lane] : 0u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) cand |= v[u];
+            }
+            // the remaining lists, entry by entry; those that only make candidates are not looked up where every passage
+            // is a candidate already
+            const int n_lists = n_ss + (__all((cand & valid) == valid) ? 0 : n_sp);
+            lcand[lane] = cand;
+            s2_wave_sync();
+            for (int u0 = 0; u0 < n_lists; u0 += 64) {
+                const int e = u0 + lane;
+                uint32_t cnt = 0u, start = 0u;
+                if (e < n_lists) {
+                    uint32_t la = list_a, lb = list_b;
+                    int64_t at = list_at;
+                    if (e >= n_ss) {
+                        const int32_t c = classified ? plist[IV_LISTS - 1 - (e - n_ss)] : uq[e - n_ss];
+                        la = table[(int64_t)c * (nr + 1) + col];
+                        lb = table[(int64_t)c * (nr + 1) + col + 1];
+                        at = ivf_offsets[c];
+                    }
+                    at += la;
+                    start = (uint32_t)at;
+                    // at most 2^13 entries (a list is ascending); lists hold fewer than 2^43 entries together
+                    cnt = (uint32_t)((uint64_t)at >> 32) << 21 | (lb > la ? lb - la : 0u) << 7 |
+                          (uint32_t)(e < n_ss ? e : 64);  // plane, 64 = the candidates
+                }
+                lstart[lane] = start;
+                lcnt[lane] = cnt;
+                s2_wave_sync();
+                const int nb = n_lists - u0 < 64 ? n_lists - u0 : 64;
+                // a quarter of the wave per list, four lists each in flight
+                const int sub = lane & 15;
+                auto apply = [&](uint32_t pid, int sl) {
+                    const uint32_t loc = pid - (uint32_t)p0;
+                    if (loc < (uint32_t)len) atomicOr(sl == 64 ? &lcand[loc >> 5] : &area[sl * nw + (int)(loc >> 5)], 1u << (loc & 31));
+                };
+                for (int l0 = lane >> 4; l0 < nb; l0 += 16) {
+                    int n[4], sl[4];
+                    uint32_t pid[4];
+                    const int32_t *src[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t pk = l0 + 4 * u < nb ? lcnt[l0 + 4 * u] : 0u;
+                        n[u] = (int)((pk >> 7) & 0x3FFFu);
+                        sl[u] = (int)(pk & 127u);
+                        src[u] = ivf_pids;
+                        if (n[u]) src[u] += (uint64_t)(pk >> 21) << 32 | lstart[l0 + 4 * u];
+                        if (sub < n[u]) pid[u] = (uint32_t)src[u][sub];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (sub < n[u]) apply(pid[u], sl[u]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        for (int x = 16 + sub; x < n[u]; x += 32) {
+                            uint32_t more[2];
+#pragma unroll
+                            for (int y = 0; y < 2; ++y)
+                                if (x + 16 * y < n[u]) more[y] = (uint32_t)src[u][x + 16 * y];
+#pragma unroll
+                            for (int y = 0; y < 2; ++y)
+                                if (x + 16 * y < n[u]) apply(more[y], sl[u]);
+                        }
+                }
+                s2_wave_sync();
+            }
+            cand = lcand[lane];
+            if (groups == 1) {
+                for (int i0 = 0; i0 < n_ss; i0 += 4) {
+                    uint32_t b[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) b[u] = i0 + u < n_ss ? area[(i0 + u) * 64 + lane] : 0u;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (i0 + u < n_ss) {
+                            const int s = __builtin_amdgcn_readlane(list_slot, i0 + u);
+                            if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= b[u];
+                            add(b[u], __builtin_amdgcn_readlane(gain_lane, s));
+                        }
+                }
+            } else {
+                for (int i0 = 0; i0 < n_ss; i0 += groups) {
+                    const int i = i0 + grp, s = __shfl(list_slot, i & 63) & 63, g = __shfl(gain_lane, s);
+                    const uint32_t b = i < n_ss ? area[i * nw + gl] : 0u;
+                    if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= b;
+                    add(b, g);
+                }
+                for (int d = nw; d < 64; d <<= 1) {
+                    uint32_t carry = 0u;
+#pragma unroll
+                    for (int k = 0; k < S2_UB_BITS; ++k) {
+                        const uint32_t x = __shfl_xor(A[k], d);
+                        const uint32_t sum = A[k] ^ x ^ carry;
+                        carry = (A[k] & x) | (carry & (A[k] | x));
+                        A[k] = sum;
+                    }
+                    cand |= __shfl_xor(cand, d);
+                    any |= __shfl_xor(any, d);
                 }
             }
-            __syncthreads();
-            const int total = ord.total;
-            for (int e = tid; e < total; e += THREADS) {
-                const int p = b0 + ord.list[e];
-                const unsigned long long members = (unsigned long long)(lsets[p] & ~(SetT)1);
-                const float score = s2_score_members_wide(members, Tl, rowsum);
-                keys_out[(int64_t)r0 + p] = plaid_score_to_ord(score);
-                atomicAdd(&lhist[plaid_s2_bin(score, bin_hi, bin_scale)], 1);
+            cand &= valid;
+            if (act) {
+                cbq[w0 + lane] = cand;
+                if (K_all <= KMAX) ebq[w0 + lane] = cand & ~any;
             }
-            if (b0 + S2_ORDER_ROUND < RANGE) __syncthreads();  // the arrays are set up again for the next round
+            if (sizeof(SetT) == 8 && K_all > KMAX) {
+                // too many survivors for slot sets: the range's candidates are scored from their token codes, all of them
+                lcand[lane] = cand;
+                s2_wave_sync();
+                const int64_t w_end = w0 + nw < cand_words ? w0 + nw : cand_words;
+                s2_gather_body(q, S, C, keepbits, keep_words, lcand, w0, w0, 1, w_end, cand_words, P, doc_offsets, codes,
+                               mt.bin_hi, mt.bin_scale, reinterpret_cast<uint32_t *>(klist), hist_q, emptybits);
+                s2_wave_sync();
+                continue;
+            }
+            uint32_t left = cand & any;
+            for (int round = 0; __any(left != 0u); ++round) {  // (no round: no candidate with a surviving centroid)
+                s2_opaque(lane);
+                // at least m scores lie in coarse bins 0 .. b: a bound in a worse bin needs no score
+                const int2 c = round == 0 ? known : s2_coarse_load(coarse_q, lane);
+                const int incl = s2_wave_scan(c.x + c.y);
+                const unsigned long long enough0 = __ballot(incl - c.y >= m), enough1 = __ballot(incl >= m);
+                if (enough1) {
+                    const int l1 = __ffsll((long long)enough1) - 1;
+                    const int b = 2 * l1 + (((enough0 >> l1) & 1ull) ? 0 : 1);
+                    const int worst = ((b + 1) << S2_COARSE_SHIFT) - 1;  // last bin of coarse bin b
+                    // smallest gain sum whose bound can still fall into a bin <= worst (bins do not rise with the sum)
+                    auto reaches = [&](int sum) {
+                        return plaid_s2_bin(mt.ub_base + mt.ub_unit * (float)sum, mt.bin_hi, mt.bin_scale) <= worst;
+                    };
+                    const unsigned long long hi = __ballot(reaches(16 * lane + 15));
+                    if (!hi) break;  // no sum does
+                    const int h = __ffsll((long long)hi) - 1;
+                    const int need = 16 * h + __ffsll((long long)__ballot(reaches(16 * h + (lane & 15)))) - 1;
+                    uint32_t above = 0u, equal = 0xFFFFFFFFu;
+#pragma unroll
+                    for (int k = S2_UB_BITS - 1; k >= 0; --k) {
+                        const uint32_t bit = (uint32_t)(((int32_t)((uint32_t)need << (31 - k))) >> 31);
+                        above |= equal & A[k] & ~bit;
+                        equal &= ~(A[k] ^ bit);
+                    }
+                    left &= above | equal;
+                }
+                uint32_t sel = left;
+                int want = enough1 ? 128 : first_batch;
+                if (s2_wave_sum6(__popc(left)) > 2 * want) {
+                    // nothing, or little, to prune with yet: the highest sums (and those that tie with the last of them)
+                    uint32_t cur = left;
+                    sel = 0u;
+#pragma unroll
+                    for (int k = S2_UB_BITS - 1; k >= 0; --k) {
+                        const uint32_t top = cur & A[k];
+                        const int n = s2_wave_sum6(__popc(top));
+                        if (n >= want) {
+                            cur = top;
+                        } else {
+                            sel |= top;
+                            want -= n;
+                            cur &= ~A[k];
+                        }
+                    }
+                    sel |= cur;
+                }
+                left &= ~sel;
+                const int pc = __popc(sel);
+                const int rank = s2_wave_scan(pc);
+                const int total = __builtin_amdgcn_readlane(rank, 63);
+                if (total == 0) break;
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&state[q].n_list, total);  // (its round trip overlaps the first batch)
+                s2_wave_sync();
+                lcnt[lane] = (uint32_t)(rank - pc);
+                lcand[lane] = sel;
+                lstart[lane] = 0u;
+                s2_wave_sync();
+                // lane = passage, 64 at a time: by their rank among the selected bits, or, where more than half of the range
+                // is selected, in passage order; two lanes per passage when there are at most 32
+                constexpr int COLS = SHIFT == 11 || sizeof(SetT) == 4 ? 16 : 4;
+                const bool walk_all = 2 * total > len, pairs = COLS == QLEN / 2 && total <= 32;
+                const int end = walk_all ? len : total;
+                for (int b0 = 0; b0 < end; b0 += 64) {
+                    s2_opaque(lane);
+                    int w, pos, at;
+                    bool live;
+                    if (walk_all && !pairs) {
+                        w = (b0 + lane) >> 5;
+                        pos = lane & 31;
+                        const uint32_t word = lcand[w];
+                        live = (word >> pos) & 1u;
+                        at = (int)lcnt[w] + __popc(word & ((1u << pos) - 1u));
+                    } else {
+                        at = pairs ? lane >> 1 : b0 + lane;
+                        live = at < total;
+                        w = 0;
+                        pos = 0;
+                        if (live) {
+#pragma unroll
+                            for (int d = 32; d > 0; d >>= 1)
+                                if ((int)lcnt[w + d] <= at) w += d;  // the last word whose first selected bit has rank <= at
+                            int r = at - (int)lcnt[w];
+                            const uint32_t word = lcand[w];
+#pragma unroll
+                            for (int d = 16; d > 0; d >>= 1) {
+                                const int n = __popc((word >> pos) & ((1u << d) - 1u));
+                                if (r >= n) {
+                                    r -= n;
+                                    pos += d;
+                                }
+                            }
+                        }
+                    }
+                    SetT rows = 0;
+                    if (live) {
+                        for (int i0 = 0; i0 < n_dense; i0 += 8) {
+                            uint32_t v[8];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) {
+                                v[u] = 0u;
+                                if (i0 + u < n_dense)
+                                    v[u] = dense_bits[(int64_t)__builtin_amdgcn_readlane(dense_row, i0 + u) * cand_words + w0 + w];
+                            }
+#pragma unroll
+                            for (int u = 0; u < 8; ++u)
+                                rows |= (SetT)((v[u] >> pos) & 1u) << __builtin_amdgcn_readlane(dense_slot, i0 + u);
+                        }
+                        for (int i0 = 0; i0 < n_ss; i0 += 8) {
+                            uint32_t v[8];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) v[u] = i0 + u < n_ss ? area[(i0 + u) * nw + w] : 0u;
+#pragma unroll
+                            for (int u = 0; u < 8; ++u)
+                                rows |= (SetT)((v[u] >> pos) & 1u) << (__builtin_amdgcn_readlane(list_slot, i0 + u) & 63);
+                        }
+                    }
+                    // bags of one member are a look-up, and a wave of nothing else (few survivors) skips the rows
+                    const bool one = (rows & (rows - 1)) == 0;
+                    float score = live && one ? rowsum[s2_first_bit(rows)] : 0.f;
+                    if (__any(!one)) {
+                        const float sum = s2_score_rows<COLS>(one ? (SetT)0 : rows, Tl, rowsum, pairs, lane);
+                        if (!one) score = sum;
+                    }
+                    if (pairs) live = live && (lane & 1);
+                    const int bin = live ? plaid_s2_bin(score, mt.bin_hi, mt.bin_scale) >> S2_COARSE_SHIFT : -1;
+                    // coarse counts in LDS; many equal bins (few survivors: few distinct scores) as one addition
+                    const int lead = __builtin_amdgcn_readlane(bin, 1);  // (an odd lane: those score where lanes pair up)
+                    const unsigned long long same = __ballot(bin == lead);
+                    if (lead >= 0 && __popcll(same) >= 8) {
+                        if (lane == 0) atomicAdd(&lstart[lead >> 1], (uint32_t)__popcll(same) << (16 * (lead & 1)));
+                    } else if (bin >= 0 && bin == lead) {
+                        atomicAdd(&lstart[bin >> 1], 1u << (16 * (bin & 1)));
+                    }
+                    if (bin >= 0 && bin != lead) atomicAdd(&lstart[bin >> 1], 1u << (16 * (bin & 1)));
+                    if (b0 == 0) base = s2_uniform(base);
+                    if (live) klist[base + at] = plaid_make_key(score, (uint32_t)(p0 + 32 * w + pos));
+                }
+                s2_wave_sync();
+                const uint32_t counts = lstart[lane];
+                if (counts & 0xFFFFu) atomicAdd(&coarse_q[2 * lane], (int32_t)(counts & 0xFFFFu));
+                if (counts >> 16) atomicAdd(&coarse_q[2 * lane + 1], (int32_t)(counts >> 16));
+            }
+            s2_wave_sync();  // the next range's planes overwrite what the last batch read
         }
     }
-    __syncthreads();
-    // the range's candidate and empty-bag words, one contiguous store each
-    int64_t w_end = w_first + RANGE / 32;
-    if (w_end > cand_words) w_end = cand_words;
-    static_assert(2 * (RANGE / 32) <= THREADS, "one thread per word of the two bitmaps");
-    if (tid < RANGE / 32 && w_first + tid < w_end) cbq[w_first + tid] = lcand[tid];
-    if (K <= S2_MAX_KEPT && tid >= RANGE / 32 && tid < 2 * (RANGE / 32) && w_first + (tid - RANGE / 32) < w_end)
-        ebq[w_first + tid - RANGE / 32] = lempty[tid - RANGE / 32];
-    if (K > S2_MAX_KEPT) {
-        // too many survivors for slot sets: the range's candidates are scored from their token codes
-        s2_gather_body(q, S, C, keepbits, keep_words, lcand, w_first, w_first + wave, THREADS / 64, w_end, cand_words, P,
-                       doc_offsets, codes, bin_hi, bin_scale, keys_out, lhist, emptybits);
-    }
-    if (K > 0) s2_flush_hist(lhist, hist + (int64_t)q * SEL_BINS);
-    if (LOOP) __syncthreads();  // the LDS arrays are set up again for the next query
-    } while (LOOP && (qi += (int)gridDim.y) < n_all);
 }
 
 void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
@@ -971,37 +1196,60 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift)
+                                  const uint32_t *dense_bits, int shift, int32_t m)
 {
     const int64_t nr = (P + (1ll << shift) - 1) >> shift;
     const int64_t nwide = (P + (1ll << UW_SHIFT) - 1) >> UW_SHIFT;
     // One workgroup per query and 2^19 passages pays off once the launch holds enough queries to fill the chip with such
-    // workgroups; below that the fine-grained kernel (one workgroup per 2^shift passages) also takes the queries
-    // without a surviving centroid.
+    // workgroups; below that the range kernel also takes the queries without a surviving centroid.
     const int wide = nq >= IVR_WIDE_MIN_QUERIES ? 1 : 0;
     if (wide)
         hipLaunchKernelGGL(s2_union_wide_kernel, dim3((unsigned)nwide, nq), dim3(UW_THREADS), 0, st, uniq, n_uniq, uniq_stride,
                            ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            b.emptybits);
-    // the looping instance (2048 passages, 64-bit sets): 128 rows of workgroups share its queries
-#define S2_INVERT(SH_, T_)                                                                                                  \
-    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)nr, (SH_ == 11 && sizeof(T_) == 8 && nq > 128) ? 128 : nq), \
-                       dim3(IVR_THREADS(SH_)), 0, st, uniq, n_uniq,                                                          \
-                       uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, P,     \
-                       b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.emptybits, wide,         \
-                       b.qcount, b.qlist, b.qlist_stride)
-    if (shift == 11 && nq < 8) {
+    // Passages per wave and step: 2048, or 128 for launches of so few passages that a wave's own chain of steps is all that
+    // counts (one query of 10 000 passages: 101 us per search with 128, 102 with 256, 110 with 512).  Steps per wave: the
+    // set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has dozens of waves to run
+    // (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M: 13.3 / 12.6 / 12.4 ms).
+    const int64_t waves = (int64_t)nq * ((P + 2047) >> 11);
+    const int len_log = waves >= 64 ? 11 : 7;
+    const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 ? 2 : 1);
+    const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
+    // Passages a wave scores before there is a threshold: all waves of a query together about eight times the m that make
+    // one, between 32 (fewer leave lanes idle) and 64 (more are scored, and counted, for nothing).
+    const int64_t per_query = (P + (1ll << len_log) - 1) >> len_log;
+    const int64_t fb = 8ll * m / per_query;
+    const int first_batch = fb < 32 ? 32 : (fb > 64 ? 64 : (int)fb);
+    const int64_t blocks = (P + per_block - 1) / per_block;
+#define S2_INVERT(SH_, T_, MODE_, NQX_)                                                                                     \
+    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)(blocks * (NQX_))), dim3(64 * IV_WAVES), 0, st, uniq,     \
+                       n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
+                       P, b.meta, b.kept_ids, b.T, b.gain, candbits, cand_words, keys2, key_stride, b.hist, b.coarse,        \
+                       b.state, b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
+                       steps, m, first_batch)
+    // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
+    // updates alone).  Workgroups are dealt to the eight XCDs in turn, so with a multiple of eight queries per passage
+    // range (empty ones added) a query's workgroups share an XCD; where that would leave much of the chip without
+    // work, every XCD of a large launch counts, and prunes by, a copy of its own (mode bit 3).
+    const int padded = (nq + 7) & ~7;
+    const bool pad = 4 * padded <= 5 * nq;
+    const int nqx = pad ? padded : nq;
+    const int own = !pad && nq * blocks > 64 ? 8 : 0;
+    if (nq < 8) {
         // a few queries: the 64-bit instance alone, taking every query (same sets, same scores, one launch less)
-        hipLaunchKernelGGL((s2_invert_kernel<11, unsigned long long>), dim3((unsigned)nr, nq), dim3(IVR_THREADS(11)), 0, st, uniq,
-                           n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets,
-                           P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.emptybits, wide | 2,
-                           b.qcount, b.qlist, b.qlist_stride);
-    } else if (shift == 11) {
-        S2_INVERT(11, uint32_t);
-        S2_INVERT(11, unsigned long long);
+        const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own;
+        if (shift == 11) S2_INVERT(11, unsigned long long, mode, nqx);
+        else S2_INVERT(13, unsigned long long, mode, nqx);
     } else {
-        S2_INVERT(13, uint32_t);
-        S2_INVERT(13, unsigned long long);
+        // the class of the 64-bit instance is empty or small more often than not: 128 columns of workgroups share it
+        const int many = nqx < 128 ? nqx : 128;
+        if (shift == 11) {
+            S2_INVERT(11, uint32_t, wide | own, nqx);
+            S2_INVERT(11, unsigned long long, wide | own, many);
+        } else {
+            S2_INVERT(13, uint32_t, wide | own, nqx);
+            S2_INVERT(13, unsigned long long, wide | own, many);
+        }
     }
 #undef S2_INVERT
 }

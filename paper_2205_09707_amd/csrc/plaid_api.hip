@@ -684,6 +684,7 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.s2.hist1 = (int32_t *)take((size_t)qc * SEL_BINS * 4);
     w.s2.hist2 = (int32_t *)take((size_t)qc * SEL_BINS * 4);
     w.s2.state = (Sel2State *)take((size_t)qc * sizeof(Sel2State));
+    w.s2.coarse = (int32_t *)take((size_t)qc * S2_COPIES * S2_COARSE * 4);
     w.s2.qcount = (int32_t *)take(4 * sizeof(int32_t));
     w.sel3_zero = take(plaid_select_zero_bytes(qc));
     w.sel4_zero = take(plaid_select_zero_bytes(qc));
@@ -701,6 +702,7 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.keys2 = (uint64_t *)take((size_t)qc * P * 8);
     w.s2.blist = (uint64_t *)take((size_t)qc * P * 8);
     w.s2.meta = (S2Meta *)take((size_t)qc * sizeof(S2Meta));
+    w.s2.gain = (int32_t *)take((size_t)qc * (S2_MAX_KEPT + 1) * 4);
     w.s2.kept_ids = (int32_t *)take((size_t)qc * S2_MAX_KEPT * 4);
     w.s2.T = (float *)take((size_t)qc * (S2_MAX_KEPT + 1) * QLEN * 4);
     w.s2.emptybits = (uint32_t *)take((size_t)qc * w.cand_words * 4);
@@ -834,12 +836,13 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         if (ix->ivr_table)
             plaid_launch_stage2_inverted(st, w.uniq, w.n_uniq, w.uniq_stride, ix->ivf_offsets, ix->ivf_pids, ix->ivr_table, w.S,
                                          C, w.keepbits, w.keep_words, ix->codes, ix->doc_offsets, P, n, w.s2, w.candbits,
-                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->ivr_shift);
+                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->ivr_shift, pl.nd);
         else
             plaid_launch_stage2(st, w.S, C, w.keepbits, w.keep_words, w.probed, nprobe, w.candbits, w.cand_words, P, ix->N,
                                 ix->doc_offsets, ix->codes, n, w.s2, w.keys2, P);
         STAMP();
-        plaid_launch_select2(st, w.keys2, P, w.candbits, n, P, w.cand_words, pl.nd, w.s2, w.sel2, pl.nd, w.n2);
+        plaid_launch_select2(st, w.keys2, P, w.candbits, n, P, w.cand_words, pl.nd, w.s2, w.sel2, pl.nd, w.n2,
+                             ix->ivr_table ? 1 : 0);
         STAMP();
         // stage 3: centroid interaction without pruning (Eq. 3-4), keep ndocs/4
         plaid_launch_ci_list(st, w.S, C, ix->doc_offsets, ix->codes, n, w.sel2, pl.nd, w.n2, pl.nd, w.keys3, pl.nd);

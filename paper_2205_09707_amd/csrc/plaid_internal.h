@@ -164,7 +164,17 @@ struct S2Meta {        // per query
     float bin_hi;      // upper bound of any non-empty passage's pruned score
     float bin_scale;   // SEL_BINS / (upper bound - lower bound), 0 when every key falls into bin 0
     int32_t hash_shift;  // hash of the streaming kernel's survivor table
+    // Additive bound of a bag's score (K <= S2_MAX_KEPT): score <= ub_base + ub_unit * sum of the members' gains.
+    float ub_base, ub_unit;
 };
+// The gains are whole numbers whose sum over all slots stays below 2^S2_UB_BITS (the inverted form adds them bit-sliced).
+#define S2_UB_BITS 10
+#define S2_UB_TOTAL 900   // sum of the gains before they are rounded up (at most one each for 63 slots)
+#define S2_COARSE 128     // bins of the coarse score histogram the inverted form prunes with
+#define S2_COARSE_SHIFT 4
+#define S2_COPIES 8       // copies of it per query (one per XCD where a query's workgroups run on several)
+static_assert(S2_UB_TOTAL + 1 + S2_MAX_KEPT < (1 << S2_UB_BITS), "the gains' sum fits the bit-sliced counter");
+static_assert((SEL_BINS >> S2_COARSE_SHIFT) == S2_COARSE, "a coarse bin is a whole number of bins");
 
 // Per-query state of the stage-2 selection (device memory, 64 bytes, zeroed before each use).
 struct Sel2State {
@@ -179,7 +189,8 @@ struct Sel2State {
     int32_t n_b2;                      // ... after the second one (only when it is launched and n_b1 > SEL2_DIGIT_MIN)
     int32_t m_rem2;
     int32_t shift2, width2;
-    int32_t pad[13];
+    int32_t n_list;                    // scored candidates in the key list (inverted form, K <= S2_MAX_KEPT)
+    int32_t pad[12];
 };
 static_assert(sizeof(Sel2State) == 128, "Sel2State is a 128-byte record");
 
@@ -198,11 +209,13 @@ struct Stage2Buffers {   // all device pointers, leading dimension = query of th
     int32_t *hist1;      // [nq][SEL_BINS]  digit histogram of an over-long boundary list
     int32_t *hist2;      // [nq][SEL_BINS]  ... of the list the first digit filter leaves, when that is over-long too
     Sel2State *state;    // [nq]
+    int32_t *coarse;     // [nq][S2_COPIES][S2_COARSE] coarse histogram of the scores the inverted form has computed so far
     int32_t *qcount;     // [3] queries of the chunk with no / 1..31 / more surviving centroids (null: not recorded)
     // no initialisation needed
     int32_t *qlist;      // [3][qlist_stride] those queries, in the order their probe workgroups finished
     int qlist_stride;
     S2Meta *meta;        // [nq]
+    int32_t *gain;       // [nq][S2_MAX_KEPT+1] gains of the slots 1..K at [0..K-1] (S2Meta::ub_base / ub_unit)
     int32_t *kept_ids;   // [nq][S2_MAX_KEPT]
     float *T;            // [nq][S2_MAX_KEPT+1][32] rows of the surviving centroids (slot 0 unused)
     uint32_t *emptybits; // [nq][cand_words] candidates whose bag is empty
@@ -211,7 +224,8 @@ struct Stage2Buffers {   // all device pointers, leading dimension = query of th
     const int64_t *ivf_offsets;  // [C + 1]: the probe kernel numbers the surviving centroids by list length
 };
 
-// Eq. 3-5 over every candidate.  The passage id of a stage-2 key is its position, so only the score half is stored:
+// Eq. 3-5 over every candidate.  The streaming form (and the inverted one for queries with more than S2_MAX_KEPT surviving
+// centroids) writes dense score words.  The passage id of a stage-2 key is its position, so only the score half is stored:
 // the 32-bit word p of query q's region of keys2 (region = key_stride 64-bit words) is the score word of candidate p
 // (plaid_score_to_ord), PLAID_S2_NO_SCORE when its bag is empty; words of 32-passage groups without candidates are left
 // untouched.  Also produced: the bin histogram of the scores and the bitmap of the candidates with an empty bag.
@@ -221,9 +235,12 @@ void plaid_launch_stage2(hipStream_t st, const float *S, int64_t C, const uint32
                          int64_t N, const int64_t *doc_offsets, const int32_t *codes, int nq, const Stage2Buffers &b,
                          uint64_t *keys2, int64_t key_stride);
 
-// Inverted form of candidate generation + stage 2 (k_stage2.hip): the same outputs as plaid_launch_ivf_union followed by
+// Inverted form of candidate generation + stage 2 (k_stage2.hip): the outputs of plaid_launch_ivf_union followed by
 // plaid_launch_stage2 (candbits included, which need not be cleared beforehand), computed from the inverted lists of
-// the probed and the surviving centroids.  table: plaid_ivf_range_table_bytes(C, P, shift) bytes filled once per index
+// the probed and the surviving centroids.  Queries with 1 .. S2_MAX_KEPT surviving centroids leave a LIST of 64-bit keys in
+// their region of keys2 (Sel2State::n_list of them, any order) instead of dense words; it and the coarse histogram (in the
+// place of the fine one) hold every candidate that can be among the best m (= the m of the selection that follows), not
+// those proven not to be.  table: plaid_ivf_range_table_bytes(C, P, shift) bytes filled once per index
 // by plaid_launch_ivf_range_table.
 // shift: log2 of the passages per table column = per workgroup of the inverted kernel, 11 or 13.
 size_t plaid_ivf_range_table_bytes(int64_t C, int64_t P, int shift);
@@ -234,7 +251,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift);
+                                  const uint32_t *dense_bits, int shift, int32_t m);
 // Bitmaps over the passages for the longest inverted lists (built once per index, next to the range table):
 // dense_id[c] = bitmap row of centroid c or -1 (counter[0], zero before the call, returns the number of rows);
 // bits: rows x words, zero before the call, words = ceil(P / 32).
@@ -263,7 +280,7 @@ void plaid_launch_ivf_build_fill(hipStream_t st, const int32_t *codes, const int
 // boundary bin is over-long), then from the empty candidates in pid order.  keys2 is overwritten (scratch).
 void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, const uint32_t *candbits, int nq, int64_t P,
                           int64_t cand_words, int32_t m, const Stage2Buffers &b, uint64_t *out, int64_t out_stride,
-                          int32_t *out_counts);
+                          int32_t *out_counts, int lists /* 1 after the inverted form */);
 
 // Eq. 3-4 over a key list (stage 3): out_keys[q][j] is the key of the passage of in_keys[q][j].
 void plaid_launch_ci_list(hipStream_t st, const float *S, int64_t C, const int64_t *doc_offsets, const int32_t *codes,
