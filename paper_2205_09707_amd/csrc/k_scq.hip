@@ -102,6 +102,7 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     int32_t *qcount;        // [3] / [3][qlist_stride]: the queries by number of surviving centroids (none, 1..31, more),
     int32_t *qlist;         //   appended as their workgroups finish (null: not recorded).  Stage 2 runs one kernel per
     int qlist_stride;       //   class and takes its queries from these lists.
+    bool need_hash;         // stage 2 will use the streaming form
 };
 
 // One entry of S_cq as the definition reads: the products of the 128 dimensions accumulated in double in index order
@@ -129,6 +130,9 @@ __device__ __forceinline__ float scq_exact_entry(const float *__restrict__ crow,
     return (float)acc;
 }
 
+// Floats per query row in the probe kernel's LDS.  The survivor table is evaluated with a lane per query token: with rows
+// of 128 floats the 32 tokens' reads fall into one bank group, and the table took 12 of the kernel's 31 us for one query.
+#define TAIL_QSTRIDE (DIM + 4)
 #define TX_STRIDE 33  // floats per row of the survivors' entries in LDS: walks along rows and along columns hit all banks
 // Survivor table of one query (runs in one workgroup, all of whose threads call it).  K = number of centroids
 // passing Eq. 5; when K <= S2_MAX_KEPT their ids are listed ascending, their rows copied to T (slot s at T[s],
@@ -140,12 +144,13 @@ __device__ __forceinline__ float scq_exact_entry(const float *__restrict__ crow,
 template <bool APPROX>
 __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ Sq, int64_t C, const uint32_t *__restrict__ kb,
                                       int64_t keep_words, const int32_t *top1, S2Meta *meta_q,
-                                      int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq, int32_t *scan /*[waves]*/,
+                                      int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq,
                                       int32_t *ids /*[S2_MAX_KEPT + 1]*/, uint32_t *trial /*[S2_NHASH][S2_HASH / 32]*/,
                                       float *colmm /*[3][32]*/, float *Tx /*[S2_MAX_KEPT][TX_STRIDE]*/, int32_t *gain_q, int32_t *misc /*[2]*/, const float *__restrict__ Cm = nullptr,
                                       const float *Qq = nullptr /* the query's rows, in LDS */,
                                       const int64_t *__restrict__ ivf_offsets = nullptr, int q = 0,
-                                      int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0)
+                                      int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0,
+                                      bool need_hash = true /* the streaming form looks survivors up */)
 {
     auto keep_word = [&](int64_t w) -> uint32_t {
         if (APPROX) return __hip_atomic_load(kb + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -158,53 +163,39 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     }
     for (int e = tid; e < S2_NHASH * (S2_HASH / 32); e += nthreads) trial[e] = 0u;
     __syncthreads();
-    // survivors in ascending id order: thread t owns the contiguous words [t * per, (t + 1) * per); positions come from
-    // a wave-level prefix sum of the per-thread counts plus the wave totals (scan[wave])
-    {
-        const int64_t per = (keep_words + nthreads - 1) / nthreads;
-        const int64_t wa = (int64_t)tid * per, wb = wa + per < keep_words ? wa + per : keep_words;
-        int cnt = 0;
-        for (int64_t w = wa; w < wb; ++w) cnt += __popc(keep_word(w));
-        int incl = cnt;
+    // the survivors' ids, in any order (sorted below): eight words per thread in flight, nearly all of them zero
+    for (int64_t w0 = tid; w0 < keep_words; w0 += 8ll * nthreads) {
+        uint32_t v[8];
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int t = __shfl_up(incl, d);
-            if ((tid & 63) >= d) incl += t;
-        }
-        if ((tid & 63) == 63) scan[tid >> 6] = incl;
-        __syncthreads();
-        int start = incl - cnt;
-        for (int wv = 0; wv < (tid >> 6); ++wv) start += scan[wv];
-        int pos = start;
-        for (int64_t w = wa; w < wb && pos < S2_MAX_KEPT; ++w) {
-            uint32_t v = keep_word(w);
-            while (v && pos < S2_MAX_KEPT) {
-                const int b = __ffs(v) - 1;
-                v &= v - 1;
-                ids[pos++] = (int32_t)(w * 32 + b);
+        for (int u = 0; u < 8; ++u) v[u] = w0 + (int64_t)u * nthreads < keep_words ? keep_word(w0 + (int64_t)u * nthreads) : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (v[u]) {
+                int pos = atomicAdd(&misc[0], __popc(v[u]));
+                for (uint32_t rest = v[u]; rest && pos < S2_MAX_KEPT; rest &= rest - 1)
+                    ids[pos++] = (int32_t)((w0 + (int64_t)u * nthreads) * 32 + __ffs(rest) - 1);
             }
-        }
-        if (tid == nthreads - 1) misc[0] = start + cnt;  // total number of survivors
-        __syncthreads();
     }
+    __syncthreads();
     int K = misc[0];
     if (C > (1ll << 26) - 2 && K <= S2_MAX_KEPT) K = S2_MAX_KEPT + 1;  // ids must fit the 26-bit field of a table entry
     // Slots in the order of decreasing inverted-list length (ties: smaller id first): the centroids most passages hold
     // get the lowest slots, which stage 2 scores through a table of their subsets.
-    if (ivf_offsets && K > 1 && K <= S2_MAX_KEPT) {
+    if (K > 1 && K <= S2_MAX_KEPT) {
         int32_t my_id = 0;
         int rank = 0;
         uint32_t *lens = trial;  // the first K words serve as the list lengths here and are cleared again below
         if (tid < K) {
             my_id = ids[tid];
-            lens[tid] = (uint32_t)(ivf_offsets[my_id + 1] - ivf_offsets[my_id]);  // at most P < 2^31 entries
+            // at most P < 2^31 entries (no lists: in the order of the ids)
+            lens[tid] = ivf_offsets ? (uint32_t)(ivf_offsets[my_id + 1] - ivf_offsets[my_id]) : 0u;
         }
         __syncthreads();
         if (tid < K) {
             const uint32_t my_len = lens[tid];
             for (int u = 0; u < K; ++u) {
                 const uint32_t len = lens[u];
-                rank += (len > my_len || (len == my_len && u < tid)) ? 1 : 0;
+                rank += (len > my_len || (len == my_len && ids[u] < my_id)) ? 1 : 0;
             }
         }
         __syncthreads();
@@ -216,7 +207,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     }
     // a hash h(c) = (c ^ (c >> sh)) & (S2_HASH - 1) that maps the survivors to distinct entries makes a lookup one
     // probe; thread t tries shift S2_SHIFT0 + t on a private bitmap.  No such shift (very rare): gather kernel.
-    if (K <= S2_MAX_KEPT) {
+    if (need_hash && K <= S2_MAX_KEPT) {
         bool ok = tid < S2_NHASH;
         if (ok) {
             const int sh = S2_SHIFT0 + tid;
@@ -233,10 +224,10 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
         __syncthreads();
         if (misc[1] < 0) K = S2_MAX_KEPT + 1;
     }
-    const int hash_shift = (K <= S2_MAX_KEPT) ? S2_SHIFT0 + (S2_NHASH - 1 - misc[1]) : 0;
+    const int hash_shift = (need_hash && K <= S2_MAX_KEPT) ? S2_SHIFT0 + (S2_NHASH - 1 - misc[1]) : 0;
     if (K <= S2_MAX_KEPT) {
         for (int e = tid; e < K * QLEN; e += nthreads) {
-            const float v = APPROX ? scq_exact_entry(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * DIM)
+            const float v = APPROX ? scq_exact_entry(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * TAIL_QSTRIDE)
                                    : Sq[(int64_t)ids[e >> 5] * QLEN + (e & 31)];
             Tq[QLEN + e] = v;
             Tx[(e >> 5) * TX_STRIDE + (e & 31)] = v;
@@ -267,6 +258,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
         __syncthreads();
         if (tid < 64 && K > 0) {  // one wave, lane = slot
             float g = 0.f, base = 0.f, scale = 0.f;
+#pragma unroll 4
             for (int i = 0; i < QLEN; ++i) {
                 const float b = colmm[2 * QLEN + i];
                 if (tid < K) g += fmaxf(Tx[tid * TX_STRIDE + i] - b, 0.f);
@@ -295,21 +287,24 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
         colmm[QLEN + tid] = -mx - 1.0f;
     }
     __syncthreads();
-    if (tid == 0) {
-        double u = 0.0, l = 0.0;
-        for (int i = 0; i < QLEN; ++i) {
-            u += (double)colmm[i];
-            l += (double)colmm[QLEN + i];
+    if (tid < 64) {  // (one wave; the bounds need no particular order of summation)
+        double u = tid < QLEN ? (double)colmm[tid] : 0.0, l = tid < QLEN ? (double)colmm[QLEN + tid] : 0.0;
+#pragma unroll
+        for (int d = 1; d < QLEN; d <<= 1) {
+            u += __shfl_xor(u, d);
+            l += __shfl_xor(l, d);
         }
-        meta_q->K = K;
-        meta_q->bin_hi = (float)u;
-        const float range = (float)u - (float)l;
-        meta_q->bin_scale = (K > 0 && range > 0.f && range < INFINITY) ? (float)SEL_BINS / range : 0.f;
-        meta_q->hash_shift = hash_shift;
-        if (qlist) {
-            const int cls = K == 0 ? 0 : (K <= 31 ? 1 : 2);
-            const int at = atomicAdd(&qcount[cls], 1);
-            if (at < qlist_stride) qlist[(int64_t)cls * qlist_stride + at] = q;  // (always, when the counts start at zero)
+        if (tid == 0) {
+            meta_q->K = K;
+            meta_q->bin_hi = (float)u;
+            const float range = (float)u - (float)l;
+            meta_q->bin_scale = (K > 0 && range > 0.f && range < INFINITY) ? (float)SEL_BINS / range : 0.f;
+            meta_q->hash_shift = hash_shift;
+            if (qlist) {
+                const int cls = K == 0 ? 0 : (K <= 31 ? 1 : 2);
+                const int at = atomicAdd(&qcount[cls], 1);
+                if (at < qlist_stride) qlist[(int64_t)cls * qlist_stride + at] = q;  // (always, when the counts start at zero)
+            }
         }
     }
 }
@@ -319,7 +314,6 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
                                                               const uint32_t *__restrict__ keepbits, int64_t keep_words,
                                                               const int32_t *__restrict__ probed, int nprobe, Stage1Out o)
 {
-    __shared__ int32_t scan[512];
     __shared__ int32_t ids[S2_MAX_KEPT + 1];
     __shared__ uint32_t trial[S2_NHASH * (S2_HASH / 32)];
     __shared__ float colmm[3 * QLEN];
@@ -330,8 +324,8 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
     if (threadIdx.x < QLEN) top1[threadIdx.x] = probed[((int64_t)q * QLEN + threadIdx.x) * nprobe];
     __syncthreads();
     stage1_survivor_table<false>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1, o.meta + q,
-                                 o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, scan, ids,
-                                 trial, colmm, Tx, o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride);
+                                 o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids,
+                                 trial, colmm, Tx, o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
 }
 
 // tilemax: [q][tile][32] column maxima of each tile (null: scores and pruning bits only).
@@ -728,7 +722,6 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
 {
     __shared__ int32_t idl[256];   // probed ids
     __shared__ int32_t top1[QLEN];
-    __shared__ int32_t scan[TAIL_THREADS / 64 + 1];
     __shared__ int32_t ids[S2_MAX_KEPT + 1];
     __shared__ uint32_t trial[S2_NHASH * (S2_HASH / 32)];
     __shared__ float colmm[3 * QLEN];
@@ -749,13 +742,14 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
     const float margin = APPROX ? x.margin : 0.f;
     // APPROX: the query's rows in LDS for the re-evaluations, and per token the rows to re-evaluate
     constexpr int TAIL_XCAP = TAIL_LANES;  // listed rows per token: one per lane
-    __shared__ __align__(16) float Qs[APPROX ? QLEN * DIM : 4];
+    __shared__ __align__(16) float Qs[APPROX ? QLEN * TAIL_QSTRIDE : 4];
     __shared__ int32_t xc_id[APPROX ? QLEN : 1][TAIL_XCAP];
     __shared__ int32_t xc_cnt[QLEN];
     const float *Qq = Qs;
     if (APPROX) {
         static_assert(TAIL_THREADS * 4 == QLEN * DIM, "one 16-byte load per thread stages the query");
-        *reinterpret_cast<float4 *>(Qs + 4 * tid) = *reinterpret_cast<const float4 *>(x.Q + (int64_t)q * QLEN * DIM + 4 * tid);
+        *reinterpret_cast<float4 *>(Qs + (tid / (DIM / 4)) * TAIL_QSTRIDE + 4 * (tid % (DIM / 4))) =
+            *reinterpret_cast<const float4 *>(x.Q + (int64_t)q * QLEN * DIM + 4 * tid);
     }
     {
         // pass 1: thread (tokens 4 tk4 .. 4 tk4 + 3, part) keeps the NP largest maxima of tiles part, part + 128, ...
@@ -904,11 +898,11 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
             if (n_x <= TAIL_XCAP) {
                 if (l < n_x) {
                     const int32_t c = xc_id[i][l];
-                    best[0] = plaid_make_key(scq_exact_entry(x.Cm + (int64_t)c * DIM, Qq + i * DIM), (uint32_t)c);
+                    best[0] = plaid_make_key(scq_exact_entry(x.Cm + (int64_t)c * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)c);
                 }
             } else {
                 walk([&](float sv, int64_t cc) {
-                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(scq_exact_entry(x.Cm + cc * DIM, Qq + i * DIM), (uint32_t)cc));
+                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(scq_exact_entry(x.Cm + cc * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)cc));
                 });
             }
         }
@@ -971,7 +965,13 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
         __syncthreads();
         {
             int cnt = 0;
-            for (int64_t w = tid; w < keep_words; w += TAIL_THREADS) cnt += __popc(abq[w]);
+            for (int64_t w0 = tid; w0 < keep_words; w0 += 8 * TAIL_THREADS) {
+                uint32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = w0 + u * TAIL_THREADS < keep_words ? abq[w0 + u * TAIL_THREADS] : 0u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) cnt += __popc(v[u]);
+            }
             if (cnt) atomicAdd(&amb_total, cnt);
         }
         __syncthreads();
@@ -997,7 +997,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
             for (int p = tid; p < n_amb * QLEN; p += TAIL_THREADS) {
                 const int64_t c = amb_rows[p >> 5];
                 const int tok = p & 31;
-                if ((!S || Sq[c * QLEN + tok] >= x.t_lo) && scq_exact_entry(x.Cm + c * DIM, Qq + tok * DIM) >= x.t_cs)
+                if ((!S || Sq[c * QLEN + tok] >= x.t_lo) && scq_exact_entry(x.Cm + c * DIM, Qq + tok * TAIL_QSTRIDE) >= x.t_cs)
                     atomicOr(&kbq[c >> 5], 1u << (c & 31));
             }
         }
@@ -1008,9 +1008,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
     }
     stage1_survivor_table<APPROX>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1,
                                   o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT,
-                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, scan, ids, trial, colmm, Tx,
+                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids, trial, colmm, Tx,
                                   o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, x.Cm, Qq,
-                                  o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride);
+                                  o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
 }
 
 // np = capacity of the tail's lists (1, 2, 4 or 8 >= nprobe); np = 0: scores and pruning bits only (large nprobe).
@@ -1100,6 +1100,7 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
     o.qcount = s2.qcount;
     o.qlist = s2.qlist;
     o.qlist_stride = s2.qlist_stride;
+    o.need_hash = s2.need_hash;
     const int np = nprobe == 1 ? 1 : (nprobe == 2 ? 2 : (nprobe <= 4 ? 4 : (nprobe <= PLAID_PROBE_FAST_MAX ? 8 : 0)));
     if (np > 0)
         launch_fused(st, phases, np, centroids, C, Q, Qd, form, A16, nq, t_cs, S, keepbits, ambbits, keep_words, tilemax, nprobe,

@@ -708,6 +708,7 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.s2.emptybits = (uint32_t *)take((size_t)qc * w.cand_words * 4);
     w.s2.qlist = (int32_t *)take((size_t)3 * qc * 4);
     w.s2.qlist_stride = qc;
+    w.s2.need_hash = ix->ivr_table == nullptr;
     w.s2.ivf_offsets = ix->ivf_offsets;
     w.sel2 = (uint64_t *)take((size_t)qc * pl.nd * 8);
     w.n2 = (int32_t *)take((size_t)qc * 4);

@@ -220,6 +220,7 @@ struct Stage2Buffers {   // all device pointers, leading dimension = query of th
     float *T;            // [nq][S2_MAX_KEPT+1][32] rows of the surviving centroids (slot 0 unused)
     uint32_t *emptybits; // [nq][cand_words] candidates whose bag is empty
     uint64_t *blist;     // [nq][P] boundary list after the bin filter
+    bool need_hash;      // the streaming form follows: the survivor table needs its hash
     // of the index (null when there is none: nearest-centroid assignment)
     const int64_t *ivf_offsets;  // [C + 1]: the probe kernel numbers the surviving centroids by list length
 };
