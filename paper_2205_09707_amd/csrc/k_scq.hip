@@ -97,7 +97,6 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     S2Meta *meta;           // [nq]
     int32_t *kept_ids;      // [nq][S2_MAX_KEPT]
     float *T;               // [nq][S2_MAX_KEPT + 1][32]
-    int32_t *gain;          // [nq][S2_MAX_KEPT + 1]
     const int64_t *ivf_offsets;  // [C + 1] inverted-list offsets: slots are numbered by list length (null: by id)
     int32_t *qcount;        // [3] / [3][qlist_stride]: the queries by number of surviving centroids (none, 1..31, more),
     int32_t *qlist;         //   appended as their workgroups finish (null: not recorded).  Stage 2 runs one kernel per
@@ -146,7 +145,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
                                       int64_t keep_words, const int32_t *top1, S2Meta *meta_q,
                                       int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq,
                                       int32_t *ids /*[S2_MAX_KEPT + 1]*/, uint32_t *trial /*[S2_NHASH][S2_HASH / 32]*/,
-                                      float *colmm /*[3][32]*/, float *Tx /*[S2_MAX_KEPT][TX_STRIDE]*/, int32_t *gain_q, int32_t *misc /*[2]*/, const float *__restrict__ Cm = nullptr,
+                                      float *colmm /*[3][32]*/, float *Tx /*[S2_MAX_KEPT][TX_STRIDE]*/, int32_t *misc /*[2]*/, const float *__restrict__ Cm = nullptr,
                                       const float *Qq = nullptr /* the query's rows, in LDS */,
                                       const int64_t *__restrict__ ivf_offsets = nullptr, int q = 0,
                                       int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0,
@@ -274,7 +273,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
             const float unit = finite ? total * (1.0f / S2_UB_TOTAL) : 0.f;
             int gq = 0;
             if (unit > 0.f && g > 0.f) gq = (int)ceilf(g / unit * 1.00002f);
-            if (tid < K) gain_q[tid] = gq;
+            if (tid < K) reinterpret_cast<uint16_t *>(Tq)[tid] = (uint16_t)gq;
             if (tid == 0) {
                 meta_q->ub_base = finite ? base + slack : INFINITY;  // infinity: nothing is ever pruned
                 meta_q->ub_unit = unit;
@@ -325,7 +324,7 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
     __syncthreads();
     stage1_survivor_table<false>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1, o.meta + q,
                                  o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids,
-                                 trial, colmm, Tx, o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
+                                 trial, colmm, Tx, misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
 }
 
 // tilemax: [q][tile][32] column maxima of each tile (null: scores and pruning bits only).
@@ -1008,8 +1007,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
     }
     stage1_survivor_table<APPROX>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1,
                                   o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT,
-                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids, trial, colmm, Tx,
-                                  o.gain + (int64_t)q * (S2_MAX_KEPT + 1), misc, x.Cm, Qq,
+                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids, trial, colmm, Tx, misc, x.Cm, Qq,
                                   o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
 }
 
@@ -1095,7 +1093,6 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
     o.meta = s2.meta;
     o.kept_ids = s2.kept_ids;
     o.T = s2.T;
-    o.gain = s2.gain;
     o.ivf_offsets = s2.ivf_offsets;
     o.qcount = s2.qcount;
     o.qlist = s2.qlist;

@@ -661,8 +661,7 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
 __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                   const uint32_t *__restrict__ candbits, int64_t cand_words,
                                                                   int64_t P, int32_t m, const S2Meta *__restrict__ meta,
-                                                                  const int32_t *__restrict__ hist, const int32_t *__restrict__ coarse,
-                                                                  Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
+                                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
                                                                   uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
 {
     __shared__ int32_t scan[SEL_THREADS];
@@ -678,7 +677,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
     if (blockIdx.x > 0 && (int64_t)blockIdx.x * SEL_THREADS * SEL2_GROUPS >= n_items) return;
     int bstar, before;
     // takes min(m, number of keys); a list comes with the coarse histogram
-    if (is_list) find_boundary<S2_COARSE, S2_COPIES>(coarse + (int64_t)seg * S2_COPIES * S2_COARSE, 0, scan, res, bstar, before, m);
+    if (is_list) find_boundary<S2_COARSE, S2_COPIES>(hist + (int64_t)seg * SEL_BINS, 0, scan, res, bstar, before, m);
     else find_boundary(hist + (int64_t)seg * SEL_BINS, 0, scan, res, bstar, before, m);
     const int bin_shift = is_list ? S2_COARSE_SHIFT : 0;
     const int32_t n_keys = scan[SEL_THREADS - 1];
@@ -1109,7 +1108,7 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
 {
     const int gx = blocks_for(P, nq);
     hipLaunchKernelGGL(sel2_filter_kernel, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P,
-                       m, b.meta, b.hist, b.coarse, b.state, out, out_stride, b.blist, P, lists);
+                       m, b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists);
     // Digit filters: only a boundary list longer than SEL2_DIGIT_MIN makes them do anything.  The second pair is worth its
     // two launches for large indexes (a tie group can be as long as the index) in launches of several queries; otherwise
     // the query's finishing workgroup handles a long remainder alone (same result).  keys2 serves as the first

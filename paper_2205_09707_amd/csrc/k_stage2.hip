@@ -735,9 +735,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
     const int32_t *__restrict__ codes, const int64_t *__restrict__ doc_offsets, int64_t P, const S2Meta *__restrict__ meta,
-    const int32_t *__restrict__ kept_ids, const float *__restrict__ T, const int32_t *__restrict__ gain,
-    uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
-    int32_t *__restrict__ hist, int32_t *__restrict__ coarse, Sel2State *__restrict__ state,
+    const int32_t *__restrict__ kept_ids, const float *__restrict__ T, uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
+    int32_t *__restrict__ hist, Sel2State *__restrict__ state,
     uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
     int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
     int steps, int32_t m, int first_batch)
@@ -789,7 +788,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         // S2_MAX_KEPT survivors and uniq_stride probes; what lies past their ends is not used)
         const S2Meta mt = meta[q];
         const int kept_lane = tid < S2_MAX_KEPT ? kept_ids[(int64_t)q * S2_MAX_KEPT + tid] : 0;
-        const int gain_any = gain[(int64_t)q * (S2_MAX_KEPT + 1) + lane];
+        const int gain_any = reinterpret_cast<const uint16_t *>(T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN)[lane];
         const int probed_c = tid < uniq_stride ? uniq[(int64_t)q * uniq_stride + tid] : 0;
         const int K_all = s2_uniform(mt.K);
         if (!take_all && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
@@ -851,7 +850,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         uint32_t *cbq = candbits + (int64_t)q * cand_words;
         uint32_t *ebq = emptybits + (int64_t)q * cand_words;
         int32_t *hist_q = hist + (int64_t)q * SEL_BINS;
-        int32_t *coarse_q = coarse + ((int64_t)q * S2_COPIES + ((mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0)) * S2_COARSE;
+        int32_t *coarse_q = hist_q + ((mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0) * S2_COARSE;
         const int64_t first = ((int64_t)(rb * IV_WAVES + wave) * steps) << len_log;
         const int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
         const int lane0 = lane;
@@ -1224,8 +1223,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
 #define S2_INVERT(SH_, T_, MODE_, NQX_)                                                                                     \
     hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)(blocks * (NQX_))), dim3(64 * IV_WAVES), 0, st, uniq,     \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
-                       P, b.meta, b.kept_ids, b.T, b.gain, candbits, cand_words, keys2, key_stride, b.hist, b.coarse,        \
-                       b.state, b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
+                       P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.state,         \
+                        b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
                        steps, m, first_batch)
     // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
     // updates alone).  Workgroups are dealt to the eight XCDs in turn, so with a multiple of eight queries per passage

@@ -684,7 +684,6 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.s2.hist1 = (int32_t *)take((size_t)qc * SEL_BINS * 4);
     w.s2.hist2 = (int32_t *)take((size_t)qc * SEL_BINS * 4);
     w.s2.state = (Sel2State *)take((size_t)qc * sizeof(Sel2State));
-    w.s2.coarse = (int32_t *)take((size_t)qc * S2_COPIES * S2_COARSE * 4);
     w.s2.qcount = (int32_t *)take(4 * sizeof(int32_t));
     w.sel3_zero = take(plaid_select_zero_bytes(qc));
     w.sel4_zero = take(plaid_select_zero_bytes(qc));
@@ -702,7 +701,6 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.keys2 = (uint64_t *)take((size_t)qc * P * 8);
     w.s2.blist = (uint64_t *)take((size_t)qc * P * 8);
     w.s2.meta = (S2Meta *)take((size_t)qc * sizeof(S2Meta));
-    w.s2.gain = (int32_t *)take((size_t)qc * (S2_MAX_KEPT + 1) * 4);
     w.s2.kept_ids = (int32_t *)take((size_t)qc * S2_MAX_KEPT * 4);
     w.s2.T = (float *)take((size_t)qc * (S2_MAX_KEPT + 1) * QLEN * 4);
     w.s2.emptybits = (uint32_t *)take((size_t)qc * w.cand_words * 4);

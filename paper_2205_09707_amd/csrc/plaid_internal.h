@@ -175,6 +175,8 @@ struct S2Meta {        // per query
 #define S2_COPIES 8       // copies of it per query (one per XCD where a query's workgroups run on several)
 static_assert(S2_UB_TOTAL + 1 + S2_MAX_KEPT < (1 << S2_UB_BITS), "the gains' sum fits the bit-sliced counter");
 static_assert((SEL_BINS >> S2_COARSE_SHIFT) == S2_COARSE, "a coarse bin is a whole number of bins");
+static_assert(S2_COPIES * S2_COARSE <= SEL_BINS, "the coarse histograms take the place of the fine one");
+static_assert((S2_MAX_KEPT + 1) * 2 <= QLEN * 4 && S2_UB_BITS <= 16, "the gains take the place of the unused row");
 
 // Per-query state of the stage-2 selection (device memory, 64 bytes, zeroed before each use).
 struct Sel2State {
@@ -205,19 +207,19 @@ __device__ __forceinline__ int plaid_s2_bin(float score, float bin_hi, float bin
 
 struct Stage2Buffers {   // all device pointers, leading dimension = query of the chunk
     // zeroed before each chunk
-    int32_t *hist;       // [nq][SEL_BINS]  bin histogram of the valid keys
+    int32_t *hist;       // [nq][SEL_BINS]  bin histogram of the valid keys; for a query that leaves a list, in its place the
+                         //   [S2_COPIES][S2_COARSE] coarse histograms of the scores computed so far
     int32_t *hist1;      // [nq][SEL_BINS]  digit histogram of an over-long boundary list
     int32_t *hist2;      // [nq][SEL_BINS]  ... of the list the first digit filter leaves, when that is over-long too
     Sel2State *state;    // [nq]
-    int32_t *coarse;     // [nq][S2_COPIES][S2_COARSE] coarse histogram of the scores the inverted form has computed so far
     int32_t *qcount;     // [3] queries of the chunk with no / 1..31 / more surviving centroids (null: not recorded)
     // no initialisation needed
     int32_t *qlist;      // [3][qlist_stride] those queries, in the order their probe workgroups finished
     int qlist_stride;
     S2Meta *meta;        // [nq]
-    int32_t *gain;       // [nq][S2_MAX_KEPT+1] gains of the slots 1..K at [0..K-1] (S2Meta::ub_base / ub_unit)
     int32_t *kept_ids;   // [nq][S2_MAX_KEPT]
-    float *T;            // [nq][S2_MAX_KEPT+1][32] rows of the surviving centroids (slot 0 unused)
+    float *T;            // [nq][S2_MAX_KEPT+1][32] rows of the surviving centroids; in the place of row 0 the gains of the
+                         //   slots 1..K as 16-bit numbers (S2Meta::ub_base / ub_unit)
     uint32_t *emptybits; // [nq][cand_words] candidates whose bag is empty
     uint64_t *blist;     // [nq][P] boundary list after the bin filter
     bool need_hash;      // the streaming form follows: the survivor table needs its hash
