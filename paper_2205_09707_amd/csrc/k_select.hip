@@ -503,6 +503,133 @@ __global__ __launch_bounds__(256) void sel_rank_output_kernel(const uint64_t *__
     }
 }
 
+// The `take` smallest (in any order) of the n <= SEL_SORT_CAP keys of `bl`, to o; every key agrees at and above bit `high`.
+// One workgroup of FIN_THREADS threads, all of which call this; sk, dh, h256, sh: LDS (keys, one digit's histogram, wave
+// totals, four words).
+#define FIN_RANK (FIN_THREADS / 4)
+__device__ __forceinline__ void sel_pick_lds(const uint64_t *__restrict__ bl, int n, int take, uint64_t *__restrict__ o, int high,
+                                             uint64_t *sk, int32_t *dh, int32_t *h256, int32_t *sh)
+{
+    int base = 0;
+    if (n > FIN_RANK) {
+        // One digit in LDS: the eleven bits from the highest in which the keys differ.  Keys below the boundary digit are
+        // taken, its own are left -- a handful, unless the keys tie in their scores' upper bits.
+        uint64_t key[SEL_SORT_CAP / FIN_THREADS];
+        const int shift = high > SEL_RADIX_BITS ? high - SEL_RADIX_BITS : 0;
+        for (int i = threadIdx.x; i < SEL_BINS; i += FIN_THREADS) dh[i] = 0;
+        if (threadIdx.x == 0) sh[0] = sh[1] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
+            const int i = threadIdx.x + u * FIN_THREADS;
+            key[u] = i < n ? bl[i] : PLAID_KEY_MAX;
+            if (i < n) atomicAdd(&dh[(int)(key[u] >> shift) & (SEL_BINS - 1)], 1);
+        }
+        __syncthreads();
+        {
+            // thread t: bins 2 t and 2 t + 1; sums over the waves before it from the waves' totals
+            const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+            const int c0 = dh[2 * threadIdx.x], c1 = dh[2 * threadIdx.x + 1];
+            int incl = c0 + c1;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int t = __shfl_up(incl, d);
+                if (lane >= d) incl += t;
+            }
+            if (lane == 63) h256[wave] = incl;
+            __syncthreads();
+            int before = incl - c0 - c1;
+            for (int w = 0; w < wave; ++w) before += h256[w];
+            if (take > 0 && before < take && before + c0 + c1 >= take) {
+                const bool second = before + c0 < take;
+                sh[2] = 2 * threadIdx.x + (second ? 1 : 0);
+                sh[3] = before + (second ? c0 : 0);
+            }
+            if (take <= 0 && threadIdx.x == 0) {
+                sh[2] = -1;
+                sh[3] = 0;
+            }
+            __syncthreads();
+        }
+        const int bd = sh[2], below = sh[3];
+#pragma unroll
+        for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
+            const int i = threadIdx.x + u * FIN_THREADS;
+            if (u * FIN_THREADS >= n) break;  // uniform
+            const int d = i < n ? (int)(key[u] >> shift) & (SEL_BINS - 1) : SEL_BINS;
+            if (d < bd) o[base + atomicAdd(&sh[0], 1)] = key[u];
+            if (d == bd) sk[atomicAdd(&sh[1], 1)] = key[u];
+        }
+        __syncthreads();
+        n = sh[1];
+        base += below;
+        take -= below;
+    } else {
+        if ((int)threadIdx.x < n) sk[threadIdx.x] = bl[threadIdx.x];
+        __syncthreads();
+    }
+    if (n <= FIN_RANK) {
+        // few keys: four threads count how many of them precede theirs
+        const int i = threadIdx.x >> 2;
+        if (i < n) {
+            const uint64_t key = sk[i];
+            int rank = 0;
+            for (int j = threadIdx.x & 3; j < n; j += 4) rank += sk[j] < key ? 1 : 0;
+            rank += __shfl_xor(rank, 1);
+            rank += __shfl_xor(rank, 2);
+            if ((threadIdx.x & 3) == 0 && rank < take) o[base + rank] = key;
+        }
+    } else {
+        const int n2 = next_pow2(n);
+        for (int i = n + threadIdx.x; i < n2; i += FIN_THREADS) sk[i] = PLAID_KEY_MAX;
+        __syncthreads();
+        lds_bitonic_sort(sk, n2);
+        for (int i = threadIdx.x; i < take; i += FIN_THREADS) o[base + i] = sk[i];
+    }
+}
+
+// The m smallest keys of each list, in no particular order: a workgroup per list, one digit and a handful of keys to rank.
+// For the few lists of a launch of single queries: rank counting, its n^2 form, takes 10 us for 1024 keys and 34 for 4096,
+// this 7 and 9.
+__global__ __launch_bounds__(FIN_THREADS) void sel_pick_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
+                                                               const int32_t *__restrict__ counts, int32_t n_cap, int32_t m,
+                                                               uint64_t *__restrict__ out, int64_t out_stride,
+                                                               int32_t *__restrict__ out_counts)
+{
+    __shared__ uint64_t sk[SEL_SORT_CAP];
+    __shared__ int32_t dh[SEL_BINS];
+    __shared__ int32_t h256[FIN_THREADS / 64];
+    __shared__ int32_t sh[4];
+    __shared__ unsigned long long differ[2];  // OR over the keys / over their complements
+    const int seg = blockIdx.x;
+    int n = counts[seg];
+    if (n > n_cap) n = n_cap;
+    const int take = m < n ? m : n;
+    if (threadIdx.x == 0) {
+        out_counts[seg] = take;
+        differ[0] = differ[1] = 0;
+    }
+    __syncthreads();
+    const uint64_t *k = keys + (int64_t)seg * key_stride;
+    unsigned long long o = 0, no = 0;
+    for (int i = threadIdx.x; i < n; i += FIN_THREADS) {
+        o |= k[i];
+        no |= ~k[i];
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        o |= __shfl_xor(o, d);
+        no |= __shfl_xor(no, d);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicOr(&differ[0], o);
+        atomicOr(&differ[1], no);
+    }
+    __syncthreads();
+    const unsigned long long diff = differ[0] & differ[1];
+    sel_pick_lds(k, n, take, out + (int64_t)seg * out_stride, diff ? 64 - __builtin_clzll(diff) : 0, sk, dh, h256, sh);
+}
+
 static inline int64_t sort_pow2(int64_t n)
 {
     int64_t p = 2;
@@ -602,7 +729,10 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
     // producer runs; see search.hip
     if (n_upper <= SEL_SORT_CAP) {
         const size_t lds = (size_t)sort_pow2(n_upper) * 8;
-        if (nseg <= RANK_MAX_LISTS) {
+        if (nseg <= RANK_MAX_LISTS && n_upper > 512 && !sorted) {
+            hipLaunchKernelGGL(sel_pick_kernel, dim3(nseg), dim3(FIN_THREADS), 0, st, keys, key_stride, counts, (int32_t)n_upper, m,
+                               out, out_stride, out_counts);
+        } else if (nseg <= RANK_MAX_LISTS) {
             const int gx = (int)((n_upper + RANK_KEYS_PER_BLOCK - 1) / RANK_KEYS_PER_BLOCK);
             hipLaunchKernelGGL(sel_rank_kernel, dim3(gx > 0 ? gx : 1, nseg), dim3(256), lds, st, keys, key_stride, counts,
                                (int32_t)n_upper, m, out, out_stride, out_counts);
@@ -898,7 +1028,6 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
     __shared__ int32_t dh[SEL_BINS];
     __shared__ int32_t h256[256];
     __shared__ int32_t sh[4];
-    constexpr int FIN_RANK = FIN_THREADS / 4;
     const int seg = blockIdx.x;
     const Sel2State *s = state + seg;
     // how many digit filters this query's boundary list went through (levels: how many were launched); the second one
@@ -914,84 +1043,8 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
     int total = n_sure + m_rem;
 
     if (nb <= SEL_SORT_CAP) {
-        int n = nb, take = m_rem, base = n_sure;
-        if (n > FIN_RANK) {
-            // One digit in LDS: the eleven bits from the highest in which the keys differ.  Keys below the boundary digit are
-            // taken, its own are left -- a handful, unless the keys tie in their scores' upper bits.
-            uint64_t key[SEL_SORT_CAP / FIN_THREADS];
-            const unsigned long long diff = done == 1 ? (s->b_or1 & s->b_nor1) : (done == 0 ? (s->b_or & s->b_nor) : 0ull);
-            const int high = diff ? 64 - __builtin_clzll(diff) : top_bit;  // keys agree at and above this bit
-            const int shift = high > SEL_RADIX_BITS ? high - SEL_RADIX_BITS : 0;
-            for (int i = threadIdx.x; i < SEL_BINS; i += FIN_THREADS) dh[i] = 0;
-            if (threadIdx.x == 0) sh[0] = sh[1] = 0;
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
-                const int i = threadIdx.x + u * FIN_THREADS;
-                key[u] = i < n ? bl[i] : PLAID_KEY_MAX;
-                if (i < n) atomicAdd(&dh[(int)(key[u] >> shift) & (SEL_BINS - 1)], 1);
-            }
-            __syncthreads();
-            {
-                // thread t: bins 2 t and 2 t + 1; sums over the waves before it from the waves' totals
-                const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-                const int c0 = dh[2 * threadIdx.x], c1 = dh[2 * threadIdx.x + 1];
-                int incl = c0 + c1;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int t = __shfl_up(incl, d);
-                    if (lane >= d) incl += t;
-                }
-                if (lane == 63) h256[wave] = incl;
-                __syncthreads();
-                int before = incl - c0 - c1;
-                for (int w = 0; w < wave; ++w) before += h256[w];
-                if (take > 0 && before < take && before + c0 + c1 >= take) {
-                    const bool second = before + c0 < take;
-                    sh[2] = 2 * threadIdx.x + (second ? 1 : 0);
-                    sh[3] = before + (second ? c0 : 0);
-                }
-                if (take <= 0 && threadIdx.x == 0) {
-                    sh[2] = -1;
-                    sh[3] = 0;
-                }
-                __syncthreads();
-            }
-            const int bd = sh[2], below = sh[3];
-#pragma unroll
-            for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
-                const int i = threadIdx.x + u * FIN_THREADS;
-                if (u * FIN_THREADS >= n) break;  // uniform
-                const int d = i < n ? (int)(key[u] >> shift) & (SEL_BINS - 1) : SEL_BINS;
-                if (d < bd) o[base + atomicAdd(&sh[0], 1)] = key[u];
-                if (d == bd) sk[atomicAdd(&sh[1], 1)] = key[u];
-            }
-            __syncthreads();
-            n = sh[1];
-            base += below;
-            take -= below;
-        } else {
-            if ((int)threadIdx.x < n) sk[threadIdx.x] = bl[threadIdx.x];
-            __syncthreads();
-        }
-        if (n <= FIN_RANK) {
-            // few keys: four threads count how many of them precede theirs
-            const int i = threadIdx.x >> 2;
-            if (i < n) {
-                const uint64_t key = sk[i];
-                int rank = 0;
-                for (int j = threadIdx.x & 3; j < n; j += 4) rank += sk[j] < key ? 1 : 0;
-                rank += __shfl_xor(rank, 1);
-                rank += __shfl_xor(rank, 2);
-                if ((threadIdx.x & 3) == 0 && rank < take) o[base + rank] = key;
-            }
-        } else {
-            const int n2 = next_pow2(n);
-            for (int i = n + threadIdx.x; i < n2; i += FIN_THREADS) sk[i] = PLAID_KEY_MAX;
-            __syncthreads();
-            lds_bitonic_sort(sk, n2);
-            for (int i = threadIdx.x; i < take; i += FIN_THREADS) o[base + i] = sk[i];
-        }
+        const unsigned long long diff = done == 1 ? (s->b_or1 & s->b_nor1) : (done == 0 ? (s->b_or & s->b_nor) : 0ull);
+        sel_pick_lds(bl, nb, m_rem, o + n_sure, diff ? 64 - __builtin_clzll(diff) : top_bit, sk, dh, h256, sh);
     } else {
         // still long (huge tie groups): radix selection over global memory by this one workgroup.  The keys of such a
         // list mostly share their digit (that is what made the list long), so a wave whose keys all have one digit
