@@ -1013,8 +1013,13 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
         int32_t *cand = (int32_t *)w.s2.blist;  // [n][P]
         plaid_launch_fill_u32(st, probebits, (int64_t)n * w.keep_words, 0u);
         plaid_launch_fill_u32(st, (uint32_t *)scp.state, (int64_t)(plaid_select_zero_bytes(n) / 4), 0u);
+        // masks of the queries per centroid, in the region of the keys that the pruning writes later (when they fit it)
+        const int64_t mask_words = C * ((n + 31) / 32);
+        uint32_t *qmask = mask_words <= (int64_t)n * P * 2 ? (uint32_t *)w.keys2 : nullptr;
+        if (qmask) plaid_launch_fill_u32(st, qmask, mask_words, 0u);
         plaid_launch_vanilla_candidates(st, w.uniq, w.n_uniq, w.uniq_stride, ix->emb_offsets, ix->emb_ids, ix->tok2pid, n,
-                                        w.keep_words, probebits, w.candbits, w.cand_words);
+                                        w.keep_words, probebits, w.candbits, w.cand_words, ix->doc_offsets, ix->codes, P, ix->N, C,
+                                        qmask, (uint32_t *)w.s2.qcount + 3);
         plaid_launch_bitmap_to_list(st, w.candbits, w.cand_words, P, n, cand, P, w.n2);
         // more than ncandidates: scored on the embeddings of the probed lists alone, the best ncandidates stay
         plaid_launch_vanilla_prune(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,

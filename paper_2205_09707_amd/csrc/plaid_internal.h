@@ -323,10 +323,12 @@ void plaid_launch_embedding_lists(hipStream_t st, const int32_t *codes, int64_t 
                                   int32_t *eids, int32_t *bad);
 void plaid_launch_tok2pid(hipStream_t st, const int64_t *doc_offsets, int64_t P, int64_t N, int32_t *tok2pid);
 // probebits (zero on entry) = bitmap of each query's probed centroids; candbits (zero on entry) |= the passages that own
-// an embedding of those centroids' embedding lists.
+// an embedding of those centroids' embedding lists.  qmask: scratch of C words per 32 queries, zero on entry (null: none);
+// work: one word, zero on entry.
 void plaid_launch_vanilla_candidates(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
                                      const int64_t *eoff, const int32_t *eids, const int32_t *tok2pid, int nq, int64_t keep_words,
-                                     uint32_t *probebits, uint32_t *candbits, int64_t cand_words);
+                                     uint32_t *probebits, uint32_t *candbits, int64_t cand_words, const int64_t *doc_offsets,
+                                     const int32_t *codes, int64_t P, int64_t N, int64_t C, uint32_t *qmask, uint32_t *work);
 // out_keys[q][j] = key of candidate cand[q][j] scored on the embeddings of the probed lists alone (score 0 for every
 // candidate of a query with at most ncandidates of them).
 void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
