@@ -519,40 +519,57 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
 }
 
 // ------------------------------------------------------------------ decompression alone (parity of the codec)
-__global__ __launch_bounds__(256) void passage_offsets_kernel(const int64_t *__restrict__ doc_offsets,
-                                                              const int32_t *__restrict__ pids, int n,
-                                                              int64_t *__restrict__ out_offsets)
+// One workgroup: four consecutive passages per thread and round, 4096 passages per round, so that a listing of thousands
+// takes one or two chains of loads (ids, then token ranges) and a scan over the waves in registers.  5000 passages: 39 us
+// with 256 passages per round and a scan through LDS, 19 us this way.
+#define OFFS_THREADS 1024
+#define OFFS_PER 4
+__global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int64_t *__restrict__ doc_offsets,
+                                                                       const int32_t *__restrict__ pids, int n,
+                                                                       int64_t *__restrict__ out_offsets)
 {
-    // one workgroup; serial carry across chunks of 256 passages
-    __shared__ int64_t scan[256];
-    __shared__ int64_t carry;
-    if (threadIdx.x == 0) {
-        carry = 0;
-        out_offsets[0] = 0;
-    }
-    __syncthreads();
-    for (int base = 0; base < n; base += 256) {
-        const int e = base + threadIdx.x;
-        int64_t len = 0;
-        if (e < n) len = doc_offsets[pids[e] + 1] - doc_offsets[pids[e]];
-        scan[threadIdx.x] = len;
-        __syncthreads();
-        for (int d = 1; d < 256; d <<= 1) {
-            const int64_t t = threadIdx.x >= d ? scan[threadIdx.x - d] : 0;
-            __syncthreads();
-            scan[threadIdx.x] += t;
-            __syncthreads();
+    __shared__ int64_t wave_sum[OFFS_THREADS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t carry = 0;  // the same in every thread
+    if (threadIdx.x == 0) out_offsets[0] = 0;
+    for (int64_t base = 0; base < n; base += OFFS_THREADS * OFFS_PER) {
+        const int64_t e0 = base + (int64_t)threadIdx.x * OFFS_PER;
+        int32_t pid[OFFS_PER];
+        int64_t len[OFFS_PER];
+#pragma unroll
+        for (int u = 0; u < OFFS_PER; ++u) pid[u] = e0 + u < n ? pids[e0 + u] : 0;
+#pragma unroll
+        for (int u = 0; u < OFFS_PER; ++u) len[u] = e0 + u < n ? doc_offsets[pid[u] + 1] - doc_offsets[pid[u]] : 0;
+        int64_t mine = 0;
+#pragma unroll
+        for (int u = 0; u < OFFS_PER; ++u) mine += len[u];
+        int64_t incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t t = __shfl_up(incl, d);
+            if (lane >= d) incl += t;
         }
-        if (e < n) out_offsets[e + 1] = carry + scan[threadIdx.x];
+        if (lane == 63) wave_sum[wave] = incl;
         __syncthreads();
-        if (threadIdx.x == 255) carry += scan[255];
-        __syncthreads();
+        int64_t run = carry + incl - mine;
+#pragma unroll
+        for (int w = 0; w < OFFS_THREADS / 64; ++w) {
+            const int64_t t = wave_sum[w];
+            if (w < wave) run += t;
+            carry += t;
+        }
+#pragma unroll
+        for (int u = 0; u < OFFS_PER; ++u) {
+            run += len[u];
+            if (e0 + u < n) out_offsets[e0 + u + 1] = run;
+        }
+        __syncthreads();  // the sums are written again in the next round
     }
 }
 void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, const int32_t *pids, int n,
                                   int64_t *out_offsets)
 {
-    hipLaunchKernelGGL(passage_offsets_kernel, dim3(1), dim3(256), 0, st, doc_offsets, pids, n, out_offsets);
+    hipLaunchKernelGGL(passage_offsets_kernel, dim3(1), dim3(OFFS_THREADS), 0, st, doc_offsets, pids, n, out_offsets);
 }
 
 // Same table, same lookup and same addition as the fused kernel; thread t handles dimensions 4t .. 4t+3.
@@ -579,21 +596,34 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
     const int len = (int)(doc_offsets[pid + 1] - t0);
     const int64_t o0 = out_offsets[a];
     const int quad = threadIdx.x & 31;
-    for (int row = threadIdx.x >> 5; row < len; row += 8) {
-        const int64_t tok = t0 + row;
-        const float *crow = centroids + (int64_t)codes[tok] * DIM;
-        const int slot = table_slot<NBITS>(residuals + tok * RB, quad);
-        const float4 c = *reinterpret_cast<const float4 *>(crow + 4 * quad);
-        const float4 w = wlut[slot];
-        if (out_vectors) {
-            float4 d = make_float4(c.x + w.x, c.y + w.y, c.z + w.z, c.w + w.w);
-            if (inv_norm) {  // scaled to unit length: one fp32 factor per token, one rounding per component
-                const float f = inv_norm[tok];
-                d = make_float4(d.x * f, d.y * f, d.z * f, d.w * f);
-            }
-            *reinterpret_cast<float4 *>(out_vectors + (o0 + row) * DIM + 4 * quad) = d;
+    // four rows per thread in flight: code and residual, then the centroid's piece, then the stores
+    for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 32) {
+        int slot[4];
+        int32_t code[4];
+        float4 c[4];
+        float f[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int row = row0 + 8 * u < len ? row0 + 8 * u : row0;  // (a row past the end repeats the first)
+            code[u] = codes[t0 + row];
+            slot[u] = table_slot<NBITS>(residuals + (t0 + row) * RB, quad);
+            f[u] = inv_norm ? inv_norm[t0 + row] : 1.0f;
         }
-        if (out_indices) *reinterpret_cast<uint32_t *>(out_indices + (o0 + row) * DIM + 4 * quad) = ilut[slot];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = *reinterpret_cast<const float4 *>(centroids + (int64_t)code[u] * DIM + 4 * quad);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int row = row0 + 8 * u;
+            if (row >= len) break;
+            const float4 w = wlut[slot[u]];
+            if (out_vectors) {
+                float4 d = make_float4(c[u].x + w.x, c[u].y + w.y, c[u].z + w.z, c[u].w + w.w);
+                // scaled to unit length: one fp32 factor per token, one rounding per component
+                if (inv_norm) d = make_float4(d.x * f[u], d.y * f[u], d.z * f[u], d.w * f[u]);
+                *reinterpret_cast<float4 *>(out_vectors + (o0 + row) * DIM + 4 * quad) = d;
+            }
+            if (out_indices) *reinterpret_cast<uint32_t *>(out_indices + (o0 + row) * DIM + 4 * quad) = ilut[slot[u]];
+        }
     }
 }
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
