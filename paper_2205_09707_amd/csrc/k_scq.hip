@@ -104,31 +104,6 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     bool need_hash;         // stage 2 will use the streaming form
 };
 
-// One entry of S_cq as the definition reads: the products of the 128 dimensions accumulated in double in index order
-// (a product of two fp32 values is exact in double, so the fused multiply-add chain is "multiply, then add"), rounded
-// once to fp32.  Used where a decision must not rest on the split-fp16 kernel's approximate scores.
-// crow: the centroid's row in global memory, fetched 32 dimensions at a time (eight 16-byte loads in flight); qrow: the
-// query token's row, which the caller keeps in LDS.
-__device__ __forceinline__ float scq_exact_entry(const float *__restrict__ crow, const float *qrow)
-{
-    double acc = 0.0;
-#pragma unroll 1
-    for (int d0 = 0; d0 < DIM; d0 += 32) {
-        float4 c[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) c[u] = *reinterpret_cast<const float4 *>(crow + d0 + 4 * u);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float4 x = *reinterpret_cast<const float4 *>(qrow + d0 + 4 * u);
-            acc = fma((double)c[u].x, (double)x.x, acc);
-            acc = fma((double)c[u].y, (double)x.y, acc);
-            acc = fma((double)c[u].z, (double)x.z, acc);
-            acc = fma((double)c[u].w, (double)x.w, acc);
-        }
-    }
-    return (float)acc;
-}
-
 // Floats per query row in the probe kernel's LDS.  The survivor table is evaluated with a lane per query token: with rows
 // of 128 floats the 32 tokens' reads fall into one bank group, and the table took 12 of the kernel's 31 us for one query.
 #define TAIL_QSTRIDE (DIM + 4)
@@ -226,7 +201,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     const int hash_shift = (need_hash && K <= S2_MAX_KEPT) ? S2_SHIFT0 + (S2_NHASH - 1 - misc[1]) : 0;
     if (K <= S2_MAX_KEPT) {
         for (int e = tid; e < K * QLEN; e += nthreads) {
-            const float v = APPROX ? scq_exact_entry(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * TAIL_QSTRIDE)
+            const float v = APPROX ? plaid_exact_dot(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * TAIL_QSTRIDE)
                                    : Sq[(int64_t)ids[e >> 5] * QLEN + (e & 31)];
             Tq[QLEN + e] = v;
             Tx[(e >> 5) * TX_STRIDE + (e & 31)] = v;
@@ -897,11 +872,11 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
             if (n_x <= TAIL_XCAP) {
                 if (l < n_x) {
                     const int32_t c = xc_id[i][l];
-                    best[0] = plaid_make_key(scq_exact_entry(x.Cm + (int64_t)c * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)c);
+                    best[0] = plaid_make_key(plaid_exact_dot(x.Cm + (int64_t)c * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)c);
                 }
             } else {
                 walk([&](float sv, int64_t cc) {
-                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(scq_exact_entry(x.Cm + cc * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)cc));
+                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(plaid_exact_dot(x.Cm + cc * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)cc));
                 });
             }
         }
@@ -996,7 +971,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
             for (int p = tid; p < n_amb * QLEN; p += TAIL_THREADS) {
                 const int64_t c = amb_rows[p >> 5];
                 const int tok = p & 31;
-                if ((!S || Sq[c * QLEN + tok] >= x.t_lo) && scq_exact_entry(x.Cm + c * DIM, Qq + tok * TAIL_QSTRIDE) >= x.t_cs)
+                if ((!S || Sq[c * QLEN + tok] >= x.t_lo) && plaid_exact_dot(x.Cm + c * DIM, Qq + tok * TAIL_QSTRIDE) >= x.t_cs)
                     atomicOr(&kbq[c >> 5], 1u << (c & 31));
             }
         }

@@ -67,7 +67,6 @@ struct plaid_index {
     void *A16 = nullptr;          // split-fp16 operand form of the centroids (owned), when scq_form is PLAID_SCQ_SPLIT16
     float *inv_norm = nullptr;    // [N] 1 / |reconstructed vector| (owned; built by plaid_index_set_renormalize)
     bool renormalize = false;     // stage 4 and plaid_decompress_passages scale reconstructed vectors to unit length
-    bool no_scores = false;       // nearest-centroid assignment with the split-fp16 kernel: S_cq itself is not stored
     uint32_t *ivr_table = nullptr;  // range table of the inverted lists (owned); null: union + code stream are used
     int32_t ivr_shift = 11;         // log2 of the passages per table column (11 or 13)
     int32_t *dense_id = nullptr;    // with the range table: bitmap row of each centroid's list, -1 for all but the longest
@@ -154,6 +153,7 @@ struct TempAlloc {  // device memory released when the call returns
 // The split kernel scales the centroids' leading fp16 terms by 2^11: a table with a component of 32 or more (or one that
 // is not a number) cannot use it.  Such an index (ix->scq_form is PLAID_SCQ_SPLIT16 on entry) gets a double-precision
 // form instead, unless the caller insisted on the split form, which is then an error.  Synchronises the stream.
+static int scq16_accept(plaid_index *ix, float largest);  // by the largest |component|
 static int scq16_check_centroids(plaid_index *ix, const float *centroids, int64_t C, hipStream_t st)
 {
     TempAlloc mb;
@@ -167,6 +167,10 @@ static int scq16_check_centroids(plaid_index *ix, const float *centroids, int64_
     float largest = 0.f;
     HIP_TRY(hipMemcpyAsync(&largest, mb.p, 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    return scq16_accept(ix, largest);
+}
+static int scq16_accept(plaid_index *ix, float largest)
+{
     if (largest <= PLAID_SCQ16_CENTROID_MAX) return PLAID_OK;
     const char *env = getenv("PLAID_SCQ_FORM");
     if (env && !strcmp(env, "split16"))
@@ -689,7 +693,7 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.sel4_zero = take(plaid_select_zero_bytes(qc));
     w.zero_bytes = off;
     w.Qd = (double *)take((size_t)qc * QLEN * DIM * 8);
-    w.S = ix->no_scores ? nullptr : (float *)take((size_t)qc * C * QLEN * 4);
+    w.S = (float *)take((size_t)qc * C * QLEN * 4);
     w.keepbits = (uint32_t *)take((size_t)qc * w.keep_words * 4);
     w.ambbits = (uint32_t *)take((size_t)qc * w.keep_words * 4);
     w.probed = (int32_t *)take((size_t)qc * QLEN * pl.nprobe * 4);
@@ -1083,7 +1087,6 @@ extern "C" int plaid_assign_centroids(const float *centroids, int64_t C, const f
     DeviceGuard g(device);
     if (!g.ok) return fail(PLAID_EHIP, "hipSetDevice(%d) failed", device);
     hipStream_t st = (hipStream_t)hip_stream;
-    // the score kernel of the search path, 32 vectors in the place of a query's 32 tokens, and its top-1 probes
     plaid_index fake;
     fake.device = device;
     fake.C = C;
@@ -1091,21 +1094,39 @@ extern "C" int plaid_assign_centroids(const float *centroids, int64_t C, const f
     int rc = choose_scq_form(&fake);
     if (rc) return rc;
     if (fake.scq_form == PLAID_SCQ_SPLIT16) {
-        rc = scq16_check_centroids(&fake, centroids, C, st);
-        if (rc) return rc;
-    }
-    TempAlloc a16;
-    if (fake.scq_form == PLAID_SCQ_SPLIT16) {
-        const size_t ab = plaid_scq16_centroid_bytes(C);
-        if (hipMalloc(&a16.p, ab) != hipSuccess) {
+        const size_t ab = plaid_assign_operand_bytes(C);
+        const int64_t groups = (n + 31) / 32;
+        // vectors per launch: about 256 MiB of scratch
+        const size_t per_group = plaid_assign_operand_bytes(32) / 16 + plaid_assign_best_bytes(C, 1);
+        int64_t gc = (int64_t)(((size_t)256 << 20) / per_group);
+        gc = gc < 16 ? 16 : gc / 16 * 16;
+        if (gc > groups) gc = groups;
+        const size_t bb = a256(plaid_assign_operand_bytes(gc * 32)), sb = plaid_assign_best_bytes(C, gc);
+        TempAlloc mem;
+        if (hipMalloc(&mem.p, 256 + a256(ab) + bb + sb) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(PLAID_ENOMEM, "hipMalloc(%zu) for the centroids' matrix operands failed", ab);
+            return fail(PLAID_ENOMEM, "hipMalloc(%zu) for the assignment workspace failed", 256 + a256(ab) + bb + sb);
         }
-        plaid_launch_scq16_split_centroids(st, centroids, C, a16.p);
-        // The probe kernel ranks by scores it re-evaluates in double and needs the tile maxima only to find the rows worth
-        // re-evaluating: the scores themselves (4 C bytes per vector, the kernel's whole memory traffic) are not stored.
-        fake.no_scores = true;
+        uint32_t *stats = (uint32_t *)mem.p;
+        char *A = (char *)mem.p + 256, *B = A + a256(ab), *best2 = B + bb;
+        HIP_TRY(hipMemsetAsync(stats, 0, 256, st));
+        plaid_launch_assign_prepare(st, centroids, C, A, stats);
+        HIP_TRY(hipGetLastError());
+        float largest = 0.f;
+        HIP_TRY(hipMemcpyAsync(&largest, stats, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        rc = scq16_accept(&fake, largest);
+        if (rc) return rc;
+        if (fake.scq_form == PLAID_SCQ_SPLIT16) {
+            for (int64_t v0 = 0; v0 < n; v0 += gc * 32)
+                plaid_launch_assign(st, centroids, C, A, stats, x + v0 * DIM, n - v0 < gc * 32 ? n - v0 : gc * 32, B, best2, codes + v0);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(hipStreamSynchronize(st));  // the workspace is released on return
+            return PLAID_OK;
+        }
     }
+    // the double-precision forms: the score kernel of the search path, 32 vectors in the place of a query's 32 tokens, and
+    // its top-1 probes
     Plan pl;
     pl.nprobe = 1;
     pl.nd = pl.m3 = pl.kk = 1;
@@ -1135,7 +1156,7 @@ extern "C" int plaid_assign_centroids(const float *centroids, int64_t C, const f
     auto run = [&](const float *src, int64_t ng, int32_t *dst, int64_t cnt) -> int {
         const Workspace w = carve((char *)ws.p, &fake, (int)ng, pl);
         for (int phase = PLAID_STAGE1_PREP; phase <= PLAID_STAGE1_PROBES; phase <<= 1)
-            plaid_launch_stage1(st, phase, centroids, C, src, w.Qd, fake.scq_form, a16.p, (int)ng, INFINITY, 1, w.S, w.keepbits,
+            plaid_launch_stage1(st, phase, centroids, C, src, w.Qd, fake.scq_form, nullptr, (int)ng, INFINITY, 1, w.S, w.keepbits,
                                 w.ambbits, w.keep_words, w.tilemax, (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed,
                                 w.uniq, w.uniq_stride, w.n_uniq, w.s2, w.probe_scratch, w.probe_scratch_bytes);
         HIP_TRY(hipGetLastError());

@@ -47,6 +47,31 @@ __device__ __forceinline__ float plaid_sum32_in_order(float m)
     return (float)d;
 }
 
+// One entry of S_cq as the definition reads: the products of the 128 dimensions accumulated in double in index order
+// (a product of two fp32 values is exact in double, so the fused multiply-add chain is "multiply, then add"), rounded
+// once to fp32.  Used where a decision must not rest on the split-fp16 kernel's approximate scores.
+// crow: the centroid's row in global memory, fetched 32 dimensions at a time (eight 16-byte loads in flight); qrow: the
+// query token's row, which the caller keeps in LDS.
+__device__ __forceinline__ float plaid_exact_dot(const float *__restrict__ crow, const float *qrow)
+{
+    double acc = 0.0;
+#pragma unroll 1
+    for (int d0 = 0; d0 < DIM; d0 += 32) {
+        float4 c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = *reinterpret_cast<const float4 *>(crow + d0 + 4 * u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float4 x = *reinterpret_cast<const float4 *>(qrow + d0 + 4 * u);
+            acc = fma((double)c[u].x, (double)x.x, acc);
+            acc = fma((double)c[u].y, (double)x.y, acc);
+            acc = fma((double)c[u].z, (double)x.z, acc);
+            acc = fma((double)c[u].w, (double)x.w, acc);
+        }
+    }
+    return (float)acc;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Selection (k_select.hip): first m keys in ascending order out of per-segment lists.
 // ---------------------------------------------------------------------------------------------
@@ -266,6 +291,14 @@ void plaid_launch_ivf_dense_fill(hipStream_t st, const int64_t *ivf_offsets, con
 // ---------------------------------------------------------------------------------------------
 // Index construction (k_build.hip)
 // ---------------------------------------------------------------------------------------------
+// Nearest centroids by screening (k_assign.hip).  A: plaid_assign_operand_bytes(C); stats: three words, zero on entry, [0]
+// returns the bit pattern of the largest centroid component; B: plaid_assign_operand_bytes(n) scratch; best2:
+// plaid_assign_best_bytes(C, ceil(n / 32)) scratch.  codes[j] = argmax_c C[c] . x[j], ties to the smaller id.
+size_t plaid_assign_operand_bytes(int64_t rows);
+size_t plaid_assign_best_bytes(int64_t C, int64_t groups);
+void plaid_launch_assign_prepare(hipStream_t st, const float *centroids, int64_t C, void *A, uint32_t *stats);
+void plaid_launch_assign(hipStream_t st, const float *centroids, int64_t C, const void *A, const uint32_t *stats, const float *x,
+                         int64_t n, void *B, void *best2, int32_t *codes);
 // residuals[j] = packed bucket indices of x[j] - centroids[codes[j]]; bad[0] is set when a code is out of range.
 void plaid_launch_encode_residuals(hipStream_t st, const float *centroids, int64_t C, const float *x, const int32_t *codes,
                                    int64_t n, const float *cutoffs, int nbits, uint8_t *residuals, int32_t *bad);
