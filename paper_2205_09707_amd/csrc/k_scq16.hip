@@ -165,7 +165,7 @@ __device__ __forceinline__ void scq16_reduce(const scq16_floatx16 (&acc)[NT], fl
 // unconditional.  The two cases are separate instances, and the first query is taken out of the loop, so that the number
 // of stores between a request for operands and the wait for them is the same on every path: the memory counter retires
 // in order, and a wait sized for the path with the fewest stores would sit out the score stores of the others.
-template <int NT, bool STORE, bool WHOLE>
+template <int NT, bool WHOLE>
 __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16,
                                            int64_t C, const scq16_half8 *__restrict__ B16, int q_begin, int q_end, float t_lo,
                                            float t_hi, float *__restrict__ S, uint32_t *__restrict__ keepbits,
@@ -249,25 +249,20 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], c
     };
     struct no_t { enum { value = 0 }; };
     struct yes_t { enum { value = 1 }; };
-    float *s0 = STORE ? S + ((int64_t)q_begin * C + (tile0 << 5) + 4 * h) * QLEN + n : nullptr;  // of the query whose stores are due
+    float *s0 = S + ((int64_t)q_begin * C + (tile0 << 5) + 4 * h) * QLEN + n;  // of the query whose stores are due
     products(q_begin, s0, no_t());
     finish(q_begin);
     for (int q = q_begin + 1; q < q_end; ++q) {
-        if (STORE) {
-            products(q, s0, yes_t());
-            s0 += C * QLEN;
-        } else {
-            products(q, s0, no_t());
-        }
+        products(q, s0, yes_t());
+        s0 += C * QLEN;
         finish(q);
     }
-    if (STORE) {  // the last query's scores
-        int lim[NT];
+    // the last query's scores
+    int lim[NT];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) lim[t] = nvalid[t] - 4 * h;
+    for (int t = 0; t < NT; ++t) lim[t] = nvalid[t] - 4 * h;
 #pragma unroll
-        for (int s = 0; s < H16_STEPS; ++s) scq16_store_part<NT, WHOLE>(s0, val, s, lim);
-    }
+    for (int s = 0; s < H16_STEPS; ++s) scq16_store_part<NT, WHOLE>(s0, val, s, lim);
 }
 
 // Grid: x = block of 32 * H16_WAVES * NT centroids, y = group of qg queries.  A16: a whole number of workgroups' tiles
@@ -278,8 +273,7 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], c
 // arrived), and those of q + 2 are requested.  Scores: the results of query q leave the accumulators (scaled, reduced
 // for the tile maxima and the pruning words) into registers of their own, and their stores are issued between the
 // matrix instructions of query q + 1, a few per step, so that the store stream and the matrix pipe run side by side.
-// STORE = false: the scores themselves are not written, only the tile maxima and the pruning words (nearest-centroid
-// assignment, which re-evaluates the rows of the best tile).
+// STORE: always true (the scores are written; the name of the instance is what the resource checks look for).
 template <int NT, bool STORE>
 __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     const scq16_half8 *__restrict__ A16, int64_t C, const scq16_half8 *__restrict__ B16, int nq, int qg, float t_lo, float t_hi,
@@ -303,9 +297,9 @@ __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     }
     // (the barriers inside are reached by all four waves in either instance: both run the same loop over the queries)
     if (whole)
-        scq16_body<NT, STORE, true>(Bs, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax);
+        scq16_body<NT, true>(Bs, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax);
     else
-        scq16_body<NT, STORE, false>(Bs, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax);
+        scq16_body<NT, false>(Bs, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax);
     if (clocks && threadIdx.x == 0) {
         atomicAdd(&clocks[0], (unsigned long long)(clock64() - sc0));
         atomicAdd(&clocks[1], (unsigned long long)(wall_clock64() - rt0));
@@ -378,10 +372,6 @@ void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *
     if (qg > 64) qg = 64;
     if (qg > nq) qg = nq;
     const unsigned gy = (unsigned)((nq + qg - 1) / qg);
-    if (S)
-        hipLaunchKernelGGL((scq16_kernel<H16_NT, true>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
-                           (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, clocks);
-    else
-        hipLaunchKernelGGL((scq16_kernel<H16_NT, false>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
-                           (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, clocks);
+    hipLaunchKernelGGL((scq16_kernel<H16_NT, true>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
+                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, clocks);
 }

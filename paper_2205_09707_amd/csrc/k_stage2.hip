@@ -686,13 +686,15 @@ __global__ __launch_bounds__(UW_THREADS) void s2_union_wide_kernel(
 //            scores have reached or passed; a passage whose bound falls into a worse bin cannot be among the best m and
 //            is not scored.  Which passages are skipped depends on timing, the best m do not.
 //   score    the remaining passages, 64 at a time with lane = passage: the bag's slots are collected from the planes
-//            and scored exactly (s2_score_members_wide), the key appended to the query's list, the bin counted.
+//            and scored exactly (s2_score_rows), the key appended to the query's list, the bin counted.
 // While the histogram does not prune yet (the first waves of a query), a wave scores the passages with the highest
 // bounds of its range, some dozens, and looks again: a thousand such waves know the final threshold almost exactly.
 //
-// Why: of cfg3's 400 000 candidates per query about one in a hundred is scored.  Scoring all of them (a set word per
-// passage built with LDS atomics, one lane per passage, sorted by bag size) took 3.5 ms per 512 queries, 25 ms per 150
-// queries of 8.8 M passages at C = 262144.
+// Why: of 400 000 candidates per query (65536 centroids, ndocs 1024) about one in thirty is scored.  Scoring all of them (a
+// set word per passage built with LDS atomics, one lane per passage, sorted by bag size) took 3.5 ms per 512 queries, this
+// 0.9; 150 queries of 8.8 M passages at 262144 centroids 25 ms, now 8.5.  What bounds it now: a wave's step of 2048
+// passages takes 16 to 20 us with 12 to 16 waves per compute unit, a third of it the additions of the bounds, the rest the
+// chains of dependent loads and LDS accesses of the other parts.
 #define IV_WAVES 4
 #define IV_LISTS 256    // probed-only lists a workgroup classifies; beyond (nprobe > 8) they are walked unclassified
 
@@ -721,14 +723,15 @@ __device__ __forceinline__ int s2_wave_scan(int v)
     return v;
 }
 
-// SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
-// the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
+// Counts of coarse bins 2 lane and 2 lane + 1, read where the other compute units' additions arrive.
 __device__ __forceinline__ int2 s2_coarse_load(const int32_t *coarse_q, int lane)
 {
     const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(coarse_q) + lane, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT);
     return make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
 }
+// SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
+// the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
 template <int SHIFT, typename SetT>
 __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4 : 3) void s2_invert_kernel(
     const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride,
