@@ -86,6 +86,28 @@ __device__ __forceinline__ void build_half_tables(s4_half8 *hlut, const float *_
     }
 }
 
+// The two fp16 terms of the query in the operand order of v_mfma_f32_32x32x16_f16, into LDS: lane 32 h + r of step s holds
+// query token r, dimensions 16 s + 8 h .. + 7.  All 256 threads of the workgroup call this, a barrier follows.
+__device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_half8 (&qs)[2][8][64])
+{
+    for (int e = threadIdx.x; e < 8 * 64; e += 256) {
+        const int s = e >> 6, l = e & 63;
+        const float4 *p = reinterpret_cast<const float4 *>(Qq + (l & 31) * DIM + 16 * s + 8 * (l >> 5));
+        const float4 u = p[0], w = p[1];
+        const float x[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
+        s4_half8 t1, t2;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            _Float16 x1, x2;
+            s4_split(x[j], x1, x2);
+            t1[j] = x1;
+            t2[j] = x2;
+        }
+        qs[0][s][l] = t1;
+        qs[1][s][l] = t2;
+    }
+}
+
 // Column maxima of a 32 x 32 result block spread over the wave as the matrix instruction leaves it: lane 32 h + n holds
 // mx[v] = the value of query token 8 (v / 4) + 4 h + v % 4 for passage-token column n.  Returns, in lane 32 h + 2 v (and
 // its odd neighbour), the maximum over the 32 columns for that query token: a butterfly in which each exchange halves the
@@ -168,22 +190,7 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
     // A operands: the two fp16 terms of query token r32, dimensions 16 s + 8 h .. + 7.  They are the same for the four
     // waves and stay in LDS (16 KB), from where each matrix step reads them: 64 registers less per lane, which buys a
     // third wave per SIMD to cover the latency of the gathers.
-    for (int e = threadIdx.x; e < 8 * 64; e += 256) {
-        const int s = e >> 6, l = e & 63;
-        const float4 *p = reinterpret_cast<const float4 *>(Qq + (l & 31) * DIM + 16 * s + 8 * (l >> 5));
-        const float4 u = p[0], w = p[1];
-        const float x[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-        s4_half8 t1, t2;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            _Float16 x1, x2;
-            s4_split(x[j], x1, x2);
-            t1[j] = x1;
-            t2[j] = x2;
-        }
-        qs[0][s][l] = t1;
-        qs[1][s][l] = t2;
-    }
+    s4_stage_query(Qq, qs);
     __syncthreads();
 
     // In front of a passage's first step stands a chain of dependent loads: its id (from the key list), its token range,
@@ -346,8 +353,10 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
 // the matrix instructions run on full 32-token steps whatever share of a passage E covers.  Queries whose candidate
 // count does not exceed ncandidates keep every candidate and are not scored: their keys get score 0.
 //   cand: [q][cand_stride] ascending candidate pids, n_cand[q] of them;  out_keys[q][j] = key of cand[q][j].
+// The query operands stay in LDS, as above: with them in registers a SIMD held three waves, and the kernel, bound by its
+// chains of gathers and table look-ups, took 10.4 ms for 16 queries of 400 000 candidates; with four 8.2 ms.
 template <int NBITS>
-__global__ __launch_bounds__(256, 3) void vanilla_prune_kernel(
+__global__ __launch_bounds__(256, 4) void vanilla_prune_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
     const uint32_t *__restrict__ probebits, int64_t keep_words, const int32_t *__restrict__ cand, int64_t cand_stride,
@@ -356,6 +365,7 @@ __global__ __launch_bounds__(256, 3) void vanilla_prune_kernel(
     constexpr int RB = 16 * NBITS;
     __shared__ s4_half8 hlut[256 * (NBITS == 2 ? 1 : 2)];
     __shared__ int32_t ring_all[4][128];
+    __shared__ s4_half8 qs[2][8][64];  // [term][step of 16 dimensions][lane]
     const int q = blockIdx.y;
     const int count = n_cand[q];
     const int lane = threadIdx.x & 63;
@@ -371,20 +381,7 @@ __global__ __launch_bounds__(256, 3) void vanilla_prune_kernel(
     const float *Qq = Q + (int64_t)q * QLEN * DIM;
     const float *Sq = S + (int64_t)q * C * QLEN;
     const uint32_t *pb = probebits + (int64_t)q * keep_words;
-    s4_half8 q1[8], q2[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const float4 *p = reinterpret_cast<const float4 *>(Qq + r32 * DIM + 16 * s + 8 * h);
-        const float4 u = p[0], w = p[1];
-        const float x[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            _Float16 x1, x2;
-            s4_split(x[j], x1, x2);
-            q1[s][j] = x1;
-            q2[s][j] = x2;
-        }
-    }
+    s4_stage_query(Qq, qs);
     __syncthreads();
     int32_t *ring = ring_all[wave];
     for (int j = (int)blockIdx.x * 4 + wave; j < count; j += (int)gridDim.x * 4) {
@@ -432,6 +429,8 @@ __global__ __launch_bounds__(256, 3) void vanilla_prune_kernel(
                 }
                 floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
                 floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                int ql = lane;  // (read anew in every step, as in the kernel above)
+                asm volatile("" : "+v"(ql));
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
                     s4_half8 a1, a2;
@@ -445,9 +444,10 @@ __global__ __launch_bounds__(256, 3) void vanilla_prune_kernel(
                         a1 = hlut[b];
                         a2 = hlut[256 + b];
                     }
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q1[s], acc, 0, 0, 0);
-                    acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q2[s], acx, 0, 0, 0);
-                    acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, q1[s], acx, 0, 0, 0);
+                    const s4_half8 q1 = qs[0][s][ql], q2 = qs[1][s][ql];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q1, acc, 0, 0, 0);
+                    acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q2, acx, 0, 0, 0);
+                    acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, q1, acx, 0, 0, 0);
                 }
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
