@@ -1209,12 +1209,16 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_union_wide_kernel, dim3((unsigned)nwide, nq), dim3(UW_THREADS), 0, st, uniq, n_uniq, uniq_stride,
                            ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            b.emptybits);
-    // Passages per wave and step: 2048, or 128 for launches of so few passages that a wave's own chain of steps is all that
-    // counts (one query of 10 000 passages: 101 us per search with 128, 102 with 256, 110 with 512).  Steps per wave: the
-    // set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has dozens of waves to run
-    // (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M: 13.3 / 12.6 / 12.4 ms).
-    const int64_t waves = (int64_t)nq * ((P + 2047) >> 11);
-    const int len_log = waves >= 64 ? 11 : 7;
+    // Passages per wave and step: 2048, fewer for indexes of so few passages that a wave's own chain of steps is all that
+    // counts and the chip has room for more waves.  One query of 10 000 passages: 109 / 99 / 90 us per search with 2048 / 512 /
+    // 128, of 60 000: 120 / 114 / 113, of 200 000: 103 / 103 / 122; five of 29 500: 135 / 134 / 120; 64 of 20 000: 185 / 172 /
+    // 196.  Steps per wave: the set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has
+    // dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M:
+    // 13.3 / 12.6 / 12.4 ms).
+    const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
+    int len_log = 11;
+    if (ranges <= 40)
+        while (len_log > 7 && (ranges << (12 - len_log)) <= 128 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 ? 2 : 1);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
     // Passages a wave scores before there is a threshold: all waves of a query together about eight times the m that make
