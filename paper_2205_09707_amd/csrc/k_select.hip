@@ -1160,7 +1160,10 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
                           int32_t *out_counts, int lists)
 {
     const int gx = blocks_for(P, nq);
-    hipLaunchKernelGGL(sel2_filter_kernel, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P,
+    // (lists hold some ten thousand keys: with many queries 16 workgroups each, which stride, are enough; 64 each took
+    // 86 us for 512 queries, nearly all of them to find that there was nothing for them to do)
+    const int gx_filter = lists && nq >= 16 && gx > 16 ? 16 : gx;
+    hipLaunchKernelGGL(sel2_filter_kernel, dim3(gx_filter, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P,
                        m, b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists);
     // Digit filters: only a boundary list longer than SEL2_DIGIT_MIN makes them do anything.  The second pair is worth its
     // two launches for large indexes (a tie group can be as long as the index) in launches of several queries; otherwise
