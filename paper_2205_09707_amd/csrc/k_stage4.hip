@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
 // The query operands stay in LDS, as above: with them in registers a SIMD held three waves, and the kernel, bound by its
 // chains of gathers and table look-ups, took 10.4 ms for 16 queries of 400 000 candidates; with four 8.2 ms.
 template <int NBITS>
-__global__ __launch_bounds__(256, 4) void vanilla_prune_kernel(
+__global__ __launch_bounds__(256, NBITS == 2 ? 4 : 3) void vanilla_prune_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
     const uint32_t *__restrict__ probebits, int64_t keep_words, const int32_t *__restrict__ cand, int64_t cand_stride,
