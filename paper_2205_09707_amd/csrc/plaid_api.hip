@@ -201,10 +201,10 @@ static int build_scq16_operands(plaid_index *ix)
 }
 
 // The inverted form of candidate generation + stage 2 needs a table of C x (P / 2^shift + 1) positions, shift = 11 or
-// 13 (2048 or 8192 passages per workgroup).  The finer one is faster at every index size measured (three or four
-// workgroups share a compute unit instead of one or two); it is built when its table is at most four times the size of
-// the inverted lists (or tiny in absolute terms), the coarser one under the same rule or when the finer table cannot
-// be allocated.  PLAID_STAGE2_FORM=stream|inverted|inverted11|inverted13 (read at index creation) overrides that.
+// 13 (a column per 2048 or 8192 passages).  A wave of the kernel takes 2048 passages: with the coarser table it reads the
+// list entries of four times as many.  The finer one is built when it is at most four times the size of the inverted lists
+// (or tiny in absolute terms), the coarser one under the same rule or when the finer table cannot be allocated.
+// PLAID_STAGE2_FORM=stream|inverted|inverted11|inverted13 (read at index creation) overrides that.
 static int build_range_table(plaid_index *ix)
 {
     const char *env = getenv("PLAID_STAGE2_FORM");

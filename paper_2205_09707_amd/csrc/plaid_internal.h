@@ -270,7 +270,7 @@ void plaid_launch_stage2(hipStream_t st, const float *S, int64_t C, const uint32
 // place of the fine one) hold every candidate that can be among the best m (= the m of the selection that follows), not
 // those proven not to be.  table: plaid_ivf_range_table_bytes(C, P, shift) bytes filled once per index
 // by plaid_launch_ivf_range_table.
-// shift: log2 of the passages per table column = per workgroup of the inverted kernel, 11 or 13.
+// shift: log2 of the passages per table column, 11 or 13.
 size_t plaid_ivf_range_table_bytes(int64_t C, int64_t P, int shift);
 void plaid_launch_ivf_range_table(hipStream_t st, const int64_t *ivf_offsets, const int32_t *ivf_pids, int64_t C, int64_t P,
                                   int shift, uint32_t *table);
