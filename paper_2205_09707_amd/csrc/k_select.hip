@@ -1169,7 +1169,9 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
     // two launches for large indexes (a tie group can be as long as the index) in launches of several queries; otherwise
     // the query's finishing workgroup handles a long remainder alone (same result).  keys2 serves as the first
     // filter's output list, b.blist (its input) as the second one's.
-    const int levels = P > SEL2_DIGIT_MIN ? ((nq >= 8 && P > SEL2_SECOND_MIN_PASSAGES) ? 2 : 1) : 0;
+    // (the coarse bins of a key list can hold two scores that millions of passages share: then the first digit leaves a whole
+    // tie group also in a launch of one query, 2.8 ms for the finishing workgroup alone on 8.8 M passages)
+    const int levels = P > SEL2_DIGIT_MIN ? (((nq >= 8 || lists) && P > SEL2_SECOND_MIN_PASSAGES) ? 2 : 1) : 0;
     if (levels >= 1) {
         hipLaunchKernelGGL(sel2_digit_hist_kernel<1>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, b.blist, P, b.state, b.hist1);
         hipLaunchKernelGGL(sel2_digit_filter_kernel<1>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, b.blist, P, b.state, b.hist1,
