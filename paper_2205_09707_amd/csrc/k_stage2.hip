@@ -1038,22 +1038,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                 lcand[lane] = cand;
                 s2_wave_sync();
                 const int64_t w_end = w0 + nw < cand_words ? w0 + nw : cand_words;
-                // (bins counted in the wave's area, which such a query has no planes for, where it has room for them)
-                if constexpr (FULL_PLANES * 64 >= SEL_BINS) {
-                    int32_t *bins = reinterpret_cast<int32_t *>(area);
-                    for (int e = lane; e < SEL_BINS; e += 64) bins[e] = 0;
-                    s2_wave_sync();
-                    s2_gather_body(q, S, C, keepbits, keep_words, lcand, w0, w0, 1, w_end, cand_words, P, doc_offsets, codes,
-                                   mt.bin_hi, mt.bin_scale, reinterpret_cast<uint32_t *>(klist), bins, emptybits);
-                    s2_wave_sync();
-                    for (int e = lane; e < SEL_BINS; e += 64) {
-                        const int32_t n = bins[e];
-                        if (n) atomicAdd(&hist_q[e], n);
-                    }
-                } else {
-                    s2_gather_body(q, S, C, keepbits, keep_words, lcand, w0, w0, 1, w_end, cand_words, P, doc_offsets, codes,
-                                   mt.bin_hi, mt.bin_scale, reinterpret_cast<uint32_t *>(klist), hist_q, emptybits);
-                }
+                s2_gather_body(q, S, C, keepbits, keep_words, lcand, w0, w0, 1, w_end, cand_words, P, doc_offsets, codes,
+                               mt.bin_hi, mt.bin_scale, reinterpret_cast<uint32_t *>(klist), hist_q, emptybits);
                 s2_wave_sync();
                 continue;
             }
