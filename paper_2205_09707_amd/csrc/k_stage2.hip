@@ -1198,7 +1198,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift, int32_t m)
+                                  const uint32_t *dense_bits, int shift, int32_t m, bool unpruned)
 {
     const int64_t nr = (P + (1ll << shift) - 1) >> shift;
     const int64_t nwide = (P + (1ll << UW_SHIFT) - 1) >> UW_SHIFT;
@@ -1215,9 +1215,14 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // 196.  Steps per wave: the set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has
     // dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M:
     // 13.3 / 12.6 / 12.4 ms).
+    // Without a pruning threshold every centroid survives and a wave gathers its passages' scores token by token: short
+    // ranges give such a launch the waves that hide the gathers (400 000 passages, one query: 15.5 -> 2.3 ms per search with
+    // 128 instead of 2048 passages per wave; 64 queries: 117 -> 106).
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
-    if (ranges <= 40)
+    if (unpruned)
+        while (len_log > 7 && (waves << (12 - len_log)) <= 262144) --len_log;
+    else if (ranges <= 40)
         while (len_log > 7 && (ranges << (12 - len_log)) <= 128 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 ? 2 : 1);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
