@@ -98,9 +98,9 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     int32_t *kept_ids;      // [nq][S2_MAX_KEPT]
     float *T;               // [nq][S2_MAX_KEPT + 1][32]
     const int64_t *ivf_offsets;  // [C + 1] inverted-list offsets: slots are numbered by list length (null: by id)
-    int32_t *qcount;        // [3] / [3][qlist_stride]: the queries by number of surviving centroids (none, 1..31, more),
-    int32_t *qlist;         //   appended as their workgroups finish (null: not recorded).  Stage 2 runs one kernel per
-    int qlist_stride;       //   class and takes its queries from these lists.
+    int32_t *qcount;        // [4] / [3][qlist_stride]: the queries by number of surviving centroids (none, 1..31, 32..63; more:
+    int32_t *qlist;         //   from the end of the last row), appended as their workgroups finish (null: not recorded).
+    int qlist_stride;       //   Stage 2 takes its queries from these lists.
     bool need_hash;         // stage 2 will use the streaming form
 };
 
@@ -275,9 +275,10 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
             meta_q->bin_scale = (K > 0 && range > 0.f && range < INFINITY) ? (float)SEL_BINS / range : 0.f;
             meta_q->hash_shift = hash_shift;
             if (qlist) {
-                const int cls = K == 0 ? 0 : (K <= 31 ? 1 : 2);
+                const int cls = K == 0 ? 0 : (K <= 31 ? 1 : (K <= S2_MAX_KEPT ? 2 : 3));
                 const int at = atomicAdd(&qcount[cls], 1);
-                if (at < qlist_stride) qlist[(int64_t)cls * qlist_stride + at] = q;  // (always, when the counts start at zero)
+                // (always in range, when the counts start at zero)
+                if (at < qlist_stride) qlist[cls < 3 ? (int64_t)cls * qlist_stride + at : 3ll * qlist_stride - 1 - at] = q;
             }
         }
     }

@@ -730,6 +730,251 @@ __device__ __forceinline__ int2 s2_coarse_load(const int32_t *coarse_q, int lane
                                                    __HIP_MEMORY_SCOPE_AGENT);
     return make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
 }
+// The candidates among the passages of the bitmap words [w0, w0 + nw), nw <= 64, all in one column of the range table: the
+// union of the nu probed lists, into lcand[0 .. nw).  All 256 threads of a workgroup call this; a barrier ends it.
+struct S2CandScratch {
+    int64_t first[IV_LISTS];
+    int32_t count[IV_LISTS];
+};
+__device__ __forceinline__ void s2_block_candidates(const int32_t *__restrict__ uq, int nu, const int64_t *__restrict__ ivf_offsets,
+                                                    const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
+                                                    int64_t nr, int shift, const int32_t *__restrict__ dense_id,
+                                                    const uint32_t *__restrict__ dense_bits, int64_t cand_words, int64_t P,
+                                                    int64_t w0, int nw, uint32_t *lcand /*[64]*/, S2CandScratch &cs,
+                                                    int32_t *rows /*[IV_LISTS]*/, int32_t *counts /*[2]*/)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid & 15;
+    const int64_t col = (w0 << 5) >> shift;
+    const uint32_t p0 = (uint32_t)(w0 << 5), len = 32u * (uint32_t)nw;
+    if (tid < 64) lcand[tid] = 0u;
+    for (int u0 = 0; u0 < nu; u0 += IV_LISTS) {
+        __syncthreads();  // the words are zero / the previous lists are done
+        if (tid < 2) counts[tid] = 0;
+        __syncthreads();
+        if (u0 + tid < nu) {
+            const int32_t c = uq[u0 + tid];
+            const int32_t d = dense_id[c];
+            const uint32_t a = table[(int64_t)c * (nr + 1) + col], b = table[(int64_t)c * (nr + 1) + col + 1];
+            if (d >= 0) {
+                rows[atomicAdd(&counts[0], 1)] = d;
+            } else if (b > a) {
+                const int i = atomicAdd(&counts[1], 1);
+                cs.first[i] = ivf_offsets[c] + a;
+                cs.count[i] = (int)(b - a);
+            }
+        }
+        __syncthreads();
+        const int n_rows = counts[0], n_lists = counts[1];
+        uint32_t v = 0u;
+        if (lane < nw)
+            for (int d0 = wave; d0 < n_rows; d0 += 4 * IV_WAVES) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (d0 + IV_WAVES * u < n_rows) v |= dense_bits[(int64_t)rows[d0 + IV_WAVES * u] * cand_words + w0 + lane];
+            }
+        if (v) atomicOr(&lcand[lane], v);
+        // sixteen lanes per list, four lists each in flight
+        for (int l0 = tid >> 4; l0 < n_lists; l0 += 4 * (64 * IV_WAVES / 16)) {
+            int n[4];
+            const int32_t *src[4];
+            uint32_t pid[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int l = l0 + u * (64 * IV_WAVES / 16);
+                n[u] = l < n_lists ? cs.count[l] : 0;
+                src[u] = ivf_pids + (l < n_lists ? cs.first[l] : 0);
+                pid[u] = sub < n[u] ? (uint32_t)src[u][sub] : 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (pid[u] - p0 < len) atomicOr(&lcand[(pid[u] - p0) >> 5], 1u << (pid[u] & 31));
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                for (int x = 16 + sub; x < n[u]; x += 16) {
+                    const uint32_t loc = (uint32_t)src[u][x] - p0;
+                    if (loc < len) atomicOr(&lcand[loc >> 5], 1u << (loc & 31));
+                }
+        }
+    }
+    __syncthreads();
+    if (tid == nw - 1 && P < ((w0 + nw) << 5)) lcand[tid] &= (1u << (uint32_t)(P & 31)) - 1u;  // (a guard: lists hold ids below P)
+    __syncthreads();
+}
+
+// Queries with more than S2_MAX_KEPT surviving centroids (low thresholds, or none): no slot sets, no planes and no bound; every
+// candidate is scored from its token codes.  Bound by the rows of S_cq it gathers, 128 bytes per surviving token.
+// S2_GATHER_BLOCKS workgroups at the end of the 64-bit instance's grid share these queries (the probe kernel lists them
+// from the end of the row of that instance's class; a launch without any loses nothing, they leave while the others
+// work).  Their shares are even in bitmap words: eight queries at a time go to one XCD each, whose workgroups
+// then gather from one query's S_cq, what is left over eight to all workgroups together.
+// Per wave sixteen passages at a time: the codes and the pruning bits of eight of them in flight, the surviving ones listed
+// in LDS, then eight rows per load instruction as in stage 3.  Bins are counted in LDS and added once per share.
+// 400 000 passages, one query: 4.1 ms per search with four waves per 2048 passages fetching two rows at a time, 15.6 with one,
+// 0.44 now; 64 queries 92, 117 and 17.
+#define S2_GATHER_BLOCKS 768  // three per compute unit: what the 64-bit instances' LDS admits
+#define S2_GATHER_STRIDE 68   // of a passage's list: eight lanes that read one column of eight lists hit all banks
+struct S2GatherScratch {
+    S2CandScratch cand;
+    float part_max[IV_WAVES][8][QLEN];
+    int32_t list[IV_WAVES][8][S2_GATHER_STRIDE];  // centroids of the surviving tokens; then the passage's column maxima
+    int32_t hist[SEL_BINS];
+};
+
+template <int N>
+__device__ __forceinline__ float4 s2_gather_rows(const float *__restrict__ Sq, const int32_t *list, int cnt, int r, int part, float4 m)
+{
+    float4 v[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int t = 8 * u + r;
+        v[u] = *reinterpret_cast<const float4 *>(Sq + (int64_t)list[t < cnt ? t : cnt - 1] * QLEN + 4 * part);
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) m = make_float4(fmaxf(m.x, v[u].x), fmaxf(m.y, v[u].y), fmaxf(m.z, v[u].z), fmaxf(m.w, v[u].w));
+    return m;
+}
+__device__ __forceinline__ float4 s2_gather_list(const float *__restrict__ Sq, const int32_t *list, int cnt, int lane, float4 m)
+{
+    const int r = lane >> 3, part = lane & 7;
+    switch ((cnt + 7) >> 3) {  // uniform
+    case 0: return m;
+    case 1: return s2_gather_rows<1>(Sq, list, cnt, r, part, m);
+    case 2: return s2_gather_rows<2>(Sq, list, cnt, r, part, m);
+    case 3: return s2_gather_rows<3>(Sq, list, cnt, r, part, m);
+    case 4: return s2_gather_rows<4>(Sq, list, cnt, r, part, m);
+    case 5: return s2_gather_rows<5>(Sq, list, cnt, r, part, m);
+    case 6: return s2_gather_rows<6>(Sq, list, cnt, r, part, m);
+    case 7: return s2_gather_rows<7>(Sq, list, cnt, r, part, m);
+    default: return s2_gather_rows<8>(Sq, list, cnt, r, part, m);
+    }
+}
+__device__ __forceinline__ int64_t s2_lane64(int64_t v, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// Share j of nj of query q (all threads of the workgroup call this).
+__device__ void s2_gather_share(int q, int64_t j, int64_t nj, const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq,
+                                int uniq_stride, const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids,
+                                const uint32_t *__restrict__ table, int64_t nr, int shift, const float *__restrict__ S, int64_t C,
+                                const uint32_t *__restrict__ keepbits, int64_t keep_words, const int32_t *__restrict__ codes,
+                                const int64_t *__restrict__ doc_offsets, int64_t P, float bin_hi, float bin_scale,
+                                uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
+                                int32_t *__restrict__ hist, uint32_t *__restrict__ emptybits,
+                                const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits, S2GatherScratch &gs,
+                                uint32_t *lcand, uint32_t *lempty, int32_t *rows, int32_t *counts)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = s2_uniform(tid >> 6);
+    const int64_t wa = cand_words * j / nj, wb = cand_words * (j + 1) / nj;
+    if (wa == wb) return;  // uniform
+    const float *Sq = S + (int64_t)q * C * QLEN;
+    const uint32_t *kb = keepbits + (int64_t)q * keep_words;
+    uint32_t *keys_out = reinterpret_cast<uint32_t *>(keys2 + (int64_t)q * key_stride);
+    for (int e = tid; e < SEL_BINS; e += 64 * IV_WAVES) gs.hist[e] = 0;
+    for (int64_t w0 = wa; w0 < wb;) {
+        const int64_t we = (w0 | 63) + 1 < wb ? (w0 | 63) + 1 : wb;  // within 2048 aligned passages: one column of the table
+        const int nw = (int)(we - w0);
+        s2_block_candidates(uniq + (int64_t)q * uniq_stride, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id, dense_bits,
+                            cand_words, P, w0, nw, lcand, gs.cand, rows, counts);
+        if (tid < 64) lempty[tid] = 0u;
+        if (tid < nw) candbits[(int64_t)q * cand_words + w0 + tid] = lcand[tid];
+        __syncthreads();
+        for (int h = wave; h < 2 * nw; h += IV_WAVES) {
+            uint32_t rest = (uint32_t)s2_uniform((int)((lcand[h >> 1] >> (16 * (h & 1))) & 0xFFFFu));
+            const int64_t p0 = ((w0 + (h >> 1)) << 5) + 16 * (h & 1);
+            int64_t off = 0;
+            if (lane <= 16) off = doc_offsets[p0 + lane < P ? p0 + lane : P];
+            uint32_t none = 0u;  // candidates without a surviving token
+            while (rest) {
+                // the first 64 codes of up to eight candidates; lane a: bit and number of surviving tokens of the a-th
+                int32_t code[8];
+                int my_bit = 0, my_cnt = 0, n = 0;
+#pragma unroll
+                for (int a = 0; a < 8; ++a) {
+                    code[a] = -1;
+                    if (rest) {
+                        const int b = __ffs((int)rest) - 1;
+                        rest &= rest - 1;
+                        if (lane == a) my_bit = b;
+                        const int64_t t0 = s2_lane64(off, b), t1 = s2_lane64(off, b + 1);
+                        if (t0 + lane < t1) code[a] = codes[t0 + lane];
+                        n = a + 1;
+                    }
+                }
+                uint32_t kept[8];
+#pragma unroll
+                for (int a = 0; a < 8; ++a) kept[a] = code[a] >= 0 ? kb[code[a] >> 5] : 0u;
+#pragma unroll
+                for (int a = 0; a < 8; ++a) {
+                    const bool hit = (kept[a] >> (code[a] & 31)) & 1u;
+                    const unsigned long long mask = __ballot(hit);
+                    if (hit) gs.list[wave][a][__popcll(mask & ((1ull << lane) - 1ull))] = code[a];
+                    if (lane == a) my_cnt = __popcll(mask);
+                }
+                s2_wave_sync();
+#pragma unroll 1
+                for (int a = 0; a < n; ++a) {
+                    int32_t *list = gs.list[wave][a];
+                    const int b = __builtin_amdgcn_readlane(my_bit, a);
+                    int cnt = __builtin_amdgcn_readlane(my_cnt, a);
+                    float4 m = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+                    m = s2_gather_list(Sq, list, cnt, lane, m);
+                    bool any = cnt > 0;
+                    const int64_t t1 = s2_lane64(off, b + 1);
+                    for (int64_t tb = s2_lane64(off, b) + 64; tb < t1; tb += 64) {  // a passage of more than 64 tokens
+                        const int32_t c = tb + lane < t1 ? codes[tb + lane] : -1;
+                        const bool hit = c >= 0 && ((kb[c >> 5] >> (c & 31)) & 1u);
+                        const unsigned long long mask = __ballot(hit);
+                        s2_wave_sync();
+                        if (hit) list[__popcll(mask & ((1ull << lane) - 1ull))] = c;
+                        s2_wave_sync();
+                        cnt = __popcll(mask);
+                        any = any || cnt > 0;
+                        m = s2_gather_list(Sq, list, cnt, lane, m);
+                    }
+                    if (!any) none |= 1u << b;
+                    *reinterpret_cast<float4 *>(&gs.part_max[wave][lane >> 3][4 * (lane & 7)]) = m;
+                    s2_wave_sync();
+                    if (lane < QLEN) {
+                        float v = gs.part_max[wave][0][lane];
+#pragma unroll
+                        for (int r = 1; r < 8; ++r) v = fmaxf(v, gs.part_max[wave][r][lane]);
+                        reinterpret_cast<float *>(list)[lane] = v;
+                    }
+                    s2_wave_sync();
+                }
+                if (lane < n) {  // lane a: the sum over the query tokens for the a-th, in double, in index order
+                    const float4 *col = reinterpret_cast<const float4 *>(gs.list[wave][lane]);
+                    double d = 0.0;
+#pragma unroll
+                    for (int i4 = 0; i4 < QLEN / 4; ++i4) {
+                        const float4 v = col[i4];
+                        d += (double)v.x;
+                        d += (double)v.y;
+                        d += (double)v.z;
+                        d += (double)v.w;
+                    }
+                    const bool empty = (none >> my_bit) & 1u;
+                    const float score = (float)d;
+                    keys_out[p0 + my_bit] = empty ? PLAID_S2_NO_SCORE : plaid_score_to_ord(score);
+                    if (!empty) atomicAdd(&gs.hist[plaid_s2_bin(score, bin_hi, bin_scale)], 1);
+                }
+                s2_wave_sync();  // the lists are written again for the next candidates
+            }
+            if (lane == 0 && none) atomicOr(&lempty[h >> 1], none << (16 * (h & 1)));
+        }
+        __syncthreads();
+        if (tid < nw) emptybits[(int64_t)q * cand_words + w0 + tid] = lempty[tid];
+        __syncthreads();  // the words are set up again for the next ones
+        w0 = we;
+    }
+    s2_flush_hist(gs.hist, hist + (int64_t)q * SEL_BINS);
+    __syncthreads();
+}
+
 // SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
 // the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
 template <int SHIFT, typename SetT>
@@ -742,7 +987,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     int32_t *__restrict__ hist, Sel2State *__restrict__ state,
     uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
     int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
-    int steps, int32_t m, int first_batch)
+    int steps, int32_t m, int first_batch, unsigned main_blocks)
 {
     constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
     // Planes of 64 words that fit a wave's area: what lets four (32-bit sets, coarse tables) or three workgroups share a
@@ -750,14 +995,14 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 36 : 24);
     static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
     constexpr int SLOTS = KMAX + 1;
-    __shared__ uint32_t area_all[IV_WAVES][FULL_PLANES * 64];
+    __shared__ __align__(16) uint32_t area_all[IV_WAVES][FULL_PLANES * 64];
     __shared__ __align__(16) float Tl[KMAX * QLEN];
     __shared__ float rowsum[SLOTS];
     __shared__ int32_t kid[SLOTS], drow[SLOTS];  // slot - 1 -> centroid, row of its list's bitmap or -1
     __shared__ uint8_t order[SLOTS];             // the slots (minus one) with a bitmap, from the back those without
     __shared__ int32_t plist[IV_LISTS];    // probed lists of no surviving centroid: bitmap rows from the front, centroids from the back
     __shared__ uint32_t probed_mask[2];    // bit s: slot s + 1 is also probed
-    __shared__ int32_t n_front, n_back, n_sparse;
+    __shared__ int32_t n_front[2], n_sparse;  // [1]: of those from the back
     // per wave; while lists are applied: start (low 32 bits), start (high bits) << 21 | entries << 7 | plane, candidate words;
     // while passages are scored: 16-bit counts of the coarse bins, ranks of the words' first bits, selected words
     __shared__ uint32_t lstart_all[IV_WAVES][64];
@@ -770,9 +1015,31 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     uint32_t *lstart = lstart_all[wave];
     uint32_t *lcnt = lcnt_all[wave];
     uint32_t *lcand = lcand_all[wave];
-    // This instance's queries, from the lists the probe kernel made: class 1 (1..31 survivors) or 2 (more), and with the
+    if constexpr (sizeof(SetT) == 8) {
+        if (blockIdx.x >= main_blocks) {  // uniform: a workgroup of the gather form
+            static_assert(sizeof(S2GatherScratch) <= sizeof(area_all), "the gather form's arrays take the place of the planes");
+            S2GatherScratch &gs = *reinterpret_cast<S2GatherScratch *>(&area_all[0][0]);
+            auto share = [&](int q, int64_t j, int64_t nj) {
+                s2_gather_share(q, j, nj, uniq, n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, SHIFT, S, C, keepbits,
+                                keep_words, codes, doc_offsets, P, meta[q].bin_hi, meta[q].bin_scale, candbits, cand_words, keys2,
+                                key_stride, hist, emptybits, dense_id, dense_bits, gs, lcand_all[0], lcnt_all[0], plist, n_front);
+            };
+            const int64_t g = blockIdx.x - main_blocks, ng = gridDim.x - main_blocks;
+            if (mode & 4) {
+                if (s2_uniform(meta[0].K) > S2_MAX_KEPT) share(0, g, ng);
+                return;
+            }
+            const int n_more = s2_uniform(qcount[3]), by_xcd = n_more & ~7;
+            const int32_t *more = qlist + 3ll * qlist_stride - 1;  // the i-th is more[-i]
+            for (int i = (int)(blockIdx.x & 7); i < by_xcd; i += 8) share(s2_uniform(more[-i]), g >> 3, ng >> 3);
+            for (int i = by_xcd; i < n_more; ++i) share(s2_uniform(more[-i]), g, ng);
+            return;
+        }
+    }
+    // This instance's queries, from the lists the probe kernel made: class 1 (1..31 survivors) or 2 (32..63), and with the
     // 32-bit instance class 0 (none) unless s2_union_wide_kernel has produced its candidate and empty-bag words (mode bit
-    // 0).  mode bit 1 (64-bit instance): the only instance launched, it takes every query.  Bit 3: see the launch.  Consecutive workgroups take
+    // 0).  mode bit 1 (64-bit instance): the only instance launched, it takes every query of these classes.  Bit 3: see the
+    // launch.  Queries with more survivors belong to the workgroups above.  Consecutive workgroups take
     // consecutive queries of one passage range: all queries of a chunk advance together, so that each has a threshold to
     // prune with after its first ranges, and the bitmap rows of the range are shared in the caches.
     const int cls = sizeof(SetT) == 4 ? 1 : 2;
@@ -795,7 +1062,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         const int probed_c = tid < uniq_stride ? uniq[(int64_t)q * uniq_stride + tid] : 0;
         const int K_all = s2_uniform(mt.K);
         if (!take_all && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
-        const int K = K_all <= KMAX ? K_all : 0;  // slots kept as planes (0 also for the queries scored from token codes)
+        if (K_all > KMAX) continue;  // (a single query of the gather form)
+        const int K = K_all;
         const int nu = n_uniq[q];
         const bool classified = nu <= IV_LISTS;
         const int32_t *uq = uniq + (int64_t)q * uniq_stride;
@@ -813,7 +1081,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             if (tid < K) order[d >= 0 ? __popcll(dm & below) : SLOTS - 1 - __popcll(sm & below)] = (uint8_t)tid;
             if (tid == 0) {
                 n_sparse = __popcll(sm);
-                n_front = n_back = 0;
+                n_front[0] = n_front[1] = 0;
                 probed_mask[0] = probed_mask[1] = 0u;
             }
         }
@@ -835,14 +1103,14 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                 int slot = -1;
                 for (int s = 0; s < K; ++s) slot = kid[s] == c ? s : slot;
                 if (slot >= 0) atomicOr(&probed_mask[slot >> 5], 1u << (slot & 31));
-                else if (d >= 0) plist[atomicAdd(&n_front, 1)] = d;
-                else plist[IV_LISTS - 1 - atomicAdd(&n_back, 1)] = c;
+                else if (d >= 0) plist[atomicAdd(&n_front[0], 1)] = d;
+                else plist[IV_LISTS - 1 - atomicAdd(&n_front[1], 1)] = c;
             }
         }
         __syncthreads();
         const uint32_t pm0 = s2_uniform((int)probed_mask[0]), pm1 = s2_uniform((int)probed_mask[1]);
-        const int n_rows = s2_uniform(n_front), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
-        const int n_sp = classified ? s2_uniform(n_back) : nu;
+        const int n_rows = s2_uniform(n_front[0]), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
+        const int n_sp = classified ? s2_uniform(n_front[1]) : nu;
         int my_log = len_log;
         while ((n_ss << (my_log - 5)) > FULL_PLANES * 64) --my_log;
         const int len = 1 << my_log, nw = len >> 5;
@@ -1031,17 +1299,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             cand &= valid;
             if (act) {
                 cbq[w0 + lane] = cand;
-                if (K_all <= KMAX) ebq[w0 + lane] = cand & ~any;
-            }
-            if (sizeof(SetT) == 8 && K_all > KMAX) {
-                // too many survivors for slot sets: the range's candidates are scored from their token codes, all of them
-                lcand[lane] = cand;
-                s2_wave_sync();
-                const int64_t w_end = w0 + nw < cand_words ? w0 + nw : cand_words;
-                s2_gather_body(q, S, C, keepbits, keep_words, lcand, w0, w0, 1, w_end, cand_words, P, doc_offsets, codes,
-                               mt.bin_hi, mt.bin_scale, reinterpret_cast<uint32_t *>(klist), hist_q, emptybits);
-                s2_wave_sync();
-                continue;
+                ebq[w0 + lane] = cand & ~any;
             }
             uint32_t left = cand & any;
             for (int round = 0; __any(left != 0u); ++round) {  // (no round: no candidate with a surviving centroid)
@@ -1198,7 +1456,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift, int32_t m, bool unpruned)
+                                  const uint32_t *dense_bits, int shift, int32_t m)
 {
     const int64_t nr = (P + (1ll << shift) - 1) >> shift;
     const int64_t nwide = (P + (1ll << UW_SHIFT) - 1) >> UW_SHIFT;
@@ -1215,14 +1473,9 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // 196.  Steps per wave: the set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has
     // dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M:
     // 13.3 / 12.6 / 12.4 ms).
-    // Without a pruning threshold every centroid survives and a wave gathers its passages' scores token by token: short
-    // ranges give such a launch the waves that hide the gathers (400 000 passages, one query: 15.5 -> 2.3 ms per search with
-    // 128 instead of 2048 passages per wave; 64 queries: 117 -> 106).
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
-    if (unpruned)
-        while (len_log > 7 && (waves << (12 - len_log)) <= 262144) --len_log;
-    else if (ranges <= 40)
+    if (ranges <= 40)
         while (len_log > 7 && (ranges << (12 - len_log)) <= 128 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 ? 2 : 1);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
@@ -1232,12 +1485,16 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int64_t fb = 8ll * m / per_query;
     const int first_batch = fb < 32 ? 32 : (fb > 64 ? 64 : (int)fb);
     const int64_t blocks = (P + per_block - 1) / per_block;
+    // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
+    const int64_t words = (nq * cand_words + 7) & ~7ll;
+    const unsigned gather = words < S2_GATHER_BLOCKS ? (unsigned)words : S2_GATHER_BLOCKS;
 #define S2_INVERT(SH_, T_, MODE_, NQX_)                                                                                     \
-    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)(blocks * (NQX_))), dim3(64 * IV_WAVES), 0, st, uniq,     \
+    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)(blocks * (NQX_)) + (sizeof(T_) == 8 ? gather : 0u)),     \
+                       dim3(64 * IV_WAVES), 0, st, uniq,                                                                      \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
                        P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.state,         \
                         b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
-                       steps, m, first_batch)
+                       steps, m, first_batch, (unsigned)(blocks * (NQX_)))
     // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
     // updates alone).  Workgroups are dealt to the eight XCDs in turn, so with a multiple of eight queries per passage
     // range (empty ones added) a query's workgroups share an XCD; where that would leave much of the chip without

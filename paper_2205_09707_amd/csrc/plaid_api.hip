@@ -688,7 +688,7 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.s2.hist1 = (int32_t *)take((size_t)qc * SEL_BINS * 4);
     w.s2.hist2 = (int32_t *)take((size_t)qc * SEL_BINS * 4);
     w.s2.state = (Sel2State *)take((size_t)qc * sizeof(Sel2State));
-    w.s2.qcount = (int32_t *)take(4 * sizeof(int32_t));
+    w.s2.qcount = (int32_t *)take(5 * sizeof(int32_t));
     w.sel3_zero = take(plaid_select_zero_bytes(qc));
     w.sel4_zero = take(plaid_select_zero_bytes(qc));
     w.zero_bytes = off;
@@ -839,8 +839,7 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         if (ix->ivr_table)
             plaid_launch_stage2_inverted(st, w.uniq, w.n_uniq, w.uniq_stride, ix->ivf_offsets, ix->ivf_pids, ix->ivr_table, w.S,
                                          C, w.keepbits, w.keep_words, ix->codes, ix->doc_offsets, P, n, w.s2, w.candbits,
-                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->ivr_shift, pl.nd,
-                                         t_cs == -INFINITY);
+                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->ivr_shift, pl.nd);
         else
             plaid_launch_stage2(st, w.S, C, w.keepbits, w.keep_words, w.probed, nprobe, w.candbits, w.cand_words, P, ix->N,
                                 ix->doc_offsets, ix->codes, n, w.s2, w.keys2, P);
@@ -1024,7 +1023,7 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
         if (qmask) plaid_launch_fill_u32(st, qmask, mask_words, 0u);
         plaid_launch_vanilla_candidates(st, w.uniq, w.n_uniq, w.uniq_stride, ix->emb_offsets, ix->emb_ids, ix->tok2pid, n,
                                         w.keep_words, probebits, w.candbits, w.cand_words, ix->doc_offsets, ix->codes, P, ix->N, C,
-                                        qmask, (uint32_t *)w.s2.qcount + 3);
+                                        qmask, (uint32_t *)w.s2.qcount + 4);
         plaid_launch_bitmap_to_list(st, w.candbits, w.cand_words, P, n, cand, P, w.n2);
         // more than ncandidates: scored on the embeddings of the probed lists alone, the best ncandidates stay
         plaid_launch_vanilla_prune(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,

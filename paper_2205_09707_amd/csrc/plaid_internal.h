@@ -237,9 +237,11 @@ struct Stage2Buffers {   // all device pointers, leading dimension = query of th
     int32_t *hist1;      // [nq][SEL_BINS]  digit histogram of an over-long boundary list
     int32_t *hist2;      // [nq][SEL_BINS]  ... of the list the first digit filter leaves, when that is over-long too
     Sel2State *state;    // [nq]
-    int32_t *qcount;     // [3] queries of the chunk with no / 1..31 / more surviving centroids (null: not recorded)
+    int32_t *qcount;     // [5] queries of the chunk with no / 1..31 / 32..S2_MAX_KEPT / more surviving centroids (null: not
+                         //   recorded); [4]: plaid_launch_vanilla_candidates' work word
     // no initialisation needed
-    int32_t *qlist;      // [3][qlist_stride] those queries, in the order their probe workgroups finished
+    int32_t *qlist;      // [3][qlist_stride] those queries, in the order their probe workgroups finished; those with more
+                         //   than S2_MAX_KEPT from the end of the last row
     int qlist_stride;
     S2Meta *meta;        // [nq]
     int32_t *kept_ids;   // [nq][S2_MAX_KEPT]
@@ -279,7 +281,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift, int32_t m, bool unpruned);
+                                  const uint32_t *dense_bits, int shift, int32_t m);
 // Bitmaps over the passages for the longest inverted lists (built once per index, next to the range table):
 // dense_id[c] = bitmap row of centroid c or -1 (counter[0], zero before the call, returns the number of rows);
 // bits: rows x words, zero before the call, words = ceil(P / 32).

@@ -40,3 +40,50 @@ def test_assignment_with_every_centroid_twice_in_a_row(C):
     plain, tied = _ms(lambda: pl.plaid_assign_centroids(cen, x)), _ms(lambda: pl.plaid_assign_centroids(twins, x))
     # measured: 1.8 to 4 times; with a block's rows walked by one thread each: 77 to 360 times
     assert tied < 10 * plain, (tied, plain)
+
+
+def _index(monkeypatch, pl, C, P, length, seed, form):
+    """An index of random passages (Zipf-like centroid popularity, residuals of one bucket) and 64 queries near centroids."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
+    codes = (C * torch.rand(P * length, generator=g, device="cuda") ** 3).int().clamp_(max=C - 1)
+    offsets = torch.arange(P + 1, device="cuda", dtype=torch.int64) * length
+    ivf_offsets, ivf_pids = pl.plaid_build_ivf(codes, offsets, C)
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
+              "residuals": torch.randint(0, 256, (P * length, 32), generator=g, device="cuda", dtype=torch.uint8),
+              "bucket_weights": torch.tensor([-0.05, -0.015, 0.015, 0.05], device="cuda")}
+    near = cen[(C * torch.rand(64 * 32, generator=g, device="cuda") ** 3).long().clamp_(max=C - 1)]
+    Q = torch.nn.functional.normalize(near + 0.03 * torch.randn(64 * 32, 128, generator=g, device="cuda"), dim=1)
+    with monkeypatch.context() as mp:
+        mp.setenv("PLAID_STAGE2_FORM", form)
+        idx = pl.plaid_index_from_view(arrays, 2, device=0, copy=False)
+    return idx, Q.reshape(64, 32, 128).contiguous()
+
+
+def test_more_than_63_survivors_in_the_inverted_form(monkeypatch):
+    """Queries with more survivors than the inverted form keeps slots for are scored from their token codes, whatever the
+    value of the threshold that lets them through, alone or among queries with few survivors: as fast as the streaming
+    form does it, and with the same results."""
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    P = 200_000
+    for form in ("inverted11", "inverted13"):
+        inv, Q = _index(monkeypatch, pl, 4096, P, 40, 5, form)
+        stream, _ = _index(monkeypatch, pl, 4096, P, 40, 5, "stream")
+        mixed = Q.clone()
+        mixed[::8] *= 3.0  # scores three times as high: hundreds of centroids pass a threshold of 0.6, few for the others
+        try:
+            for name, q, t_cs, limit in [("one, finite", Q[:1], -2.0, 1.5), ("one, unbounded", Q[:1], -float("inf"), 1.5),
+                                         ("nine", Q[:9], -2.0, 1.5), ("mixed", mixed, 0.6, 1.5)]:
+                q = q.contiguous()
+                a = pl.plaid_search(inv, q, 2, t_cs, 500, 50)
+                b = pl.plaid_search(stream, q, 2, t_cs, 500, 50)
+                np.testing.assert_array_equal(a[0].cpu().numpy(), b[0].cpu().numpy(), err_msg=name)
+                np.testing.assert_array_equal(a[1].cpu().numpy(), b[1].cpu().numpy(), err_msg=name)
+                ti, ts = (_ms(lambda: pl.plaid_search(x, q, 2, t_cs, 500, 50)) for x in (inv, stream))
+                print(f"{form} {name}: {ti:.3f} ms, streaming form {ts:.3f} ms")
+                assert ti < limit * ts, (form, name, ti, ts)
+        finally:
+            pl.plaid_index_free(inv)
+            pl.plaid_index_free(stream)
