@@ -696,7 +696,7 @@ __global__ __launch_bounds__(UW_THREADS) void s2_union_wide_kernel(
 // passages takes 16 to 20 us with 12 to 16 waves per compute unit, a third of it the additions of the bounds, the rest the
 // chains of dependent loads and LDS accesses of the other parts.
 #define IV_WAVES 4
-#define IV_LISTS 256    // probed-only lists a workgroup classifies; beyond (nprobe > 8) they are walked unclassified
+#define IV_LISTS 256    // probed lists a workgroup classifies; beyond (nprobe > 8) s2_candidates_kernel walks them
 
 // Makes the compiler forget what it has derived from v.  Addresses and lane masks computed from the lane number would
 // otherwise be kept in registers across the range kernel's loops (25 registers past what four waves per SIMD leave).
@@ -801,6 +801,29 @@ __device__ __forceinline__ void s2_block_candidates(const int32_t *__restrict__ 
     __syncthreads();
 }
 
+// The candidate words of every query, 64 per workgroup, for launches whose probed lists are more than a workgroup of the range
+// kernel classifies (nprobe > 8).  A wave of that kernel owns 2048 passages, and walked all of the lists for them alone, 64 to
+// a round and the long ones entry by entry: stage 2 of one query of 400 000 passages took 35 / 129 / 219 us with nprobe 9 / 16 /
+// 64 that way, 44 / 46 / 58 with the
+// words given; 64 queries 539 / 621 / 981 and 203 / 231 / 408.
+__global__ __launch_bounds__(64 * IV_WAVES) void s2_candidates_kernel(
+    const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride, const int64_t *__restrict__ ivf_offsets,
+    const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table, int64_t nr, int shift, int64_t P,
+    const S2Meta *__restrict__ meta, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
+    uint32_t *__restrict__ candbits, int64_t cand_words, int skip_none /* s2_union_wide_kernel has done those without survivors */)
+{
+    __shared__ S2CandScratch cs;
+    __shared__ uint32_t lcand[64];
+    __shared__ int32_t rows[IV_LISTS], counts[2];
+    const int q = blockIdx.y, tid = threadIdx.x;
+    if (skip_none && s2_uniform(meta[q].K) == 0) return;  // uniform
+    const int64_t w0 = (int64_t)blockIdx.x * 64;
+    const int nw = cand_words - w0 < 64 ? (int)(cand_words - w0) : 64;
+    s2_block_candidates(uniq + (int64_t)q * uniq_stride, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id, dense_bits,
+                        cand_words, P, w0, nw, lcand, cs, rows, counts);
+    if (tid < nw) candbits[(int64_t)q * cand_words + w0 + tid] = lcand[tid];
+}
+
 // Queries with more than S2_MAX_KEPT surviving centroids (low thresholds, or none): no slot sets, no planes and no bound; every
 // candidate is scored from its token codes.  Bound by the rows of S_cq it gathers, 128 bytes per surviving token.
 // S2_GATHER_BLOCKS workgroups at the end of the 64-bit instance's grid share these queries (the probe kernel lists them
@@ -810,7 +833,7 @@ __device__ __forceinline__ void s2_block_candidates(const int32_t *__restrict__ 
 // Per wave sixteen passages at a time: the codes and the pruning bits of eight of them in flight, the surviving ones listed
 // in LDS, then eight rows per load instruction as in stage 3.  Bins are counted in LDS and added once per share.
 // 400 000 passages, one query: 4.1 ms per search with four waves per 2048 passages fetching two rows at a time, 15.6 with one,
-// 0.44 now; 64 queries 92, 117 and 17.
+// 0.44 to 0.47 now; 64 queries 92, 117 and 17 to 19.
 #define S2_GATHER_BLOCKS 768  // three per compute unit: what the 64-bit instances' LDS admits
 #define S2_GATHER_STRIDE 68   // of a passage's list: eight lanes that read one column of eight lists hit all banks
 struct S2GatherScratch {
@@ -864,7 +887,7 @@ __device__ void s2_gather_share(int q, int64_t j, int64_t nj, const int32_t *__r
                                 uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
                                 int32_t *__restrict__ hist, uint32_t *__restrict__ emptybits,
                                 const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits, S2GatherScratch &gs,
-                                uint32_t *lcand, uint32_t *lempty, int32_t *rows, int32_t *counts)
+                                uint32_t *lcand, uint32_t *lempty, int32_t *rows, int32_t *counts, bool given)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = s2_uniform(tid >> 6);
@@ -877,10 +900,15 @@ __device__ void s2_gather_share(int q, int64_t j, int64_t nj, const int32_t *__r
     for (int64_t w0 = wa; w0 < wb;) {
         const int64_t we = (w0 | 63) + 1 < wb ? (w0 | 63) + 1 : wb;  // within 2048 aligned passages: one column of the table
         const int nw = (int)(we - w0);
-        s2_block_candidates(uniq + (int64_t)q * uniq_stride, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id, dense_bits,
-                            cand_words, P, w0, nw, lcand, gs.cand, rows, counts);
+        uint32_t *cbq = candbits + (int64_t)q * cand_words + w0;
+        if (given) {  // uniform: s2_candidates_kernel's
+            if (tid < nw) lcand[tid] = cbq[tid];
+        } else {
+            s2_block_candidates(uniq + (int64_t)q * uniq_stride, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id,
+                                dense_bits, cand_words, P, w0, nw, lcand, gs.cand, rows, counts);
+            if (tid < nw) cbq[tid] = lcand[tid];
+        }
         if (tid < 64) lempty[tid] = 0u;
-        if (tid < nw) candbits[(int64_t)q * cand_words + w0 + tid] = lcand[tid];
         __syncthreads();
         for (int h = wave; h < 2 * nw; h += IV_WAVES) {
             uint32_t rest = (uint32_t)s2_uniform((int)((lcand[h >> 1] >> (16 * (h & 1))) & 0xFFFFu));
@@ -1015,24 +1043,24 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     uint32_t *lstart = lstart_all[wave];
     uint32_t *lcnt = lcnt_all[wave];
     uint32_t *lcand = lcand_all[wave];
+    const bool given = mode & 16;  // s2_candidates_kernel has written the candidate words
     if constexpr (sizeof(SetT) == 8) {
         if (blockIdx.x >= main_blocks) {  // uniform: a workgroup of the gather form
             static_assert(sizeof(S2GatherScratch) <= sizeof(area_all), "the gather form's arrays take the place of the planes");
             S2GatherScratch &gs = *reinterpret_cast<S2GatherScratch *>(&area_all[0][0]);
-            auto share = [&](int q, int64_t j, int64_t nj) {
-                s2_gather_share(q, j, nj, uniq, n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, SHIFT, S, C, keepbits,
-                                keep_words, codes, doc_offsets, P, meta[q].bin_hi, meta[q].bin_scale, candbits, cand_words, keys2,
-                                key_stride, hist, emptybits, dense_id, dense_bits, gs, lcand_all[0], lcnt_all[0], plist, n_front);
-            };
             const int64_t g = blockIdx.x - main_blocks, ng = gridDim.x - main_blocks;
-            if (mode & 4) {
-                if (s2_uniform(meta[0].K) > S2_MAX_KEPT) share(0, g, ng);
-                return;
-            }
-            const int n_more = s2_uniform(qcount[3]), by_xcd = n_more & ~7;
+            const int n_more = mode & 4 ? (s2_uniform(meta[0].K) > S2_MAX_KEPT ? 1 : 0) : s2_uniform(qcount[3]);
+            const int by_xcd = n_more & ~7;
             const int32_t *more = qlist + 3ll * qlist_stride - 1;  // the i-th is more[-i]
-            for (int i = (int)(blockIdx.x & 7); i < by_xcd; i += 8) share(s2_uniform(more[-i]), g >> 3, ng >> 3);
-            for (int i = by_xcd; i < n_more; ++i) share(s2_uniform(more[-i]), g, ng);
+            for (int i = by_xcd ? (int)(blockIdx.x & 7) : 0; i < n_more;) {
+                const bool own_xcd = i < by_xcd;
+                const int q = mode & 4 ? 0 : s2_uniform(more[-i]);
+                s2_gather_share(q, own_xcd ? g >> 3 : g, own_xcd ? ng >> 3 : ng, uniq, n_uniq, uniq_stride, ivf_offsets, ivf_pids,
+                                table, nr, SHIFT, S, C, keepbits, keep_words, codes, doc_offsets, P, meta[q].bin_hi,
+                                meta[q].bin_scale, candbits, cand_words, keys2, key_stride, hist, emptybits, dense_id, dense_bits, gs,
+                                lcand_all[0], lcnt_all[0], plist, n_front, given);
+                i = !own_xcd ? i + 1 : (i + 8 < by_xcd ? i + 8 : by_xcd);
+            }
             return;
         }
     }
@@ -1065,8 +1093,6 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         if (K_all > KMAX) continue;  // (a single query of the gather form)
         const int K = K_all;
         const int nu = n_uniq[q];
-        const bool classified = nu <= IV_LISTS;
-        const int32_t *uq = uniq + (int64_t)q * uniq_stride;
         __syncthreads();  // the previous query's readers are done
         if (tid < 64) {
             int32_t c = -1, d = -1;
@@ -1095,7 +1121,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             for (int i = 0; i < QLEN; ++i) d += (double)Tl[s2_row_piece(tid, i >> 2) + (i & 3)];
             rowsum[tid] = (float)d;
         }
-        if (classified) {
+        if (!given) {
             static_assert(64 * IV_WAVES >= IV_LISTS, "one thread per probed list");
             if (tid < nu) {
                 const int32_t c = probed_c;
@@ -1110,7 +1136,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         __syncthreads();
         const uint32_t pm0 = s2_uniform((int)probed_mask[0]), pm1 = s2_uniform((int)probed_mask[1]);
         const int n_rows = s2_uniform(n_front[0]), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
-        const int n_sp = classified ? s2_uniform(n_front[1]) : nu;
+        const int n_sp = s2_uniform(n_front[1]);
         int my_log = len_log;
         while ((n_ss << (my_log - 5)) > FULL_PLANES * 64) --my_log;
         const int len = 1 << my_log, nw = len >> 5;
@@ -1150,7 +1176,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             uint32_t A[S2_UB_BITS];
 #pragma unroll
             for (int k = 0; k < S2_UB_BITS; ++k) A[k] = 0u;
-            uint32_t any = 0u, cand = 0u;
+            uint32_t any = 0u, cand = given && act ? cbq[w0 + lane] : 0u;
             auto add = [&](uint32_t b, int g) {
                 any |= b;
                 uint32_t carry = 0u;
@@ -1211,7 +1237,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                     uint32_t la = list_a, lb = list_b;
                     int64_t at = list_at;
                     if (e >= n_ss) {
-                        const int32_t c = classified ? plist[IV_LISTS - 1 - (e - n_ss)] : uq[e - n_ss];
+                        const int32_t c = plist[IV_LISTS - 1 - (e - n_ss)];
                         la = table[(int64_t)c * (nr + 1) + col];
                         lb = table[(int64_t)c * (nr + 1) + col + 1];
                         at = ivf_offsets[c];
@@ -1467,6 +1493,11 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_union_wide_kernel, dim3((unsigned)nwide, nq), dim3(UW_THREADS), 0, st, uniq, n_uniq, uniq_stride,
                            ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            b.emptybits);
+    const int given = uniq_stride > IV_LISTS ? 16 : 0;
+    if (given)
+        hipLaunchKernelGGL(s2_candidates_kernel, dim3((unsigned)((cand_words + 63) / 64), nq), dim3(64 * IV_WAVES), 0, st, uniq, n_uniq,
+                           uniq_stride, ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
+                           wide);
     // Passages per wave and step: 2048, fewer for indexes of so few passages that a wave's own chain of steps is all that
     // counts and the chip has room for more waves.  One query of 10 000 passages: 109 / 99 / 90 us per search with 2048 / 512 /
     // 128, of 60 000: 120 / 114 / 113, of 200 000: 103 / 103 / 122; five of 29 500: 135 / 134 / 120; 64 of 20 000: 185 / 172 /
@@ -1502,7 +1533,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int padded = (nq + 7) & ~7;
     const bool pad = 4 * padded <= 5 * nq;
     const int nqx = pad ? padded : nq;
-    const int own = !pad && nq * blocks > 64 ? 8 : 0;
+    const int own = (!pad && nq * blocks > 64 ? 8 : 0) | given;
     if (nq < 8) {
         // a few queries: the 64-bit instance alone, taking every query (same sets, same scores, one launch less)
         const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own;

@@ -87,3 +87,38 @@ def test_more_than_63_survivors_in_the_inverted_form(monkeypatch):
         finally:
             pl.plaid_index_free(inv)
             pl.plaid_index_free(stream)
+
+
+def test_probing_many_centroids_of_a_single_query(monkeypatch):
+    """nprobe 64 probes seven times the lists of nprobe 9, most of them short: stage 2 of one query grows little by them."""
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    for form in ("inverted11", "inverted13"):
+        idx, Q = _index(monkeypatch, pl, 16384, 400_000, 40, 6, form)
+        stream, _ = _index(monkeypatch, pl, 16384, 400_000, 40, 6, "stream")
+        try:
+            for nq, t_cs in [(1, 0.6), (40, 0.6), (3, float("inf")), (2, 0.2)]:  # (40: workgroups of their own for no survivor)
+                q = Q[:nq].clone()
+                q[::3] *= 0.5  # below the threshold: no survivor
+                a, b = pl.plaid_search(idx, q, 64, t_cs, 1000, 100), pl.plaid_search(stream, q, 64, t_cs, 1000, 100)
+                np.testing.assert_array_equal(a[0].cpu().numpy(), b[0].cpu().numpy())
+                np.testing.assert_array_equal(a[1].cpu().numpy(), b[1].cpu().numpy())
+            q = Q[1:2].contiguous()
+
+            def stage2(nprobe):
+                pl.plaid_set_stage_timing(idx, True)
+                best = float("inf")
+                for _ in range(6):
+                    pl.plaid_search(idx, q, nprobe, 0.6, 1000, 100)
+                    torch.cuda.synchronize()
+                    ms = list(pl.plaid_get_stage_ms(idx).values())
+                    best = min(best, ms[3] + ms[4])  # candidates and stage-2 scores
+                pl.plaid_set_stage_timing(idx, False)
+                return best
+            few, many = stage2(9), stage2(64)
+            print(f"{form}: stage 2 {few:.4f} ms with 9 probes, {many:.4f} with 64")
+            # measured 1.4 times; walked list by list by every wave 2.5 times
+            assert many < 2 * few, (form, few, many)
+        finally:
+            pl.plaid_index_free(idx)
+            pl.plaid_index_free(stream)
