@@ -833,7 +833,7 @@ __global__ __launch_bounds__(64 * IV_WAVES) void s2_candidates_kernel(
 // Per wave sixteen passages at a time: the codes and the pruning bits of eight of them in flight, the surviving ones listed
 // in LDS, then eight rows per load instruction as in stage 3.  Bins are counted in LDS and added once per share.
 // 400 000 passages, one query: 4.1 ms per search with four waves per 2048 passages fetching two rows at a time, 15.6 with one,
-// 0.44 to 0.47 now; 64 queries 92, 117 and 17 to 19.
+// 0.40 now; 64 queries 92, 117 and 16.
 #define S2_GATHER_BLOCKS 768  // three per compute unit: what the 64-bit instances' LDS admits
 #define S2_GATHER_STRIDE 68   // of a passage's list: eight lanes that read one column of eight lists hit all banks
 struct S2GatherScratch {
@@ -879,7 +879,7 @@ __device__ __forceinline__ int64_t s2_lane64(int64_t v, int lane)
 }
 
 // Share j of nj of query q (all threads of the workgroup call this).
-__device__ void s2_gather_share(int q, int64_t j, int64_t nj, const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq,
+__device__ __forceinline__ void s2_gather_share(int q, int64_t j, int64_t nj, const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq,
                                 int uniq_stride, const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids,
                                 const uint32_t *__restrict__ table, int64_t nr, int shift, const float *__restrict__ S, int64_t C,
                                 const uint32_t *__restrict__ keepbits, int64_t keep_words, const int32_t *__restrict__ codes,
