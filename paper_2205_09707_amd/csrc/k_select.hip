@@ -96,9 +96,13 @@ __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int
     constexpr int PER = BINS > SEL_THREADS ? BINS / SEL_THREADS : 1;
     int32_t loc[PER];
     int32_t sum = 0;
+    // (no condition where every thread has bins: with one per bin the loads, two of 16 bytes, became eight of 4 bytes, each
+    // behind a branch, and the boundary pass of 2048 lists of 65536 keys took 427 us for 327)
+    const bool has_bins = BINS >= SEL_THREADS || (int)threadIdx.x < BINS;
+#pragma unroll
     for (int j = 0; j < PER; ++j) {
         loc[j] = 0;
-        if ((int)threadIdx.x * PER + j < BINS)
+        if (has_bins)
 #pragma unroll
             for (int c = 0; c < COPIES; ++c) loc[j] += gh[c * BINS + threadIdx.x * PER + j];
         sum += loc[j];

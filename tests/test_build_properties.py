@@ -72,3 +72,13 @@ def test_hot_kernels_do_not_spill(tmp_path):
         assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0, f"{name} spills: {m}"
         assert m["vgpr_count"] + m["agpr_count"] <= max_vgpr, f"{name}: {m['vgpr_count']} + {m['agpr_count']} registers"
         assert m["group_segment_fixed_size"] <= max_lds, f"{name}: {m['group_segment_fixed_size']} bytes of LDS"
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+def test_boundary_search_reads_its_histogram_in_16_byte_pieces(tmp_path):
+    """find_boundary opens every workgroup of the level kernels: eight bins per thread, two loads and no branch about them."""
+    text = _assembly("k_select.hip", str(tmp_path / "k_select.s"))
+    for level in (0, 1):
+        body = re.search(r"^_Z16sel_level_kernelILi%dE.*?s_barrier" % level, text, re.M | re.S).group(0)
+        assert len(re.findall(r"global_load_dwordx4", body)) == 2, body
+        assert "global_load_dword " not in body and "s_cbranch" not in body, body
