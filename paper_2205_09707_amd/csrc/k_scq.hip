@@ -108,6 +108,34 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
 // of 128 floats the 32 tokens' reads fall into one bank group, and the table took 12 of the kernel's 31 us for one query.
 #define TAIL_QSTRIDE (DIM + 4)
 #define TX_STRIDE 33  // floats per row of the survivors' entries in LDS: walks along rows and along columns hit all banks
+// Largest, smallest and `rank`-th largest (the smallest, when there are fewer) of column `tid` of the K rows, to colmm.
+#define SCQ_BASE_FIRST 30  // survivors from which on the rank is (K + 6) / 9 = 4 .. 7
+static_assert((S2_MAX_KEPT + 6) / 9 <= 7 && (SCQ_BASE_FIRST + 6) / 9 == 4, "the ranks are 3 .. 7");
+template <int N>
+__device__ __forceinline__ void scq_column_bounds(const float *Tx, int K, int rank, int tid, float *colmm /*[3][32]*/)
+{
+    float t[N], mn = INFINITY;
+#pragma unroll
+    for (int k = 0; k < N; ++k) t[k] = -INFINITY;
+#pragma unroll 4
+    for (int s = 0; s < K; ++s) {
+        float v = Tx[s * TX_STRIDE + tid];
+        mn = fminf(mn, v);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const float a = fminf(t[k], v);
+            t[k] = fmaxf(t[k], v);
+            v = a;
+        }
+    }
+    float base = t[2];
+#pragma unroll
+    for (int k = 3; k < N; ++k) base = rank > k ? t[k] : base;
+    colmm[tid] = t[0];
+    colmm[QLEN + tid] = mn;
+    colmm[2 * QLEN + tid] = K >= 3 ? base : mn;
+}
+
 // Survivor table of one query (runs in one workgroup, all of whose threads call it).  K = number of centroids
 // passing Eq. 5; when K <= S2_MAX_KEPT their ids are listed ascending, their rows copied to T (slot s at T[s],
 // s = 1..K), a collision-free hash shift is chosen for stage 2's table, and bin_hi / bin_scale are set from bounds
@@ -208,26 +236,17 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
         }
         if (tid < K) kept_ids_q[tid] = ids[tid];
         __syncthreads();
-        // Per query token: bounds of the rows for the bins, and the third largest entry as the base of the additive bound
+        // Per query token: bounds of the rows for the bins, and the base of the additive bound
         // score(bag) <= sum_i base_i + sum over the members of sum_i max(0, row_i - base_i): true for any base, and tight
-        // for one that only a token's own centroid (and perhaps one more) exceeds.  With the third largest entry the
-        // passages whose bound reaches the ndocs-th best score are 1.5 to 5 times ndocs on the synthetic collections; the
-        // second largest leaves up to ten times as many at 262144 centroids, the fifth three times as many at 65536.
+        // for one that only a token's own centroid (and perhaps one more) exceeds.  That is the third largest entry of some
+        // twenty-five rows, but every further row is one more that may exceed it by chance, so that the
+        // rank grows with their number, by one in nine.  Passages whose bound reaches the ndocs-th best score, as a multiple of ndocs, with the
+        // third / fifth / sixth largest entry (400 000 passages, 65536 centroids, ndocs 1024): 4.1 / 9.8 / 14 with 24..29
+        // survivors, 15 / 4.2 / 6.6 with 42..47, 56 / 7.6 / 5.6 with 54..59.  Stage 2 of one query with 58 survivors took
+        // 119 to 184 us with the third, 82 to 100 with this; 64 queries with 36 to 66 each 693 -> 356.
         if (tid < QLEN) {
-            float t0 = -INFINITY, t1 = -INFINITY, t2 = -INFINITY, mn = INFINITY;
-#pragma unroll 4
-            for (int s = 0; s < K; ++s) {
-                const float v = Tx[s * TX_STRIDE + tid];
-                const float a = fminf(t0, v);
-                t0 = fmaxf(t0, v);
-                const float b = fminf(t1, a);
-                t1 = fmaxf(t1, a);
-                t2 = fmaxf(t2, b);
-                mn = fminf(mn, v);
-            }
-            colmm[tid] = t0;
-            colmm[QLEN + tid] = mn;
-            colmm[2 * QLEN + tid] = K >= 3 ? t2 : mn;
+            if (K < SCQ_BASE_FIRST) scq_column_bounds<3>(Tx, K, 3, tid, colmm);
+            else scq_column_bounds<7>(Tx, K, (K + 6) / 9, tid, colmm);
         }
         __syncthreads();
         if (tid < 64 && K > 0) {  // one wave, lane = slot
