@@ -1019,7 +1019,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
 {
     constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
     // Planes of 64 words that fit a wave's area: what lets four (32-bit sets, coarse tables) or three workgroups share a
-    // compute unit.  A query with more slots takes half or a quarter of the passages at a time.
+    // compute unit.  A query with more of them takes two waves' area for one wave where the launch has workgroups to spare
+    // (mode bit 5), otherwise half or a quarter of the passages at a time.
     constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 36 : 24);
     static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
     constexpr int SLOTS = KMAX + 1;
@@ -1039,7 +1040,6 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     static_assert(S2_COARSE == 128, "two 16-bit coarse counts per lane");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = s2_uniform(tid >> 6);
-    uint32_t *area = area_all[wave];
     uint32_t *lstart = lstart_all[wave];
     uint32_t *lcnt = lcnt_all[wave];
     uint32_t *lcand = lcand_all[wave];
@@ -1091,6 +1091,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         const int K_all = s2_uniform(mt.K);
         if (!take_all && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
         if (K_all > KMAX) continue;  // (a single query of the gather form)
+        if (K_all <= FULL_PLANES && (int64_t)rb * IV_WAVES * steps >= (P + (1ll << len_log) - 1) >> len_log) continue;  // spare
         const int K = K_all;
         const int nu = n_uniq[q];
         __syncthreads();  // the previous query's readers are done
@@ -1137,8 +1138,10 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         const uint32_t pm0 = s2_uniform((int)probed_mask[0]), pm1 = s2_uniform((int)probed_mask[1]);
         const int n_rows = s2_uniform(n_front[0]), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
         const int n_sp = s2_uniform(n_front[1]);
+        const bool two_areas = (mode & 32) && n_ss > FULL_PLANES;
+        uint32_t *area = two_areas ? area_all[(2 * wave) % IV_WAVES] : area_all[wave];
         int my_log = len_log;
-        while ((n_ss << (my_log - 5)) > FULL_PLANES * 64) --my_log;
+        while ((n_ss << (my_log - 5)) > (two_areas ? 2 : 1) * FULL_PLANES * 64) --my_log;
         const int len = 1 << my_log, nw = len >> 5;
         // lane i: the i-th slot with a bitmap and its row / the i-th slot without one and its centroid
         const int dense_slot = lane < n_dense ? order[lane] : 0, dense_row = lane < n_dense ? drow[dense_slot] : 0;
@@ -1148,8 +1151,9 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         uint32_t *ebq = emptybits + (int64_t)q * cand_words;
         int32_t *hist_q = hist + (int64_t)q * SEL_BINS;
         int32_t *coarse_q = hist_q + ((mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0) * S2_COARSE;
-        const int64_t first = ((int64_t)(rb * IV_WAVES + wave) * steps) << len_log;
-        const int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
+        const int64_t first = ((int64_t)(rb * (two_areas ? IV_WAVES / 2 : IV_WAVES) + wave) * steps) << len_log;
+        int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
+        if (two_areas && wave >= IV_WAVES / 2) last = first;  // its area is lent
         const int lane0 = lane;
         for (int64_t p0 = first; p0 < last; p0 += len) {  // uniform
             int lane = lane0;
@@ -1519,35 +1523,42 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
     const int64_t words = (nq * cand_words + 7) & ~7ll;
     const unsigned gather = words < S2_GATHER_BLOCKS ? (unsigned)words : S2_GATHER_BLOCKS;
-#define S2_INVERT(SH_, T_, MODE_, NQX_)                                                                                     \
-    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)(blocks * (NQX_)) + (sizeof(T_) == 8 ? gather : 0u)),     \
+#define S2_INVERT(SH_, T_, MODE_, NQX_, BLOCKS_)                                                                                     \
+    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (sizeof(T_) == 8 ? gather : 0u)),     \
                        dim3(64 * IV_WAVES), 0, st, uniq,                                                                      \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
                        P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.state,         \
                         b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
-                       steps, m, first_batch, (unsigned)(blocks * (NQX_)))
+                       steps, m, first_batch, (unsigned)((BLOCKS_) * (NQX_)))
     // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
     // updates alone).  Workgroups are dealt to the eight XCDs in turn, so with a multiple of eight queries per passage
     // range (empty ones added) a query's workgroups share an XCD; where that would leave much of the chip without
-    // work, every XCD of a large launch counts, and prunes by, a copy of its own (mode bit 3).
+    // work (seven queries and a spare XCD: 2 M passages 311 -> 166 us), every XCD of a large launch counts, and prunes by, a copy of its own (mode bit 3).
     const int padded = (nq + 7) & ~7;
-    const bool pad = 4 * padded <= 5 * nq;
+    const bool pad = nq >= 8 && 4 * padded <= 5 * nq;
     const int nqx = pad ? padded : nq;
     const int own = (!pad && nq * blocks > 64 ? 8 : 0) | given;
-    if (nq < 8) {
-        // a few queries: the 64-bit instance alone, taking every query (same sets, same scores, one launch less)
-        const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own;
-        if (shift == 11) S2_INVERT(11, unsigned long long, mode, nqx);
-        else S2_INVERT(13, unsigned long long, mode, nqx);
+    // Few workgroups, at most the three per compute unit that the 64-bit instance's LDS admits: that instance alone, taking
+    // every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
+    // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
+    // 65 / 70); with twice the workgroups,
+    // so that queries with more slots than a wave's area holds can have two (mode bit 5).  More: the 32-bit
+    // instance's scoring and its fourth workgroup per compute unit win (eight of 2 M: 232 with two, 327 with one).
+    const bool fits = blocks * nqx <= S2_GATHER_BLOCKS;
+    if (nq < 8 || fits) {
+        const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0);
+        const int64_t all = fits ? 2 * blocks : blocks;
+        if (shift == 11) S2_INVERT(11, unsigned long long, mode, nqx, all);
+        else S2_INVERT(13, unsigned long long, mode, nqx, all);
     } else {
         // the class of the 64-bit instance is empty or small more often than not: 128 columns of workgroups share it
         const int many = nqx < 128 ? nqx : 128;
         if (shift == 11) {
-            S2_INVERT(11, uint32_t, wide | own, nqx);
-            S2_INVERT(11, unsigned long long, wide | own, many);
+            S2_INVERT(11, uint32_t, wide | own, nqx, blocks);
+            S2_INVERT(11, unsigned long long, wide | own, many, blocks);
         } else {
-            S2_INVERT(13, uint32_t, wide | own, nqx);
-            S2_INVERT(13, unsigned long long, wide | own, many);
+            S2_INVERT(13, uint32_t, wide | own, nqx, blocks);
+            S2_INVERT(13, unsigned long long, wide | own, many, blocks);
         }
     }
 #undef S2_INVERT

@@ -159,3 +159,24 @@ def test_survivors_up_to_63_cost_little_more_than_a_few(monkeypatch):
         assert ms[58] < 1.9 * ms[26], ms
     finally:
         pl.plaid_index_free(idx)
+
+
+def test_a_launch_of_a_few_more_queries(monkeypatch):
+    """Stage 2 of seven queries of many short passages costs about what six cost, of eight with 40 survivors about seven."""
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    idx, Q = _index(monkeypatch, pl, 65536, 2_000_000, 4, 8, "inverted13")
+    try:
+        six, seven = (_stage2_ms(pl, idx, Q[:n].contiguous(), 2, 0.5, 1000) for n in (6, 7))
+        print(f"2 M passages: six {six:.4f} ms, seven {seven:.4f}")
+        assert seven < 1.4 * six, (six, seven)
+    finally:
+        pl.plaid_index_free(idx)
+    idx, Q, cen = _index(monkeypatch, pl, 16384, 200_000, 60, 9, "inverted11", centroids=True)
+    try:
+        t_cs = sorted(_thresholds(cen, Q[:8], 40))[4]
+        seven, eight = (_stage2_ms(pl, idx, Q[:n].contiguous(), 2, t_cs, 256) for n in (7, 8))
+        print(f"200 000 passages: seven {seven:.4f} ms, eight {eight:.4f}")
+        assert eight < 1.35 * seven, (seven, eight)
+    finally:
+        pl.plaid_index_free(idx)
