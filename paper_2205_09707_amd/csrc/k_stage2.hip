@@ -1335,7 +1335,23 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             for (int round = 0; __any(left != 0u); ++round) {  // (no round: no candidate with a surviving centroid)
                 s2_opaque(lane);
                 // at least m scores lie in coarse bins 0 .. b: a bound in a worse bin needs no score
-                const int2 c = round == 0 ? known : s2_coarse_load(coarse_q, lane);
+                int2 c = known;
+                if (round > 0) {
+                    // the copies of all XCDs: one alone knows of an eighth of the query's scores, and a threshold from it
+                    // lets through up to eight times as many
+                    int2 v[S2_COPIES];
+#pragma unroll
+                    for (int x = 0; x < S2_COPIES; ++x) {
+                        v[x] = make_int2(0, 0);
+                        if (x == 0 || (mode & 8)) v[x] = s2_coarse_load(hist_q + x * S2_COARSE, lane);
+                    }
+                    c = v[0];
+#pragma unroll
+                    for (int x = 1; x < S2_COPIES; ++x) {
+                        c.x += v[x].x;
+                        c.y += v[x].y;
+                    }
+                }
                 const int incl = s2_wave_scan(c.x + c.y);
                 const unsigned long long enough0 = __ballot(incl - c.y >= m), enough1 = __ballot(incl >= m);
                 if (enough1) {
@@ -1531,13 +1547,17 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                         b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
                        steps, m, first_batch, (unsigned)((BLOCKS_) * (NQX_)))
     // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
-    // updates alone).  Workgroups are dealt to the eight XCDs in turn, so with a multiple of eight queries per passage
-    // range (empty ones added) a query's workgroups share an XCD; where that would leave much of the chip without
-    // work (seven queries and a spare XCD: 2 M passages 311 -> 166 us), every XCD of a large launch counts, and prunes by, a copy of its own (mode bit 3).
-    const int padded = (nq + 7) & ~7;
-    const bool pad = nq >= 8 && 4 * padded <= 5 * nq;
-    const int nqx = pad ? padded : nq;
-    const int own = (!pad && nq * blocks > 64 ? 8 : 0) | given;
+    // updates alone).  Workgroups are dealt to the eight XCDs in turn: with many queries their number, per passage range,
+    // is made a multiple of eight (empty ones added), so that a query's workgroups share an XCD.  With few, that would
+    // leave XCDs and, in the end, most of the chip waiting for the query with the most to do: an odd number spreads
+    // every query over all XCDs, each of which counts in a copy of its own (mode bit 3) and reads the others' once it has
+    // scored its first batch.  Stage 2 and selection, us, multiple of eight / spread, copies read singly / all:
+    //   7 and 8 queries of 2 M passages (65536 centroids)   311 / 202 / 172    219 / 232 / 166
+    //   8, 16, 32 queries of 8.8 M                          1000, 1360, 2350 / - / 600, 950, 1710
+    //   40, 64 of 400 000                                   139, 187 / - / 141, 191      of 2 M: 403, 552 / - / 451, 622
+    const bool spread = nq <= 32;
+    const int nqx = spread ? (nq | 1) : (nq + 7) & ~7;
+    const int own = (spread && nq * blocks > 64 ? 8 : 0) | given;
     // Few workgroups, at most the three per compute unit that the 64-bit instance's LDS admits: that instance alone, taking
     // every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
     // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->

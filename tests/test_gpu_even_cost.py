@@ -180,3 +180,20 @@ def test_a_launch_of_a_few_more_queries(monkeypatch):
         assert eight < 1.35 * seven, (seven, eight)
     finally:
         pl.plaid_index_free(idx)
+
+
+def test_seven_queries_learn_the_threshold_like_one(monkeypatch):
+    """Stage 2 prunes by the scores of all workgroups of a query: a small batch, each query of which runs on several XCDs,
+    takes little longer than one of its queries."""
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    idx, Q, cen = _index(monkeypatch, pl, 16384, 400_000, 60, 7, "inverted11", centroids=True)
+    try:
+        for K in (26, 40):
+            t_cs = sorted(_thresholds(cen, Q[:8], K))[4]
+            one, seven = sum(_stage2_ms(pl, idx, Q[i:i + 1].contiguous(), 2, t_cs, 1000) for i in range(7)) / 7, \
+                _stage2_ms(pl, idx, Q[:7].contiguous(), 2, t_cs, 1000)
+            print(f"{K} survivors: one {one:.4f} ms, seven {seven:.4f}")
+            assert seven < 2 * one, (K, one, seven)
+    finally:
+        pl.plaid_index_free(idx)
