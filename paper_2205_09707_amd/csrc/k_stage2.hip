@@ -1024,6 +1024,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 36 : 24);
     static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
     constexpr int SLOTS = KMAX + 1;
+    constexpr int MORE = SHIFT == 11 ? 2 : 4;  // loads in flight per lane of a long list (of a coarse column: four times as long)
     __shared__ __align__(16) uint32_t area_all[IV_WAVES][FULL_PLANES * 64];
     __shared__ __align__(16) float Tl[KMAX * QLEN];
     __shared__ float rowsum[SLOTS];
@@ -1280,13 +1281,13 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                         if (sub < n[u]) apply(pid[u], sl[u]);
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
-                        for (int x = 16 + sub; x < n[u]; x += 32) {
-                            uint32_t more[2];
+                        for (int x = 16 + sub; x < n[u]; x += 16 * MORE) {
+                            uint32_t more[MORE];
 #pragma unroll
-                            for (int y = 0; y < 2; ++y)
+                            for (int y = 0; y < MORE; ++y)
                                 if (x + 16 * y < n[u]) more[y] = (uint32_t)src[u][x + 16 * y];
 #pragma unroll
-                            for (int y = 0; y < 2; ++y)
+                            for (int y = 0; y < MORE; ++y)
                                 if (x + 16 * y < n[u]) apply(more[y], sl[u]);
                         }
                 }
@@ -1528,13 +1529,17 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     int len_log = 11;
     if (ranges <= 40)
         while (len_log > 7 && (ranges << (12 - len_log)) <= 128 && (waves << (12 - len_log)) <= 2560) --len_log;
+    // An ndocs so large that a wave has several batches to score in any case (one query of 400 000 passages, ndocs 100 000:
+    // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
+    // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
+    while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 ? 2 : 1);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
     // Passages a wave scores before there is a threshold: all waves of a query together about eight times the m that make
-    // one, between 32 (fewer leave lanes idle) and 64 (more are scored, and counted, for nothing).
-    const int64_t per_query = (P + (1ll << len_log) - 1) >> len_log;
-    const int64_t fb = 8ll * m / per_query;
-    const int first_batch = fb < 32 ? 32 : (fb > 64 ? 64 : (int)fb);
+    // one, between 32 (fewer leave lanes idle) and 64 (more are scored, and counted, for nothing) -- or their share of m,
+    // which has to be scored whatever the bounds say.
+    const int64_t share = ((int64_t)m << len_log) / P, fb = 8 * share < 64 ? 8 * share : 64;
+    const int first_batch = (int)(share > fb ? share : (fb > 32 ? fb : 32));
     const int64_t blocks = (P + per_block - 1) / per_block;
     // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
     const int64_t words = (nq * cand_words + 7) & ~7ll;

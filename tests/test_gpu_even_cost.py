@@ -197,3 +197,18 @@ def test_seven_queries_learn_the_threshold_like_one(monkeypatch):
             assert seven < 2 * one, (K, one, seven)
     finally:
         pl.plaid_index_free(idx)
+
+
+def test_stage2_that_keeps_every_passage(monkeypatch):
+    """With an ndocs no passage can fail there is nothing to prune: every wave scores what it has at once."""
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    P = 400_000
+    idx, Q = _index(monkeypatch, pl, 16384, P, 60, 7, "inverted11")
+    try:
+        q = Q[:1].contiguous()
+        few, every = _stage2_ms(pl, idx, q, 2, 0.6, 1000), _stage2_ms(pl, idx, q, 2, 0.6, P)
+        print(f"ndocs 1000: {few:.4f} ms, all passages: {every:.4f}")
+        assert every < 2.5 * few, (few, every)
+    finally:
+        pl.plaid_index_free(idx)
