@@ -1005,7 +1005,8 @@ __device__ __forceinline__ void s2_gather_share(int q, int64_t j, int64_t nj, co
 
 // SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
 // the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
-template <int SHIFT, typename SetT>
+// PLAIN: no copies of the histogram and no candidate words given (large batches; the two cost the kernel 2 % there).
+template <int SHIFT, typename SetT, bool PLAIN>
 __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4 : 3) void s2_invert_kernel(
     const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride,
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
@@ -1044,7 +1045,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     uint32_t *lstart = lstart_all[wave];
     uint32_t *lcnt = lcnt_all[wave];
     uint32_t *lcand = lcand_all[wave];
-    const bool given = mode & 16;  // s2_candidates_kernel has written the candidate words
+    const bool given = !PLAIN && (mode & 16);  // s2_candidates_kernel has written the candidate words
     if constexpr (sizeof(SetT) == 8) {
         if (blockIdx.x >= main_blocks) {  // uniform: a workgroup of the gather form
             static_assert(sizeof(S2GatherScratch) <= sizeof(area_all), "the gather form's arrays take the place of the planes");
@@ -1092,7 +1093,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         const int K_all = s2_uniform(mt.K);
         if (!take_all && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
         if (K_all > KMAX) continue;  // (a single query of the gather form)
-        if (K_all <= FULL_PLANES && (int64_t)rb * IV_WAVES * steps >= (P + (1ll << len_log) - 1) >> len_log) continue;  // spare
+        if (KMAX > FULL_PLANES && K_all <= FULL_PLANES && (int64_t)rb * IV_WAVES * steps >= (P + (1ll << len_log) - 1) >> len_log) continue;  // spare
         const int K = K_all;
         const int nu = n_uniq[q];
         __syncthreads();  // the previous query's readers are done
@@ -1139,10 +1140,10 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         const uint32_t pm0 = s2_uniform((int)probed_mask[0]), pm1 = s2_uniform((int)probed_mask[1]);
         const int n_rows = s2_uniform(n_front[0]), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
         const int n_sp = s2_uniform(n_front[1]);
-        const bool two_areas = (mode & 32) && n_ss > FULL_PLANES;
+        const bool two_areas = KMAX > FULL_PLANES && (mode & 32) && n_ss > FULL_PLANES;
         uint32_t *area = two_areas ? area_all[(2 * wave) % IV_WAVES] : area_all[wave];
         int my_log = len_log;
-        while ((n_ss << (my_log - 5)) > (two_areas ? 2 : 1) * FULL_PLANES * 64) --my_log;
+        while (KMAX > FULL_PLANES && (n_ss << (my_log - 5)) > (two_areas ? 2 : 1) * FULL_PLANES * 64) --my_log;
         const int len = 1 << my_log, nw = len >> 5;
         // lane i: the i-th slot with a bitmap and its row / the i-th slot without one and its centroid
         const int dense_slot = lane < n_dense ? order[lane] : 0, dense_row = lane < n_dense ? drow[dense_slot] : 0;
@@ -1151,7 +1152,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         uint32_t *cbq = candbits + (int64_t)q * cand_words;
         uint32_t *ebq = emptybits + (int64_t)q * cand_words;
         int32_t *hist_q = hist + (int64_t)q * SEL_BINS;
-        int32_t *coarse_q = hist_q + ((mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0) * S2_COARSE;
+        int32_t *coarse_q = hist_q + (!PLAIN && (mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0) * S2_COARSE;
         const int64_t first = ((int64_t)(rb * (two_areas ? IV_WAVES / 2 : IV_WAVES) + wave) * steps) << len_log;
         int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
         if (two_areas && wave >= IV_WAVES / 2) last = first;  // its area is lent
@@ -1340,17 +1341,16 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                 if (round > 0) {
                     // the copies of all XCDs: one alone knows of an eighth of the query's scores, and a threshold from it
                     // lets through up to eight times as many
-                    int2 v[S2_COPIES];
+                    c = s2_coarse_load(hist_q, lane);
+                    if (!PLAIN && (mode & 8)) {  // uniform
+                        int2 v[S2_COPIES];
 #pragma unroll
-                    for (int x = 0; x < S2_COPIES; ++x) {
-                        v[x] = make_int2(0, 0);
-                        if (x == 0 || (mode & 8)) v[x] = s2_coarse_load(hist_q + x * S2_COARSE, lane);
-                    }
-                    c = v[0];
+                        for (int x = 1; x < S2_COPIES; ++x) v[x] = s2_coarse_load(hist_q + x * S2_COARSE, lane);
 #pragma unroll
-                    for (int x = 1; x < S2_COPIES; ++x) {
-                        c.x += v[x].x;
-                        c.y += v[x].y;
+                        for (int x = 1; x < S2_COPIES; ++x) {
+                            c.x += v[x].x;
+                            c.y += v[x].y;
+                        }
                     }
                 }
                 const int incl = s2_wave_scan(c.x + c.y);
@@ -1544,8 +1544,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
     const int64_t words = (nq * cand_words + 7) & ~7ll;
     const unsigned gather = words < S2_GATHER_BLOCKS ? (unsigned)words : S2_GATHER_BLOCKS;
-#define S2_INVERT(SH_, T_, MODE_, NQX_, BLOCKS_)                                                                                     \
-    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (sizeof(T_) == 8 ? gather : 0u)),     \
+#define S2_INVERT(SH_, T_, PLAIN_, MODE_, NQX_, BLOCKS_)                                                                                     \
+    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_, PLAIN_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (sizeof(T_) == 8 ? gather : 0u)),     \
                        dim3(64 * IV_WAVES), 0, st, uniq,                                                                      \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
                        P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.state,         \
@@ -1573,17 +1573,19 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     if (nq < 8 || fits) {
         const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0);
         const int64_t all = fits ? 2 * blocks : blocks;
-        if (shift == 11) S2_INVERT(11, unsigned long long, mode, nqx, all);
-        else S2_INVERT(13, unsigned long long, mode, nqx, all);
+        if (shift == 11) S2_INVERT(11, unsigned long long, false, mode, nqx, all);
+        else S2_INVERT(13, unsigned long long, false, mode, nqx, all);
     } else {
         // the class of the 64-bit instance is empty or small more often than not: 128 columns of workgroups share it
         const int many = nqx < 128 ? nqx : 128;
         if (shift == 11) {
-            S2_INVERT(11, uint32_t, wide | own, nqx, blocks);
-            S2_INVERT(11, unsigned long long, wide | own, many, blocks);
+            if (own) S2_INVERT(11, uint32_t, false, wide | own, nqx, blocks);
+            else S2_INVERT(11, uint32_t, true, wide, nqx, blocks);
+            S2_INVERT(11, unsigned long long, false, wide | own, many, blocks);
         } else {
-            S2_INVERT(13, uint32_t, wide | own, nqx, blocks);
-            S2_INVERT(13, unsigned long long, wide | own, many, blocks);
+            if (own) S2_INVERT(13, uint32_t, false, wide | own, nqx, blocks);
+            else S2_INVERT(13, uint32_t, true, wide, nqx, blocks);
+            S2_INVERT(13, unsigned long long, false, wide | own, many, blocks);
         }
     }
 #undef S2_INVERT

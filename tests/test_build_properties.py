@@ -21,10 +21,14 @@ KERNELS = {
     "stage1_tail_kernelILi2ELb1E": ("k_scq.hip", 128, 64 << 10),   # ... also with the re-evaluations in double
     "stage1_tail_kernelILi8ELb1E": ("k_scq.hip", 128, 64 << 10),
     "scq16_kernelILi2ELb1E": ("k_scq16.hip", 256, 40 << 10),       # two waves per SIMD, two to four workgroups per CU
-    "s2_invert_kernelILi11EjE": ("k_stage2.hip", 168, 53 << 10),   # 2048 passages per workgroup, three workgroups (of four waves) per CU
-    "s2_invert_kernelILi11EyE": ("k_stage2.hip", 168, 53 << 10),
-    "s2_invert_kernelILi13EjE": ("k_stage2.hip", 128, 80 << 10),   # 8192 passages, 1024 threads, 32-bit sets: two per CU
-    "s2_invert_kernelILi13EyE": ("k_stage2.hip", 128, 100 << 10),  # ... 64-bit sets: one per CU
+    # a wave per 2048 passages, 256 threads: what the workgroups per compute unit that its launch bounds name can have
+    "s2_invert_kernelILi11EjLb0E": ("k_stage2.hip", 128, 40 << 10),   # 32-bit sets: four
+    "s2_invert_kernelILi11EjLb1E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi13EjLb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi13EjLb1E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi11EyLb0E": ("k_stage2.hip", 168, 53 << 10),   # 64-bit sets: three
+    "s2_invert_kernelILi13EyLb0E": ("k_stage2.hip", 128, 40 << 10),   # ... with coarse table columns: four
+    "s2_candidates_kernel": ("k_stage2.hip", 64, 8 << 10),
     "s2_union_wide_kernel": ("k_stage2.hip", 128, 80 << 10),       # two workgroups of 1024 threads per CU
     "s2_stream_kernel": ("k_stage2.hip", 128, 40 << 10),
     "ci_list_kernelILb0E": ("k_ci.hip", 96, 8 << 10),              # five waves per SIMD; wave-private LDS areas
