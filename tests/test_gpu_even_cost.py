@@ -42,8 +42,8 @@ def test_assignment_with_every_centroid_twice_in_a_row(C):
     assert tied < 10 * plain, (tied, plain)
 
 
-def _index(monkeypatch, pl, C, P, length, seed, form, centroids=False):
-    """An index of random passages (Zipf-like centroid popularity, residuals of one bucket) and 64 queries near centroids."""
+def _index(monkeypatch, pl, C, P, length, seed, form, centroids=False, nq=64):
+    """An index of random passages (Zipf-like centroid popularity, residuals of one bucket) and nq queries near centroids."""
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
@@ -53,12 +53,12 @@ def _index(monkeypatch, pl, C, P, length, seed, form, centroids=False):
     arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
               "residuals": torch.randint(0, 256, (P * length, 32), generator=g, device="cuda", dtype=torch.uint8),
               "bucket_weights": torch.tensor([-0.05, -0.015, 0.015, 0.05], device="cuda")}
-    near = cen[(C * torch.rand(64 * 32, generator=g, device="cuda") ** 3).long().clamp_(max=C - 1)]
-    Q = torch.nn.functional.normalize(near + 0.03 * torch.randn(64 * 32, 128, generator=g, device="cuda"), dim=1)
+    near = cen[(C * torch.rand(nq * 32, generator=g, device="cuda") ** 3).long().clamp_(max=C - 1)]
+    Q = torch.nn.functional.normalize(near + 0.03 * torch.randn(nq * 32, 128, generator=g, device="cuda"), dim=1)
     with monkeypatch.context() as mp:
         mp.setenv("PLAID_STAGE2_FORM", form)
         idx = pl.plaid_index_from_view(arrays, 2, device=0, copy=False)
-    Q = Q.reshape(64, 32, 128).contiguous()
+    Q = Q.reshape(nq, 32, 128).contiguous()
     return (idx, Q, cen) if centroids else (idx, Q)
 
 
