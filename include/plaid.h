@@ -247,8 +247,8 @@ int plaid_workspace_bytes(int64_t C, int64_t P, int32_t nq, int32_t nprobe, int3
 
 /* Nearest centroid of each vector (Section 3.1: a token is stored with the id of its closest centroid):
  * codes[j] = the centroid with the largest dot product centroids[c] . x[j], the dot products accumulated in double over
- * the dimensions in index order and rounded once to fp32, exactly as S_cq of Eq. 2 is (the same kernel computes them,
- * 32 vectors at a time); among equal scores the smaller id wins.
+ * the dimensions in index order and rounded once to fp32, exactly as S_cq of Eq. 2 is (a screening in half
+ * precision with a proven error bound decides what it can, these dot products the rest); among equal scores the smaller id wins.
  *   centroids  [C][128] fp32, 16-byte aligned     x  [n][128] fp32, 16-byte aligned     codes  [n] int32 (output)
  * Errors: PLAID_EINVAL (null or misaligned pointers, sizes out of range), PLAID_ENOMEM, PLAID_EHIP. */
 int plaid_assign_centroids(const float *centroids, int64_t C, const float *x, int64_t n, int32_t *codes, int device,

@@ -137,8 +137,9 @@ __device__ __forceinline__ void scq_column_bounds(const float *Tx, int K, int ra
 }
 
 // Survivor table of one query (runs in one workgroup, all of whose threads call it).  K = number of centroids
-// passing Eq. 5; when K <= S2_MAX_KEPT their ids are listed ascending, their rows copied to T (slot s at T[s],
-// s = 1..K), a collision-free hash shift is chosen for stage 2's table, and bin_hi / bin_scale are set from bounds
+// passing Eq. 5; when K <= S2_MAX_KEPT their ids are listed by decreasing length of their inverted lists (without lists, and
+// among equals, ascending), their rows copied to T (slot s at T[s], s = 1..K), a collision-free hash shift is chosen for the
+// streaming form's table, the gains and the base of the additive score bound are set, and bin_hi / bin_scale from bounds
 // of any non-empty passage's pruned score.  top1[i] = best centroid of token i (gives the bounds when K is large).
 // APPROX (Sq comes from the split-fp16 kernel): the pruning bits were completed by this workgroup a moment ago with
 // atomics, so they are read past the first-level cache, and the rows of T are re-evaluated in double from the centroids
@@ -181,8 +182,8 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     __syncthreads();
     int K = misc[0];
     if (C > (1ll << 26) - 2 && K <= S2_MAX_KEPT) K = S2_MAX_KEPT + 1;  // ids must fit the 26-bit field of a table entry
-    // Slots in the order of decreasing inverted-list length (ties: smaller id first): the centroids most passages hold
-    // get the lowest slots, which stage 2 scores through a table of their subsets.
+    // Slots in one order, whatever order the ids were found in: by decreasing inverted-list length, ties by id, so that a
+    // query's gains are the same each time.  Stage 2 needs no particular order.
     if (K > 1 && K <= S2_MAX_KEPT) {
         int32_t my_id = 0;
         int rank = 0;

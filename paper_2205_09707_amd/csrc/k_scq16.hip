@@ -273,8 +273,7 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], c
 // arrived), and those of q + 2 are requested.  Scores: the results of query q leave the accumulators (scaled, reduced
 // for the tile maxima and the pruning words) into registers of their own, and their stores are issued between the
 // matrix instructions of query q + 1, a few per step, so that the store stream and the matrix pipe run side by side.
-// STORE: always true (the scores are written; the name of the instance is what the resource checks look for).
-template <int NT, bool STORE>
+template <int NT>
 __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     const scq16_half8 *__restrict__ A16, int64_t C, const scq16_half8 *__restrict__ B16, int nq, int qg, float t_lo, float t_hi,
     float *__restrict__ S, uint32_t *__restrict__ keepbits, uint32_t *__restrict__ ambbits, int64_t keep_words,
@@ -372,6 +371,6 @@ void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *
     if (qg > 64) qg = 64;
     if (qg > nq) qg = nq;
     const unsigned gy = (unsigned)((nq + qg - 1) / qg);
-    hipLaunchKernelGGL((scq16_kernel<H16_NT, true>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
+    hipLaunchKernelGGL((scq16_kernel<H16_NT>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
                        (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, clocks);
 }

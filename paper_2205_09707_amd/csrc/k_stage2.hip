@@ -1,29 +1,27 @@
 // Stage 2: centroid interaction with centroid pruning (Eq. 3-5) over every candidate passage.
 //
-// A passage's pruned score is sum_i max_j S_cq[code_j][i] over its tokens whose centroid passes
-// Eq. 5, so it depends only on WHICH surviving centroids occur in the passage.  Few centroids
-// survive t_cs (a small tail of high scores, Section 3.4), so the work splits in two:
+// A passage's pruned score is sum_i max_j S_cq[code_j][i] over its tokens whose centroid passes Eq. 5, so it depends only on
+// WHICH surviving centroids occur in the passage.  Few centroids survive t_cs (a small tail of high scores, Section 3.4), so
+// the work splits in two: find every passage's set of surviving centroids, then take the column maxima of the rows the set
+// names (rows staged in LDS) and sum the 32 maxima in double, in index order.  No matrix D~ is ever stacked
+// (Section 4.5's padding-free idea), nothing is padded, and the order-independent max plus the fixed-order sum make a
+// score a pure function of the passage.  There are two forms:
 //
-//   streaming part   the candidates' token codes are read once, coalesced, straight from HBM
-//                    (128-byte lines that no candidate touches are skipped); each code is looked
-//                    up in a small LDS table of the K surviving centroids and turned into a slot
-//                    number; one lane per passage then folds its slots into a K-bit set;
-//   scoring part     the lane takes the column maxima of the <= K surviving rows named by the
-//                    set (rows staged in LDS) and sums the 32 maxima in double, in index order.
+//   streaming   the candidates' token codes are read once, coalesced, straight from HBM (128-byte lines that no candidate
+//               touches are skipped); each code is looked up in a small LDS table of the K surviving centroids and turned
+//               into a slot number; one lane per passage folds its slots into a K-bit set and scores it.  Queries with
+//               more than S2_MAX_KEPT survivors (very low thresholds) take one wave per passage instead, which fetches the
+//               surviving rows from S_cq.  Output per query: the score word of candidate p at position p of its region
+//               (slots of non-candidates are neither written nor read), the fine histogram of the scores' bins, counted in
+//               LDS and added once per workgroup, and the bitmap of the candidates whose bag is empty (score -infinity;
+//               they rank last, in passage-id order).  No atomics with a return value on this path.
+//   inverted    candidates and sets follow from the inverted lists, and only passages whose score bound reaches the best
+//               ndocs so far are scored (see there).  Output per query: the keys of the scored candidates as a LIST, a
+//               wave's positions in which come from one returning atomic per round of up to 2048 passages, the coarse
+//               histogram of their bins, the candidate words and the bitmap of the empty bags.  Queries with more than
+//               S2_MAX_KEPT survivors are scored from their token codes and leave what the streaming form leaves.
 //
-// No matrix D~ is ever stacked (Section 4.5's padding-free idea), nothing is padded, and the
-// order-independent max plus the fixed-order sum make a score a pure function of the passage.
-// Queries with more than S2_MAX_KEPT surviving centroids (very low thresholds) take the gather
-// form instead: one wave per passage fetching surviving rows from the L2-resident S_cq.
-//
-// Output of either form, per query: slot p of the key array holds the ranking key of candidate p
-// when its bag is non-empty and the invalid key otherwise (slots of non-candidates are neither
-// written nor read), a histogram of the valid keys' bins for the selection that follows, and a
-// bitmap of the candidates whose bag is empty (score -infinity; they rank last, in passage-id
-// order).  A query without any surviving centroid skips all of this: its candidates are exactly
-// its empty-bag set.  No counters and no atomics with a return value on this path; a workgroup counts bins
-// in LDS and adds its non-zero bins to the query's histogram once, at its end, so that queries
-// whose passages all share one score (a single surviving centroid) do not queue up on one address.
+// A query without any surviving centroid skips all of this: its candidates are exactly its empty-bag set.
 #include "plaid_internal.h"
 
 #include <math.h>
@@ -36,7 +34,7 @@
 #define S2_TSTRIDE 36    // floats per staged S_cq row (16-byte aligned, rows spread over the banks)
 static_assert(S2_LBWORDS <= 64, "one lane clears one word of the line bitmap");
 
-// ------------------------------------------------------------------ gather form (K > S2_MAX_KEPT)
+// ------------------------------------------------------------------ gather form (K > S2_MAX_KEPT) of the streaming kernel
 // Pruned score of the passage with tokens [t0, t1): uniform across the wave; `any` tells whether a token survived.
 __device__ __forceinline__ float s2_gather_passage(const float *__restrict__ Sq, const uint32_t *__restrict__ kb,
                                                    int64_t t0, int64_t t1, const int32_t *__restrict__ codes, int lane,

@@ -20,7 +20,7 @@ KERNELS = {
     "stage1_tail_kernelILi8ELb0E": ("k_scq.hip", 128, 64 << 10),
     "stage1_tail_kernelILi2ELb1E": ("k_scq.hip", 128, 64 << 10),   # ... also with the re-evaluations in double
     "stage1_tail_kernelILi8ELb1E": ("k_scq.hip", 128, 64 << 10),
-    "scq16_kernelILi2ELb1E": ("k_scq16.hip", 256, 40 << 10),       # two waves per SIMD, two to four workgroups per CU
+    "scq16_kernelILi2E": ("k_scq16.hip", 256, 40 << 10),       # two waves per SIMD, two to four workgroups per CU
     # a wave per 2048 passages, 256 threads: what the workgroups per compute unit that its launch bounds name can have
     "s2_invert_kernelILi11EjLb0E": ("k_stage2.hip", 128, 40 << 10),   # 32-bit sets: four
     "s2_invert_kernelILi11EjLb1E": ("k_stage2.hip", 128, 40 << 10),
@@ -35,6 +35,16 @@ KERNELS = {
     "decompress_maxsim_kernelILi2ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD (query operands in LDS)
     "decompress_maxsim_kernelILi1ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
     "decompress_maxsim_kernelILi2ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),   # ... with unit-length reconstruction
+    "vanilla_prune_kernelILi2E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD
+    "vanilla_prune_kernelILi1E": ("k_stage4.hip", 168, 32 << 10),   # three
+    "decompress_dump_kernelILi2E": ("k_stage4.hip", 64, 8 << 10),
+    "passage_offsets_kernel": ("k_stage4.hip", 64, 1 << 10),
+    "van_codes_kernel": ("k_vanilla.hip", 64, 1 << 10),
+    "van_union_kernel": ("k_vanilla.hip", 64, 8 << 10),
+    "asg_screen_kernel": ("k_assign.hip", 256, 20 << 10),          # two waves per SIMD: 128 registers of operands, 64 of results
+    "asg_pick_kernel": ("k_assign.hip", 96, 32 << 10),             # five waves per SIMD, five workgroups per CU
+    "sel_pick_kernel": ("k_select.hip", 64, 80 << 10),             # 1024 threads, two workgroups per CU
+    "sel2_finish_kernel": ("k_select.hip", 64, 80 << 10),
     "sel_sort_kernelILi512E": ("k_select.hip", 64, 0),             # dynamic LDS only
     "sel2_filter_kernel": ("k_select.hip", 64, 8 << 10),
     "encode_residuals_kernelILi2E": ("k_build.hip", 64, 0),
