@@ -690,9 +690,9 @@ __global__ __launch_bounds__(UW_THREADS) void s2_union_wide_kernel(
 //
 // Why: of 400 000 candidates per query (65536 centroids, ndocs 1024) about one in thirty is scored.  Scoring all of them (a
 // set word per passage built with LDS atomics, one lane per passage, sorted by bag size) took 3.5 ms per 512 queries, this
-// 0.9; 150 queries of 8.8 M passages at 262144 centroids 25 ms, now 8.5.  What bounds it now: a wave's step of 2048
-// passages takes 16 to 20 us with 12 to 16 waves per compute unit, a third of it the additions of the bounds, the rest the
-// chains of dependent loads and LDS accesses of the other parts.
+// 0.9; 150 queries of 8.8 M passages at 262144 centroids 25 ms, now 6.6.  What bounds it now: a wave's step of 2048
+// passages takes 16 to 20 us with 12 to 16 waves per compute unit: the additions of the bounds and the chains of dependent
+// loads and LDS accesses of the other parts.
 #define IV_WAVES 4
 #define IV_LISTS 256    // probed lists a workgroup classifies; beyond (nprobe > 8) s2_candidates_kernel walks them
 
