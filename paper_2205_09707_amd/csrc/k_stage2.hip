@@ -1337,13 +1337,14 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                 // at least m scores lie in coarse bins 0 .. b: a bound in a worse bin needs no score
                 int2 c = known;
                 if (round > 0) {
-                    // the copies of all XCDs: one alone knows of an eighth of the query's scores, and a threshold from it
-                    // lets through up to eight times as many
-                    c = s2_coarse_load(hist_q, lane);
-                    if (!PLAIN && (mode & 8)) {  // uniform
+                    // the copies of all XCDs where that pays (see the launch)
+                    if (PLAIN || !(mode & 64)) {  // uniform
+                        c = s2_coarse_load(coarse_q, lane);
+                    } else {
                         int2 v[S2_COPIES];
 #pragma unroll
-                        for (int x = 1; x < S2_COPIES; ++x) v[x] = s2_coarse_load(hist_q + x * S2_COARSE, lane);
+                        for (int x = 0; x < S2_COPIES; ++x) v[x] = s2_coarse_load(hist_q + x * S2_COARSE, lane);
+                        c = v[0];
 #pragma unroll
                         for (int x = 1; x < S2_COPIES; ++x) {
                             c.x += v[x].x;
@@ -1553,14 +1554,18 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // updates alone).  Workgroups are dealt to the eight XCDs in turn: with many queries their number, per passage range,
     // is made a multiple of eight (empty ones added), so that a query's workgroups share an XCD.  With few, that would
     // leave XCDs and, in the end, most of the chip waiting for the query with the most to do: an odd number spreads
-    // every query over all XCDs, each of which counts in a copy of its own (mode bit 3) and reads the others' once it has
-    // scored its first batch.  Stage 2 and selection, us, multiple of eight / spread, copies read singly / all:
+    // every query over all XCDs, each of which counts in a copy of its own (mode bit 3).  That copy alone, an eighth of the
+    // scores, gives a threshold that lets through up to eight times as many as all copies do: 8 m scores in all, so
+    // once that is several per wave, a wave reads the others' copies too after its first batch (mode bit 6; one query,
+    // own / all: ndocs 256 of 5.2 M passages 78 / 92 us, 1024 of 4 M 67 / 69, 4096 of 8.8 M 195 / 183, 1024 of 1 M 84 / 76, of
+    // 400 000, three queries, 45 / 37).  Stage 2 and selection, us, multiple of eight / spread, copies read singly / all:
     //   7 and 8 queries of 2 M passages (65536 centroids)   311 / 202 / 172    219 / 232 / 166
     //   8, 16, 32 queries of 8.8 M                          1000, 1360, 2350 / - / 600, 950, 1710
     //   40, 64 of 400 000                                   139, 187 / - / 141, 191      of 2 M: 403, 552 / - / 451, 622
     const bool spread = nq <= 32;
     const int nqx = spread ? (nq | 1) : (nq + 7) & ~7;
-    const int own = (spread && nq * blocks > 64 ? 8 : 0) | given;
+    const int copies = spread && nq * blocks > 64 ? (4ll * m >= 3 * ((P + (1ll << len_log) - 1) >> len_log) ? 8 | 64 : 8) : 0;
+    const int own = copies | given;
     // Few workgroups, at most the three per compute unit that the 64-bit instance's LDS admits: that instance alone, taking
     // every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
     // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
