@@ -184,10 +184,8 @@ __device__ __forceinline__ float s2_score_members(uint64_t members, const float 
     return (float)d;
 }
 
-// The same score from rows of 32 floats without padding (slot s at row s - 1): the 16-byte pieces of row r are stored in the
-// order g ^ (r & 7), so that lanes that read one piece of different rows spread over the banks.  COLS query tokens at a
-// time and two rows per step; the additions are the same and in the same order as in s2_score_members.
-__device__ __forceinline__ int s2_row_piece(int r, int g) { return r * QLEN + 4 * (g ^ (r & 7)); }
+// The same score with slot s at row s - 1.  COLS query tokens at a time and two rows per step; the additions are the same
+// and in the same order as in s2_score_members.
 __device__ __forceinline__ int s2_first_bit(uint32_t v) { return __ffs((int)v) - 1; }
 __device__ __forceinline__ int s2_first_bit(unsigned long long v) { return __ffsll((long long)v) - 1; }
 // pairs (uniform): the lanes 2 j and 2 j + 1 share a bag and take half of the query tokens each, the odd lane continuing
@@ -213,12 +211,13 @@ __device__ __forceinline__ float s2_score_rows(SetT rows, const float *Tl, const
             }
 #pragma unroll
             for (int g = 0; g < COLS / 4; ++g) {
-                const float4 a = *reinterpret_cast<const float4 *>(Tl + s2_row_piece(r0, g_first + g0 + g));
-                const float4 b = *reinterpret_cast<const float4 *>(Tl + s2_row_piece(r1, g_first + g0 + g));
+                const float4 a = *reinterpret_cast<const float4 *>(Tl + r0 * S2_TSTRIDE + 4 * (g_first + g0 + g));
+                const float4 b = *reinterpret_cast<const float4 *>(Tl + r1 * S2_TSTRIDE + 4 * (g_first + g0 + g));
                 acc[4 * g] = fmaxf(acc[4 * g], fmaxf(a.x, b.x));
                 acc[4 * g + 1] = fmaxf(acc[4 * g + 1], fmaxf(a.y, b.y));
                 acc[4 * g + 2] = fmaxf(acc[4 * g + 2], fmaxf(a.z, b.z));
                 acc[4 * g + 3] = fmaxf(acc[4 * g + 3], fmaxf(a.w, b.w));
+                if (g == COLS / 8 - 1) __builtin_amdgcn_sched_barrier(0);  // (all rows in flight at once would spill)
             }
         }
 #pragma unroll 1
@@ -700,14 +699,6 @@ __global__ __launch_bounds__(UW_THREADS) void s2_union_wide_kernel(
 // otherwise be kept in registers across the range kernel's loops (25 registers past what four waves per SIMD leave).
 __device__ __forceinline__ void s2_opaque(int &v) { asm volatile("" : "+v"(v)); }
 
-// Sum over the lanes of a value below 64: one ballot per bit, no exchange between lanes.
-__device__ __forceinline__ int s2_wave_sum6(int v)
-{
-    int n = 0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) n += __popcll(__ballot((v >> k) & 1)) << k;
-    return n;
-}
 // Inclusive prefix sum over the lanes: additions with data-parallel-primitive operands (shifts by 1, 2, 4, 8 within a row of
 // sixteen lanes, then the last lane of a row added to the rows that follow), no LDS exchange.  All lanes active.
 __device__ __forceinline__ int s2_wave_scan(int v)
@@ -720,6 +711,9 @@ __device__ __forceinline__ int s2_wave_scan(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return v;
 }
+
+// Sum over the lanes, uniform.
+__device__ __forceinline__ int s2_wave_sum(int v) { return __builtin_amdgcn_readlane(s2_wave_scan(v), 63); }
 
 // Counts of coarse bins 2 lane and 2 lane + 1, read where the other compute units' additions arrive.
 __device__ __forceinline__ int2 s2_coarse_load(const int32_t *coarse_q, int lane)
@@ -1001,6 +995,34 @@ __device__ __forceinline__ void s2_gather_share(int q, int64_t j, int64_t nj, co
     __syncthreads();
 }
 
+// A += g where b's bits are set, for 32 passages per lane; A[k] bit p = bit k of the sum of passage p, g < 2^S2_UB_BITS.  A full
+// adder is two three-input instructions (v_bitop3_b32: sum 0x96, carry 0xE8; src0, src1, src2 stand for 0xF0, 0xCC, 0xAA)
+// once the gain's bit has been masked in; the compiler's own choice for the same expressions took five, and the additions
+// were 2000 of the 3400 vector instructions per 2048 passages of a query with 38 survivors.  With that, the comparison
+// and the reductions of a round in fewer instructions and rows that are addressed without arithmetic: batch of 150
+// queries of 8.8 M passages 9.46 -> 8.66 ms, of 512 of 400 000 2.90 -> 2.74, of 256 of 200 000 561 -> 532 us (whole search).
+__device__ __forceinline__ uint32_t s2_gain_bit(int g, int k) { return (uint32_t)(((int32_t)((uint32_t)g << (31 - k))) >> 31); }
+__device__ __forceinline__ void s2_add_gain(uint32_t (&A)[S2_UB_BITS], uint32_t b, int g)
+{
+    const uint32_t g0 = s2_gain_bit(g, 0);
+    uint32_t carry = __builtin_amdgcn_bitop3_b32(A[0], b, g0, 0x80);
+    A[0] = __builtin_amdgcn_bitop3_b32(A[0], b, g0, 0x78);
+#pragma unroll
+    for (int k = 1; k < S2_UB_BITS; ++k) {
+        const uint32_t x = b & s2_gain_bit(g, k), up = __builtin_amdgcn_bitop3_b32(A[k], x, carry, 0xE8);
+        A[k] = __builtin_amdgcn_bitop3_b32(A[k], x, carry, 0x96);
+        carry = up;
+    }
+}
+// The passages whose sum is at least `least` (uniform): the carry of sum + ~least + 1, one instruction per bit.
+__device__ __forceinline__ uint32_t s2_sum_reaches(const uint32_t (&A)[S2_UB_BITS], int least)
+{
+    uint32_t ge = 0xFFFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < S2_UB_BITS; ++k) ge = __builtin_amdgcn_bitop3_b32(A[k], s2_gain_bit(least, k), ge, 0xB2);
+    return ge;
+}
+
 // SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
 // the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
 // PLAIN: no copies of the histogram and no candidate words given (large batches; the two cost the kernel 2 % there).
@@ -1025,7 +1047,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     constexpr int SLOTS = KMAX + 1;
     constexpr int MORE = SHIFT == 11 ? 2 : 4;  // loads in flight per lane of a long list (of a coarse column: four times as long)
     __shared__ __align__(16) uint32_t area_all[IV_WAVES][FULL_PLANES * 64];
-    __shared__ __align__(16) float Tl[KMAX * QLEN];
+    __shared__ __align__(16) float Tl[KMAX * S2_TSTRIDE];
     __shared__ float rowsum[SLOTS];
     __shared__ int32_t kid[SLOTS], drow[SLOTS];  // slot - 1 -> centroid, row of its list's bitmap or -1
     __shared__ uint8_t order[SLOTS];             // the slots (minus one) with a bitmap, from the back those without
@@ -1113,13 +1135,13 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             }
         }
         for (int e = tid; e < K * (QLEN / 4); e += 64 * IV_WAVES)
-            *reinterpret_cast<float4 *>(Tl + s2_row_piece(e >> 3, e & 7)) =
+            *reinterpret_cast<float4 *>(Tl + (e >> 3) * S2_TSTRIDE + 4 * (e & 7)) =
                 *reinterpret_cast<const float4 *>(T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN + QLEN + 4 * e);
         const int gain_lane = lane < K ? gain_any : 0;
         __syncthreads();
         if (tid < K) {  // one survivor in the bag: its row, summed in the same order as in s2_score_rows
             double d = 0.0;
-            for (int i = 0; i < QLEN; ++i) d += (double)Tl[s2_row_piece(tid, i >> 2) + (i & 3)];
+            for (int i = 0; i < QLEN; ++i) d += (double)Tl[tid * S2_TSTRIDE + i];
             rowsum[tid] = (float)d;
         }
         if (!given) {
@@ -1183,14 +1205,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             uint32_t any = 0u, cand = given && act ? cbq[w0 + lane] : 0u;
             auto add = [&](uint32_t b, int g) {
                 any |= b;
-                uint32_t carry = 0u;
-#pragma unroll
-                for (int k = 0; k < S2_UB_BITS; ++k) {
-                    const uint32_t x = b & (uint32_t)(((int32_t)((uint32_t)g << (31 - k))) >> 31);
-                    const uint32_t sum = A[k] ^ x ^ carry;
-                    carry = (A[k] & x) | (carry & (A[k] | x));
-                    A[k] = sum;
-                }
+                s2_add_gain(A, b, g);
             };
             const int groups = 64 / nw, grp = lane / nw, gl = lane % nw;
             const bool gact = w0 + gl < cand_words;
@@ -1317,10 +1332,9 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                     uint32_t carry = 0u;
 #pragma unroll
                     for (int k = 0; k < S2_UB_BITS; ++k) {
-                        const uint32_t x = __shfl_xor(A[k], d);
-                        const uint32_t sum = A[k] ^ x ^ carry;
-                        carry = (A[k] & x) | (carry & (A[k] | x));
-                        A[k] = sum;
+                        const uint32_t x = __shfl_xor(A[k], d), up = __builtin_amdgcn_bitop3_b32(A[k], x, carry, 0xE8);
+                        A[k] = __builtin_amdgcn_bitop3_b32(A[k], x, carry, 0x96);
+                        carry = up;
                     }
                     cand |= __shfl_xor(cand, d);
                     any |= __shfl_xor(any, d);
@@ -1366,25 +1380,18 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                     if (!hi) break;  // no sum does
                     const int h = __ffsll((long long)hi) - 1;
                     const int need = 16 * h + __ffsll((long long)__ballot(reaches(16 * h + (lane & 15)))) - 1;
-                    uint32_t above = 0u, equal = 0xFFFFFFFFu;
-#pragma unroll
-                    for (int k = S2_UB_BITS - 1; k >= 0; --k) {
-                        const uint32_t bit = (uint32_t)(((int32_t)((uint32_t)need << (31 - k))) >> 31);
-                        above |= equal & A[k] & ~bit;
-                        equal &= ~(A[k] ^ bit);
-                    }
-                    left &= above | equal;
+                    left &= s2_sum_reaches(A, need);
                 }
                 uint32_t sel = left;
                 int want = enough1 ? 128 : first_batch;
-                if (s2_wave_sum6(__popc(left)) > 2 * want) {
+                if (s2_wave_sum(__popc(left)) > 2 * want) {
                     // nothing, or little, to prune with yet: the highest sums (and those that tie with the last of them)
                     uint32_t cur = left;
                     sel = 0u;
 #pragma unroll
                     for (int k = S2_UB_BITS - 1; k >= 0; --k) {
                         const uint32_t top = cur & A[k];
-                        const int n = s2_wave_sum6(__popc(top));
+                        const int n = s2_wave_sum(__popc(top));
                         if (n >= want) {
                             cur = top;
                         } else {
