@@ -826,7 +826,7 @@ __global__ __launch_bounds__(64 * IV_WAVES) void s2_candidates_kernel(
 // in LDS, then eight rows per load instruction as in stage 3.  Bins are counted in LDS and added once per share.
 // 400 000 passages, one query: 4.1 ms per search with four waves per 2048 passages fetching two rows at a time, 15.6 with one,
 // 0.40 now; 64 queries 92, 117 and 16.
-#define S2_GATHER_BLOCKS 768  // three per compute unit: what the 64-bit instances' LDS admits
+#define S2_GATHER_BLOCKS 768  // three per compute unit
 #define S2_GATHER_STRIDE 68   // of a passage's list: eight lanes that read one column of eight lists hit all banks
 struct S2GatherScratch {
     S2CandScratch cand;
@@ -1027,7 +1027,7 @@ __device__ __forceinline__ uint32_t s2_sum_reaches(const uint32_t (&A)[S2_UB_BIT
 // the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
 // PLAIN: no copies of the histogram and no candidate words given (large batches; the two cost the kernel 2 % there).
 template <int SHIFT, typename SetT, bool PLAIN>
-__global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4 : 3) void s2_invert_kernel(
+__global__ __launch_bounds__(64 * IV_WAVES, 4) void s2_invert_kernel(
     const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride,
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
@@ -1039,10 +1039,12 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
     int steps, int32_t m, int first_batch, unsigned main_blocks)
 {
     constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
-    // Planes of 64 words that fit a wave's area: what lets four (32-bit sets, coarse tables) or three workgroups share a
-    // compute unit.  A query with more of them takes two waves' area for one wave where the launch has workgroups to spare
-    // (mode bit 5), otherwise half or a quarter of the passages at a time.
-    constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 36 : 24);
+    // Planes of 64 words that fit a wave's area: what lets four workgroups share a compute unit.  Only lists with an entry in
+    // the range's column need one: of the 20 to 32 lists without a bitmap that a query of 40 survivors has on 8.8 M passages,
+    // five or more have none in 2048 passages.  Where there are more planes than fit, one wave takes two waves' area if the
+    // launch has workgroups to spare (mode bit 5), otherwise half or a quarter of the passages at a time.  (36 planes and
+    // three workgroups: 150 queries of 8.8 M passages 8.66 ms, this 7.2.)
+    constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 26 : 24);
     static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
     constexpr int SLOTS = KMAX + 1;
     constexpr int MORE = SHIFT == 11 ? 2 : 4;  // loads in flight per lane of a long list (of a coarse column: four times as long)
@@ -1162,9 +1164,6 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         const int n_sp = s2_uniform(n_front[1]);
         const bool two_areas = KMAX > FULL_PLANES && (mode & 32) && n_ss > FULL_PLANES;
         uint32_t *area = two_areas ? area_all[(2 * wave) % IV_WAVES] : area_all[wave];
-        int my_log = len_log;
-        while (KMAX > FULL_PLANES && (n_ss << (my_log - 5)) > (two_areas ? 2 : 1) * FULL_PLANES * 64) --my_log;
-        const int len = 1 << my_log, nw = len >> 5;
         // lane i: the i-th slot with a bitmap and its row / the i-th slot without one and its centroid
         const int dense_slot = lane < n_dense ? order[lane] : 0, dense_row = lane < n_dense ? drow[dense_slot] : 0;
         const int list_slot = lane < n_ss ? order[SLOTS - 1 - lane] : 64, list_c = lane < n_ss ? kid[list_slot] : -1;
@@ -1177,16 +1176,12 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
         int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
         if (two_areas && wave >= IV_WAVES / 2) last = first;  // its area is lent
         const int lane0 = lane;
+        int len;
         for (int64_t p0 = first; p0 < last; p0 += len) {  // uniform
             int lane = lane0;
             s2_opaque(lane);
-            const int64_t w0 = p0 >> 5;
-            const bool act = lane < nw && w0 + lane < cand_words;  // the lanes that hold a word of the range
-            uint32_t valid = 0u;
-            if (act) valid = P - (p0 + 32 * lane) >= 32 ? 0xFFFFFFFFu : (1u << (uint32_t)(P - (p0 + 32 * lane))) - 1u;
-            // what is known of the scores so far (used below, once the bounds are there)
-            const int2 known = s2_coarse_load(coarse_q, lane);
-            // where the surviving centroids' other lists enter the range (used further down)
+            // where the surviving centroids' other lists enter the range; those with an entry in this column of the table get a
+            // plane, in the order of the lists (looked at only where the planes may not fit: the loads are used further down)
             const int64_t col = p0 >> SHIFT;
             uint32_t list_a = 0u, list_b = 0u;
             int64_t list_at = 0;
@@ -1195,8 +1190,20 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                 list_b = table[(int64_t)list_c * (nr + 1) + col + 1];
                 list_at = ivf_offsets[list_c];
             }
-            for (int i = 0; i < n_ss; ++i)
-                if (lane < nw) area[i * nw + lane] = 0u;
+            int my_log = len_log;
+            const int room = (two_areas ? 2 : 1) * FULL_PLANES * 64;  // words
+            if (KMAX > FULL_PLANES && (n_ss << (my_log - 5)) > room) {
+                const int n = __popcll(__ballot(lane < n_ss && list_b > list_a));
+                while ((n << (my_log - 5)) > room) --my_log;
+            }
+            len = 1 << my_log;
+            const int nw = len >> 5;
+            const int64_t w0 = p0 >> 5;
+            const bool act = lane < nw && w0 + lane < cand_words;  // the lanes that hold a word of the range
+            uint32_t valid = 0u;
+            if (act) valid = P - (p0 + 32 * lane) >= 32 ? 0xFFFFFFFFu : (1u << (uint32_t)(P - (p0 + 32 * lane))) - 1u;
+            // what is known of the scores so far (used below, once the bounds are there)
+            const int2 known = s2_coarse_load(coarse_q, lane);
             // bounds, bit-sliced; A[k] bit b = bit k of the gain sum of passage p0 + 32 lane + b.  A range shorter than 2048
             // passages leaves lanes over: groups of nw lanes then take a slot each and add up their sums at the end.
             uint32_t A[S2_UB_BITS];
@@ -1246,29 +1253,31 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             }
             // the remaining lists, entry by entry; those that only make candidates are not looked up where every passage
             // is a candidate already
-            const int n_lists = n_ss + (__all((cand & valid) == valid) ? 0 : n_sp);
+            const unsigned long long has = __ballot(lane < n_ss && list_b > list_a);
+            const int n_act = __popcll(has), my_plane = __popcll(has & ((1ull << lane) - 1ull));
+            for (int i = 0; i < n_act; ++i)
+                if (lane < nw) area[i * nw + lane] = 0u;
+            const int n_lists = n_act + (__all((cand & valid) == valid) ? 0 : n_sp);
             lcand[lane] = cand;
+            // lane i: the slot of plane i
+            if ((has >> lane) & 1ull) lstart[my_plane] = (uint32_t)list_slot;
+            s2_wave_sync();
+            const int plane_slot = lane < n_act ? (int)lstart[lane] : 64;
             s2_wave_sync();
             for (int u0 = 0; u0 < n_lists; u0 += 64) {
-                const int e = u0 + lane;
-                uint32_t cnt = 0u, start = 0u;
-                if (e < n_lists) {
-                    uint32_t la = list_a, lb = list_b;
-                    int64_t at = list_at;
-                    if (e >= n_ss) {
-                        const int32_t c = plist[IV_LISTS - 1 - (e - n_ss)];
-                        la = table[(int64_t)c * (nr + 1) + col];
-                        lb = table[(int64_t)c * (nr + 1) + col + 1];
-                        at = ivf_offsets[c];
-                    }
-                    at += la;
-                    start = (uint32_t)at;
+                // an entry of the table: start (low 32 bits), start (high bits) << 21 | entries << 7 | plane, 64 = the candidates
+                auto put = [&](int at, int64_t start, uint32_t la, uint32_t lb, int plane) {
+                    start += la;
+                    lstart[at] = (uint32_t)start;
                     // at most 2^13 entries (a list is ascending); lists hold fewer than 2^43 entries together
-                    cnt = (uint32_t)((uint64_t)at >> 32) << 21 | (lb > la ? lb - la : 0u) << 7 |
-                          (uint32_t)(e < n_ss ? e : 64);  // plane, 64 = the candidates
+                    lcnt[at] = (uint32_t)((uint64_t)start >> 32) << 21 | (lb > la ? lb - la : 0u) << 7 | (uint32_t)plane;
+                };
+                if (u0 == 0 && ((has >> lane) & 1ull)) put(my_plane, list_at, list_a, list_b, my_plane);
+                const int e = u0 == 0 ? n_act + lane : u0 + lane;
+                if (e < n_lists && e - u0 < 64) {
+                    const int32_t c = plist[IV_LISTS - 1 - (e - n_act)];
+                    put(e - u0, ivf_offsets[c], table[(int64_t)c * (nr + 1) + col], table[(int64_t)c * (nr + 1) + col + 1], 64);
                 }
-                lstart[lane] = start;
-                lcnt[lane] = cnt;
                 s2_wave_sync();
                 const int nb = n_lists - u0 < 64 ? n_lists - u0 : 64;
                 // a quarter of the wave per list, four lists each in flight
@@ -1309,22 +1318,22 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
             }
             cand = lcand[lane];
             if (groups == 1) {
-                for (int i0 = 0; i0 < n_ss; i0 += 4) {
+                for (int i0 = 0; i0 < n_act; i0 += 4) {
                     uint32_t b[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) b[u] = i0 + u < n_ss ? area[(i0 + u) * 64 + lane] : 0u;
+                    for (int u = 0; u < 4; ++u) b[u] = i0 + u < n_act ? area[(i0 + u) * 64 + lane] : 0u;
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
-                        if (i0 + u < n_ss) {
-                            const int s = __builtin_amdgcn_readlane(list_slot, i0 + u);
+                        if (i0 + u < n_act) {
+                            const int s = __builtin_amdgcn_readlane(plane_slot, i0 + u);
                             if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= b[u];
                             add(b[u], __builtin_amdgcn_readlane(gain_lane, s));
                         }
                 }
             } else {
-                for (int i0 = 0; i0 < n_ss; i0 += groups) {
-                    const int i = i0 + grp, s = __shfl(list_slot, i & 63) & 63, g = __shfl(gain_lane, s);
-                    const uint32_t b = i < n_ss ? area[i * nw + gl] : 0u;
+                for (int i0 = 0; i0 < n_act; i0 += groups) {
+                    const int i = i0 + grp, s = __shfl(plane_slot, i & 63) & 63, g = __shfl(gain_lane, s);
+                    const uint32_t b = i < n_act ? area[i * nw + gl] : 0u;
                     if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= b;
                     add(b, g);
                 }
@@ -1464,13 +1473,13 @@ __global__ __launch_bounds__(64 * IV_WAVES, SHIFT == 13 || sizeof(SetT) == 4 ? 4
                             for (int u = 0; u < 8; ++u)
                                 rows |= (SetT)((v[u] >> pos) & 1u) << __builtin_amdgcn_readlane(dense_slot, i0 + u);
                         }
-                        for (int i0 = 0; i0 < n_ss; i0 += 8) {
+                        for (int i0 = 0; i0 < n_act; i0 += 8) {
                             uint32_t v[8];
 #pragma unroll
-                            for (int u = 0; u < 8; ++u) v[u] = i0 + u < n_ss ? area[(i0 + u) * nw + w] : 0u;
+                            for (int u = 0; u < 8; ++u) v[u] = i0 + u < n_act ? area[(i0 + u) * nw + w] : 0u;
 #pragma unroll
                             for (int u = 0; u < 8; ++u)
-                                rows |= (SetT)((v[u] >> pos) & 1u) << (__builtin_amdgcn_readlane(list_slot, i0 + u) & 63);
+                                rows |= (SetT)((v[u] >> pos) & 1u) << (__builtin_amdgcn_readlane(plane_slot, i0 + u) & 63);
                         }
                     }
                     // bags of one member are a look-up, and a wave of nothing else (few survivors) skips the rows
@@ -1530,7 +1539,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // 128, of 60 000: 120 / 114 / 113, of 200 000: 103 / 103 / 122; five of 29 500: 135 / 134 / 120; 64 of 20 000: 185 / 172 /
     // 196.  Steps per wave: the set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has
     // dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M:
-    // 13.3 / 12.6 / 12.4 ms).
+    // 13.3 / 12.6 / 12.4 ms).  A single query of more ranges than the chip holds waves (4096): two each, so that all run at
+    // once and the second ranges find a threshold (8.8 M passages: 347 us per search with one, 322 with two).
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
     if (ranges <= 40)
@@ -1539,7 +1549,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
     // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
     while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
-    const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 ? 2 : 1);
+    const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 || (nq == 1 && waves > 4096) ? 2 : 1);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
     // Passages a wave scores before there is a threshold: all waves of a query together about eight times the m that make
     // one, between 32 (fewer leave lanes idle) and 64 (more are scored, and counted, for nothing) -- or their share of m,
@@ -1573,7 +1583,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int nqx = spread ? (nq | 1) : (nq + 7) & ~7;
     const int copies = spread && nq * blocks > 64 ? (4ll * m >= 3 * ((P + (1ll << len_log) - 1) >> len_log) ? 8 | 64 : 8) : 0;
     const int own = copies | given;
-    // Few workgroups, at most the three per compute unit that the 64-bit instance's LDS admits: that instance alone, taking
+    // Few workgroups, at most three per compute unit: that instance alone, taking
     // every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
     // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
     // 65 / 70); with twice the workgroups,
