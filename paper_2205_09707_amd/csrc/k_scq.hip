@@ -28,8 +28,8 @@
 // Either way the tile of results then yields the row maxima (pruning bits) and, per query token, the maximum of the
 // tile's column.  The probes come from those maxima: with T the nprobe-th largest tile maximum of a token, each of
 // the nprobe best tiles holds a score >= T, so the nprobe-th best score is >= T and every centroid among the nprobe
-// best lies in a tile whose maximum is >= T -- normally just nprobe tiles.  A one-workgroup-per-query kernel finds T,
-// ranks the rows of those tiles from S_cq, and builds the duplicate-free union of the probes and the survivor table.
+// best lies in a tile whose maximum is >= T -- normally just nprobe tiles.  The tail kernel finds T, ranks the rows of
+// those tiles from S_cq and builds the duplicate-free union of the probes, and next to that the survivor table.
 // (Ranking inside the score kernel instead costs it a third of its running time: its waves' vector instructions
 // queue behind other waves' matrix instructions.)
 #include "plaid_internal.h"
@@ -72,20 +72,6 @@ __device__ __forceinline__ void scq_insert_key(uint64_t (&best)[NP], uint64_t ke
                 best[j] = key;
             }
         }
-    }
-}
-
-// v into a descending list of NP values (the smallest drops out)
-template <int NP>
-__device__ __forceinline__ void scq_insert_desc(float (&top)[NP], float v)
-{
-    if (v > top[NP - 1]) {
-#pragma unroll
-        for (int j = NP - 1; j >= 0; --j)
-            if (v > top[j]) {
-                if (j + 1 < NP) top[j + 1] = top[j];
-                top[j] = v;
-            }
     }
 }
 
@@ -136,70 +122,133 @@ __device__ __forceinline__ void scq_column_bounds(const float *Tx, int K, int ra
     colmm[2 * QLEN + tid] = K >= 3 ? base : mn;
 }
 
-// Survivor table of one query (runs in one workgroup, all of whose threads call it).  K = number of centroids
-// passing Eq. 5; when K <= S2_MAX_KEPT their ids are listed by decreasing length of their inverted lists (without lists, and
-// among equals, ascending), their rows copied to T (slot s at T[s], s = 1..K), a collision-free hash shift is chosen for the
-// streaming form's table, the gains and the base of the additive score bound are set, and bin_hi / bin_scale from bounds
-// of any non-empty passage's pruned score.  top1[i] = best centroid of token i (gives the bounds when K is large).
-// APPROX (Sq comes from the split-fp16 kernel): the pruning bits were completed by this workgroup a moment ago with
-// atomics, so they are read past the first-level cache, and the rows of T are re-evaluated in double from the centroids
-// Cm and the query Qq, which makes every stage-2 score that is built from T the exact one.
-template <bool APPROX>
-__device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ Sq, int64_t C, const uint32_t *__restrict__ kb,
-                                      int64_t keep_words, const int32_t *top1, S2Meta *meta_q,
-                                      int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq,
-                                      int32_t *ids /*[S2_MAX_KEPT + 1]*/, uint32_t *trial /*[S2_NHASH][S2_HASH / 32]*/,
-                                      float *colmm /*[3][32]*/, float *Tx /*[S2_MAX_KEPT][TX_STRIDE]*/, int32_t *misc /*[2]*/, const float *__restrict__ Cm = nullptr,
-                                      const float *Qq = nullptr /* the query's rows, in LDS */,
+// What the survivor table keeps in LDS.
+#define TAIL_AMB 2048  // ambiguous rows decided per round
+struct SurvivorScratch {
+    float Tx[S2_MAX_KEPT * TX_STRIDE];
+    uint32_t trial[S2_NHASH * (S2_HASH / 32)];
+    float colmm[3 * QLEN];
+    int32_t ids[S2_MAX_KEPT + 1], rank[S2_MAX_KEPT + 1];
+    int32_t misc[2];  // number of survivors, chosen hash trial
+    int32_t amb_n, amb_total;
+    uint32_t amb_pass[TAIL_AMB / 32];
+};
+struct SurvivorRows {  // APPROX only: the re-evaluations' operands
+    float Qs[QLEN * TAIL_QSTRIDE];
+    union {
+        float row[(S2_MAX_KEPT + 1) * TAIL_QSTRIDE];  // (whole tiles of sixteen)
+        int32_t amb[TAIL_AMB];
+    };
+    bool matrix;  // see tail_exact_rows
+};
+
+// The dot products of n rows with the 32 query rows, both in LDS TAIL_QSTRIDE floats apart, as the definition reads: put(row,
+// token, value).  All threads of the workgroup call this; what it read may be written again after a barrier, rows n ..
+// up to a multiple of sixteen are read and not used.  matrix: by the double-precision matrix instruction, which is the chain
+// of fused multiply-adds (see the top of this file) -- a tile of 16 rows and 16 tokens per wave, 32 instructions one after
+// the other; else a product per thread.  The conversions to double and the additions of 768 products, a thread each, take 19 us on one
+// compute unit, the tiles 2.
+typedef double scq_double4 __attribute__((ext_vector_type(4)));
+template <typename Put>
+__device__ __forceinline__ void tail_exact_rows(const float *row, int n, const float *Qs, bool matrix, Put put)
+{
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    if (matrix) {  // uniform
+        const int n_tiles = ((n + 15) >> 4) * (QLEN / 16);
+        for (int t = __builtin_amdgcn_readfirstlane(tid >> 6); t < n_tiles; t += (int)blockDim.x >> 6) {
+            const int r0 = 16 * (t / (QLEN / 16)), c0 = 16 * (t % (QLEN / 16));
+            const float *a = row + (r0 + li) * TAIL_QSTRIDE + lg, *b = Qs + (c0 + li) * TAIL_QSTRIDE + lg;
+            scq_double4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+            for (int s = 0; s < DIM / 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[4 * s], (double)b[4 * s], acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (r0 + 4 * r + lg < n) put(r0 + 4 * r + lg, c0 + li, (float)acc[r]);
+        }
+    } else {
+        for (int e = tid; e < n * QLEN; e += (int)blockDim.x)
+            put(e >> 5, e & 31, plaid_exact_dot_lds(row + (e >> 5) * TAIL_QSTRIDE, Qs + (e & 31) * TAIL_QSTRIDE));
+    }
+}
+
+// The rows whose bit is set in the query's pruning words, in any order (the table sorts them), and with amb the number of
+// those set there, to amb_total: sixteen words of each per thread in flight, nearly all of them zero.  All threads call this;
+// the counters are zero and published, a barrier has to follow.
+__device__ __forceinline__ void stage1_list_survivors(const uint32_t *__restrict__ kb, const uint32_t *__restrict__ amb, int64_t keep_words,
+                                                      SurvivorScratch &sh)
+{
+    const int tid = threadIdx.x, nthreads = blockDim.x;
+    int open = 0;
+    for (int64_t w0 = tid; w0 < keep_words; w0 += 16ll * nthreads) {
+        uint32_t v[16], a[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int64_t w = w0 + (int64_t)u * nthreads;
+            v[u] = w < keep_words ? kb[w] : 0u;
+            a[u] = amb && w < keep_words ? amb[w] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            open += __popc(a[u]);
+            if (v[u]) {
+                int pos = atomicAdd(&sh.misc[0], __popc(v[u]));
+                for (uint32_t rest = v[u]; rest && pos < S2_MAX_KEPT; rest &= rest - 1)
+                    sh.ids[pos++] = (int32_t)((w0 + (int64_t)u * nthreads) * 32 + __ffs(rest) - 1);
+            }
+        }
+    }
+    if (open) atomicAdd(&sh.amb_total, open);
+}
+
+// Survivor table of one query (runs in one workgroup, all of whose threads call it).  misc[0] = number K of centroids
+// passing Eq. 5, ids = the first of them, in any order; when K <= S2_MAX_KEPT their ids are listed by decreasing length of
+// their inverted lists (without lists, and among equals, ascending), their rows copied to T (slot s at T[s], s = 1..K), a
+// collision-free hash shift is chosen for the streaming form's table, the gains and the base of the additive score bound are
+// set, and bin_hi / bin_scale from bounds of any non-empty passage's pruned score.  col_max(colmm): the largest entry of each
+// of the 32 columns to colmm[0 .. 31] (asked for when K is large; all threads call it, a barrier follows).
+// APPROX (Sq comes from the split-fp16 kernel): the rows of T are re-evaluated in double from the centroids Cm and the query
+// in x.Qs, which makes every stage-2 score that is built from T the exact one.  The rows are staged in LDS, so that the
+// chains of additions wait for one round trip to memory and not for four.
+template <bool APPROX, typename ColMax>
+__device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ Sq, int64_t C, ColMax col_max, S2Meta *meta_q,
+                                      int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq, SurvivorScratch &sh,
+                                      SurvivorRows *x = nullptr, const float *__restrict__ Cm = nullptr,
                                       const int64_t *__restrict__ ivf_offsets = nullptr, int q = 0,
                                       int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0,
                                       bool need_hash = true /* the streaming form looks survivors up */)
 {
-    auto keep_word = [&](int64_t w) -> uint32_t {
-        if (APPROX) return __hip_atomic_load(kb + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return kb[w];
-    };
     const int tid = threadIdx.x, nthreads = blockDim.x;
-    if (tid == 0) {
-        misc[0] = 0;   // running count of survivors
-        misc[1] = -1;  // chosen hash trial
-    }
-    for (int e = tid; e < S2_NHASH * (S2_HASH / 32); e += nthreads) trial[e] = 0u;
-    __syncthreads();
-    // the survivors' ids, in any order (sorted below): eight words per thread in flight, nearly all of them zero
-    for (int64_t w0 = tid; w0 < keep_words; w0 += 8ll * nthreads) {
-        uint32_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = w0 + (int64_t)u * nthreads < keep_words ? keep_word(w0 + (int64_t)u * nthreads) : 0u;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (v[u]) {
-                int pos = atomicAdd(&misc[0], __popc(v[u]));
-                for (uint32_t rest = v[u]; rest && pos < S2_MAX_KEPT; rest &= rest - 1)
-                    ids[pos++] = (int32_t)((w0 + (int64_t)u * nthreads) * 32 + __ffs(rest) - 1);
-            }
-    }
-    __syncthreads();
+    int32_t *ids = sh.ids, *misc = sh.misc;
+    uint32_t *trial = sh.trial;
+    float *colmm = sh.colmm, *Tx = sh.Tx;
     int K = misc[0];
     if (C > (1ll << 26) - 2 && K <= S2_MAX_KEPT) K = S2_MAX_KEPT + 1;  // ids must fit the 26-bit field of a table entry
     // Slots in one order, whatever order the ids were found in: by decreasing inverted-list length, ties by id, so that a
     // query's gains are the same each time.  Stage 2 needs no particular order.
-    if (K > 1 && K <= S2_MAX_KEPT) {
+    if (K > 0 && K <= S2_MAX_KEPT) {
         int32_t my_id = 0;
         int rank = 0;
-        uint32_t *lens = trial;  // the first K words serve as the list lengths here and are cleared again below
+        uint32_t *lens = trial;  // its first K words serve as the list lengths; the hash trials start from zeros
+        for (int e = tid; need_hash && e < S2_NHASH * (S2_HASH / 32); e += nthreads)
+            if (e >= K) trial[e] = 0u;
         if (tid < K) {
             my_id = ids[tid];
             // at most P < 2^31 entries (no lists: in the order of the ids)
             lens[tid] = ivf_offsets ? (uint32_t)(ivf_offsets[my_id + 1] - ivf_offsets[my_id]) : 0u;
         }
+        if (APPROX)
+            for (int e = tid; e < K * (DIM / 4); e += nthreads)
+                *reinterpret_cast<float4 *>(x->row + e / (DIM / 4) * TAIL_QSTRIDE + 4 * (e % (DIM / 4))) =
+                    *reinterpret_cast<const float4 *>(Cm + (int64_t)ids[e / (DIM / 4)] * DIM + 4 * (e % (DIM / 4)));
         __syncthreads();
         if (tid < K) {
             const uint32_t my_len = lens[tid];
+#pragma unroll 4
             for (int u = 0; u < K; ++u) {
                 const uint32_t len = lens[u];
                 rank += (len > my_len || (len == my_len && ids[u] < my_id)) ? 1 : 0;
             }
+            sh.rank[tid] = rank;
         }
         __syncthreads();
         if (tid < K) {
@@ -210,7 +259,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     }
     // a hash h(c) = (c ^ (c >> sh)) & (S2_HASH - 1) that maps the survivors to distinct entries makes a lookup one
     // probe; thread t tries shift S2_SHIFT0 + t on a private bitmap.  No such shift (very rare): gather kernel.
-    if (need_hash && K <= S2_MAX_KEPT) {
+    if (need_hash && K <= S2_MAX_KEPT) {  // (K = 0: any shift will do, no trial is looked at)
         bool ok = tid < S2_NHASH;
         if (ok) {
             const int sh = S2_SHIFT0 + tid;
@@ -229,12 +278,14 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     }
     const int hash_shift = (need_hash && K <= S2_MAX_KEPT) ? S2_SHIFT0 + (S2_NHASH - 1 - misc[1]) : 0;
     if (K <= S2_MAX_KEPT) {
-        for (int e = tid; e < K * QLEN; e += nthreads) {
-            const float v = APPROX ? plaid_exact_dot(Cm + (int64_t)ids[e >> 5] * DIM, Qq + (e & 31) * TAIL_QSTRIDE)
-                                   : Sq[(int64_t)ids[e >> 5] * QLEN + (e & 31)];
-            Tq[QLEN + e] = v;
-            Tx[(e >> 5) * TX_STRIDE + (e & 31)] = v;
-        }
+        auto put = [&](int slot, int tok, float v) {
+            Tq[QLEN + slot * QLEN + tok] = v;
+            Tx[slot * TX_STRIDE + tok] = v;
+        };
+        if (APPROX)  // (the staged rows lie in the order the ids were found in)
+            tail_exact_rows(x->row, K, x->Qs, x->matrix, [&](int r, int tok, float v) { put(sh.rank[r], tok, v); });
+        else
+            for (int e = tid; e < K * QLEN; e += nthreads) put(e >> 5, e & 31, Sq[(int64_t)ids[e >> 5] * QLEN + (e & 31)]);
         if (tid < K) kept_ids_q[tid] = ids[tid];
         __syncthreads();
         // Per query token: bounds of the rows for the bins, and the base of the additive bound
@@ -250,9 +301,9 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
             else scq_column_bounds<7>(Tx, K, (K + 6) / 9, tid, colmm);
         }
         __syncthreads();
-        if (tid < 64 && K > 0) {  // one wave, lane = slot
+        if (tid < 64 && K > 0) {  // one wave, lane = slot (the next one fills in the rest of the record)
             float g = 0.f, base = 0.f, scale = 0.f;
-#pragma unroll 4
+#pragma unroll 8
             for (int i = 0; i < QLEN; ++i) {
                 const float b = colmm[2 * QLEN + i];
                 if (tid < K) g += fmaxf(Tx[tid * TX_STRIDE + i] - b, 0.f);
@@ -274,21 +325,22 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
                 meta_q->ub_unit = unit;
             }
         }
-    } else if (tid < QLEN) {
-        // many survivors: the best centroid of each token bounds every row from above
-        const float mx = Sq[(int64_t)top1[tid] * QLEN + tid];
-        colmm[tid] = mx;
-        colmm[QLEN + tid] = -mx - 1.0f;
+    } else {
+        // many survivors: the largest entry of each column bounds every row from above
+        col_max(colmm);
+        __syncthreads();
+        if (tid < QLEN) colmm[QLEN + tid] = -colmm[tid] - 1.0f;
+        __syncthreads();
     }
-    __syncthreads();
-    if (tid < 64) {  // (one wave; the bounds need no particular order of summation)
-        double u = tid < QLEN ? (double)colmm[tid] : 0.0, l = tid < QLEN ? (double)colmm[QLEN + tid] : 0.0;
+    if (tid >= 64 && tid < 128) {  // (one wave; the bounds need no particular order of summation)
+        const int i = tid - 64;
+        double u = i < QLEN ? (double)colmm[i] : 0.0, l = i < QLEN ? (double)colmm[QLEN + i] : 0.0;
 #pragma unroll
         for (int d = 1; d < QLEN; d <<= 1) {
             u += __shfl_xor(u, d);
             l += __shfl_xor(l, d);
         }
-        if (tid == 0) {
+        if (i == 0) {
             meta_q->K = K;
             meta_q->bin_hi = (float)u;
             const float range = (float)u - (float)l;
@@ -309,18 +361,22 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
                                                               const uint32_t *__restrict__ keepbits, int64_t keep_words,
                                                               const int32_t *__restrict__ probed, int nprobe, Stage1Out o)
 {
-    __shared__ int32_t ids[S2_MAX_KEPT + 1];
-    __shared__ uint32_t trial[S2_NHASH * (S2_HASH / 32)];
-    __shared__ float colmm[3 * QLEN];
-    __shared__ float Tx[S2_MAX_KEPT * TX_STRIDE];
-    __shared__ int32_t misc[2];
+    __shared__ SurvivorScratch sh;
     __shared__ int32_t top1[QLEN];
     const int q = blockIdx.x;
+    const float *Sq = S + (int64_t)q * C * QLEN;
     if (threadIdx.x < QLEN) top1[threadIdx.x] = probed[((int64_t)q * QLEN + threadIdx.x) * nprobe];
+    if (threadIdx.x == 0) {
+        sh.misc[0] = 0;
+        sh.misc[1] = -1;
+    }
     __syncthreads();
-    stage1_survivor_table<false>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1, o.meta + q,
-                                 o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids,
-                                 trial, colmm, Tx, misc, nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
+    stage1_list_survivors(keepbits + (int64_t)q * keep_words, nullptr, keep_words, sh);
+    __syncthreads();
+    stage1_survivor_table<false>(Sq, C,
+                                 [&](float *colmm) { if (threadIdx.x < QLEN) colmm[threadIdx.x] = Sq[(int64_t)top1[threadIdx.x] * QLEN + threadIdx.x]; },
+                                 o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, sh,
+                                 nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
 }
 
 // tilemax: [q][tile][32] column maxima of each tile (null: scores and pruning bits only).
@@ -445,7 +501,6 @@ __global__ __launch_bounds__(SCQ_THREADS) void scq_fused_kernel(const float *__r
 
 
 // ------------------------------------------------------------------ matrix form
-typedef double scq_double4 __attribute__((ext_vector_type(4)));
 // Four waves of 32 rows measured best: eight waves of 16 rows (more waves per SIMD to fill the matrix pipe while
 // others are in their epilogue) lose more to the per-wave epilogue instructions than they gain (5.2 vs 4.95 ms per 512
 // queries on C = 65536), 64 rows per wave halve the occupancy.
@@ -681,15 +736,20 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok)
     return 0;
 }
 
-// One workgroup per query: the probes (rank order) from the tiles' column maxima, their ascending duplicate-free
-// union, and the survivor table.  tilemax is [tile][token]: a thread reads four tokens of every 128th tile (16-byte
-// loads, consecutive threads at consecutive addresses, eight loads in flight) and keeps each token's NP largest; the
-// eight lanes of a wave that share tokens merge their lists by shuffles.  Then 32 consecutive lanes share a token:
-// T = the nprobe-th largest of the token's tile maxima (nprobe rounds of "maximum over the 32 lanes, its first holder
-// drops it").  A second pass over tilemax lists the tiles whose maximum is >= T in LDS (normally nprobe of them; a
-// tie group too long for the list makes the lanes walk all tiles instead); their rows are ranked by (score
-// descending, id ascending) from S_cq, four loads per lane in flight, and the 32 lists are merged by a shuffle tree.
-// tile_rows = centroid rows per tile.
+// Probes and survivors of a query, a workgroup each (blockIdx.y): the two share nothing but their inputs, and each is a
+// chain of dependent steps of a microsecond, so that side by side they take half the time (one query of 400 000 passages,
+// 65536 centroids: 40 us one after the other, with the tiles' maxima read twice over by one workgroup and the rows to
+// re-evaluate fetched in four round trips; 19 now; 8.8 M passages, 262144 centroids 79 -> 27; 10 000, 1024 27 -> 12.5).
+//
+// Probes (rank order), from the column maxima of the score kernel's tiles, and their ascending duplicate-free union.  The
+// split-fp16 kernel also reports the maxima of groups of 2^gs tiles; otherwise a tile is its own group.  gmax is
+// [group][token]: a thread reads four tokens of every 128th group (16-byte loads, consecutive threads at consecutive
+// addresses, eight loads in flight) and keeps their largest values; its rows are one of 128 blocks.  Then 32 consecutive
+// lanes share a token: the nprobe-th largest of the block maxima (nprobe rounds of "maximum over the 32 lanes, its first
+// holder drops it"), and the groups whose maximum reaches it, listed in LDS; the same once more over the tiles of those
+// groups gives T, the nprobe-th largest tile maximum, and the tiles whose maximum is >= T (normally nprobe of them; a tie
+// group too long for a list makes the lanes walk all tiles instead).  Their rows with a score >= T are ranked by (score
+// descending, id ascending).  tile_rows = centroid rows per tile.
 //
 // APPROX: S, its tile maxima and the pruning bits come from the split-fp16 kernel, every entry within eps =
 // PLAID_SCQ16_EPS of the exact one.  The decisions stay those of the exact scores:
@@ -700,146 +760,182 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok)
 //   pruning  a row whose approximate maximum lies within eps of t_cs was left open by the score kernel (ambbits): its
 //            entries >= t_cs - eps are re-evaluated and the row's bit is set when one of them reaches t_cs;
 //   table    the rows of the surviving centroids that stage 2 scores with are re-evaluated (stage1_survivor_table).
-#define TAIL_SEL 16  // listed tiles per token
-#define TAIL_AMB 2048  // ambiguous rows decided per round
+#define TAIL_SEL 16   // listed groups, and listed tiles, per token
+#define TAIL_XCAP 32  // listed rows per token: one per lane
+#define TAIL_ROWS 128  // rows staged at most for the re-evaluation of the probes, half of their dimensions at a time; more of them
+                       // are re-evaluated straight from memory, a lane each
+#define TAIL_HSTRIDE (DIM / 2 + 4)  // floats per staged half row
 struct Stage1Exact {        // what the re-evaluations need (APPROX only)
     const float *Cm;        // [C][128] centroids
     const float *Q;         // [nq][32][128] queries
     const uint32_t *ambbits;  // [nq][keep_words]
     float t_cs, t_lo;       // threshold of Eq. 5 and the smallest approximate score that can still reach it
     float margin;           // 2 eps
+    bool matrix;            // the double-precision matrix instruction gives the definition's bits
 };
-template <int NP, bool APPROX>
-__global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *__restrict__ S, int64_t C,
-                                                                   uint32_t *__restrict__ keepbits, int64_t keep_words,
-                                                                   const float *__restrict__ tilemax, int nblk, int tile_rows,
-                                                                   int nprobe, Stage1Out o, Stage1Exact x)
+// The query's rows to LDS, TAIL_QSTRIDE floats apart.
+__device__ __forceinline__ void tail_stage_query(const float *__restrict__ Q, int q, float *Qs)
 {
-    __shared__ int32_t idl[256];   // probed ids
-    __shared__ int32_t top1[QLEN];
-    __shared__ int32_t ids[S2_MAX_KEPT + 1];
-    __shared__ uint32_t trial[S2_NHASH * (S2_HASH / 32)];
-    __shared__ float colmm[3 * QLEN];
-    __shared__ float Tx[S2_MAX_KEPT * TX_STRIDE];
-    __shared__ int32_t misc[2];
-    constexpr int TAIL_WAVES = TAIL_THREADS / 64;
+    static_assert(TAIL_THREADS * 4 == QLEN * DIM, "one 16-byte load per thread stages the query");
+    const int tid = threadIdx.x;
+    *reinterpret_cast<float4 *>(Qs + (tid / (DIM / 4)) * TAIL_QSTRIDE + 4 * (tid % (DIM / 4))) =
+        *reinterpret_cast<const float4 *>(Q + (int64_t)q * QLEN * DIM + 4 * tid);
+}
+
+template <bool APPROX>
+struct ProbeScratch {
+    float Qs[APPROX ? QLEN * TAIL_QSTRIDE : 4];
+    union {
+        float block[4 * TAIL_LANES][QLEN + 4];                // each thread's largest group maximum of its tokens
+        float row[APPROX ? TAIL_ROWS * TAIL_HSTRIDE : 4];   // later: half of the dimensions of the rows to re-evaluate
+    };
+    union {
+        int32_t sel_grp[QLEN][TAIL_SEL];   // listed groups
+        float xscore[QLEN][TAIL_XCAP];     // later: exact scores of the listed rows
+    };
+    int32_t xc_id[QLEN][TAIL_XCAP];    // the listed rows
+    int32_t xc_cnt[QLEN], xc_first[QLEN + 1];
+    int16_t row_of[TAIL_ROWS];       // token and place among its listed rows of the rows that are staged
+    int32_t sel_tile[QLEN][TAIL_SEL];  // listed tiles
+    int32_t grp_cnt[QLEN], tile_cnt[QLEN];
+    float Tsh[QLEN];
+    int32_t wave_n[4];
+    alignas(16) int32_t idl[256];    // probed ids
+    int32_t sorted[256];
+};
+
+// Maximum over the 32 lanes of a token (every lane gets it): rotations within rows of sixteen lanes, then the other row's.
+__device__ __forceinline__ float tail_max32(float m)
+{
+#define TAIL_ROR(n) __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(m), 0x120 + (n), 0xf, 0xf, false))
+    m = fmaxf(m, TAIL_ROR(8));
+    m = fmaxf(m, TAIL_ROR(4));
+    m = fmaxf(m, TAIL_ROR(2));
+    m = fmaxf(m, TAIL_ROR(1));
+#undef TAIL_ROR
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// The nprobe-th largest of the values the 32 lanes of a token hold, four each (-infinity where there are fewer).
+__device__ __forceinline__ float tail_nth_largest(float (&v)[4], int nprobe, int l)
+{
+    float T = -INFINITY;
+    for (int r = 0; r < nprobe; ++r) {  // uniform
+        const float mine = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+        T = tail_max32(mine);
+        const unsigned long long who = __ballot(mine == T);
+        const uint32_t half = (threadIdx.x & 32) ? (uint32_t)(who >> 32) : (uint32_t)who;  // this token's 32 lanes
+        if (l == __ffs(half) - 1) {  // the first holder drops it
+            bool gone = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool drop = !gone && v[u] == T;
+                gone = gone || drop;
+                v[u] = drop ? -INFINITY : v[u];
+            }
+        }
+    }
+    return T;
+}
+
+template <int NP, bool APPROX>
+__device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, const float *__restrict__ S, int64_t C,
+                                            const float *__restrict__ tmq, int nblk, int tile_rows, const float *__restrict__ gmq,
+                                            int ng, int gs, int nprobe, const Stage1Out o, const Stage1Exact x)
+{
     constexpr int TAIL_FLY = 8;                          // loads in flight per thread
     constexpr int TAIL_PARTS = TAIL_THREADS / (QLEN / 4);  // threads that share four tokens
-    __shared__ float cand[QLEN][TAIL_WAVES * NP + 1];  // each wave's NP largest tile maxima of every token
-    static_assert(TAIL_WAVES <= TAIL_LANES, "one lane per wave list");
-    __shared__ float Tsh[QLEN];
-    __shared__ int32_t sel_cnt[QLEN];
-    __shared__ int32_t sel_tile[QLEN][TAIL_SEL];
-    static_assert(TAIL_THREADS == QLEN * TAIL_LANES && TAIL_LANES == 32, "32 lanes per query token");
-    const int q = blockIdx.x, tid = threadIdx.x;
+    static_assert(TAIL_LANES == 32, "32 lanes per query token");
+    const int tid = threadIdx.x;
     const float *__restrict__ Sq = S + (int64_t)q * C * QLEN;
-    const float *__restrict__ tmq = tilemax + (int64_t)q * nblk * QLEN;
     const float margin = APPROX ? x.margin : 0.f;
-    // APPROX: the query's rows in LDS for the re-evaluations, and per token the rows to re-evaluate
-    constexpr int TAIL_XCAP = TAIL_LANES;  // listed rows per token: one per lane
-    __shared__ __align__(16) float Qs[APPROX ? QLEN * TAIL_QSTRIDE : 4];
-    __shared__ int32_t xc_id[APPROX ? QLEN : 1][TAIL_XCAP];
-    __shared__ int32_t xc_cnt[QLEN];
-    const float *Qq = Qs;
-    if (APPROX) {
-        static_assert(TAIL_THREADS * 4 == QLEN * DIM, "one 16-byte load per thread stages the query");
-        *reinterpret_cast<float4 *>(Qs + (tid / (DIM / 4)) * TAIL_QSTRIDE + 4 * (tid % (DIM / 4))) =
-            *reinterpret_cast<const float4 *>(x.Q + (int64_t)q * QLEN * DIM + 4 * tid);
-    }
-    {
-        // pass 1: thread (tokens 4 tk4 .. 4 tk4 + 3, part) keeps the NP largest maxima of tiles part, part + 128, ...
-        const int tk4 = tid % (QLEN / 4), part = tid / (QLEN / 4);
-        float top[4][NP];
+    if (APPROX) tail_stage_query(x.Q, q, sh.Qs);
+    // pass 1: the maxima of groups part, part + 128, ... of tokens 4 tk4 .. 4 tk4 + 3, one block of rows per thread
+    const int tk4 = tid % (QLEN / 4), part = tid / (QLEN / 4);
+    float4 g[TAIL_FLY];  // the first of them stay in registers
+    auto load = [&](int b0) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int j = 0; j < NP; ++j) top[c][j] = -INFINITY;
-        for (int b0 = part; b0 < nblk; b0 += TAIL_PARTS * TAIL_FLY) {
-            float4 v[TAIL_FLY];
-#pragma unroll
-            for (int u = 0; u < TAIL_FLY; ++u) {
-                const int b = b0 + TAIL_PARTS * u;
-                v[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-                if (b < nblk) v[u] = *reinterpret_cast<const float4 *>(tmq + (int64_t)b * QLEN + 4 * tk4);
-            }
-#pragma unroll
-            for (int u = 0; u < TAIL_FLY; ++u) {
-                const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) scq_insert_desc<NP>(top[c], x[c]);
-            }
+        for (int u = 0; u < TAIL_FLY; ++u) {
+            const int b = b0 + TAIL_PARTS * u;
+            g[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            if (b < ng) g[u] = *reinterpret_cast<const float4 *>(gmq + (int64_t)b * QLEN + 4 * tk4);
         }
-        // the lanes of a wave with the same tk4 are 8 apart
+    };
+    float4 most = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    for (int b0 = part; b0 < ng; b0 += TAIL_PARTS * TAIL_FLY) {
+        load(b0);
 #pragma unroll
-        for (int d = QLEN / 4; d < 64; d <<= 1)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float other[NP];
-#pragma unroll
-                for (int j = 0; j < NP; ++j) other[j] = __shfl_xor(top[c][j], d);
-#pragma unroll
-                for (int j = 0; j < NP; ++j) scq_insert_desc<NP>(top[c], other[j]);
-            }
-        if ((tid & 63) < QLEN / 4) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int j = 0; j < NP; ++j) cand[4 * tk4 + c][(tid >> 6) * NP + j] = top[c][j];
-        }
+        for (int u = 0; u < TAIL_FLY; ++u)
+            most = make_float4(fmaxf(most.x, g[u].x), fmaxf(most.y, g[u].y), fmaxf(most.z, g[u].z), fmaxf(most.w, g[u].w));
     }
+    *reinterpret_cast<float4 *>(&sh.block[part][4 * tk4]) = most;
     __syncthreads();
-    const int i = tid / TAIL_LANES, l = tid % TAIL_LANES;
+    const int i = tid / TAIL_LANES, l = tid % TAIL_LANES;  // the token that this lane shares, its number among those that do
     {
-        float top[NP];  // descending
+        float v[4];
 #pragma unroll
-        for (int j = 0; j < NP; ++j) top[j] = l < TAIL_WAVES ? cand[i][l * NP + j] : -INFINITY;
-        float T = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < NP; ++r)
-            if (r < nprobe) {  // uniform
-                float m = top[0];
-#pragma unroll
-                for (int d = TAIL_LANES / 2; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-                T = m;
-                const unsigned long long who = __ballot(top[0] == m);
-                const uint32_t mine = (tid & 32) ? (uint32_t)(who >> 32) : (uint32_t)who;  // this token's 32 lanes
-                if (l == __ffs(mine) - 1) {
-#pragma unroll
-                    for (int j = 0; j + 1 < NP; ++j) top[j] = top[j + 1];
-                    top[NP - 1] = -INFINITY;
-                }
-            }
+        for (int u = 0; u < 4; ++u) v[u] = sh.block[l + TAIL_LANES * u][i];
+        static_assert(TAIL_PARTS == 4 * TAIL_LANES, "four blocks per lane");
+        const float T0 = tail_nth_largest(v, nprobe, l);
         if (l == 0) {
-            Tsh[i] = T;
-            sel_cnt[i] = 0;
-            xc_cnt[i] = 0;
+            sh.Tsh[i] = T0;
+            sh.grp_cnt[i] = 0;
+            sh.tile_cnt[i] = 0;
+            sh.xc_cnt[i] = 0;
         }
     }
     __syncthreads();
     {
-        // pass 2, same thread -> (tokens, tiles) map: list the tiles that can hold one of the nprobe best
-        const int tk4 = tid % (QLEN / 4), part = tid / (QLEN / 4);
-        const float T4[4] = {Tsh[4 * tk4] - margin, Tsh[4 * tk4 + 1] - margin, Tsh[4 * tk4 + 2] - margin,
-                             Tsh[4 * tk4 + 3] - margin};
-        for (int b0 = part; b0 < nblk; b0 += TAIL_PARTS * TAIL_FLY) {
-            float4 v[TAIL_FLY];
+        // pass 2, same thread -> (tokens, groups) map: list the groups that can hold one of the nprobe best
+        const float T4[4] = {sh.Tsh[4 * tk4] - margin, sh.Tsh[4 * tk4 + 1] - margin, sh.Tsh[4 * tk4 + 2] - margin,
+                             sh.Tsh[4 * tk4 + 3] - margin};
+        for (int b0 = part; b0 < ng; b0 += TAIL_PARTS * TAIL_FLY) {
+            if (ng > TAIL_PARTS * TAIL_FLY) load(b0);  // uniform
 #pragma unroll
             for (int u = 0; u < TAIL_FLY; ++u) {
                 const int b = b0 + TAIL_PARTS * u;
-                v[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-                if (b < nblk) v[u] = *reinterpret_cast<const float4 *>(tmq + (int64_t)b * QLEN + 4 * tk4);
-            }
-#pragma unroll
-            for (int u = 0; u < TAIL_FLY; ++u) {
-                const int b = b0 + TAIL_PARTS * u;
-                const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                const float e[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (b < nblk && x[c] >= T4[c]) {
-                        const int pos = atomicAdd(&sel_cnt[4 * tk4 + c], 1);
-                        if (pos < TAIL_SEL) sel_tile[4 * tk4 + c][pos] = b;
+                    if (b < ng && e[c] >= T4[c]) {
+                        const int pos = atomicAdd(&sh.grp_cnt[4 * tk4 + c], 1);
+                        if (pos < TAIL_SEL) sh.sel_grp[4 * tk4 + c][pos] = b;
                     }
             }
+        }
+    }
+    __syncthreads();
+    float T;  // the nprobe-th largest tile maximum (or a smaller value that nprobe rows reach), less the margin
+    {
+        // tiles of the listed groups (of all, when too many groups tie): up to four per lane stay in registers
+        const bool listed = sh.grp_cnt[i] <= TAIL_SEL;
+        const int n_tiles = listed ? sh.grp_cnt[i] << gs : nblk;
+        auto tile_of = [&](int it) { return listed ? (sh.sel_grp[i][it >> gs] << gs) + (it & ((1 << gs) - 1)) : it; };
+        float v[4], kept[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int it = l + TAIL_LANES * u, t = it < n_tiles ? tile_of(it) : nblk;
+            v[u] = kept[u] = t < nblk ? tmq[(int64_t)t * QLEN + i] : -INFINITY;
+        }
+        for (int it = l + 4 * TAIL_LANES; it < n_tiles; it += TAIL_LANES) {  // more than that: a lane's share is one block
+            const int t = tile_of(it);
+            if (t < nblk) kept[0] = fmaxf(kept[0], tmq[(int64_t)t * QLEN + i]);
+        }
+        T = tail_nth_largest(kept, nprobe, l) - margin;
+        auto list = [&](float m, int t) {
+            if (m >= T) {
+                const int pos = atomicAdd(&sh.tile_cnt[i], 1);
+                if (pos < TAIL_SEL) sh.sel_tile[i][pos] = t;
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int it = l + TAIL_LANES * u;
+            if (it < n_tiles && tile_of(it) < nblk) list(v[u], tile_of(it));
+        }
+        for (int it = l + 4 * TAIL_LANES; it < n_tiles; it += TAIL_LANES) {
+            const int t = tile_of(it);
+            if (t < nblk) list(tmq[(int64_t)t * QLEN + i], t);
         }
     }
     __syncthreads();
@@ -847,134 +943,237 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
         uint64_t best[NP];
 #pragma unroll
         for (int j = 0; j < NP; ++j) best[j] = PLAID_KEY_MAX;
-        const float T = Tsh[i] - margin;
-        const int n_sel = sel_cnt[i];
+        const int n_sel = sh.tile_cnt[i];
         const bool listed = n_sel <= TAIL_SEL;
         const int chunks = (tile_rows + TAIL_LANES - 1) / TAIL_LANES;  // 32-row pieces of a tile
         const int n_items = (listed ? n_sel : nblk) * chunks;
         // walk: every listed row with its score; what happens to a row is up to `visit`
+        constexpr int FLY = NP <= 2 ? 4 : 8;  // score rows in flight per lane
         auto walk = [&](auto visit) {
-            for (int it0 = 0; it0 < n_items; it0 += 4) {
-                float sv[4];
-                int64_t cc[4];
-                bool ok[4];
+            for (int it0 = 0; it0 < n_items; it0 += FLY) {
+                float sv[FLY];
+                int64_t cc[FLY];
+                bool ok[FLY];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < FLY; ++u) {
                     const int it = it0 + u;
                     ok[u] = it < n_items;
                     const int k = ok[u] ? it / chunks : 0, r = (it % chunks) * TAIL_LANES + l;
-                    const int t = listed ? sel_tile[i][k] : k;
+                    const int t = listed ? sh.sel_tile[i][k] : k;
                     if (!listed && ok[u]) ok[u] = tmq[(int64_t)t * QLEN + i] >= T;
                     cc[u] = (int64_t)t * tile_rows + r;
                     ok[u] = ok[u] && r < tile_rows && cc[u] < C;
                     sv[u] = ok[u] ? Sq[cc[u] * QLEN + i] : 0.f;
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < FLY; ++u)
                     if (ok[u]) visit(sv[u], cc[u]);
             }
         };
+        // (listed with no tile at all: scores that are not numbers; sel_tile is not read then, n_items is zero)
+        bool ranked = false;  // the keys of this token are in LDS, to be ranked by counting
+        int n_x = 0;
         if (!APPROX) {
             walk([&](float sv, int64_t cc) { scq_insert_key<NP>(best, plaid_make_key(sv, (uint32_t)cc)); });
         } else {
             // Only a row that can be among the nprobe best (score >= T - 2 eps) is ranked, and by its exact score.  The
-            // rows are listed first and re-evaluated one per lane, all at once; a token with more such rows than lanes
-            // (many equal scores) re-evaluates them as it meets them.
+            // rows are listed first and re-evaluated all at once: staged in LDS, a thread each.  A token with more such rows
+            // than lanes (many equal scores) re-evaluates them as it meets them.
             walk([&](float sv, int64_t cc) {
                 if (sv >= T) {
-                    const int pos = atomicAdd(&xc_cnt[i], 1);
-                    if (pos < TAIL_XCAP) xc_id[i][pos] = (int32_t)cc;
+                    const int pos = atomicAdd(&sh.xc_cnt[i], 1);
+                    if (pos < TAIL_XCAP) sh.xc_id[i][pos] = (int32_t)cc;
                 }
             });
             __syncthreads();
-            const int n_x = xc_cnt[i];
-            if (n_x <= TAIL_XCAP) {
-                if (l < n_x) {
-                    const int32_t c = xc_id[i][l];
-                    best[0] = plaid_make_key(plaid_exact_dot(x.Cm + (int64_t)c * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)c);
+            n_x = sh.xc_cnt[i];
+            if (tid < 64) {  // where each token's rows start in the list of all
+                const int n = tid < QLEN && sh.xc_cnt[tid & (QLEN - 1)] <= TAIL_XCAP ? sh.xc_cnt[tid & (QLEN - 1)] : 0;
+                int incl = n;
+#pragma unroll
+                for (int d = 1; d < QLEN; d <<= 1) {
+                    const int below = __shfl_up(incl, d);
+                    incl += tid >= d ? below : 0;
                 }
-            } else {
+                if (tid < QLEN) sh.xc_first[tid] = incl - n;
+                if (tid == QLEN - 1) sh.xc_first[QLEN] = incl;
+            }
+            __syncthreads();
+            const int n_all = sh.xc_first[QLEN];  // uniform
+            ranked = n_x <= TAIL_XCAP;
+            if (x.matrix && n_all <= TAIL_ROWS) {
+                // a token's lanes fetch its rows, a 16-byte piece per lane, all of them before the first is used; the lower half
+                // of the dimensions is staged and multiplied, then the upper half (see tail_exact_rows; a wave keeps its tiles'
+                // sums in between)
+                constexpr int PIECES = NP <= 2 ? 4 : 8;
+                float4 piece[PIECES];
+                const float *src = x.Cm + 4 * l;
+                const int mine = ranked ? n_x : 0;
+#pragma unroll
+                for (int u = 0; u < PIECES; ++u) {
+                    piece[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (u < mine) piece[u] = *reinterpret_cast<const float4 *>(src + (int64_t)sh.xc_id[i][u] * DIM);
+                }
+                if (ranked && l < n_x) sh.row_of[sh.xc_first[i] + l] = (int16_t)(i * TAIL_XCAP + l);
+                constexpr int TILES = TAIL_ROWS / 16 * (QLEN / 16) / (TAIL_THREADS / 64);  // of a wave
+                static_assert(TILES * (TAIL_THREADS / 64) == TAIL_ROWS / 16 * (QLEN / 16), "every wave has as many tiles");
+                const int lane = tid & 63, li = lane & 15, lg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+                scq_double4 acc[TILES];
+#pragma unroll
+                for (int t = 0; t < TILES; ++t) acc[t] = scq_double4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+                for (int half = 0; half < 2; ++half) {
+                    if (half) __syncthreads();  // the lower half is used
+                    if (l / (TAIL_LANES / 2) == half) {
+                        float *dst = sh.row + sh.xc_first[i] * TAIL_HSTRIDE + 4 * (l % (TAIL_LANES / 2));
+#pragma unroll
+                        for (int u = 0; u < PIECES; ++u)
+                            if (u < mine) *reinterpret_cast<float4 *>(dst + u * TAIL_HSTRIDE) = piece[u];
+                        for (int u = PIECES; u < mine; ++u)  // (near ties)
+                            *reinterpret_cast<float4 *>(dst + u * TAIL_HSTRIDE) =
+                                *reinterpret_cast<const float4 *>(src + (int64_t)sh.xc_id[i][u] * DIM);
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) {
+                        const int at = wave + t * (TAIL_THREADS / 64), r0 = 16 * (at / (QLEN / 16)), c0 = 16 * (at % (QLEN / 16));
+                        if (r0 < n_all) {  // uniform
+                            const float *a = sh.row + (r0 + li) * TAIL_HSTRIDE + lg, *bq = sh.Qs + (c0 + li) * TAIL_QSTRIDE + half * (DIM / 2) + lg;
+#pragma unroll 8
+                            for (int k = 0; k < DIM / 8; ++k)
+                                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[4 * k], (double)bq[4 * k], acc[t], 0, 0, 0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < TILES; ++t) {
+                    const int at = wave + t * (TAIL_THREADS / 64), r0 = 16 * (at / (QLEN / 16)), c0 = 16 * (at % (QLEN / 16));
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (r0 + 4 * r + lg < n_all) {  // (the row's own token is the only one of interest)
+                            const int of = sh.row_of[r0 + 4 * r + lg];
+                            if (of / TAIL_XCAP == c0 + li) sh.xscore[c0 + li][of % TAIL_XCAP] = (float)acc[t][r];
+                        }
+                }
+            } else if (ranked && l < n_x) {
+                sh.xscore[i][l] = plaid_exact_dot(x.Cm + (int64_t)sh.xc_id[i][l] * DIM, sh.Qs + i * TAIL_QSTRIDE);
+            }
+            if (!ranked)
                 walk([&](float sv, int64_t cc) {
-                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(plaid_exact_dot(x.Cm + cc * DIM, Qq + i * TAIL_QSTRIDE), (uint32_t)cc));
+                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(plaid_exact_dot(x.Cm + cc * DIM, sh.Qs + i * TAIL_QSTRIDE), (uint32_t)cc));
                 });
+            __syncthreads();
+        }
+        // A list entry can only be missing when the scores are not numbers (a query holding NaN compares false against
+        // every threshold): later kernels index the inverted lists with these ids, so such a slot gets centroid j
+        // (nprobe <= C), never an id out of range.
+        int32_t *probed_i = o.probed + ((int64_t)q * QLEN + i) * nprobe;
+        auto put = [&](int j, int32_t id) {
+            probed_i[j] = id;
+            sh.idl[i * nprobe + j] = id;
+        };
+        if (__any(!ranked)) {
+            // shuffle tree over the 32 lanes of this token (lanes l and l ^ d exchange lists; both keep the merged list)
+#pragma unroll
+            for (int d = 1; d < TAIL_LANES; d <<= 1) {
+                uint64_t other[NP];
+#pragma unroll
+                for (int j = 0; j < NP; ++j) other[j] = __shfl_xor(best[j], d);
+#pragma unroll
+                for (int j = 0; j < NP; ++j) scq_insert_key<NP>(best, other[j]);
             }
         }
-        // shuffle tree over the 32 lanes of this token (lanes l and l ^ d exchange lists; both keep the merged list)
-#pragma unroll
-        for (int d = 1; d < TAIL_LANES; d <<= 1) {
-            uint64_t other[NP];
-#pragma unroll
-            for (int j = 0; j < NP; ++j) other[j] = __shfl_xor(best[j], d);
-#pragma unroll
-            for (int j = 0; j < NP; ++j) scq_insert_key<NP>(best, other[j]);
-        }
-        if (l == 0) {
+        if (ranked) {
+            // each key's rank by counting (keys are unique)
+            if (l < n_x) {
+                const uint64_t key = plaid_make_key(sh.xscore[i][l], (uint32_t)sh.xc_id[i][l]);
+                int rank = 0;
+                for (int j = 0; j < n_x; ++j) rank += plaid_make_key(sh.xscore[i][j], (uint32_t)sh.xc_id[i][j]) < key ? 1 : 0;
+                if (rank < nprobe) put(rank, (int32_t)(key & 0xFFFFFFFFu));
+            }
+            if (l >= n_x && l < nprobe) put(l, l);
+        } else if (l == 0) {
 #pragma unroll
             for (int j = 0; j < NP; ++j)
-                if (j < nprobe) {
-                    // A list entry can only be missing when the scores are not numbers (a query holding NaN compares
-                    // false against every threshold): later kernels index the inverted lists with these ids, so such a
-                    // slot gets centroid j (nprobe <= C), never an id out of range.
-                    const int32_t id = best[j] == PLAID_KEY_MAX ? j : (int32_t)(best[j] & 0xFFFFFFFFu);
-                    o.probed[((int64_t)q * QLEN + i) * nprobe + j] = id;
-                    idl[i * nprobe + j] = id;
-                }
-            top1[i] = best[0] == PLAID_KEY_MAX ? 0 : (int32_t)(best[0] & 0xFFFFFFFFu);
+                if (j < nprobe) put(j, best[j] == PLAID_KEY_MAX ? j : (int32_t)(best[j] & 0xFFFFFFFFu));
         }
     }
     __syncthreads();
-    // ascending duplicate-free union of the n = 32 * nprobe (<= 256) probed ids by counting: an id is kept at its first
-    // occurrence, at position = number of distinct smaller ids.  Four lanes share the n comparisons of one id.
+    // ascending duplicate-free union of the n = 32 * nprobe (<= 256) probed ids: each id's place in sorted order by counting
+    // (four lanes share the comparisons, four ids per read), then those that differ from the id before them
     {
         const int n = QLEN * nprobe;
         const int t = tid >> 2, part = tid & 3;
-        const int32_t id = t < n ? idl[t] : 0x7FFFFFFF;
-        int earlier_same = 0;
-        for (int u = part; u < n; u += 4) earlier_same += (idl[u] == id && u < t) ? 1 : 0;
-        earlier_same += __shfl_xor(earlier_same, 1);
-        earlier_same += __shfl_xor(earlier_same, 2);
-        const bool fo = t < n && earlier_same == 0;
-        // position = number of first occurrences with a smaller id
-        __shared__ int32_t first[256];
-        if (part == 0 && t < n) first[t] = fo ? 1 : 0;
-        __syncthreads();
-        int pos = 0;
-        for (int u = part; u < n; u += 4) pos += (first[u] && idl[u] < id) ? 1 : 0;
-        pos += __shfl_xor(pos, 1);
-        pos += __shfl_xor(pos, 2);
-        if (fo && part == 0) o.uniq[(int64_t)q * o.uniq_stride + pos] = id;
-        const int total = __syncthreads_count(fo && part == 0);
-        if (tid == 0) o.n_uniq[q] = total;
-    }
-    if (APPROX) {
-        // Eq. 5 for the rows the score kernel left open.  Rounds of at most TAIL_AMB rows: the rows of a range of bitmap
-        // words are listed in LDS, then their 32 entries each are spread over the workgroup.  (One round, a handful of
-        // rows, unless the threshold sits where many row maxima do.)
-        __shared__ int32_t amb_rows[TAIL_AMB];
-        __shared__ int32_t amb_n, amb_total;
-        uint32_t *kbq = keepbits + (int64_t)q * keep_words;
-        const uint32_t *abq = x.ambbits + (int64_t)q * keep_words;
-        if (tid == 0) amb_total = 0;
-        __syncthreads();
-        {
-            int cnt = 0;
-            for (int64_t w0 = tid; w0 < keep_words; w0 += 8 * TAIL_THREADS) {
-                uint32_t v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = w0 + u * TAIL_THREADS < keep_words ? abq[w0 + u * TAIL_THREADS] : 0u;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) cnt += __popc(v[u]);
+        const int32_t id = t < n ? sh.idl[t] : 0x7FFFFFFF;
+        int place = 0;
+        if (t < n)
+#pragma unroll 2
+            for (int u = 4 * part; u < n; u += 16) {
+                const int4 v = *reinterpret_cast<const int4 *>(sh.idl + u);
+                place += (v.x < id || (v.x == id && u < t) ? 1 : 0) + (v.y < id || (v.y == id && u + 1 < t) ? 1 : 0) +
+                         (v.z < id || (v.z == id && u + 2 < t) ? 1 : 0) + (v.w < id || (v.w == id && u + 3 < t) ? 1 : 0);
             }
-            if (cnt) atomicAdd(&amb_total, cnt);
+        place += __shfl_xor(place, 1);
+        place += __shfl_xor(place, 2);
+        if (part == 0 && t < n) sh.sorted[place] = id;
+        __syncthreads();
+        if (tid < 256) {  // four whole waves
+            const bool first = tid < n && (tid == 0 || sh.sorted[tid] != sh.sorted[tid - 1]);
+            const unsigned long long m = __ballot(first);
+            if ((tid & 63) == 0) sh.wave_n[tid >> 6] = __popcll(m);
         }
         __syncthreads();
-        const int total = amb_total;  // uniform
+        if (tid < n) {
+            const int32_t v = sh.sorted[tid];
+            const bool first = tid == 0 || v != sh.sorted[tid - 1];
+            const unsigned long long m = __ballot(first);
+            int before = 0;
+            for (int w = 0; w < (tid >> 6); ++w) before += sh.wave_n[w];
+            if (first) o.uniq[(int64_t)q * o.uniq_stride + before + __popcll(m & ((1ull << (tid & 63)) - 1ull))] = v;
+        }
+        if (tid == 0) o.n_uniq[q] = sh.wave_n[0] + sh.wave_n[1] + sh.wave_n[2] + sh.wave_n[3];
+    }
+}
+
+template <bool APPROX>
+struct TableScratch {
+    SurvivorScratch t;
+    SurvivorRows x[APPROX ? 1 : 0];
+};
+
+template <bool APPROX>
+__device__ __forceinline__ void tail_survivors(TableScratch<APPROX> &ts, int q, const float *__restrict__ S, int64_t C,
+                                               uint32_t *__restrict__ kbq, int64_t keep_words, const float *__restrict__ gmq, int ng,
+                                               const Stage1Out o, const Stage1Exact x)
+{
+    SurvivorScratch &sh = ts.t;
+    const int tid = threadIdx.x;
+    const float *__restrict__ Sq = S + (int64_t)q * C * QLEN;
+    const uint32_t *abq = APPROX ? x.ambbits + (int64_t)q * keep_words : nullptr;
+    if (tid == 0) {
+        sh.misc[0] = 0;
+        sh.misc[1] = -1;
+        sh.amb_total = 0;
+    }
+    if (APPROX) tail_stage_query(x.Q, q, ts.x[0].Qs);
+    if (APPROX && tid == 0) ts.x[0].matrix = x.matrix;
+    __syncthreads();
+    stage1_list_survivors(kbq, abq, keep_words, sh);
+    __syncthreads();
+    if (APPROX) {
+        // Eq. 5 for the rows the score kernel left open.  Rounds of at most TAIL_AMB rows: the rows of a range of bitmap
+        // words are listed in LDS, then their 32 entries each are spread over the workgroup; a row that passes joins the
+        // survivors, once, and its bit the pruning words that later kernels read.  (One round, a handful of rows, unless the
+        // threshold sits where many row maxima do.)
+        const int total = sh.amb_total;  // uniform
         // words taken per round: all of them when every open row fits the list (the usual case: one round), else as
         // many as always fit
         const int64_t round_words = total <= TAIL_AMB ? keep_words : TAIL_AMB / 32;
         for (int64_t w0 = 0; total > 0 && w0 < keep_words; w0 += round_words) {
+            int32_t *amb_rows = ts.x[0].amb;
             __syncthreads();
-            if (tid == 0) amb_n = 0;
+            if (tid == 0) sh.amb_n = 0;
+            if (tid < TAIL_AMB / 32) sh.amb_pass[tid] = 0u;
             __syncthreads();
             const int64_t w1 = w0 + round_words < keep_words ? w0 + round_words : keep_words;
             for (int64_t w = w0 + tid; w < w1; w += TAIL_THREADS) {
@@ -982,34 +1181,68 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
                 while (v) {
                     const int b = __ffs(v) - 1;
                     v &= v - 1;
-                    amb_rows[atomicAdd(&amb_n, 1)] = (int32_t)(w * 32 + b);
+                    amb_rows[atomicAdd(&sh.amb_n, 1)] = (int32_t)(w * 32 + b);
                 }
             }
             __syncthreads();
-            const int n_amb = amb_n;
+            const int n_amb = sh.amb_n;
             for (int p = tid; p < n_amb * QLEN; p += TAIL_THREADS) {
-                const int64_t c = amb_rows[p >> 5];
+                const int32_t c = amb_rows[p >> 5];
                 const int tok = p & 31;
-                if (Sq[c * QLEN + tok] >= x.t_lo && plaid_exact_dot(x.Cm + c * DIM, Qq + tok * TAIL_QSTRIDE) >= x.t_cs)
-                    atomicOr(&kbq[c >> 5], 1u << (c & 31));
+                if (Sq[(int64_t)c * QLEN + tok] >= x.t_lo &&
+                    plaid_exact_dot(x.Cm + (int64_t)c * DIM, ts.x[0].Qs + tok * TAIL_QSTRIDE) >= x.t_cs) {
+                    const uint32_t bit = 1u << ((p >> 5) & 31);
+                    if (!(atomicOr(&sh.amb_pass[p >> 10], bit) & bit)) {  // the first of the row's entries
+                        atomicOr(&kbq[c >> 5], 1u << (c & 31));
+                        const int pos = atomicAdd(&sh.misc[0], 1);
+                        if (pos < S2_MAX_KEPT) sh.ids[pos] = c;
+                    }
+                }
             }
         }
-        // The updates of the pruning words above are atomics, performed in the second-level cache, and the table below
-        // reads the words there too (atomic loads): the barrier's wait for this wave's outstanding memory operations is
-        // all the ordering the two need.
         __syncthreads();
     }
-    stage1_survivor_table<APPROX>(S + (int64_t)q * C * QLEN, C, keepbits + (int64_t)q * keep_words, keep_words, top1,
-                                  o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT,
-                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, ids, trial, colmm, Tx, misc, x.Cm, Qq,
-                                  o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
+    auto col_max = [&](float *colmm) {  // over the groups' maxima
+        float m = -INFINITY;
+        for (int64_t e = tid; e < (int64_t)ng * QLEN; e += TAIL_THREADS) m = fmaxf(m, gmq[e]);
+        float *part = sh.Tx;  // [the waves' halves][32]
+        part[tid] = m;
+        __syncthreads();
+        if (tid < QLEN) {
+            for (int w = 1; w < TAIL_THREADS / QLEN; ++w) m = fmaxf(m, part[w * QLEN + tid]);
+            colmm[tid] = m;
+        }
+    };
+    static_assert(TAIL_THREADS <= S2_MAX_KEPT * TX_STRIDE, "the partial maxima take the place of the survivors' entries");
+    stage1_survivor_table<APPROX>(Sq, C, col_max, o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT,
+                                  o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, sh, APPROX ? ts.x : nullptr, x.Cm, o.ivf_offsets, q, o.qcount,
+                                  o.qlist, o.qlist_stride, o.need_hash);
+}
+
+template <int NP, bool APPROX>
+__global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *__restrict__ S, int64_t C,
+                                                                   uint32_t *__restrict__ keepbits, int64_t keep_words,
+                                                                   const float *__restrict__ tilemax, int nblk, int tile_rows,
+                                                                   const float *__restrict__ gmax, int ng, int gs,
+                                                                   int nprobe, Stage1Out o, Stage1Exact x)
+{
+    __shared__ __align__(16) union {
+        ProbeScratch<APPROX> p;
+        TableScratch<APPROX> t;
+    } sh;
+    const int q = blockIdx.x;
+    const float *gmq = gmax + (int64_t)q * ng * QLEN;
+    if (blockIdx.y == 0)
+        tail_probes<NP, APPROX>(sh.p, q, S, C, tilemax + (int64_t)q * nblk * QLEN, nblk, tile_rows, gmq, ng, gs, nprobe, o, x);
+    else
+        tail_survivors<APPROX>(sh.t, q, S, C, keepbits + (int64_t)q * keep_words, keep_words, gmq, ng, o, x);
 }
 
 // np = capacity of the tail's lists (1, 2, 4 or 8 >= nprobe); np = 0: scores and pruning bits only (large nprobe).
 static void launch_fused(hipStream_t st, int phases, int np, const float *centroids, int64_t C, const float *Q, const void *Qx,
-                         int form, const void *A16, int nq, float t_cs, float *S, uint32_t *keepbits, uint32_t *ambbits,
-                         int64_t keep_words, float *tilemax, int nprobe, const Stage1Out &o, uint32_t *zero, int64_t zero_words,
-                         unsigned long long *score_clocks)
+                         int form, bool matrix_ok, const void *A16, int nq, float t_cs, float *S, uint32_t *keepbits, uint32_t *ambbits,
+                         int64_t keep_words, float *tilemax, float *groupmax, int nprobe, const Stage1Out &o, uint32_t *zero,
+                         int64_t zero_words, unsigned long long *score_clocks)
 {
     const bool matrix_form = form == PLAID_SCQ_MATRIX;
     const int tile_rows = form == PLAID_SCQ_VECTOR ? SCQ_ROWS : SM_WROWS;  // rows per tile of column maxima
@@ -1020,7 +1253,7 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
     static_assert(SM_WROWS == 32, "the split-fp16 kernel emits column maxima per 32 rows, like the matrix form");
     if (!(phases & PLAID_STAGE1_SCORES)) {
     } else if (form == PLAID_SCQ_SPLIT16) {
-        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, score_clocks);
+        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, tmx ? groupmax : nullptr, score_clocks);
     } else if (matrix_form) {
         if (nq == 1)
             hipLaunchKernelGGL(scq_mfma_kernel<1>, dim3(1, nblk), dim3(SM_THREADS), 0, st, centroids, C, Q, nq, t_cs, S, keepbits,
@@ -1040,9 +1273,15 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
         x.t_cs = t_cs;
         x.t_lo = (t_cs > -INFINITY && t_cs < INFINITY) ? nextafterf(t_cs - PLAID_SCQ16_EPS, -INFINITY) : t_cs;
         x.margin = 2.0f * PLAID_SCQ16_EPS;
+        x.matrix = matrix_ok;
+        // the split-fp16 kernel reports maxima of groups of tiles too, where there is room for them
+        const bool grouped = form == PLAID_SCQ_SPLIT16 && groupmax;
+        const int gs = grouped ? 3 : 0, ng = (n_tiles + (1 << gs) - 1) >> gs;
+        static_assert(PLAID_SCQ16_GROUP_ROWS == SM_WROWS << 3, "eight tiles per group");
+        const float *gmx = grouped ? groupmax : tilemax;
 #define TAIL(NP_, AP_)                                                                                                     \
-    hipLaunchKernelGGL((stage1_tail_kernel<NP_, AP_>), dim3(nq), dim3(TAIL_THREADS), 0, st, S, C, keepbits, keep_words,     \
-                       tilemax, n_tiles, tile_rows, nprobe, o, x)
+    hipLaunchKernelGGL((stage1_tail_kernel<NP_, AP_>), dim3(nq, 2), dim3(TAIL_THREADS), 0, st, S, C, keepbits, keep_words, \
+                       tilemax, n_tiles, tile_rows, gmx, ng, gs, nprobe, o, x)
         if (form == PLAID_SCQ_SPLIT16) {
             if (np == 1) TAIL(1, true);
             else if (np == 2) TAIL(2, true);
@@ -1065,9 +1304,14 @@ size_t plaid_stage1_tilemax_bytes(int64_t C, int nq, int nprobe)
     return (size_t)nq * ((C + rows - 1) / rows) * QLEN * 4;
 }
 
+size_t plaid_stage1_groupmax_bytes(int64_t C, int nq)
+{
+    return (size_t)nq * ((C + PLAID_SCQ16_GROUP_ROWS - 1) / PLAID_SCQ16_GROUP_ROWS) * QLEN * 4;
+}
+
 void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int64_t C, const float *Q, void *Qd, int form,
-                         const void *A16, int nq, float t_cs, int nprobe, float *S, uint32_t *keepbits, uint32_t *ambbits,
-                         int64_t keep_words, float *tilemax, uint32_t *zero, int64_t zero_words, int32_t *probed,
+                         bool matrix_ok, const void *A16, int nq, float t_cs, int nprobe, float *S, uint32_t *keepbits, uint32_t *ambbits,
+                         int64_t keep_words, float *tilemax, float *groupmax, uint32_t *zero, int64_t zero_words, int32_t *probed,
                          int32_t *uniq, int uniq_stride, int32_t *n_uniq, const Stage2Buffers &s2, void *probe_scratch,
                          size_t probe_scratch_bytes, unsigned long long *score_clocks)
 {
@@ -1094,11 +1338,11 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
     o.need_hash = s2.need_hash;
     const int np = nprobe == 1 ? 1 : (nprobe == 2 ? 2 : (nprobe <= 4 ? 4 : (nprobe <= PLAID_PROBE_FAST_MAX ? 8 : 0)));
     if (np > 0)
-        launch_fused(st, phases, np, centroids, C, Q, Qd, form, A16, nq, t_cs, S, keepbits, ambbits, keep_words, tilemax, nprobe,
+        launch_fused(st, phases, np, centroids, C, Q, Qd, form, matrix_ok, A16, nq, t_cs, S, keepbits, ambbits, keep_words, tilemax, groupmax, nprobe,
                      o, zero, zero_words, score_clocks);
     else {
         // large nprobe: scores and pruning bits here, probes through the generic selection, survivor table after it
-        launch_fused(st, phases, 0, centroids, C, Q, Qd, form, A16, nq, t_cs, S, keepbits, ambbits, keep_words, tilemax, nprobe,
+        launch_fused(st, phases, 0, centroids, C, Q, Qd, form, matrix_ok, A16, nq, t_cs, S, keepbits, ambbits, keep_words, tilemax, groupmax, nprobe,
                      o, zero, zero_words, score_clocks);
         if (phases & PLAID_STAGE1_PROBES) {
             plaid_launch_top_nprobe_general(st, S, C, nq, nprobe, probed, uniq, uniq_stride, n_uniq, probe_scratch,

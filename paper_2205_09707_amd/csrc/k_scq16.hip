@@ -112,13 +112,15 @@ __device__ __forceinline__ void scq16_store_part(float *__restrict__ s0, const f
 }
 
 // Out of the accumulators of one query: the scores (val, scaled back), the tiles' column maxima and the pruning words.
+// Returns the column maxima over the wave's tiles.
 template <int NT>
-__device__ __forceinline__ void scq16_reduce(const scq16_floatx16 (&acc)[NT], float (&val)[NT][16], const int (&nvalid)[NT],
+__device__ __forceinline__ float scq16_reduce(const scq16_floatx16 (&acc)[NT], float (&val)[NT][16], const int (&nvalid)[NT],
                                              int64_t tile0, int64_t n_blk, int q, int lane, float t_lo, float t_hi,
                                              uint32_t *__restrict__ keepbits, uint32_t *__restrict__ ambbits, int64_t keep_words,
                                              float *__restrict__ tilemax)
 {
     const int n = lane & 31, h = lane >> 5;
+    float wmax = -INFINITY;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
 #pragma unroll
@@ -153,12 +155,14 @@ __device__ __forceinline__ void scq16_reduce(const scq16_floatx16 (&acc)[NT], fl
         }
         const uint32_t valid = nvalid[t] == 32 ? 0xFFFFFFFFu : (1u << nvalid[t]) - 1u;  // rows past the end never pass
         cmax = fmaxf(cmax, __shfl_xor(cmax, 32));
+        wmax = fmaxf(wmax, cmax);
         if (tilemax && h == 0) tilemax[((int64_t)q * n_blk + tile) * QLEN + n] = cmax;
         if (lane == 0) {
             keepbits[(int64_t)q * keep_words + tile] = sure & valid;
             ambbits[(int64_t)q * keep_words + tile] = maybe & ~sure & valid;
         }
     }
+    return wmax;
 }
 
 // The kernel's body.  WHOLE (uniform over the wave): each of its tiles has all 32 rows, so every score store is
@@ -166,10 +170,11 @@ __device__ __forceinline__ void scq16_reduce(const scq16_floatx16 (&acc)[NT], fl
 // of stores between a request for operands and the wait for them is the same on every path: the memory counter retires
 // in order, and a wait sized for the path with the fewest stores would sit out the score stores of the others.
 template <int NT, bool WHOLE>
-__device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16,
+__device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], float (&gmax)[2][H16_WAVES][QLEN], const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16,
                                            int64_t C, const scq16_half8 *__restrict__ B16, int q_begin, int q_end, float t_lo,
                                            float t_hi, float *__restrict__ S, uint32_t *__restrict__ keepbits,
-                                           uint32_t *__restrict__ ambbits, int64_t keep_words, float *__restrict__ tilemax)
+                                           uint32_t *__restrict__ ambbits, int64_t keep_words, float *__restrict__ tilemax,
+                                           float *__restrict__ groupmax)
 {
     constexpr int NPRE = H16_TILE_VEC / H16_THREADS;  // operand vectors a thread moves per query
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
@@ -244,8 +249,17 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], c
 #pragma unroll
             for (int k = 0; k < NPRE; ++k) pre[k] = bsrc[k * H16_THREADS];
         }
-        scq16_reduce<NT>(acc, val, nvalid, tile0, n_blk, q, lane, t_lo, t_hi, keepbits, ambbits, keep_words, tilemax);
-        scq16_lds_barrier();  // publishes nxt; every wave is done reading buf
+        const float wmax = scq16_reduce<NT>(acc, val, nvalid, tile0, n_blk, q, lane, t_lo, t_hi, keepbits, ambbits, keep_words, tilemax);
+        float (&gm)[H16_WAVES][QLEN] = gmax[(q - q_begin) & 1];
+        if (h == 0) gm[wave][n] = wmax;
+        scq16_lds_barrier();  // publishes nxt and gm; every wave is done reading buf
+        // the maxima over the workgroup's rows, by each wave in turn (gm is written again two barriers from here)
+        if (groupmax && wave == (q & (H16_WAVES - 1)) && h == 0) {
+            float m = gm[0][n];
+#pragma unroll
+            for (int w = 1; w < H16_WAVES; ++w) m = fmaxf(m, gm[w][n]);
+            groupmax[((int64_t)q * gridDim.x + blockIdx.x) * QLEN + n] = m;
+        }
     };
     struct no_t { enum { value = 0 }; };
     struct yes_t { enum { value = 1 }; };
@@ -267,7 +281,7 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], c
 
 // Grid: x = block of 32 * H16_WAVES * NT centroids, y = group of qg queries.  A16: a whole number of workgroups' tiles
 // (rows past C are zero).  keepbits / ambbits: [q][keep_words], bit c = row c passes Eq. 5 for sure / is ambiguous;
-// tilemax: [q][ceil(C/32)][32].
+// tilemax: [q][ceil(C/32)][32]; groupmax (may be null): [q][gridDim.x][32], the maxima over the workgroup's rows.
 // The loop over the group's queries is software-pipelined twice over.  Operands: those of query q + 1 are requested
 // before the matrix instructions of query q, moved into the other LDS buffer right after them (by then they have
 // arrived), and those of q + 2 are requested.  Scores: the results of query q leave the accumulators (scaled, reduced
@@ -277,9 +291,10 @@ template <int NT>
 __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     const scq16_half8 *__restrict__ A16, int64_t C, const scq16_half8 *__restrict__ B16, int nq, int qg, float t_lo, float t_hi,
     float *__restrict__ S, uint32_t *__restrict__ keepbits, uint32_t *__restrict__ ambbits, int64_t keep_words,
-    float *__restrict__ tilemax, unsigned long long *__restrict__ clocks)
+    float *__restrict__ tilemax, float *__restrict__ groupmax, unsigned long long *__restrict__ clocks)
 {
     __shared__ scq16_half8 Bs[2][H16_TILE_VEC];
+    __shared__ float gmax[2][H16_WAVES][QLEN];
     // clocks (may be null): every workgroup adds how far the shader-clock counter and the fixed-rate (100 MHz) timer moved
     // while it ran -- the ratio of the two sums is the clock the chip held during this kernel
     const long long sc0 = clocks ? clock64() : 0, rt0 = clocks ? wall_clock64() : 0;
@@ -296,9 +311,9 @@ __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     }
     // (the barriers inside are reached by all four waves in either instance: both run the same loop over the queries)
     if (whole)
-        scq16_body<NT, true>(Bs, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax);
+        scq16_body<NT, true>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
     else
-        scq16_body<NT, false>(Bs, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax);
+        scq16_body<NT, false>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
     if (clocks && threadIdx.x == 0) {
         atomicAdd(&clocks[0], (unsigned long long)(clock64() - sc0));
         atomicAdd(&clocks[1], (unsigned long long)(wall_clock64() - rt0));
@@ -355,8 +370,10 @@ void plaid_launch_scq16_split_queries(hipStream_t st, const float *Q, int nq, vo
 }
 
 void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *B16, int nq, float t_cs, float *S,
-                        uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax, unsigned long long *clocks)
+                        uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax, float *groupmax,
+                        unsigned long long *clocks)
 {
+    static_assert(32 * H16_WG_TILES == PLAID_SCQ16_GROUP_ROWS, "a workgroup's rows are a group");
     // the two thresholds of the pruning test, rounded away from t_cs (infinite t_cs: both equal it, nothing is ambiguous)
     float t_lo = t_cs, t_hi = t_cs;
     if (t_cs > -INFINITY && t_cs < INFINITY) {
@@ -372,5 +389,5 @@ void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *
     if (qg > nq) qg = nq;
     const unsigned gy = (unsigned)((nq + qg - 1) / qg);
     hipLaunchKernelGGL((scq16_kernel<H16_NT>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
-                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, clocks);
+                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax, clocks);
 }

@@ -72,6 +72,21 @@ __device__ __forceinline__ float plaid_exact_dot(const float *__restrict__ crow,
     return (float)acc;
 }
 
+// The same with the centroid's row in LDS too.
+__device__ __forceinline__ float plaid_exact_dot_lds(const float *crow, const float *qrow)
+{
+    double acc = 0.0;
+#pragma unroll 4
+    for (int d = 0; d < DIM; d += 4) {
+        const float4 c = *reinterpret_cast<const float4 *>(crow + d), x = *reinterpret_cast<const float4 *>(qrow + d);
+        acc = fma((double)c.x, (double)x.x, acc);
+        acc = fma((double)c.y, (double)x.y, acc);
+        acc = fma((double)c.z, (double)x.z, acc);
+        acc = fma((double)c.w, (double)x.w, acc);
+    }
+    return (float)acc;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Selection (k_select.hip): first m keys in ascending order out of per-segment lists.
 // ---------------------------------------------------------------------------------------------
@@ -143,11 +158,12 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok);  // returns a hipError_t 
 #define PLAID_SCQ_MATRIX 1
 #define PLAID_SCQ_SPLIT16 2
 void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int64_t C, const float *Q, void *Qx, int form,
-                         const void *A16, int nq, float t_cs, int nprobe, float *S, uint32_t *keepbits, uint32_t *ambbits,
-                         int64_t keep_words, float *tilemax, uint32_t *zero, int64_t zero_words, int32_t *probed,
+                         bool matrix_ok /* plaid_scq_matrix_form_ok */, const void *A16, int nq, float t_cs, int nprobe, float *S, uint32_t *keepbits, uint32_t *ambbits,
+                         int64_t keep_words, float *tilemax, float *groupmax /* may be null */, uint32_t *zero, int64_t zero_words, int32_t *probed,
                          int32_t *uniq, int uniq_stride, int32_t *n_uniq, const struct Stage2Buffers &s2, void *probe_scratch,
                          size_t probe_scratch_bytes, unsigned long long *score_clocks = nullptr);
 size_t plaid_stage1_tilemax_bytes(int64_t C, int nq, int nprobe);
+size_t plaid_stage1_groupmax_bytes(int64_t C, int nq);
 
 // Split-fp16 form of Eq. 2 (k_scq16.hip).  S differs from the exact dot products by at most PLAID_SCQ16_EPS for
 // vectors of norm <= 1 (components within fp16's range); keepbits holds the rows that pass Eq. 5 even if every entry
@@ -155,6 +171,8 @@ size_t plaid_stage1_tilemax_bytes(int64_t C, int nq, int nprobe);
 #define PLAID_SCQ16_EPS 3.0517578125e-05f  // 2^-15
 // The kernel forms 2^11 a1 in fp16 on the centroid side: components must stay below this magnitude.
 #define PLAID_SCQ16_CENTROID_MAX 31.0f
+// Rows whose column maxima a workgroup of the kernel reports together (groupmax, [nq][ceil(C / 256)][32], may be null).
+#define PLAID_SCQ16_GROUP_ROWS 256
 // max_bits[0] (zero on entry) = bit pattern of the largest |x[i]|, infinity's when a value is not a number.
 void plaid_launch_scq16_max_abs(hipStream_t st, const float *x, int64_t n, uint32_t *max_bits);
 size_t plaid_scq16_centroid_bytes(int64_t C);  // operand form of the centroid table, built once per index
@@ -163,7 +181,7 @@ void plaid_launch_scq16_split_centroids(hipStream_t st, const float *centroids, 
 void plaid_launch_scq16_split_queries(hipStream_t st, const float *Q, int nq, void *B16, uint32_t *zero, int64_t zero_words);
 // clocks (may be null): [0] += shader-clock ticks, [1] += 100 MHz timer ticks, both summed over the workgroups.
 void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *B16, int nq, float t_cs, float *S,
-                        uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax,
+                        uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax, float *groupmax,
                         unsigned long long *clocks = nullptr);
 
 // General top-nprobe (nprobe > PLAID_PROBE_FAST_MAX): ranking keys of every S column through the generic selection.
