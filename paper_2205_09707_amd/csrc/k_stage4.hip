@@ -8,13 +8,14 @@
 //
 // The contraction runs on the half-precision matrix instruction with both operands split into two fp16
 // terms, x = x1 + 2^-11 x2 (|x - x1 - 2^-11 x2| <= 2^-22 |x|): three products per term, each exact in
-// fp32, the leading one in one accumulator and the two cross terms in a second, scaled one.  The table
-// therefore stores, per byte value, the fp16 terms of the bucket weights of the byte's dimensions, in
-// the order the instruction wants them: one 16-byte LDS read yields the operand halves of four
-// dimensions (2-bit codes) or the eight leading / eight trailing terms of a byte (1-bit codes), and the
-// decoded 32-token x 128 residual tile never leaves registers.  Against fp32 arithmetic the residual's
-// dot product loses at most 3 * 2^-22 |r||q|, far inside the score tolerance; it is 16 times cheaper on
-// the matrix pipe, which leaves the kernel bound by its gathers and its decoding.
+// fp32, the leading one in one accumulator and the two cross terms in a second, scaled one.  Two tables
+// hold, per byte value, the leading and the trailing fp16 terms of the bucket weights of the byte's
+// dimensions, in the order the instruction wants them: an LDS read yields half of an operand (2-bit codes)
+// or all of it (1-bit codes) in place, and the decoded 32-token x 128 residual tile never leaves registers.
+// (One vector instruction per byte, to form the address.  With both terms in one 16-byte entry, registers had to be moved, six
+// per byte; picking the terms by byte permutations from registers takes nine per byte.)
+// Against fp32 arithmetic the residual's dot product loses at most 3 * 2^-22 |r||q|, far inside the score
+// tolerance.
 // The standalone decompression kernel below produces the reconstructed vectors themselves
 // (centroid + weight, one fp32 addition).
 #include "plaid_internal.h"
@@ -61,41 +62,82 @@ __device__ __forceinline__ int table_slot(const uint8_t *__restrict__ r, int qua
     return 2 * r[quad >> 1] + (quad & 1);
 }
 
-// Operand table of the scoring kernel.  2-bit codes: hlut[v] = {x1 of the byte's four dimensions, x2 of the same}.
-// 1-bit codes: hlut[v] = x1 of the byte's eight dimensions, hlut[256 + v] = their x2.
+// Operand tables of the scoring kernels: entry v (S4_SECOND + v) holds the leading (trailing) fp16 terms of the
+// weights of the dimensions packed in byte v: four of them (2-bit codes) or eight.
+// (257 entries between them: the two halves of a byte are then two LDS reads, each straight to its operand; at a distance one
+// instruction can span the compiler makes them one, whose result has to be moved apart.)
+#define S4_SECOND 257
 template <int NBITS>
-__device__ __forceinline__ void build_half_tables(s4_half8 *hlut, const float *__restrict__ weights, int tid, int nthreads)
+struct S4Entry {
+    typedef s4_half4 type;
+};
+template <>
+struct S4Entry<1> {
+    typedef s4_half8 type;
+};
+template <int NBITS>
+__device__ __forceinline__ void s4_build_tables(typename S4Entry<NBITS>::type *hlut, const float *__restrict__ weights, int tid,
+                                                int nthreads)
 {
     for (int v = tid; v < 256; v += nthreads) {
-        s4_half8 a, b;
+        typename S4Entry<NBITS>::type a, b;
 #pragma unroll
         for (int d = 0; d < 8 / NBITS; ++d) {
-            const int idx = (v >> (8 - NBITS * (d + 1))) & ((1 << NBITS) - 1);
             _Float16 x1, x2;
-            s4_split(weights[idx], x1, x2);
-            if (NBITS == 2) {
-                a[d] = x1;
-                a[4 + d] = x2;
-            } else {
-                a[d] = x1;
-                b[d] = x2;
-            }
+            s4_split(weights[(v >> (8 - NBITS * (d + 1))) & ((1 << NBITS) - 1)], x1, x2);
+            a[d] = x1;
+            b[d] = x2;
         }
         hlut[v] = a;
-        if (NBITS == 1) hlut[256 + v] = b;
+        hlut[S4_SECOND + v] = b;
     }
+}
+// A half of the wave (h = lane / 32) contracts half of the 128 dimensions, the 2 NBITS packed words 2 NBITS h .. of a token;
+// step s = 0 .. 7 takes two bytes (2-bit codes) or one of them.
+__device__ __forceinline__ int s4_dim(int s, int h, int e)  // dimension of element e of the operands of step s, half h
+{
+    return 64 * h + 8 * s + e;
+}
+template <int NBITS>
+__device__ __forceinline__ void s4_decode(const uint32_t (&rw)[2 * NBITS], int s, const typename S4Entry<NBITS>::type *hlut,
+                                          s4_half8 &a1, s4_half8 &a2)
+{
+    if constexpr (NBITS == 2) {
+        const uint32_t w = rw[s >> 1] >> (16 * (s & 1)), b0 = w & 0xFFu, b1 = (w >> 8) & 0xFFu;
+        const s4_half4 x0 = hlut[b0], x1 = hlut[b1], y0 = hlut[S4_SECOND + b0], y1 = hlut[S4_SECOND + b1];
+        a1 = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
+        a2 = __builtin_shufflevector(y0, y1, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+        const uint32_t b = (rw[s >> 2] >> (8 * (s & 3))) & 0xFFu;
+        a1 = hlut[b];
+        a2 = hlut[S4_SECOND + b];
+    }
+}
+// fmaxf without the canonicalising copies the compiler puts in front of it.
+__device__ __forceinline__ float s4_max(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float s4_max3(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
 // The two fp16 terms of the query in the operand order of v_mfma_f32_32x32x16_f16, into LDS: lane 32 h + r of step s holds
-// query token r, dimensions 16 s + 8 h .. + 7.  All 256 threads of the workgroup call this, a barrier follows.
+// query token r, dimensions s4_dim(s, h, 0) .. + 7.  All 256 threads of the workgroup call this, a barrier follows.
 __device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_half8 (&qs)[2][8][64])
 {
-    for (int e = threadIdx.x; e < 8 * 64; e += 256) {
-        const int s = e >> 6, l = e & 63;
-        const float4 *p = reinterpret_cast<const float4 *>(Qq + (l & 31) * DIM + 16 * s + 8 * (l >> 5));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int e = (int)threadIdx.x + 256 * i, s = e >> 6, l = e & 63;
+        s4_half8 t1, t2;
+        const float4 *p = reinterpret_cast<const float4 *>(Qq + (l & 31) * DIM + s4_dim(s, l >> 5, 0));
         const float4 u = p[0], w = p[1];
         const float x[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-        s4_half8 t1, t2;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             _Float16 x1, x2;
@@ -105,6 +147,44 @@ __device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_
         }
         qs[0][s][l] = t1;
         qs[1][s][l] = t2;
+    }
+}
+
+// Residual dot products of 32 tokens (packed words rw, this half's) with the 32 query tokens: acc += leading products, acx +=
+// cross terms, scaled by 2^11.  TOKENS_A: rows = tokens, columns = query tokens; else the other way round.  The query
+// operands are read from LDS in every step, through an index the compiler cannot tell from the last call's (kept across
+// calls they would take 64 registers).  AHEAD: they and the table entries are requested one step of 16 dimensions ahead, for
+// which a kernel of four waves per SIMD lacks the registers.
+template <int NBITS, bool TOKENS_A, bool AHEAD>
+__device__ __forceinline__ void s4_products(const uint32_t (&rw)[2 * NBITS], const typename S4Entry<NBITS>::type *hlut,
+                                            const s4_half8 (&qs)[2][8][64], int lane, floatx16 &acc, floatx16 &acx)
+{
+    int ql = lane;
+    asm volatile("" : "+v"(ql));
+    s4_half8 a1, a2, q1 = qs[0][0][ql], q2 = qs[1][0][ql];
+    s4_decode<NBITS>(rw, 0, hlut, a1, a2);
+    if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        s4_half8 n1 = a1, n2 = a2, r1 = q1, r2 = q2;
+        if (s < 7) {
+            r1 = qs[0][s + 1][ql];
+            r2 = qs[1][s + 1][ql];
+            s4_decode<NBITS>(rw, s + 1, hlut, n1, n2);
+        }
+        acx = TOKENS_A ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q2, acx, 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(q2, a1, acx, 0, 0, 0);
+        acc = TOKENS_A ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q1, acc, 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(q1, a1, acc, 0, 0, 0);
+        acx = TOKENS_A ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, q1, acx, 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(q1, a2, acx, 0, 0, 0);
+        if (AHEAD && s < 7) {
+            __builtin_amdgcn_sched_group_barrier(0x002, NBITS, 0);              // the addresses,
+            __builtin_amdgcn_sched_group_barrier(0x100, NBITS == 2 ? 6 : 4, 0);  // LDS reads, then the matrix instructions
+            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+        }
+        a1 = n1, a2 = n2, q1 = r1, q2 = r2;
+        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -119,21 +199,21 @@ __device__ __forceinline__ float s4_column_maxima(const float (&mx)[16], int lan
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const float keep = b4 ? mx[8 + e] : mx[e], send = b4 ? mx[e] : mx[8 + e];
-        a8[e] = fmaxf(keep, __shfl_xor(send, 16));
+        a8[e] = s4_max(keep, __shfl_xor(send, 16));
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float keep = b3 ? a8[4 + e] : a8[e], send = b3 ? a8[e] : a8[4 + e];
-        a4[e] = fmaxf(keep, __shfl_xor(send, 8));
+        a4[e] = s4_max(keep, __shfl_xor(send, 8));
     }
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         const float keep = b2 ? a4[2 + e] : a4[e], send = b2 ? a4[e] : a4[2 + e];
-        a2[e] = fmaxf(keep, __shfl_xor(send, 4));
+        a2[e] = s4_max(keep, __shfl_xor(send, 4));
     }
     const float keep = b1 ? a2[1] : a2[0], send = b1 ? a2[0] : a2[1];
-    const float a1 = fmaxf(keep, __shfl_xor(send, 2));
-    return fmaxf(a1, __shfl_xor(a1, 1));
+    const float a1 = s4_max(keep, __shfl_xor(send, 2));
+    return s4_max(a1, __shfl_xor(a1, 1));
 }
 // The lane that holds query token i after s4_column_maxima, and the query token of an even lane.
 __device__ __forceinline__ constexpr int s4_lane_of_token(int i) { return 32 * ((i >> 2) & 1) + 2 * (4 * (i >> 3) + (i & 3)); }
@@ -158,7 +238,7 @@ __device__ __forceinline__ int s4_token_of_lane(int lane)
 // RN: the storage variant in which a reconstructed vector is scaled to unit length: its dot products are multiplied by
 // the token's factor inv_norm[token] = 1 / |centroid + residual| (plaid_launch_token_inv_norm).
 template <int NBITS, bool COOP, bool RN>
-__global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
+__global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
     const float *__restrict__ inv_norm,
@@ -166,7 +246,7 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
     int spread, uint64_t *__restrict__ out_keys, int64_t out_stride)
 {
     constexpr int RB = 16 * NBITS;
-    __shared__ s4_half8 hlut[256 * (NBITS == 2 ? 1 : 2)];
+    __shared__ typename S4Entry<NBITS>::type hlut[S4_SECOND + 256];
     __shared__ float wmax[4][QLEN];
     __shared__ s4_half8 qs[2][8][64];  // [term][step of 16 dimensions][lane]
     int q, bx;
@@ -184,10 +264,10 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r32 = lane & 31, h = lane >> 5;
-    build_half_tables<NBITS>(hlut, weights, threadIdx.x, 256);
+    s4_build_tables<NBITS>(hlut, weights, threadIdx.x, 256);
     const float *Qq = Q + (int64_t)q * QLEN * DIM;
     const char *Sq = reinterpret_cast<const char *>(S + (int64_t)q * C * QLEN);
-    // A operands: the two fp16 terms of query token r32, dimensions 16 s + 8 h .. + 7.  They are the same for the four
+    // A operands: the two fp16 terms of query token r32, dimensions s4_dim(s, h, ..).  They are the same for the four
     // waves and stay in LDS (16 KB), from where each matrix step reads them: 64 registers less per lane, which buys a
     // third wave per SIMD to cover the latency of the gathers.
     s4_stage_query(Qq, qs);
@@ -211,19 +291,19 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
         return ((int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
                (uint32_t)__builtin_amdgcn_readfirstlane((int)(v & 0xFFFFFFFFll));
     };
-    constexpr int RW = RB / 4;
+    constexpr int RW = 2 * NBITS;
     auto request = [&](int64_t t0, int len, int b, int32_t &c, float &nf, uint32_t (&r)[RW]) {
         const int row = b + r32;  // this lane's passage token
         const int64_t tok = t0 + (row < len ? row : len - 1);
         c = codes[tok];
         if (RN) nf = inv_norm[tok];
-        // the token's packed residual: both halves of the wave read all of it, each uses half of the bytes
-        const uint4 *rp = reinterpret_cast<const uint4 *>(residuals + tok * RB);
-        const uint4 v0 = rp[0];
-        r[0] = v0.x, r[1] = v0.y, r[2] = v0.z, r[3] = v0.w;
+        // this half's half of the token's packed residual
         if (NBITS == 2) {
-            const uint4 v1 = rp[1];
-            r[4] = v1.x, r[5] = v1.y, r[6] = v1.z, r[7] = v1.w;
+            const uint4 v = reinterpret_cast<const uint4 *>(residuals + tok * RB)[h];
+            r[0] = v.x, r[1] = v.y, r[2 % RW] = v.z, r[3 % RW] = v.w;
+        } else {
+            const uint2 v = reinterpret_cast<const uint2 *>(residuals + tok * RB)[h];
+            r[0] = v.x, r[1] = v.y;
         }
     };
     constexpr int STEP = COOP ? 128 : 32;
@@ -275,45 +355,22 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
             }
             floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // cross terms, scaled by 2^11
-            // (the query operands are read anew in every step, through an index the compiler cannot tell from the last
-            // step's: kept across steps they would take the 64 registers again)
-            int ql = lane;
-            asm volatile("" : "+v"(ql));
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                // dimensions 16 s + 8 h .. + 7: bytes 4 s + 2 h and 4 s + 2 h + 1 of a 2-bit code, byte 2 s + h of a 1-bit one
-                s4_half8 a1, a2;
-                if (NBITS == 2) {
-                    const uint32_t two = rw[s] >> (16 * h);
-                    const s4_half8 e0 = hlut[two & 0xFF], e1 = hlut[(two >> 8) & 0xFF];
-                    a1 = s4_half8{e0[0], e0[1], e0[2], e0[3], e1[0], e1[1], e1[2], e1[3]};
-                    a2 = s4_half8{e0[4], e0[5], e0[6], e0[7], e1[4], e1[5], e1[6], e1[7]};
-                } else {
-                    const uint32_t b = (rw[s >> 1] >> (16 * (s & 1) + 8 * h)) & 0xFF;
-                    a1 = hlut[b];
-                    a2 = hlut[256 + b];
-                }
-                const s4_half8 q1 = qs[0][s][ql], q2 = qs[1][s][ql];
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(q1, a1, acc, 0, 0, 0);
-                acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(q2, a1, acx, 0, 0, 0);
-                acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(q1, a2, acx, 0, 0, 0);
-            }
+            s4_products<NBITS, false, COOP>(rw, hlut, qs, lane, acc, acx);
             const float svf[16] = {sv[0].x, sv[0].y, sv[0].z, sv[0].w, sv[1].x, sv[1].y, sv[1].z, sv[1].w,
                                    sv[2].x, sv[2].y, sv[2].z, sv[2].w, sv[3].x, sv[3].y, sv[3].z, sv[3].w};
-            // (med3(a, b, +inf) = max(a, b) for ordered operands, without the canonicalising copies of fmaxf)
             if (base + 32 <= len) {  // (uniform) a full step: every column counts
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     float x = fmaf(acx[v], 1.0f / S4_SCALE, acc[v]) + svf[v];
                     if (RN) x *= nf;
-                    mx[v] = __builtin_amdgcn_fmed3f(mx[v], x, INFINITY);
+                    mx[v] = s4_max(mx[v], x);
                 }
             } else if (base + r32 < len) {  // this lane's column is a token of the passage
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     float x = fmaf(acx[v], 1.0f / S4_SCALE, acc[v]) + svf[v];
                     if (RN) x *= nf;
-                    mx[v] = __builtin_amdgcn_fmed3f(mx[v], x, INFINITY);
+                    mx[v] = s4_max(mx[v], x);
                 }
             }
             code = code_next;
@@ -347,118 +404,337 @@ __global__ __launch_bounds__(256, 4) void decompress_maxsim_kernel(
     }
 }
 
-// Vanilla ColBERTv2's pruning of an over-large candidate set (Section 4.1): a candidate's score from the embeddings
-// of E alone, E = the tokens whose centroid was probed (probebits: bit c = centroid c probed), each decompressed in full
-// like in the kernel above.  One wave per candidate; the tokens of E are compacted through a small LDS ring so that
-// the matrix instructions run on full 32-token steps whatever share of a passage E covers.  Queries whose candidate
-// count does not exceed ncandidates keep every candidate and are not scored: their keys get score 0.
-//   cand: [q][cand_stride] ascending candidate pids, n_cand[q] of them;  out_keys[q][j] = key of cand[q][j].
-// The query operands stay in LDS, as above: with them in registers a SIMD held three waves, and the kernel, bound by its
-// chains of gathers and table look-ups, took 10.4 ms for 16 queries of 400 000 candidates; with four 8.2 ms.
-template <int NBITS>
-__global__ __launch_bounds__(256, NBITS == 2 ? 4 : 3) void vanilla_prune_kernel(
+// Many passages per wave: the tokens to score are listed in LDS, VP_GROUP passages at a time, each passage's rounded up to
+// eight by repeats of its last one, and the steps of 32 tokens run over the list whatever passage a token belongs to.  Rows
+// of the matrix instruction are list positions, columns query tokens: lane 32 h + n gets, for query token n, positions
+// 8 g + 4 h .. + 3 of the groups of eight g = 0 .. 3, adds the rows of S_cq (two whole rows per load instruction) and keeps
+// one running maximum, which goes to LDS where a passage ends; eight lanes then add up the 32 maxima of eight passages.
+// Against steps of one passage each this saves the padding (a third of the steps at 20 tokens per passage, a sixth at 65),
+// the exchange of maxima between lanes and a wave-wide chain of 32 additions per passage.  The next step's residuals, codes and
+// tokens are requested during a step, the next group's codes before the steps of this one.
+//
+// FILTER = false: the passages of in_keys[q], all of their tokens (stage 4 of long launches).  The grid is laid out as in
+// the kernel above.  512 queries of 256 passages: 399 us with a wave-wide step per 32 tokens of one passage and table
+// entries of both terms, 344 us; 144 of 1024 543 -> 393 us.
+// FILTER = true: vanilla ColBERTv2's pruning of an over-large candidate set (Section 4.1): a candidate's score from the
+// embeddings of E alone, E = the tokens whose centroid was probed (probebits: bit c = centroid c probed; staged in LDS up
+// to VP_LDS_WORDS words).  Queries whose candidate count does not exceed ncandidates keep every candidate and are not
+// scored: their keys get score 0.  cand: [q][cand_stride] ascending candidate pids, in_counts[q] of them; out_keys[q][j] =
+// key of cand[q][j].  The candidates of different queries are mostly the same passages: workgroup L takes query
+// L / 8 % nq and a share of the (L % 8)-th eighth of its candidates, so that the queries read a passage at about the same
+// time through the same partition's cache (16 queries: 17 GB from memory with a grid column per query, 1.2 GB this way).
+// 16 queries of 400 000 candidates: 8.4 -> 4.9 ms, of which listing the tokens takes 1.9 (scalar and vector instructions) and
+// the products 2.0 (matrix instructions 1.7).
+#define VP_GROUP 4
+#define VP_CAP 288  // listed positions: what is left of the last list (< 32), one chunk of 64 and its padding always fit
+#define VP_SLOTS 16
+#define VP_LDS_WORDS 2048
+#define VP_RESIDENT_BLOCKS 768
+struct VpArea {  // of one wave
+    int32_t code[VP_CAP];
+    uint32_t row[VP_CAP];       // token within its passage
+    int64_t base[VP_CAP / 8];   // first token of the passage of a group of eight positions
+    int32_t end[VP_CAP / 8];    // slot of the passage that ends with the group, -1
+    float sums[VP_SLOTS][QLEN + 1];
+    int32_t slot_j[VP_SLOTS], slot_pid[VP_SLOTS];
+};
+
+__device__ __forceinline__ void vp_sync()  // orders a wave's LDS accesses
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// WIDE: rows of S_cq need 64-bit offsets (C > 2^25)
+template <int NBITS, bool FILTER, bool RN, bool WIDE>
+__global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
+    const float *__restrict__ inv_norm, const uint64_t *__restrict__ in_keys, int64_t in_stride,
     const uint32_t *__restrict__ probebits, int64_t keep_words, const int32_t *__restrict__ cand, int64_t cand_stride,
-    const int32_t *__restrict__ n_cand, int32_t ncandidates, uint64_t *__restrict__ out_keys, int64_t out_stride)
+    const int32_t *__restrict__ in_counts, int32_t ncandidates, int nq, int gx, int spread, uint64_t *__restrict__ out_keys,
+    int64_t out_stride)
 {
-    constexpr int RB = 16 * NBITS;
-    __shared__ s4_half8 hlut[256 * (NBITS == 2 ? 1 : 2)];
-    __shared__ int32_t ring_all[4][128];
-    __shared__ s4_half8 qs[2][8][64];  // [term][step of 16 dimensions][lane]
-    const int q = blockIdx.y;
-    const int count = n_cand[q];
+    constexpr int RB = 16 * NBITS, RW = 2 * NBITS;
+    __shared__ s4_half8 qs[2][8][64];  // [term][step][lane]
+    __shared__ typename S4Entry<NBITS>::type hlut[S4_SECOND + 256];
+    __shared__ __attribute__((aligned(16))) VpArea areas[4];
+    __shared__ float inv_norms[RN ? 4 : 1][RN ? VP_CAP : 1];
+    extern __shared__ uint32_t probe_lds[];  // FILTER: keep_words words, when at most VP_LDS_WORDS
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t *cq = cand + (int64_t)q * cand_stride;
-    if (count <= ncandidates) {  // (uniform) no pruning for this query
-        for (int j = blockIdx.x * 256 + threadIdx.x; j < count; j += gridDim.x * 256)
-            out_keys[(int64_t)q * out_stride + j] = plaid_make_key(0.0f, (uint32_t)cq[j]);
-        return;
+    int q, bx;
+    if (FILTER) {
+        q = (int)(blockIdx.x >> 3) % nq;
+        bx = (int)(blockIdx.x >> 3) / nq;
+    } else if (spread) {
+        q = blockIdx.x / gx;
+        bx = blockIdx.x % gx;
+    } else {
+        const int k = blockIdx.x >> 3;
+        q = 8 * (k / gx) + (blockIdx.x & 7);
+        bx = k % gx;
     }
-    const int r32 = lane & 31, h = lane >> 5;
-    build_half_tables<NBITS>(hlut, weights, threadIdx.x, 256);
-    const float *Qq = Q + (int64_t)q * QLEN * DIM;
-    const float *Sq = S + (int64_t)q * C * QLEN;
-    const uint32_t *pb = probebits + (int64_t)q * keep_words;
-    s4_stage_query(Qq, qs);
-    __syncthreads();
-    int32_t *ring = ring_all[wave];
-    for (int j = (int)blockIdx.x * 4 + wave; j < count; j += (int)gridDim.x * 4) {
-        const uint32_t pid = (uint32_t)__builtin_amdgcn_readfirstlane(cq[j]);
-        const int64_t t0v = doc_offsets[pid];
-        const int64_t t0 = ((int64_t)__builtin_amdgcn_readfirstlane((int)(t0v >> 32)) << 32) |
-                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(t0v & 0xFFFFFFFFll));
-        const int len = __builtin_amdgcn_readfirstlane((int)(doc_offsets[pid + 1] - t0v));
-        float m = -INFINITY;
-        int have = 0, done = 0;  // uniform: tokens of E listed so far / scored so far
-        for (int src = 0; src < len || done < have; src += 64) {
-            if (src < len) {
-                const int row = src + lane;
-                const int32_t c = row < len ? codes[t0 + row] : 0;
-                const bool in = row < len && ((pb[c >> 5] >> (c & 31)) & 1u);
-                const unsigned long long mask = __ballot(in);
-                if (in) ring[(have + __popcll(mask & ((1ull << lane) - 1ull))) & 127] = row;
-                have += __popcll(mask);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
-            // full steps while 32 listed tokens wait; the remainder once the passage has been read
-            while (have - done >= 32 || (src + 64 >= len && done < have)) {
-                const int nrow = have - done < 32 ? have - done : 32;  // uniform
-                const int row = ring[(done + (r32 < nrow ? r32 : 0)) & 127];
-                const int64_t tok = t0 + row;
-                const int32_t code = codes[tok];
-                uint32_t rw[RB / 4];
-                {
-                    const uint4 *rp = reinterpret_cast<const uint4 *>(residuals + tok * RB);
-                    const uint4 v0 = rp[0];
-                    rw[0] = v0.x, rw[1] = v0.y, rw[2] = v0.z, rw[3] = v0.w;
-                    if (NBITS == 2) {
-                        const uint4 v1 = rp[1];
-                        rw[4] = v1.x, rw[5] = v1.y, rw[6] = v1.z, rw[7] = v1.w;
-                    }
-                }
-                float sv[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int rr = 8 * (v >> 2) + 4 * h + (v & 3);
-                    const uint32_t cv = (uint32_t)__shfl(code, rr);
-                    sv[v] = Sq[cv * (uint32_t)QLEN + (uint32_t)r32];
-                }
-                floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                int ql = lane;  // (read anew in every step, as in the kernel above)
-                asm volatile("" : "+v"(ql));
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    s4_half8 a1, a2;
-                    if (NBITS == 2) {
-                        const uint32_t two = rw[s] >> (16 * h);
-                        const s4_half8 e0 = hlut[two & 0xFF], e1 = hlut[(two >> 8) & 0xFF];
-                        a1 = s4_half8{e0[0], e0[1], e0[2], e0[3], e1[0], e1[1], e1[2], e1[3]};
-                        a2 = s4_half8{e0[4], e0[5], e0[6], e0[7], e1[4], e1[5], e1[6], e1[7]};
-                    } else {
-                        const uint32_t b = (rw[s >> 1] >> (16 * (s & 1) + 8 * h)) & 0xFF;
-                        a1 = hlut[b];
-                        a2 = hlut[256 + b];
-                    }
-                    const s4_half8 q1 = qs[0][s][ql], q2 = qs[1][s][ql];
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q1, acc, 0, 0, 0);
-                    acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q2, acx, 0, 0, 0);
-                    acx = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, q1, acx, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (8 * (v >> 2) + 4 * h + (v & 3) < nrow) m = fmaxf(m, fmaf(acx[v], 1.0f / S4_SCALE, acc[v]) + sv[v]);
-                done += nrow;
-            }
+    if (q >= nq) return;
+    const int total = in_counts[q];
+    const int32_t *cq = FILTER ? cand + (int64_t)q * cand_stride : nullptr;
+    const uint32_t *ik = FILTER ? nullptr : reinterpret_cast<const uint32_t *>(in_keys + (int64_t)q * in_stride);  // low word: id
+    uint64_t *oq = out_keys + (int64_t)q * out_stride;
+    // the workgroup's passages: groups bx 4 + wave, + 4 gx, ... of [lo, count)
+    int64_t lo = 0, count = total;
+    if (FILTER) {
+        const int64_t share = ((int64_t)total + 8 * VP_GROUP - 1) / (8 * VP_GROUP) * VP_GROUP;
+        lo = share * (blockIdx.x & 7);
+        if (lo + share < count) count = lo + share;
+        if (total <= ncandidates) {  // (uniform) no pruning for this query
+            for (int64_t j = lo + (int64_t)bx * 256 + threadIdx.x; j < count; j += (int64_t)gx * 256)
+                oq[j] = plaid_make_key(0.0f, (uint32_t)cq[j]);
+            return;
         }
-        m = fmaxf(m, __shfl_xor(m, 32));
-        const float total = plaid_sum32_in_order(m);
-        if (lane == 0) out_keys[(int64_t)q * out_stride + j] = plaid_make_key(have > 0 ? total : -INFINITY, pid);
     }
+    if (lo + (int64_t)bx * 4 * VP_GROUP >= count) return;  // uniform for the workgroup
+    const int r32 = lane & 31, h = lane >> 5;
+    s4_build_tables<NBITS>(hlut, weights, threadIdx.x, 256);
+    const char *Sq = reinterpret_cast<const char *>(S + (int64_t)q * C * QLEN);
+    const uint32_t *pb = FILTER ? probebits + (int64_t)q * keep_words : nullptr;
+    const bool pb_in_lds = FILTER && keep_words <= VP_LDS_WORDS;
+    if (pb_in_lds)
+        for (int w = threadIdx.x; w < (int)keep_words; w += 256) probe_lds[w] = pb[w];
+    s4_stage_query(Q + (int64_t)q * QLEN * DIM, qs);
+    __syncthreads();
+    VpArea &A = areas[wave];
+    float *anf = inv_norms[RN ? wave : 0];
+    int have = 0;                                // positions listed
+    int assigned = 0, completed = 0, summed = 0;  // passages listed, scored, written out
+    float m = -INFINITY;                          // the running maximum of the passage at the head of the list
+
+    auto token_at = [&](int at) -> int64_t { return A.base[(at + r32) >> 3] + A.row[at + r32]; };  // of position at + r32
+    auto request = [&](int64_t tok, uint32_t (&r)[RW]) {  // this lane's half of the packed residual of a token
+        if (NBITS == 2) {
+            const uint4 v = reinterpret_cast<const uint4 *>(residuals + tok * RB)[h];
+            r[0] = v.x, r[1] = v.y, r[2 % RW] = v.z, r[3 % RW] = v.w;
+        } else {
+            const uint2 v = reinterpret_cast<const uint2 *>(residuals + tok * RB)[h];
+            r[0] = v.x, r[1] = v.y;
+        }
+    };
+    auto codes_at = [&](int at, int4 (&cc)[4]) {  // of positions at + 8 g + 4 h .. + 3
+#pragma unroll
+        for (int g = 0; g < 4; ++g) cc[g] = *reinterpret_cast<const int4 *>(&A.code[at + 8 * g + 4 * h]);
+    };
+    auto write_out = [&](int n) {  // the next n <= 8 passages
+        vp_sync();
+        if (lane < n) {
+            const int s = (summed + lane) & (VP_SLOTS - 1);
+            double d = 0.0;
+#pragma unroll
+            for (int i = 0; i < QLEN; ++i) d += (double)A.sums[s][i];
+            oq[A.slot_j[s]] = plaid_make_key((float)d, (uint32_t)A.slot_pid[s]);
+        }
+        summed += n;
+        vp_sync();
+    };
+    // the full steps of the list; what is left moves to its front
+    auto drain = [&]() {
+        vp_sync();
+        int at = 0;
+        uint32_t rw[RW];
+        int4 cc[4], ends;
+        int64_t tok_next;
+        if (have < 32) return;  // uniform
+        request(token_at(0), rw);
+        codes_at(0, cc);
+        ends = *reinterpret_cast<const int4 *>(&A.end[0]);
+        tok_next = token_at(have >= 64 ? 32 : 0);
+        for (; have - at >= 32; at += 32) {  // uniform
+            // Requested ahead of time: the residuals of the next step, and, from the list, its codes and the tokens of the one
+            // after it (while this step's products leave the matrix unit)
+            float sv[16];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int32_t c4[4] = {cc[g].x, cc[g].y, cc[g].z, cc[g].w};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (WIDE) sv[4 * g + v] = *reinterpret_cast<const float *>(Sq + (((uint64_t)(uint32_t)c4[v] << 7) | 4u * (uint32_t)r32));
+                    else sv[4 * g + v] = *reinterpret_cast<const float *>(Sq + (((uint32_t)c4[v] << 7) | 4u * (uint32_t)r32));
+                }
+            }
+            uint32_t rw_next[RW];
+            request(tok_next, rw_next);  // (past the last step: some token of the list again, not used)
+            floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // cross terms, scaled by 2^11
+            s4_products<NBITS, true, true>(rw, hlut, qs, lane, acc, acx);
+            const int32_t end[4] = {ends.x, ends.y, ends.z, ends.w};
+            const int next = have - at >= 64 ? at + 32 : at;
+            codes_at(next, cc);
+            ends = *reinterpret_cast<const int4 *>(&A.end[next >> 3]);
+            tok_next = token_at(have - at >= 96 ? at + 64 : next);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float x[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[v] = fmaf(acx[4 * g + v], 1.0f / S4_SCALE, acc[4 * g + v]) + sv[4 * g + v];
+                if (RN) {
+                    const float4 f = *reinterpret_cast<const float4 *>(&anf[at + 8 * g + 4 * h]);
+                    x[0] *= f.x, x[1] *= f.y, x[2] *= f.z, x[3] *= f.w;
+                }
+                m = s4_max3(m, x[0], x[1]);
+                m = s4_max3(m, x[2], x[3]);
+                const int slot = __builtin_amdgcn_readfirstlane(end[g]);
+                if (slot >= 0) {  // uniform
+                    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+                    const float mm = s4_max(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+                    if (lane < QLEN) A.sums[slot][lane] = mm;
+                    m = -INFINITY;
+                    ++completed;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < RW; ++e) rw[e] = rw_next[e];
+        }
+        {  // fewer than 32 positions, four groups, are left
+            const int left = have - at;
+            int32_t c = 0;
+            uint32_t r = 0u;
+            int64_t b = 0;
+            int32_t e = -1;
+            float f = 1.0f;
+            if (lane < left) c = A.code[at + lane], r = A.row[at + lane];
+            if (RN && lane < left) f = anf[at + lane];
+            if (lane < (left + 7) >> 3) b = A.base[(at >> 3) + lane], e = A.end[(at >> 3) + lane];
+            vp_sync();
+            if (lane < left) A.code[lane] = c, A.row[lane] = r;
+            if (RN && lane < left) anf[lane] = f;
+            if (lane < (left + 7) >> 3) A.base[lane] = b, A.end[lane] = e;
+            have = left;
+        }
+        // at most 4 + VP_GROUP passages are listed and not written out besides these
+        if (completed - summed >= 8) write_out(8);
+    };
+
+    const int64_t waves = (int64_t)gx * 4, first = (int64_t)bx * 4 + wave;
+    // ids and token ranges of a group, in lanes 0 .. VP_GROUP - 1 (repeated in the others); past the end no tokens
+    auto load_id = [&](int64_t g) -> int32_t {
+        const int64_t j = lo + g * VP_GROUP + (lane & (VP_GROUP - 1));
+        return j < count ? (FILTER ? cq[j] : (int32_t)ik[2 * j]) : -1;
+    };
+    auto wanted = [&](int32_t code) -> unsigned long long {  // the lanes whose token (code >= 0) is scored
+        if (!FILTER) return __ballot(code >= 0);
+        const uint32_t w = (uint32_t)code >> 5;
+        const uint32_t bits = code < 0 ? 0u : (pb_in_lds ? probe_lds[w] : pb[w]);
+        return __ballot((bits >> (code & 31)) & 1u);
+    };
+    // the first two chunks of 64 codes of a group's passages
+    int64_t t0[VP_GROUP];
+    int len[VP_GROUP];
+    int32_t c[VP_GROUP][2];
+    auto request_codes = [&](int64_t o0, int64_t o1) {
+#pragma unroll
+        for (int k = 0; k < VP_GROUP; ++k) {
+            const uint32_t lo32 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)o0, k);
+            const uint32_t hi32 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)o0 >> 32), k);
+            t0[k] = (int64_t)((uint64_t)hi32 << 32 | lo32);
+            len[k] = __builtin_amdgcn_readlane((int)(o1 - o0), k);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) c[k][u] = 64 * u + lane < len[k] ? codes[t0[k] + 64 * u + lane] : -1;
+        }
+    };
+    // the chain id -> token range -> codes is started two groups ahead and advanced one link per group
+    int32_t pid = load_id(first), pid1 = load_id(first + waves);
+    int64_t o0 = 0, o1 = 0;
+    if (pid >= 0) o0 = doc_offsets[pid], o1 = doc_offsets[pid + 1];
+    request_codes(o0, o1);
+    for (int64_t g = first;; g += waves) {  // uniform
+        const bool more = lo + g * VP_GROUP < count;
+        const int32_t pid2 = load_id(g + 2 * waves);
+        o0 = o1 = 0;
+        if (pid1 >= 0) o0 = doc_offsets[pid1], o1 = doc_offsets[pid1 + 1];
+        unsigned long long masks[VP_GROUP][2];
+#pragma unroll
+        for (int k = 0; k < VP_GROUP; ++k)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) masks[k][u] = wanted(c[k][u]);
+        int k0 = 0, src0 = 0;  // passage and chunk to go on with
+        bool any = false, again;
+        int32_t last_code = 0;  // of the last position listed
+        uint32_t last_row = 0u;
+        float last_nf = 1.0f;
+        do {
+            again = false;
+#pragma unroll
+            for (int k = 0; k < VP_GROUP; ++k) {
+                const int64_t j = lo + g * VP_GROUP + k;
+                if (again || k < k0 || j >= count) continue;  // uniform
+#pragma unroll 1
+                for (int src = src0; src < len[k]; src += 64) {  // uniform
+                    int32_t cc = src == 0 ? c[k][0] : c[k][1];
+                    unsigned long long mask = src == 0 ? masks[k][0] : masks[k][1];
+                    if (src >= 128) {
+                        cc = src + lane < len[k] ? codes[t0[k] + src + lane] : -1;
+                        mask = wanted(cc);
+                    }
+                    if (!mask) continue;
+                    if (have + 72 > VP_CAP) {
+                        again = true;
+                        k0 = k;
+                        src0 = src;
+                        break;
+                    }
+                    const int n = __popcll(mask), at = have + __popcll(mask & ((1ull << lane) - 1ull));
+                    if ((mask >> lane) & 1ull) A.code[at] = cc, A.row[at] = (uint32_t)(src + lane);
+                    const int top = 63 - __clzll((long long)mask);
+                    last_code = __builtin_amdgcn_readlane(cc, top);
+                    last_row = (uint32_t)(src + top);
+                    if (RN) {
+                        const float f = src + lane < len[k] ? inv_norm[t0[k] + src + lane] : 0.0f;
+                        if ((mask >> lane) & 1ull) anf[at] = f;
+                        last_nf = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(f), top));
+                    }
+                    const int o = (have >> 3) + lane;
+                    have += n;
+                    if (8 * o < have && lane < 9) A.base[o] = t0[k], A.end[o] = -1;
+                    any = true;
+                }
+                if (again) continue;
+                src0 = 0;
+                const int32_t p = __builtin_amdgcn_readlane(pid, k);
+                if (!any) {  // uniform
+                    if (lane == 0) oq[j] = plaid_make_key(-INFINITY, (uint32_t)p);
+                    continue;
+                }
+                any = false;
+                const int fill = -have & 7;  // repeats of the last position
+                if (lane < fill) A.code[have + lane] = last_code, A.row[have + lane] = last_row;
+                if (RN && lane < fill) anf[have + lane] = last_nf;
+                have += fill;
+                const int slot = assigned++ & (VP_SLOTS - 1);
+                if (lane == 0) {
+                    A.end[(have >> 3) - 1] = slot;
+                    A.slot_j[slot] = (int32_t)j;
+                    A.slot_pid[slot] = p;
+                }
+            }
+            if (!again) {  // the next group's codes, before the steps
+                request_codes(o0, o1);
+                pid = pid1;
+                pid1 = pid2;
+            }
+            if (!more && have > 0) {  // the remainder, filled up to a whole step
+                vp_sync();
+                const int32_t lc = A.code[0];
+                const uint32_t lr = A.row[0];
+                const int64_t lb = A.base[0];
+                if (have + lane < 32) A.code[have + lane] = lc, A.row[have + lane] = lr;
+                if (RN && have + lane < 32) anf[have + lane] = 1.0f;
+                if ((have >> 3) + lane < 4) A.base[(have >> 3) + lane] = lb, A.end[(have >> 3) + lane] = -1;
+                have = 32;
+            }
+            if (have >= 32) drain();
+        } while (again);
+        if (!more) break;
+    }
+    if (completed > summed) write_out(completed - summed);
 }
 
 void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
@@ -468,16 +744,25 @@ void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, 
                                 int64_t out_stride)
 {
     if (n_upper <= 0 || nq <= 0) return;
-    int64_t gx = (n_upper + 3) / 4;
-    const int64_t cap = (S4_RESIDENT_BLOCKS * 4 + nq - 1) / nq;
+    // three workgroups per compute unit, four rounds of them; at least a workgroup per query and eighth
+    int64_t gx = (n_upper + 32 * VP_GROUP - 1) / (32 * VP_GROUP);
+    const int64_t cap = (4 * VP_RESIDENT_BLOCKS + 8 * nq - 1) / (8 * nq);
     if (gx > cap) gx = cap;
-    if (gx < 1) gx = 1;
-    if (nbits == 2)
-        hipLaunchKernelGGL(vanilla_prune_kernel<2>, dim3((unsigned)gx, nq), dim3(256), 0, st, Q, S, C, doc_offsets, codes, residuals,
-                           bucket_weights, probebits, keep_words, cand, cand_stride, n_cand, ncandidates, out_keys, out_stride);
-    else
-        hipLaunchKernelGGL(vanilla_prune_kernel<1>, dim3((unsigned)gx, nq), dim3(256), 0, st, Q, S, C, doc_offsets, codes, residuals,
-                           bucket_weights, probebits, keep_words, cand, cand_stride, n_cand, ncandidates, out_keys, out_stride);
+    const size_t lds = keep_words <= VP_LDS_WORDS ? (size_t)keep_words * 4 : 0;
+#define PLAID_VP_LAUNCH(NB, WIDE)                                                                                              \
+    hipLaunchKernelGGL((maxsim_list_kernel<NB, true, false, WIDE>), dim3((unsigned)(8 * nq * gx)), dim3(256), lds, st, Q, S, C, \
+                       doc_offsets, codes, residuals, bucket_weights, (const float *)nullptr, (const uint64_t *)nullptr,       \
+                       (int64_t)0, probebits, keep_words, cand, cand_stride, n_cand, ncandidates, nq, (int)gx, 0, out_keys,     \
+                       out_stride)
+    const bool wide = C > (1ll << 25);
+    if (nbits == 2) {
+        if (wide) PLAID_VP_LAUNCH(2, true);
+        else PLAID_VP_LAUNCH(2, false);
+    } else {
+        if (wide) PLAID_VP_LAUNCH(1, true);
+        else PLAID_VP_LAUNCH(1, false);
+    }
+#undef PLAID_VP_LAUNCH
 }
 
 void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
@@ -487,34 +772,46 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
                                     const float *inv_norm)
 {
     if (n_upper <= 0 || nq <= 0) return;
-    // few passages in all (short lists of few queries): a workgroup per passage; otherwise waves stride over the lists,
-    // several passages each, so that the per-workgroup set-up (table, query operands) is paid rarely
-    const bool coop = (int64_t)n_upper * nq <= 2048;
-    int gx = coop ? n_upper : (n_upper + 3) / 4;
+    // Few passages in all (short lists of few queries): a workgroup per passage.  Otherwise waves stride over the lists,
+    // several passages each, so that the per-workgroup set-up (table, query operands) is paid rarely.  From 48 passages per
+    // workgroup of a full chip (three per compute unit) on, steps packed across passages, 32 passages per workgroup: 512
+    // queries of 256 passages 374 -> 344 us (48, 64, 128 per workgroup: 381, 362, 390), 144 of 1024 488 -> 393 us (421, 401,
+    // 438); below, a wave's list of four passages leaves too few waves: 256 queries of 64 48 -> 50 us, 23 of 250 25 -> 46 us.
+    const int64_t all = (int64_t)n_upper * nq;
+    const bool coop = all <= 2048, pack = all >= 48ll * VP_RESIDENT_BLOCKS;
+    int gx = coop ? n_upper : (pack ? (n_upper + 31) / 32 : (n_upper + 3) / 4);
     // (256 compute units x 4 resident workgroups: one full round of waves, each striding over several passages)
     const int cap = coop ? 2048 : (S4_RESIDENT_BLOCKS + nq - 1) / nq;
-    if (gx > cap) gx = cap;
+    if (!pack && gx > cap) gx = cap;
     const int spread = nq < 8 ? 1 : 0;
     const int64_t slots = spread ? nq : 8 * (((int64_t)nq + 7) / 8);  // query slots of the one-dimensional grid
     if (slots * gx > (1ll << 23)) gx = (int)((1ll << 23) / slots);  // (the waves stride over longer lists)
     if (gx < 1) gx = 1;
+    const bool wide = C > (1ll << 25);
 #define PLAID_S4_LAUNCH(NB, CO, RN)                                                                                       \
     hipLaunchKernelGGL((decompress_maxsim_kernel<NB, CO, RN>), dim3((unsigned)(slots * gx)), dim3(256), 0, st, Q, S, C,      \
                        doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, in_counts, nq, gx,       \
                        spread, out_keys, out_stride)
-#define PLAID_S4_LAUNCH_RN(NB, CO)                                                                                        \
-    do {                                                                                                                  \
-        if (inv_norm) PLAID_S4_LAUNCH(NB, CO, true);                                                                      \
-        else PLAID_S4_LAUNCH(NB, CO, false);                                                                              \
+#define PLAID_S4_PACK(NB, RN, WIDE)                                                                                          \
+    hipLaunchKernelGGL((maxsim_list_kernel<NB, false, RN, WIDE>), dim3((unsigned)(slots * gx)), dim3(256), 0, st, Q, S, C,    \
+                       doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, (const uint32_t *)nullptr,\
+                       (int64_t)0, (const int32_t *)nullptr, (int64_t)0, in_counts, 0, nq, gx, spread, out_keys, out_stride)
+#define PLAID_S4_FORMS(NB, RN)                                   \
+    do {                                                          \
+        if (pack && wide) PLAID_S4_PACK(NB, RN, true);            \
+        else if (pack) PLAID_S4_PACK(NB, RN, false);              \
+        else if (coop) PLAID_S4_LAUNCH(NB, true, RN);             \
+        else PLAID_S4_LAUNCH(NB, false, RN);                      \
     } while (0)
     if (nbits == 2) {
-        if (coop) PLAID_S4_LAUNCH_RN(2, true);
-        else PLAID_S4_LAUNCH_RN(2, false);
+        if (inv_norm) PLAID_S4_FORMS(2, true);
+        else PLAID_S4_FORMS(2, false);
     } else {
-        if (coop) PLAID_S4_LAUNCH_RN(1, true);
-        else PLAID_S4_LAUNCH_RN(1, false);
+        if (inv_norm) PLAID_S4_FORMS(1, true);
+        else PLAID_S4_FORMS(1, false);
     }
-#undef PLAID_S4_LAUNCH_RN
+#undef PLAID_S4_FORMS
+#undef PLAID_S4_PACK
 #undef PLAID_S4_LAUNCH
 }
 

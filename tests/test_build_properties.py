@@ -35,8 +35,11 @@ KERNELS = {
     "decompress_maxsim_kernelILi2ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD (query operands in LDS)
     "decompress_maxsim_kernelILi1ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
     "decompress_maxsim_kernelILi2ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),   # ... with unit-length reconstruction
-    "vanilla_prune_kernelILi2E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD
-    "vanilla_prune_kernelILi1E": ("k_stage4.hip", 168, 32 << 10),   # three
+    # three waves per SIMD, three workgroups per CU (the pruning instances add 8 KB of dynamic LDS)
+    "maxsim_list_kernelILi2ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
+    "maxsim_list_kernelILi1ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
+    "maxsim_list_kernelILi2ELb0ELb0ELb0E": ("k_stage4.hip", 168, 53 << 10),
+    "maxsim_list_kernelILi1ELb0ELb1ELb0E": ("k_stage4.hip", 168, 53 << 10),
     "decompress_dump_kernelILi2E": ("k_stage4.hip", 64, 8 << 10),
     "passage_offsets_kernel": ("k_stage4.hip", 64, 1 << 10),
     "van_codes_kernel": ("k_vanilla.hip", 64, 1 << 10),
