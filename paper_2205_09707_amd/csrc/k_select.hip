@@ -107,20 +107,30 @@ __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int
             for (int c = 0; c < COPIES; ++c) loc[j] += gh[c * BINS + threadIdx.x * PER + j];
         sum += loc[j];
     }
-    scan[threadIdx.x] = sum;
+    // prefix sums: within the wave by shuffles, the waves' totals through LDS (two barriers in all; a scan of all threads in
+    // LDS takes eighteen)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t v = __shfl_up(incl, d);
+        if (lane >= d) incl += v;
+    }
+    if (lane == 63) scan[wave] = incl;
     if (threadIdx.x == 0) {
         res[0] = SEL_BINS;
         res[1] = 0;
     }
     __syncthreads();
-    for (int d = 1; d < SEL_THREADS; d <<= 1) {
-        int32_t v = threadIdx.x >= d ? scan[threadIdx.x - d] : 0;
-        __syncthreads();
-        scan[threadIdx.x] += v;
-        __syncthreads();
+    int32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < SEL_THREADS / 64; ++w) {
+        const int32_t v = scan[w];
+        if (w < wave) incl += v;
+        total += v;
     }
-    const int32_t incl = scan[threadIdx.x], excl = incl - sum;
-    if (m_cap != 0x7FFFFFFF) m_rem = m_cap < scan[SEL_THREADS - 1] ? m_cap : scan[SEL_THREADS - 1];  // min(m, #keys)
+    const int32_t excl = incl - sum;
+    if (m_cap != 0x7FFFFFFF) m_rem = m_cap < total ? m_cap : total;  // min(m, #keys)
     if (m_rem > 0 && excl < m_rem && m_rem <= incl) {
         int32_t run = excl;
         for (int j = 0; j < PER; ++j) {
@@ -136,10 +146,11 @@ __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int
         res[0] = -1;  // take nothing, keep nothing
         res[1] = 0;
     }
+    if (threadIdx.x == SEL_THREADS - 1) scan[SEL_THREADS - 1] = total;  // for the callers
     __syncthreads();
     bstar = res[0];
     before = res[1];
-    if (bstar == SEL_BINS) before = scan[SEL_THREADS - 1];
+    if (bstar == SEL_BINS) before = total;
 }
 
 // ------------------------------------------------------------------ level kernel: split a list by its digit
@@ -792,7 +803,84 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
 // Candidates with an empty bag (-infinity) are appended last, in passage-id order, straight from
 // their bitmap.
 // =================================================================================================
-__global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
+#define SEL2_GROUPS 8                              // keys a thread takes per step
+#define SEL2_STEP (SEL_THREADS * SEL2_GROUPS)     // keys a workgroup takes per step
+struct Sel2Place {                                // LDS of sel2_place
+    int32_t cnt[2][2][SEL_THREADS / 64];          // [parity of the step][selected / boundary][wave]
+    int32_t base[2];
+    unsigned long long bits[2][SEL_THREADS / 64];
+};
+// Writes a step's keys of class 0 (selected) to out and of class 1 (boundary) to bl; o, no collect the boundary keys' bits and
+// their complements.  The workgroup reserves its positions with one update of each counter per step: the counters of a query
+// are two words that every workgroup of the launch updates and waits for, one after the other.  One query of 8.8 M passages:
+// with an update per wave the bin filter took 27.6 us and the digit filter, 64 keys a wave, 19.9; now 8.1 and 5.8.  All
+// threads call this.
+__device__ __forceinline__ void sel2_place(const uint64_t (&key)[SEL2_GROUPS], const int (&cls)[SEL2_GROUPS], int parity, Sel2Place &l,
+                                           int32_t *n_sure, int32_t *n_boundary, uint64_t *__restrict__ out,
+                                           uint64_t *__restrict__ bl, unsigned long long &o, unsigned long long &no)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long b0[SEL2_GROUPS], b1[SEL2_GROUPS];
+    int n0 = 0, n1 = 0;
+#pragma unroll
+    for (int u = 0; u < SEL2_GROUPS; ++u) {
+        b0[u] = __ballot(cls[u] == 0);
+        b1[u] = __ballot(cls[u] == 1);
+        n0 += __popcll(b0[u]);
+        n1 += __popcll(b1[u]);
+    }
+    if (lane == 0) {
+        l.cnt[parity][0][wave] = n0;
+        l.cnt[parity][1][wave] = n1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < SEL_THREADS / 64; ++w) n += l.cnt[parity][threadIdx.x][w];
+        l.base[threadIdx.x] = n ? atomicAdd(threadIdx.x == 0 ? n_sure : n_boundary, n) : 0;
+    }
+    __syncthreads();
+    int base0 = l.base[0], base1 = l.base[1];
+    for (int w = 0; w < wave; ++w) {
+        base0 += l.cnt[parity][0][w];
+        base1 += l.cnt[parity][1][w];
+    }
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int u = 0; u < SEL2_GROUPS; ++u) {
+        if (cls[u] == 0) out[base0 + __popcll(b0[u] & below)] = key[u];
+        if (cls[u] == 1) {
+            bl[base1 + __popcll(b1[u] & below)] = key[u];
+            o |= key[u];
+            no |= ~key[u];
+        }
+        base0 += __popcll(b0[u]);
+        base1 += __popcll(b1[u]);
+    }
+}
+// The workgroup's boundary bits to the query's.  All threads call this, once.
+__device__ __forceinline__ void sel2_place_bits(unsigned long long o, unsigned long long no, Sel2Place &l, unsigned long long *b_or,
+                                                unsigned long long *b_nor)
+{
+    for (int d = 1; d < 64; d <<= 1) {
+        o |= __shfl_xor(o, d);
+        no |= __shfl_xor(no, d);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        l.bits[0][threadIdx.x >> 6] = o;
+        l.bits[1][threadIdx.x >> 6] = no;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long v = 0;
+#pragma unroll
+        for (int w = 0; w < SEL_THREADS / 64; ++w) v |= l.bits[threadIdx.x][w];
+        if (v) atomicOr(threadIdx.x == 0 ? b_or : b_nor, v);
+    }
+}
+
+__global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                   const uint32_t *__restrict__ candbits, int64_t cand_words,
                                                                   int64_t P, int32_t m, const S2Meta *__restrict__ meta,
                                                                   const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
@@ -800,15 +888,15 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
 {
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
+    __shared__ Sel2Place place;
     const int seg = blockIdx.y;
     Sel2State *s = state + seg;
     const S2Meta mt = meta[seg];
     if (mt.K == 0) return;  // no surviving centroid: no valid key, the state stays zero and the fill takes over
-    constexpr int SEL2_GROUPS = 8;
     const bool is_list = lists && mt.K <= S2_MAX_KEPT;
     const int64_t n_items = is_list ? (int64_t)s->n_list : P;
     // a list is short next to the passages the grid is sized for: most of its workgroups have nothing to read
-    if (blockIdx.x > 0 && (int64_t)blockIdx.x * SEL_THREADS * SEL2_GROUPS >= n_items) return;
+    if (blockIdx.x > 0 && (int64_t)blockIdx.x * SEL2_STEP >= n_items) return;
     int bstar, before;
     // takes min(m, number of keys); a list comes with the coarse histogram
     if (is_list) find_boundary<S2_COARSE, S2_COPIES>(hist + (int64_t)seg * SEL_BINS, 0, scan, res, bstar, before, m);
@@ -822,16 +910,13 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
     uint64_t *my_out = out + (int64_t)seg * out_stride;
     uint64_t *my_bl = blist + (int64_t)seg * blist_stride;
     const int lane = threadIdx.x & 63;
-    // A wave takes SEL2_GROUPS x 64 consecutive slots per step and reserves its output positions with one pair of
-    // counter updates per step (the updates return a value, so their round trip is the step's latency).
-    const int64_t wave_id = (int64_t)blockIdx.x * (SEL_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t n_waves = (int64_t)gridDim.x * (SEL_THREADS / 64);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     unsigned long long o = 0, no = 0;
-    for (int64_t i0 = wave_id * (64 * SEL2_GROUPS); i0 < n_items; i0 += n_waves * (64 * SEL2_GROUPS)) {  // uniform per wave
+    int parity = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * SEL2_STEP; s0 < n_items; s0 += (int64_t)gridDim.x * SEL2_STEP, parity ^= 1) {  // uniform
+        const int64_t i0 = s0 + 64 * SEL2_GROUPS * wave;  // a wave takes consecutive slots
         uint64_t key[SEL2_GROUPS];
         int cls[SEL2_GROUPS];  // 0 = surely selected, 1 = boundary, 2 = dropped
-        unsigned long long b0[SEL2_GROUPS], b1[SEL2_GROUPS];
-        int n0 = 0, n1 = 0;
         if (is_list) {  // uniform
             const uint64_t *kl = keys + (int64_t)seg * key_stride;
 #pragma unroll
@@ -864,39 +949,10 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_filter_kernel(const uint64_t
                 const int d = plaid_s2_bin(plaid_ord_to_score((uint32_t)(key[u] >> 32)), mt.bin_hi, mt.bin_scale) >> bin_shift;
                 cls[u] = d < bstar ? 0 : (d == bstar ? 1 : 2);
             }
-            b0[u] = __ballot(cls[u] == 0);
-            b1[u] = __ballot(cls[u] == 1);
-            n0 += __popcll(b0[u]);
-            n1 += __popcll(b1[u]);
         }
-        const unsigned long long below = (1ull << lane) - 1ull;
-        int base0 = 0, base1 = 0;
-        if (lane == 0) {
-            if (n0) base0 = atomicAdd(&s->n_sure, n0);
-            if (n1) base1 = atomicAdd(&s->n_b, n1);
-        }
-        base0 = __shfl(base0, 0);
-        base1 = __shfl(base1, 0);
-#pragma unroll
-        for (int u = 0; u < SEL2_GROUPS; ++u) {
-            if (cls[u] == 0) my_out[base0 + __popcll(b0[u] & below)] = key[u];
-            if (cls[u] == 1) {
-                my_bl[base1 + __popcll(b1[u] & below)] = key[u];
-                o |= key[u];
-                no |= ~key[u];
-            }
-            base0 += __popcll(b0[u]);
-            base1 += __popcll(b1[u]);
-        }
+        sel2_place(key, cls, parity, place, &s->n_sure, &s->n_b, my_out, my_bl, o, no);
     }
-    for (int d = 1; d < 64; d <<= 1) {
-        o |= __shfl_xor(o, d);
-        no |= __shfl_xor(no, d);
-    }
-    if (lane == 0 && (o | no)) {
-        atomicOr(&s->b_or, o);
-        atomicOr(&s->b_nor, no);
-    }
+    sel2_place_bits(o, no, place, &s->b_or, &s->b_nor);
 }
 
 // A boundary list longer than this goes through a digit pass (all workgroups of the query) before the finishing
@@ -933,7 +989,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_hist_kernel(const uint
     Sel2State *s = state + seg;
     int m_rem;
     const int n = sel2_level_input<LEVEL>(s, m_rem);
-    if (n <= SEL2_DIGIT_MIN) return;
+    if (n <= SEL2_DIGIT_MIN || (int64_t)blockIdx.x * SEL_THREADS >= n) return;
     int shift, width;
     sel2_digit_plan<LEVEL>(s, shift, width);
     for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS) lh[b] = 0;
@@ -963,11 +1019,12 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_filter_kernel(const ui
 {
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
+    __shared__ Sel2Place place;
     const int seg = blockIdx.y;
     Sel2State *s = state + seg;
     int32_t m_rem;
     const int n = sel2_level_input<LEVEL>(s, m_rem);
-    if (n <= SEL2_DIGIT_MIN) return;
+    if (n <= SEL2_DIGIT_MIN || (int64_t)blockIdx.x * SEL2_STEP >= n) return;
     int shift, width;
     sel2_digit_plan<LEVEL>(s, shift, width);
     int bstar, before;
@@ -980,43 +1037,24 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_filter_kernel(const ui
     const uint64_t *k = blist + (int64_t)seg * blist_stride;
     uint64_t *my_out = out + (int64_t)seg * out_stride;
     uint64_t *my_bl = blist1 + (int64_t)seg * blist1_stride;
-    const int lane = threadIdx.x & 63;
-    const int64_t n_round = ((int64_t)n + 63) & ~63ll;
     unsigned long long o = 0, no = 0;
-    for (int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x; i < n_round; i += (int64_t)gridDim.x * SEL_THREADS) {
-        uint64_t key = 0;
-        int cls = 2;
-        if (i < n) {
-            key = k[i];
-            const int d = digit_of(key, shift, width);
-            cls = d < bstar ? 0 : (d == bstar ? 1 : 2);
+    int parity = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * SEL2_STEP; s0 < n; s0 += (int64_t)gridDim.x * SEL2_STEP, parity ^= 1) {  // uniform
+        uint64_t key[SEL2_GROUPS];
+        int cls[SEL2_GROUPS];
+#pragma unroll
+        for (int u = 0; u < SEL2_GROUPS; ++u) {
+            const int64_t i = s0 + u * SEL_THREADS + threadIdx.x;
+            key[u] = i < n ? k[i] : 0ull;
         }
-        const unsigned long long b0 = __ballot(cls == 0), b1 = __ballot(cls == 1);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        int base0 = 0, base1 = 0;
-        if (lane == 0) {
-            if (b0) base0 = atomicAdd(&s->n_sure, __popcll(b0));
-            if (b1) base1 = atomicAdd(n_left, __popcll(b1));
+#pragma unroll
+        for (int u = 0; u < SEL2_GROUPS; ++u) {
+            const int d = digit_of(key[u], shift, width);
+            cls[u] = s0 + u * SEL_THREADS + threadIdx.x < n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
         }
-        base0 = __shfl(base0, 0);
-        base1 = __shfl(base1, 0);
-        if (cls == 0) my_out[base0 + __popcll(b0 & below)] = key;
-        if (cls == 1) {
-            my_bl[base1 + __popcll(b1 & below)] = key;
-            o |= key;
-            no |= ~key;
-        }
+        sel2_place(key, cls, parity, place, &s->n_sure, n_left, my_out, my_bl, o, no);
     }
-    if (LEVEL == 1) {
-        for (int d = 1; d < 64; d <<= 1) {
-            o |= __shfl_xor(o, d);
-            no |= __shfl_xor(no, d);
-        }
-        if (lane == 0 && (o | no)) {
-            atomicOr(&s->b_or1, o);
-            atomicOr(&s->b_nor1, no);
-        }
-    }
+    if (LEVEL == 1) sel2_place_bits(o, no, place, &s->b_or1, &s->b_nor1);
 }
 
 // One workgroup per query: finish the boundary list, then append empty-bag candidates in pid order.
