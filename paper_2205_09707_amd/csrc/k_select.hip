@@ -519,94 +519,126 @@ __global__ __launch_bounds__(256) void sel_rank_output_kernel(const uint64_t *__
 }
 
 // The `take` smallest (in any order) of the n <= SEL_SORT_CAP keys of `bl`, to o; every key agrees at and above bit `high`.
-// One workgroup of FIN_THREADS threads, all of which call this; sk, dh, h256, sh: LDS (keys, one digit's histogram, wave
-// totals, four words).
+// One workgroup of FIN_THREADS threads, all of which call this; sk, dh, h256, sh, differ: LDS (keys, one digit's histogram, wave
+// totals, four words, two words).
+// A digit at a time in LDS, the eleven bits from the highest in which the keys differ: keys below the boundary digit are taken,
+// its own are left -- a handful, unless the keys tie in their scores: then the next digit lies in the ids.  What is left is
+// ranked by counting.  (Sorting a tie group instead, 45 to 78 dependent steps, was the longest query of most launches: 144
+// queries of 8.8 M passages 117 -> 52 us, 512 of 400 000 39 -> 20, 23 of 123 457 13.5 -> 7.6.)
 #define FIN_RANK (FIN_THREADS / 4)
+// One digit: keys from bl (STAGED: from sk); n, take, base, high: those of the keys that are left, which go to sk.
+template <bool STAGED>
+__device__ __forceinline__ void sel_pick_digit(const uint64_t *__restrict__ bl, int &n, int &take, uint64_t *__restrict__ o, int &base,
+                                               int &high, uint64_t *sk, int32_t *dh, int32_t *h256, int32_t *sh,
+                                               unsigned long long *differ)
+{
+    uint64_t key[SEL_SORT_CAP / FIN_THREADS];
+    const int shift = high > SEL_RADIX_BITS ? high - SEL_RADIX_BITS : 0;
+    for (int i = threadIdx.x; i < SEL_BINS; i += FIN_THREADS) dh[i] = 0;
+    if (threadIdx.x < 2) {
+        sh[threadIdx.x] = 0;
+        differ[threadIdx.x] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
+        const int i = threadIdx.x + u * FIN_THREADS;
+        key[u] = i < n ? (STAGED ? sk[i] : bl[i]) : PLAID_KEY_MAX;
+        if (i < n) atomicAdd(&dh[(int)(key[u] >> shift) & (SEL_BINS - 1)], 1);
+    }
+    __syncthreads();
+    {
+        // thread t: bins 2 t and 2 t + 1; sums over the waves before it from the waves' totals
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int c0 = dh[2 * threadIdx.x], c1 = dh[2 * threadIdx.x + 1];
+        int incl = c0 + c1;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d);
+            if (lane >= d) incl += t;
+        }
+        if (lane == 63) h256[wave] = incl;
+        __syncthreads();
+        int ahead = lane < wave ? h256[lane] : 0;  // (sixteen waves)
+#pragma unroll
+        for (int d = 1; d < FIN_THREADS / 64; d <<= 1) ahead += __shfl_xor(ahead, d);
+        const int before = __builtin_amdgcn_readfirstlane(ahead) + incl - c0 - c1;
+        if (take > 0 && before < take && before + c0 + c1 >= take) {
+            const bool second = before + c0 < take;
+            sh[2] = 2 * threadIdx.x + (second ? 1 : 0);
+            sh[3] = before + (second ? c0 : 0);
+        }
+        if (take <= 0 && threadIdx.x == 0) {
+            sh[2] = -1;
+            sh[3] = 0;
+        }
+        __syncthreads();
+    }
+    const int bd = sh[2], below = sh[3];
+#pragma unroll
+    for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
+        const int i = threadIdx.x + u * FIN_THREADS;
+        if (u * FIN_THREADS >= n) break;  // uniform
+        const int d = i < n ? (int)(key[u] >> shift) & (SEL_BINS - 1) : SEL_BINS;
+        if (d < bd) o[base + atomicAdd(&sh[0], 1)] = key[u];
+        if (d == bd) sk[atomicAdd(&sh[1], 1)] = key[u];
+    }
+    __syncthreads();
+    n = sh[1];
+    base += below;
+    take -= below;
+    if (n > FIN_RANK) {  // in which bits the keys that are left differ
+        unsigned long long any = 0, none = 0;
+#pragma unroll 1
+        for (int i = threadIdx.x; i < n; i += FIN_THREADS) {
+            any |= sk[i];
+            none |= ~sk[i];
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            any |= __shfl_xor(any, d);
+            none |= __shfl_xor(none, d);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicOr(&differ[0], any);
+            atomicOr(&differ[1], none);
+        }
+        __syncthreads();
+        const unsigned long long diff = differ[0] & differ[1];
+        high = diff ? 64 - __builtin_clzll(diff) : 0;
+        __syncthreads();  // sh and differ are cleared next
+    }
+}
 __device__ __forceinline__ void sel_pick_lds(const uint64_t *__restrict__ bl, int n, int take, uint64_t *__restrict__ o, int high,
-                                             uint64_t *sk, int32_t *dh, int32_t *h256, int32_t *sh)
+                                             uint64_t *sk, int32_t *dh, int32_t *h256, int32_t *sh, unsigned long long *differ)
 {
     int base = 0;
     if (n > FIN_RANK) {
-        // One digit in LDS: the eleven bits from the highest in which the keys differ.  Keys below the boundary digit are
-        // taken, its own are left -- a handful, unless the keys tie in their scores' upper bits.
-        uint64_t key[SEL_SORT_CAP / FIN_THREADS];
-        const int shift = high > SEL_RADIX_BITS ? high - SEL_RADIX_BITS : 0;
-        for (int i = threadIdx.x; i < SEL_BINS; i += FIN_THREADS) dh[i] = 0;
-        if (threadIdx.x == 0) sh[0] = sh[1] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
-            const int i = threadIdx.x + u * FIN_THREADS;
-            key[u] = i < n ? bl[i] : PLAID_KEY_MAX;
-            if (i < n) atomicAdd(&dh[(int)(key[u] >> shift) & (SEL_BINS - 1)], 1);
-        }
-        __syncthreads();
-        {
-            // thread t: bins 2 t and 2 t + 1; sums over the waves before it from the waves' totals
-            const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-            const int c0 = dh[2 * threadIdx.x], c1 = dh[2 * threadIdx.x + 1];
-            int incl = c0 + c1;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int t = __shfl_up(incl, d);
-                if (lane >= d) incl += t;
-            }
-            if (lane == 63) h256[wave] = incl;
-            __syncthreads();
-            int before = incl - c0 - c1;
-            for (int w = 0; w < wave; ++w) before += h256[w];
-            if (take > 0 && before < take && before + c0 + c1 >= take) {
-                const bool second = before + c0 < take;
-                sh[2] = 2 * threadIdx.x + (second ? 1 : 0);
-                sh[3] = before + (second ? c0 : 0);
-            }
-            if (take <= 0 && threadIdx.x == 0) {
-                sh[2] = -1;
-                sh[3] = 0;
-            }
-            __syncthreads();
-        }
-        const int bd = sh[2], below = sh[3];
-#pragma unroll
-        for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
-            const int i = threadIdx.x + u * FIN_THREADS;
-            if (u * FIN_THREADS >= n) break;  // uniform
-            const int d = i < n ? (int)(key[u] >> shift) & (SEL_BINS - 1) : SEL_BINS;
-            if (d < bd) o[base + atomicAdd(&sh[0], 1)] = key[u];
-            if (d == bd) sk[atomicAdd(&sh[1], 1)] = key[u];
-        }
-        __syncthreads();
-        n = sh[1];
-        base += below;
-        take -= below;
+        sel_pick_digit<false>(bl, n, take, o, base, high, sk, dh, h256, sh, differ);
+        // (uniform; keys are unique: a digit that ends at bit 0 leaves one)
+#pragma unroll 1
+        while (n > FIN_RANK) sel_pick_digit<true>(bl, n, take, o, base, high, sk, dh, h256, sh, differ);
     } else {
         if ((int)threadIdx.x < n) sk[threadIdx.x] = bl[threadIdx.x];
         __syncthreads();
     }
-    if (n <= FIN_RANK) {
-        // few keys: four threads count how many of them precede theirs
-        const int i = threadIdx.x >> 2;
-        if (i < n) {
-            const uint64_t key = sk[i];
-            int rank = 0;
-            for (int j = threadIdx.x & 3; j < n; j += 4) rank += sk[j] < key ? 1 : 0;
-            rank += __shfl_xor(rank, 1);
-            rank += __shfl_xor(rank, 2);
-            if ((threadIdx.x & 3) == 0 && rank < take) o[base + rank] = key;
-        }
-    } else {
-        const int n2 = next_pow2(n);
-        for (int i = n + threadIdx.x; i < n2; i += FIN_THREADS) sk[i] = PLAID_KEY_MAX;
-        __syncthreads();
-        lds_bitonic_sort(sk, n2);
-        for (int i = threadIdx.x; i < take; i += FIN_THREADS) o[base + i] = sk[i];
+    // few keys: four threads count how many of them precede theirs
+    const int i = threadIdx.x >> 2;
+    if (i < n) {
+        const uint64_t key = sk[i];
+        int rank = 0;
+#pragma unroll 4
+        for (int j = threadIdx.x & 3; j < n; j += 4) rank += sk[j] < key ? 1 : 0;
+        rank += __shfl_xor(rank, 1);
+        rank += __shfl_xor(rank, 2);
+        if ((threadIdx.x & 3) == 0 && rank < take) o[base + rank] = key;
     }
 }
 
 // The m smallest keys of each list, in no particular order: a workgroup per list, one digit and a handful of keys to rank.
-// For the few lists of a launch of single queries: rank counting, its n^2 form, takes 10 us for 1024 keys and 34 for 4096,
-// this 7 and 9.
-__global__ __launch_bounds__(FIN_THREADS) void sel_pick_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
+// Rank counting, its n^2 form for few lists, takes 10 us for 1024 keys and 34 for 4096, this 5 and 7; sorting in LDS, with many
+// lists, 14.9 us for 23 of 1000 keys, 9.7 for 256 of 256, 20.7 for 512 of 1024, 37 for 144 of 4096, this 6, 6, 9 and 9.
+__global__ __launch_bounds__(FIN_THREADS, 8) void sel_pick_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                const int32_t *__restrict__ counts, int32_t n_cap, int32_t m,
                                                                uint64_t *__restrict__ out, int64_t out_stride,
                                                                int32_t *__restrict__ out_counts)
@@ -616,6 +648,7 @@ __global__ __launch_bounds__(FIN_THREADS) void sel_pick_kernel(const uint64_t *_
     __shared__ int32_t h256[FIN_THREADS / 64];
     __shared__ int32_t sh[4];
     __shared__ unsigned long long differ[2];  // OR over the keys / over their complements
+    __shared__ unsigned long long left[2];
     const int seg = blockIdx.x;
     int n = counts[seg];
     if (n > n_cap) n = n_cap;
@@ -642,7 +675,7 @@ __global__ __launch_bounds__(FIN_THREADS) void sel_pick_kernel(const uint64_t *_
     }
     __syncthreads();
     const unsigned long long diff = differ[0] & differ[1];
-    sel_pick_lds(k, n, take, out + (int64_t)seg * out_stride, diff ? 64 - __builtin_clzll(diff) : 0, sk, dh, h256, sh);
+    sel_pick_lds(k, n, take, out + (int64_t)seg * out_stride, diff ? 64 - __builtin_clzll(diff) : 0, sk, dh, h256, sh, left);
 }
 
 static inline int64_t sort_pow2(int64_t n)
@@ -744,7 +777,7 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
     // producer runs; see search.hip
     if (n_upper <= SEL_SORT_CAP) {
         const size_t lds = (size_t)sort_pow2(n_upper) * 8;
-        if (nseg <= RANK_MAX_LISTS && n_upper > 512 && !sorted) {
+        if (!sorted && (nseg > RANK_MAX_LISTS || n_upper > 512)) {
             hipLaunchKernelGGL(sel_pick_kernel, dim3(nseg), dim3(FIN_THREADS), 0, st, keys, key_stride, counts, (int32_t)n_upper, m,
                                out, out_stride, out_counts);
         } else if (nseg <= RANK_MAX_LISTS) {
@@ -1057,8 +1090,59 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_filter_kernel(const ui
     if (LEVEL == 1) sel2_place_bits(o, no, place, &s->b_or1, &s->b_nor1);
 }
 
+// The passages of the words [w0, w1) of a bitmap to o[total ..], until m are there; positions from a wave-level prefix sum of the
+// popcounts plus the waves' totals (wsum).  PER words per thread and round.  PER = 1: in ascending order.  PER > 1: rounds that
+// are taken as a whole, in any order; a round of more passages than are wanted is left to the caller (returns its w0).
+// All threads call this.
+template <int PER>
+__device__ __forceinline__ int64_t sel2_fill(const uint32_t *__restrict__ eb, int64_t w0, int64_t w1, int64_t P, int32_t m,
+                                             int32_t *wsum, uint64_t *__restrict__ o, int &total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (; w0 < w1 && total < m; w0 += FIN_THREADS * PER) {
+        const int64_t w = w0 + 64 * PER * wave + lane;  // words w, w + 64, ..
+        uint32_t v[PER];
+        int cnt = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) v[u] = w + 64 * u < w1 ? eb[w + 64 * u] : 0u;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if ((w + 64 * u + 1) * 32 > P) {
+                const int64_t keep = P - (w + 64 * u) * 32;
+                v[u] = keep <= 0 ? 0u : (keep >= 32 ? v[u] : (v[u] & ((1u << keep) - 1u)));
+            }
+            cnt += __popc(v[u]);
+        }
+        int incl = cnt;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d);
+            if (lane >= d) incl += t;
+        }
+        __syncthreads();  // the previous round's readers of wsum are done
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        int pos = total + incl - cnt, all = 0;
+        for (int wv = 0; wv < FIN_THREADS / 64; ++wv) {
+            const int t = wsum[wv];
+            if (wv < wave) pos += t;
+            all += t;
+        }
+        if (PER > 1 && total + all > m) return w0;  // uniform: every thread adds the same wave totals
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            while (v[u] && pos < m) {
+                const int bit = __ffs(v[u]) - 1;
+                v[u] &= v[u] - 1;
+                o[pos++] = plaid_make_key(-INFINITY, (uint32_t)((w + 64 * u) * 32 + bit));
+            }
+        total = total + all < m ? total + all : m;
+    }
+    return w0;
+}
+
 // One workgroup per query: finish the boundary list, then append empty-bag candidates in pid order.
-__global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t *__restrict__ blist, int64_t blist_stride,
+__global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint64_t *__restrict__ blist, int64_t blist_stride,
                                                                   const uint64_t *__restrict__ blist1,
                                                                   int64_t blist1_stride, const Sel2State *state,
                                                                   const uint32_t *__restrict__ emptybits,
@@ -1070,6 +1154,7 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
     __shared__ int32_t dh[SEL_BINS];
     __shared__ int32_t h256[256];
     __shared__ int32_t sh[4];
+    __shared__ unsigned long long differ[2];
     const int seg = blockIdx.x;
     const Sel2State *s = state + seg;
     // how many digit filters this query's boundary list went through (levels: how many were launched); the second one
@@ -1086,7 +1171,7 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
 
     if (nb <= SEL_SORT_CAP) {
         const unsigned long long diff = done == 1 ? (s->b_or1 & s->b_nor1) : (done == 0 ? (s->b_or & s->b_nor) : 0ull);
-        sel_pick_lds(bl, nb, m_rem, o + n_sure, diff ? 64 - __builtin_clzll(diff) : top_bit, sk, dh, h256, sh);
+        sel_pick_lds(bl, nb, m_rem, o + n_sure, diff ? 64 - __builtin_clzll(diff) : top_bit, sk, dh, h256, sh, differ);
     } else {
         // still long (huge tie groups): radix selection over global memory by this one workgroup.  The keys of such a
         // list mostly share their digit (that is what made the list long), so a wave whose keys all have one digit
@@ -1154,45 +1239,14 @@ __global__ __launch_bounds__(FIN_THREADS) void sel2_finish_kernel(const uint64_t
     }
     __syncthreads();
 
-    // empty-bag candidates: ascending pid, until m slots are filled.  One bitmap word per thread and round; positions
-    // from a wave-level prefix sum of the popcounts plus the wave totals.
+    // empty-bag candidates: those of the smallest pids, until m slots are filled.  One bitmap word per thread in the first round,
+    // which is enough where nearly every passage is one, then rounds of eight (8.8 M passages are 275 000 words, 268 rounds of
+    // one) up to the one in which the last of them lies.
     if (total < m) {
-        int32_t *wsum = h256;  // [FIN_THREADS / 64] wave totals
         const uint32_t *eb = emptybits + (int64_t)seg * cand_words;
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        for (int64_t w0 = 0; w0 < cand_words && total < m; w0 += FIN_THREADS) {
-            const int64_t w = w0 + threadIdx.x;
-            uint32_t v = 0u;
-            if (w < cand_words) {
-                v = eb[w];
-                if ((w + 1) * 32 > P) {
-                    const int64_t keep = P - w * 32;
-                    v = keep <= 0 ? 0u : (keep >= 32 ? v : (v & ((1u << keep) - 1u)));
-                }
-            }
-            const int cnt = __popc(v);
-            int incl = cnt;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int t = __shfl_up(incl, d);
-                if (lane >= d) incl += t;
-            }
-            __syncthreads();  // the previous round's readers of wsum are done
-            if (lane == 63) wsum[wave] = incl;
-            __syncthreads();
-            int pos = total + incl - cnt, all = 0;
-            for (int wv = 0; wv < FIN_THREADS / 64; ++wv) {
-                const int t = wsum[wv];
-                if (wv < wave) pos += t;
-                all += t;
-            }
-            while (v && pos < m) {
-                const int bit = __ffs(v) - 1;
-                v &= v - 1;
-                o[pos++] = plaid_make_key(-INFINITY, (uint32_t)(w * 32 + bit));
-            }
-            total = total + all < m ? total + all : m;  // uniform: every thread adds the same wave totals
-        }
+        int64_t w0 = sel2_fill<1>(eb, 0, cand_words < FIN_THREADS ? cand_words : FIN_THREADS, P, m, h256, o, total);
+        w0 = sel2_fill<8>(eb, w0, cand_words, P, m, h256, o, total);
+        sel2_fill<1>(eb, w0, cand_words, P, m, h256, o, total);
     }
     if (threadIdx.x == 0) out_counts[seg] = total;
 }
