@@ -133,9 +133,9 @@ struct SurvivorScratch {
     int32_t amb_n, amb_total;
     uint32_t amb_pass[TAIL_AMB / 32];
 };
-struct SurvivorRows {  // APPROX only: the re-evaluations' operands
-    float Qs[QLEN * TAIL_QSTRIDE];
-    union {
+struct SurvivorRows {  // APPROX only: the re-evaluations' operands, written and read in 16-byte pieces
+    alignas(16) float Qs[QLEN * TAIL_QSTRIDE];
+    alignas(16) union {
         float row[(S2_MAX_KEPT + 1) * TAIL_QSTRIDE];  // (whole tiles of sixteen)
         int32_t amb[TAIL_AMB];
     };

@@ -99,3 +99,24 @@ def test_boundary_search_reads_its_histogram_in_16_byte_pieces(tmp_path):
         body = re.search(r"^_Z16sel_level_kernelILi%dE.*?s_barrier" % level, text, re.M | re.S).group(0)
         assert len(re.findall(r"global_load_dwordx4", body)) == 2, body
         assert "global_load_dword " not in body and "s_cbranch" not in body, body
+
+
+# LDS arrays that are accessed in 16-byte pieces: (source file, where the array starts within the record it lies in)
+LDS_PIECES = [
+    ("k_scq.hip", ["offsetof(SurvivorRows, Qs)", "offsetof(SurvivorRows, row)", "offsetof(TableScratch<true>, x)",
+                   "offsetof(ProbeScratch<true>, Qs)", "offsetof(ProbeScratch<true>, block)", "offsetof(ProbeScratch<true>, row)",
+                   "offsetof(ProbeScratch<true>, idl)", "offsetof(ProbeScratch<false>, block)", "offsetof(ProbeScratch<false>, idl)"]),
+    ("k_stage2.hip", ["offsetof(S2GatherScratch, list)", "offsetof(S2GatherScratch, part_max)"]),
+    ("k_stage4.hip", ["offsetof(VpArea, code)", "offsetof(VpArea, end)", "sizeof(VpArea)"]),
+]
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+@pytest.mark.parametrize("src,places", LDS_PIECES, ids=[s for s, _ in LDS_PIECES])
+def test_lds_arrays_accessed_in_16_byte_pieces_are_aligned(tmp_path, src, places):
+    unit = tmp_path / "places.hip"
+    unit.write_text(f'#include "{src}"\n#include <cstddef>\n' +
+                    "".join(f'static_assert(({p}) % 16 == 0, "{p}");\n' for p in places))
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+                        "--cuda-host-only", "-fsyntax-only", str(unit)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
