@@ -826,7 +826,13 @@ __global__ __launch_bounds__(64 * IV_WAVES) void s2_candidates_kernel(
 // in LDS, then eight rows per load instruction as in stage 3.  Bins are counted in LDS and added once per share.
 // 400 000 passages, one query: 4.1 ms per search with four waves per 2048 passages fetching two rows at a time, 15.6 with one,
 // 0.40 now; 64 queries 92, 117 and 16.
-#define S2_GATHER_BLOCKS 768  // three per compute unit
+// One round of workgroups, as many per compute unit as run there together: shares are even, so what is missing to a round
+// leaves units behind the others, and what exceeds it runs alone.  No pruning, 400 000 passages, ndocs 4096, 128 / 8 / 1 queries,
+// us per search with 512, 768, 1024, 1280, 2048 workgroups where four run together: 48 800, 36 100, 27 000, 37 900, 28 400 /
+// 3140, 2180, 1710, 2310, 1710 / 449, 360, 317, 401, 342 (768 where three do: 32 600 / 2090 / 402).
+#define S2_UNIT_BLOCKS 4
+#define S2_GATHER_BLOCKS (256 * S2_UNIT_BLOCKS)
+#define S2_FITS_BLOCKS 768    // launches of up to this many workgroups run the 64-bit instance alone
 #define S2_GATHER_STRIDE 68   // of a passage's list: eight lanes that read one column of eight lists hit all banks
 struct S2GatherScratch {
     S2CandScratch cand;
@@ -1026,8 +1032,9 @@ __device__ __forceinline__ uint32_t s2_sum_reaches(const uint32_t (&A)[S2_UB_BIT
 // SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
 // the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
 // PLAIN: no copies of the histogram and no candidate words given (large batches; the two cost the kernel 2 % there).
+static_assert(IV_WAVES == 4, "a workgroup is a wave per SIMD");
 template <int SHIFT, typename SetT, bool PLAIN>
-__global__ __launch_bounds__(64 * IV_WAVES, 4) void s2_invert_kernel(
+__global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kernel(
     const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride,
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
@@ -1583,13 +1590,13 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int nqx = spread ? (nq | 1) : (nq + 7) & ~7;
     const int copies = spread && nq * blocks > 64 ? (4ll * m >= 3 * ((P + (1ll << len_log) - 1) >> len_log) ? 8 | 64 : 8) : 0;
     const int own = copies | given;
-    // Few workgroups, at most three per compute unit: that instance alone, taking
-    // every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
+    // Few workgroups, at most S2_FITS_BLOCKS: the 64-bit instance alone, taking every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
     // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
     // 65 / 70); with twice the workgroups,
     // so that queries with more slots than a wave's area holds can have two (mode bit 5).  More: the 32-bit
-    // instance's scoring and its fourth workgroup per compute unit win (eight of 2 M: 232 with two, 327 with one).
-    const bool fits = blocks * nqx <= S2_GATHER_BLOCKS;
+    // instance's scoring wins (eight of 2 M: 232 with two, 327 with one).  The line: 768 and 1024 make no difference beyond
+    // 2 % (16 of 400 000: 166 / 164 us per search, 32 and 40 of 200 000: 146 / 143 and 155 / 152, eight of 1 M: 160 / 160).
+    const bool fits = blocks * nqx <= S2_FITS_BLOCKS;
     if (nq < 8 || fits) {
         const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0);
         const int64_t all = fits ? 2 * blocks : blocks;

@@ -26,8 +26,8 @@ KERNELS = {
     "s2_invert_kernelILi11EjLb1E": ("k_stage2.hip", 128, 40 << 10),
     "s2_invert_kernelILi13EjLb0E": ("k_stage2.hip", 128, 40 << 10),
     "s2_invert_kernelILi13EjLb1E": ("k_stage2.hip", 128, 40 << 10),
-    "s2_invert_kernelILi11EyLb0E": ("k_stage2.hip", 168, 53 << 10),   # 64-bit sets: three
-    "s2_invert_kernelILi13EyLb0E": ("k_stage2.hip", 128, 40 << 10),   # ... with coarse table columns: four
+    "s2_invert_kernelILi11EyLb0E": ("k_stage2.hip", 128, 40 << 10),   # 64-bit sets: four
+    "s2_invert_kernelILi13EyLb0E": ("k_stage2.hip", 128, 40 << 10),
     "s2_candidates_kernel": ("k_stage2.hip", 64, 8 << 10),
     "s2_union_wide_kernel": ("k_stage2.hip", 128, 80 << 10),       # two workgroups of 1024 threads per CU
     "s2_stream_kernel": ("k_stage2.hip", 128, 40 << 10),
@@ -99,6 +99,23 @@ def test_boundary_search_reads_its_histogram_in_16_byte_pieces(tmp_path):
         body = re.search(r"^_Z16sel_level_kernelILi%dE.*?s_barrier" % level, text, re.M | re.S).group(0)
         assert len(re.findall(r"global_load_dwordx4", body)) == 2, body
         assert "global_load_dword " not in body and "s_cbranch" not in body, body
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+def test_gather_form_has_the_workgroups_that_run_at_once(tmp_path):
+    """The gather form's even shares, S2_GATHER_BLOCKS of them, take one round of the chip's 256 compute units: as many per unit
+    as the registers and the LDS of the 64-bit instances admit, no fewer (some units would hold more than others) and no more
+    (a second round of few)."""
+    meta = _metadata(_assembly("k_stage2.hip", str(tmp_path / "k_stage2.s")))
+    defines = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-E", "-dD",
+                              "--cuda-host-only", os.path.join(CSRC, "k_stage2.hip")], check=True, stdout=subprocess.PIPE,
+                             stderr=subprocess.DEVNULL, text=True).stdout
+    define = dict(re.findall(r"^#define (S2_GATHER_BLOCKS|S2_UNIT_BLOCKS)\s+(.*?)(?://.*)?$", defines, re.M))
+    blocks = eval(define["S2_GATHER_BLOCKS"].strip(), {}, {k: int(v) for k, v in define.items() if v.strip().isdigit()})
+    for key in ("s2_invert_kernelILi11EyLb0E", "s2_invert_kernelILi13EyLb0E"):
+        m, = [m for n, m in meta.items() if key in n]
+        vgprs = -(-(m["vgpr_count"] + m["agpr_count"]) // 8) * 8
+        assert blocks == 256 * min(512 // vgprs, (160 << 10) // m["group_segment_fixed_size"]), (key, blocks, m)
 
 
 # LDS arrays that are accessed in 16-byte pieces: (source file, where the array starts within the record it lies in)
