@@ -21,6 +21,7 @@
 #include "plaid_internal.h"
 
 #include <math.h>
+#include <type_traits>
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 s4_half8 __attribute__((ext_vector_type(8)));
@@ -237,7 +238,8 @@ __device__ __forceinline__ int s4_token_of_lane(int lane)
 // second-level cache and the rows of S_cq its passages have in common are fetched once.
 // RN: the storage variant in which a reconstructed vector is scaled to unit length: its dot products are multiplied by
 // the token's factor inv_norm[token] = 1 / |centroid + residual| (plaid_launch_token_inv_norm).
-template <int NBITS, bool COOP, bool RN>
+// WIDE: rows of S_cq need 64-bit offsets (C > 2^25).
+template <int NBITS, bool COOP, bool RN, bool WIDE>
 __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
@@ -343,7 +345,8 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
             // used after the matrix instructions)
             float4 sv[4];
             {
-                const uint32_t off = (uint32_t)code * (uint32_t)(QLEN * 4) + 16u * (uint32_t)h;
+                typename std::conditional<WIDE, uint64_t, uint32_t>::type off = (uint32_t)code;
+                off = off * (uint32_t)(QLEN * 4) + 16u * (uint32_t)h;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) sv[g] = *reinterpret_cast<const float4 *>(Sq + off + 32u * g);
             }
@@ -446,7 +449,7 @@ __device__ __forceinline__ void vp_sync()  // orders a wave's LDS accesses
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// WIDE: rows of S_cq need 64-bit offsets (C > 2^25)
+// RN, WIDE: as above.
 template <int NBITS, bool FILTER, bool RN, bool WIDE>
 __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
@@ -788,28 +791,33 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
     if (slots * gx > (1ll << 23)) gx = (int)((1ll << 23) / slots);  // (the waves stride over longer lists)
     if (gx < 1) gx = 1;
     const bool wide = C > (1ll << 25);
-#define PLAID_S4_LAUNCH(NB, CO, RN)                                                                                       \
-    hipLaunchKernelGGL((decompress_maxsim_kernel<NB, CO, RN>), dim3((unsigned)(slots * gx)), dim3(256), 0, st, Q, S, C,      \
+#define PLAID_S4_LAUNCH(NB, CO, RN, WIDE)                                                                                 \
+    hipLaunchKernelGGL((decompress_maxsim_kernel<NB, CO, RN, WIDE>), dim3((unsigned)(slots * gx)), dim3(256), 0, st, Q, S, C,      \
                        doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, in_counts, nq, gx,       \
                        spread, out_keys, out_stride)
 #define PLAID_S4_PACK(NB, RN, WIDE)                                                                                          \
     hipLaunchKernelGGL((maxsim_list_kernel<NB, false, RN, WIDE>), dim3((unsigned)(slots * gx)), dim3(256), 0, st, Q, S, C,    \
                        doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, (const uint32_t *)nullptr,\
                        (int64_t)0, (const int32_t *)nullptr, (int64_t)0, in_counts, 0, nq, gx, spread, out_keys, out_stride)
-#define PLAID_S4_FORMS(NB, RN)                                   \
+#define PLAID_S4_FORMS(NB, RN, WIDE)                              \
     do {                                                          \
-        if (pack && wide) PLAID_S4_PACK(NB, RN, true);            \
-        else if (pack) PLAID_S4_PACK(NB, RN, false);              \
-        else if (coop) PLAID_S4_LAUNCH(NB, true, RN);             \
-        else PLAID_S4_LAUNCH(NB, false, RN);                      \
+        if (pack) PLAID_S4_PACK(NB, RN, WIDE);                    \
+        else if (coop) PLAID_S4_LAUNCH(NB, true, RN, WIDE);       \
+        else PLAID_S4_LAUNCH(NB, false, RN, WIDE);                \
+    } while (0)
+#define PLAID_S4_WIDTHS(NB, RN)                                   \
+    do {                                                          \
+        if (wide) PLAID_S4_FORMS(NB, RN, true);                   \
+        else PLAID_S4_FORMS(NB, RN, false);                       \
     } while (0)
     if (nbits == 2) {
-        if (inv_norm) PLAID_S4_FORMS(2, true);
-        else PLAID_S4_FORMS(2, false);
+        if (inv_norm) PLAID_S4_WIDTHS(2, true);
+        else PLAID_S4_WIDTHS(2, false);
     } else {
-        if (inv_norm) PLAID_S4_FORMS(1, true);
-        else PLAID_S4_FORMS(1, false);
+        if (inv_norm) PLAID_S4_WIDTHS(1, true);
+        else PLAID_S4_WIDTHS(1, false);
     }
+#undef PLAID_S4_WIDTHS
 #undef PLAID_S4_FORMS
 #undef PLAID_S4_PACK
 #undef PLAID_S4_LAUNCH

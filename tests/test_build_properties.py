@@ -32,9 +32,10 @@ KERNELS = {
     "s2_union_wide_kernel": ("k_stage2.hip", 128, 80 << 10),       # two workgroups of 1024 threads per CU
     "s2_stream_kernel": ("k_stage2.hip", 128, 40 << 10),
     "ci_list_kernelILb0E": ("k_ci.hip", 96, 8 << 10),              # five waves per SIMD; wave-private LDS areas
-    "decompress_maxsim_kernelILi2ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD (query operands in LDS)
-    "decompress_maxsim_kernelILi1ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
-    "decompress_maxsim_kernelILi2ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),   # ... with unit-length reconstruction
+    "decompress_maxsim_kernelILi2ELb0ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD (query operands in LDS)
+    "decompress_maxsim_kernelILi1ELb0ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
+    "decompress_maxsim_kernelILi2ELb0ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),   # ... with 64-bit offsets of rows
+    "decompress_maxsim_kernelILi2ELb0ELb1ELb0E": ("k_stage4.hip", 128, 32 << 10),   # ... with unit-length reconstruction
     # three waves per SIMD, three workgroups per CU (the pruning instances add 8 KB of dynamic LDS)
     "maxsim_list_kernelILi2ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
     "maxsim_list_kernelILi1ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
