@@ -741,8 +741,8 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok)
 // 65536 centroids: 40 us one after the other, with the tiles' maxima read twice over by one workgroup and the rows to
 // re-evaluate fetched in four round trips; 19 now; 8.8 M passages, 262144 centroids 79 -> 27; 10 000, 1024 27 -> 12.5).
 //
-// Probes (rank order), from the column maxima of the score kernel's tiles, and their ascending duplicate-free union.  The
-// split-fp16 kernel also reports the maxima of groups of 2^gs tiles; otherwise a tile is its own group.  gmax is
+// Probes (rank order), from the column maxima of the score kernel's tiles, and their ascending duplicate-free union.  Where
+// there are many tiles the split-fp16 kernel also reports the maxima of groups of 2^gs of them; otherwise a tile is its own group.  gmax is
 // [group][token]: a thread reads four tokens of every 128th group (16-byte loads, consecutive threads at consecutive
 // addresses, eight loads in flight) and keeps their largest values; its rows are one of 128 blocks.  Then 32 consecutive
 // lanes share a token: the nprobe-th largest of the block maxima (nprobe rounds of "maximum over the 32 lanes, its first
@@ -760,6 +760,8 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok)
 //   pruning  a row whose approximate maximum lies within eps of t_cs was left open by the score kernel (ambbits): its
 //            entries >= t_cs - eps are re-evaluated and the row's bit is set when one of them reaches t_cs;
 //   table    the rows of the surviving centroids that stage 2 scores with are re-evaluated (stage1_survivor_table).
+#define TAIL_FLY 8    // group maxima in flight per thread
+#define TAIL_PARTS (TAIL_THREADS / (QLEN / 4))  // threads that share four tokens
 #define TAIL_SEL 16   // listed groups, and listed tiles, per token
 #define TAIL_XCAP 32  // listed rows per token: one per lane
 #define TAIL_ROWS 128  // rows staged at most for the re-evaluation of the probes, half of their dimensions at a time; more of them
@@ -843,8 +845,6 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                                             const float *__restrict__ tmq, int nblk, int tile_rows, const float *__restrict__ gmq,
                                             int ng, int gs, int nprobe, const Stage1Out o, const Stage1Exact x)
 {
-    constexpr int TAIL_FLY = 8;                          // loads in flight per thread
-    constexpr int TAIL_PARTS = TAIL_THREADS / (QLEN / 4);  // threads that share four tokens
     static_assert(TAIL_LANES == 32, "32 lanes per query token");
     const int tid = threadIdx.x;
     const float *__restrict__ Sq = S + (int64_t)q * C * QLEN;
@@ -1251,9 +1251,16 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
     const int n_tiles = (int)((C + tile_rows - 1) / tile_rows);
     float *tmx = np > 0 ? tilemax : nullptr;
     static_assert(SM_WROWS == 32, "the split-fp16 kernel emits column maxima per 32 rows, like the matrix form");
+    // The split-fp16 kernel reports maxima of groups of eight tiles too, where there is room for them and a query has more tiles
+    // than the probe kernel has loads for in one round.  They cost the score kernel 2 to 4 %, and save the probe kernel a round
+    // of loads per 1024 tiles.  Scores and probes together, us, with / without: one query of 65536 centroids 38 / 42, of 262144
+    // 77 / 95; 512 queries of 65536 1009 / 1006, of 131072 1899 / 1936; 256 of 262144 1871 / 1930.  Up to 1024 tiles they save
+    // nothing: 512 queries of 16384 centroids 327 / 323, of 32768 565 / 553, one of 32768 31.6 / 31.7.
+    const bool grouped = form == PLAID_SCQ_SPLIT16 && tmx && groupmax && n_tiles > TAIL_PARTS * TAIL_FLY;
+    static_assert(PLAID_SCQ16_GROUP_ROWS == SM_WROWS << 3, "eight tiles per group");
     if (!(phases & PLAID_STAGE1_SCORES)) {
     } else if (form == PLAID_SCQ_SPLIT16) {
-        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, tmx ? groupmax : nullptr, score_clocks);
+        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, grouped ? groupmax : nullptr, score_clocks);
     } else if (matrix_form) {
         if (nq == 1)
             hipLaunchKernelGGL(scq_mfma_kernel<1>, dim3(1, nblk), dim3(SM_THREADS), 0, st, centroids, C, Q, nq, t_cs, S, keepbits,
@@ -1274,10 +1281,7 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
         x.t_lo = (t_cs > -INFINITY && t_cs < INFINITY) ? nextafterf(t_cs - PLAID_SCQ16_EPS, -INFINITY) : t_cs;
         x.margin = 2.0f * PLAID_SCQ16_EPS;
         x.matrix = matrix_ok;
-        // the split-fp16 kernel reports maxima of groups of tiles too, where there is room for them
-        const bool grouped = form == PLAID_SCQ_SPLIT16 && groupmax;
         const int gs = grouped ? 3 : 0, ng = (n_tiles + (1 << gs) - 1) >> gs;
-        static_assert(PLAID_SCQ16_GROUP_ROWS == SM_WROWS << 3, "eight tiles per group");
         const float *gmx = grouped ? groupmax : tilemax;
 #define TAIL(NP_, AP_)                                                                                                     \
     hipLaunchKernelGGL((stage1_tail_kernel<NP_, AP_>), dim3(nq, 2), dim3(TAIL_THREADS), 0, st, S, C, keepbits, keep_words, \

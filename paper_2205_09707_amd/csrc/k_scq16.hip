@@ -112,7 +112,7 @@ __device__ __forceinline__ void scq16_store_part(float *__restrict__ s0, const f
 }
 
 // Out of the accumulators of one query: the scores (val, scaled back), the tiles' column maxima and the pruning words.
-// Returns the column maxima over the wave's tiles.
+// Returns the column maxima over the wave's tiles (used with GROUPS only).
 template <int NT>
 __device__ __forceinline__ float scq16_reduce(const scq16_floatx16 (&acc)[NT], float (&val)[NT][16], const int (&nvalid)[NT],
                                              int64_t tile0, int64_t n_blk, int q, int lane, float t_lo, float t_hi,
@@ -169,7 +169,7 @@ __device__ __forceinline__ float scq16_reduce(const scq16_floatx16 (&acc)[NT], f
 // unconditional.  The two cases are separate instances, and the first query is taken out of the loop, so that the number
 // of stores between a request for operands and the wait for them is the same on every path: the memory counter retires
 // in order, and a wait sized for the path with the fewest stores would sit out the score stores of the others.
-template <int NT, bool WHOLE>
+template <int NT, bool WHOLE, bool GROUPS>
 __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], float (&gmax)[2][H16_WAVES][QLEN], const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16,
                                            int64_t C, const scq16_half8 *__restrict__ B16, int q_begin, int q_end, float t_lo,
                                            float t_hi, float *__restrict__ S, uint32_t *__restrict__ keepbits,
@@ -251,10 +251,10 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], f
         }
         const float wmax = scq16_reduce<NT>(acc, val, nvalid, tile0, n_blk, q, lane, t_lo, t_hi, keepbits, ambbits, keep_words, tilemax);
         float (&gm)[H16_WAVES][QLEN] = gmax[(q - q_begin) & 1];
-        if (h == 0) gm[wave][n] = wmax;
+        if (GROUPS && h == 0) gm[wave][n] = wmax;
         scq16_lds_barrier();  // publishes nxt and gm; every wave is done reading buf
         // the maxima over the workgroup's rows, by each wave in turn (gm is written again two barriers from here)
-        if (groupmax && wave == (q & (H16_WAVES - 1)) && h == 0) {
+        if (GROUPS && wave == (q & (H16_WAVES - 1)) && h == 0) {
             float m = gm[0][n];
 #pragma unroll
             for (int w = 1; w < H16_WAVES; ++w) m = fmaxf(m, gm[w][n]);
@@ -281,13 +281,13 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], f
 
 // Grid: x = block of 32 * H16_WAVES * NT centroids, y = group of qg queries.  A16: a whole number of workgroups' tiles
 // (rows past C are zero).  keepbits / ambbits: [q][keep_words], bit c = row c passes Eq. 5 for sure / is ambiguous;
-// tilemax: [q][ceil(C/32)][32]; groupmax (may be null): [q][gridDim.x][32], the maxima over the workgroup's rows.
+// tilemax: [q][ceil(C/32)][32]; groupmax (GROUPS only): [q][gridDim.x][32], the maxima over the workgroup's rows.
 // The loop over the group's queries is software-pipelined twice over.  Operands: those of query q + 1 are requested
 // before the matrix instructions of query q, moved into the other LDS buffer right after them (by then they have
 // arrived), and those of q + 2 are requested.  Scores: the results of query q leave the accumulators (scaled, reduced
 // for the tile maxima and the pruning words) into registers of their own, and their stores are issued between the
 // matrix instructions of query q + 1, a few per step, so that the store stream and the matrix pipe run side by side.
-template <int NT>
+template <int NT, bool GROUPS>
 __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     const scq16_half8 *__restrict__ A16, int64_t C, const scq16_half8 *__restrict__ B16, int nq, int qg, float t_lo, float t_hi,
     float *__restrict__ S, uint32_t *__restrict__ keepbits, uint32_t *__restrict__ ambbits, int64_t keep_words,
@@ -311,9 +311,9 @@ __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     }
     // (the barriers inside are reached by all four waves in either instance: both run the same loop over the queries)
     if (whole)
-        scq16_body<NT, true>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
+        scq16_body<NT, true, GROUPS>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
     else
-        scq16_body<NT, false>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
+        scq16_body<NT, false, GROUPS>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
     if (clocks && threadIdx.x == 0) {
         atomicAdd(&clocks[0], (unsigned long long)(clock64() - sc0));
         atomicAdd(&clocks[1], (unsigned long long)(wall_clock64() - rt0));
@@ -388,6 +388,10 @@ void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *
     if (qg > 64) qg = 64;
     if (qg > nq) qg = nq;
     const unsigned gy = (unsigned)((nq + qg - 1) / qg);
-    hipLaunchKernelGGL((scq16_kernel<H16_NT>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,
-                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax, clocks);
+#define PLAID_SCQ16_LAUNCH(GR)                                                                                                \
+    hipLaunchKernelGGL((scq16_kernel<H16_NT, GR>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,        \
+                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax, clocks)
+    if (groupmax) PLAID_SCQ16_LAUNCH(true);
+    else PLAID_SCQ16_LAUNCH(false);
+#undef PLAID_SCQ16_LAUNCH
 }

@@ -20,7 +20,8 @@ KERNELS = {
     "stage1_tail_kernelILi8ELb0E": ("k_scq.hip", 128, 64 << 10),
     "stage1_tail_kernelILi2ELb1E": ("k_scq.hip", 128, 64 << 10),   # ... also with the re-evaluations in double
     "stage1_tail_kernelILi8ELb1E": ("k_scq.hip", 128, 64 << 10),
-    "scq16_kernelILi2E": ("k_scq16.hip", 256, 40 << 10),       # two waves per SIMD, two to four workgroups per CU
+    "scq16_kernelILi2ELb1E": ("k_scq16.hip", 256, 40 << 10),   # two waves per SIMD, two to four workgroups per CU
+    "scq16_kernelILi2ELb0E": ("k_scq16.hip", 256, 32 << 10),   # without group maxima: the two operand buffers and nothing else
     # a wave per 2048 passages, 256 threads: what the workgroups per compute unit that its launch bounds name can have
     "s2_invert_kernelILi11EjLb0E": ("k_stage2.hip", 128, 40 << 10),   # 32-bit sets: four
     "s2_invert_kernelILi11EjLb1E": ("k_stage2.hip", 128, 40 << 10),

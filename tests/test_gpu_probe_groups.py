@@ -1,6 +1,6 @@
-"""The probes come from the maxima of 256-row groups, of 32-row tiles and of rows in turn, and rows that may be among the best
-are re-evaluated in double together: the probed centroids and the pruning map must be those of the exact scores at the edges
-of the groups, past the 1024 groups that stay in registers, where rows repeat (more ties than a token's lists and than one
+"""The probes come from the maxima of 256-row groups (where there are more than 1024 tiles), of 32-row tiles and of rows in turn,
+and rows that may be among the best are re-evaluated in double together: the probed centroids and the pruning map must be those
+of the exact scores at the edges of the groups, past the 1024 groups that stay in registers, where rows repeat (more ties than a token's lists and than one
 staging of rows hold) and for an index too small to lend the group maxima any memory."""
 import pytest
 import torch
@@ -9,9 +9,11 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # C, copies of each row next to each other, passages
-    (1, 1, 40), (31, 1, 40), (256, 1, 400), (257, 1, 400), (2049, 1, 400), (70_001, 1, 5000), (270_001, 1, 20_000),
+    (1, 1, 40), (31, 1, 40), (256, 1, 400), (257, 1, 400), (2049, 1, 400),
+    (32_768, 1, 5000), (32_769, 1, 5000), (70_001, 1, 5000), (270_001, 1, 20_000),
     (513, 2, 400), (3000, 3, 400), (4096, 6, 400), (6000, 40, 400), (20_000, 300, 2000),
-    (8000, 1, 20), (8000, 5, 20),  # fewer than C / 16 passages
+    (8000, 1, 20), (8000, 5, 20), (40_000, 1, 20),  # fewer than C / 16 passages
+    (33_000, 3, 5000), (36_000, 40, 5000), (40_000, 300, 5000),  # ties with groups
 ]
 
 
