@@ -1520,6 +1520,19 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
     }
 }
 
+// Ranges that a wave takes one after the other (waves: how many there are with one each).  The set-up of a workgroup (10 us when
+// the chip is full) is worth sharing once every SIMD has dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 /
+// 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M: 13.3 / 12.6 / 12.4 ms).  A single query of somewhat more ranges than the chip holds
+// waves (4096): two each, so that no second round of few waves follows the first and the second ranges find a threshold.  With
+// more ranges the second round is nearly a whole one and prunes by what the first has found, and half the waves, two ranges each, take
+// longer.  us per search with one / two, millions of passages, nprobe 4 and ndocs 4096: 8.8 290 / 276, 10.6 307 / 292, 12 303 / 288,
+// 12.8 311 / 297, 14 318 / 319, 16 318 / 340, 20 358 / 390; nprobe 1 and ndocs 256: 226 / 189, 230 / 188, 233 / 211, 227 / 213,
+// 246 / 242, 232 / 248, 260 / 284.
+static constexpr int s2_steps(int nq, int64_t waves)
+{
+    return waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 || (nq == 1 && waves > 4096 && waves <= 7000) ? 2 : 1);
+}
+
 void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
                                   const int64_t *ivf_offsets, const int32_t *ivf_pids, const uint32_t *table, const float *S,
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
@@ -1544,10 +1557,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // Passages per wave and step: 2048, fewer for indexes of so few passages that a wave's own chain of steps is all that
     // counts and the chip has room for more waves.  One query of 10 000 passages: 109 / 99 / 90 us per search with 2048 / 512 /
     // 128, of 60 000: 120 / 114 / 113, of 200 000: 103 / 103 / 122; five of 29 500: 135 / 134 / 120; 64 of 20 000: 185 / 172 /
-    // 196.  Steps per wave: the set-up of a workgroup (10 us when the chip is full) is worth sharing once every SIMD has
-    // dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 / 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M:
-    // 13.3 / 12.6 / 12.4 ms).  A single query of more ranges than the chip holds waves (4096): two each, so that all run at
-    // once and the second ranges find a threshold (8.8 M passages: 347 us per search with one, 322 with two).
+    // 196.
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
     if (ranges <= 40)
@@ -1556,7 +1566,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
     // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
     while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
-    const int steps = waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 || (nq == 1 && waves > 4096) ? 2 : 1);
+    const int steps = s2_steps(nq, waves);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
     // Passages a wave scores before there is a threshold: all waves of a query together about eight times the m that make
     // one, between 32 (fewer leave lanes idle) and 64 (more are scored, and counted, for nothing) -- or their share of m,

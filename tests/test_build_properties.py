@@ -139,3 +139,21 @@ def test_lds_arrays_accessed_in_16_byte_pieces_are_aligned(tmp_path, src, places
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
                         "--cuda-host-only", "-fsyntax-only", str(unit)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
+
+
+# What the rules that choose a kernel's form say on both sides of the lines that were measured: (source file, expression).
+RULES = [
+    # one query of 8.4, 8.8, 14 and 16, 20 million passages; two of 8.8; many
+    ("k_stage2.hip", ["s2_steps(1, 4096) == 1", "s2_steps(1, 4297) == 2", "s2_steps(1, 6836) == 2", "s2_steps(1, 7813) == 1",
+                      "s2_steps(1, 9766) == 1", "s2_steps(2, 8594) == 1", "s2_steps(512, 100352) == 2", "s2_steps(150, 644550) == 4"]),
+]
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+@pytest.mark.parametrize("src,claims", RULES, ids=[s for s, _ in RULES])
+def test_rules_on_sizes(tmp_path, src, claims):
+    unit = tmp_path / "rules.hip"
+    unit.write_text(f'#include "{src}"\n' + "".join(f'static_assert({c}, "{c}");\n' for c in claims))
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+                        "--cuda-host-only", "-fsyntax-only", str(unit)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
