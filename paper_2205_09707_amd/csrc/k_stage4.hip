@@ -768,6 +768,16 @@ void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, 
 #undef PLAID_VP_LAUNCH
 }
 
+// Many passages (48 per workgroup of a full chip, three per compute unit) in lists of some length: steps packed across passages, 32
+// passages per workgroup.  512 queries of 256 passages 374 -> 344 us (48, 64, 128 per workgroup: 381, 362, 390), 144 of 1024 488 -> 393
+// us (421, 401, 438).  Fewer passages: a wave's list of four leaves too few waves (256 queries of 64 48 -> 50 us, 23 of 250 25 -> 46 us,
+// 40 of 256 41 -> 49; from about 20 000 on little depends on it: 80 of 256 75 -> 70, 320 of 64 74 -> 72).  Short lists: the remainder of
+// each wave's list is filled up to a whole step, and a query has two workgroups that end together.  us of a launch with a passage at a
+// time / packed, 30 to 90 tokens and 8 to 180 with unit-length reconstruction, 512 queries: lists of 72 103 / 115, of 96 133 / 130 and
+// 159 / 167, of 128 162 / 157 and 193 / 199, of 192 234 / 224 and 281 / 285; 384 queries: of 96 115 / 108 and 134 / 139, of 128 140 / 119
+// and 162 / 153.
+static constexpr bool s4_packed(int n_upper, int nq) { return n_upper >= 96 && (int64_t)n_upper * nq >= 48ll * VP_RESIDENT_BLOCKS; }
+
 void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
                                     const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                     int nbits, int nq, const uint64_t *in_keys, int64_t in_stride,
@@ -776,12 +786,9 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
 {
     if (n_upper <= 0 || nq <= 0) return;
     // Few passages in all (short lists of few queries): a workgroup per passage.  Otherwise waves stride over the lists,
-    // several passages each, so that the per-workgroup set-up (table, query operands) is paid rarely.  From 48 passages per
-    // workgroup of a full chip (three per compute unit) on, steps packed across passages, 32 passages per workgroup: 512
-    // queries of 256 passages 374 -> 344 us (48, 64, 128 per workgroup: 381, 362, 390), 144 of 1024 488 -> 393 us (421, 401,
-    // 438); below, a wave's list of four passages leaves too few waves: 256 queries of 64 48 -> 50 us, 23 of 250 25 -> 46 us.
+    // several passages each, so that the per-workgroup set-up (table, query operands) is paid rarely.
     const int64_t all = (int64_t)n_upper * nq;
-    const bool coop = all <= 2048, pack = all >= 48ll * VP_RESIDENT_BLOCKS;
+    const bool coop = all <= 2048, pack = s4_packed(n_upper, nq);
     int gx = coop ? n_upper : (pack ? (n_upper + 31) / 32 : (n_upper + 3) / 4);
     // (256 compute units x 4 resident workgroups: one full round of waves, each striding over several passages)
     const int cap = coop ? 2048 : (S4_RESIDENT_BLOCKS + nq - 1) / nq;

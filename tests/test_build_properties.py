@@ -146,6 +146,9 @@ RULES = [
     # one query of 8.4, 8.8, 14 and 16, 20 million passages; two of 8.8; many
     ("k_stage2.hip", ["s2_steps(1, 4096) == 1", "s2_steps(1, 4297) == 2", "s2_steps(1, 6836) == 2", "s2_steps(1, 7813) == 1",
                       "s2_steps(1, 9766) == 1", "s2_steps(2, 8594) == 1", "s2_steps(512, 100352) == 2", "s2_steps(150, 644550) == 4"]),
+    # long lists in great number only
+    ("k_stage4.hip", ["s4_packed(256, 512)", "s4_packed(1024, 36)", "!s4_packed(1024, 35)", "s4_packed(96, 384)", "!s4_packed(72, 512)",
+                      "!s4_packed(64, 576)", "!s4_packed(64, 2048)", "!s4_packed(16, 2304)"]),
 ]
 
 
