@@ -1197,6 +1197,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
                 list_b = table[(int64_t)list_c * (nr + 1) + col + 1];
                 list_at = ivf_offsets[list_c];
             }
+            // The length depends on the column alone: a column's ranges all have the same, so that p0 stays a multiple of it and the
+            // wave's last range ends where its part does.
             int my_log = len_log;
             const int room = (two_areas ? 2 : 1) * FULL_PLANES * 64;  // words
             if (KMAX > FULL_PLANES && (n_ss << (my_log - 5)) > room) {

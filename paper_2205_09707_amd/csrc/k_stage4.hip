@@ -225,7 +225,7 @@ __device__ __forceinline__ int s4_token_of_lane(int lane)
 }
 
 // Passages are scored 32 tokens per step with v_mfma_f32_32x32x16_f16: rows = the 32 query tokens (A operand), columns
-// = 32 passage tokens (B operand); lane 32 h + r holds row / column r of its operand, dimensions 16 s + 8 h .. + 7 at
+// = 32 passage tokens (B operand); lane 32 h + r holds row / column r of its operand, dimensions s4_dim(s, h, 0) .. + 7 at
 // step s of the 128 dimensions.  A lane therefore decodes the residual of one passage token, gets the results of that
 // token's column (16 query tokens: 8 g + 4 h + 0..3), and adds the centroid's share from its own token's row of S_cq
 // (four 16-byte loads, no exchange between lanes).  It keeps 16 running maxima over the steps of a passage; the maxima
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
     __shared__ s4_half8 qs[2][8][64];  // [term][step][lane]
     __shared__ typename S4Entry<NBITS>::type hlut[S4_SECOND + 256];
     __shared__ __attribute__((aligned(16))) VpArea areas[4];
-    __shared__ float inv_norms[RN ? 4 : 1][RN ? VP_CAP : 1];
+    __shared__ __align__(16) float inv_norms[RN ? 4 : 1][RN ? VP_CAP : 1];
     extern __shared__ uint32_t probe_lds[];  // FILTER: keep_words words, when at most VP_LDS_WORDS
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -586,6 +586,9 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
                 m = s4_max3(m, x[2], x[3]);
                 const int slot = __builtin_amdgcn_readfirstlane(end[g]);
                 if (slot >= 0) {  // uniform
+                    // (The exchange needs two wait states after a vector instruction that writes its operands, and the compiler does not
+                    // count those in assembly statements, such as the one that made m.  It counts its own copy of m to the second
+                    // operand, which comes after that.)
                     const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
                     const float mm = s4_max(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
                     if (lane < QLEN) A.sums[slot][lane] = mm;

@@ -160,3 +160,22 @@ def test_rules_on_sizes(tmp_path, src, claims):
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
                         "--cuda-host-only", "-fsyntax-only", str(unit)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+def test_half_exchanges_wait_for_their_operands(tmp_path):
+    """v_permlane32_swap needs two wait states after a vector instruction that writes one of its operands.  The compiler sees to that,
+    but for instructions in assembly statements, whose results the exchanges of k_stage4.hip take."""
+    lines = [l.split(";")[0].strip() for l in _assembly("k_stage4.hip", str(tmp_path / "k_stage4.s")).splitlines()]
+    lines = [l for l in lines if l and not l.startswith(".") and not l.endswith(":")]
+    swaps = [i for i, l in enumerate(lines) if l.startswith("v_permlane32_swap")]
+    assert swaps
+    for i in swaps:
+        operands = re.findall(r"v\d+", lines[i])
+        states = 0
+        for l in reversed(lines[max(0, i - 2):i]):
+            if states >= 2:
+                break
+            op, _, rest = l.partition(" ")
+            assert not (op.startswith("v_") and re.match(r"v\d+", rest.strip()) and re.match(r"v\d+", rest.strip()).group(0) in operands), lines[i - 4:i + 1]
+            states += int(rest) + 1 if op == "s_nop" else 1

@@ -54,12 +54,16 @@ def test_final_scores_of_packed_lists(nbits, renormalize):
         if renormalize:
             pl.plaid_index_set_renormalize(idx, True)
         Q = torch.nn.functional.normalize(torch.randn(nq, 32, 128, generator=g, device="cuda"), dim=2).contiguous()
-        ids, scores = pl.plaid_search(idx, Q, 4, -1.0, 4 * n3, n3)
+        ids, scores, b = pl.plaid_search_debug(idx, Q, 4, -1.0, 4 * n3, n3, want=["sel3_ids", "n3"])
         torch.cuda.synchronize()
         for q in range(0, nq, 5):
             ref = _maxima(idx, pl, a["doc_offsets"], Q[q])
             got = ids[q] >= 0
-            assert int(got.sum()) == min(n3, int((ids[q] >= 0).sum())) and int(got.sum()) > 500
+            n = int(b["n3"][q])
+            assert 500 < n <= n3 and int(got.sum()) == n
+            # every passage of the list once, the best first
+            assert torch.equal(torch.sort(ids[q][got]).values, torch.sort(b["sel3_ids"][q, :n]).values)
+            assert bool((scores[q][got][1:] <= scores[q][got][:-1]).all())
             assert float((scores[q][got].double() - ref[ids[q][got].long()]).abs().max()) < pu.TOL
     finally:
         pl.plaid_index_free(idx)

@@ -43,7 +43,7 @@ def test_pruned_stage2_keeps_the_best(C, P, lo, hi, nq, seed, stage2):
 def _launch(P, nq):
     """The launch rules of k_stage2.hip for collections of more than 40 ranges of 2048 passages (and an ndocs far below P)."""
     ranges = -(-P // 2048)
-    steps = 4 if nq * ranges >= 16 * 12288 else (2 if nq * ranges >= 4 * 12288 else 1)
+    steps = 4 if nq * ranges >= 16 * 12288 else (2 if nq * ranges >= 4 * 12288 or (nq == 1 and 4096 < ranges <= 7000) else 1)
     blocks = -(-P // (4 * steps * 2048))
     spread = nq <= 32
     nqx = nq | 1 if spread else (nq + 7) // 8 * 8
@@ -80,3 +80,67 @@ def test_launches_that_fill_the_chip(monkeypatch, P, nq, claims, stage2):
     finally:
         pl.plaid_index_free(inv)
         pl.plaid_index_free(stream)
+
+
+def _uneven_columns(monkeypatch, pl, P, nq, forms):
+    """Passages of five tokens, each 2048 of them with tokens of another number (0 to 63) and choice of the first 63 centroids, and
+    nq queries whose token i lies between centroids 2 i and 2 i + 1: at a threshold of 0.55 those 63 survive, and the planes that
+    a range needs are as many as its column holds."""
+    import torch
+    C, length = 4096, 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
+    codes = torch.randint(64, C, (P, length), generator=g, device="cuda", dtype=torch.int32)
+    col = torch.arange(-(-P // 2048), device="cuda").repeat_interleave(63 * 2)
+    s = torch.arange(63, device="cuda").repeat_interleave(2).repeat(-(-P // 2048))
+    n = 7 * col % 64
+    at = col * 2048 + torch.randint(0, 2048, (col.numel(),), generator=g, device="cuda")
+    use = (s < n) & (at < P)
+    codes[at[use], s[use] % length] = ((5 * s + col) % 63).int()[use]
+    offsets = torch.arange(P + 1, device="cuda", dtype=torch.int64) * length
+    ivf_offsets, ivf_pids = pl.plaid_build_ivf(codes.reshape(-1), offsets, C)
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes.reshape(-1), "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
+              "residuals": torch.randint(0, 256, (P * length, 32), generator=g, device="cuda", dtype=torch.uint8),
+              "bucket_weights": torch.tensor([-0.05, -0.015, 0.015, 0.05], device="cuda")}
+    i = torch.arange(32, device="cuda")
+    near = cen[2 * i] + cen[(2 * i + 1).clamp_(max=62)]
+    Q = near / near.norm(dim=1, keepdim=True) + 0.01 * torch.randn(nq, 32, 128, generator=g, device="cuda")
+    Q[1::3, 20:] = Q[1::3, :12]  # every third query: tokens repeat, 40 survivors
+    Q = torch.nn.functional.normalize(Q, dim=2).contiguous()
+    index = []
+    for form in forms:
+        with monkeypatch.context() as mp:
+            mp.setenv("PLAID_STAGE2_FORM", form)
+            index.append(pl.plaid_index_from_view(arrays, 2, device=0, copy=False))
+    return index, Q, cen
+
+
+@pytest.mark.parametrize("P,nq,claims", [
+    (100_001, 1, {"two_areas": True, "steps": 1}),
+    (8_600_000, 1, {"two_areas": True, "steps": 2}),
+    (900_001, 9, {"one_instance": False, "steps": 1}),
+    (200_001, 512, {"one_instance": False, "steps": 2}),
+])
+def test_ranges_whose_planes_do_not_fit(monkeypatch, P, nq, claims):
+    """63 and 40 survivors without bitmaps: ranges whose columns hold more of them than a wave's area has planes for (26 or 24, 52 or 48
+    where it has two) go in halves or quarters, their neighbours whole, one or two ranges per wave."""
+    import torch
+
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    shape = _launch(P, nq)
+    assert {k: shape[k] for k in claims} == claims, shape
+    forms = ("stream", "inverted11", "inverted13")
+    index, Q, cen = _uneven_columns(monkeypatch, pl, P, nq, forms)
+    try:
+        for q in range(min(nq, 3)):
+            assert int(((cen @ Q[q].T).max(1).values >= 0.55).sum()) == (40 if q % 3 == 1 else 63)
+        for nprobe, ndocs in ((3, 900), (2, 100)):
+            want = pl.plaid_search(index[0], Q, nprobe, 0.55, ndocs, ndocs // 4)
+            for form, idx in zip(forms[1:], index[1:]):
+                got = pl.plaid_search(idx, Q, nprobe, 0.55, ndocs, ndocs // 4)
+                assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (form, nprobe, ndocs)
+    finally:
+        for idx in index:
+            pl.plaid_index_free(idx)
