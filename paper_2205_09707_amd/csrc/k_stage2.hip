@@ -548,6 +548,32 @@ __global__ __launch_bounds__(256) void ivr_dense_fill_kernel(const int64_t *__re
         }
     }
 }
+// total += entries x columns with an entry of the lists without a bitmap.
+__global__ __launch_bounds__(256) void ivr_plane_share_kernel(const uint32_t *__restrict__ table, const int32_t *__restrict__ dense_id,
+                                                              int64_t C, int64_t nr, double *__restrict__ total)
+{
+    __shared__ int32_t columns;
+    double sum = 0.0;
+    for (int64_t c = blockIdx.x; c < C; c += gridDim.x) {
+        if (dense_id[c] >= 0) continue;  // uniform
+        const uint32_t *row = table + c * (nr + 1);
+        if (threadIdx.x == 0) columns = 0;
+        __syncthreads();
+        int n = 0;
+        for (int64_t r = threadIdx.x; r < nr; r += 256) n += row[r + 1] > row[r] ? 1 : 0;
+        if (n) atomicAdd(&columns, n);
+        __syncthreads();
+        sum += (double)row[nr] * columns;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && sum > 0.0) atomicAdd(total, sum);
+}
+void plaid_launch_ivf_plane_share(hipStream_t st, const uint32_t *table, const int32_t *dense_id, int64_t C, int64_t P, int shift,
+                                  double *total)
+{
+    const int64_t nr = (P + (1ll << shift) - 1) >> shift;
+    hipLaunchKernelGGL(ivr_plane_share_kernel, dim3((unsigned)(C < 4096 ? C : 4096)), dim3(256), 0, st, table, dense_id, C, nr, total);
+}
 void plaid_launch_ivf_dense_mark(hipStream_t st, const int64_t *ivf_offsets, int64_t C, int64_t P, int32_t *dense_id,
                                  int32_t *counter)
 {
@@ -833,6 +859,9 @@ __global__ __launch_bounds__(64 * IV_WAVES) void s2_candidates_kernel(
 #define S2_UNIT_BLOCKS 4
 #define S2_GATHER_BLOCKS (256 * S2_UNIT_BLOCKS)
 #define S2_FITS_BLOCKS 768    // launches of up to this many workgroups run the 64-bit instance alone
+#define S2_PLANES 26          // of a wave of the 64-bit instance, and of the one that is TALL
+#define S2_TALL_PLANES 36
+#define S2_TALL_UNIT_BLOCKS 3
 #define S2_GATHER_STRIDE 68   // of a passage's list: eight lanes that read one column of eight lists hit all banks
 struct S2GatherScratch {
     S2CandScratch cand;
@@ -1032,9 +1061,11 @@ __device__ __forceinline__ uint32_t s2_sum_reaches(const uint32_t (&A)[S2_UB_BIT
 // SHIFT: log2 of the passages per range-table column.  SetT: word that holds a bag's slot set; the 32-bit instance serves
 // the queries with at most 31 surviving centroids, the 64-bit instance the others (for small launches: all queries).
 // PLAIN: no copies of the histogram and no candidate words given (large batches; the two cost the kernel 2 % there).
+// ALL: a 64-bit instance that is launched alone and takes every query; only these lend areas.
+// TALL: a 64-bit instance with more planes and fewer workgroups per compute unit (s2_tall_queries).
 static_assert(IV_WAVES == 4, "a workgroup is a wave per SIMD");
-template <int SHIFT, typename SetT, bool PLAIN>
-__global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kernel(
+template <int SHIFT, typename SetT, bool PLAIN, bool ALL, bool TALL>
+__global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT_BLOCKS) void s2_invert_kernel(
     const int32_t *__restrict__ uniq, const int32_t *__restrict__ n_uniq, int uniq_stride,
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
@@ -1043,15 +1074,15 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
     int32_t *__restrict__ hist, Sel2State *__restrict__ state,
     uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
     int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
-    int steps, int32_t m, int first_batch, unsigned main_blocks)
+    int steps, int32_t m, int first_batch, unsigned main_blocks, uint32_t tall)
 {
     constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
     // Planes of 64 words that fit a wave's area: what lets four workgroups share a compute unit.  Only lists with an entry in
     // the range's column need one: of the 20 to 32 lists without a bitmap that a query of 40 survivors has on 8.8 M passages,
-    // five or more have none in 2048 passages.  Where there are more planes than fit, one wave takes two waves' area if the
-    // launch has workgroups to spare (mode bit 5), otherwise half or a quarter of the passages at a time.  (36 planes and
-    // three workgroups: 150 queries of 8.8 M passages 8.66 ms, this 7.2.)
-    constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? 26 : 24);
+    // five or more have none in 2048 passages.  Where there are more planes than fit, one wave takes the area of two, or of all
+    // four, if the launch has workgroups to spare (mode bits 5 and 7), otherwise half or a quarter of the passages at a time.  (36
+    // planes and three workgroups for all queries: 150 of 8.8 M passages 8.66 ms, this 7.2.)
+    constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? (TALL ? S2_TALL_PLANES : S2_PLANES) : 24);
     static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
     constexpr int SLOTS = KMAX + 1;
     constexpr int MORE = SHIFT == 11 ? 2 : 4;  // loads in flight per lane of a long list (of a coarse column: four times as long)
@@ -1097,20 +1128,19 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
     }
     // This instance's queries, from the lists the probe kernel made: class 1 (1..31 survivors) or 2 (32..63), and with the
     // 32-bit instance class 0 (none) unless s2_union_wide_kernel has produced its candidate and empty-bag words (mode bit
-    // 0).  mode bit 1 (64-bit instance): the only instance launched, it takes every query of these classes.  Bit 3: see the
-    // launch.  Queries with more survivors belong to the workgroups above.  Consecutive workgroups take
+    // 0).  ALL: every query of these classes.  Bit 3: see the launch.  Queries with more survivors belong to the workgroups above.  Consecutive workgroups take
     // consecutive queries of one passage range: all queries of a chunk advance together, so that each has a threshold to
     // prune with after its first ranges, and the bitmap rows of the range are shared in the caches.
     const int cls = sizeof(SetT) == 4 ? 1 : 2;
-    const bool take_all = sizeof(SetT) == 8 && (mode & 2);
-    const bool single = take_all && (mode & 4);  // one query: number 0, whatever its class
-    const int n_first = single ? 1 : (take_all ? qcount[1] : qcount[cls]);
-    const int n_second = take_all && !single ? qcount[2] : 0;
-    const int n_none = ((cls == 1 || take_all) && !single && !(mode & 1)) ? qcount[0] : 0;
+    static_assert(!ALL || sizeof(SetT) == 8, "31 slots do not do for every query");
+    const bool single = ALL && (mode & 4);  // one query: number 0, whatever its class
+    const int n_first = single ? 1 : (ALL ? qcount[1] : qcount[cls]);
+    const int n_second = ALL && !single ? qcount[2] : 0;
+    const int n_none = ((cls == 1 || ALL) && !single && !(mode & 1)) ? qcount[0] : 0;
     const int n_all = n_first + n_second + n_none;
     const int rb = (int)(blockIdx.x / (unsigned)nqx);
     for (int qi = (int)(blockIdx.x % (unsigned)nqx); qi < n_all; qi += nqx) {
-        const int q = single ? 0 : s2_uniform(qi < n_first ? qlist[(int64_t)(take_all ? 1 : cls) * qlist_stride + qi]
+        const int q = single ? 0 : s2_uniform(qi < n_first ? qlist[(int64_t)(ALL ? 1 : cls) * qlist_stride + qi]
                                               : (qi < n_first + n_second ? qlist[2ll * qlist_stride + qi - n_first]
                                                                          : qlist[qi - n_first - n_second]));
         // everything that does not depend on the number of survivors is requested at once (the tables have room for
@@ -1120,9 +1150,11 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
         const int gain_any = reinterpret_cast<const uint16_t *>(T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN)[lane];
         const int probed_c = tid < uniq_stride ? uniq[(int64_t)q * uniq_stride + tid] : 0;
         const int K_all = s2_uniform(mt.K);
-        if (!take_all && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
+        if (!ALL && (K_all <= 31) != (sizeof(SetT) == 4)) continue;  // (never: the lists are made from the same K)
         if (K_all > KMAX) continue;  // (a single query of the gather form)
-        if (KMAX > FULL_PLANES && K_all <= FULL_PLANES && (int64_t)rb * IV_WAVES * steps >= (P + (1ll << len_log) - 1) >> len_log) continue;  // spare
+        if (sizeof(SetT) == 8 && !ALL && ((tall >> (K_all - 32)) & 1u) != (TALL ? 1u : 0u)) continue;  // the other 64-bit instance's
+        const int lend_most = K_all <= FULL_PLANES ? 0 : (K_all <= 2 * FULL_PLANES ? 1 : 2);
+        if (ALL && ((int64_t)rb * IV_WAVES * steps) >> lend_most >= (P + (1ll << len_log) - 1) >> len_log) continue;  // spare
         const int K = K_all;
         const int nu = n_uniq[q];
         __syncthreads();  // the previous query's readers are done
@@ -1169,8 +1201,9 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
         const uint32_t pm0 = s2_uniform((int)probed_mask[0]), pm1 = s2_uniform((int)probed_mask[1]);
         const int n_rows = s2_uniform(n_front[0]), n_ss = s2_uniform(n_sparse), n_dense = K - n_ss;
         const int n_sp = s2_uniform(n_front[1]);
-        const bool two_areas = KMAX > FULL_PLANES && (mode & 32) && n_ss > FULL_PLANES;
-        uint32_t *area = two_areas ? area_all[(2 * wave) % IV_WAVES] : area_all[wave];
+        // log2 of the areas that a wave takes
+        const int lend = ALL && (mode & 32) && n_ss > FULL_PLANES ? ((mode & 128) && n_ss > 2 * FULL_PLANES ? 2 : 1) : 0;
+        uint32_t *area = area_all[(wave << lend) % IV_WAVES];
         // lane i: the i-th slot with a bitmap and its row / the i-th slot without one and its centroid
         const int dense_slot = lane < n_dense ? order[lane] : 0, dense_row = lane < n_dense ? drow[dense_slot] : 0;
         const int list_slot = lane < n_ss ? order[SLOTS - 1 - lane] : 64, list_c = lane < n_ss ? kid[list_slot] : -1;
@@ -1179,9 +1212,10 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
         uint32_t *ebq = emptybits + (int64_t)q * cand_words;
         int32_t *hist_q = hist + (int64_t)q * SEL_BINS;
         int32_t *coarse_q = hist_q + (!PLAIN && (mode & 8) ? (blockIdx.x & (S2_COPIES - 1)) : 0) * S2_COARSE;
-        const int64_t first = ((int64_t)(rb * (two_areas ? IV_WAVES / 2 : IV_WAVES) + wave) * steps) << len_log;
+        const int64_t first = ((int64_t)(rb * (IV_WAVES >> lend) + wave) * steps) << len_log;
         int64_t last = first + ((int64_t)steps << len_log) < P ? first + ((int64_t)steps << len_log) : P;
-        if (two_areas && wave >= IV_WAVES / 2) last = first;  // its area is lent
+        if (wave >= IV_WAVES >> lend) last = first;  // its area is lent
+        const int room = (FULL_PLANES * 64) << lend;  // words
         const int lane0 = lane;
         int len;
         for (int64_t p0 = first; p0 < last; p0 += len) {  // uniform
@@ -1200,7 +1234,6 @@ __global__ __launch_bounds__(64 * IV_WAVES, S2_UNIT_BLOCKS) void s2_invert_kerne
             // The length depends on the column alone: a column's ranges all have the same, so that p0 stays a multiple of it and the
             // wave's last range ends where its part does.
             int my_log = len_log;
-            const int room = (two_areas ? 2 : 1) * FULL_PLANES * 64;  // words
             if (KMAX > FULL_PLANES && (n_ss << (my_log - 5)) > room) {
                 const int n = __popcll(__ballot(lane < n_ss && list_b > list_a));
                 while ((n << (my_log - 5)) > room) --my_log;
@@ -1535,12 +1568,32 @@ static constexpr int s2_steps(int nq, int64_t waves)
     return waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 || (nq == 1 && waves > 4096 && waves <= 7000) ? 2 : 1);
 }
 
+// The numbers of survivors K (bit K - 32) whose queries the TALL instance takes in launches of many workgroups.  share: how
+// often a surviving centroid needs a plane (plaid_launch_ivf_plane_share): K of them need K share, give or take the root of K share
+// (1 - share).  With 26 planes four workgroups run on a compute unit, with 36 three: the second wins where it goes through whole
+// ranges or halves and the first through halves or quarters.  Even lists of 2 M passages, share 0.97, 200 queries, us per search with
+// 26 / 36 planes: K = 33 2573 / 2225, 36 2742 / 2337, 40 2977 / 3478, 52 3402 / 4019, 56 4562 / 4141, 62 4885 / 4433; share 0.85: K = 33
+// 2383 / 1999, 40 2554 / 2427, 46 2669 / 3131, 62 4101 / 3678; share 0.71: K = 33 2012 / 2024, 36 2314 / 2062, 46 2745 / 2538, 52 2852 /
+// 3172.  Popularities as uneven as Zipf(1.1) give 0.4 to 0.5; so few planes leave little to gain, and their launches are spared one
+// that is mostly empty.
+static constexpr uint32_t s2_tall_queries(double share)
+{
+    uint32_t set = 0u;
+    if (share > 1.0) share = 1.0;
+    for (int K = 32; share > 0.65 && K <= S2_MAX_KEPT; ++K) {
+        const double n = K * share;
+        auto fit = [=](double planes) { return n <= planes && 4.0 * (planes - n) * (planes - n) >= n * (1.0 - share); };
+        if ((!fit(S2_PLANES + 0.5) && fit(S2_TALL_PLANES + 0.5)) || !fit(2 * S2_PLANES + 0.5)) set |= 1u << (K - 32);
+    }
+    return set;
+}
+
 void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
                                   const int64_t *ivf_offsets, const int32_t *ivf_pids, const uint32_t *table, const float *S,
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift, int32_t m)
+                                  const uint32_t *dense_bits, double plane_share, int shift, int32_t m)
 {
     const int64_t nr = (P + (1ll << shift) - 1) >> shift;
     const int64_t nwide = (P + (1ll << UW_SHIFT) - 1) >> UW_SHIFT;
@@ -1579,13 +1632,15 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
     const int64_t words = (nq * cand_words + 7) & ~7ll;
     const unsigned gather = words < S2_GATHER_BLOCKS ? (unsigned)words : S2_GATHER_BLOCKS;
-#define S2_INVERT(SH_, T_, PLAIN_, MODE_, NQX_, BLOCKS_)                                                                                     \
-    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_, PLAIN_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (sizeof(T_) == 8 ? gather : 0u)),     \
+    const unsigned gather_tall = words < 256 * S2_TALL_UNIT_BLOCKS ? (unsigned)words : 256 * S2_TALL_UNIT_BLOCKS;
+    const uint32_t tall = shift == 11 ? s2_tall_queries(plane_share) : 0u;
+#define S2_INVERT(SH_, T_, PLAIN_, ALL_, TALL_, MODE_, NQX_, BLOCKS_, GATHER_)                                                                            \
+    hipLaunchKernelGGL((s2_invert_kernel<SH_, T_, PLAIN_, ALL_, TALL_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (GATHER_)),                    \
                        dim3(64 * IV_WAVES), 0, st, uniq,                                                                      \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
                        P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.state,         \
                         b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
-                       steps, m, first_batch, (unsigned)((BLOCKS_) * (NQX_)))
+                       steps, m, first_batch, (unsigned)((BLOCKS_) * (NQX_)), tall)
     // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
     // updates alone).  Workgroups are dealt to the eight XCDs in turn: with many queries their number, per passage range,
     // is made a multiple of eight (empty ones added), so that a query's workgroups share an XCD.  With few, that would
@@ -1604,27 +1659,32 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int own = copies | given;
     // Few workgroups, at most S2_FITS_BLOCKS: the 64-bit instance alone, taking every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
     // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
-    // 65 / 70); with twice the workgroups,
-    // so that queries with more slots than a wave's area holds can have two (mode bit 5).  More: the 32-bit
+    // 65 / 70); with twice the workgroups, so that queries with more slots than a wave's area holds can have two (mode bit 5), or
+    // four times, where they all run at once, for four areas (bit 7).  More: the 32-bit
     // instance's scoring wins (eight of 2 M: 232 with two, 327 with one).  The line: 768 and 1024 make no difference beyond
     // 2 % (16 of 400 000: 166 / 164 us per search, 32 and 40 of 200 000: 146 / 143 and 155 / 152, eight of 1 M: 160 / 160).
     const bool fits = blocks * nqx <= S2_FITS_BLOCKS;
     if (nq < 8 || fits) {
-        const int mode = wide | 2 | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0);
-        const int64_t all = fits ? 2 * blocks : blocks;
-        if (shift == 11) S2_INVERT(11, unsigned long long, false, mode, nqx, all);
-        else S2_INVERT(13, unsigned long long, false, mode, nqx, all);
+        const bool fits4 = 4 * blocks * nqx <= 256 * S2_UNIT_BLOCKS;
+        const int mode = wide | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0) | (fits4 ? 128 : 0);
+        const int64_t all = fits4 ? 4 * blocks : (fits ? 2 * blocks : blocks);
+        // (where the second areas do not come from workgroups that run at once, queries of 27 to 36 lists are better off with the
+        // planes for them: twelve of 400 000 passages, even lists, K = 33 211 -> 164 us)
+        if (tall && fits && 2 * blocks * nqx > 256 * S2_UNIT_BLOCKS) S2_INVERT(11, unsigned long long, false, true, true, mode, nqx, all, gather_tall);
+        else if (shift == 11) S2_INVERT(11, unsigned long long, false, true, false, mode, nqx, all, gather);
+        else S2_INVERT(13, unsigned long long, false, true, false, mode, nqx, all, gather);
     } else {
         // the class of the 64-bit instance is empty or small more often than not: 128 columns of workgroups share it
         const int many = nqx < 128 ? nqx : 128;
         if (shift == 11) {
-            if (own) S2_INVERT(11, uint32_t, false, wide | own, nqx, blocks);
-            else S2_INVERT(11, uint32_t, true, wide, nqx, blocks);
-            S2_INVERT(11, unsigned long long, false, wide | own, many, blocks);
+            if (own) S2_INVERT(11, uint32_t, false, false, false, wide | own, nqx, blocks, 0u);
+            else S2_INVERT(11, uint32_t, true, false, false, wide, nqx, blocks, 0u);
+            if (tall) S2_INVERT(11, unsigned long long, false, false, true, wide | own, many, blocks, 0u);
+            S2_INVERT(11, unsigned long long, false, false, false, wide | own, many, blocks, gather);
         } else {
-            if (own) S2_INVERT(13, uint32_t, false, wide | own, nqx, blocks);
-            else S2_INVERT(13, uint32_t, true, wide, nqx, blocks);
-            S2_INVERT(13, unsigned long long, false, wide | own, many, blocks);
+            if (own) S2_INVERT(13, uint32_t, false, false, false, wide | own, nqx, blocks, 0u);
+            else S2_INVERT(13, uint32_t, true, false, false, wide, nqx, blocks, 0u);
+            S2_INVERT(13, unsigned long long, false, false, false, wide | own, many, blocks, gather);
         }
     }
 #undef S2_INVERT

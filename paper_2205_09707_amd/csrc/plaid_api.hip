@@ -71,6 +71,7 @@ struct plaid_index {
     int32_t ivr_shift = 11;         // log2 of the passages per table column (11 or 13)
     int32_t *dense_id = nullptr;    // with the range table: bitmap row of each centroid's list, -1 for all but the longest
     uint32_t *dense_bits = nullptr; // [rows][ceil(P / 32)]
+    double plane_share = 0.0;       // plaid_launch_ivf_plane_share's total over entries and columns
     // vanilla ColBERTv2 retrieval (built on its first use): embedding-level inverted lists and the passage of each token
     int64_t *emb_offsets = nullptr;  // [C + 1]
     int32_t *emb_ids = nullptr;      // [N] ascending token indices per centroid
@@ -243,18 +244,22 @@ static int build_range_table(plaid_index *ix)
     HIP_TRY(hipStreamSynchronize(nullptr));
     // bitmaps of the longest lists
     const int64_t words = (ix->P + 31) / 32;
-    int32_t *did = nullptr, *counter = nullptr;
-    if (hipMalloc((void **)&did, (size_t)ix->C * 4) != hipSuccess || hipMalloc((void **)&counter, 4) != hipSuccess) {
+    int32_t *did = nullptr;
+    struct { int64_t rows; double planes; } sums = {0, 0.0}, *counter = nullptr;
+    if (hipMalloc((void **)&did, (size_t)ix->C * 4) != hipSuccess || hipMalloc((void **)&counter, sizeof(sums)) != hipSuccess) {
         (void)hipGetLastError();
         if (did) (void)hipFree(did);
         return fail(PLAID_ENOMEM, "hipMalloc for the dense-list index failed");
     }
     ix->owned.push_back(did);
     ix->owned.push_back(counter);
-    HIP_TRY(hipMemset(counter, 0, 4));
-    plaid_launch_ivf_dense_mark(nullptr, ix->ivf_offsets, ix->C, ix->P, did, counter);
-    int32_t rows = 0;
-    HIP_TRY(hipMemcpy(&rows, counter, 4, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemset(counter, 0, sizeof(sums)));
+    plaid_launch_ivf_dense_mark(nullptr, ix->ivf_offsets, ix->C, ix->P, did, (int32_t *)&counter->rows);
+    if (shift == 11) plaid_launch_ivf_plane_share(nullptr, (const uint32_t *)d, did, ix->C, ix->P, shift, &counter->planes);
+    HIP_TRY(hipMemcpy(&sums, counter, sizeof(sums), hipMemcpyDeviceToHost));
+    const int64_t rows = sums.rows;
+    const double columns = (double)((ix->P + (1ll << shift) - 1) >> shift);
+    ix->plane_share = ix->ivf_len > 0 ? sums.planes / ((double)ix->ivf_len * columns) : 0.0;
     void *db = nullptr;
     const size_t dbytes = (size_t)(rows > 0 ? rows : 1) * (size_t)words * 4;
     if (hipMalloc(&db, dbytes) != hipSuccess) {
@@ -843,7 +848,7 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         if (ix->ivr_table)
             plaid_launch_stage2_inverted(st, w.uniq, w.n_uniq, w.uniq_stride, ix->ivf_offsets, ix->ivf_pids, ix->ivr_table, w.S,
                                          C, w.keepbits, w.keep_words, ix->codes, ix->doc_offsets, P, n, w.s2, w.candbits,
-                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->ivr_shift, pl.nd);
+                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->plane_share, ix->ivr_shift, pl.nd);
         else
             plaid_launch_stage2(st, w.S, C, w.keepbits, w.keep_words, w.probed, nprobe, w.candbits, w.cand_words, P, ix->N,
                                 ix->doc_offsets, ix->codes, n, w.s2, w.keys2, P);

@@ -299,7 +299,12 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, int shift, int32_t m);
+                                  const uint32_t *dense_bits, double plane_share, int shift, int32_t m);
+// total[0] (zero before the call) += over the lists without a bitmap, entries x table columns in which the list has an entry: divided
+// by all entries and by the columns, how often a centroid, picked by its number of passages, has entries but no bitmap where stage 2
+// looks for them.
+void plaid_launch_ivf_plane_share(hipStream_t st, const uint32_t *table, const int32_t *dense_id, int64_t C, int64_t P, int shift,
+                                  double *total);
 // Bitmaps over the passages for the longest inverted lists (built once per index, next to the range table):
 // dense_id[c] = bitmap row of centroid c or -1 (counter[0], zero before the call, returns the number of rows);
 // bits: rows x words, zero before the call, words = ceil(P / 32).

@@ -23,12 +23,16 @@ KERNELS = {
     "scq16_kernelILi2ELb1E": ("k_scq16.hip", 256, 40 << 10),   # two waves per SIMD, two to four workgroups per CU
     "scq16_kernelILi2ELb0E": ("k_scq16.hip", 256, 32 << 10),   # without group maxima: the two operand buffers and nothing else
     # a wave per 2048 passages, 256 threads: what the workgroups per compute unit that its launch bounds name can have
-    "s2_invert_kernelILi11EjLb0E": ("k_stage2.hip", 128, 40 << 10),   # 32-bit sets: four
-    "s2_invert_kernelILi11EjLb1E": ("k_stage2.hip", 128, 40 << 10),
-    "s2_invert_kernelILi13EjLb0E": ("k_stage2.hip", 128, 40 << 10),
-    "s2_invert_kernelILi13EjLb1E": ("k_stage2.hip", 128, 40 << 10),
-    "s2_invert_kernelILi11EyLb0E": ("k_stage2.hip", 128, 40 << 10),   # 64-bit sets: four
-    "s2_invert_kernelILi13EyLb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi11EjLb0ELb0ELb0E": ("k_stage2.hip", 128, 40 << 10),   # 32-bit sets: four
+    "s2_invert_kernelILi11EjLb1ELb0ELb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi13EjLb0ELb0ELb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi13EjLb1ELb0ELb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi11EyLb0ELb0ELb0E": ("k_stage2.hip", 128, 40 << 10),   # 64-bit sets: four
+    "s2_invert_kernelILi13EyLb0ELb0ELb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi11EyLb0ELb1ELb0E": ("k_stage2.hip", 128, 40 << 10),   # ... launched alone
+    "s2_invert_kernelILi13EyLb0ELb1ELb0E": ("k_stage2.hip", 128, 40 << 10),
+    "s2_invert_kernelILi11EyLb0ELb0ELb1E": ("k_stage2.hip", 168, 53 << 10),   # ... with 36 planes per wave: three
+    "s2_invert_kernelILi11EyLb0ELb1ELb1E": ("k_stage2.hip", 168, 53 << 10),
     "s2_candidates_kernel": ("k_stage2.hip", 64, 8 << 10),
     "s2_union_wide_kernel": ("k_stage2.hip", 128, 80 << 10),       # two workgroups of 1024 threads per CU
     "s2_stream_kernel": ("k_stage2.hip", 128, 40 << 10),
@@ -114,7 +118,8 @@ def test_gather_form_has_the_workgroups_that_run_at_once(tmp_path):
                              stderr=subprocess.DEVNULL, text=True).stdout
     define = dict(re.findall(r"^#define (S2_GATHER_BLOCKS|S2_UNIT_BLOCKS)\s+(.*?)(?://.*)?$", defines, re.M))
     blocks = eval(define["S2_GATHER_BLOCKS"].strip(), {}, {k: int(v) for k, v in define.items() if v.strip().isdigit()})
-    for key in ("s2_invert_kernelILi11EyLb0E", "s2_invert_kernelILi13EyLb0E"):
+    for key in ("s2_invert_kernelILi11EyLb0ELb0ELb0E", "s2_invert_kernelILi13EyLb0ELb0ELb0E", "s2_invert_kernelILi11EyLb0ELb1ELb0E",
+                "s2_invert_kernelILi13EyLb0ELb1ELb0E"):
         m, = [m for n, m in meta.items() if key in n]
         vgprs = -(-(m["vgpr_count"] + m["agpr_count"]) // 8) * 8
         assert blocks == 256 * min(512 // vgprs, (160 << 10) // m["group_segment_fixed_size"]), (key, blocks, m)
@@ -145,7 +150,11 @@ def test_lds_arrays_accessed_in_16_byte_pieces_are_aligned(tmp_path, src, places
 RULES = [
     # one query of 8.4, 8.8, 14 and 16, 20 million passages; two of 8.8; many
     ("k_stage2.hip", ["s2_steps(1, 4096) == 1", "s2_steps(1, 4297) == 2", "s2_steps(1, 6836) == 2", "s2_steps(1, 7813) == 1",
-                      "s2_steps(1, 9766) == 1", "s2_steps(2, 8594) == 1", "s2_steps(512, 100352) == 2", "s2_steps(150, 644550) == 4"]),
+                      "s2_steps(1, 9766) == 1", "s2_steps(2, 8594) == 1", "s2_steps(512, 100352) == 2", "s2_steps(150, 644550) == 4",
+                      # which of 32 (bit 0) to 63 survivors: a list in every range, in most of them, and where few need planes
+                      "s2_tall_queries(1.0) == 0xFFE0001Fu", "s2_tall_queries(0.9999) == 0xFFE0001Fu", "s2_tall_queries(0.975) == 0xFFC0001Fu",
+                      "s2_tall_queries(0.85) == 0xE00003FFu", "s2_tall_queries(0.71) == 0x0003FFF0u",
+                      "s2_tall_queries(0.65) == 0", "s2_tall_queries(0.0) == 0"]),
     # long lists in great number only
     ("k_stage4.hip", ["s4_packed(256, 512)", "s4_packed(1024, 36)", "!s4_packed(1024, 35)", "s4_packed(96, 384)", "!s4_packed(72, 512)",
                       "!s4_packed(64, 576)", "!s4_packed(64, 2048)", "!s4_packed(16, 2304)"]),

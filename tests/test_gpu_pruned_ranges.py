@@ -48,7 +48,8 @@ def _launch(P, nq):
     spread = nq <= 32
     nqx = nq | 1 if spread else (nq + 7) // 8 * 8
     return {"steps": steps, "copies": spread and nq * blocks > 64, "padded": not spread and nqx > nq,
-            "one_instance": nq < 8 or blocks * nqx <= 768, "two_areas": blocks * nqx <= 768}
+            "one_instance": nq < 8 or blocks * nqx <= 768, "two_areas": blocks * nqx <= 768,
+            "four_areas": 4 * blocks * nqx <= 1024, "tall_alone": 1024 < 2 * blocks * nqx <= 1536}
 
 
 @pytest.mark.parametrize("P,nq,claims", [
@@ -117,14 +118,19 @@ def _uneven_columns(monkeypatch, pl, P, nq, forms):
 
 
 @pytest.mark.parametrize("P,nq,claims", [
-    (100_001, 1, {"two_areas": True, "steps": 1}),
-    (8_600_000, 1, {"two_areas": True, "steps": 2}),
+    (100_001, 1, {"four_areas": True, "steps": 1}),
+    (400_000, 5, {"four_areas": True, "steps": 1}),
+    (600_001, 5, {"four_areas": False, "two_areas": True, "steps": 1}),
+    (500_000, 11, {"two_areas": True, "tall_alone": True}),
+    (8_600_000, 1, {"four_areas": False, "two_areas": True, "steps": 2}),
     (900_001, 9, {"one_instance": False, "steps": 1}),
     (200_001, 512, {"one_instance": False, "steps": 2}),
 ])
 def test_ranges_whose_planes_do_not_fit(monkeypatch, P, nq, claims):
-    """63 and 40 survivors without bitmaps: ranges whose columns hold more of them than a wave's area has planes for (26 or 24, 52 or 48
-    where it has two) go in halves or quarters, their neighbours whole, one or two ranges per wave."""
+    """63 and 40 survivors without bitmaps: ranges whose columns hold more of them than a wave's area has planes for (26 or 24, twice or
+    four times that where it has the areas of others) go in halves or quarters, their neighbours whole, one or two ranges per wave.
+    Nine columns in ten hold a given list, so that with columns of 2048 passages and many workgroups the 63 go to the
+    instance of 36 planes and the 40 do not (launches of some workgroups run that instance alone, also for queries of more than 63)."""
     import torch
 
     import paper_2205_09707_amd as pl
@@ -136,11 +142,11 @@ def test_ranges_whose_planes_do_not_fit(monkeypatch, P, nq, claims):
     try:
         for q in range(min(nq, 3)):
             assert int(((cen @ Q[q].T).max(1).values >= 0.55).sum()) == (40 if q % 3 == 1 else 63)
-        for nprobe, ndocs in ((3, 900), (2, 100)):
-            want = pl.plaid_search(index[0], Q, nprobe, 0.55, ndocs, ndocs // 4)
+        for nprobe, t_cs, ndocs in ((3, 0.55, 900), (2, 0.55, 100), (2, 0.3, 900)):
+            want = pl.plaid_search(index[0], Q, nprobe, t_cs, ndocs, ndocs // 4)
             for form, idx in zip(forms[1:], index[1:]):
-                got = pl.plaid_search(idx, Q, nprobe, 0.55, ndocs, ndocs // 4)
-                assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (form, nprobe, ndocs)
+                got = pl.plaid_search(idx, Q, nprobe, t_cs, ndocs, ndocs // 4)
+                assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (form, nprobe, t_cs, ndocs)
     finally:
         for idx in index:
             pl.plaid_index_free(idx)
