@@ -764,8 +764,11 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok)
 #define TAIL_PARTS (TAIL_THREADS / (QLEN / 4))  // threads that share four tokens
 #define TAIL_SEL 16   // listed groups, and listed tiles, per token
 #define TAIL_XCAP 32  // listed rows per token: one per lane
-#define TAIL_ROWS 128  // rows staged at most for the re-evaluation of the probes, half of their dimensions at a time; more of them
-                       // are re-evaluated straight from memory, a lane each
+// Rows staged at most for the re-evaluation of the probes, half of their dimensions at a time: 32 tokens with four each.  More of them
+// (a near tie at nprobe 4, most queries from 5 on) are re-evaluated straight from memory, a lane each.  At 128 rows each wave has one
+// tile; no step shows there.  Probe kernel, us, 65536 centroids, nprobe 2 / 3 / 4 / 5 / 6 / 8: one query 19.4 / 24.4 / 29.0 / 32.3 /
+// 35.7 / 43.4, 32 queries 20.4 / 25.8 / 31.1 / 33.6 / 37.2 / 45.2, 512 81 / 107 / 125 / 142 / 157 / 190.
+#define TAIL_ROWS 128
 #define TAIL_HSTRIDE (DIM / 2 + 4)  // floats per staged half row
 struct Stage1Exact {        // what the re-evaluations need (APPROX only)
     const float *Cm;        // [C][128] centroids

@@ -1660,7 +1660,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // Few workgroups, at most S2_FITS_BLOCKS: the 64-bit instance alone, taking every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
     // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
     // 65 / 70); with twice the workgroups, so that queries with more slots than a wave's area holds can have two (mode bit 5), or
-    // four times, where they all run at once, for four areas (bit 7).  More: the 32-bit
+    // four times, where they all run at once, for four areas (bit 7; four queries of 400 000 passages, even lists, 62 survivors 192 ->
+    // 148 us).  More: the 32-bit
     // instance's scoring wins (eight of 2 M: 232 with two, 327 with one).  The line: 768 and 1024 make no difference beyond
     // 2 % (16 of 400 000: 166 / 164 us per search, 32 and 40 of 200 000: 146 / 143 and 155 / 152, eight of 1 M: 160 / 160).
     const bool fits = blocks * nqx <= S2_FITS_BLOCKS;

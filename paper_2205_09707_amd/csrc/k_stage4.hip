@@ -425,7 +425,7 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
 // scored: their keys get score 0.  cand: [q][cand_stride] ascending candidate pids, in_counts[q] of them; out_keys[q][j] =
 // key of cand[q][j].  The candidates of different queries are mostly the same passages: workgroup L takes query
 // L / 8 % nq and a share of the (L % 8)-th eighth of its candidates, so that the queries read a passage at about the same
-// time through the same partition's cache (16 queries: 17 GB from memory with a grid column per query, 1.2 GB this way).
+// time through the same partition's cache (16 queries: the counter of fetches, which sees half of the bytes, shows 17 GB with a grid column per query, 1.2 GB this way).
 // 16 queries of 400 000 candidates: 8.4 -> 4.9 ms, of which listing the tokens takes 1.9 (scalar and vector instructions) and
 // the products 2.0 (matrix instructions 1.7).
 #define VP_GROUP 4
