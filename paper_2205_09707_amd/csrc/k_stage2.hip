@@ -1091,7 +1091,6 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     __shared__ __align__(16) float Tl[KMAX * S2_TSTRIDE];
     __shared__ float rowsum[SLOTS];
     __shared__ int32_t kid[SLOTS], drow[SLOTS];  // slot - 1 -> centroid, row of its list's bitmap or -1
-    __shared__ uint8_t order[SLOTS];             // the slots (minus one) with a bitmap, from the back those without
     __shared__ int32_t plist[IV_LISTS];    // probed lists of no surviving centroid: bitmap rows from the front, centroids from the back
     __shared__ uint32_t probed_mask[2];    // bit s: slot s + 1 is also probed
     __shared__ int32_t n_front[2], n_sparse;  // [1]: of those from the back
@@ -1167,9 +1166,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                 kid[tid] = c;
                 drow[tid] = d;
             }
-            const unsigned long long below = (1ull << tid) - 1ull;
-            const unsigned long long sm = __ballot(tid < K && d < 0), dm = __ballot(tid < K && d >= 0);
-            if (tid < K) order[d >= 0 ? __popcll(dm & below) : SLOTS - 1 - __popcll(sm & below)] = (uint8_t)tid;
+            const unsigned long long sm = __ballot(tid < K && d < 0);
             if (tid == 0) {
                 n_sparse = __popcll(sm);
                 n_front[0] = n_front[1] = 0;
@@ -1205,9 +1202,11 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         // log2 of the areas that a wave takes
         const int lend = ALL && (mode & 32) && n_ss > FULL_PLANES ? ((mode & 128) && n_ss > 2 * FULL_PLANES ? 2 : 1) : 0;
         uint32_t *area = area_all[(wave << lend) % IV_WAVES];
-        // lane i: the i-th slot with a bitmap and its row / the i-th slot without one and its centroid
-        const int dense_slot = lane < n_dense ? order[lane] : 0, dense_row = lane < n_dense ? drow[dense_slot] : 0;
-        const int list_slot = lane < n_ss ? order[SLOTS - 1 - lane] : 64, list_c = lane < n_ss ? kid[list_slot] : -1;
+        // Slots are numbered by list length, so that those with a bitmap come first.  lane i: the row of slot i's / the centroid of
+        // the i-th slot without one
+        const int dense_row = lane < n_dense ? drow[lane] : 0;
+        const int list_c = lane < n_ss ? kid[n_dense + lane] : -1;
+        const bool all_probed = (uint32_t)__popc(pm0) + (uint32_t)__popc(pm1) == (uint32_t)K;
         uint64_t *klist = keys2 + (int64_t)q * key_stride;
         uint32_t *cbq = candbits + (int64_t)q * cand_words;
         uint32_t *ebq = emptybits + (int64_t)q * cand_words;
@@ -1253,8 +1252,10 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
 #pragma unroll
             for (int k = 0; k < S2_UB_BITS; ++k) A[k] = 0u;
             uint32_t any = 0u, cand = given && act ? cbq[w0 + lane] : 0u;
-            auto add = [&](uint32_t b, int g) {
+            // a passage with a probed survivor is a candidate; where all survivors are probed (nearly always) `any` tells
+            auto add = [&](uint32_t b, int s, int g) {
                 any |= b;
+                if (!all_probed && (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u)) cand |= b;
                 s2_add_gain(A, b, g);
             };
             const int groups = 64 / nw, grp = lane / nw, gl = lane % nw;
@@ -1270,60 +1271,33 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                     }
 #pragma unroll
                     for (int u = 0; u < 8; ++u)
-                        if (i0 + u < n_dense) {
-                            const int s = __builtin_amdgcn_readlane(dense_slot, i0 + u);
-                            if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= v[u];
-                            add(v[u], __builtin_amdgcn_readlane(gain_lane, s));
-                        }
+                        if (i0 + u < n_dense) add(v[u], i0 + u, __builtin_amdgcn_readlane(gain_lane, i0 + u));
                 }
             } else {
                 for (int i0 = 0; i0 < n_dense; i0 += groups) {
-                    const int i = i0 + grp, s = __shfl(dense_slot, i & 63), row = __shfl(dense_row, i & 63);
-                    const int g = __shfl(gain_lane, s);
-                    const uint32_t v = i < n_dense && gact ? dense_bits[(int64_t)row * cand_words + w0 + gl] : 0u;
-                    if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= v;
-                    add(v, g);
+                    const int i = i0 + grp, row = __shfl(dense_row, i & 63), g = __shfl(gain_lane, i & 63);
+                    add(i < n_dense && gact ? dense_bits[(int64_t)row * cand_words + w0 + gl] : 0u, i & 63, g);
                 }
-                for (int d = nw; d < 64; d <<= 1) cand |= __shfl_xor(cand, d);
             }
-            for (int d0 = 0; d0 < n_rows; d0 += 8) {
-                uint32_t v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    v[u] = d0 + u < n_rows && act ? dense_bits[(int64_t)s2_uniform(plist[d0 + u]) * cand_words + w0 + lane] : 0u;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) cand |= v[u];
-            }
-            // the remaining lists, entry by entry; those that only make candidates are not looked up where every passage
-            // is a candidate already
+            // the planes of the survivors' other lists, entry by entry
             const unsigned long long has = __ballot(lane < n_ss && list_b > list_a);
             const int n_act = __popcll(has), my_plane = __popcll(has & ((1ull << lane) - 1ull));
             for (int i = 0; i < n_act; ++i)
                 if (lane < nw) area[i * nw + lane] = 0u;
-            const int n_lists = n_act + (__all((cand & valid) == valid) ? 0 : n_sp);
-            lcand[lane] = cand;
             // lane i: the slot of plane i
-            if ((has >> lane) & 1ull) lstart[my_plane] = (uint32_t)list_slot;
+            if ((has >> lane) & 1ull) lstart[my_plane] = (uint32_t)(n_dense + lane);
             s2_wave_sync();
             const int plane_slot = lane < n_act ? (int)lstart[lane] : 64;
             s2_wave_sync();
-            for (int u0 = 0; u0 < n_lists; u0 += 64) {
-                // an entry of the table: start (low 32 bits), start (high bits) << 21 | entries << 7 | plane, 64 = the candidates
-                auto put = [&](int at, int64_t start, uint32_t la, uint32_t lb, int plane) {
-                    start += la;
-                    lstart[at] = (uint32_t)start;
-                    // at most 2^13 entries (a list is ascending); lists hold fewer than 2^43 entries together
-                    lcnt[at] = (uint32_t)((uint64_t)start >> 32) << 21 | (lb > la ? lb - la : 0u) << 7 | (uint32_t)plane;
-                };
-                if (u0 == 0 && ((has >> lane) & 1ull)) put(my_plane, list_at, list_a, list_b, my_plane);
-                const int e = u0 == 0 ? n_act + lane : u0 + lane;
-                if (e < n_lists && e - u0 < 64) {
-                    const int32_t c = plist[IV_LISTS - 1 - (e - n_act)];
-                    put(e - u0, ivf_offsets[c], table[(int64_t)c * (nr + 1) + col], table[(int64_t)c * (nr + 1) + col + 1], 64);
-                }
-                s2_wave_sync();
-                const int nb = n_lists - u0 < 64 ? n_lists - u0 : 64;
-                // a quarter of the wave per list, four lists each in flight
+            // an entry of the table of lists: start (low 32 bits), start (high bits) << 21 | entries << 7 | plane, 64 = the candidates
+            auto put = [&](int at, int64_t start, uint32_t la, uint32_t lb, int plane) {
+                start += la;
+                lstart[at] = (uint32_t)start;
+                // at most 2^13 entries (a list is ascending); lists hold fewer than 2^43 entries together
+                lcnt[at] = (uint32_t)((uint64_t)start >> 32) << 21 | (lb > la ? lb - la : 0u) << 7 | (uint32_t)plane;
+            };
+            // the bits of the entries of nb lists: a quarter of the wave per list, four lists each in flight
+            auto walk = [&](int nb) {
                 const int sub = lane & 15;
                 auto apply = [&](uint32_t pid, int sl) {
                     const uint32_t loc = pid - (uint32_t)p0;
@@ -1358,8 +1332,10 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                         }
                 }
                 s2_wave_sync();
-            }
-            cand = lcand[lane];
+            };
+            if ((has >> lane) & 1ull) put(my_plane, list_at, list_a, list_b, my_plane);
+            s2_wave_sync();
+            walk(n_act);
             if (groups == 1) {
                 for (int i0 = 0; i0 < n_act; i0 += 4) {
                     uint32_t b[4];
@@ -1369,16 +1345,13 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                     for (int u = 0; u < 4; ++u)
                         if (i0 + u < n_act) {
                             const int s = __builtin_amdgcn_readlane(plane_slot, i0 + u);
-                            if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= b[u];
-                            add(b[u], __builtin_amdgcn_readlane(gain_lane, s));
+                            add(b[u], s, __builtin_amdgcn_readlane(gain_lane, s));
                         }
                 }
             } else {
                 for (int i0 = 0; i0 < n_act; i0 += groups) {
                     const int i = i0 + grp, s = __shfl(plane_slot, i & 63) & 63, g = __shfl(gain_lane, s);
-                    const uint32_t b = i < n_act ? area[i * nw + gl] : 0u;
-                    if (((s < 32 ? pm0 : pm1) >> (s & 31)) & 1u) cand |= b;
-                    add(b, g);
+                    add(i < n_act ? area[i * nw + gl] : 0u, s, g);
                 }
                 for (int d = nw; d < 64; d <<= 1) {
                     uint32_t carry = 0u;
@@ -1392,17 +1365,65 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                     any |= __shfl_xor(any, d);
                 }
             }
-            cand &= valid;
-            if (act) {
+            any &= valid;
+            cand = (all_probed ? cand | any : cand) & valid;
+            // Smallest gain sum whose bound can reach the best m: at least m scores lie in coarse bins 0 .. b, so a bound in a worse
+            // bin needs no score.  -1 while fewer than m scores are known.
+            auto least_sum = [&](int2 c) -> int {
+                const int incl = s2_wave_scan(c.x + c.y);
+                const unsigned long long enough0 = __ballot(incl - c.y >= m), enough1 = __ballot(incl >= m);
+                if (!enough1) return -1;
+                const int l1 = __ffsll((long long)enough1) - 1;
+                const int b = 2 * l1 + (((enough0 >> l1) & 1ull) ? 0 : 1);
+                const int worst = ((b + 1) << S2_COARSE_SHIFT) - 1;  // last bin of coarse bin b
+                // (bins do not rise with the sum)
+                auto reaches = [&](int sum) {
+                    return plaid_s2_bin(mt.ub_base + mt.ub_unit * (float)sum, mt.bin_hi, mt.bin_scale) <= worst;
+                };
+                const unsigned long long hi = __ballot(reaches(16 * lane + 15));
+                if (!hi) return 1 << S2_UB_BITS;  // no sum does
+                const int h = __ffsll((long long)hi) - 1;
+                return 16 * h + __ffsll((long long)__ballot(reaches(16 * h + (lane & 15)))) - 1;
+            };
+            int need = least_sum(known);
+            uint32_t left = any;
+            if (need >= 0) left = need >> S2_UB_BITS ? 0u : left & s2_sum_reaches(A, need);
+            // The probed lists of no surviving centroid, which only make candidates (usually two thirds of the probed lists).  Once m
+            // scores are known, what has no survivor cannot be among the best m and nobody reads its bits any more; then the
+            // lists matter only to a passage that would be scored and is not known to be a candidate.  (Search of 150 queries of 8.8 M
+            // passages, 73 of 106 probed lists without a survivor: 6880 -> 6309 us; 512 of 400 000 2555 -> 2524.)
+            if (!given && (need < 0 || (mode & 256) || __any((left & ~cand) != 0u))) {
+                for (int d0 = 0; d0 < n_rows; d0 += 8) {
+                    uint32_t v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        v[u] = d0 + u < n_rows && act ? dense_bits[(int64_t)s2_uniform(plist[d0 + u]) * cand_words + w0 + lane] : 0u;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) cand |= v[u];
+                }
+                cand &= valid;
+                lcand[lane] = cand;
+                const int n_lists = __all(cand == valid) ? 0 : n_sp;
+                for (int u0 = 0; u0 < n_lists; u0 += 64) {
+                    const int e = u0 + lane;
+                    if (e < n_lists) {
+                        const int32_t c = plist[IV_LISTS - 1 - e];
+                        put(lane, ivf_offsets[c], table[(int64_t)c * (nr + 1) + col], table[(int64_t)c * (nr + 1) + col + 1], 64);
+                    }
+                    s2_wave_sync();
+                    walk(n_lists - u0 < 64 ? n_lists - u0 : 64);
+                }
+                cand = lcand[lane] & valid;
+            }
+            if ((given || need < 0 || (mode & 256)) && act) {
                 cbq[w0 + lane] = cand;
                 ebq[w0 + lane] = cand & ~any;
             }
-            uint32_t left = cand & any;
+            left &= cand;
             for (int round = 0; __any(left != 0u); ++round) {  // (no round: no candidate with a surviving centroid)
                 s2_opaque(lane);
-                // at least m scores lie in coarse bins 0 .. b: a bound in a worse bin needs no score
-                int2 c = known;
                 if (round > 0) {
+                    int2 c;
                     // the copies of all XCDs where that pays (see the launch)
                     if (PLAIN || !(mode & 64)) {  // uniform
                         c = s2_coarse_load(coarse_q, lane);
@@ -1417,25 +1438,12 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                             c.y += v[x].y;
                         }
                     }
-                }
-                const int incl = s2_wave_scan(c.x + c.y);
-                const unsigned long long enough0 = __ballot(incl - c.y >= m), enough1 = __ballot(incl >= m);
-                if (enough1) {
-                    const int l1 = __ffsll((long long)enough1) - 1;
-                    const int b = 2 * l1 + (((enough0 >> l1) & 1ull) ? 0 : 1);
-                    const int worst = ((b + 1) << S2_COARSE_SHIFT) - 1;  // last bin of coarse bin b
-                    // smallest gain sum whose bound can still fall into a bin <= worst (bins do not rise with the sum)
-                    auto reaches = [&](int sum) {
-                        return plaid_s2_bin(mt.ub_base + mt.ub_unit * (float)sum, mt.bin_hi, mt.bin_scale) <= worst;
-                    };
-                    const unsigned long long hi = __ballot(reaches(16 * lane + 15));
-                    if (!hi) break;  // no sum does
-                    const int h = __ffsll((long long)hi) - 1;
-                    const int need = 16 * h + __ffsll((long long)__ballot(reaches(16 * h + (lane & 15)))) - 1;
-                    left &= s2_sum_reaches(A, need);
+                    need = least_sum(c);
+                    if (need >> S2_UB_BITS == 1) break;
+                    if (need >= 0) left &= s2_sum_reaches(A, need);
                 }
                 uint32_t sel = left;
-                int want = enough1 ? 128 : first_batch;
+                int want = need >= 0 ? 128 : first_batch;
                 if (s2_wave_sum(__popc(left)) > 2 * want) {
                     // nothing, or little, to prune with yet: the highest sums (and those that tie with the last of them)
                     uint32_t cur = left;
@@ -1514,7 +1522,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                             }
 #pragma unroll
                             for (int u = 0; u < 8; ++u)
-                                rows |= (SetT)((v[u] >> pos) & 1u) << __builtin_amdgcn_readlane(dense_slot, i0 + u);
+                                rows |= (SetT)((v[u] >> pos) & 1u) << (i0 + u);
                         }
                         for (int i0 = 0; i0 < n_act; i0 += 8) {
                             uint32_t v[8];
@@ -1594,7 +1602,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, double plane_share, int shift, int32_t m)
+                                  const uint32_t *dense_bits, double plane_share, int shift, int32_t m, bool all_candidates)
 {
     const int64_t nr = (P + (1ll << shift) - 1) >> shift;
     const int64_t nwide = (P + (1ll << UW_SHIFT) - 1) >> UW_SHIFT;
@@ -1605,6 +1613,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_union_wide_kernel, dim3((unsigned)nwide, nq), dim3(UW_THREADS), 0, st, uniq, n_uniq, uniq_stride,
                            ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            b.emptybits);
+    const int base = wide | (all_candidates ? 256 : 0);
     const int given = uniq_stride > IV_LISTS ? 16 : 0;
     if (given)
         hipLaunchKernelGGL(s2_candidates_kernel, dim3((unsigned)((cand_words + 63) / 64), nq), dim3(64 * IV_WAVES), 0, st, uniq, n_uniq,
@@ -1668,7 +1677,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const bool fits = blocks * nqx <= S2_FITS_BLOCKS;
     if (nq < 8 || fits) {
         const bool fits4 = 4 * blocks * nqx <= 256 * S2_UNIT_BLOCKS;
-        const int mode = wide | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0) | (fits4 ? 128 : 0);
+        const int mode = base | (nq == 1 ? 4 : 0) | own | (fits ? 32 : 0) | (fits4 ? 128 : 0);
         const int64_t all = fits4 ? 4 * blocks : (fits ? 2 * blocks : blocks);
         // (where the second areas do not come from workgroups that run at once, queries of 27 to 36 lists are better off with the
         // planes for them: twelve of 400 000 passages, even lists, K = 33 211 -> 164 us)
@@ -1679,14 +1688,14 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         // the class of the 64-bit instance is empty or small more often than not: 128 columns of workgroups share it
         const int many = nqx < 128 ? nqx : 128;
         if (shift == 11) {
-            if (own) S2_INVERT(11, uint32_t, false, false, false, wide | own, nqx, blocks, 0u);
-            else S2_INVERT(11, uint32_t, true, false, false, wide, nqx, blocks, 0u);
-            if (tall) S2_INVERT(11, unsigned long long, false, false, true, wide | own, many, blocks, 0u);
-            S2_INVERT(11, unsigned long long, false, false, false, wide | own, many, blocks, gather);
+            if (own) S2_INVERT(11, uint32_t, false, false, false, base | own, nqx, blocks, 0u);
+            else S2_INVERT(11, uint32_t, true, false, false, base, nqx, blocks, 0u);
+            if (tall) S2_INVERT(11, unsigned long long, false, false, true, base | own, many, blocks, 0u);
+            S2_INVERT(11, unsigned long long, false, false, false, base | own, many, blocks, gather);
         } else {
-            if (own) S2_INVERT(13, uint32_t, false, false, false, wide | own, nqx, blocks, 0u);
-            else S2_INVERT(13, uint32_t, true, false, false, wide, nqx, blocks, 0u);
-            S2_INVERT(13, unsigned long long, false, false, false, wide | own, many, blocks, gather);
+            if (own) S2_INVERT(13, uint32_t, false, false, false, base | own, nqx, blocks, 0u);
+            else S2_INVERT(13, uint32_t, true, false, false, base, nqx, blocks, 0u);
+            S2_INVERT(13, unsigned long long, false, false, false, base | own, many, blocks, gather);
         }
     }
 #undef S2_INVERT

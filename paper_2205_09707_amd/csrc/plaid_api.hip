@@ -848,7 +848,8 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         if (ix->ivr_table)
             plaid_launch_stage2_inverted(st, w.uniq, w.n_uniq, w.uniq_stride, ix->ivf_offsets, ix->ivf_pids, ix->ivr_table, w.S,
                                          C, w.keepbits, w.keep_words, ix->codes, ix->doc_offsets, P, n, w.s2, w.candbits,
-                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->plane_share, ix->ivr_shift, pl.nd);
+                                         w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->plane_share, ix->ivr_shift, pl.nd,
+                                         dbg && (dbg->cand || dbg->n_cand));
         else
             plaid_launch_stage2(st, w.S, C, w.keepbits, w.keep_words, w.probed, nprobe, w.candbits, w.cand_words, P, ix->N,
                                 ix->doc_offsets, ix->codes, n, w.s2, w.keys2, P);

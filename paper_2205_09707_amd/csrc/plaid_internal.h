@@ -290,7 +290,8 @@ void plaid_launch_stage2(hipStream_t st, const float *S, int64_t C, const uint32
 // place of the fine one) hold every candidate that can be among the best m (= the m of the selection that follows), not
 // those proven not to be.  table: plaid_ivf_range_table_bytes(C, P, shift) bytes filled once per index
 // by plaid_launch_ivf_range_table.
-// shift: log2 of the passages per table column, 11 or 13.
+// shift: log2 of the passages per table column, 11 or 13.  all_candidates: the candidate words are complete (otherwise they, and the
+// empty-bag words, may be missing where m scores were known already: the selection that follows does not read them then).
 size_t plaid_ivf_range_table_bytes(int64_t C, int64_t P, int shift);
 void plaid_launch_ivf_range_table(hipStream_t st, const int64_t *ivf_offsets, const int32_t *ivf_pids, int64_t C, int64_t P,
                                   int shift, uint32_t *table);
@@ -299,7 +300,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
                                   int64_t cand_words, uint64_t *keys2, int64_t key_stride, const int32_t *dense_id,
-                                  const uint32_t *dense_bits, double plane_share, int shift, int32_t m);
+                                  const uint32_t *dense_bits, double plane_share, int shift, int32_t m,
+                                  bool all_candidates);
 // total[0] (zero before the call) += over the lists without a bitmap, entries x table columns in which the list has an entry: divided
 // by all entries and by the columns, how often a centroid, picked by its number of passages, has entries but no bitmap where stage 2
 // looks for them.
