@@ -137,6 +137,7 @@ __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int
             if (run + loc[j] >= m_rem) {
                 res[0] = threadIdx.x * PER + j;
                 res[1] = run;
+                scan[SEL_THREADS - 2] = loc[j];
                 break;
             }
             run += loc[j];
@@ -146,7 +147,7 @@ __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int
         res[0] = -1;  // take nothing, keep nothing
         res[1] = 0;
     }
-    if (threadIdx.x == SEL_THREADS - 1) scan[SEL_THREADS - 1] = total;  // for the callers
+    if (threadIdx.x == SEL_THREADS - 1) scan[SEL_THREADS - 1] = total;  // for the callers, and before it the keys of the boundary bin
     __syncthreads();
     bstar = res[0];
     before = res[1];
@@ -518,6 +519,20 @@ __global__ __launch_bounds__(256) void sel_rank_output_kernel(const uint64_t *__
     }
 }
 
+// Keys that other workgroups of the same launch write or read (AGENT) go past the second-level caches, which are not coherent between
+// the XCDs.
+template <bool AGENT>
+__device__ __forceinline__ uint64_t sel_key(const uint64_t *p)
+{
+    return AGENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <bool AGENT>
+__device__ __forceinline__ void sel_put(uint64_t *p, uint64_t key)
+{
+    if (AGENT) __hip_atomic_store(p, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = key;
+}
+
 // The `take` smallest (in any order) of the n <= SEL_SORT_CAP keys of `bl`, to o; every key agrees at and above bit `high`.
 // One workgroup of FIN_THREADS threads, all of which call this; sk, dh, h256, sh, differ: LDS (keys, one digit's histogram, wave
 // totals, four words, two words).
@@ -527,7 +542,7 @@ __global__ __launch_bounds__(256) void sel_rank_output_kernel(const uint64_t *__
 // queries of 8.8 M passages 117 -> 52 us, 512 of 400 000 39 -> 20, 23 of 123 457 13.5 -> 7.6.)
 #define FIN_RANK (FIN_THREADS / 4)
 // One digit: keys from bl (STAGED: from sk); n, take, base, high: those of the keys that are left, which go to sk.
-template <bool STAGED>
+template <bool STAGED, bool AGENT>
 __device__ __forceinline__ void sel_pick_digit(const uint64_t *__restrict__ bl, int &n, int &take, uint64_t *__restrict__ o, int &base,
                                                int &high, uint64_t *sk, int32_t *dh, int32_t *h256, int32_t *sh,
                                                unsigned long long *differ)
@@ -543,7 +558,7 @@ __device__ __forceinline__ void sel_pick_digit(const uint64_t *__restrict__ bl, 
 #pragma unroll
     for (int u = 0; u < SEL_SORT_CAP / FIN_THREADS; ++u) {
         const int i = threadIdx.x + u * FIN_THREADS;
-        key[u] = i < n ? (STAGED ? sk[i] : bl[i]) : PLAID_KEY_MAX;
+        key[u] = i < n ? (STAGED ? sk[i] : sel_key<AGENT>(bl + i)) : PLAID_KEY_MAX;
         if (i < n) atomicAdd(&dh[(int)(key[u] >> shift) & (SEL_BINS - 1)], 1);
     }
     __syncthreads();
@@ -609,17 +624,18 @@ __device__ __forceinline__ void sel_pick_digit(const uint64_t *__restrict__ bl, 
         __syncthreads();  // sh and differ are cleared next
     }
 }
+template <bool AGENT>
 __device__ __forceinline__ void sel_pick_lds(const uint64_t *__restrict__ bl, int n, int take, uint64_t *__restrict__ o, int high,
                                              uint64_t *sk, int32_t *dh, int32_t *h256, int32_t *sh, unsigned long long *differ)
 {
     int base = 0;
     if (n > FIN_RANK) {
-        sel_pick_digit<false>(bl, n, take, o, base, high, sk, dh, h256, sh, differ);
+        sel_pick_digit<false, AGENT>(bl, n, take, o, base, high, sk, dh, h256, sh, differ);
         // (uniform; keys are unique: a digit that ends at bit 0 leaves one)
 #pragma unroll 1
-        while (n > FIN_RANK) sel_pick_digit<true>(bl, n, take, o, base, high, sk, dh, h256, sh, differ);
+        while (n > FIN_RANK) sel_pick_digit<true, AGENT>(bl, n, take, o, base, high, sk, dh, h256, sh, differ);
     } else {
-        if ((int)threadIdx.x < n) sk[threadIdx.x] = bl[threadIdx.x];
+        if ((int)threadIdx.x < n) sk[threadIdx.x] = sel_key<AGENT>(bl + threadIdx.x);
         __syncthreads();
     }
     // few keys: four threads count how many of them precede theirs
@@ -675,7 +691,7 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel_pick_kernel(const uint64_t
     }
     __syncthreads();
     const unsigned long long diff = differ[0] & differ[1];
-    sel_pick_lds(k, n, take, out + (int64_t)seg * out_stride, diff ? 64 - __builtin_clzll(diff) : 0, sk, dh, h256, sh, left);
+    sel_pick_lds<false>(k, n, take, out + (int64_t)seg * out_stride, diff ? 64 - __builtin_clzll(diff) : 0, sk, dh, h256, sh, left);
 }
 
 static inline int64_t sort_pow2(int64_t n)
@@ -838,25 +854,27 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
 // =================================================================================================
 #define SEL2_GROUPS 8                              // keys a thread takes per step
 #define SEL2_STEP (SEL_THREADS * SEL2_GROUPS)     // keys a workgroup takes per step
+template <int THREADS>
 struct Sel2Place {                                // LDS of sel2_place
-    int32_t cnt[2][2][SEL_THREADS / 64];          // [parity of the step][selected / boundary][wave]
+    int32_t cnt[2][2][THREADS / 64];              // [parity of the step][selected / boundary][wave]
     int32_t base[2];
-    unsigned long long bits[2][SEL_THREADS / 64];
+    unsigned long long bits[2][THREADS / 64];
 };
 // Writes a step's keys of class 0 (selected) to out and of class 1 (boundary) to bl; o, no collect the boundary keys' bits and
 // their complements.  The workgroup reserves its positions with one update of each counter per step: the counters of a query
 // are two words that every workgroup of the launch updates and waits for, one after the other.  One query of 8.8 M passages:
 // with an update per wave the bin filter took 27.6 us and the digit filter, 64 keys a wave, 19.9; now 8.1 and 5.8.  All
 // threads call this.
-__device__ __forceinline__ void sel2_place(const uint64_t (&key)[SEL2_GROUPS], const int (&cls)[SEL2_GROUPS], int parity, Sel2Place &l,
+template <int THREADS, int GROUPS, bool AGENT>
+__device__ __forceinline__ void sel2_place(const uint64_t (&key)[GROUPS], const int (&cls)[GROUPS], int parity, Sel2Place<THREADS> &l,
                                            int32_t *n_sure, int32_t *n_boundary, uint64_t *__restrict__ out,
                                            uint64_t *__restrict__ bl, unsigned long long &o, unsigned long long &no)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long b0[SEL2_GROUPS], b1[SEL2_GROUPS];
+    unsigned long long b0[GROUPS], b1[GROUPS];
     int n0 = 0, n1 = 0;
 #pragma unroll
-    for (int u = 0; u < SEL2_GROUPS; ++u) {
+    for (int u = 0; u < GROUPS; ++u) {
         b0[u] = __ballot(cls[u] == 0);
         b1[u] = __ballot(cls[u] == 1);
         n0 += __popcll(b0[u]);
@@ -870,7 +888,7 @@ __device__ __forceinline__ void sel2_place(const uint64_t (&key)[SEL2_GROUPS], c
     if (threadIdx.x < 2) {
         int n = 0;
 #pragma unroll
-        for (int w = 0; w < SEL_THREADS / 64; ++w) n += l.cnt[parity][threadIdx.x][w];
+        for (int w = 0; w < THREADS / 64; ++w) n += l.cnt[parity][threadIdx.x][w];
         l.base[threadIdx.x] = n ? atomicAdd(threadIdx.x == 0 ? n_sure : n_boundary, n) : 0;
     }
     __syncthreads();
@@ -881,10 +899,10 @@ __device__ __forceinline__ void sel2_place(const uint64_t (&key)[SEL2_GROUPS], c
     }
     const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
-    for (int u = 0; u < SEL2_GROUPS; ++u) {
+    for (int u = 0; u < GROUPS; ++u) {
         if (cls[u] == 0) out[base0 + __popcll(b0[u] & below)] = key[u];
         if (cls[u] == 1) {
-            bl[base1 + __popcll(b1[u] & below)] = key[u];
+            sel_put<AGENT>(&bl[base1 + __popcll(b1[u] & below)], key[u]);
             o |= key[u];
             no |= ~key[u];
         }
@@ -893,7 +911,8 @@ __device__ __forceinline__ void sel2_place(const uint64_t (&key)[SEL2_GROUPS], c
     }
 }
 // The workgroup's boundary bits to the query's.  All threads call this, once.
-__device__ __forceinline__ void sel2_place_bits(unsigned long long o, unsigned long long no, Sel2Place &l, unsigned long long *b_or,
+template <int THREADS>
+__device__ __forceinline__ void sel2_place_bits(unsigned long long o, unsigned long long no, Sel2Place<THREADS> &l, unsigned long long *b_or,
                                                 unsigned long long *b_nor)
 {
     for (int d = 1; d < 64; d <<= 1) {
@@ -908,20 +927,58 @@ __device__ __forceinline__ void sel2_place_bits(unsigned long long o, unsigned l
     if (threadIdx.x < 2) {
         unsigned long long v = 0;
 #pragma unroll
-        for (int w = 0; w < SEL_THREADS / 64; ++w) v |= l.bits[threadIdx.x][w];
+        for (int w = 0; w < THREADS / 64; ++w) v |= l.bits[threadIdx.x][w];
         if (v) atomicOr(threadIdx.x == 0 ? b_or : b_nor, v);
     }
 }
 
-__global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
-                                                                  const uint32_t *__restrict__ candbits, int64_t cand_words,
-                                                                  int64_t P, int32_t m, const S2Meta *__restrict__ meta,
-                                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
-                                                                  uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
+// A boundary list longer than this goes through a digit pass (all workgroups of the query) before the finishing workgroup
+// takes its digits in LDS.  Where the line lies matters little: the stage with 2048 / 4096 / 8192 (all that LDS holds), us, 32
+// queries of 400 000 passages 28 / 23 / 23, 512 of them 94 / 90 / 83, of 8.8 M 8 queries 46 / 44 / 47, 150 189 / 186 / 178; the whole searches
+// do not differ.  Two such passes can be chained (LEVEL 1 reads the bin filter's list, LEVEL 2 the list
+// LEVEL 1 leaves): when a few distinct scores are shared by very many passages, the first digit falls into the score
+// bits and leaves one whole tie group, the second falls into the passage-id bits and leaves 2^-11 of it.
+#define SEL2_DIGIT_MIN 4096
+#define SEL2_SECOND_MIN_PASSAGES (1 << 19)  // indexes with more passages than this get the second digit pass
+#define SEL2_SUB 1024                       // digits of either kind that sel2_bins_kernel counts
+static_assert(2 * SEL2_SUB <= SEL_BINS, "both kinds of digits in one histogram");
+static constexpr int sel2_id_shift(int64_t P)  // passage id -> digit
+{
+    int bits = 10;
+    while ((int64_t)1 << bits < P) ++bits;
+    return bits - 10;
+}
+// The digit of a score within its bin: not falling in the rank, like the bin.
+__device__ __forceinline__ int sel2_sub_bin(uint64_t key, const S2Meta &mt, int bin, int bin_shift)
+{
+    float x = (mt.bin_hi - plaid_ord_to_score((uint32_t)(key >> 32))) * mt.bin_scale;  // (as in plaid_s2_bin)
+    x = fminf(fmaxf(x, 0.f), (float)(SEL_BINS - 1));
+    x = (x - (float)(bin << bin_shift)) * (float)(SEL2_SUB >> bin_shift);
+    return (int)fminf(fmaxf(x, 0.f), (float)(SEL2_SUB - 1));
+}
+static_assert(SEL2_SUB >> S2_COARSE_SHIFT > 0, "a coarse bin has digits");
+
+// Counts the lanes' digits (-1: none).  All lanes call this, one at least has a digit.
+__device__ __forceinline__ void sel2_count(int32_t *lh, int digit)
+{
+    const unsigned long long have = __ballot(digit >= 0);
+    const int lane = (int)(threadIdx.x & 63), lead = (int)__builtin_ctzll(have);
+    const unsigned long long same = __ballot(digit == __builtin_amdgcn_readlane(digit, lead));
+    if (lane == lead) atomicAdd(&lh[digit], __popcll(same));
+    else if (digit >= 0 && !((same >> lane) & 1ull)) atomicAdd(&lh[digit], 1);
+}
+// DIGITS: counts the boundary keys' digits in hist1 ([nq][SEL_BINS]: the scores', then the passage ids') where there are more than
+// SEL_SORT_CAP of them.
+template <bool DIGITS>
+__device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ keys, int64_t key_stride, const uint32_t *__restrict__ candbits,
+                                                 int64_t cand_words, int64_t P, int32_t m, const S2Meta *__restrict__ meta,
+                                                 const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
+                                                 int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride, int lists,
+                                                 int id_shift, int32_t *__restrict__ hist1, int32_t *lh /* [SEL_BINS] */)
 {
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
-    __shared__ Sel2Place place;
+    __shared__ Sel2Place<SEL_THREADS> place;
     const int seg = blockIdx.y;
     Sel2State *s = state + seg;
     const S2Meta mt = meta[seg];
@@ -936,8 +993,16 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint6
     else find_boundary(hist + (int64_t)seg * SEL_BINS, 0, scan, res, bstar, before, m);
     const int bin_shift = is_list ? S2_COARSE_SHIFT : 0;
     const int32_t n_keys = scan[SEL_THREADS - 1];
-    if (blockIdx.x == 0 && threadIdx.x == 0) s->m_rem = (m < n_keys ? m : n_keys) - before;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        s->m_rem = (m < n_keys ? m : n_keys) - before;
+        s->bin = bstar;
+    }
     if (n_keys == 0) return;
+    const bool count = DIGITS && scan[SEL_THREADS - 2] > SEL_SORT_CAP;  // uniform
+    if (count) {
+        for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS) lh[b] = 0;
+        __syncthreads();
+    }
     const uint32_t *k = reinterpret_cast<const uint32_t *>(keys + (int64_t)seg * key_stride);  // score word of passage i
     const uint32_t *cb = candbits + (int64_t)seg * cand_words;
     uint64_t *my_out = out + (int64_t)seg * out_stride;
@@ -983,19 +1048,45 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint6
                 cls[u] = d < bstar ? 0 : (d == bstar ? 1 : 2);
             }
         }
-        sel2_place(key, cls, parity, place, &s->n_sure, &s->n_b, my_out, my_bl, o, no);
+        sel2_place<SEL_THREADS, SEL2_GROUPS, false>(key, cls, parity, place, &s->n_sure, &s->n_b, my_out, my_bl, o, no);
+        if (count) {
+#pragma unroll
+            for (int u = 0; u < SEL2_GROUPS; ++u)
+                if (__any(cls[u] == 1)) {  // (the keys of a wave mostly share one digit or both: one update for those)
+                    sel2_count(lh, cls[u] == 1 ? sel2_sub_bin(key[u], mt, bstar, bin_shift) : -1);
+                    sel2_count(lh + SEL2_SUB, cls[u] == 1 ? (int)((uint32_t)key[u] >> id_shift) : -1);
+                }
+        }
     }
-    sel2_place_bits(o, no, place, &s->b_or, &s->b_nor);
+    sel2_place_bits<SEL_THREADS>(o, no, place, &s->b_or, &s->b_nor);
+    if (count) {
+        __syncthreads();
+        int32_t *gh = hist1 + (int64_t)seg * SEL_BINS;
+        for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS)
+            if (lh[b]) atomicAdd(&gh[b], lh[b]);
+    }
+}
+__global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
+                                                                  const uint32_t *__restrict__ candbits, int64_t cand_words,
+                                                                  int64_t P, int32_t m, const S2Meta *__restrict__ meta,
+                                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
+                                                                  uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
+{
+    sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists, 0,
+                            nullptr, nullptr);
+}
+__global__ __launch_bounds__(SEL_THREADS, 6) void sel2_bins_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
+                                                                const uint32_t *__restrict__ candbits, int64_t cand_words, int64_t P,
+                                                                int32_t m, const S2Meta *__restrict__ meta,
+                                                                const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
+                                                                int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride,
+                                                                int lists, int id_shift, int32_t *__restrict__ hist1)
+{
+    __shared__ int32_t lh[SEL_BINS];
+    sel2_filter_body<true>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists,
+                           id_shift, hist1, lh);
 }
 
-// A boundary list longer than this goes through a digit pass (all workgroups of the query) before the finishing workgroup
-// takes its digits in LDS.  Where the line lies matters little: the stage with 2048 / 4096 / 8192 (all that LDS holds), us, 32
-// queries of 400 000 passages 28 / 23 / 23, 512 of them 94 / 90 / 83, of 8.8 M 8 queries 46 / 44 / 47, 150 189 / 186 / 178; the whole searches
-// do not differ.  Two such passes can be chained (LEVEL 1 reads the bin filter's list, LEVEL 2 the list
-// LEVEL 1 leaves): when a few distinct scores are shared by very many passages, the first digit falls into the score
-// bits and leaves one whole tie group, the second falls into the passage-id bits and leaves 2^-11 of it.
-#define SEL2_DIGIT_MIN 4096
-#define SEL2_SECOND_MIN_PASSAGES (1 << 19)  // indexes with more passages than this get the second digit pass
 template <int LEVEL>
 __device__ __forceinline__ int sel2_level_input(const Sel2State *s, int &m_rem)
 {
@@ -1053,7 +1144,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_filter_kernel(const ui
 {
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
-    __shared__ Sel2Place place;
+    __shared__ Sel2Place<SEL_THREADS> place;
     const int seg = blockIdx.y;
     Sel2State *s = state + seg;
     int32_t m_rem;
@@ -1086,9 +1177,9 @@ __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_filter_kernel(const ui
             const int d = digit_of(key[u], shift, width);
             cls[u] = s0 + u * SEL_THREADS + threadIdx.x < n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
         }
-        sel2_place(key, cls, parity, place, &s->n_sure, n_left, my_out, my_bl, o, no);
+        sel2_place<SEL_THREADS, SEL2_GROUPS, false>(key, cls, parity, place, &s->n_sure, n_left, my_out, my_bl, o, no);
     }
-    if (LEVEL == 1) sel2_place_bits(o, no, place, &s->b_or1, &s->b_nor1);
+    if (LEVEL == 1) sel2_place_bits<SEL_THREADS>(o, no, place, &s->b_or1, &s->b_nor1);
 }
 
 // The passages of the words [w0, w1) of a bitmap to o[total ..], until m are there; positions from a wave-level prefix sum of the
@@ -1142,37 +1233,23 @@ __device__ __forceinline__ int64_t sel2_fill(const uint32_t *__restrict__ eb, in
     return w0;
 }
 
-// One workgroup per query: finish the boundary list, then append empty-bag candidates in pid order.
-__global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint64_t *__restrict__ blist, int64_t blist_stride,
-                                                                  const uint64_t *__restrict__ blist1,
-                                                                  int64_t blist1_stride, const Sel2State *state,
-                                                                  const uint32_t *__restrict__ emptybits,
-                                                                  int64_t cand_words, int64_t P, int32_t m, int levels,
-                                                                  uint64_t *__restrict__ out, int64_t out_stride,
-                                                                  int32_t *__restrict__ out_counts)
+// The end of a query's selection, by one workgroup: the m_rem best of the nb boundary keys bl, which agree on every bit at or above
+// top_bit, behind the n_sure selected ones, then empty-bag candidates in pid order.
+struct Sel2Finish {
+    uint64_t sk[SEL_SORT_CAP];
+    int32_t dh[SEL_BINS];
+    int32_t h256[256];
+    int32_t sh[4];
+    unsigned long long differ[2];
+};
+template <bool AGENT>
+__device__ __forceinline__ void sel2_finish_body(Sel2Finish &l, const uint64_t *bl, int nb, int m_rem, int n_sure, int top_bit,
+                                                 const uint32_t *__restrict__ eb, int64_t cand_words, int64_t P, int32_t m, uint64_t *o,
+                                                 int32_t *__restrict__ out_count)
 {
-    __shared__ uint64_t sk[SEL_SORT_CAP];
-    __shared__ int32_t dh[SEL_BINS];
-    __shared__ int32_t h256[256];
-    __shared__ int32_t sh[4];
-    __shared__ unsigned long long differ[2];
-    const int seg = blockIdx.x;
-    const Sel2State *s = state + seg;
-    // how many digit filters this query's boundary list went through (levels: how many were launched); the second one
-    // writes where the first one read
-    const int done = (levels >= 1 && s->n_b > SEL2_DIGIT_MIN) ? ((levels >= 2 && s->n_b1 > SEL2_DIGIT_MIN) ? 2 : 1) : 0;
-    const uint64_t *bl = done == 1 ? blist1 + (int64_t)seg * blist1_stride : blist + (int64_t)seg * blist_stride;
-    const int nb = done == 2 ? s->n_b2 : (done == 1 ? s->n_b1 : s->n_b);
-    const int m_rem = done == 2 ? s->m_rem2 : (done == 1 ? s->m_rem1 : s->m_rem);
-    const int n_sure = s->n_sure;
-    // boundary keys agree on every bit at or above this position
-    const int top_bit = done == 2 ? s->shift2 : (done == 1 ? s->shift1 : 64);
-    uint64_t *o = out + (int64_t)seg * out_stride;
     int total = n_sure + m_rem;
-
     if (nb <= SEL_SORT_CAP) {
-        const unsigned long long diff = done == 1 ? (s->b_or1 & s->b_nor1) : (done == 0 ? (s->b_or & s->b_nor) : 0ull);
-        sel_pick_lds(bl, nb, m_rem, o + n_sure, diff ? 64 - __builtin_clzll(diff) : top_bit, sk, dh, h256, sh, differ);
+        sel_pick_lds<AGENT>(bl, nb, m_rem, o + n_sure, top_bit, l.sk, l.dh, l.h256, l.sh, l.differ);
     } else {
         // still long (huge tie groups): radix selection over global memory by this one workgroup.  The keys of such a
         // list mostly share their digit (that is what made the list long), so a wave whose keys all have one digit
@@ -1185,14 +1262,14 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint6
         while (pos > 0 && r > 0) {
             const int w = pos < 8 ? pos : 8;
             pos -= w;
-            for (int b = threadIdx.x; b < 256; b += FIN_THREADS) h256[b] = 0;
+            for (int b = threadIdx.x; b < 256; b += FIN_THREADS) l.h256[b] = 0;
             __syncthreads();
             for (int i0 = threadIdx.x; i0 < nb_round; i0 += 4 * FIN_THREADS) {
                 uint64_t key[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int i = i0 + u * FIN_THREADS;
-                    key[u] = i < nb ? bl[i] : ~prefix;  // a key past the end never matches the prefix
+                    key[u] = i < nb ? sel_key<AGENT>(bl + i) : ~prefix;  // a key past the end never matches the prefix
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -1201,9 +1278,9 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint6
                     const int first = __builtin_amdgcn_readfirstlane(dgt);
                     const unsigned long long same = __ballot(dgt == first);
                     if (same == __ballot(true)) {  // uniform digit (or no key in play) in this wave
-                        if (lane == (int)__builtin_ctzll(same) && first >= 0) atomicAdd(&h256[first], __popcll(same));
+                        if (lane == (int)__builtin_ctzll(same) && first >= 0) atomicAdd(&l.h256[first], __popcll(same));
                     } else if (dgt >= 0) {
-                        atomicAdd(&h256[dgt], 1);
+                        atomicAdd(&l.h256[dgt], 1);
                     }
                 }
             }
@@ -1211,28 +1288,28 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint6
             if (threadIdx.x == 0) {
                 int run = 0, b = 0;
                 for (; b < (1 << w); ++b) {
-                    if (run + h256[b] >= r) break;
-                    run += h256[b];
+                    if (run + l.h256[b] >= r) break;
+                    run += l.h256[b];
                 }
-                sh[0] = b;
-                sh[1] = run;
+                l.sh[0] = b;
+                l.sh[1] = run;
             }
             __syncthreads();
-            prefix |= (uint64_t)sh[0] << pos;
+            prefix |= (uint64_t)l.sh[0] << pos;
             pmask |= (uint64_t)((1u << w) - 1u) << pos;
-            r -= sh[1];
+            r -= l.sh[1];
             __syncthreads();
         }
-        if (threadIdx.x == 0) sh[2] = 0;
+        if (threadIdx.x == 0) l.sh[2] = 0;
         __syncthreads();
         if (m_rem > 0)
             for (int i0 = threadIdx.x; i0 < nb_round; i0 += FIN_THREADS) {
-                const uint64_t key = i0 < nb ? bl[i0] : 0;
+                const uint64_t key = i0 < nb ? sel_key<AGENT>(bl + i0) : 0;
                 const bool take = i0 < nb && (key & pmask) <= prefix;
                 const unsigned long long tk = __ballot(take);
                 if (tk) {  // one counter update per wave
                     int base = 0;
-                    if (lane == (int)__builtin_ctzll(tk)) base = atomicAdd(&sh[2], __popcll(tk));
+                    if (lane == (int)__builtin_ctzll(tk)) base = atomicAdd(&l.sh[2], __popcll(tk));
                     base = __shfl(base, (int)__builtin_ctzll(tk));
                     if (take) o[n_sure + base + __popcll(tk & ((1ull << lane) - 1ull))] = key;
                 }
@@ -1244,12 +1321,162 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint6
     // which is enough where nearly every passage is one, then rounds of eight (8.8 M passages are 275 000 words, 268 rounds of
     // one) up to the one in which the last of them lies.
     if (total < m) {
-        const uint32_t *eb = emptybits + (int64_t)seg * cand_words;
-        int64_t w0 = sel2_fill<1>(eb, 0, cand_words < FIN_THREADS ? cand_words : FIN_THREADS, P, m, h256, o, total);
-        w0 = sel2_fill<8>(eb, w0, cand_words, P, m, h256, o, total);
-        sel2_fill<1>(eb, w0, cand_words, P, m, h256, o, total);
+        int64_t w0 = sel2_fill<1>(eb, 0, cand_words < FIN_THREADS ? cand_words : FIN_THREADS, P, m, l.h256, o, total);
+        w0 = sel2_fill<8>(eb, w0, cand_words, P, m, l.h256, o, total);
+        sel2_fill<1>(eb, w0, cand_words, P, m, l.h256, o, total);
     }
-    if (threadIdx.x == 0) out_counts[seg] = total;
+    if (threadIdx.x == 0) *out_count = total;
+}
+__device__ __forceinline__ int sel2_top_bit(unsigned long long any, unsigned long long none)
+{
+    return any & none ? 64 - __builtin_clzll(any & none) : 0;
+}
+// One workgroup per query: finish the boundary list, then append empty-bag candidates in pid order.
+__global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint64_t *__restrict__ blist, int64_t blist_stride,
+                                                                  const uint64_t *__restrict__ blist1,
+                                                                  int64_t blist1_stride, const Sel2State *state,
+                                                                  const uint32_t *__restrict__ emptybits,
+                                                                  int64_t cand_words, int64_t P, int32_t m, int levels,
+                                                                  uint64_t *__restrict__ out, int64_t out_stride,
+                                                                  int32_t *__restrict__ out_counts)
+{
+    __shared__ Sel2Finish l;
+    const int seg = blockIdx.x;
+    const Sel2State *s = state + seg;
+    // how many digit filters this query's boundary list went through (levels: how many were launched); the second one
+    // writes where the first one read
+    const int done = (levels >= 1 && s->n_b > SEL2_DIGIT_MIN) ? ((levels >= 2 && s->n_b1 > SEL2_DIGIT_MIN) ? 2 : 1) : 0;
+    const uint64_t *bl = done == 1 ? blist1 + (int64_t)seg * blist1_stride : blist + (int64_t)seg * blist_stride;
+    const int nb = done == 2 ? s->n_b2 : (done == 1 ? s->n_b1 : s->n_b);
+    const int m_rem = done == 2 ? s->m_rem2 : (done == 1 ? s->m_rem1 : s->m_rem);
+    const int top_bit = done == 2 ? s->shift2 : (done == 1 ? sel2_top_bit(s->b_or1, s->b_nor1) : sel2_top_bit(s->b_or, s->b_nor));
+    sel2_finish_body<false>(l, bl, nb, m_rem, s->n_sure, top_bit, emptybits + (int64_t)seg * cand_words, cand_words, P, m,
+                            out + (int64_t)seg * out_stride, out_counts + seg);
+}
+
+// Launches of few queries.  A boundary list longer than what LDS holds goes through a digit pass by all workgroups of the query.  The
+// bin filter, which every query goes through in any case, counts the pass's digits: both that it may be, the score within the bin and
+// the passage id (keys that share their score).  The pass itself, sel2_cut_kernel<1>, takes one or the other, and the last of its workgroups to
+// arrive cuts what is left; a list that is not too long the query's first workgroup cuts at once.  So a selection is two launches, of
+// which each costs 4.6 us when it waits for the one before, however little it does (a search of
+// one query of 10 000 / 200 000 / 400 000 / 8.8 M passages took 71.8 / 81.1 / 104.5 / 279 us with the digits counted, filtered and the
+// rest cut by launches of their own, now 68.1 / 78.4 / 101.7 / 269; 23 queries of 123 457 167.0 / 162.4).  In launches of many queries
+// the other form wins: its workgroups are small, most find nothing to do, and tie groups do not meet in one histogram's word (512 of
+// 400 000: 78 us for the selection, 105 with this one; hardly a survivor 105, 180).
+// Two passes can be chained: when a few distinct scores are shared by very many passages, the first digit falls into the score
+// and leaves one whole tie group, the second, from the highest bit in which the keys left differ, falls into the passage-id bits and
+// leaves 2^-11 of it.
+#define SEL2_FEW 32
+// The boundary digit of a histogram of PER digits per thread: the smallest whose count, and those before it, reach r.  Every thread of
+// the workgroup returns the same.
+template <int PER>
+__device__ __forceinline__ void sel2_boundary(const int32_t *__restrict__ gh, int r, Sel2Finish &l, int &bstar, int &before)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c0 = gh[PER * threadIdx.x], c1 = PER == 2 ? gh[PER * threadIdx.x + 1] : 0;
+    int incl = c0 + c1;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+    }
+    if (lane == 63) l.h256[wave] = incl;
+    if (threadIdx.x == 0) {
+        l.sh[0] = SEL_BINS;
+        l.sh[1] = 0;
+    }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += l.h256[w];
+    const int excl = incl - c0 - c1;
+    if (excl < r && incl >= r) {
+        const bool second = excl + c0 < r;
+        l.sh[0] = PER * threadIdx.x + (second ? 1 : 0);
+        l.sh[1] = excl + (second ? c0 : 0);
+    }
+    __syncthreads();
+    bstar = __builtin_amdgcn_readfirstlane(l.sh[0]);
+    before = __builtin_amdgcn_readfirstlane(l.sh[1]);
+    __syncthreads();
+}
+
+// Digit pass over an over-long boundary list by all of a query's workgroups (smaller digits are selected, the boundary digit's keys
+// are left) and, by the last of them to arrive, the end of the selection; a list that LDS holds is cut by the first workgroup
+// alone.  LEVEL 1: the bin filter's list; what it leaves goes on to LEVEL 2 if that is launched (second) and LDS does not hold it.
+// Nobody waits for anybody; what the last workgroup reads of the others' goes past the XCDs' caches (AGENT).
+template <int LEVEL>
+__global__ __launch_bounds__(FIN_THREADS, 8) void sel2_cut_kernel(const uint64_t *__restrict__ list, int64_t list_stride, Sel2State *state,
+                                                               const int32_t *__restrict__ hist, const S2Meta *__restrict__ meta, int lists,
+                                                               int id_shift, int second, uint64_t *left, int64_t left_stride,
+                                                               const uint32_t *__restrict__ emptybits, int64_t cand_words, int64_t P,
+                                                               int32_t m, uint64_t *out, int64_t out_stride, int32_t *__restrict__ out_counts)
+{
+    __shared__ Sel2Finish l;
+    __shared__ Sel2Place<FIN_THREADS> place;
+    constexpr int GROUPS = SEL2_GROUPS / 2, STEP = FIN_THREADS * GROUPS;
+    const int seg = blockIdx.y;
+    Sel2State *s = state + seg;
+    const uint64_t *bl = list + (int64_t)seg * list_stride;
+    uint64_t *o = out + (int64_t)seg * out_stride;
+    int n = LEVEL == 1 ? s->n_b : s->n_b1, m_rem = LEVEL == 1 ? s->m_rem : s->m_rem1, n_sure = s->n_sure, top_bit;
+    if (LEVEL == 2 && n <= SEL_SORT_CAP) return;  // (uniform) LEVEL 1 has ended the selection
+    if (n <= SEL_SORT_CAP) {
+        if (blockIdx.x > 0) return;
+        top_bit = sel2_top_bit(s->b_or, s->b_nor);
+    } else {
+        if ((int64_t)blockIdx.x * STEP >= n) return;
+        const int n_work = (n + STEP - 1) / STEP < (int)gridDim.x ? (n + STEP - 1) / STEP : (int)gridDim.x;
+        // LEVEL 1: the digit of the score, or of the id where all keys share the score
+        const bool tie = LEVEL == 1 && ((s->b_or & s->b_nor) >> 32) == 0;
+        const S2Meta mt = meta[seg];
+        const int bin = s->bin, bin_shift = lists && mt.K <= S2_MAX_KEPT ? S2_COARSE_SHIFT : 0;
+        int shift = 0, width = 0, bstar, before;
+        if (LEVEL == 2) sel2_digit_plan<2>(s, shift, width);
+        const int32_t *gh = hist + (int64_t)seg * SEL_BINS;
+        sel2_boundary<LEVEL == 1 ? 1 : 2>(tie ? gh + SEL2_SUB : gh, m_rem, l, bstar, before);
+        uint64_t *my_left = left + (int64_t)seg * left_stride;
+        unsigned long long any = 0, none = 0;
+        int parity = 0;
+        for (int64_t s0 = (int64_t)blockIdx.x * STEP; s0 < n; s0 += (int64_t)n_work * STEP, parity ^= 1) {  // uniform
+            uint64_t key[GROUPS];
+            int cls[GROUPS];
+#pragma unroll
+            for (int u = 0; u < GROUPS; ++u) {
+                const int64_t i = s0 + u * FIN_THREADS + threadIdx.x;
+                key[u] = i < n ? bl[i] : 0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < GROUPS; ++u) {
+                const int d = LEVEL == 2 ? digit_of(key[u], shift, width)
+                                         : (tie ? (int)((uint32_t)key[u] >> id_shift) : sel2_sub_bin(key[u], mt, bin, bin_shift));
+                cls[u] = s0 + u * FIN_THREADS + threadIdx.x < n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
+            }
+            sel2_place<FIN_THREADS, GROUPS, true>(key, cls, parity, place, &s->n_sure, LEVEL == 1 ? &s->n_b1 : &s->n_b2, o, my_left, any, none);
+        }
+        if (LEVEL == 1) sel2_place_bits<FIN_THREADS>(any, none, place, &s->b_or1, &s->b_nor1);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);  // every store and atomic of this wave has completed
+        __syncthreads();
+        if (threadIdx.x == 0) l.sh[0] = __hip_atomic_fetch_add(&s->arrived[LEVEL - 1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (l.sh[0] != n_work - 1) return;  // uniform
+        auto word = [](const int32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        n = word(LEVEL == 1 ? &s->n_b1 : &s->n_b2);
+        n_sure = word(&s->n_sure);
+        m_rem -= before;
+        if (LEVEL == 1) {
+            if (second && n > SEL_SORT_CAP) {  // uniform
+                if (threadIdx.x == 0) s->m_rem1 = m_rem;
+                return;
+            }
+            top_bit = sel2_top_bit(__hip_atomic_load(&s->b_or1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                                   __hip_atomic_load(&s->b_nor1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        } else {
+            top_bit = shift;
+        }
+        bl = my_left;
+        __syncthreads();
+    }
+    sel2_finish_body<true>(l, bl, n, m_rem, n_sure, top_bit, emptybits + (int64_t)seg * cand_words, cand_words, P, m, o, out_counts + seg);
 }
 
 void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, const uint32_t *candbits, int nq, int64_t P,
@@ -1260,6 +1487,21 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
     // (lists hold some ten thousand keys: with many queries 16 workgroups each, which stride, are enough; 64 each took
     // 86 us for 512 queries, nearly all of them to find that there was nothing for them to do)
     const int gx_filter = lists && nq >= 16 && gx > 16 ? 16 : gx;
+    if (nq <= SEL2_FEW && P > SEL_SORT_CAP) {
+        // (the second pass as below; a list of no more than LDS holds has not gone through the first)
+        const int second = (nq >= 8 || lists) && P > SEL2_SECOND_MIN_PASSAGES ? 1 : 0;
+        const int id_shift = sel2_id_shift(P), cut = gx < 2 ? 1 : gx / 2;
+        hipLaunchKernelGGL(sel2_bins_kernel, dim3(gx_filter, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P, m,
+                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1);
+        hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.meta, lists,
+                           id_shift, second, keys2, key_stride, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
+        if (second) {
+            hipLaunchKernelGGL(sel2_digit_hist_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state, b.hist2);
+            hipLaunchKernelGGL(sel2_cut_kernel<2>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, keys2, key_stride, b.state, b.hist2, b.meta,
+                               lists, id_shift, 0, b.blist, P, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
+        }
+        return;
+    }
     hipLaunchKernelGGL(sel2_filter_kernel, dim3(gx_filter, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P,
                        m, b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists);
     // Digit filters: only a boundary list longer than SEL2_DIGIT_MIN makes them do anything.  The second pair is worth its

@@ -235,7 +235,9 @@ struct Sel2State {
     int32_t m_rem2;
     int32_t shift2, width2;
     int32_t n_list;                    // scored candidates in the key list (inverted form, K <= S2_MAX_KEPT)
-    int32_t pad[12];
+    int32_t bin;                       // the boundary bin
+    int32_t arrived[2];                // workgroups of each of sel2_cut_kernel's passes that have handed over what they kept
+    int32_t pad[9];
 };
 static_assert(sizeof(Sel2State) == 128, "Sel2State is a 128-byte record");
 
