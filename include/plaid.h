@@ -167,7 +167,8 @@ int plaid_search_vanilla(plaid_index *idx, const float *Q, int32_t nq, int32_t n
  *   out_vectors  DEVICE [total][128] fp32 reconstructed vectors, passages concatenated in list order (may be NULL)
  *   out_indices  DEVICE [total][128] uint8 unpacked bucket indices (may be NULL)
  *   capacity     rows available in out_vectors / out_indices; PLAID_EINVAL if total exceeds it
- * Synchronises the stream once (the total is read back to check the capacity). */
+ * Waits once for the stream to reach the call (the device reports the total, which is checked against the capacity), not for
+ * the vectors.  On error the outputs hold nothing of use. */
 int plaid_decompress_passages(plaid_index *idx, const int32_t *pids, int32_t n, int64_t *out_offsets,
                               float *out_vectors, uint8_t *out_indices, int64_t capacity, void *hip_stream);
 

@@ -834,57 +834,86 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
 }
 
 // ------------------------------------------------------------------ decompression alone (parity of the codec)
-// One workgroup: four consecutive passages per thread and round, 4096 passages per round, so that a listing of thousands
-// takes one or two chains of loads (ids, then token ranges) and a scan over the waves in registers.  5000 passages: 39 us
-// with 256 passages per round and a scan through LDS, 19 us this way.
+// Token counts of the listed passages, a passage per thread, and their prefix sums by the workgroup that arrives last (a lane's
+// address each is what a gather of token ranges costs: one compute unit alone takes 15 us for 5000 of them).
+// The ids are the caller's, and nothing is read by one out of range; where there is one the last offset becomes -1, which
+// tells the decompression kernel that nothing is to be done, as a total above the capacity does.  work (two words, zero before and
+// after): workgroups arrived, and how far from the list's end the first id out of range is.  report (memory of the host, which waits
+// for the last word): total, place of that id or -1, the id, 1.
 #define OFFS_THREADS 1024
 #define OFFS_PER 4
-__global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int64_t *__restrict__ doc_offsets,
-                                                                       const int32_t *__restrict__ pids, int n,
-                                                                       int64_t *__restrict__ out_offsets)
+__global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int64_t *__restrict__ doc_offsets, int64_t P,
+                                                                       const int32_t *__restrict__ pids, int n, int64_t *out_offsets,
+                                                                       uint32_t *work, int64_t *report)
 {
     __shared__ int64_t wave_sum[OFFS_THREADS / 64];
+    __shared__ uint32_t arrived;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t e = (int64_t)blockIdx.x * OFFS_THREADS + threadIdx.x;
+    if (e < n) {
+        const int32_t pid = pids[e];
+        int64_t len = 0;
+        if ((uint64_t)(int64_t)pid < (uint64_t)P) len = doc_offsets[(int64_t)pid + 1] - doc_offsets[pid];
+        else atomicMax(&work[1], (uint32_t)(n - e));
+        __hip_atomic_store(&out_offsets[e + 1], len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores and updates have completed
+    __syncthreads();
+    if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(&work[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived != gridDim.x - 1) return;  // uniform
+    const uint32_t bad = __hip_atomic_load(&work[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int64_t carry = 0;  // the same in every thread
-    if (threadIdx.x == 0) out_offsets[0] = 0;
-    for (int64_t base = 0; base < n; base += OFFS_THREADS * OFFS_PER) {
-        const int64_t e0 = base + (int64_t)threadIdx.x * OFFS_PER;
-        int32_t pid[OFFS_PER];
-        int64_t len[OFFS_PER];
+    if (!bad) {         // uniform
+        if (threadIdx.x == 0) out_offsets[0] = 0;
+        for (int64_t base = 0; base < n; base += OFFS_THREADS * OFFS_PER) {
+            // a wave's passages are consecutive, 64 per load
+            const int64_t e0 = base + (int64_t)wave * (64 * OFFS_PER) + lane;
+            int64_t incl[OFFS_PER], sum = 0;
 #pragma unroll
-        for (int u = 0; u < OFFS_PER; ++u) pid[u] = e0 + u < n ? pids[e0 + u] : 0;
+            for (int u = 0; u < OFFS_PER; ++u)
+                incl[u] = e0 + 64 * u < n ? __hip_atomic_load(&out_offsets[e0 + 64 * u + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
 #pragma unroll
-        for (int u = 0; u < OFFS_PER; ++u) len[u] = e0 + u < n ? doc_offsets[pid[u] + 1] - doc_offsets[pid[u]] : 0;
-        int64_t mine = 0;
+            for (int u = 0; u < OFFS_PER; ++u) {
 #pragma unroll
-        for (int u = 0; u < OFFS_PER; ++u) mine += len[u];
-        int64_t incl = mine;
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int64_t t = __shfl_up(incl[u], d);
+                    if (lane >= d) incl[u] += t;
+                }
+                incl[u] += sum;
+                sum = __shfl(incl[u], 63);
+            }
+            if (lane == 63) wave_sum[wave] = sum;
+            __syncthreads();
+            int64_t run = carry;
+#pragma unroll 1
+            for (int w = 0; w < OFFS_THREADS / 64; ++w) {
+                const int64_t t = wave_sum[w];
+                if (w < wave) run += t;
+                carry += t;
+            }
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int64_t t = __shfl_up(incl, d);
-            if (lane >= d) incl += t;
+            for (int u = 0; u < OFFS_PER; ++u)
+                if (e0 + 64 * u < n) out_offsets[e0 + 64 * u + 1] = run + incl[u];
+            __syncthreads();  // the sums are written again in the next round
         }
-        if (lane == 63) wave_sum[wave] = incl;
-        __syncthreads();
-        int64_t run = carry + incl - mine;
-#pragma unroll
-        for (int w = 0; w < OFFS_THREADS / 64; ++w) {
-            const int64_t t = wave_sum[w];
-            if (w < wave) run += t;
-            carry += t;
-        }
-#pragma unroll
-        for (int u = 0; u < OFFS_PER; ++u) {
-            run += len[u];
-            if (e0 + u < n) out_offsets[e0 + u + 1] = run;
-        }
-        __syncthreads();  // the sums are written again in the next round
+    }
+    if (threadIdx.x == 0) {
+        if (bad) out_offsets[n] = -1;
+        work[0] = 0u;
+        work[1] = 0u;
+        report[0] = carry;
+        report[1] = bad ? (int64_t)n - bad : -1;
+        report[2] = bad ? pids[n - bad] : 0;
+        __hip_atomic_store(&report[3], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
-void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, const int32_t *pids, int n,
-                                  int64_t *out_offsets)
+void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, int64_t P, const int32_t *pids, int n, int64_t *out_offsets,
+                                  uint32_t *work, int64_t *report)
 {
-    hipLaunchKernelGGL(passage_offsets_kernel, dim3(1), dim3(OFFS_THREADS), 0, st, doc_offsets, pids, n, out_offsets);
+    const unsigned grid = n > 0 ? (unsigned)(((int64_t)n + OFFS_THREADS - 1) / OFFS_THREADS) : 1u;
+    hipLaunchKernelGGL(passage_offsets_kernel, dim3(grid), dim3(OFFS_THREADS), 0, st, doc_offsets, P, pids, n, out_offsets, work, report);
 }
 
 // Same table, same lookup and same addition as the fused kernel; thread t handles dimensions 4t .. 4t+3.
@@ -897,12 +926,14 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
                                                               const int32_t *__restrict__ pids,
                                                               const int64_t *__restrict__ out_offsets,
                                                               float *__restrict__ out_vectors,
-                                                              uint8_t *__restrict__ out_indices,
+                                                              uint8_t *__restrict__ out_indices, int64_t capacity,
                                                               const float *__restrict__ inv_norm)
 {
     constexpr int RB = 16 * NBITS;
     __shared__ float4 wlut[256 * (NBITS == 2 ? 1 : 2)];
     __shared__ uint32_t ilut[256 * (NBITS == 2 ? 1 : 2)];
+    const int64_t total = out_offsets[gridDim.x];
+    if (total < 0 || total > capacity) return;  // (uniform) passage_offsets_kernel has refused an id, or there is no room
     build_tables<NBITS>(wlut, ilut, weights, threadIdx.x, 256);
     __syncthreads();
     const int a = blockIdx.x;
@@ -944,15 +975,15 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                   int nbits, const int32_t *pids, int n, const int64_t *out_offsets, float *out_vectors,
-                                  uint8_t *out_indices, const float *inv_norm)
+                                  uint8_t *out_indices, int64_t capacity, const float *inv_norm)
 {
     if (n <= 0) return;
     if (nbits == 2)
         hipLaunchKernelGGL(decompress_dump_kernel<2>, dim3(n), dim3(256), 0, st, centroids, doc_offsets, codes, residuals,
-                           bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm);
+                           bucket_weights, pids, out_offsets, out_vectors, out_indices, capacity, inv_norm);
     else
         hipLaunchKernelGGL(decompress_dump_kernel<1>, dim3(n), dim3(256), 0, st, centroids, doc_offsets, codes, residuals,
-                           bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm);
+                           bucket_weights, pids, out_offsets, out_vectors, out_indices, capacity, inv_norm);
 }
 
 // Storage variant "reconstructed vectors scaled to unit length" (the other reading of Section 4.5's reconstruction):

@@ -1,0 +1,116 @@
+"""plaid_decompress_passages: ids out of range at the edges of the offsets kernel's workgroups (1024 ids) and rounds (4096) are refused with their place and
+the index serves the next call; lists around a round's length; several threads with streams of their own."""
+import threading
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _index(pl, P, nbits=2):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P)
+    C = 64
+    lengths = torch.randint(0, 9, (P,), generator=g, device="cuda")
+    offsets = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(lengths, 0)
+    N = int(offsets[-1])
+    codes = torch.randint(0, C, (N,), generator=g, device="cuda", dtype=torch.int32)
+    io, ip = pl.plaid_build_ivf(codes, offsets, C)
+    arrays = {"centroids": torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous(),
+              "doc_offsets": offsets, "codes": codes, "ivf_offsets": io, "ivf_pids": ip,
+              "residuals": torch.randint(0, 256, (N, 16 * nbits), generator=g, device="cuda", dtype=torch.uint8),
+              "bucket_weights": torch.tensor([-0.05, -0.015, 0.015, 0.05][:1 << nbits], device="cuda")}
+    return pl.plaid_index_from_view(arrays, nbits, device=0, copy=False), arrays
+
+
+def _expected(arrays, pids):
+    o = arrays["doc_offsets"]
+    tok = torch.cat([torch.arange(int(o[p]), int(o[p + 1]), device="cuda") for p in pids.tolist()] or [torch.empty(0, dtype=torch.int64, device="cuda")])
+    r = arrays["residuals"][tok].int()
+    ind = torch.stack([(r >> s) & 3 for s in (6, 4, 2, 0)], dim=2).reshape(len(tok), 128)
+    return arrays["centroids"][arrays["codes"][tok].long()] + arrays["bucket_weights"][ind], ind.byte()
+
+
+@pytest.mark.parametrize("n", [0, 1, 63, 1023, 1025, 4096, 4097, 16_385])
+def test_lists_around_a_round(n):
+    import paper_2205_09707_amd as pl
+    idx, arrays = _index(pl, 3000)
+    try:
+        pids = (torch.arange(n, device="cuda") * 37 % 3000).int()
+        o = arrays["doc_offsets"]
+        want = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        want[1:] = torch.cumsum(o[pids.long() + 1] - o[pids.long()], 0)
+        total = int(want[-1])
+        offs, vec, ind = pl.plaid_decompress_passages(idx, pids, total)
+        assert torch.equal(offs, want)
+        few = pids[:300]
+        v, i = _expected(arrays, few)
+        assert torch.equal(vec[:len(v)], v) and torch.equal(ind[:len(i)], i)
+        if total:
+            with pytest.raises(RuntimeError, match="capacity"):
+                pl.plaid_decompress_passages(idx, pids, total - 1)
+    finally:
+        pl.plaid_index_free(idx)
+
+
+@pytest.mark.parametrize("n,places", [(1, [0]), (100, [99]), (4096, [4095]), (4097, [4096]), (20_000, [1024, 19_999]), (20_000, [5, 8191, 16_384])])
+@pytest.mark.parametrize("value", [-1, 3000, 2**31 - 1])
+def test_ids_out_of_range_are_refused(n, places, value):
+    import paper_2205_09707_amd as pl
+    idx, arrays = _index(pl, 3000)
+    try:
+        pids = (torch.arange(n, device="cuda") * 7 % 3000).int()
+        bad = pids.clone()
+        bad[places] = value
+        with pytest.raises(RuntimeError, match=rf"pids\[{places[0]}\] = {value} out of range"):
+            pl.plaid_decompress_passages(idx, bad, 9 * n)
+        assert int(pl.plaid_decompress_passages(idx, pids, 9 * n)[0][-1]) > 0  # the index serves the next call
+    finally:
+        pl.plaid_index_free(idx)
+
+
+def test_refused_under_capture():
+    import paper_2205_09707_amd as pl
+    idx, arrays = _index(pl, 3000)
+    pids = torch.arange(10, device="cuda", dtype=torch.int32)
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    try:
+        with torch.cuda.graph(graph, stream=stream):
+            x = torch.ones(4, device="cuda")
+            with pytest.raises(RuntimeError):
+                pl.plaid_decompress_passages(idx, pids, 90)
+            y = x + 1
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, torch.full((4,), 2.0, device="cuda"))
+    finally:
+        pl.plaid_index_free(idx)
+
+
+def test_several_threads():
+    import paper_2205_09707_amd as pl
+    idx, arrays = _index(pl, 3000)
+    wrong = []
+
+    def work(t):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            pids = (torch.arange(50 + t, device="cuda") * (11 + t) % 3000).int()
+            v, i = _expected(arrays, pids)
+            for _ in range(20):
+                offs, vec, ind = pl.plaid_decompress_passages(idx, pids, len(v))
+                if not (torch.equal(vec, v) and torch.equal(ind, i)):
+                    wrong.append(t)
+            torch.cuda.current_stream().synchronize()
+
+    try:
+        torch.cuda.synchronize()
+        threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong
+    finally:
+        pl.plaid_index_free(idx)
