@@ -1261,9 +1261,11 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
     // nothing: 512 queries of 16384 centroids 327 / 323, of 32768 565 / 553, one of 32768 31.6 / 31.7.
     const bool grouped = form == PLAID_SCQ_SPLIT16 && tmx && groupmax && n_tiles > TAIL_PARTS * TAIL_FLY;
     static_assert(PLAID_SCQ16_GROUP_ROWS == SM_WROWS << 3, "eight tiles per group");
+    const bool takes = form == PLAID_SCQ_SPLIT16 && plaid_scq16_takes_queries(C, nq, zero_words);
     if (!(phases & PLAID_STAGE1_SCORES)) {
     } else if (form == PLAID_SCQ_SPLIT16) {
-        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, grouped ? groupmax : nullptr, score_clocks);
+        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, grouped ? groupmax : nullptr, score_clocks, takes ? Q : nullptr, takes ? zero : nullptr,
+                           takes ? zero_words : 0);
     } else if (matrix_form) {
         if (nq == 1)
             hipLaunchKernelGGL(scq_mfma_kernel<1>, dim3(1, nblk), dim3(SM_THREADS), 0, st, centroids, C, Q, nq, t_cs, S, keepbits,
@@ -1322,7 +1324,8 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
                          int32_t *uniq, int uniq_stride, int32_t *n_uniq, const Stage2Buffers &s2, void *probe_scratch,
                          size_t probe_scratch_bytes, unsigned long long *score_clocks)
 {
-    if ((phases & PLAID_STAGE1_PREP) && form == PLAID_SCQ_SPLIT16) plaid_launch_scq16_split_queries(st, Q, nq, Qd, zero, zero_words);
+    if ((phases & PLAID_STAGE1_PREP) && form == PLAID_SCQ_SPLIT16 && !plaid_scq16_takes_queries(C, nq, zero_words))
+        plaid_launch_scq16_split_queries(st, Q, nq, Qd, zero, zero_words);
     if ((phases & PLAID_STAGE1_PREP) && form == PLAID_SCQ_VECTOR) {
         int64_t gz = (zero_words + 256 * 8 - 1) / (256 * 8);
         if (gz < nq) gz = nq;

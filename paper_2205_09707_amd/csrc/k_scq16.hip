@@ -38,6 +38,18 @@ typedef float scq16_floatx16 __attribute__((ext_vector_type(16)));
 // Operand layout of v_mfma_f32_32x32x16_f16, lane = 32 h + m: the A operand holds row m of a 32-row tile, the B operand
 // column m, both at dimensions 16 s + 8 h .. 16 s + 8 h + 7 of step s.  Centroid tiles and queries use the same layout:
 // dst[tile][term][step][lane] = eight consecutive dimensions of row 32 tile + m, term 0 = a1, term 1 = a2.
+// The two terms of the eight values at p.
+__device__ __forceinline__ void scq16_split(const float4 *__restrict__ p, scq16_half8 &h1, scq16_half8 &h2)
+{
+    const float4 u = p[0], v = p[1];
+    const float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const _Float16 a1 = fabsf(x[j]) >= 6.103515625e-05f ? (_Float16)x[j] : (_Float16)0.0f;  // 2^-14
+        h1[j] = a1;
+        h2[j] = (_Float16)((x[j] - (float)a1) * H16_SCALE);
+    }
+}
 // Rows at or past n_rows are zero.  zero / zero_words: workspace words this launch clears on the side (may be null).
 __global__ __launch_bounds__(256) void scq16_split_kernel(const float *__restrict__ src, int64_t n_rows, int64_t n_tiles,
                                                           scq16_half8 *__restrict__ dst, uint32_t *__restrict__ zero,
@@ -50,19 +62,8 @@ __global__ __launch_bounds__(256) void scq16_split_kernel(const float *__restric
         const int s = (int)(e >> 6) & (H16_STEPS - 1), lane = (int)(e & 63);
         const int64_t row = tile * 32 + (lane & 31);
         const int k0 = 16 * s + 8 * (lane >> 5);
-        float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (row < n_rows) {
-            const float4 *p = reinterpret_cast<const float4 *>(src + row * DIM + k0);
-            const float4 u = p[0], v = p[1];
-            x[0] = u.x, x[1] = u.y, x[2] = u.z, x[3] = u.w, x[4] = v.x, x[5] = v.y, x[6] = v.z, x[7] = v.w;
-        }
-        scq16_half8 h1, h2;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const _Float16 a1 = fabsf(x[j]) >= 6.103515625e-05f ? (_Float16)x[j] : (_Float16)0.0f;  // 2^-14
-            h1[j] = a1;
-            h2[j] = (_Float16)((x[j] - (float)a1) * H16_SCALE);
-        }
+        scq16_half8 h1 = {0, 0, 0, 0, 0, 0, 0, 0}, h2 = h1;
+        if (row < n_rows) scq16_split(reinterpret_cast<const float4 *>(src + row * DIM + k0), h1, h2);
         dst[(tile * 2 + 0) * (H16_STEPS * 64) + s * 64 + lane] = h1;
         dst[(tile * 2 + 1) * (H16_STEPS * 64) + s * 64 + lane] = h2;
     }
@@ -171,7 +172,7 @@ __device__ __forceinline__ float scq16_reduce(const scq16_floatx16 (&acc)[NT], f
 // in order, and a wait sized for the path with the fewest stores would sit out the score stores of the others.
 template <int NT, bool WHOLE, bool GROUPS>
 __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], float (&gmax)[2][H16_WAVES][QLEN], const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16,
-                                           int64_t C, const scq16_half8 *__restrict__ B16, int q_begin, int q_end, float t_lo,
+                                           int64_t C, const scq16_half8 *__restrict__ B16, const float *__restrict__ Q, int q_begin, int q_end, float t_lo,
                                            float t_hi, float *__restrict__ S, uint32_t *__restrict__ keepbits,
                                            uint32_t *__restrict__ ambbits, int64_t keep_words, float *__restrict__ tilemax,
                                            float *__restrict__ groupmax)
@@ -184,8 +185,17 @@ __device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], f
 
     scq16_half8 pre[NPRE];
     const scq16_half8 *bsrc = B16 + (int64_t)q_begin * H16_TILE_VEC + tid;
+    if (Q) {  // (uniform) the one query, not laid out yet
+        static_assert(NPRE == 4 && H16_TILE_VEC == 2 * 2 * H16_THREADS, "a thread has both terms of two vectors");
 #pragma unroll
-    for (int k = 0; k < NPRE; ++k) pre[k] = bsrc[k * H16_THREADS];
+        for (int k = 0; k < 2; ++k) {
+            const int e = tid + k * H16_THREADS, l = e & 63;
+            scq16_split(reinterpret_cast<const float4 *>(Q + (l & 31) * DIM + 16 * (e >> 6) + 8 * (l >> 5)), pre[k], pre[k + 2]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NPRE; ++k) pre[k] = bsrc[k * H16_THREADS];
+    }
 
     scq16_half8 a[NT][2][H16_STEPS];
 #pragma unroll
@@ -291,7 +301,8 @@ template <int NT, bool GROUPS>
 __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     const scq16_half8 *__restrict__ A16, int64_t C, const scq16_half8 *__restrict__ B16, int nq, int qg, float t_lo, float t_hi,
     float *__restrict__ S, uint32_t *__restrict__ keepbits, uint32_t *__restrict__ ambbits, int64_t keep_words,
-    float *__restrict__ tilemax, float *__restrict__ groupmax, unsigned long long *__restrict__ clocks)
+    float *__restrict__ tilemax, float *__restrict__ groupmax, unsigned long long *__restrict__ clocks, const float *__restrict__ Q,
+    uint32_t *__restrict__ zero, int64_t zero_words)
 {
     __shared__ scq16_half8 Bs[2][H16_TILE_VEC];
     __shared__ float gmax[2][H16_WAVES][QLEN];
@@ -301,6 +312,8 @@ __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int64_t tile0 = ((int64_t)blockIdx.x * H16_WAVES + wave) * NT;
     const int q_begin = blockIdx.y * qg, q_end = q_begin + qg < nq ? q_begin + qg : nq;
+    // (with Q: one query, which the workgroups lay out themselves, and workspace words to clear on the side)
+    for (int64_t i = (int64_t)blockIdx.x * H16_THREADS + threadIdx.x; i < zero_words; i += (int64_t)gridDim.x * H16_THREADS) zero[i] = 0u;
     int nvalid[NT];  // (uniform) rows of each tile that exist: 0 for a tile past the end of the table
     bool whole = true;
 #pragma unroll
@@ -311,9 +324,9 @@ __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     }
     // (the barriers inside are reached by all four waves in either instance: both run the same loop over the queries)
     if (whole)
-        scq16_body<NT, true, GROUPS>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
+        scq16_body<NT, true, GROUPS>(Bs, gmax, nvalid, A16, C, B16, Q, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
     else
-        scq16_body<NT, false, GROUPS>(Bs, gmax, nvalid, A16, C, B16, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
+        scq16_body<NT, false, GROUPS>(Bs, gmax, nvalid, A16, C, B16, Q, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
     if (clocks && threadIdx.x == 0) {
         atomicAdd(&clocks[0], (unsigned long long)(clock64() - sc0));
         atomicAdd(&clocks[1], (unsigned long long)(wall_clock64() - rt0));
@@ -369,9 +382,16 @@ void plaid_launch_scq16_split_queries(hipStream_t st, const float *Q, int nq, vo
                        zero, zero_words);
 }
 
+// One query: its operands are formed by the score kernel's workgroups, each for itself, instead of by a launch of their own, and the
+// words that start at zero are cleared there, where those are few per workgroup (a search of one query of 10 000 / 200 000 / 400 000 /
+// 8.8 M passages 66.3 / 77.6 / 98.8 / 268.3 us with that launch, 66.0 / 75.9 / 97.8 / 266.9 without).
+bool plaid_scq16_takes_queries(int64_t C, int nq, int64_t zero_words)
+{
+    return nq == 1 && zero_words <= 32 * H16_THREADS * ((C + 32 * H16_WG_TILES - 1) / (32 * H16_WG_TILES));
+}
 void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *B16, int nq, float t_cs, float *S,
                         uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax, float *groupmax,
-                        unsigned long long *clocks)
+                        unsigned long long *clocks, const float *Q, uint32_t *zero, int64_t zero_words)
 {
     static_assert(32 * H16_WG_TILES == PLAID_SCQ16_GROUP_ROWS, "a workgroup's rows are a group");
     // the two thresholds of the pruning test, rounded away from t_cs (infinite t_cs: both equal it, nothing is ambiguous)
@@ -390,7 +410,8 @@ void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *
     const unsigned gy = (unsigned)((nq + qg - 1) / qg);
 #define PLAID_SCQ16_LAUNCH(GR)                                                                                                \
     hipLaunchKernelGGL((scq16_kernel<H16_NT, GR>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,        \
-                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax, clocks)
+                       (const scq16_half8 *)B16, nq, qg, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax, clocks, Q, \
+                       zero, zero_words)
     if (groupmax) PLAID_SCQ16_LAUNCH(true);
     else PLAID_SCQ16_LAUNCH(false);
 #undef PLAID_SCQ16_LAUNCH

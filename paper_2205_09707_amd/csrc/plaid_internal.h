@@ -182,7 +182,9 @@ void plaid_launch_scq16_split_queries(hipStream_t st, const float *Q, int nq, vo
 // clocks (may be null): [0] += shader-clock ticks, [1] += 100 MHz timer ticks, both summed over the workgroups.
 void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *B16, int nq, float t_cs, float *S,
                         uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax, float *groupmax,
-                        unsigned long long *clocks = nullptr);
+                        unsigned long long *clocks = nullptr, const float *Q = nullptr, uint32_t *zero = nullptr, int64_t zero_words = 0);
+// Whether plaid_launch_scq16 takes the query itself (Q, and zero words to clear) in place of its operand form.
+bool plaid_scq16_takes_queries(int64_t C, int nq, int64_t zero_words);
 
 // General top-nprobe (nprobe > PLAID_PROBE_FAST_MAX): ranking keys of every S column through the generic selection.
 void plaid_launch_top_nprobe_general(hipStream_t st, const float *S, int64_t C, int nq, int nprobe, int32_t *probed,
