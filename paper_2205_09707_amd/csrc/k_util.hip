@@ -67,51 +67,82 @@ void plaid_launch_keys_to_pairs(hipStream_t st, const uint64_t *keys, int64_t ke
                        out_scores, out_counts);
 }
 
-// Ascending list of the set bits of bits[q][0..words): one workgroup per query, chunked prefix sums.
+// Ascending list of the set bits of bits[q][0..words).  A workgroup lists `chunk` words (a multiple of 1024) and counts the bits of all
+// words before them itself, a few loads per thread and no waiting for another workgroup.  A wave writes the ids of 64 passages at a
+// time, side by side.  Sixteen queries of 400 000 candidates: 12 us, with one workgroup per query, a scan through LDS and a thread
+// per word 239.
 __global__ __launch_bounds__(1024) void bitmap_to_list_kernel(const uint32_t *__restrict__ bits, int64_t words,
-                                                              int64_t nvalid, int32_t *__restrict__ out,
+                                                              int64_t nvalid, int64_t chunk, int32_t *__restrict__ out,
                                                               int64_t out_stride, int32_t *__restrict__ out_counts)
 {
-    __shared__ int32_t scan[1024];
-    __shared__ int32_t base_s;
-    const int q = blockIdx.x;
+    __shared__ int32_t wave_sum[16];
+    const int q = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const uint32_t *b = bits + (int64_t)q * words;
     int32_t *o = out ? out + (int64_t)q * out_stride : nullptr;
-    if (threadIdx.x == 0) base_s = 0;
-    __syncthreads();
-    for (int64_t w0 = 0; w0 < words; w0 += 1024) {
-        const int64_t w = w0 + threadIdx.x;
-        uint32_t v = w < words ? b[w] : 0u;
-        if (w < words && (w + 1) * 32 > nvalid) {  // mask bits beyond the valid range
-            const int64_t keep = nvalid - w * 32;
-            v = keep <= 0 ? 0u : (keep >= 32 ? v : (v & ((1u << keep) - 1u)));
-        }
-        const int cnt = __popc(v);
-        scan[threadIdx.x] = cnt;
-        __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            const int t = threadIdx.x >= d ? scan[threadIdx.x - d] : 0;
-            __syncthreads();
-            scan[threadIdx.x] += t;
-            __syncthreads();
-        }
-        int pos = base_s + scan[threadIdx.x] - cnt;
-        if (o)
-            while (v) {
-                const int bit = __ffs(v) - 1;
-                v &= v - 1;
-                o[pos++] = (int32_t)(w * 32 + bit);
-            }
-        __syncthreads();
-        if (threadIdx.x == 1023) base_s += scan[1023];
-        __syncthreads();
+    auto valid = [&](int64_t w, uint32_t v) -> uint32_t {  // bits beyond the valid range do not count
+        const int64_t keep = nvalid - w * 32;
+        return keep >= 32 ? v : (keep <= 0 ? 0u : v & ((1u << keep) - 1u));
+    };
+    const int64_t first = (int64_t)blockIdx.x * chunk, last = first + chunk < words ? first + chunk : words;
+    int cnt = 0;
+    for (int64_t w = threadIdx.x; w < first; w += 8 * 1024) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = w + 1024 * u < first ? b[w + 1024 * u] : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cnt += __popc(w + 1024 * u < first ? valid(w + 1024 * u, v[u]) : 0u);
     }
-    if (threadIdx.x == 0 && out_counts) out_counts[q] = base_s;
+    int incl = cnt;
+    // inclusive sums over the waves' lanes; the waves' totals in LDS; what lies before this wave, and the total
+    auto totals = [&](int &before, int &all) {
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d);
+            if (lane >= d) incl += t;
+        }
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        before = all = 0;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int t = wave_sum[v];
+            if (v < wave) before += t;
+            all += t;
+        }
+        __syncthreads();  // (the sums are written again)
+    };
+    int before, base;
+    totals(before, base);  // base: bits of the words before `first`
+    for (int64_t w0 = first; w0 < last; w0 += 1024) {  // uniform
+        const int64_t w = w0 + threadIdx.x;
+        const uint32_t v = w < last ? valid(w, b[w]) : 0u;
+        incl = __popc(v);
+        const int mine = incl;
+        int all;
+        totals(before, all);
+        const int at = base + before + incl - mine;  // of this lane's first bit
+        if (o && __any(v != 0u)) {                   // uniform over the wave
+#pragma unroll 4
+            for (int k = 0; k < 64; k += 2) {
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)v, k), hi = (uint32_t)__builtin_amdgcn_readlane((int)v, k + 1);
+                const int place = __builtin_amdgcn_readlane(at, k);
+                const unsigned long long m = (unsigned long long)hi << 32 | lo;
+                if ((m >> lane) & 1ull)
+                    o[place + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)((w0 + 64 * wave + k) * 32 + lane);
+            }
+        }
+        base += all;
+    }
+    if (threadIdx.x == 0 && out_counts && blockIdx.x == gridDim.x - 1) out_counts[q] = base;
 }
 void plaid_launch_bitmap_to_list(hipStream_t st, const uint32_t *bits, int64_t words, int64_t nbits_valid, int nq,
                                  int32_t *out, int64_t out_stride, int32_t *out_counts)
 {
-    hipLaunchKernelGGL(bitmap_to_list_kernel, dim3(nq), dim3(1024), 0, st, bits, words, nbits_valid, out, out_stride,
+    // (64 workgroups per query at most: each reads the words before its own)
+    const int64_t parts = (words + 1023) / 1024, most = 64, per = (parts + most - 1) / most;
+    const int64_t chunk = 1024 * (per > 1 ? per : 1);
+    const int64_t gx = words > chunk ? (words + chunk - 1) / chunk : 1;
+    hipLaunchKernelGGL(bitmap_to_list_kernel, dim3((unsigned)gx, nq), dim3(1024), 0, st, bits, words, nbits_valid, chunk, out, out_stride,
                        out_counts);
 }
 
