@@ -154,7 +154,82 @@ __device__ void find_boundary(const int32_t *__restrict__ gh, int32_t m_rem, int
     if (bstar == SEL_BINS) before = total;
 }
 
+// Keys that other workgroups of the same launch write or read (AGENT) go past the second-level caches, which are not coherent between
+// the XCDs.
+template <bool AGENT>
+__device__ __forceinline__ uint64_t sel_key(const uint64_t *p)
+{
+    return AGENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <bool AGENT>
+__device__ __forceinline__ void sel_put(uint64_t *p, uint64_t key)
+{
+    if (AGENT) __hip_atomic_store(p, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = key;
+}
+
+#define SEL2_GROUPS 8                              // keys a thread takes per step
+#define SEL2_STEP (SEL_THREADS * SEL2_GROUPS)     // keys a workgroup takes per step
+template <int THREADS>
+struct Sel2Place {                                // LDS of sel2_place
+    int32_t cnt[2][2][THREADS / 64];              // [parity of the step][selected / boundary][wave]
+    int32_t base[2];
+    unsigned long long bits[2][THREADS / 64];
+};
+// Writes a step's keys of class 0 (selected) to out and of class 1 (boundary) to bl; o, no collect the boundary keys' bits and
+// their complements.  The workgroup reserves its positions with one update of each counter per step: the counters of a query
+// are two words that every workgroup of the launch updates and waits for, one after the other.  One query of 8.8 M passages:
+// with an update per wave the bin filter took 27.6 us and the digit filter, 64 keys a wave, 19.9; now 8.1 and 5.8.  All
+// threads call this.
+template <int THREADS, int GROUPS, bool AGENT>
+__device__ __forceinline__ void sel2_place(const uint64_t (&key)[GROUPS], const int (&cls)[GROUPS], int parity, Sel2Place<THREADS> &l,
+                                           int32_t *n_sure, int32_t *n_boundary, uint64_t *__restrict__ out,
+                                           uint64_t *__restrict__ bl, unsigned long long &o, unsigned long long &no)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long b0[GROUPS], b1[GROUPS];
+    int n0 = 0, n1 = 0;
+#pragma unroll
+    for (int u = 0; u < GROUPS; ++u) {
+        b0[u] = __ballot(cls[u] == 0);
+        b1[u] = __ballot(cls[u] == 1);
+        n0 += __popcll(b0[u]);
+        n1 += __popcll(b1[u]);
+    }
+    if (lane == 0) {
+        l.cnt[parity][0][wave] = n0;
+        l.cnt[parity][1][wave] = n1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < THREADS / 64; ++w) n += l.cnt[parity][threadIdx.x][w];
+        l.base[threadIdx.x] = n ? atomicAdd(threadIdx.x == 0 ? n_sure : n_boundary, n) : 0;
+    }
+    __syncthreads();
+    int base0 = l.base[0], base1 = l.base[1];
+    for (int w = 0; w < wave; ++w) {
+        base0 += l.cnt[parity][0][w];
+        base1 += l.cnt[parity][1][w];
+    }
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int u = 0; u < GROUPS; ++u) {
+        if (cls[u] == 0) out[base0 + __popcll(b0[u] & below)] = key[u];
+        if (cls[u] == 1) {
+            sel_put<AGENT>(&bl[base1 + __popcll(b1[u] & below)], key[u]);
+            o |= key[u];
+            no |= ~key[u];
+        }
+        base0 += __popcll(b0[u]);
+        base1 += __popcll(b1[u]);
+    }
+}
+
 // ------------------------------------------------------------------ level kernel: split a list by its digit
+// Positions are reserved by the workgroup, once per counter and 2048 keys (sixteen lists of 400 000 keys, the best 16 384 of each: 199 us
+// with an update per wave and 64 keys, 24 now; the second level 39 -> 11).
 template <int LEVEL>
 __global__ __launch_bounds__(SEL_THREADS) void sel_level_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                 SelState *state, int32_t *__restrict__ hist,
@@ -164,6 +239,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_level_kernel(const uint64_t *
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
     __shared__ int32_t lh[LEVEL == 0 ? SEL_BINS : 1];
+    __shared__ Sel2Place<SEL_THREADS> place;
     const int seg = blockIdx.y;
     SelState *s = state_of(state, seg);
     const int n = LEVEL == 0 ? s->n_in : s->n_list[0];
@@ -180,30 +256,23 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_level_kernel(const uint64_t *
     const uint64_t *k = keys + (int64_t)seg * key_stride;
     uint64_t *my_sure = sure + (int64_t)seg * sure_stride;
     uint64_t *my_out = list_out + (int64_t)seg * list_stride;
-    const int lane = threadIdx.x & 63;
-    const int64_t n_round = ((int64_t)n + 63) & ~63ll;  // whole waves iterate together (ballots below)
-    for (int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x; i < n_round; i += (int64_t)gridDim.x * SEL_THREADS) {
-        uint64_t key = 0;
-        int cls = 2;  // 0 = surely selected, 1 = boundary, 2 = dropped
-        if (i < n) {
-            key = k[i];
-            const int d = digit_of(key, shift, width);
-            cls = d < bstar ? 0 : (d == bstar ? 1 : 2);
+    unsigned long long any = 0, none = 0;  // (not used here)
+    int parity = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * SEL2_STEP; s0 < n; s0 += (int64_t)gridDim.x * SEL2_STEP, parity ^= 1) {  // uniform
+        uint64_t key[SEL2_GROUPS];
+        int cls[SEL2_GROUPS];  // 0 = surely selected, 1 = boundary, 2 = dropped
+#pragma unroll
+        for (int u = 0; u < SEL2_GROUPS; ++u) {
+            const int64_t i = s0 + u * SEL_THREADS + threadIdx.x;
+            key[u] = i < n ? k[i] : 0ull;
         }
-        const unsigned long long b0 = __ballot(cls == 0), b1 = __ballot(cls == 1);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        int base0 = 0, base1 = 0;
-        if (lane == 0) {
-            if (b0) base0 = atomicAdd(&s->n_sure, __popcll(b0));
-            if (b1) base1 = atomicAdd(&s->n_list[LEVEL], __popcll(b1));
+#pragma unroll
+        for (int u = 0; u < SEL2_GROUPS; ++u) {
+            const int d = digit_of(key[u], shift, width);
+            cls[u] = s0 + u * SEL_THREADS + threadIdx.x < n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
+            if (LEVEL == 0 && cls[u] == 1) atomicAdd(&lh[digit_of(key[u], shift_n, width_n)], 1);
         }
-        base0 = __shfl(base0, 0);
-        base1 = __shfl(base1, 0);
-        if (cls == 0) my_sure[base0 + __popcll(b0 & below)] = key;
-        if (cls == 1) {
-            my_out[base1 + __popcll(b1 & below)] = key;
-            if (LEVEL == 0) atomicAdd(&lh[digit_of(key, shift_n, width_n)], 1);
-        }
+        sel2_place<SEL_THREADS, SEL2_GROUPS, false>(key, cls, parity, place, &s->n_sure, &s->n_list[LEVEL], my_sure, my_out, any, none);
     }
     if (LEVEL == 0) {
         __syncthreads();
@@ -517,20 +586,6 @@ __global__ __launch_bounds__(256) void sel_rank_output_kernel(const uint64_t *__
         oi[rank] = (int32_t)(key & 0xFFFFFFFFu);
         os[rank] = plaid_ord_to_score((uint32_t)(key >> 32));
     }
-}
-
-// Keys that other workgroups of the same launch write or read (AGENT) go past the second-level caches, which are not coherent between
-// the XCDs.
-template <bool AGENT>
-__device__ __forceinline__ uint64_t sel_key(const uint64_t *p)
-{
-    return AGENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
-}
-template <bool AGENT>
-__device__ __forceinline__ void sel_put(uint64_t *p, uint64_t key)
-{
-    if (AGENT) __hip_atomic_store(p, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = key;
 }
 
 // The `take` smallest (in any order) of the n <= SEL_SORT_CAP keys of `bl`, to o; every key agrees at and above bit `high`.
@@ -852,64 +907,6 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
 // Candidates with an empty bag (-infinity) are appended last, in passage-id order, straight from
 // their bitmap.
 // =================================================================================================
-#define SEL2_GROUPS 8                              // keys a thread takes per step
-#define SEL2_STEP (SEL_THREADS * SEL2_GROUPS)     // keys a workgroup takes per step
-template <int THREADS>
-struct Sel2Place {                                // LDS of sel2_place
-    int32_t cnt[2][2][THREADS / 64];              // [parity of the step][selected / boundary][wave]
-    int32_t base[2];
-    unsigned long long bits[2][THREADS / 64];
-};
-// Writes a step's keys of class 0 (selected) to out and of class 1 (boundary) to bl; o, no collect the boundary keys' bits and
-// their complements.  The workgroup reserves its positions with one update of each counter per step: the counters of a query
-// are two words that every workgroup of the launch updates and waits for, one after the other.  One query of 8.8 M passages:
-// with an update per wave the bin filter took 27.6 us and the digit filter, 64 keys a wave, 19.9; now 8.1 and 5.8.  All
-// threads call this.
-template <int THREADS, int GROUPS, bool AGENT>
-__device__ __forceinline__ void sel2_place(const uint64_t (&key)[GROUPS], const int (&cls)[GROUPS], int parity, Sel2Place<THREADS> &l,
-                                           int32_t *n_sure, int32_t *n_boundary, uint64_t *__restrict__ out,
-                                           uint64_t *__restrict__ bl, unsigned long long &o, unsigned long long &no)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long b0[GROUPS], b1[GROUPS];
-    int n0 = 0, n1 = 0;
-#pragma unroll
-    for (int u = 0; u < GROUPS; ++u) {
-        b0[u] = __ballot(cls[u] == 0);
-        b1[u] = __ballot(cls[u] == 1);
-        n0 += __popcll(b0[u]);
-        n1 += __popcll(b1[u]);
-    }
-    if (lane == 0) {
-        l.cnt[parity][0][wave] = n0;
-        l.cnt[parity][1][wave] = n1;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        int n = 0;
-#pragma unroll
-        for (int w = 0; w < THREADS / 64; ++w) n += l.cnt[parity][threadIdx.x][w];
-        l.base[threadIdx.x] = n ? atomicAdd(threadIdx.x == 0 ? n_sure : n_boundary, n) : 0;
-    }
-    __syncthreads();
-    int base0 = l.base[0], base1 = l.base[1];
-    for (int w = 0; w < wave; ++w) {
-        base0 += l.cnt[parity][0][w];
-        base1 += l.cnt[parity][1][w];
-    }
-    const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int u = 0; u < GROUPS; ++u) {
-        if (cls[u] == 0) out[base0 + __popcll(b0[u] & below)] = key[u];
-        if (cls[u] == 1) {
-            sel_put<AGENT>(&bl[base1 + __popcll(b1[u] & below)], key[u]);
-            o |= key[u];
-            no |= ~key[u];
-        }
-        base0 += __popcll(b0[u]);
-        base1 += __popcll(b1[u]);
-    }
-}
 // The workgroup's boundary bits to the query's.  All threads call this, once.
 template <int THREADS>
 __device__ __forceinline__ void sel2_place_bits(unsigned long long o, unsigned long long no, Sel2Place<THREADS> &l, unsigned long long *b_or,
