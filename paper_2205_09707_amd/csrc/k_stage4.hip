@@ -76,7 +76,7 @@ template <>
 struct S4Entry<1> {
     typedef s4_half8 type;
 };
-template <int NBITS>
+template <int NBITS, bool SECOND = true>
 __device__ __forceinline__ void s4_build_tables(typename S4Entry<NBITS>::type *hlut, const float *__restrict__ weights, int tid,
                                                 int nthreads)
 {
@@ -90,7 +90,7 @@ __device__ __forceinline__ void s4_build_tables(typename S4Entry<NBITS>::type *h
             b[d] = x2;
         }
         hlut[v] = a;
-        hlut[S4_SECOND + v] = b;
+        if (SECOND) hlut[S4_SECOND + v] = b;
     }
 }
 // A half of the wave (h = lane / 32) contracts half of the 128 dimensions, the 2 NBITS packed words 2 NBITS h .. of a token;
@@ -130,7 +130,8 @@ __device__ __forceinline__ float s4_max3(float a, float b, float c)
 
 // The two fp16 terms of the query in the operand order of v_mfma_f32_32x32x16_f16, into LDS: lane 32 h + r of step s holds
 // query token r, dimensions s4_dim(s, h, 0) .. + 7.  All 256 threads of the workgroup call this, a barrier follows.
-__device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_half8 (&qs)[2][8][64])
+template <int TERMS>
+__device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_half8 (&qs)[TERMS][8][64])
 {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -147,7 +148,7 @@ __device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_
             t2[j] = x2;
         }
         qs[0][s][l] = t1;
-        qs[1][s][l] = t2;
+        if constexpr (TERMS > 1) qs[TERMS - 1][s][l] = t2;
     }
 }
 
@@ -186,6 +187,35 @@ __device__ __forceinline__ void s4_products(const uint32_t (&rw)[2 * NBITS], con
         }
         a1 = n1, a2 = n2, q1 = r1, q2 = r2;
         if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The leading products alone, rows = tokens.
+template <int NBITS>
+__device__ __forceinline__ void s4_leading_products(const uint32_t (&rw)[2 * NBITS], const typename S4Entry<NBITS>::type *hlut,
+                                                    const s4_half8 (&qs)[8][64], int lane, floatx16 &acc)
+{
+    auto decode = [&](int s) -> s4_half8 {
+        if constexpr (NBITS == 2) {
+            const uint32_t w = rw[s >> 1] >> (16 * (s & 1));
+            const s4_half4 x0 = hlut[w & 0xFFu], x1 = hlut[(w >> 8) & 0xFFu];
+            return __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+            return hlut[(rw[s >> 2] >> (8 * (s & 3))) & 0xFFu];
+        }
+    };
+    int ql = lane;
+    asm volatile("" : "+v"(ql));
+    s4_half8 a = decode(0), q = qs[0][ql];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        s4_half8 n = a, r = q;
+        if (s < 7) {
+            r = qs[s + 1][ql];
+            n = decode(s + 1);
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, q, acc, 0, 0, 0);
+        a = n, q = r;
     }
 }
 
@@ -449,9 +479,10 @@ __device__ __forceinline__ void vp_sync()  // orders a wave's LDS accesses
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// RN, WIDE: as above.
-template <int NBITS, bool FILTER, bool RN, bool WIDE>
-__global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
+// RN, WIDE: as above.  COARSE (with FILTER): the leading products only, a third of the matrix instructions and half of the table
+// look-ups; every score lies within the bound that van_bounds_kernel computes of the full one.
+template <int NBITS, bool FILTER, bool RN, bool WIDE, bool COARSE>
+__device__ __forceinline__ void maxsim_list_body(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
     const float *__restrict__ inv_norm, const uint64_t *__restrict__ in_keys, int64_t in_stride,
@@ -460,8 +491,8 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
     int64_t out_stride)
 {
     constexpr int RB = 16 * NBITS, RW = 2 * NBITS;
-    __shared__ s4_half8 qs[2][8][64];  // [term][step][lane]
-    __shared__ typename S4Entry<NBITS>::type hlut[S4_SECOND + 256];
+    __shared__ s4_half8 qs[COARSE ? 1 : 2][8][64];  // [term][step][lane]
+    __shared__ typename S4Entry<NBITS>::type hlut[COARSE ? 256 : S4_SECOND + 256];
     __shared__ __attribute__((aligned(16))) VpArea areas[4];
     __shared__ __align__(16) float inv_norms[RN ? 4 : 1][RN ? VP_CAP : 1];
     extern __shared__ uint32_t probe_lds[];  // FILTER: keep_words words, when at most VP_LDS_WORDS
@@ -498,7 +529,7 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
     }
     if (lo + (int64_t)bx * 4 * VP_GROUP >= count) return;  // uniform for the workgroup
     const int r32 = lane & 31, h = lane >> 5;
-    s4_build_tables<NBITS>(hlut, weights, threadIdx.x, 256);
+    s4_build_tables<NBITS, !COARSE>(hlut, weights, threadIdx.x, 256);
     const char *Sq = reinterpret_cast<const char *>(S + (int64_t)q * C * QLEN);
     const uint32_t *pb = FILTER ? probebits + (int64_t)q * keep_words : nullptr;
     const bool pb_in_lds = FILTER && keep_words <= VP_LDS_WORDS;
@@ -567,7 +598,8 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
             request(tok_next, rw_next);  // (past the last step: some token of the list again, not used)
             floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // cross terms, scaled by 2^11
-            s4_products<NBITS, true, true>(rw, hlut, qs, lane, acc, acx);
+            if constexpr (COARSE) s4_leading_products<NBITS>(rw, hlut, qs[0], lane, acc);
+            else s4_products<NBITS, true, true>(rw, hlut, qs, lane, acc, acx);
             const int32_t end[4] = {ends.x, ends.y, ends.z, ends.w};
             const int next = have - at >= 64 ? at + 32 : at;
             codes_at(next, cc);
@@ -577,7 +609,7 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
             for (int g = 0; g < 4; ++g) {
                 float x[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] = fmaf(acx[4 * g + v], 1.0f / S4_SCALE, acc[4 * g + v]) + sv[4 * g + v];
+                for (int v = 0; v < 4; ++v) x[v] = (COARSE ? acc[4 * g + v] : fmaf(acx[4 * g + v], 1.0f / S4_SCALE, acc[4 * g + v])) + sv[4 * g + v];
                 if (RN) {
                     const float4 f = *reinterpret_cast<const float4 *>(&anf[at + 8 * g + 4 * h]);
                     x[0] *= f.x, x[1] *= f.y, x[2] *= f.z, x[3] *= f.w;
@@ -741,6 +773,190 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
         if (!more) break;
     }
     if (completed > summed) write_out(completed - summed);
+}
+
+template <int NBITS, bool FILTER, bool RN, bool WIDE>
+__global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
+    const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
+    const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
+    const float *__restrict__ inv_norm, const uint64_t *__restrict__ in_keys, int64_t in_stride,
+    const uint32_t *__restrict__ probebits, int64_t keep_words, const int32_t *__restrict__ cand, int64_t cand_stride,
+    const int32_t *__restrict__ in_counts, int32_t ncandidates, int nq, int gx, int spread, uint64_t *__restrict__ out_keys,
+    int64_t out_stride)
+{
+    maxsim_list_body<NBITS, FILTER, RN, WIDE, false>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits, keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys, out_stride);
+}
+template <int NBITS>
+__global__ __launch_bounds__(256, 4) void van_coarse_kernel(
+    const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
+    const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
+    const float *__restrict__ inv_norm, const uint64_t *__restrict__ in_keys, int64_t in_stride,
+    const uint32_t *__restrict__ probebits, int64_t keep_words, const int32_t *__restrict__ cand, int64_t cand_stride,
+    const int32_t *__restrict__ in_counts, int32_t ncandidates, int nq, int gx, int spread, uint64_t *__restrict__ out_keys,
+    int64_t out_stride)
+{
+    maxsim_list_body<NBITS, true, false, false, true>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits, keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys, out_stride);
+}
+
+// Pruning by coarse scores.  Most candidates lie far from the cut: scores from the leading products decide them, and only those
+// within the coarse scores' error of it are scored in full.  With T the ncandidates-th best coarse score and E the largest difference
+// between a coarse and a full score of the query, ncandidates full scores are >= T - E, and no more than ncandidates - 1 are > T + E: what
+// has a coarse score > T + 2 E is kept, what has one < T - 2 E is not, and the rest compete by their full scores for the places left.
+// E: of a query token's product with a residual the coarse score misses w . (q - q1) + (w - w1) . q1, at most
+// wmax sum |q - q1| + max |w - w1| sum |q1|; both scores' sums of 128 products of size wmax |q| in fp32, and the additions of the centroid's
+// share (at most centroid_max sum |q|), are rounded.
+struct VanBand {
+    float lo, hi;  // coarse scores within [lo, hi] do not decide
+};
+__global__ __launch_bounds__(1024) void van_bounds_kernel(const float *__restrict__ Q, const float *__restrict__ weights, int nbits,
+                                                          float centroid_max, const uint64_t *__restrict__ kept, int64_t kept_stride,
+                                                          const int32_t *__restrict__ n_kept, const int32_t *__restrict__ n_cand,
+                                                          VanBand *__restrict__ band)
+{
+    __shared__ double part[16];
+    __shared__ unsigned long long worst[16];
+    const int q = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float wmax = 0.f, dw = 0.f;
+    for (int b = 0; b < 1 << nbits; ++b) {
+        _Float16 w1, w2;
+        s4_split(weights[b], w1, w2);
+        wmax = fmaxf(wmax, fabsf(weights[b]));
+        dw = fmaxf(dw, fabsf(weights[b] - (float)w1));
+    }
+    double e = 0.0;
+    for (int i = threadIdx.x; i < QLEN * DIM; i += 1024) {
+        const float x = Q[(int64_t)q * QLEN * DIM + i];
+        _Float16 x1, x2;
+        s4_split(x, x1, x2);
+        const double a = fabs((double)x), b = fabs((double)(float)x1);
+        e += (double)wmax * fabs((double)x - (double)(float)x1) + (double)dw * b;
+        e += 3.0 * 128.0 * 0x1p-24 * (double)wmax * (a + b);         // the fp32 sums of either score
+        e += 0x1p-20 * (a + b) * ((double)centroid_max + (double)wmax);  // the additions of the centroid's share, the sums' last rounding
+    }
+    unsigned long long w = 0;  // the largest key kept: the worst
+    for (int j = threadIdx.x; j < n_kept[q]; j += 1024) {
+        const uint64_t key = kept[(int64_t)q * kept_stride + j];
+        w = key > w ? key : w;
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+        e += __shfl_xor(e, d);
+        const unsigned long long o = __shfl_xor(w, d);
+        w = o > w ? o : w;
+    }
+    if (lane == 0) part[wave] = e, worst[wave] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int v = 1; v < 16; ++v) {
+            e += part[v];
+            w = worst[v] > w ? worst[v] : w;
+        }
+        VanBand r;
+        const float T = plaid_ord_to_score((uint32_t)(w >> 32)), E = (float)e * 2.0f * 1.001f;
+        if (n_cand[q] <= n_kept[q]) r.lo = r.hi = -INFINITY;                   // (all are kept: every score is above)
+        else if (!(T > -INFINITY && T < INFINITY && E < INFINITY)) r.lo = -INFINITY, r.hi = INFINITY;  // nothing is decided
+        else r.lo = nextafterf(T - E, -INFINITY), r.hi = nextafterf(T + E, INFINITY);
+        band[q] = r;
+    }
+}
+// Sorts the candidates by their coarse keys: kept for sure (sure, best_stride keys of room, counted in state's n_sure), to be scored (their ids to
+// open, counted in n_b), out.  One update of each counter per workgroup and 2048 keys.
+__global__ __launch_bounds__(256) void van_band_kernel(const uint64_t *__restrict__ keys, int64_t key_stride, const int32_t *__restrict__ n_cand,
+                                                       const VanBand *__restrict__ band, Sel2State *state, uint64_t *__restrict__ sure,
+                                                       int64_t sure_stride, int32_t *__restrict__ open, int64_t open_stride)
+{
+    __shared__ int32_t cnt[2][4], base[2];
+    const int q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = n_cand[q];
+    const VanBand b = band[q];
+    const uint64_t *k = keys + (int64_t)q * key_stride;
+    Sel2State *s = state + q;
+    for (int64_t s0 = (int64_t)blockIdx.x * 2048; s0 < n; s0 += (int64_t)gridDim.x * 2048) {  // uniform
+        uint64_t key[8];
+        unsigned long long m[2][8];
+        int mine[2] = {0, 0};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = s0 + 256 * u + threadIdx.x;
+            key[u] = i < n ? k[i] : PLAID_KEY_MAX;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool in = s0 + 256 * u + threadIdx.x < n;
+            const float score = plaid_ord_to_score((uint32_t)(key[u] >> 32));
+            // (a score that is not a number, and an empty one where everything is kept, go with the open and the kept)
+            const bool above = score > b.hi || (b.hi == -INFINITY && b.lo == -INFINITY);
+            m[0][u] = __ballot(in && above);
+            m[1][u] = __ballot(in && !above && !(score < b.lo));
+            mine[0] += __popcll(m[0][u]);
+            mine[1] += __popcll(m[1][u]);
+        }
+        if (lane == 0) cnt[0][wave] = mine[0], cnt[1][wave] = mine[1];
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            int t = 0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) t += cnt[threadIdx.x][w];
+            base[threadIdx.x] = t ? atomicAdd(threadIdx.x == 0 ? &s->n_sure : &s->n_b, t) : 0;
+        }
+        __syncthreads();
+        int at[2] = {base[0], base[1]};
+        for (int w = 0; w < wave; ++w) at[0] += cnt[0][w], at[1] += cnt[1][w];
+        const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int p0 = at[0] + __popcll(m[0][u] & below), p1 = at[1] + __popcll(m[1][u] & below);
+            if (((m[0][u] >> lane) & 1ull) && p0 < sure_stride) sure[(int64_t)q * sure_stride + p0] = key[u];
+            if ((m[1][u] >> lane) & 1ull) open[(int64_t)q * open_stride + p1] = (int32_t)(uint32_t)key[u];
+            at[0] += __popcll(m[0][u]);
+            at[1] += __popcll(m[1][u]);
+        }
+        __syncthreads();
+    }
+}
+// Behind the places of the open ones: the kept ones, with keys that no full score can beat.  n_open, n_all: what is to be scored, and all
+// that the cut chooses from.
+__global__ __launch_bounds__(256) void van_join_kernel(const Sel2State *__restrict__ state, const uint64_t *__restrict__ sure, int64_t sure_stride,
+                                                       uint64_t *__restrict__ keys, int64_t key_stride, int32_t *__restrict__ n_open,
+                                                       int32_t *__restrict__ n_all)
+{
+    const int q = blockIdx.y, open = state[q].n_b, n = state[q].n_sure < sure_stride ? state[q].n_sure : (int)sure_stride;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        n_open[q] = open;
+        n_all[q] = open + n;
+    }
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256)
+        keys[(int64_t)q * key_stride + open + i] = plaid_make_key(INFINITY, (uint32_t)sure[(int64_t)q * sure_stride + i]);
+}
+
+void plaid_launch_vanilla_coarse(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
+                                 const int32_t *codes, const uint8_t *residuals, const float *bucket_weights, int nbits,
+                                 const uint32_t *probebits, int64_t keep_words, int nq, const int32_t *cand, int64_t cand_stride,
+                                 const int32_t *n_cand, int64_t n_upper, int32_t ncandidates, uint64_t *out_keys, int64_t out_stride)
+{
+    // four workgroups per compute unit, four rounds of them
+    int64_t gx = (n_upper + 32 * VP_GROUP - 1) / (32 * VP_GROUP);
+    const int64_t cap = (4 * 1024 + 8 * nq - 1) / (8 * nq);
+    if (gx > cap) gx = cap;
+    const size_t lds = keep_words <= VP_LDS_WORDS ? (size_t)keep_words * 4 : 0;
+#define PLAID_VC_LAUNCH(NB)                                                                                                         \
+    hipLaunchKernelGGL(van_coarse_kernel<NB>, dim3((unsigned)(8 * nq * gx)), dim3(256), lds, st, Q, S, C, doc_offsets, codes, residuals, \
+                       bucket_weights, (const float *)nullptr, (const uint64_t *)nullptr, (int64_t)0, probebits, keep_words, cand,       \
+                       cand_stride, n_cand, ncandidates, nq, (int)gx, 0, out_keys, out_stride)
+    if (nbits == 2) PLAID_VC_LAUNCH(2);
+    else PLAID_VC_LAUNCH(1);
+#undef PLAID_VC_LAUNCH
+}
+void plaid_launch_vanilla_band(hipStream_t st, const float *Q, const float *bucket_weights, int nbits, float centroid_max, int nq, int64_t P,
+                               uint64_t *kept, int64_t kept_stride, const int32_t *n_kept, int32_t *n_cand, uint64_t *keys,
+                               int64_t key_stride, void *band, Sel2State *state, int32_t *open, int64_t open_stride, int32_t *n_open)
+{
+    hipLaunchKernelGGL(van_bounds_kernel, dim3(nq), dim3(1024), 0, st, Q, bucket_weights, nbits, centroid_max, kept, kept_stride, n_kept,
+                       n_cand, (VanBand *)band);
+    const int64_t parts = (P + 2047) / 2048, most = nq >= 16 ? 64 : (nq >= 4 ? 256 : 1024);
+    hipLaunchKernelGGL(van_band_kernel, dim3((unsigned)(parts < most ? parts : most), nq), dim3(256), 0, st, keys, key_stride, n_cand,
+                       (const VanBand *)band, state, kept, kept_stride, open, open_stride);
+    const int64_t joins = (kept_stride + 1023) / 1024;
+    hipLaunchKernelGGL(van_join_kernel, dim3((unsigned)(joins < 64 ? joins : 64), nq), dim3(256), 0, st, state, kept, kept_stride, keys, key_stride,
+                       n_open, n_cand);
 }
 
 void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,

@@ -400,6 +400,17 @@ void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, 
                                 const uint32_t *probebits, int64_t keep_words, int nq, const int32_t *cand, int64_t cand_stride,
                                 const int32_t *n_cand, int64_t n_upper, int32_t ncandidates, uint64_t *out_keys,
                                 int64_t out_stride);
+// The same scores from the leading fp16 terms of query and residuals alone (C <= 2^25).
+void plaid_launch_vanilla_coarse(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
+                                 const int32_t *codes, const uint8_t *residuals, const float *bucket_weights, int nbits,
+                                 const uint32_t *probebits, int64_t keep_words, int nq, const int32_t *cand, int64_t cand_stride,
+                                 const int32_t *n_cand, int64_t n_upper, int32_t ncandidates, uint64_t *out_keys, int64_t out_stride);
+// After the cut of those (kept, n_kept of them): the candidates that the coarse scores leave open (open, n_open) and, in keys behind
+// the places of their full scores, those that are kept whatever these are; n_cand becomes the number of both together.  kept is
+// overwritten.  centroid_max: largest |component| of a centroid; band: 8 bytes per query; state: zero on entry.
+void plaid_launch_vanilla_band(hipStream_t st, const float *Q, const float *bucket_weights, int nbits, float centroid_max, int nq, int64_t P,
+                               uint64_t *kept, int64_t kept_stride, const int32_t *n_kept, int32_t *n_cand, uint64_t *keys,
+                               int64_t key_stride, void *band, Sel2State *state, int32_t *open, int64_t open_stride, int32_t *n_open);
 
 // Small utilities
 void plaid_launch_fill_u32(hipStream_t st, uint32_t *p, int64_t n, uint32_t v);

@@ -1,0 +1,68 @@
+"""Vanilla retrieval that prunes by coarse scores first gives what pruning by full scores gives (the debug form, which returns the kept
+scores, prunes by full ones): many and few candidates, ties at the cut, both code widths, chunks, residual weights below fp16's range."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _index(pl, P, C, nbits, scale, copies, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
+    lengths = torch.randint(0, 30, (P // copies,), generator=g, device="cuda").repeat(copies)
+    offsets = torch.zeros(len(lengths) + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(lengths, 0)
+    N = int(offsets[-1])
+    per = N // copies
+    u = torch.rand(per, generator=g, device="cuda")
+    codes = ((C - 1) * u ** 3).int().repeat(copies)  # some centroids in most passages
+    res = torch.randint(0, 256, (per, 16 * nbits), generator=g, device="cuda", dtype=torch.uint8).repeat(copies, 1)
+    io, ip = pl.plaid_build_ivf(codes, offsets, C)
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": io, "ivf_pids": ip, "residuals": res,
+              "bucket_weights": scale * torch.tensor([-1.5, -0.4, 0.4, 1.5][:1 << nbits] if nbits == 2 else [-0.9, 1.0], device="cuda")}
+    idx = pl.plaid_index_from_view(arrays, nbits, device=0, copy=False)
+    src = torch.randint(0, N, (16 * 32,), generator=g, device="cuda")
+    Q = cen[codes[src].long()] + 0.03 * torch.randn(16 * 32, 128, generator=g, device="cuda")
+    return idx, torch.nn.functional.normalize(Q, dim=1).reshape(16, 32, 128).contiguous(), arrays
+
+
+@pytest.mark.parametrize("P,C,nbits,scale,copies,nprobe,ncand,chunk", [
+    (70_000, 2048, 2, 0.02, 1, 4, 2000, None),
+    (70_000, 2048, 1, 0.02, 1, 2, 17_000, None),
+    (66_000, 1000, 2, 0.02, 3, 1, 1, None),        # every passage three times: ties at the cut
+    (72_000, 1000, 2, 0.1, 4, 3, 4096, 8),         # ... in chunks, which fall below the rule
+    (70_000, 512, 2, 1e-5, 1, 1, 300, None),       # weights that fp16 cannot hold: the coarse scores miss the residuals
+    (140_001, 70_000, 2, 0.02, 1, 1, 9000, None),  # some queries have no more candidates than that
+])
+def test_coarse_pruning_keeps_what_full_scores_keep(P, C, nbits, scale, copies, nprobe, ncand, chunk):
+    import paper_2205_09707_amd as pl
+    idx, Q, arrays = _index(pl, P, C, nbits, scale, copies, P + C)
+    try:
+        if chunk:
+            pl.plaid_set_max_chunk(idx, chunk)
+        k = min(ncand, 500)
+        ids, scores = pl.plaid_search_vanilla(idx, Q, nprobe, ncand, k)
+        want_ids, want_scores, dbg = pl.plaid_search_vanilla(idx, Q, nprobe, ncand, k, debug=True)
+        torch.cuda.synchronize()
+        print("candidates", dbg["n_cand"].tolist())
+        assert torch.equal(ids, want_ids) and torch.equal(scores, want_scores)
+    finally:
+        pl.plaid_index_free(idx)
+
+
+def test_queries_that_are_not_numbers():
+    import paper_2205_09707_amd as pl
+    idx, Q, arrays = _index(pl, 70_000, 2048, 2, 0.02, 1, 5)
+    try:
+        ids, scores = pl.plaid_search_vanilla(idx, Q, 2, 2000, 100)
+        bad = Q.clone()
+        bad[3, 5, 7] = float("nan")
+        bad[9, :, :] = float("inf")
+        got, _ = pl.plaid_search_vanilla(idx, bad, 2, 2000, 100)
+        torch.cuda.synchronize()
+        assert int(got.min()) >= -1 and int(got.max()) < 70_000
+        clean = [q for q in range(16) if q not in (3, 9)]
+        assert torch.equal(got[clean], ids[clean])
+    finally:
+        pl.plaid_index_free(idx)
