@@ -1634,25 +1634,26 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_candidates_kernel, dim3((unsigned)((cand_words + 63) / 64), nq), dim3(64 * IV_WAVES), 0, st, uniq, n_uniq,
                            uniq_stride, ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            wide);
-    // Passages per wave and step: 2048, fewer for indexes of so few passages that a wave's own chain of steps is all that
-    // counts and the chip has room for more waves.  One query of 10 000 passages: 109 / 99 / 90 us per search with 2048 / 512 /
-    // 128, of 60 000: 120 / 114 / 113, of 200 000: 103 / 103 / 122; five of 29 500: 135 / 134 / 120; 64 of 20 000: 185 / 172 /
-    // 196.
+    // Passages per wave and step: 2048, fewer (512 at least) for indexes of so few passages that a wave's own chain of steps is all
+    // that counts and the chip has room for more waves, up to 400 of a query: beyond, what they add to one histogram and score before there is a
+    // threshold costs more.  us per search with 2048 / 1024 / 512 / 256: one query of 10 000 passages 77 / 69 / 65 / 66, of 40 000 73 / 70 /
+    // 70 / 73, of 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 / 129 / 148), of a million
+    // 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of 400 000 120 / 120 / 131 / 151.
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
-    if (ranges <= 40)
-        while (len_log > 7 && (ranges << (12 - len_log)) <= 128 && (waves << (12 - len_log)) <= 2560) --len_log;
+    while (len_log > 9 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
     // An ndocs so large that a wave has several batches to score in any case (one query of 400 000 passages, ndocs 100 000:
     // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
     // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
     while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = s2_steps(nq, waves);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
-    // Passages a wave scores before there is a threshold: all waves of a query together about eight times the m that make
-    // one, between 32 (fewer leave lanes idle) and 64 (more are scored, and counted, for nothing) -- or their share of m,
-    // which has to be scored whatever the bounds say.
-    const int64_t share = ((int64_t)m << len_log) / P, fb = 8 * share < 64 ? 8 * share : 64;
-    const int first_batch = (int)(share > fb ? share : (fb > 32 ? fb : 32));
+    // Passages a wave scores before there is a threshold: 24 (and those that tie with the last of them), which mostly fit a batch of 32 in which
+    // two lanes share a passage, or its share of m, which has to be scored whatever the bounds say.  us per search with 16 / 24 / 32 / 48, one
+    // query: of 40 000 passages (512 per wave) 70 / 70 / 73 / 71, of 100 000 (1024) 83 / 82 / 83 / 83, of 400 000 and ndocs 4096 (1024) 124 / 123 /
+    // 124 / 124; eight times the share, up to 64: 73, 86 and 126.
+    const int64_t share = ((int64_t)m << len_log) / P;
+    const int first_batch = (int)(share > 24 ? share : 24);
     const int64_t blocks = (P + per_block - 1) / per_block;
     // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
     const int64_t words = (nq * cand_words + 7) & ~7ll;
