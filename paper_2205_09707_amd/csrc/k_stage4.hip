@@ -21,6 +21,7 @@
 #include "plaid_internal.h"
 
 #include <math.h>
+#include <stddef.h>
 #include <type_traits>
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -457,21 +458,35 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
 // L / 8 % nq and a share of the (L % 8)-th eighth of its candidates, so that the queries read a passage at about the same
 // time through the same partition's cache (16 queries: the counter of fetches, which sees half of the bytes, shows 17 GB with a grid column per query, 1.2 GB this way).
 // 16 queries of 400 000 candidates: 8.4 -> 4.9 ms, of which listing the tokens takes 1.9 (scalar and vector instructions) and
-// the products 2.0 (matrix instructions 1.7).
+// the products 2.0 (matrix instructions 1.7).  The list holds a token's number itself, unless 32 bits do not hold that (WIDE), and its lanes are taken from the
+// mask as it is: the pruning by coarse scores of 16 queries 3.10 -> 2.84 ms (before: rows within the passage, and its first token per group of eight positions).
+// (Rows of S_cq requested a step ahead: 2.96 -> 3.07 ms, 144 queries of 1024 passages 414 -> 426 us; eight passages at a time: the same; a
+// table entry per half byte in banks of a lane's own, so that look-ups never conflict: 3 to 5 % slower, its reads being twice as many.)
 #define VP_GROUP 4
 #define VP_CAP 288  // listed positions: what is left of the last list (< 32), one chunk of 64 and its padding always fit
 #define VP_SLOTS 16
 #define VP_LDS_WORDS 2048
 #define VP_RESIDENT_BLOCKS 768
-struct VpArea {  // of one wave
+template <bool WIDE>
+struct alignas(16) VpAreaOf {  // of one wave
     int32_t code[VP_CAP];
-    uint32_t row[VP_CAP];       // token within its passage
-    int64_t base[VP_CAP / 8];   // first token of the passage of a group of eight positions
-    int32_t end[VP_CAP / 8];    // slot of the passage that ends with the group, -1
+    uint32_t row[VP_CAP];       // token; WIDE: within its passage
+    int32_t end[VP_CAP / 8];    // slot of the passage that ends with a group of eight positions, -1 (also in the groups not listed yet)
+    int64_t base[WIDE ? VP_CAP / 8 : 1];  // WIDE: first token of a group's passage
     float sums[VP_SLOTS][QLEN + 1];
     int32_t slot_j[VP_SLOTS], slot_pid[VP_SLOTS];
 };
+typedef VpAreaOf<true> VpArea;
+static_assert(offsetof(VpAreaOf<false>, end) % 16 == 0 && sizeof(VpAreaOf<false>) % 16 == 0, "read 16 bytes at a time");
 
+template <int CTRL>
+__device__ __forceinline__ double vp_dpp(double d)  // of another lane
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, d);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 __device__ __forceinline__ void vp_sync()  // orders a wave's LDS accesses
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -479,7 +494,7 @@ __device__ __forceinline__ void vp_sync()  // orders a wave's LDS accesses
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// RN, WIDE: as above.  COARSE (with FILTER): the leading products only, a third of the matrix instructions and half of the table
+// RN: as above; WIDE: 2^25 centroids or 2^32 tokens are not enough.  COARSE (with FILTER): the leading products only, a third of the matrix instructions and half of the table
 // look-ups; every score lies within the bound that van_bounds_kernel computes of the full one.
 template <int NBITS, bool FILTER, bool RN, bool WIDE, bool COARSE>
 __device__ __forceinline__ void maxsim_list_body(
@@ -493,9 +508,9 @@ __device__ __forceinline__ void maxsim_list_body(
     constexpr int RB = 16 * NBITS, RW = 2 * NBITS;
     __shared__ s4_half8 qs[COARSE ? 1 : 2][8][64];  // [term][step][lane]
     __shared__ typename S4Entry<NBITS>::type hlut[COARSE ? 256 : S4_SECOND + 256];
-    __shared__ __attribute__((aligned(16))) VpArea areas[4];
+    __shared__ VpAreaOf<WIDE> areas[4];
     __shared__ __align__(16) float inv_norms[RN ? 4 : 1][RN ? VP_CAP : 1];
-    extern __shared__ uint32_t probe_lds[];  // FILTER: keep_words words, when at most VP_LDS_WORDS
+    extern __shared__ uint32_t probe_lds[];  // FILTER: keep_words words and one of zeros, when at most VP_LDS_WORDS
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int q, bx;
@@ -534,22 +549,27 @@ __device__ __forceinline__ void maxsim_list_body(
     const uint32_t *pb = FILTER ? probebits + (int64_t)q * keep_words : nullptr;
     const bool pb_in_lds = FILTER && keep_words <= VP_LDS_WORDS;
     if (pb_in_lds)
-        for (int w = threadIdx.x; w < (int)keep_words; w += 256) probe_lds[w] = pb[w];
+        for (int w = threadIdx.x; w <= (int)keep_words; w += 256) probe_lds[w] = w < (int)keep_words ? pb[w] : 0u;
     s4_stage_query(Q + (int64_t)q * QLEN * DIM, qs);
     __syncthreads();
-    VpArea &A = areas[wave];
+    VpAreaOf<WIDE> &A = areas[wave];
     float *anf = inv_norms[RN ? wave : 0];
+    if (lane < VP_CAP / 8) A.end[lane] = -1;
     int have = 0;                                // positions listed
     int assigned = 0, completed = 0, summed = 0;  // passages listed, scored, written out
     float m = -INFINITY;                          // the running maximum of the passage at the head of the list
 
-    auto token_at = [&](int at) -> int64_t { return A.base[(at + r32) >> 3] + A.row[at + r32]; };  // of position at + r32
-    auto request = [&](int64_t tok, uint32_t (&r)[RW]) {  // this lane's half of the packed residual of a token
+    typedef typename std::conditional<WIDE, int64_t, uint32_t>::type token_t;
+    auto token_at = [&](int at) -> token_t {  // of position at + r32
+        if constexpr (WIDE) return A.base[(at + r32) >> 3] + A.row[at + r32];
+        else return A.row[at + r32];
+    };
+    auto request = [&](token_t tok, uint32_t (&r)[RW]) {  // this lane's half of the packed residual of a token
         if (NBITS == 2) {
-            const uint4 v = reinterpret_cast<const uint4 *>(residuals + tok * RB)[h];
+            const uint4 v = reinterpret_cast<const uint4 *>(residuals + (uint64_t)tok * RB)[h];
             r[0] = v.x, r[1] = v.y, r[2 % RW] = v.z, r[3 % RW] = v.w;
         } else {
-            const uint2 v = reinterpret_cast<const uint2 *>(residuals + tok * RB)[h];
+            const uint2 v = reinterpret_cast<const uint2 *>(residuals + (uint64_t)tok * RB)[h];
             r[0] = v.x, r[1] = v.y;
         }
     };
@@ -559,7 +579,15 @@ __device__ __forceinline__ void maxsim_list_body(
     };
     auto write_out = [&](int n) {  // the next n <= 8 passages
         vp_sync();
-        if (lane < n) {
+        if constexpr (COARSE) {  // eight lanes a passage: the order of these additions is free
+            const int s = (summed + (lane >> 3)) & (VP_SLOTS - 1);
+            const float *v = &A.sums[s][4 * (lane & 7)];
+            double d = ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
+            d += vp_dpp<0xB1>(d);   // the neighbour, the other pair,
+            d += vp_dpp<0x4E>(d);
+            d += vp_dpp<0x141>(d);  // the other four lanes of the eight
+            if ((lane & 7) == 0 && (lane >> 3) < n) oq[A.slot_j[s]] = plaid_make_key((float)d, (uint32_t)A.slot_pid[s]);
+        } else if (lane < n) {
             const int s = (summed + lane) & (VP_SLOTS - 1);
             double d = 0.0;
 #pragma unroll
@@ -575,7 +603,7 @@ __device__ __forceinline__ void maxsim_list_body(
         int at = 0;
         uint32_t rw[RW];
         int4 cc[4], ends;
-        int64_t tok_next;
+        token_t tok_next;
         if (have < 32) return;  // uniform
         request(token_at(0), rw);
         codes_at(0, cc);
@@ -640,11 +668,15 @@ __device__ __forceinline__ void maxsim_list_body(
             float f = 1.0f;
             if (lane < left) c = A.code[at + lane], r = A.row[at + lane];
             if (RN && lane < left) f = anf[at + lane];
-            if (lane < (left + 7) >> 3) b = A.base[(at >> 3) + lane], e = A.end[(at >> 3) + lane];
+            if (lane < (left + 7) >> 3) {
+                if (WIDE) b = A.base[(at >> 3) + lane];
+                e = A.end[(at >> 3) + lane];
+            }
             vp_sync();
             if (lane < left) A.code[lane] = c, A.row[lane] = r;
             if (RN && lane < left) anf[lane] = f;
-            if (lane < (left + 7) >> 3) A.base[lane] = b, A.end[lane] = e;
+            if (WIDE && lane < (left + 7) >> 3) A.base[lane] = b;
+            if (lane < VP_CAP / 8) A.end[lane] = e;
             have = left;
         }
         // at most 4 + VP_GROUP passages are listed and not written out besides these
@@ -657,11 +689,13 @@ __device__ __forceinline__ void maxsim_list_body(
         const int64_t j = lo + g * VP_GROUP + (lane & (VP_GROUP - 1));
         return j < count ? (FILTER ? cq[j] : (int32_t)ik[2 * j]) : -1;
     };
-    auto wanted = [&](int32_t code) -> unsigned long long {  // the lanes whose token (code >= 0) is scored
-        if (!FILTER) return __ballot(code >= 0);
+    // the code of a lane without a token: one whose bit is never set
+    const int32_t none = pb_in_lds ? 32 * (int32_t)keep_words : -1;
+    auto wanted = [&](int32_t code, int n) -> unsigned long long {  // the lanes whose token is scored, of n tokens
+        if (!FILTER) return n >= 64 ? ~0ull : (n > 0 ? (1ull << n) - 1ull : 0ull);
         const uint32_t w = (uint32_t)code >> 5;
-        const uint32_t bits = code < 0 ? 0u : (pb_in_lds ? probe_lds[w] : pb[w]);
-        return __ballot((bits >> (code & 31)) & 1u);
+        const uint32_t bits = pb_in_lds ? probe_lds[w] : (code < 0 ? 0u : pb[w]);
+        return __ballot(__builtin_amdgcn_ubfe(bits, (uint32_t)code, 1u) != 0u);
     };
     // the first two chunks of 64 codes of a group's passages
     int64_t t0[VP_GROUP];
@@ -675,7 +709,7 @@ __device__ __forceinline__ void maxsim_list_body(
             t0[k] = (int64_t)((uint64_t)hi32 << 32 | lo32);
             len[k] = __builtin_amdgcn_readlane((int)(o1 - o0), k);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) c[k][u] = 64 * u + lane < len[k] ? codes[t0[k] + 64 * u + lane] : -1;
+            for (int u = 0; u < 2; ++u) c[k][u] = 64 * u + lane < len[k] ? codes[t0[k] + 64 * u + lane] : none;
         }
     };
     // the chain id -> token range -> codes is started two groups ahead and advanced one link per group
@@ -692,12 +726,13 @@ __device__ __forceinline__ void maxsim_list_body(
 #pragma unroll
         for (int k = 0; k < VP_GROUP; ++k)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) masks[k][u] = wanted(c[k][u]);
+            for (int u = 0; u < 2; ++u) masks[k][u] = wanted(c[k][u], len[k] - 64 * u);
         int k0 = 0, src0 = 0;  // passage and chunk to go on with
         bool any = false, again;
         int32_t last_code = 0;  // of the last position listed
         uint32_t last_row = 0u;
         float last_nf = 1.0f;
+        const int32_t j_lane = (int32_t)(lo + g * VP_GROUP) + lane;  // of passage `lane` of the group, whose id is in this lane
         do {
             again = false;
 #pragma unroll
@@ -709,8 +744,8 @@ __device__ __forceinline__ void maxsim_list_body(
                     int32_t cc = src == 0 ? c[k][0] : c[k][1];
                     unsigned long long mask = src == 0 ? masks[k][0] : masks[k][1];
                     if (src >= 128) {
-                        cc = src + lane < len[k] ? codes[t0[k] + src + lane] : -1;
-                        mask = wanted(cc);
+                        cc = src + lane < len[k] ? codes[t0[k] + src + lane] : none;
+                        mask = wanted(cc, len[k] - src);
                     }
                     if (!mask) continue;
                     if (have + 72 > VP_CAP) {
@@ -719,26 +754,31 @@ __device__ __forceinline__ void maxsim_list_body(
                         src0 = src;
                         break;
                     }
-                    const int n = __popcll(mask), at = have + __popcll(mask & ((1ull << lane) - 1ull));
-                    if ((mask >> lane) & 1ull) A.code[at] = cc, A.row[at] = (uint32_t)(src + lane);
+                    const bool listed = __builtin_amdgcn_inverse_ballot_w64(mask);
+                    const int n = __popcll(mask);
+                    const int at = FILTER ? (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)have))
+                                          : have + lane;
+                    const uint32_t row0 = WIDE ? (uint32_t)src : (uint32_t)t0[k] + (uint32_t)src;
+                    if (listed) A.code[at] = cc, A.row[at] = row0 + (uint32_t)lane;
                     const int top = 63 - __clzll((long long)mask);
                     last_code = __builtin_amdgcn_readlane(cc, top);
-                    last_row = (uint32_t)(src + top);
+                    last_row = row0 + (uint32_t)top;
                     if (RN) {
                         const float f = src + lane < len[k] ? inv_norm[t0[k] + src + lane] : 0.0f;
-                        if ((mask >> lane) & 1ull) anf[at] = f;
+                        if (listed) anf[at] = f;
                         last_nf = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(f), top));
                     }
-                    const int o = (have >> 3) + lane;
+                    if constexpr (WIDE) {
+                        const int o = (have >> 3) + lane;
+                        if (8 * o < have + n && lane < 9) A.base[o] = t0[k];
+                    }
                     have += n;
-                    if (8 * o < have && lane < 9) A.base[o] = t0[k], A.end[o] = -1;
                     any = true;
                 }
                 if (again) continue;
                 src0 = 0;
-                const int32_t p = __builtin_amdgcn_readlane(pid, k);
                 if (!any) {  // uniform
-                    if (lane == 0) oq[j] = plaid_make_key(-INFINITY, (uint32_t)p);
+                    if (lane == k) oq[j] = plaid_make_key(-INFINITY, (uint32_t)pid);
                     continue;
                 }
                 any = false;
@@ -747,10 +787,10 @@ __device__ __forceinline__ void maxsim_list_body(
                 if (RN && lane < fill) anf[have + lane] = last_nf;
                 have += fill;
                 const int slot = assigned++ & (VP_SLOTS - 1);
-                if (lane == 0) {
+                if (lane == k) {
                     A.end[(have >> 3) - 1] = slot;
-                    A.slot_j[slot] = (int32_t)j;
-                    A.slot_pid[slot] = p;
+                    A.slot_j[slot] = j_lane;
+                    A.slot_pid[slot] = pid;
                 }
             }
             if (!again) {  // the next group's codes, before the steps
@@ -762,10 +802,10 @@ __device__ __forceinline__ void maxsim_list_body(
                 vp_sync();
                 const int32_t lc = A.code[0];
                 const uint32_t lr = A.row[0];
-                const int64_t lb = A.base[0];
+                const int64_t lb = WIDE ? A.base[0] : 0;
                 if (have + lane < 32) A.code[have + lane] = lc, A.row[have + lane] = lr;
                 if (RN && have + lane < 32) anf[have + lane] = 1.0f;
-                if ((have >> 3) + lane < 4) A.base[(have >> 3) + lane] = lb, A.end[(have >> 3) + lane] = -1;
+                if (WIDE && (have >> 3) + lane < 4) A.base[(have >> 3) + lane] = lb;
                 have = 32;
             }
             if (have >= 32) drain();
@@ -936,7 +976,7 @@ void plaid_launch_vanilla_coarse(hipStream_t st, const float *Q, const float *S,
     int64_t gx = (n_upper + 32 * VP_GROUP - 1) / (32 * VP_GROUP);
     const int64_t cap = (4 * 1024 + 8 * nq - 1) / (8 * nq);
     if (gx > cap) gx = cap;
-    const size_t lds = keep_words <= VP_LDS_WORDS ? (size_t)keep_words * 4 : 0;
+    const size_t lds = keep_words <= VP_LDS_WORDS ? (size_t)keep_words * 4 + 4 : 0;
 #define PLAID_VC_LAUNCH(NB)                                                                                                         \
     hipLaunchKernelGGL(van_coarse_kernel<NB>, dim3((unsigned)(8 * nq * gx)), dim3(256), lds, st, Q, S, C, doc_offsets, codes, residuals, \
                        bucket_weights, (const float *)nullptr, (const uint64_t *)nullptr, (int64_t)0, probebits, keep_words, cand,       \
@@ -959,7 +999,7 @@ void plaid_launch_vanilla_band(hipStream_t st, const float *Q, const float *buck
                        n_open, n_cand);
 }
 
-void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
+void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets,
                                 const int32_t *codes, const uint8_t *residuals, const float *bucket_weights, int nbits,
                                 const uint32_t *probebits, int64_t keep_words, int nq, const int32_t *cand, int64_t cand_stride,
                                 const int32_t *n_cand, int64_t n_upper, int32_t ncandidates, uint64_t *out_keys,
@@ -970,13 +1010,13 @@ void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, 
     int64_t gx = (n_upper + 32 * VP_GROUP - 1) / (32 * VP_GROUP);
     const int64_t cap = (4 * VP_RESIDENT_BLOCKS + 8 * nq - 1) / (8 * nq);
     if (gx > cap) gx = cap;
-    const size_t lds = keep_words <= VP_LDS_WORDS ? (size_t)keep_words * 4 : 0;
+    const size_t lds = keep_words <= VP_LDS_WORDS ? (size_t)keep_words * 4 + 4 : 0;
 #define PLAID_VP_LAUNCH(NB, WIDE)                                                                                              \
     hipLaunchKernelGGL((maxsim_list_kernel<NB, true, false, WIDE>), dim3((unsigned)(8 * nq * gx)), dim3(256), lds, st, Q, S, C, \
                        doc_offsets, codes, residuals, bucket_weights, (const float *)nullptr, (const uint64_t *)nullptr,       \
                        (int64_t)0, probebits, keep_words, cand, cand_stride, n_cand, ncandidates, nq, (int)gx, 0, out_keys,     \
                        out_stride)
-    const bool wide = C > (1ll << 25);
+    const bool wide = plaid_wide(C, N);
     if (nbits == 2) {
         if (wide) PLAID_VP_LAUNCH(2, true);
         else PLAID_VP_LAUNCH(2, false);
@@ -997,7 +1037,7 @@ void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, 
 // and 162 / 153.
 static constexpr bool s4_packed(int n_upper, int nq) { return n_upper >= 96 && (int64_t)n_upper * nq >= 48ll * VP_RESIDENT_BLOCKS; }
 
-void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
+void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets,
                                     const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                     int nbits, int nq, const uint64_t *in_keys, int64_t in_stride,
                                     const int32_t *in_counts, int n_upper, uint64_t *out_keys, int64_t out_stride,
@@ -1016,7 +1056,7 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
     const int64_t slots = spread ? nq : 8 * (((int64_t)nq + 7) / 8);  // query slots of the one-dimensional grid
     if (slots * gx > (1ll << 23)) gx = (int)((1ll << 23) / slots);  // (the waves stride over longer lists)
     if (gx < 1) gx = 1;
-    const bool wide = C > (1ll << 25);
+    const bool wide = plaid_wide(C, N);
 #define PLAID_S4_LAUNCH(NB, CO, RN, WIDE)                                                                                 \
     hipLaunchKernelGGL((decompress_maxsim_kernel<NB, CO, RN, WIDE>), dim3((unsigned)(slots * gx)), dim3(256), 0, st, Q, S, C,      \
                        doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, in_counts, nq, gx,       \

@@ -879,7 +879,7 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         plaid_launch_select(st, w.keys3, pl.nd, w.n2, n, pl.nd, pl.m3, w.sel3, pl.m3, w.n3, 0, sc3, 0);
         STAMP();
         // stage 4: decompression (Section 4.5) + exact MaxSim (Eq. 1), best k
-        plaid_launch_decompress_maxsim(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights,
+        plaid_launch_decompress_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights,
                                        ix->nbits, n, w.sel3, pl.m3, w.n3, pl.m3, w.keys4, pl.m3,
                                        ix->renormalize ? ix->inv_norm : nullptr);
         STAMP();
@@ -1059,7 +1059,7 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
                                         qmask, (uint32_t *)w.s2.qcount + 4);
         plaid_launch_bitmap_to_list(st, w.candbits, w.cand_words, P, n, cand, P, w.n2);
         // more than ncandidates: scored on the embeddings of the probed lists alone, the best ncandidates stay
-        if (!dbg && vanilla_screens(n, P, pl.nd) && ix->scq_form == PLAID_SCQ_SPLIT16 && C <= (1ll << 25)) {
+        if (!dbg && vanilla_screens(n, P, pl.nd) && ix->scq_form == PLAID_SCQ_SPLIT16 && !plaid_wide(C, ix->N)) {
             // coarsely first, and in full where that does not decide (the caller who asks for the kept scores gets full ones)
             int32_t *open = cand + (int64_t)n * P;  // [n][P], the rest of the boundary list's memory
             plaid_launch_vanilla_coarse(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,
@@ -1068,14 +1068,14 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
             plaid_launch_vanilla_band(st, Qc, ix->weights, ix->nbits, ix->centroid_max, n, P, w.sel2, pl.nd, w.n3, w.n2, w.keys2, P, w.s2.meta,
                                       w.s2.state, open, P, w.n_out);
             plaid_launch_fill_u32(st, (uint32_t *)scp.state, (int64_t)(plaid_select_zero_bytes(n) / 4), 0u);
-            plaid_launch_vanilla_prune(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,
+            plaid_launch_vanilla_prune(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,
                                        w.keep_words, n, open, P, w.n_out, P, -1, w.keys2, P);
         } else
-            plaid_launch_vanilla_prune(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,
+            plaid_launch_vanilla_prune(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,
                                    w.keep_words, n, cand, P, w.n2, P, pl.nd, w.keys2, P);
         plaid_launch_select(st, w.keys2, P, w.n2, n, P, pl.nd, w.sel2, pl.nd, w.n3, 0, scp, 0);
         // every token of every remaining candidate: decompression + exact MaxSim (Section 3.2, Eq. 1), best k
-        plaid_launch_decompress_maxsim(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, n,
+        plaid_launch_decompress_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, n,
                                        w.sel2, pl.nd, w.n3, pl.nd, w.keys4, pl.m3);
         if (pl.m3 <= SEL_SORT_CAP) {
             plaid_launch_rank_output(st, w.keys4, pl.m3, w.n3, n, pl.m3, k, out_ids + (int64_t)q0 * k, out_scores + (int64_t)q0 * k);

@@ -354,8 +354,10 @@ void plaid_launch_ci_list(hipStream_t st, const float *S, int64_t C, const int64
                           int nq, const uint64_t *in_keys, int64_t in_stride, const int32_t *in_counts, int n_upper,
                           uint64_t *out_keys, int64_t out_stride);
 
+// Offsets of rows of S_cq, or numbers of tokens, that 32 bits do not hold: stage 4's kernels have a form for those.
+static constexpr bool plaid_wide(int64_t C, int64_t N) { return C > (1ll << 25) || N > (1ll << 32); }
 // Section 4.5 + Eq. 1 over a key list (stage 4); S = this chunk's S_cq, whose rows supply the centroids' share.
-void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
+void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets,
                                     const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                     int nbits, int nq, const uint64_t *in_keys, int64_t in_stride,
                                     const int32_t *in_counts, int n_upper, uint64_t *out_keys, int64_t out_stride,
@@ -395,7 +397,7 @@ void plaid_launch_vanilla_candidates(hipStream_t st, const int32_t *uniq, const 
                                      const int32_t *codes, int64_t P, int64_t N, int64_t C, uint32_t *qmask, uint32_t *work);
 // out_keys[q][j] = key of candidate cand[q][j] scored on the embeddings of the probed lists alone (score 0 for every
 // candidate of a query with at most ncandidates of them).
-void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, const int64_t *doc_offsets,
+void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets,
                                 const int32_t *codes, const uint8_t *residuals, const float *bucket_weights, int nbits,
                                 const uint32_t *probebits, int64_t keep_words, int nq, const int32_t *cand, int64_t cand_stride,
                                 const int32_t *n_cand, int64_t n_upper, int32_t ncandidates, uint64_t *out_keys,

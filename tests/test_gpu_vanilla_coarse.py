@@ -66,3 +66,22 @@ def test_queries_that_are_not_numbers():
         assert torch.equal(got[clean], ids[clean])
     finally:
         pl.plaid_index_free(idx)
+
+
+@pytest.mark.parametrize("nbits", [1, 2])
+def test_passages_around_the_chunks_of_a_list(nbits):
+    """Lists that end within a group of eight, a step of 32 and a chunk of 64 tokens, and passages that fill a wave's list by themselves."""
+    import paper_2205_09707_amd as pl
+    import test_gpu_maxsim_lists as lists
+    P = 52_000
+    idx, a, g = lists._index(pl, P, 300, nbits, 11 + nbits)
+    try:
+        Q = torch.nn.functional.normalize(torch.randn(16, 32, 128, generator=g, device="cuda"), dim=2).contiguous()
+        for nprobe, ncand in [(1, 7), (4, 13_000)]:
+            got = pl.plaid_search_vanilla(idx, Q, nprobe, ncand, min(ncand, 500))
+            want = pl.plaid_search_vanilla(idx, Q, nprobe, ncand, min(ncand, 500), debug=True)
+            torch.cuda.synchronize()
+            print("candidates", want[2]["n_cand"].tolist())
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    finally:
+        pl.plaid_index_free(idx)
