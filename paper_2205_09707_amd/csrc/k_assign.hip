@@ -82,16 +82,6 @@ __global__ __launch_bounds__(256) void asg_stats_kernel(const float *__restrict_
     }
 }
 
-// fmaxf without the canonicalising instruction the compiler puts in front of it for an operand it has not computed as a float:
-// 64 of the 281 per group of 32 vectors below, 117 000 vectors against 32 768 centroids 1028 -> 983 us.  (A score that is not a number or infinite comes from a vector whose bound is not
-// finite either, and every row of such a vector is looked at whatever is reported here.)
-__device__ __forceinline__ float asg_max(float a, float b)
-{
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 // LDS-only barrier: the operands requested for the next group but one stay in flight across it.
 __device__ __forceinline__ void asg_lds_barrier()
 {
@@ -103,8 +93,10 @@ __device__ __forceinline__ void asg_lds_barrier()
 // Grid: x = block of 512 centroids, y = range of qg groups of 32 vectors.  A wave keeps the operands of its 128 rows in
 // registers (four tiles: each operand of a group read from LDS feeds four matrix instructions) and walks the groups, whose
 // 8 KB of operands pass through LDS, double-buffered.  Per group it reports, for every vector, its best row's score --
-// with the row's number in the seven lowest bits -- and the second best one: three vector instructions per score, issued
-// under the other wave's matrix instructions.  best2[group][ceil(C / 128)][32].
+// with the row's number in the seven lowest bits -- and the second best one: three vector instructions per score, between the matrix
+// instructions of the same wave: the scores of two tiles while the products of the other two are formed, eight vector
+// instructions (of 4 cycles) to a matrix instruction (of 32).  117 000 vectors against 32 768 centroids 986 us with the choice after a
+// group's products, where only the other wave's hide it, 917 this way.  best2[group][ceil(C / 128)][32].
 template <bool WHOLE>
 __device__ __forceinline__ void asg_screen_body(asg_half8 (&Bs)[2][ASG_TILE_VEC], const asg_half8 *__restrict__ A, int64_t C,
                                                 int64_t tile0, const asg_half8 *__restrict__ B, int g_begin, int g_end,
@@ -131,19 +123,73 @@ __device__ __forceinline__ void asg_screen_body(asg_half8 (&Bs)[2][ASG_TILE_VEC]
     asg_lds_barrier();
     const int64_t blk = tile0 / ASG_NT;
     const int rows = C - tile0 * 32 < ASG_ROWS ? (int)(C - tile0 * 32) : ASG_ROWS;  // (not positive: a block past the end)
-    for (int g = g_begin; g < g_end; ++g) {
-        const asg_half8 *buf = Bs[(g - g_begin) & 1];
-        asg_floatx16 acc[ASG_NT];
+    // A maximum is the median with infinity, in a register the compiler knows nothing of: fmaxf costs a canonicalising instruction for an
+    // operand that was not computed as a float.  (A score that is not a number or infinite comes from a vector whose bound is not finite
+    // either, and every row of such a vector is looked at whatever is reported here.)
+    float inf;
+    asm volatile("s_mov_b32 %0, 0x7f800000" : "=s"(inf));
+    asg_floatx16 acc[ASG_NT];
 #pragma unroll
-        for (int t = 0; t < ASG_NT; ++t)
+    for (int t = 0; t < ASG_NT; ++t)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+    float m1 = -INFINITY, m2 = -INFINITY;
+    // the matrix work of tiles half, half + 1 for a group, with the choice among the scores of the other two tiles between its instructions
+    auto step = [&](const asg_half8 *buf, auto half_) {
+        constexpr int half = decltype(half_)::value, other = 2 - half;
+        int lim = rows - 4 * h;
+        if (!WHOLE) asm volatile("" : "+v"(lim));  // or 64 lane masks would be formed ahead of the loop and kept
+        asg_floatx16 n[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) n[t][v] = 0.f;
 #pragma unroll
         for (int s = 0; s < ASG_STEPS; ++s) {
             const asg_half8 b = buf[s * 64 + lane];
 #pragma unroll
-            for (int t = 0; t < ASG_NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[t][s], b, acc[t], 0, 0, 0);
+            for (int t = 0; t < 2; ++t) n[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[half + t][s], b, n[t], 0, 0, 0);
         }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int t = other + u;
+            float t1 = -INFINITY, t2 = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = 8 * (v >> 2) + (v & 3);  // row 32 t + r + 4 h of the block
+                float x = __uint_as_float((__float_as_uint(acc[t][v]) & ~127u) | (uint32_t)r);
+                if (!WHOLE && 32 * t + r >= lim) x = -INFINITY;
+                t2 = __builtin_amdgcn_fmed3f(t1, t2, x);
+                t1 = __builtin_amdgcn_fmed3f(t1, x, inf);
+            }
+            if (t1 > -INFINITY) t1 = __uint_as_float(__float_as_uint(t1) | (uint32_t)(32 * t));
+            m2 = fmaxf(fmaxf(m2, t2), fminf(m1, t1));
+            m1 = fmaxf(m1, t1);
+        }
+        asm volatile("" : "+v"(m1), "+v"(m2));  // (here, or the choice sinks below to where its result is used)
+        __builtin_amdgcn_sched_barrier(0);
+        acc[half] = n[0];
+        acc[half + 1] = n[1];
+    };
+    auto finish = [&]() {  // m1, m2: over both halves of the wave
+        if (m1 > -INFINITY) m1 = __uint_as_float(__float_as_uint(m1) | (uint32_t)(4 * h));
+        const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32);
+        m2 = fmaxf(fmaxf(m2, o2), fminf(m1, o1));
+        m1 = fmaxf(m1, o1);
+    };
+    auto report = [&](int g, float r1, float r2) {
+        if (h == 0 && rows > 0) best2[((int64_t)g * n_blk + blk) * 32 + lane] = make_float2(r1, r2);
+    };
+    struct lower { enum { value = 0 }; };
+    struct upper { enum { value = 2 }; };
+    for (int g = g_begin; g < g_end; ++g) {
+        const asg_half8 *buf = Bs[(g - g_begin) & 1];
+        step(buf, lower());
+        finish();
+        const float r1 = m1, r2 = m2;  // of the group before
+        m1 = m2 = -INFINITY;
+        step(buf, upper());
+        if (g > g_begin) report(g - 1, r1, r2);
         asg_half8 *nxt = Bs[(g - g_begin + 1) & 1];
         if (g + 1 < g_end) {
 #pragma unroll
@@ -154,28 +200,12 @@ __device__ __forceinline__ void asg_screen_body(asg_half8 (&Bs)[2][ASG_TILE_VEC]
 #pragma unroll
             for (int k = 0; k < NPRE; ++k) pre[k] = src[k * ASG_THREADS];
         }
-        float m1 = -INFINITY, m2 = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < ASG_NT; ++t) {
-            float t1 = -INFINITY, t2 = -INFINITY;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 8 * (v >> 2) + (v & 3);  // row 32 t + r + 4 h of the block
-                float x = __uint_as_float((__float_as_uint(acc[t][v]) & ~127u) | (uint32_t)r);
-                if (!WHOLE && 32 * t + r + 4 * h >= rows) x = -INFINITY;
-                t2 = __builtin_amdgcn_fmed3f(t1, t2, x);
-                t1 = asg_max(t1, x);
-            }
-            if (t1 > -INFINITY) t1 = __uint_as_float(__float_as_uint(t1) | (uint32_t)(32 * t));
-            m2 = fmaxf(fmaxf(m2, t2), fminf(m1, t1));
-            m1 = fmaxf(m1, t1);
-        }
-        if (m1 > -INFINITY) m1 = __uint_as_float(__float_as_uint(m1) | (uint32_t)(4 * h));
-        const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32);
-        m2 = fmaxf(fmaxf(m2, o2), fminf(m1, o1));
-        m1 = fmaxf(m1, o1);
-        if (h == 0 && rows > 0) best2[((int64_t)g * n_blk + blk) * 32 + lane] = make_float2(m1, m2);
         asg_lds_barrier();  // publishes nxt; every wave is done reading buf
+    }
+    if (g_begin < g_end) {  // the upper tiles' scores of the last group
+        step(Bs[(g_end - 1 - g_begin) & 1], lower());
+        finish();
+        report(g_end - 1, m1, m2);
     }
 }
 __global__ __launch_bounds__(ASG_THREADS, 2) void asg_screen_kernel(const asg_half8 *__restrict__ A, int64_t C,
