@@ -156,23 +156,25 @@ __device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_
 // Residual dot products of 32 tokens (packed words rw, this half's) with the 32 query tokens: acc += leading products, acx +=
 // cross terms, scaled by 2^11.  TOKENS_A: rows = tokens, columns = query tokens; else the other way round.  The query
 // operands are read from LDS in every step, through an index the compiler cannot tell from the last call's (kept across
-// calls they would take 64 registers).  AHEAD: they and the table entries are requested one step of 16 dimensions ahead, for
+// calls they would take 64 registers), but for the first H1 of the leading and H2 of the trailing terms, which the caller holds.  AHEAD: they and the table entries are requested one step of 16 dimensions ahead, for
 // which a kernel of four waves per SIMD lacks the registers.
-template <int NBITS, bool TOKENS_A, bool AHEAD>
+template <int NBITS, bool TOKENS_A, bool AHEAD, int H1, int H2>
 __device__ __forceinline__ void s4_products(const uint32_t (&rw)[2 * NBITS], const typename S4Entry<NBITS>::type *hlut,
-                                            const s4_half8 (&qs)[2][8][64], int lane, floatx16 &acc, floatx16 &acx)
+                                            const s4_half8 (&qs)[2][8][64], const s4_half8 *held1, const s4_half8 *held2, int lane, floatx16 &acc, floatx16 &acx)
 {
     int ql = lane;
     asm volatile("" : "+v"(ql));
-    s4_half8 a1, a2, q1 = qs[0][0][ql], q2 = qs[1][0][ql];
+    auto first = [&](int s) { return s < H1 ? held1[s] : qs[0][s][ql]; };
+    auto second = [&](int s) { return s < H2 ? held2[s] : qs[1][s][ql]; };
+    s4_half8 a1, a2, q1 = first(0), q2 = second(0);
     s4_decode<NBITS>(rw, 0, hlut, a1, a2);
     if (AHEAD) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
         s4_half8 n1 = a1, n2 = a2, r1 = q1, r2 = q2;
         if (s < 7) {
-            r1 = qs[0][s + 1][ql];
-            r2 = qs[1][s + 1][ql];
+            r1 = first(s + 1);
+            r2 = second(s + 1);
             s4_decode<NBITS>(rw, s + 1, hlut, n1, n2);
         }
         acx = TOKENS_A ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, q2, acx, 0, 0, 0)
@@ -183,7 +185,10 @@ __device__ __forceinline__ void s4_products(const uint32_t (&rw)[2 * NBITS], con
                        : __builtin_amdgcn_mfma_f32_32x32x16_f16(q1, a2, acx, 0, 0, 0);
         if (AHEAD && s < 7) {
             __builtin_amdgcn_sched_group_barrier(0x002, NBITS, 0);              // the addresses,
-            __builtin_amdgcn_sched_group_barrier(0x100, NBITS == 2 ? 6 : 4, 0);  // LDS reads, then the matrix instructions
+            // LDS reads, then the matrix instructions
+            if (s + 1 < H1 && s + 1 < H2) __builtin_amdgcn_sched_group_barrier(0x100, NBITS == 2 ? 4 : 2, 0);
+            else if (s + 1 < H1 || s + 1 < H2) __builtin_amdgcn_sched_group_barrier(0x100, NBITS == 2 ? 5 : 3, 0);
+            else __builtin_amdgcn_sched_group_barrier(0x100, NBITS == 2 ? 6 : 4, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
         }
         a1 = n1, a2 = n2, q1 = r1, q2 = r2;
@@ -192,9 +197,9 @@ __device__ __forceinline__ void s4_products(const uint32_t (&rw)[2 * NBITS], con
 }
 
 // The leading products alone, rows = tokens.
-template <int NBITS>
+template <int NBITS, int H1>
 __device__ __forceinline__ void s4_leading_products(const uint32_t (&rw)[2 * NBITS], const typename S4Entry<NBITS>::type *hlut,
-                                                    const s4_half8 (&qs)[8][64], int lane, floatx16 &acc)
+                                                    const s4_half8 (&qs)[8][64], const s4_half8 *held1, int lane, floatx16 &acc)
 {
     auto decode = [&](int s) -> s4_half8 {
         if constexpr (NBITS == 2) {
@@ -207,12 +212,13 @@ __device__ __forceinline__ void s4_leading_products(const uint32_t (&rw)[2 * NBI
     };
     int ql = lane;
     asm volatile("" : "+v"(ql));
-    s4_half8 a = decode(0), q = qs[0][ql];
+    auto first = [&](int s) { return s < H1 ? held1[s] : qs[s][ql]; };
+    s4_half8 a = decode(0), q = first(0);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
         s4_half8 n = a, r = q;
         if (s < 7) {
-            r = qs[s + 1][ql];
+            r = first(s + 1);
             n = decode(s + 1);
         }
         acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, q, acc, 0, 0, 0);
@@ -389,7 +395,7 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
             }
             floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // cross terms, scaled by 2^11
-            s4_products<NBITS, false, COOP>(rw, hlut, qs, lane, acc, acx);
+            s4_products<NBITS, false, COOP, 0, 0>(rw, hlut, qs, nullptr, nullptr, lane, acc, acx);
             const float svf[16] = {sv[0].x, sv[0].y, sv[0].z, sv[0].w, sv[1].x, sv[1].y, sv[1].z, sv[1].w,
                                    sv[2].x, sv[2].y, sv[2].z, sv[2].w, sv[3].x, sv[3].y, sv[3].z, sv[3].w};
             if (base + 32 <= len) {  // (uniform) a full step: every column counts
@@ -552,6 +558,15 @@ __device__ __forceinline__ void maxsim_list_body(
         for (int w = threadIdx.x; w <= (int)keep_words; w += 256) probe_lds[w] = w < (int)keep_words ? pb[w] : 0u;
     s4_stage_query(Q + (int64_t)q * QLEN * DIM, qs);
     __syncthreads();
+    // The query's operands that fit the registers beside the rest, at three waves per SIMD (COARSE: four), are read from LDS once: reads
+    // of LDS, the busiest unit, bound the steps.  512 queries of 256 passages 345 us with none held, 334 with the leading terms, 329 so;
+    // 144 of 1024 391, 378, 374; the coarse scores of 16 queries 2.77 ms with none, 2.70.  (All of them, at two waves: 380, 411.)
+    constexpr int H1 = COARSE ? (NBITS == 2 ? 6 : 5) : 8, H2 = COARSE ? 0 : (RN ? 1 : 3);
+    s4_half8 held1[H1 ? H1 : 1], held2[H2 ? H2 : 1];
+#pragma unroll
+    for (int s = 0; s < H1; ++s) held1[s] = qs[0][s][lane];
+#pragma unroll
+    for (int s = 0; s < H2; ++s) held2[s] = qs[COARSE ? 0 : 1][s][lane];
     VpAreaOf<WIDE> &A = areas[wave];
     float *anf = inv_norms[RN ? wave : 0];
     if (lane < VP_CAP / 8) A.end[lane] = -1;
@@ -626,8 +641,8 @@ __device__ __forceinline__ void maxsim_list_body(
             request(tok_next, rw_next);  // (past the last step: some token of the list again, not used)
             floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // cross terms, scaled by 2^11
-            if constexpr (COARSE) s4_leading_products<NBITS>(rw, hlut, qs[0], lane, acc);
-            else s4_products<NBITS, true, true>(rw, hlut, qs, lane, acc, acx);
+            if constexpr (COARSE) s4_leading_products<NBITS, H1>(rw, hlut, qs[0], held1, lane, acc);
+            else s4_products<NBITS, true, true, H1, H2>(rw, hlut, qs, held1, held2, lane, acc, acx);
             const int32_t end[4] = {ends.x, ends.y, ends.z, ends.w};
             const int next = have - at >= 64 ? at + 32 : at;
             codes_at(next, cc);
