@@ -389,6 +389,18 @@ bool plaid_scq16_takes_queries(int64_t C, int nq, int64_t zero_words)
 {
     return nq == 1 && zero_words <= 32 * H16_THREADS * ((C + 32 * H16_WG_TILES - 1) / (32 * H16_WG_TILES));
 }
+// Queries per workgroup, which walks them one after the other: with few workgroups that chain is the launch's time, with many its centroid operands
+// should be loaded for as many queries as leave the chip filled several times over.  Up to 512 workgroups of one query run at once.
+// us of a launch with 1 / 2 / 4 / 8 queries per workgroup: 8 queries of 1024 centroids 7 / 11 / 17 / 27, 200 17 / 15 / 18 / 29; 23 of 10 007
+// 16 / 14 / 17 / 28, 50 28 / 25 / 24 / 31; 4 of 32 768 10 / 12 / 17 / 17, 9 20 / 17 / 19 / 30, 40 64 / 53 / 50 / 55; 8 of 65 536 32 / 26 / 25 / 33, 16 58 / 48 /
+// 42 / 43; 6 of 262 144 143 / 105 / 79 / 60; 256 of 16 384 189 / 156 / 141 / 138.
+static constexpr int scq16_queries(int64_t nq, int64_t gx)
+{
+    const int64_t work = nq * gx, full = (work + 2047) / 2048, half = (work + 1023) / 1024, once = (work + 511) / 512;
+    int64_t qg = once < 4 ? once : half < 4 ? 4 : half < 8 ? half : full < 8 ? 8 : full < 64 ? full : 64;
+    if (qg > nq) qg = nq;
+    return (int)(qg < 1 ? 1 : qg);
+}
 void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *B16, int nq, float t_cs, float *S,
                         uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax, float *groupmax,
                         unsigned long long *clocks, const float *Q, uint32_t *zero, int64_t zero_words)
@@ -401,12 +413,7 @@ void plaid_launch_scq16(hipStream_t st, const void *A16, int64_t C, const void *
         t_hi = nextafterf(t_cs + PLAID_SCQ16_EPS, INFINITY);
     }
     const unsigned gx = (unsigned)((C + 32 * H16_WG_TILES - 1) / (32 * H16_WG_TILES));
-    // queries per workgroup: enough workgroups to fill the chip several times over, yet many queries per workgroup, since
-    // its centroid operands are loaded once
-    int qg = (int)(((int64_t)nq * gx + 2047) / 2048);
-    if (qg < 8) qg = 8;
-    if (qg > 64) qg = 64;
-    if (qg > nq) qg = nq;
+    const int qg = scq16_queries(nq, gx);
     const unsigned gy = (unsigned)((nq + qg - 1) / qg);
 #define PLAID_SCQ16_LAUNCH(GR)                                                                                                \
     hipLaunchKernelGGL((scq16_kernel<H16_NT, GR>), dim3(gx, gy), dim3(H16_THREADS), 0, st, (const scq16_half8 *)A16, C,        \
