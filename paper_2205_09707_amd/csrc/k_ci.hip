@@ -88,20 +88,17 @@ __device__ __forceinline__ float4 ci_passage(const float *__restrict__ Sq, int64
 // on one partition and the rows its passages share (a query's passages name the same frequent centroids over and over)
 // are fetched into that cache once.  With fewer than eight queries (spread) a query's workgroups go to all partitions.
 //
-// A wave takes CI_PPW consecutive passages at a time: their ids, then their token ranges, then their first 64 codes are
+// A wave takes G consecutive passages at a time: their ids, then their token ranges, then their first 64 codes are
 // requested together, so that the chain of dependent loads in front of the row gathers is paid once per group.  The
 // lanes' partial maxima meet in LDS (wave-private areas, no workgroup barrier): lane t < 32 takes the maximum of query
 // token t over the eight token classes, and when the group is done lane a adds up the 32 maxima of passage a -- one
 // chain of additions for the whole group.
-template <bool WIDE>
-__global__ __launch_bounds__(256) void ci_list_kernel(const float *__restrict__ S, int64_t C,
-                                                      const int64_t *__restrict__ doc_offsets,
-                                                      const int32_t *__restrict__ codes,
-                                                      const uint64_t *__restrict__ in_keys, int64_t in_stride,
-                                                      const int32_t *__restrict__ in_counts, int nq, int gx, int spread,
-                                                      uint64_t *__restrict__ out_keys, int64_t out_stride)
+template <bool WIDE, int G>
+__device__ __forceinline__ void ci_list_body(const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
+                                             const int32_t *__restrict__ codes, const uint64_t *__restrict__ in_keys, int64_t in_stride,
+                                             const int32_t *__restrict__ in_counts, int nq, int gx, int spread,
+                                             uint64_t *__restrict__ out_keys, int64_t out_stride)
 {
-    constexpr int G = CI_PPW;
     __shared__ __align__(16) float part_max[4][8][QLEN];  // [wave][token class r][query token]
     __shared__ __align__(16) float col_max[4][G][QLEN];   // [wave][passage of the group][query token]
     int q, x;
@@ -175,6 +172,26 @@ __global__ __launch_bounds__(256) void ci_list_kernel(const float *__restrict__ 
         }
     }
 }
+template <bool WIDE>
+__global__ __launch_bounds__(256) void ci_list_kernel(const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
+                                                      const int32_t *__restrict__ codes, const uint64_t *__restrict__ in_keys, int64_t in_stride,
+                                                      const int32_t *__restrict__ in_counts, int nq, int gx, int spread,
+                                                      uint64_t *__restrict__ out_keys, int64_t out_stride)
+{
+    ci_list_body<WIDE, CI_PPW>(S, C, doc_offsets, codes, in_keys, in_stride, in_counts, nq, gx, spread, out_keys, out_stride);
+}
+// Launches that are over in two rounds of waves: a passage each, so that none waits for another; more waves than that gain from the shared
+// chain of loads.  us of a launch with two / one, 30 to 90 tokens: one query of 256 passages 6.6 / 5.1, of 1024 6.6 / 4.9, of 4096 7.2 / 6.0, four of 1024
+// 7.8 / 6.3, eight 9.2 / 8.6, sixteen 15.8 / 14.5, 64 of 256 16.6 / 15.3, 23 of 1000 (8 to 180 tokens) 19.6 / 19.7, 256 of 256 47.9 / 49.7.
+template <bool WIDE>
+__global__ __launch_bounds__(256) void ci_few_kernel(const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
+                                                      const int32_t *__restrict__ codes, const uint64_t *__restrict__ in_keys, int64_t in_stride,
+                                                      const int32_t *__restrict__ in_counts, int nq, int gx, int spread,
+                                                      uint64_t *__restrict__ out_keys, int64_t out_stride)
+{
+    ci_list_body<WIDE, 1>(S, C, doc_offsets, codes, in_keys, in_stride, in_counts, nq, gx, spread, out_keys, out_stride);
+}
+#define CI_FEW 16384
 
 void plaid_launch_ci_list(hipStream_t st, const float *S, int64_t C, const int64_t *doc_offsets, const int32_t *codes,
                           int nq, const uint64_t *in_keys, int64_t in_stride, const int32_t *in_counts, int n_upper,
@@ -182,14 +199,22 @@ void plaid_launch_ci_list(hipStream_t st, const float *S, int64_t C, const int64
 {
     const int spread = nq < 8 ? 1 : 0;
     const int64_t slots = spread ? nq : 8 * (((int64_t)nq + 7) / 8);  // query slots of the grid
-    int64_t gx = ((int64_t)n_upper + 4 * CI_PPW - 1) / (4 * CI_PPW);
+    const bool few = (int64_t)nq * n_upper <= CI_FEW;
+    const int per_wave = few ? 1 : CI_PPW;
+    int64_t gx = ((int64_t)n_upper + 4 * per_wave - 1) / (4 * per_wave);
     const int64_t cap = (1ll << 23) / slots;  // at most 2^23 workgroups (2^31 threads) per launch
     if (gx > cap) gx = cap;
     if (gx < 1) gx = 1;
-    if (C <= (1ll << 25))
-        hipLaunchKernelGGL(ci_list_kernel<false>, dim3((unsigned)(slots * gx)), dim3(256), 0, st, S, C, doc_offsets, codes,
-                           in_keys, in_stride, in_counts, nq, (int)gx, spread, out_keys, out_stride);
-    else
-        hipLaunchKernelGGL(ci_list_kernel<true>, dim3((unsigned)(slots * gx)), dim3(256), 0, st, S, C, doc_offsets, codes,
-                           in_keys, in_stride, in_counts, nq, (int)gx, spread, out_keys, out_stride);
+    const bool wide = C > (1ll << 25);
+#define PLAID_CI_LAUNCH(KERNEL)                                                                                                 \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(slots * gx)), dim3(256), 0, st, S, C, doc_offsets, codes, in_keys, in_stride, in_counts, \
+                       nq, (int)gx, spread, out_keys, out_stride)
+    if (few) {
+        if (wide) PLAID_CI_LAUNCH(ci_few_kernel<true>);
+        else PLAID_CI_LAUNCH(ci_few_kernel<false>);
+    } else {
+        if (wide) PLAID_CI_LAUNCH(ci_list_kernel<true>);
+        else PLAID_CI_LAUNCH(ci_list_kernel<false>);
+    }
+#undef PLAID_CI_LAUNCH
 }
