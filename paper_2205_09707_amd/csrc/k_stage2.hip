@@ -1634,7 +1634,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_candidates_kernel, dim3((unsigned)((cand_words + 63) / 64), nq), dim3(64 * IV_WAVES), 0, st, uniq, n_uniq,
                            uniq_stride, ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            wide);
-    // Passages per wave and step: 2048, fewer (512 at least) for indexes of so few passages that a wave's own chain of steps is all
+    // Passages per wave and step: 2048, fewer (512 at least, but see below) for indexes of so few passages that a wave's own chain of steps is all
     // that counts and the chip has room for more waves, up to 400 of a query: beyond, what they add to one histogram and score before there is a
     // threshold costs more.  us per search with 2048 / 1024 / 512 / 256: one query of 10 000 passages 77 / 69 / 65 / 66, of 40 000 73 / 70 /
     // 70 / 73, of 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 / 129 / 148), of a million
@@ -1646,6 +1646,9 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
     // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
     while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
+    // A small collection of which a large share is kept: down to 128, while a wave's share of m is more than 64.  us per search of 10 000 passages, ndocs 4096,
+    // with 512 / this: one query 134 / 105, four 155 / 125, fifteen 207 / 177; of 15 000 112 / 102, 138 / 126, 194 / 184.
+    while (len_log > 7 && ((int64_t)m << len_log) / P > 64 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = s2_steps(nq, waves);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
     // Passages a wave scores before there is a threshold: 24 (and those that tie with the last of them), which mostly fit a batch of 32 in which
