@@ -1105,17 +1105,19 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
 }
 
 // ------------------------------------------------------------------ decompression alone (parity of the codec)
-// Token counts of the listed passages, a passage per thread, and their prefix sums by the workgroup that arrives last (a lane's
-// address each is what a gather of token ranges costs: one compute unit alone takes 15 us for 5000 of them).
-// The ids are the caller's, and nothing is read by one out of range; where there is one the last offset becomes -1, which
-// tells the decompression kernel that nothing is to be done, as a total above the capacity does.  work (two words, zero before and
-// after): workgroups arrived, and how far from the list's end the first id out of range is.  report (memory of the host, which waits
-// for the last word): total, place of that id or -1, the id, 1.
+// Token counts of the listed passages, a passage per thread, to lens, and their prefix sums by the workgroup that arrives last
+// (a lane's address each is what a gather of token ranges costs: one compute unit alone takes 15 us for 5000 of them).
+// The ids are the caller's: nothing is read by one out of range, and out_offsets is left alone where there is one.  A list
+// with such an id, or of more tokens than capacity, leaves its ticket in *refused: the decompression kernel behind this one
+// does nothing then.  lens, work and refused are the library's, so that no write to the caller's buffers gets a refused list
+// past that.  work (two words, zero before and after): workgroups arrived, and how far from the list's end the first id out of
+// range is.  report (memory of the host, which waits for the last word): total, place of that id or -1, the id, 1.
 #define OFFS_THREADS 1024
 #define OFFS_PER 4
 __global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int64_t *__restrict__ doc_offsets, int64_t P,
-                                                                       const int32_t *__restrict__ pids, int n, int64_t *out_offsets,
-                                                                       uint32_t *work, int64_t *report)
+                                                                       const int32_t *__restrict__ pids, int n, int64_t *lens,
+                                                                       int64_t *__restrict__ out_offsets, int64_t capacity, uint32_t *work,
+                                                                       int64_t *refused, int64_t ticket, int64_t *report)
 {
     __shared__ int64_t wave_sum[OFFS_THREADS / 64];
     __shared__ uint32_t arrived;
@@ -1126,7 +1128,7 @@ __global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int
         int64_t len = 0;
         if ((uint64_t)(int64_t)pid < (uint64_t)P) len = doc_offsets[(int64_t)pid + 1] - doc_offsets[pid];
         else atomicMax(&work[1], (uint32_t)(n - e));
-        __hip_atomic_store(&out_offsets[e + 1], len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&lens[e], len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);  // this wave's stores and updates have completed
@@ -1144,7 +1146,7 @@ __global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int
             int64_t incl[OFFS_PER], sum = 0;
 #pragma unroll
             for (int u = 0; u < OFFS_PER; ++u)
-                incl[u] = e0 + 64 * u < n ? __hip_atomic_load(&out_offsets[e0 + 64 * u + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+                incl[u] = e0 + 64 * u < n ? __hip_atomic_load(&lens[e0 + 64 * u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
 #pragma unroll
             for (int u = 0; u < OFFS_PER; ++u) {
 #pragma unroll
@@ -1171,7 +1173,7 @@ __global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int
         }
     }
     if (threadIdx.x == 0) {
-        if (bad) out_offsets[n] = -1;
+        if (bad || carry > capacity) *refused = ticket;
         work[0] = 0u;
         work[1] = 0u;
         report[0] = carry;
@@ -1180,11 +1182,13 @@ __global__ __launch_bounds__(OFFS_THREADS) void passage_offsets_kernel(const int
         __hip_atomic_store(&report[3], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
-void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, int64_t P, const int32_t *pids, int n, int64_t *out_offsets,
-                                  uint32_t *work, int64_t *report)
+void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, int64_t P, const int32_t *pids, int n, int64_t *lens,
+                                  int64_t *out_offsets, int64_t capacity, uint32_t *work, int64_t *refused, int64_t ticket,
+                                  int64_t *report)
 {
     const unsigned grid = n > 0 ? (unsigned)(((int64_t)n + OFFS_THREADS - 1) / OFFS_THREADS) : 1u;
-    hipLaunchKernelGGL(passage_offsets_kernel, dim3(grid), dim3(OFFS_THREADS), 0, st, doc_offsets, P, pids, n, out_offsets, work, report);
+    hipLaunchKernelGGL(passage_offsets_kernel, dim3(grid), dim3(OFFS_THREADS), 0, st, doc_offsets, P, pids, n, lens, out_offsets,
+                       capacity, work, refused, ticket, report);
 }
 
 // Same table, same lookup and same addition as the fused kernel; thread t handles dimensions 4t .. 4t+3.
@@ -1197,14 +1201,15 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
                                                               const int32_t *__restrict__ pids,
                                                               const int64_t *__restrict__ out_offsets,
                                                               float *__restrict__ out_vectors,
-                                                              uint8_t *__restrict__ out_indices, int64_t capacity,
-                                                              const float *__restrict__ inv_norm)
+                                                              uint8_t *__restrict__ out_indices,
+                                                              const float *__restrict__ inv_norm,
+                                                              const int64_t *refused, int64_t ticket)
 {
     constexpr int RB = 16 * NBITS;
     __shared__ float4 wlut[256 * (NBITS == 2 ? 1 : 2)];
     __shared__ uint32_t ilut[256 * (NBITS == 2 ? 1 : 2)];
-    const int64_t total = out_offsets[gridDim.x];
-    if (total < 0 || total > capacity) return;  // (uniform) passage_offsets_kernel has refused an id, or there is no room
+    // (uniform) refused by passage_offsets_kernel; another call that is refused meanwhile leaves another ticket
+    if (*refused == ticket) return;
     build_tables<NBITS>(wlut, ilut, weights, threadIdx.x, 256);
     __syncthreads();
     const int a = blockIdx.x;
@@ -1246,15 +1251,15 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                   int nbits, const int32_t *pids, int n, const int64_t *out_offsets, float *out_vectors,
-                                  uint8_t *out_indices, int64_t capacity, const float *inv_norm)
+                                  uint8_t *out_indices, const float *inv_norm, const int64_t *refused, int64_t ticket)
 {
     if (n <= 0) return;
     if (nbits == 2)
         hipLaunchKernelGGL(decompress_dump_kernel<2>, dim3(n), dim3(256), 0, st, centroids, doc_offsets, codes, residuals,
-                           bucket_weights, pids, out_offsets, out_vectors, out_indices, capacity, inv_norm);
+                           bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm, refused, ticket);
     else
         hipLaunchKernelGGL(decompress_dump_kernel<1>, dim3(n), dim3(256), 0, st, centroids, doc_offsets, codes, residuals,
-                           bucket_weights, pids, out_offsets, out_vectors, out_indices, capacity, inv_norm);
+                           bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm, refused, ticket);
 }
 
 // Storage variant "reconstructed vectors scaled to unit length" (the other reading of Section 4.5's reconstruction):

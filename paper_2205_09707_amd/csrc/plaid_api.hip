@@ -83,8 +83,12 @@ struct plaid_index {
     hipEvent_t ev[N_EVENTS] = {nullptr};
     // what a call waits for the device to report: one per call that is under way, kept for the next one
     struct Report {
-        int64_t *words;  // pinned host memory
-        uint32_t *work;  // device memory, zero between calls
+        int64_t *words;   // pinned host memory
+        uint32_t *work;   // device memory: two words, zero between calls, and the ticket of the last call that was refused
+        int64_t *lens;    // device memory, room words
+        int64_t room;
+        int64_t tickets;  // given out
+        int64_t *refused() const { return (int64_t *)(work + 2); }
     };
     std::vector<Report> reports;  // all of them
     std::vector<size_t> free_reports;
@@ -291,15 +295,16 @@ static int build_range_table(plaid_index *ix)
 
 // A report of the index for the length of a call.
 struct ReportLease {
+    static constexpr int64_t LENS_LEAST = 1 << 14;
     plaid_index *ix;
-    plaid_index::Report r = {nullptr, nullptr};
+    plaid_index::Report r = {nullptr, nullptr, nullptr, 0, 0};
     size_t at = 0;
     explicit ReportLease(plaid_index *index) : ix(index) {}
-    int take()
+    int take(int64_t n)  // for a list of n passages
     {
         const std::lock_guard<std::mutex> lock(ix->reports_guard);
         if (ix->free_reports.empty()) {
-            plaid_index::Report fresh = {nullptr, nullptr};
+            plaid_index::Report fresh = {nullptr, nullptr, nullptr, 0, 0};
             if (hipHostMalloc((void **)&fresh.words, 64, hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) {
                 (void)hipGetLastError();
                 return fail(PLAID_ENOMEM, "pinned host memory for a report failed");
@@ -321,9 +326,22 @@ struct ReportLease {
                 return fail(PLAID_ENOMEM, "host allocation failed");
             }
         }
+        plaid_index::Report &f = ix->reports[ix->free_reports.back()];
+        if (f.room < n) {  // (the report of the call that used it last was the last thing to read it)
+            if (f.lens) (void)hipFree(f.lens);
+            f.lens = nullptr;
+            f.room = 0;
+            const int64_t room = n > LENS_LEAST ? n + n / 2 : LENS_LEAST;
+            if (hipMalloc((void **)&f.lens, (size_t)room * 8) != hipSuccess) {
+                (void)hipGetLastError();
+                return fail(PLAID_ENOMEM, "device memory for the token counts of %lld passages failed", (long long)n);
+            }
+            f.room = room;
+        }
+        ++f.tickets;
         at = ix->free_reports.back();
         ix->free_reports.pop_back();
-        r = ix->reports[at];
+        r = f;
         return PLAID_OK;
     }
     ~ReportLease()
@@ -394,6 +412,7 @@ extern "C" void plaid_index_free(plaid_index *idx)
     for (int i = 0; i < N_EVENTS; ++i)
         if (idx->ev[i]) (void)hipEventDestroy(idx->ev[i]);
     for (const plaid_index::Report &r : idx->reports) {
+        if (r.lens) (void)hipFree(r.lens);
         (void)hipFree(r.work);
         (void)hipHostFree(r.words);
     }
@@ -497,7 +516,7 @@ extern "C" int plaid_index_from_view(const plaid_index_view *v, int device, int 
     }
     {  // the words of a first call of plaid_decompress_passages, which otherwise makes them (213 us, now 121); without them that call tries again
         ReportLease first(ix);
-        (void)first.take();
+        (void)first.take(ReportLease::LENS_LEAST);
     }
     *out = ix;
     return PLAID_OK;
@@ -1340,6 +1359,7 @@ extern "C" int plaid_build_ivf(const int32_t *codes, const int64_t *doc_offsets,
     HIP_TRY(hipStreamSynchronize(st));  // the scratch area is released on return
     return PLAID_OK;
 }
+
 // ------------------------------------------------------------------ decompression alone
 extern "C" int plaid_decompress_passages(plaid_index *ix, const int32_t *pids, int32_t n, int64_t *out_offsets,
                                          float *out_vectors, uint8_t *out_indices, int64_t capacity, void *hip_stream)
@@ -1360,20 +1380,23 @@ extern "C" int plaid_decompress_passages(plaid_index *ix, const int32_t *pids, i
         if (rc) return rc;
         offs = (int64_t *)ix->ws;
     }
-    // The ids come from the caller: the offsets kernel checks them before anything is read by them, and the decompression
-    // checks the total against the capacity; it is enqueued before the host knows either, and the host waits for the offsets
-    // kernel's report alone, a word of host memory.  (Ids checked on the host, then the total read back, two round trips with the device
-    // idle: 5000 passages 129.5 us a call; one event for the report 94.0, the word 84.4.)
+    // The ids come from the caller: the offsets kernel checks them before anything is read by them, and the total against the
+    // capacity; the decompression is enqueued before the host knows either, and the host waits for the offsets kernel's report
+    // alone, a word of host memory.  (Ids checked on the host, then the total read back, two round trips with the device idle:
+    // 5000 passages 129.5 us a call; one event for the report 94.0, the word 84.4.)
+    const bool vectors = out_vectors || out_indices;
     ReportLease report(ix);
-    int rc = report.take();
+    int rc = report.take(n);
     if (rc) return rc;
-    volatile int64_t *words = report.r.words;
+    const plaid_index::Report &r = report.r;
+    volatile int64_t *words = r.words;
     words[3] = 0;
-    plaid_launch_passage_offsets(st, ix->doc_offsets, ix->P, pids, n, offs, report.r.work, report.r.words);
+    plaid_launch_passage_offsets(st, ix->doc_offsets, ix->P, pids, n, r.lens, offs, vectors ? capacity : INT64_MAX, r.work, r.refused(),
+                                 r.tickets, r.words);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && (out_vectors || out_indices)) {
-        plaid_launch_decompress_dump(st, ix->centroids, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits,
-                                     pids, n, offs, out_vectors, out_indices, capacity, ix->renormalize ? ix->inv_norm : nullptr);
+    if (e == hipSuccess && vectors) {
+        plaid_launch_decompress_dump(st, ix->centroids, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, pids, n, offs,
+                                     out_vectors, out_indices, ix->renormalize ? ix->inv_norm : nullptr, r.refused(), r.tickets);
         e = hipGetLastError();
     }
     // the report arrives while the decompression runs; a stream with more before it is waited for the usual way
@@ -1386,9 +1409,9 @@ extern "C" int plaid_decompress_passages(plaid_index *ix, const int32_t *pids, i
     if (e == hipSuccess && !words[3]) e = hipErrorUnknown;
     std::atomic_thread_fence(std::memory_order_acquire);
     HIP_TRY(e);
-    if (report.r.words[1] >= 0)
-        return fail(PLAID_EINVAL, "pids[%lld] = %lld out of range", (long long)report.r.words[1], (long long)report.r.words[2]);
-    if (report.r.words[0] > capacity && (out_vectors || out_indices))
-        return fail(PLAID_EINVAL, "passages hold %lld tokens, capacity is %lld", (long long)report.r.words[0], (long long)capacity);
-    return PLAID_OK;
+    const bool bad = words[1] >= 0;
+    if (!bad && !(vectors && words[0] > capacity)) return PLAID_OK;
+    if (vectors) HIP_TRY(hipStreamSynchronize(st));  // nothing of a refused call is left behind
+    if (bad) return fail(PLAID_EINVAL, "pids[%lld] = %lld out of range", (long long)words[1], (long long)words[2]);
+    return fail(PLAID_EINVAL, "passages hold %lld tokens, capacity is %lld", (long long)words[0], (long long)capacity);
 }

@@ -367,12 +367,15 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                   int nbits, const int32_t *pids, int n, const int64_t *out_offsets, float *out_vectors,
-                                  uint8_t *out_indices, int64_t capacity, const float *inv_norm = nullptr);
+                                  uint8_t *out_indices, const float *inv_norm, const int64_t *refused, int64_t ticket);
 // inv_norm[t] = 1 / |centroid[code_t] + residual_t| (fp32, from a double-precision sum of squares), 0 for a zero vector.
 void plaid_launch_token_inv_norm(hipStream_t st, const float *centroids, const int32_t *codes, const uint8_t *residuals,
                                  const float *bucket_weights, int nbits, int64_t N, float *inv_norm);
-void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, int64_t P, const int32_t *pids, int n, int64_t *out_offsets,
-                                  uint32_t *work /* two words, zero */, int64_t *report /* host memory, four words, the last zero */);
+// lens: n words; work: two words, zero; *refused becomes ticket, which no other call on it has, if the list is refused;
+// report: host memory, four words, the last zero.
+void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, int64_t P, const int32_t *pids, int n, int64_t *lens,
+                                  int64_t *out_offsets, int64_t capacity, uint32_t *work, int64_t *refused, int64_t ticket,
+                                  int64_t *report);
 
 // Structural check of device-resident index arrays (k_util.hip); bad[0] (zero before the call) receives a bit per kind
 // of violation: 1 doc_offsets, 2 codes, 4 ivf_offsets, 8 passage id out of range, 16 inverted list not strictly ascending.

@@ -1,5 +1,7 @@
-"""plaid_decompress_passages: ids out of range at the edges of the offsets kernel's workgroups (1024 ids) and rounds (4096) are refused with their place and
-the index serves the next call; lists around a round's length; several threads with streams of their own."""
+"""plaid_decompress_passages: ids out of range at the edges of the offsets kernel's workgroups (1024 ids) and rounds (4096) are
+refused with their place, leave the outputs alone and nothing on the stream, and the index serves the next call; lists around a
+round's length; several threads with streams of their own."""
+import ctypes as ct
 import threading
 
 import pytest
@@ -67,6 +69,55 @@ def test_ids_out_of_range_are_refused(n, places, value):
         with pytest.raises(RuntimeError, match=rf"pids\[{places[0]}\] = {value} out of range"):
             pl.plaid_decompress_passages(idx, bad, 9 * n)
         assert int(pl.plaid_decompress_passages(idx, pids, 9 * n)[0][-1]) > 0  # the index serves the next call
+    finally:
+        pl.plaid_index_free(idx)
+
+
+@pytest.mark.parametrize("n", [1, 1025, 20_000])
+def test_a_refused_call_leaves_the_outputs_alone(n):
+    """... and nothing on the stream, whose caller may use the buffers again from elsewhere."""
+    import paper_2205_09707_amd as pl
+    idx, arrays = _index(pl, 3000)
+    lib = pl.load_library()
+    try:
+        pids = (torch.arange(n, device="cuda") * 7 % 3000).int()
+        o = arrays["doc_offsets"]
+        want = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        want[1:] = torch.cumsum(o[pids.long() + 1] - o[pids.long()], 0)
+        total = int(want[-1])
+        assert total > 0
+        bad = pids.clone()
+        bad[n // 2] = 3000
+        offs = torch.full((n + 1,), 77, dtype=torch.int64, device="cuda")
+        vec = torch.full((total, 128), 7.0, device="cuda")
+        ind = torch.full((total, 128), 9, dtype=torch.uint8, device="cuda")
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+
+        def call(list_, capacity, vectors=True):
+            p = [ct.c_void_p(t.data_ptr()) for t in (list_, offs, vec, ind)]
+            return lib.plaid_decompress_passages(idx.handle, p[0], n, p[1], p[2] if vectors else None, p[3] if vectors else None,
+                                                 capacity, ct.c_void_p(stream.cuda_stream))
+
+        def untouched():
+            return bool((vec == 7.0).all()) and bool((ind == 9).all())
+
+        assert call(bad, total) == -1 and "out of range" in pl.plaid_last_error()
+        assert stream.query() and untouched() and bool((offs == 77).all())
+        assert call(bad, 0, vectors=False) == -1
+        stream.synchronize()
+        assert bool((offs == 77).all())
+        assert call(pids, total - 1) == -1 and "capacity" in pl.plaid_last_error()
+        assert stream.query() and untouched() and torch.equal(offs, want)
+        offs.fill_(77)
+        torch.cuda.synchronize()
+        assert call(pids, 0, vectors=False) == 0  # (no rows asked for: the capacity does not matter)
+        stream.synchronize()
+        assert torch.equal(offs, want)
+        assert call(pids, total) == 0
+        stream.synchronize()
+        v, i = _expected(arrays, pids[:300])
+        assert torch.equal(vec[:len(v)], v) and torch.equal(ind[:len(i)], i)
     finally:
         pl.plaid_index_free(idx)
 
