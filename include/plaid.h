@@ -167,10 +167,11 @@ int plaid_search_vanilla(plaid_index *idx, const float *Q, int32_t nq, int32_t n
  *   out_vectors  DEVICE [total][128] fp32 reconstructed vectors, passages concatenated in list order (may be NULL)
  *   out_indices  DEVICE [total][128] uint8 unpacked bucket indices (may be NULL)
  *   capacity     rows available in out_vectors / out_indices; PLAID_EINVAL if total exceeds it
- * Waits once for the stream to reach the call (the device checks the ids and reports the total), not for the vectors: pids
- * and out_offsets must stay as they are until the stream has passed the call.  A refused list (PLAID_EINVAL: an id outside
- * [0, num_passages), more tokens than capacity) leaves nothing on the stream; out_vectors and out_indices are then untouched,
- * out_offsets too for an id out of range, and hold the prefix sum for a capacity too small. */
+ * Waits for the stream to reach the call (the device checks the ids and reports the total), the first 500 us of it without
+ * giving up the processor, and not for the vectors: pids and out_offsets must stay as they are until the stream has passed
+ * the call.  A refused list (PLAID_EINVAL: an id outside [0, num_passages), more tokens than capacity) leaves nothing on the
+ * stream; out_vectors and out_indices are then untouched, out_offsets too for an id out of range, and hold the prefix sum for a
+ * capacity too small.  PLAID_EHIP on a stream that is being captured. */
 int plaid_decompress_passages(plaid_index *idx, const int32_t *pids, int32_t n, int64_t *out_offsets,
                               float *out_vectors, uint8_t *out_indices, int64_t capacity, void *hip_stream);
 

@@ -11,6 +11,7 @@
 #include <chrono>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "plaid_internal.h"
@@ -1399,14 +1400,22 @@ extern "C" int plaid_decompress_passages(plaid_index *ix, const int32_t *pids, i
                                      out_vectors, out_indices, ix->renormalize ? ix->inv_norm : nullptr, r.refused(), r.tickets);
         e = hipGetLastError();
     }
-    // the report arrives while the decompression runs; a stream with more before it is waited for the usual way
+    // The report arrives while the decompression runs.  A stream with more than a little before it is asked now and then: to wait for
+    // the stream would be to wait for the vectors.
     const auto start = std::chrono::steady_clock::now();
-    while (e == hipSuccess && !words[3] && std::chrono::steady_clock::now() - start < std::chrono::microseconds(500)) __builtin_ia32_pause();
-    if (!words[3]) {
-        const hipError_t w = hipStreamSynchronize(st);  // (also after a failed launch: the report is the kernel's until then)
-        if (e == hipSuccess) e = w;
+    while (e == hipSuccess && !words[3]) {
+        if (std::chrono::steady_clock::now() - start < std::chrono::microseconds(500)) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+        const hipError_t s = hipStreamQuery(st);
+        if (s == hipSuccess) break;
+        (void)hipGetLastError();  // (not ready)
+        if (s != hipErrorNotReady) e = s;
     }
-    if (e == hipSuccess && !words[3]) e = hipErrorUnknown;
+    if (e != hipSuccess) (void)hipStreamSynchronize(st);  // (after a failed launch: the report is the kernel's until then)
+    else if (!words[3]) e = hipErrorUnknown;
     std::atomic_thread_fence(std::memory_order_acquire);
     HIP_TRY(e);
     const bool bad = words[1] >= 0;

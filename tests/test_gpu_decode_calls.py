@@ -1,6 +1,6 @@
 """plaid_decompress_passages: ids out of range at the edges of the offsets kernel's workgroups (1024 ids) and rounds (4096) are
 refused with their place, leave the outputs alone and nothing on the stream, and the index serves the next call; lists around a
-round's length; several threads with streams of their own."""
+round's length; a stream with work before the call; several threads with streams of their own."""
 import ctypes as ct
 import threading
 
@@ -118,6 +118,25 @@ def test_a_refused_call_leaves_the_outputs_alone(n):
         stream.synchronize()
         v, i = _expected(arrays, pids[:300])
         assert torch.equal(vec[:len(v)], v) and torch.equal(ind[:len(i)], i)
+    finally:
+        pl.plaid_index_free(idx)
+
+
+def test_a_busy_stream_is_not_waited_for_past_the_report():
+    """Behind several milliseconds of other work the call returns with the report, before the vectors (5 GB of them) are there."""
+    import paper_2205_09707_amd as pl
+    idx, arrays = _index(pl, 3000)
+    try:
+        pids = (torch.arange(2_000_000, device="cuda") * 7 % 3000).int()
+        o = arrays["doc_offsets"]
+        total = int((o[pids.long() + 1] - o[pids.long()]).sum())
+        pl.plaid_decompress_passages(idx, pids, total)
+        torch.cuda.synchronize()
+        torch.cuda._sleep(20_000_000)
+        offs, vec, ind = pl.plaid_decompress_passages(idx, pids, total)
+        assert not torch.cuda.current_stream().query()
+        v, i = _expected(arrays, pids[:300])
+        assert int(offs[-1]) == total and torch.equal(vec[:len(v)], v) and torch.equal(ind[:len(i)], i)
     finally:
         pl.plaid_index_free(idx)
 
