@@ -160,27 +160,42 @@ def test_refused_under_capture():
 
 
 def test_several_threads():
+    """Lists of their own, one thread with an id out of range and one with too little room now and then: each call reports on its
+    own list."""
     import paper_2205_09707_amd as pl
     idx, arrays = _index(pl, 3000)
-    wrong = []
+    wrong, done = [], []
 
     def work(t):
-        with torch.cuda.stream(torch.cuda.Stream()):
-            pids = (torch.arange(50 + t, device="cuda") * (11 + t) % 3000).int()
-            v, i = _expected(arrays, pids)
-            for _ in range(20):
-                offs, vec, ind = pl.plaid_decompress_passages(idx, pids, len(v))
-                if not (torch.equal(vec, v) and torch.equal(ind, i)):
-                    wrong.append(t)
-            torch.cuda.current_stream().synchronize()
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                pids = (torch.arange(50 + 700 * t, device="cuda") * (11 + t) % 3000).int()
+                bad = pids.clone()
+                bad[t] = -5 - t
+                v, i = _expected(arrays, pids)
+                torch.cuda.current_stream().synchronize()
+                for r in range(20):
+                    offs, vec, ind = pl.plaid_decompress_passages(idx, pids, len(v))
+                    if not (int(offs[-1]) == len(v) and torch.equal(vec, v) and torch.equal(ind, i)):
+                        wrong.append((t, r))
+                    if t == 1:
+                        with pytest.raises(RuntimeError, match=rf"pids\[{t}\] = {-5 - t} out of range"):
+                            pl.plaid_decompress_passages(idx, bad, len(v))
+                    if t == 2:
+                        with pytest.raises(RuntimeError, match=f"passages hold {len(v)} tokens, capacity is {len(v) - 1}"):
+                            pl.plaid_decompress_passages(idx, pids, len(v) - 1)
+                    done.append(t)
+                torch.cuda.current_stream().synchronize()
+        except BaseException as e:
+            wrong.append((t, repr(e)))
 
     try:
         torch.cuda.synchronize()
-        threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+        threads = [threading.Thread(target=work, args=(t,)) for t in range(5)]
         for t in threads:
             t.start()
         for t in threads:
             t.join()
-        assert not wrong
+        assert not wrong and len(done) == 100
     finally:
         pl.plaid_index_free(idx)
