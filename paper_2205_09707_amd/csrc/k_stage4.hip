@@ -853,13 +853,16 @@ __global__ __launch_bounds__(256, 4) void van_coarse_kernel(
     maxsim_list_body<NBITS, true, false, false, true>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits, keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys, out_stride);
 }
 
-// Pruning by coarse scores.  Most candidates lie far from the cut: scores from the leading products decide them, and only those
-// within the coarse scores' error of it are scored in full.  With T the ncandidates-th best coarse score and E the largest difference
-// between a coarse and a full score of the query, ncandidates full scores are >= T - E, and no more than ncandidates - 1 are > T + E: what
-// has a coarse score > T + 2 E is kept, what has one < T - 2 E is not, and the rest compete by their full scores for the places left.
-// E: of a query token's product with a residual the coarse score misses w . (q - q1) + (w - w1) . q1, at most
-// wmax sum |q - q1| + max |w - w1| sum |q1|; both scores' sums of 128 products of size wmax |q| in fp32, and the additions of the centroid's
-// share (at most centroid_max sum |q|), are rounded.
+// Pruning by coarse scores.  Most candidates lie far from the cut: scores from the leading products decide them, and only
+// those within the coarse scores' error of it are scored in full.  With T the ncandidates-th best coarse score and E the largest
+// difference between a coarse and a full score of the query, ncandidates full scores are >= T - E, and no more than
+// ncandidates - 1 are > T + E: what has a coarse score > T + 2 E is kept, what has one < T - 2 E is not, and the rest compete by
+// their full scores for the places left.
+// E: of a query token's product with a residual the coarse score misses w1 . q2 + w2 . q1, w2 and q2 being what the trailing
+// terms stand for: w - w1 and q - q1 rounded to fp16 at 2^11 times their size, that is by 2^-11 of themselves or, below fp16's
+// normal range, by 2^-36.  (Without the latter, queries of components near 2^-36, where a trailing term can be twice what it stands
+// for, had passages kept and dropped that full scores rank the other way.)  Both scores' sums of 128 products of size wmax |q| in
+// fp32, and the additions of the centroid's share (at most centroid_max sum |q|), are rounded.
 struct VanBand {
     float lo, hi;  // coarse scores within [lo, hi] do not decide
 };
@@ -884,9 +887,11 @@ __global__ __launch_bounds__(1024) void van_bounds_kernel(const float *__restric
         _Float16 x1, x2;
         s4_split(x, x1, x2);
         const double a = fabs((double)x), b = fabs((double)(float)x1);
-        e += (double)wmax * fabs((double)x - (double)(float)x1) + (double)dw * b;
-        e += 3.0 * 128.0 * 0x1p-24 * (double)wmax * (a + b);         // the fp32 sums of either score
-        e += 0x1p-20 * (a + b) * ((double)centroid_max + (double)wmax);  // the additions of the centroid's share, the sums' last rounding
+        const double up = 1.0 + 0x1p-11;  // an fp16 number is at most this times what was rounded to it, above 2^-14
+        e += up * (double)wmax * (up * fabs((double)x - (double)(float)x1) + 0x1p-36);  // |w1| <= up wmax
+        e += (up * (double)dw + 0x1p-36) * b;
+        e += 3.0 * 128.0 * 0x1p-24 * (double)wmax * (a + b);             // the fp32 sums of either score
+        e += 0x1p-20 * (a + b) * ((double)centroid_max + (double)wmax);  // the centroid's share, the sums' last rounding
     }
     unsigned long long w = 0;  // the largest key kept: the worst
     for (int j = threadIdx.x; j < n_kept[q]; j += 1024) {
@@ -906,7 +911,7 @@ __global__ __launch_bounds__(1024) void van_bounds_kernel(const float *__restric
             w = worst[v] > w ? worst[v] : w;
         }
         VanBand r;
-        const float T = plaid_ord_to_score((uint32_t)(w >> 32)), E = (float)e * 2.0f * 1.001f;
+        const float T = plaid_ord_to_score((uint32_t)(w >> 32)), E = (float)e * 2.0f * 1.00001f;  // (the factor: this product's own roundings)
         if (n_cand[q] <= n_kept[q]) r.lo = r.hi = -INFINITY;                   // (all are kept: every score is above)
         else if (!(T > -INFINITY && T < INFINITY && E < INFINITY)) r.lo = -INFINITY, r.hi = INFINITY;  // nothing is decided
         else r.lo = nextafterf(T - E, -INFINITY), r.hi = nextafterf(T + E, INFINITY);

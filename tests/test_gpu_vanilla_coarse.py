@@ -51,6 +51,36 @@ def test_coarse_pruning_keeps_what_full_scores_keep(P, C, nbits, scale, copies, 
         pl.plaid_index_free(idx)
 
 
+@pytest.mark.parametrize("exponent", [-60, -36, -35, -34, -26, -16, -12, 0])
+def test_queries_below_the_range_of_the_trailing_terms(exponent):
+    """One passage leads by its centroid what its residual costs it.  Where the components are near 2^-36 the residual's part of the full
+    score, formed of trailing terms below fp16's normal range, is up to twice the exact one, and the coarse score has none of it."""
+    import paper_2205_09707_amd as pl
+    P, w, ncand = 131_072, 0.0625, 64
+    x = 1.02 * 2.0 ** exponent
+    trailing = 2.0 ** -35 * round(x * 2 ** 35) / x if exponent <= -25 else 1.0  # of one: trailing term over exact value
+    cen = torch.full((4, 128), -0.25, device="cuda")
+    cen[0] = 0.25
+    cen[1] = 0.25 + 2.3 * w / max(trailing, 1.0)
+    codes = torch.zeros(P, dtype=torch.int32, device="cuda")
+    codes[-1] = 1
+    offsets = torch.arange(P + 1, dtype=torch.int64, device="cuda")
+    io, ip = pl.plaid_build_ivf(codes, offsets, 4)
+    res = torch.full((P, 16), 255, dtype=torch.uint8, device="cuda")
+    res[-1] = 0
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": io, "ivf_pids": ip, "residuals": res,
+              "bucket_weights": torch.tensor([-w, w], device="cuda")}
+    idx = pl.plaid_index_from_view(arrays, 1, device=0, copy=False)
+    try:
+        Q = torch.full((8, 32, 128), x, device="cuda")
+        ids, scores = pl.plaid_search_vanilla(idx, Q, 2, ncand, ncand)
+        want_ids, want_scores, _ = pl.plaid_search_vanilla(idx, Q, 2, ncand, ncand, debug=True)
+        torch.cuda.synchronize()
+        assert torch.equal(ids, want_ids) and torch.equal(scores, want_scores)
+    finally:
+        pl.plaid_index_free(idx)
+
+
 def test_queries_that_are_not_numbers():
     import paper_2205_09707_amd as pl
     idx, Q, arrays = _index(pl, 70_000, 2048, 2, 0.02, 1, 5)
