@@ -954,6 +954,12 @@ __device__ __forceinline__ int sel2_sub_bin(uint64_t key, const S2Meta &mt, int 
     return (int)fminf(fmaxf(x, 0.f), (float)(SEL2_SUB - 1));
 }
 static_assert(SEL2_SUB >> S2_COARSE_SHIFT > 0, "a coarse bin has digits");
+// Scores that lie nearer to one another than that tells apart: of a list whose scores are fewer than SEL2_SUB representable
+// numbers apart the digit is the number itself, counted by its ten lowest bits (in the half of the fine histogram's place that the
+// coarse ones leave free).  Bins that come with the fine histogram have digits near a rounding step as it is.  Two scores 16 numbers
+// apart, which share the passages of an index between them, us per search with / without: one query of 100 000 passages 223 / 409, of 400 000
+// 404 / 1091, of 8.8 M 412 / 6350, sixteen of 8.8 M 2894 / 12 310 (one score for all: 354 / 360 and 2394 / 2298).
+static_assert(S2_COPIES * S2_COARSE + SEL2_SUB <= SEL_BINS, "both in the fine histogram's place");
 
 // Counts the lanes' digits (-1: none).  All lanes call this, one at least has a digit.
 __device__ __forceinline__ void sel2_count(int32_t *lh, int digit)
@@ -964,14 +970,28 @@ __device__ __forceinline__ void sel2_count(int32_t *lh, int digit)
     if (lane == lead) atomicAdd(&lh[digit], __popcll(same));
     else if (digit >= 0 && !((same >> lane) & 1ull)) atomicAdd(&lh[digit], 1);
 }
-// DIGITS: counts the boundary keys' digits in hist1 ([nq][SEL_BINS]: the scores', then the passage ids') where there are more than
-// SEL_SORT_CAP of them.
+// The same for the scores' digits of either kind: lh[sub], lh[SEL_BINS + low bits of ord], for the lanes with `in`.
+__device__ __forceinline__ void sel2_count_score(int32_t *lh, bool in, int sub, uint32_t ord)
+{
+    const unsigned long long have = __ballot(in);
+    const int lane = (int)(threadIdx.x & 63), lead = (int)__builtin_ctzll(have);
+    const unsigned long long same = __ballot(in && ord == (uint32_t)__builtin_amdgcn_readlane((int)ord, lead));
+    const int n = lane == lead ? __popcll(same) : (in && !((same >> lane) & 1ull) ? 1 : 0);
+    if (n) {
+        atomicAdd(&lh[sub], n);
+        atomicAdd(&lh[SEL_BINS + (ord & (SEL2_SUB - 1))], n);
+    }
+}
+// DIGITS: where there are more than SEL_SORT_CAP boundary keys, the extremes of their scores take the place of their bits, and their
+// digits are counted in hist1 ([nq][SEL_BINS]: the scores', then the passage ids') and, of a list, the scores' lowest bits in low
+// ([nq][SEL_BINS]: the last SEL2_SUB).
 template <bool DIGITS>
 __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ keys, int64_t key_stride, const uint32_t *__restrict__ candbits,
                                                  int64_t cand_words, int64_t P, int32_t m, const S2Meta *__restrict__ meta,
                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
                                                  int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride, int lists,
-                                                 int id_shift, int32_t *__restrict__ hist1, int32_t *lh /* [SEL_BINS] */)
+                                                 int id_shift, int32_t *__restrict__ hist1, int32_t *__restrict__ low,
+                                                 int32_t *lh /* [SEL_BINS + SEL2_SUB] */)
 {
     __shared__ int32_t scan[SEL_THREADS];
     __shared__ int32_t res[2];
@@ -997,9 +1017,10 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
     if (n_keys == 0) return;
     const bool count = DIGITS && scan[SEL_THREADS - 2] > SEL_SORT_CAP;  // uniform
     if (count) {
-        for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS) lh[b] = 0;
+        for (int b = threadIdx.x; b < SEL_BINS + SEL2_SUB; b += SEL_THREADS) lh[b] = 0;
         __syncthreads();
     }
+    uint32_t ord_max = 0, ord_nmin = 0;  // of the boundary keys' scores; the latter's complement
     const uint32_t *k = reinterpret_cast<const uint32_t *>(keys + (int64_t)seg * key_stride);  // score word of passage i
     const uint32_t *cb = candbits + (int64_t)seg * cand_words;
     uint64_t *my_out = out + (int64_t)seg * out_stride;
@@ -1050,17 +1071,44 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
 #pragma unroll
             for (int u = 0; u < SEL2_GROUPS; ++u)
                 if (__any(cls[u] == 1)) {  // (the keys of a wave mostly share one digit or both: one update for those)
-                    sel2_count(lh, cls[u] == 1 ? sel2_sub_bin(key[u], mt, bstar, bin_shift) : -1);
+                    const uint32_t ord = (uint32_t)(key[u] >> 32);
+                    sel2_count_score(lh, cls[u] == 1, sel2_sub_bin(key[u], mt, bstar, bin_shift), ord);
                     sel2_count(lh + SEL2_SUB, cls[u] == 1 ? (int)((uint32_t)key[u] >> id_shift) : -1);
+                    if (cls[u] == 1) {
+                        ord_max = max(ord_max, ord);
+                        ord_nmin = max(ord_nmin, ~ord);
+                    }
                 }
         }
     }
-    sel2_place_bits<SEL_THREADS>(o, no, place, &s->b_or, &s->b_nor);
-    if (count) {
+    if (!count) {
+        sel2_place_bits<SEL_THREADS>(o, no, place, &s->b_or, &s->b_nor);
+    } else {
+        for (int d = 1; d < 64; d <<= 1) {
+            ord_max = max(ord_max, (uint32_t)__shfl_xor((int)ord_max, d));
+            ord_nmin = max(ord_nmin, (uint32_t)__shfl_xor((int)ord_nmin, d));
+        }
+        if (lane == 0) {
+            place.bits[0][wave] = ord_max;
+            place.bits[1][wave] = ord_nmin;
+        }
         __syncthreads();
         int32_t *gh = hist1 + (int64_t)seg * SEL_BINS;
         for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS)
             if (lh[b]) atomicAdd(&gh[b], lh[b]);
+        if (is_list) {
+            gh = low + (int64_t)(seg + 1) * SEL_BINS - SEL2_SUB;
+            for (int b = threadIdx.x; b < SEL2_SUB; b += SEL_THREADS)
+                if (lh[SEL_BINS + b]) atomicAdd(&gh[b], lh[SEL_BINS + b]);
+        }
+        // (one update per workgroup, and last: the workgroups that are still reserving positions wait for this line.  A query of 8.8 M
+        // equal scores: 64 us, with the extremes in front of the digits 141, with the bits of the keys in their place 72)
+        if (threadIdx.x < 2) {
+            uint32_t v = 0;
+#pragma unroll
+            for (int w = 0; w < SEL_THREADS / 64; ++w) v = max(v, (uint32_t)place.bits[threadIdx.x][w]);
+            if (v) atomicMax(threadIdx.x == 0 ? &s->ord_max : &s->ord_nmin, v);
+        }
     }
 }
 __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
@@ -1070,18 +1118,19 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint6
                                                                   uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
 {
     sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists, 0,
-                            nullptr, nullptr);
+                            nullptr, nullptr, nullptr);
 }
 __global__ __launch_bounds__(SEL_THREADS, 6) void sel2_bins_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                 const uint32_t *__restrict__ candbits, int64_t cand_words, int64_t P,
                                                                 int32_t m, const S2Meta *__restrict__ meta,
                                                                 const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
                                                                 int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride,
-                                                                int lists, int id_shift, int32_t *__restrict__ hist1)
+                                                                int lists, int id_shift, int32_t *__restrict__ hist1,
+                                                                int32_t *__restrict__ low)
 {
-    __shared__ int32_t lh[SEL_BINS];
+    __shared__ int32_t lh[SEL_BINS + SEL2_SUB];
     sel2_filter_body<true>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists,
-                           id_shift, hist1, lh);
+                           id_shift, hist1, low, lh);
 }
 
 template <int LEVEL>
@@ -1364,13 +1413,13 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint6
 // and leaves one whole tie group, the second, from the highest bit in which the keys left differ, falls into the passage-id bits and
 // leaves 2^-11 of it.
 #define SEL2_FEW 32
-// The boundary digit of a histogram of PER digits per thread: the smallest whose count, and those before it, reach r.  Every thread of
-// the workgroup returns the same.
+// The boundary digit of a histogram of PER digits per thread (which starts at digit `first` and comes round): the smallest whose count,
+// and those before it, reach r.  Every thread of the workgroup returns the same.
 template <int PER>
-__device__ __forceinline__ void sel2_boundary(const int32_t *__restrict__ gh, int r, Sel2Finish &l, int &bstar, int &before)
+__device__ __forceinline__ void sel2_boundary(const int32_t *__restrict__ gh, uint32_t first, int r, Sel2Finish &l, int &bstar, int &before)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c0 = gh[PER * threadIdx.x], c1 = PER == 2 ? gh[PER * threadIdx.x + 1] : 0;
+    const int c0 = gh[PER == 1 ? (threadIdx.x + first) & (FIN_THREADS - 1) : 2 * threadIdx.x], c1 = PER == 2 ? gh[PER * threadIdx.x + 1] : 0;
     int incl = c0 + c1;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -1402,7 +1451,8 @@ __device__ __forceinline__ void sel2_boundary(const int32_t *__restrict__ gh, in
 // Nobody waits for anybody; what the last workgroup reads of the others' goes past the XCDs' caches (AGENT).
 template <int LEVEL>
 __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_cut_kernel(const uint64_t *__restrict__ list, int64_t list_stride, Sel2State *state,
-                                                               const int32_t *__restrict__ hist, const S2Meta *__restrict__ meta, int lists,
+                                                               const int32_t *__restrict__ hist, const int32_t *__restrict__ low,
+                                                               const S2Meta *__restrict__ meta, int lists,
                                                                int id_shift, int second, uint64_t *left, int64_t left_stride,
                                                                const uint32_t *__restrict__ emptybits, int64_t cand_words, int64_t P,
                                                                int32_t m, uint64_t *out, int64_t out_stride, int32_t *__restrict__ out_counts)
@@ -1422,14 +1472,17 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_cut_kernel(const uint64_t
     } else {
         if ((int64_t)blockIdx.x * STEP >= n) return;
         const int n_work = (n + STEP - 1) / STEP < (int)gridDim.x ? (n + STEP - 1) / STEP : (int)gridDim.x;
-        // LEVEL 1: the digit of the score, or of the id where all keys share the score
-        const bool tie = LEVEL == 1 && ((s->b_or & s->b_nor) >> 32) == 0;
+        // LEVEL 1: the digit of the score, its lowest bits where all lie that near, or the id's where all keys share the score
+        const uint32_t ord_min = ~s->ord_nmin, ord_span = s->ord_max - ord_min;
+        const bool tie = LEVEL == 1 && ord_span == 0;
         const S2Meta mt = meta[seg];
-        const int bin = s->bin, bin_shift = lists && mt.K <= S2_MAX_KEPT ? S2_COARSE_SHIFT : 0;
+        const bool is_list = lists && mt.K <= S2_MAX_KEPT;
+        const int bin = s->bin, bin_shift = is_list ? S2_COARSE_SHIFT : 0;
+        const bool near = LEVEL == 1 && !tie && is_list && ord_span < SEL2_SUB;
         int shift = 0, width = 0, bstar, before;
         if (LEVEL == 2) sel2_digit_plan<2>(s, shift, width);
-        const int32_t *gh = hist + (int64_t)seg * SEL_BINS;
-        sel2_boundary<LEVEL == 1 ? 1 : 2>(tie ? gh + SEL2_SUB : gh, m_rem, l, bstar, before);
+        const int32_t *gh = near ? low + (int64_t)(seg + 1) * SEL_BINS - SEL2_SUB : hist + (int64_t)seg * SEL_BINS;
+        sel2_boundary<LEVEL == 1 ? 1 : 2>(tie ? gh + SEL2_SUB : gh, near ? ord_min : 0u, m_rem, l, bstar, before);
         uint64_t *my_left = left + (int64_t)seg * left_stride;
         unsigned long long any = 0, none = 0;
         int parity = 0;
@@ -1444,7 +1497,9 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_cut_kernel(const uint64_t
 #pragma unroll
             for (int u = 0; u < GROUPS; ++u) {
                 const int d = LEVEL == 2 ? digit_of(key[u], shift, width)
-                                         : (tie ? (int)((uint32_t)key[u] >> id_shift) : sel2_sub_bin(key[u], mt, bin, bin_shift));
+                              : tie        ? (int)((uint32_t)key[u] >> id_shift)
+                              : near       ? (int)((uint32_t)(key[u] >> 32) - ord_min)
+                                           : sel2_sub_bin(key[u], mt, bin, bin_shift);
                 cls[u] = s0 + u * FIN_THREADS + threadIdx.x < n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
             }
             sel2_place<FIN_THREADS, GROUPS, true>(key, cls, parity, place, &s->n_sure, LEVEL == 1 ? &s->n_b1 : &s->n_b2, o, my_left, any, none);
@@ -1489,12 +1544,12 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
         const int second = (nq >= 8 || lists) && P > SEL2_SECOND_MIN_PASSAGES ? 1 : 0;
         const int id_shift = sel2_id_shift(P), cut = gx < 2 ? 1 : gx / 2;
         hipLaunchKernelGGL(sel2_bins_kernel, dim3(gx_filter, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P, m,
-                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1);
-        hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.meta, lists,
+                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1, b.hist);
+        hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.hist, b.meta, lists,
                            id_shift, second, keys2, key_stride, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
         if (second) {
             hipLaunchKernelGGL(sel2_digit_hist_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state, b.hist2);
-            hipLaunchKernelGGL(sel2_cut_kernel<2>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, keys2, key_stride, b.state, b.hist2, b.meta,
+            hipLaunchKernelGGL(sel2_cut_kernel<2>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, keys2, key_stride, b.state, b.hist2, b.hist, b.meta,
                                lists, id_shift, 0, b.blist, P, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
         }
         return;

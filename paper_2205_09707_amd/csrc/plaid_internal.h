@@ -223,7 +223,7 @@ static_assert((SEL_BINS >> S2_COARSE_SHIFT) == S2_COARSE, "a coarse bin is a who
 static_assert(S2_COPIES * S2_COARSE <= SEL_BINS, "the coarse histograms take the place of the fine one");
 static_assert((S2_MAX_KEPT + 1) * 2 <= QLEN * 4 && S2_UB_BITS <= 16, "the gains take the place of the unused row");
 
-// Per-query state of the stage-2 selection (device memory, 64 bytes, zeroed before each use).
+// Per-query state of the stage-2 selection (device memory, zeroed before each use).
 struct Sel2State {
     unsigned long long b_or, b_nor;    // OR over the boundary keys / over their complements
     unsigned long long b_or1, b_nor1;  // the same over the list the first digit filter leaves
@@ -239,7 +239,8 @@ struct Sel2State {
     int32_t n_list;                    // scored candidates in the key list (inverted form, K <= S2_MAX_KEPT)
     int32_t bin;                       // the boundary bin
     int32_t arrived[2];                // workgroups of each of sel2_cut_kernel's passes that have handed over what they kept
-    int32_t pad[9];
+    uint32_t ord_max, ord_nmin;        // extremes of a long boundary list's score words (sel2_bins_kernel); the latter's complement
+    int32_t pad[7];
 };
 static_assert(sizeof(Sel2State) == 128, "Sel2State is a 128-byte record");
 
@@ -255,7 +256,8 @@ __device__ __forceinline__ int plaid_s2_bin(float score, float bin_hi, float bin
 struct Stage2Buffers {   // all device pointers, leading dimension = query of the chunk
     // zeroed before each chunk
     int32_t *hist;       // [nq][SEL_BINS]  bin histogram of the valid keys; for a query that leaves a list, in its place the
-                         //   [S2_COPIES][S2_COARSE] coarse histograms of the scores computed so far
+                         //   [S2_COPIES][S2_COARSE] coarse histograms of the scores computed so far and, behind them, counts of the lowest
+                         //   bits of a long boundary list's scores (sel2_bins_kernel)
     int32_t *hist1;      // [nq][SEL_BINS]  digit histogram of an over-long boundary list
     int32_t *hist2;      // [nq][SEL_BINS]  ... of the list the first digit filter leaves, when that is over-long too
     Sel2State *state;    // [nq]

@@ -50,3 +50,40 @@ def test_cuts_within_a_bin(P, near, nq):
                 assert torch.equal(kept, torch.sort(order[:m]).values), (m, i)
     finally:
         pl.plaid_index_free(idx)
+
+
+@pytest.mark.parametrize("P", [40_961, 600_001])
+@pytest.mark.parametrize("near,apart", [(2, 1), (2, 16), (3, 400), (7, 170), (7, 171)])
+def test_scores_closer_than_a_digit(P, near, apart):
+    """`near` scores, `apart` representable numbers from one to the next and many passages each: up to 1023 between the first and the
+    last they are told apart by their lowest bits, here so that these come round from 1023 to 0 between the first and the second."""
+    import paper_2205_09707_amd as pl
+    C = 64
+    q = torch.zeros(128, device="cuda")
+    q[0] = 1.0
+    cen = torch.zeros(C, 128, device="cuda")
+    # products with q are exact, and 32 of them lie in [16, 32), whose spacing is 2^-19: 1024 of those is a multiple of 2^-9
+    cen[:near, 0] = 1.0 - 2.0 ** -14 + 2.0 ** -24 * (apart // 2) - 2.0 ** -24 * apart * torch.arange(near, device="cuda")
+    cen[near, 0] = 0.3  # the survivor far below stretches the bins
+    cen[near + 1:, 1] = 1.0
+    codes = (torch.arange(P, device="cuda") * 7919 % 1009 % near).int()
+    codes[::97] = near
+    offsets = torch.arange(P + 1, dtype=torch.int64, device="cuda")
+    ivf_offsets, ivf_pids = pl.plaid_build_ivf(codes, offsets, C)
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
+              "residuals": torch.full((P, 32), 27, dtype=torch.uint8, device="cuda"),
+              "bucket_weights": torch.tensor([-0.02, -0.01, 0.01, 0.02], device="cuda")}
+    idx = pl.plaid_index_from_view(arrays, 2, device=0, copy=False)
+    try:
+        order = torch.argsort(codes, stable=True)  # the centroids' numbers fall with their scores
+        per = int((codes == 0).sum())
+        for nq in (1, 32):
+            Q = q.expand(nq, 32, 128).contiguous()
+            for m in (1, 5000, per - 1, per, per + 1, per + 5000, near * per - 3, P // 2, P - 1):
+                _, _, dbg = pl.plaid_search_debug(idx, Q, 8, 0.25, m, 1, want=["sel2_ids", "n2"])
+                for i in {0, nq - 1}:
+                    assert int(dbg["n2"][i]) == m
+                    kept = torch.sort(dbg["sel2_ids"][i, :m].long()).values
+                    assert torch.equal(kept, torch.sort(order[:m]).values), (m, nq, i)
+    finally:
+        pl.plaid_index_free(idx)
