@@ -958,7 +958,7 @@ static_assert(SEL2_SUB >> S2_COARSE_SHIFT > 0, "a coarse bin has digits");
 // numbers apart the digit is the number itself, counted by its ten lowest bits (in the half of the fine histogram's place that the
 // coarse ones leave free).  Bins that come with the fine histogram have digits near a rounding step as it is.  Two scores 16 numbers
 // apart, which share the passages of an index between them, us per search with / without: one query of 100 000 passages 223 / 409, of 400 000
-// 404 / 1091, of 8.8 M 412 / 6350, sixteen of 8.8 M 2894 / 12 310 (one score for all: 354 / 360 and 2394 / 2298).
+// 403 / 1091, of 8.8 M 404 / 6350, sixteen of 8.8 M 2915 / 12 310 (one score for all: 353 / 360 and 2344 / 2298).
 static_assert(S2_COPIES * S2_COARSE + SEL2_SUB <= SEL_BINS, "both in the fine histogram's place");
 
 // Counts the lanes' digits (-1: none).  All lanes call this, one at least has a digit.
@@ -970,13 +970,22 @@ __device__ __forceinline__ void sel2_count(int32_t *lh, int digit)
     if (lane == lead) atomicAdd(&lh[digit], __popcll(same));
     else if (digit >= 0 && !((same >> lane) & 1ull)) atomicAdd(&lh[digit], 1);
 }
-// The same for the scores' digits of either kind: lh[sub], lh[SEL_BINS + low bits of ord], for the lanes with `in`.
+// The same for the scores' digits of either kind: lh[sub], lh[SEL_BINS + low bits of ord], for the lanes with `in`; the lanes of two
+// of the scores add as one each.
 __device__ __forceinline__ void sel2_count_score(int32_t *lh, bool in, int sub, uint32_t ord)
 {
-    const unsigned long long have = __ballot(in);
-    const int lane = (int)(threadIdx.x & 63), lead = (int)__builtin_ctzll(have);
-    const unsigned long long same = __ballot(in && ord == (uint32_t)__builtin_amdgcn_readlane((int)ord, lead));
-    const int n = lane == lead ? __popcll(same) : (in && !((same >> lane) & 1ull) ? 1 : 0);
+    const int lane = (int)(threadIdx.x & 63);
+    unsigned long long left = __ballot(in);
+    int n = in ? 1 : 0;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        if (left) {  // uniform
+            const int lead = (int)__builtin_ctzll(left);
+            const bool equal = ord == (uint32_t)__builtin_amdgcn_readlane((int)ord, lead);
+            const unsigned long long same = left & __ballot(equal);
+            if (in && equal) n = lane == lead ? __popcll(same) : 0;
+            left &= ~same;
+        }
     if (n) {
         atomicAdd(&lh[sub], n);
         atomicAdd(&lh[SEL_BINS + (ord & (SEL2_SUB - 1))], n);
