@@ -1495,13 +1495,14 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_cut_kernel(const uint64_t
         uint64_t *my_left = left + (int64_t)seg * left_stride;
         unsigned long long any = 0, none = 0;
         int parity = 0;
-        for (int64_t s0 = (int64_t)blockIdx.x * STEP; s0 < n; s0 += (int64_t)n_work * STEP, parity ^= 1) {  // uniform
+        // (positions in 32 bits, n + the step of all workgroups < 2^32: with 64 LEVEL 2 spilled a register)
+        for (uint32_t s0 = blockIdx.x * STEP; s0 < (uint32_t)n; s0 += (uint32_t)n_work * STEP, parity ^= 1) {  // uniform
             uint64_t key[GROUPS];
             int cls[GROUPS];
 #pragma unroll
             for (int u = 0; u < GROUPS; ++u) {
-                const int64_t i = s0 + u * FIN_THREADS + threadIdx.x;
-                key[u] = i < n ? bl[i] : 0ull;
+                const uint32_t i = s0 + u * FIN_THREADS + threadIdx.x;
+                key[u] = i < (uint32_t)n ? bl[i] : 0ull;
             }
 #pragma unroll
             for (int u = 0; u < GROUPS; ++u) {
@@ -1509,7 +1510,7 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_cut_kernel(const uint64_t
                               : tie        ? (int)((uint32_t)key[u] >> id_shift)
                               : near       ? (int)((uint32_t)(key[u] >> 32) - ord_min)
                                            : sel2_sub_bin(key[u], mt, bin, bin_shift);
-                cls[u] = s0 + u * FIN_THREADS + threadIdx.x < n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
+                cls[u] = s0 + u * FIN_THREADS + threadIdx.x < (uint32_t)n ? (d < bstar ? 0 : (d == bstar ? 1 : 2)) : 2;
             }
             sel2_place<FIN_THREADS, GROUPS, true>(key, cls, parity, place, &s->n_sure, LEVEL == 1 ? &s->n_b1 : &s->n_b2, o, my_left, any, none);
         }

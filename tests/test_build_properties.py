@@ -36,6 +36,7 @@ KERNELS = {
     "s2_candidates_kernel": ("k_stage2.hip", 64, 8 << 10),
     "s2_union_wide_kernel": ("k_stage2.hip", 128, 80 << 10),       # two workgroups of 1024 threads per CU
     "s2_stream_kernel": ("k_stage2.hip", 128, 40 << 10),
+    "ci_few_kernelILb0E": ("k_ci.hip", 64, 8 << 10),               # eight waves per SIMD
     "ci_list_kernelILb0E": ("k_ci.hip", 96, 8 << 10),              # five waves per SIMD; wave-private LDS areas
     "decompress_maxsim_kernelILi2ELb0ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),   # four waves per SIMD (query operands in LDS)
     "decompress_maxsim_kernelILi1ELb0ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
@@ -46,6 +47,11 @@ KERNELS = {
     "maxsim_list_kernelILi1ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
     "maxsim_list_kernelILi2ELb0ELb0ELb0E": ("k_stage4.hip", 168, 53 << 10),
     "maxsim_list_kernelILi1ELb0ELb1ELb0E": ("k_stage4.hip", 168, 53 << 10),
+    # four waves per SIMD, four workgroups per CU with the 8 KB of dynamic LDS
+    "van_coarse_kernelILi2E": ("k_stage4.hip", 128, 32 << 10),
+    "van_coarse_kernelILi1E": ("k_stage4.hip", 128, 32 << 10),
+    "van_bounds_kernel": ("k_stage4.hip", 64, 1 << 10),
+    "van_band_kernel": ("k_stage4.hip", 64, 1 << 10),
     "decompress_dump_kernelILi2E": ("k_stage4.hip", 64, 8 << 10),
     "passage_offsets_kernel": ("k_stage4.hip", 64, 1 << 10),
     "van_codes_kernel": ("k_vanilla.hip", 64, 1 << 10),
@@ -56,6 +62,10 @@ KERNELS = {
     "sel2_finish_kernel": ("k_select.hip", 64, 80 << 10),
     "sel_sort_kernelILi512E": ("k_select.hip", 64, 0),             # dynamic LDS only
     "sel2_filter_kernel": ("k_select.hip", 64, 8 << 10),
+    "sel2_bins_kernel": ("k_select.hip", 80, 16 << 10),            # six waves per SIMD
+    "sel2_cut_kernelILi1E": ("k_select.hip", 64, 80 << 10),        # 1024 threads, two workgroups per CU
+    "sel2_cut_kernelILi2E": ("k_select.hip", 64, 80 << 10),
+    "bitmap_to_list_kernel": ("k_util.hip", 64, 1 << 10),          # 1024 threads, two workgroups per CU
     "encode_residuals_kernelILi2E": ("k_build.hip", 64, 0),
     "ivb_rank_kernel": ("k_build.hip", 64, 0),
     "ivb_sort_short_kernel": ("k_build.hip", 64, 32 << 10),      # a 2048-entry LDS area per wave
