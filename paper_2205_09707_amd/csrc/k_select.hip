@@ -1158,18 +1158,18 @@ __device__ __forceinline__ void sel2_digit_plan(const Sel2State *s, int &shift, 
     shift = hi + 1 - width;
 }
 
-// Digit histogram of an over-long boundary list (no-op otherwise).
+// Digit histogram of a boundary list of more than `least` keys (no-op otherwise).
 template <int LEVEL>
 __global__ __launch_bounds__(SEL_THREADS) void sel2_digit_hist_kernel(const uint64_t *__restrict__ blist,
                                                                       int64_t blist_stride, Sel2State *state,
-                                                                      int32_t *__restrict__ hist1)
+                                                                      int32_t *__restrict__ hist1, int least)
 {
     __shared__ int32_t lh[SEL_BINS];
     const int seg = blockIdx.y;
     Sel2State *s = state + seg;
     int m_rem;
     const int n = sel2_level_input<LEVEL>(s, m_rem);
-    if (n <= SEL2_DIGIT_MIN || (int64_t)blockIdx.x * SEL_THREADS >= n) return;
+    if (n <= least || (int64_t)blockIdx.x * SEL_THREADS >= n) return;
     int shift, width;
     sel2_digit_plan<LEVEL>(s, shift, width);
     for (int b = threadIdx.x; b < SEL_BINS; b += SEL_THREADS) lh[b] = 0;
@@ -1558,7 +1558,8 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
         hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.hist, b.meta, lists,
                            id_shift, second, keys2, key_stride, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
         if (second) {
-            hipLaunchKernelGGL(sel2_digit_hist_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state, b.hist2);
+            hipLaunchKernelGGL(sel2_digit_hist_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state, b.hist2,
+                               SEL_SORT_CAP);
             hipLaunchKernelGGL(sel2_cut_kernel<2>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, keys2, key_stride, b.state, b.hist2, b.hist, b.meta,
                                lists, id_shift, 0, b.blist, P, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
         }
@@ -1574,12 +1575,14 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
     // tie group also in a launch of one query, 2.8 ms for the finishing workgroup alone on 8.8 M passages)
     const int levels = P > SEL2_DIGIT_MIN ? (((nq >= 8 || lists) && P > SEL2_SECOND_MIN_PASSAGES) ? 2 : 1) : 0;
     if (levels >= 1) {
-        hipLaunchKernelGGL(sel2_digit_hist_kernel<1>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, b.blist, P, b.state, b.hist1);
+        hipLaunchKernelGGL(sel2_digit_hist_kernel<1>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, b.blist, P, b.state, b.hist1,
+                           SEL2_DIGIT_MIN);
         hipLaunchKernelGGL(sel2_digit_filter_kernel<1>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, b.blist, P, b.state, b.hist1,
                            out, out_stride, keys2, key_stride);
     }
     if (levels >= 2) {
-        hipLaunchKernelGGL(sel2_digit_hist_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state, b.hist2);
+        hipLaunchKernelGGL(sel2_digit_hist_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state, b.hist2,
+                           SEL2_DIGIT_MIN);
         hipLaunchKernelGGL(sel2_digit_filter_kernel<2>, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, b.state,
                            b.hist2, out, out_stride, b.blist, P);
     }
