@@ -148,7 +148,9 @@ int plaid_search_static(plaid_index *idx, const float *Q, int32_t nq, int32_t np
  *      like plaid_search returns them.
  * dbg may be NULL; its pointers are DEVICE, caller-owned and may each be NULL:
  *   cand [nq][P] ascending candidate pids, n_cand [nq];  kept_ids / kept_scores [nq][ncandidates] the candidates after
- *   step 3 in unspecified order with their pruning scores (0 for a query that needed no pruning), n_kept [nq].
+ *   step 3 in unspecified order with their pruning scores (0 for a query that needed no pruning), n_kept [nq].  Step 3
+ *   may decide most candidates by coarse scores and a bound of their error; with kept_scores it scores all of them in
+ *   full (the same candidates stay).
  * The first call synchronises the device.  Errors as plaid_search. */
 typedef struct {
     int32_t *cand;

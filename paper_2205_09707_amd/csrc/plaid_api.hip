@@ -1127,8 +1127,9 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
                                         w.keep_words, probebits, w.candbits, w.cand_words, ix->doc_offsets, ix->codes, P, ix->N, C,
                                         qmask, (uint32_t *)w.s2.qcount + 4);
         plaid_launch_bitmap_to_list(st, w.candbits, w.cand_words, P, n, cand, P, w.n2);
+        if (dbg && dbg->n_cand) HIP_TRY(hipMemcpyAsync(dbg->n_cand + q0, w.n2, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
         // more than ncandidates: scored on the embeddings of the probed lists alone, the best ncandidates stay
-        if (!dbg && vanilla_screens(n, P, pl.nd) && ix->scq_form == PLAID_SCQ_SPLIT16 && !plaid_wide(C, ix->N)) {
+        if (!(dbg && dbg->kept_scores) && vanilla_screens(n, P, pl.nd) && ix->scq_form == PLAID_SCQ_SPLIT16 && !plaid_wide(C, ix->N)) {
             // coarsely first, and in full where that does not decide (the caller who asks for the kept scores gets full ones)
             int32_t *open = cand + (int64_t)n * P;  // [n][P], the rest of the boundary list's memory
             plaid_launch_vanilla_coarse(st, Qc, w.S, C, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, probebits,
@@ -1157,7 +1158,6 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
             if (dbg->cand)
                 HIP_TRY(hipMemcpy2DAsync(dbg->cand + (int64_t)q0 * P, (size_t)P * 4, cand, (size_t)P * 4, (size_t)P * 4, n,
                                          hipMemcpyDeviceToDevice, st));
-            if (dbg->n_cand) HIP_TRY(hipMemcpyAsync(dbg->n_cand + q0, w.n2, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
             if (dbg->kept_ids || dbg->kept_scores || dbg->n_kept)
                 plaid_launch_keys_to_pairs(st, w.sel2, pl.nd, w.n3, n, ncandidates,
                                            dbg->kept_ids ? dbg->kept_ids + (int64_t)q0 * ncandidates : nullptr,

@@ -141,7 +141,8 @@ LDS_PIECES = [
                    "offsetof(ProbeScratch<true>, Qs)", "offsetof(ProbeScratch<true>, block)", "offsetof(ProbeScratch<true>, row)",
                    "offsetof(ProbeScratch<true>, idl)", "offsetof(ProbeScratch<false>, block)", "offsetof(ProbeScratch<false>, idl)"]),
     ("k_stage2.hip", ["offsetof(S2GatherScratch, list)", "offsetof(S2GatherScratch, part_max)"]),
-    ("k_stage4.hip", ["offsetof(VpArea, code)", "offsetof(VpArea, end)", "sizeof(VpArea)"]),
+    ("k_stage4.hip", ["offsetof(VpArea, code)", "offsetof(VpArea, end)", "sizeof(VpArea)", "offsetof(VpAreaOf<false>, code)",
+                      "offsetof(VpAreaOf<false>, end)", "sizeof(VpAreaOf<false>)"]),
 ]
 
 
@@ -168,6 +169,11 @@ RULES = [
     # long lists in great number only
     ("k_stage4.hip", ["s4_packed(256, 512)", "s4_packed(1024, 36)", "!s4_packed(1024, 35)", "s4_packed(96, 384)", "!s4_packed(72, 512)",
                       "!s4_packed(64, 576)", "!s4_packed(64, 2048)", "!s4_packed(16, 2304)"]),
+    # pruning by coarse scores (queries of a chunk, passages, candidates kept): the calls of test_gpu_vanilla_coarse.py
+    ("plaid_api.hip", ["vanilla_screens(16, 70000, 17000)", "!vanilla_screens(16, 70000, 17501)", "vanilla_screens(16, 66000, 1)",
+                       "vanilla_screens(6, 140000, 4096)", "!vanilla_screens(4, 140000, 4096)", "vanilla_screens(4, 200000, 3000)",
+                       "vanilla_screens(16, 140001, 9000)", "vanilla_screens(8, 131072, 64)", "vanilla_screens(16, 52000, 13000)",
+                       "vanilla_screens(16, 70000, 300)", "vanilla_screens(16, 70000, 2000)"]),
 ]
 
 

@@ -1,5 +1,8 @@
-"""Vanilla retrieval that prunes by coarse scores first gives what pruning by full scores gives (the debug form, which returns the kept
-scores, prunes by full ones): many and few candidates, ties at the cut, both code widths, chunks, residual weights below fp16's range."""
+"""Vanilla retrieval that prunes by coarse scores first keeps and gives what pruning by full scores keeps and gives (the debug form that
+returns the kept scores prunes by full ones): many and few candidates, ties at the cut, both code widths, chunks, residual weights below
+fp16's range.  Which of the calls here prune coarsely is checked by test_build_properties.py."""
+import ctypes as ct
+
 import pytest
 import torch
 
@@ -27,11 +30,26 @@ def _index(pl, P, C, nbits, scale, copies, seed):
     return idx, torch.nn.functional.normalize(Q, dim=1).reshape(16, 32, 128).contiguous(), arrays
 
 
+def _kept(pl, idx, Q, nprobe, ncand, k):
+    """What the call keeps when its scores are not asked for, as a plain call does."""
+    nq = len(Q)
+    b = {"ids": (nq, k), "cand": (nq, idx.P), "n_cand": (nq,), "kept_ids": (nq, ncand), "n_kept": (nq,)}
+    b = {n: torch.zeros(shape, dtype=torch.int32, device="cuda") for n, shape in b.items()}
+    b["scores"] = torch.zeros((nq, k), device="cuda")
+    dbg = pl.plaid.plaid_vanilla_debug(**{n: b[n].data_ptr() for n in ("cand", "n_cand", "kept_ids", "n_kept")})
+    rc = pl.load_library().plaid_search_vanilla(idx.handle, ct.c_void_p(Q.data_ptr()), nq, nprobe, ncand, k, ct.c_void_p(b["ids"].data_ptr()),
+                                                ct.c_void_p(b["scores"].data_ptr()),
+                                                ct.c_void_p(torch.cuda.current_stream().cuda_stream), ct.byref(dbg))
+    assert rc == 0, pl.plaid_last_error()
+    return b
+
+
 @pytest.mark.parametrize("P,C,nbits,scale,copies,nprobe,ncand,chunk", [
     (70_000, 2048, 2, 0.02, 1, 4, 2000, None),
     (70_000, 2048, 1, 0.02, 1, 2, 17_000, None),
     (66_000, 1000, 2, 0.02, 3, 1, 1, None),        # every passage three times: ties at the cut
-    (72_000, 1000, 2, 0.1, 4, 3, 4096, 8),         # ... in chunks, which fall below the rule
+    (140_000, 1000, 2, 0.1, 4, 3, 4096, 6),        # ... in chunks of 6, 6 and 4, the last of which falls below the rule
+    (200_000, 1000, 1, 0.1, 4, 3, 3000, 6),        # ... none does
     (70_000, 512, 2, 1e-5, 1, 1, 300, None),       # weights that fp16 cannot hold: the coarse scores miss the residuals
     (140_001, 70_000, 2, 0.02, 1, 1, 9000, None),  # some queries have no more candidates than that
 ])
@@ -44,9 +62,39 @@ def test_coarse_pruning_keeps_what_full_scores_keep(P, C, nbits, scale, copies, 
         k = min(ncand, 500)
         ids, scores = pl.plaid_search_vanilla(idx, Q, nprobe, ncand, k)
         want_ids, want_scores, dbg = pl.plaid_search_vanilla(idx, Q, nprobe, ncand, k, debug=True)
+        got = _kept(pl, idx, Q, nprobe, ncand, k)
         torch.cuda.synchronize()
         print("candidates", dbg["n_cand"].tolist())
         assert torch.equal(ids, want_ids) and torch.equal(scores, want_scores)
+        assert torch.equal(got["ids"], want_ids) and torch.equal(got["scores"], want_scores)
+        assert torch.equal(got["n_cand"], dbg["n_cand"]) and torch.equal(got["n_kept"], dbg["n_kept"])
+        assert bool((dbg["n_cand"] > ncand).any())  # (something is pruned)
+        for q in range(len(Q)):
+            n = int(dbg["n_kept"][q])
+            assert n == min(ncand, int(dbg["n_cand"][q]))
+            assert torch.equal(got["cand"][q, :int(got["n_cand"][q])], dbg["cand"][q, :int(got["n_cand"][q])])
+            assert torch.equal(torch.sort(got["kept_ids"][q, :n]).values, torch.sort(dbg["kept_ids"][q, :n]).values), q
+    finally:
+        pl.plaid_index_free(idx)
+
+
+def test_coarse_scores_decide_most_candidates():
+    """The full scores of the few that they leave open take less time than the coarse scores of all."""
+    import paper_2205_09707_amd as pl
+    from torch.profiler import ProfilerActivity, profile
+    idx, Q, _ = _index(pl, 200_000, 2048, 2, 0.02, 1, 9)
+    try:
+        pl.plaid_search_vanilla(idx, Q, 4, 2000, 100)
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            pl.plaid_search_vanilla(idx, Q, 4, 2000, 100)
+            torch.cuda.synchronize()
+        us = {e.key: e.device_time_total for e in p.key_averages()}
+        if not us:
+            pytest.skip("no kernel times from torch's profiler here")
+        coarse = sum(t for name, t in us.items() if "van_coarse_kernel" in name)
+        full = sum(t for name, t in us.items() if "maxsim_list_kernel<2, true" in name)
+        assert 0 < full < 0.5 * coarse
     finally:
         pl.plaid_index_free(idx)
 
