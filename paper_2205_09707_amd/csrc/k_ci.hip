@@ -181,8 +181,9 @@ __global__ __launch_bounds__(256) void ci_list_kernel(const float *__restrict__ 
     ci_list_body<WIDE, CI_PPW>(S, C, doc_offsets, codes, in_keys, in_stride, in_counts, nq, gx, spread, out_keys, out_stride);
 }
 // Launches that are over in two rounds of waves: a passage each, so that none waits for another; more waves than that gain from the shared
-// chain of loads.  us of a launch with two / one, 30 to 90 tokens: one query of 256 passages 6.6 / 5.1, of 1024 6.6 / 4.9, of 4096 7.2 / 6.0, four of 1024
-// 7.8 / 6.3, eight 9.2 / 8.6, sixteen 15.8 / 14.5, 64 of 256 16.6 / 15.3, 23 of 1000 (8 to 180 tokens) 19.6 / 19.7, 256 of 256 47.9 / 49.7.
+// chain of loads.  us of a launch with two / one, 30 to 90 tokens: one query of 256 passages 6.6 / 5.1, of 1024 6.6 / 4.9, of 4096
+// 7.2 / 6.0, four of 1024 7.8 / 6.3, eight 9.2 / 8.6, sixteen 15.8 / 14.5, 64 of 256 16.6 / 15.3, 23 of 1000 (8 to 180 tokens) 19.6
+// / 19.7, 256 of 256 47.9 / 49.7.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void ci_few_kernel(const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
                                                       const int32_t *__restrict__ codes, const uint64_t *__restrict__ in_keys, int64_t in_stride,

@@ -1264,8 +1264,8 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
     const bool takes = form == PLAID_SCQ_SPLIT16 && plaid_scq16_takes_queries(C, nq, zero_words);
     if (!(phases & PLAID_STAGE1_SCORES)) {
     } else if (form == PLAID_SCQ_SPLIT16) {
-        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, grouped ? groupmax : nullptr, score_clocks, takes ? Q : nullptr, takes ? zero : nullptr,
-                           takes ? zero_words : 0);
+        plaid_launch_scq16(st, A16, C, Qx, nq, t_cs, S, keepbits, ambbits, keep_words, tmx, grouped ? groupmax : nullptr, score_clocks,
+                           takes ? Q : nullptr, takes ? zero : nullptr, takes ? zero_words : 0);
     } else if (matrix_form) {
         if (nq == 1)
             hipLaunchKernelGGL(scq_mfma_kernel<1>, dim3(1, nblk), dim3(SM_THREADS), 0, st, centroids, C, Q, nq, t_cs, S, keepbits,

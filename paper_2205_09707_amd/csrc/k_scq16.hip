@@ -171,9 +171,10 @@ __device__ __forceinline__ float scq16_reduce(const scq16_floatx16 (&acc)[NT], f
 // of stores between a request for operands and the wait for them is the same on every path: the memory counter retires
 // in order, and a wait sized for the path with the fewest stores would sit out the score stores of the others.
 template <int NT, bool WHOLE, bool GROUPS>
-__device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], float (&gmax)[2][H16_WAVES][QLEN], const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16,
-                                           int64_t C, const scq16_half8 *__restrict__ B16, const float *__restrict__ Q, int q_begin, int q_end, float t_lo,
-                                           float t_hi, float *__restrict__ S, uint32_t *__restrict__ keepbits,
+__device__ __forceinline__ void scq16_body(scq16_half8 (&Bs)[2][H16_TILE_VEC], float (&gmax)[2][H16_WAVES][QLEN],
+                                           const int (&nvalid)[NT], const scq16_half8 *__restrict__ A16, int64_t C,
+                                           const scq16_half8 *__restrict__ B16, const float *__restrict__ Q, int q_begin,
+                                           int q_end, float t_lo, float t_hi, float *__restrict__ S, uint32_t *__restrict__ keepbits,
                                            uint32_t *__restrict__ ambbits, int64_t keep_words, float *__restrict__ tilemax,
                                            float *__restrict__ groupmax)
 {
@@ -324,9 +325,11 @@ __global__ __launch_bounds__(H16_THREADS, NT == 2 ? 2 : 4) void scq16_kernel(
     }
     // (the barriers inside are reached by all four waves in either instance: both run the same loop over the queries)
     if (whole)
-        scq16_body<NT, true, GROUPS>(Bs, gmax, nvalid, A16, C, B16, Q, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
+        scq16_body<NT, true, GROUPS>(Bs, gmax, nvalid, A16, C, B16, Q, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits,
+                                     keep_words, tilemax, groupmax);
     else
-        scq16_body<NT, false, GROUPS>(Bs, gmax, nvalid, A16, C, B16, Q, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits, keep_words, tilemax, groupmax);
+        scq16_body<NT, false, GROUPS>(Bs, gmax, nvalid, A16, C, B16, Q, q_begin, q_end, t_lo, t_hi, S, keepbits, ambbits,
+                                     keep_words, tilemax, groupmax);
     if (clocks && threadIdx.x == 0) {
         atomicAdd(&clocks[0], (unsigned long long)(clock64() - sc0));
         atomicAdd(&clocks[1], (unsigned long long)(wall_clock64() - rt0));
@@ -392,8 +395,8 @@ bool plaid_scq16_takes_queries(int64_t C, int nq, int64_t zero_words)
 // Queries per workgroup, which walks them one after the other: with few workgroups that chain is the launch's time, with many its centroid operands
 // should be loaded for as many queries as leave the chip filled several times over.  Up to 512 workgroups of one query run at once.
 // us of a launch with 1 / 2 / 4 / 8 queries per workgroup: 8 queries of 1024 centroids 7 / 11 / 17 / 27, 200 17 / 15 / 18 / 29; 23 of 10 007
-// 16 / 14 / 17 / 28, 50 28 / 25 / 24 / 31; 4 of 32 768 10 / 12 / 17 / 17, 9 20 / 17 / 19 / 30, 40 64 / 53 / 50 / 55; 8 of 65 536 32 / 26 / 25 / 33, 16 58 / 48 /
-// 42 / 43; 6 of 262 144 143 / 105 / 79 / 60; 256 of 16 384 189 / 156 / 141 / 138.
+// 16 / 14 / 17 / 28, 50 28 / 25 / 24 / 31; 4 of 32 768 10 / 12 / 17 / 17, 9 20 / 17 / 19 / 30, 40 64 / 53 / 50 / 55; 8 of 65 536 32
+// / 26 / 25 / 33, 16 58 / 48 / 42 / 43; 6 of 262 144 143 / 105 / 79 / 60; 256 of 16 384 189 / 156 / 141 / 138.
 static constexpr int scq16_queries(int64_t nq, int64_t gx)
 {
     const int64_t work = nq * gx, full = (work + 2047) / 2048, half = (work + 1023) / 1024, once = (work + 511) / 512;

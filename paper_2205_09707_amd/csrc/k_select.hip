@@ -1123,7 +1123,8 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
 __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                   const uint32_t *__restrict__ candbits, int64_t cand_words,
                                                                   int64_t P, int32_t m, const S2Meta *__restrict__ meta,
-                                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out, int64_t out_stride,
+                                                                  const int32_t *__restrict__ hist, Sel2State *state,
+                                                                  uint64_t *__restrict__ out, int64_t out_stride,
                                                                   uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
 {
     sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists, 0,

@@ -1071,8 +1071,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     const int64_t *__restrict__ ivf_offsets, const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
     const int32_t *__restrict__ codes, const int64_t *__restrict__ doc_offsets, int64_t P, const S2Meta *__restrict__ meta,
-    const int32_t *__restrict__ kept_ids, const float *__restrict__ T, uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
-    int32_t *__restrict__ hist, Sel2State *__restrict__ state,
+    const int32_t *__restrict__ kept_ids, const float *__restrict__ T, uint32_t *__restrict__ candbits, int64_t cand_words,
+    uint64_t *__restrict__ keys2, int64_t key_stride, int32_t *__restrict__ hist, Sel2State *__restrict__ state,
     uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
     int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
     int steps, int32_t m, int first_batch, unsigned main_blocks, uint32_t tall)
@@ -1128,9 +1128,9 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     }
     // This instance's queries, from the lists the probe kernel made: class 1 (1..31 survivors) or 2 (32..63), and with the
     // 32-bit instance class 0 (none) unless s2_union_wide_kernel has produced its candidate and empty-bag words (mode bit
-    // 0).  ALL: every query of these classes.  Bit 3: see the launch.  Queries with more survivors belong to the workgroups above.  Consecutive workgroups take
-    // consecutive queries of one passage range: all queries of a chunk advance together, so that each has a threshold to
-    // prune with after its first ranges, and the bitmap rows of the range are shared in the caches.
+    // 0).  ALL: every query of these classes.  Bit 3: see the launch.  Queries with more survivors belong to the workgroups above.
+    // Consecutive workgroups take consecutive queries of one passage range: all queries of a chunk advance together, so that each
+    // has a threshold to prune with after its first ranges, and the bitmap rows of the range are shared in the caches.
     const int cls = sizeof(SetT) == 4 ? 1 : 2;
     static_assert(!ALL || sizeof(SetT) == 8, "31 slots do not do for every query");
     const bool single = ALL && (mode & 4);  // one query: number 0, whatever its class
@@ -1637,17 +1637,20 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // Passages per wave and step: 2048, fewer (512 at least, but see below) for indexes of so few passages that a wave's own chain of steps is all
     // that counts and the chip has room for more waves, up to 400 of a query: beyond, what they add to one histogram and score before there is a
     // threshold costs more.  us per search with 2048 / 1024 / 512 / 256: one query of 10 000 passages 77 / 69 / 65 / 66, of 40 000 73 / 70 /
-    // 70 / 73, of 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 / 129 / 148), of a million
-    // 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of 400 000 120 / 120 / 131 / 151.
+    // 70 / 73, of 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 /
+    // 129 / 148), of a million 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of
+    // 400 000 120 / 120 / 131 / 151.
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
     while (len_log > 9 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
     // An ndocs so large that a wave has several batches to score in any case (one query of 400 000 passages, ndocs 100 000:
     // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
-    // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
+    // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter
+    // ranges while the chip has room.
     while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
-    // A small collection of which a large share is kept: down to 128, while a wave's share of m is more than 64.  us per search of 10 000 passages, ndocs 4096,
-    // with 512 / this: one query 134 / 105, four 155 / 125, fifteen 207 / 177; of 15 000 112 / 102, 138 / 126, 194 / 184.
+    // A small collection of which a large share is kept: down to 128, while a wave's share of m is more than 64.  us per search of
+    // 10 000 passages, ndocs 4096, with 512 / this: one query 134 / 105, four 155 / 125, fifteen 207 / 177; of 15 000 112 / 102,
+    // 138 / 126, 194 / 184.
     while (len_log > 7 && ((int64_t)m << len_log) / P > 64 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
     const int steps = s2_steps(nq, waves);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
@@ -1686,13 +1689,13 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int nqx = spread ? (nq | 1) : (nq + 7) & ~7;
     const int copies = spread && nq * blocks > 64 ? (4ll * m >= 3 * ((P + (1ll << len_log) - 1) >> len_log) ? 8 | 64 : 8) : 0;
     const int own = copies | given;
-    // Few workgroups, at most S2_FITS_BLOCKS: the 64-bit instance alone, taking every query (same sets, same scores, one launch less, and no waiting of one class for the other: eight queries of
-    // 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 / 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 ->
-    // 65 / 70); with twice the workgroups, so that queries with more slots than a wave's area holds can have two (mode bit 5), or
-    // four times, where they all run at once, for four areas (bit 7; four queries of 400 000 passages, even lists, 62 survivors 192 ->
-    // 148 us).  More: the 32-bit
-    // instance's scoring wins (eight of 2 M: 232 with two, 327 with one).  The line: 768 and 1024 make no difference beyond
-    // 2 % (16 of 400 000: 166 / 164 us per search, 32 and 40 of 200 000: 146 / 143 and 155 / 152, eight of 1 M: 160 / 160).
+    // Few workgroups, at most S2_FITS_BLOCKS: the 64-bit instance alone, taking every query (same sets, same scores, one launch
+    // less, and no waiting of one class for the other: eight queries of 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 /
+    // 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 -> 65 / 70); with twice the workgroups, so that queries with
+    // more slots than a wave's area holds can have two (mode bit 5), or four times, where they all run at once, for four areas (bit
+    // 7; four queries of 400 000 passages, even lists, 62 survivors 192 -> 148 us).  More: the 32-bit instance's scoring wins
+    // (eight of 2 M: 232 with two, 327 with one).  The line: 768 and 1024 make no difference beyond 2 % (16 of 400 000: 166 / 164
+    // us per search, 32 and 40 of 200 000: 146 / 143 and 155 / 152, eight of 1 M: 160 / 160).
     const bool fits = blocks * nqx <= S2_FITS_BLOCKS;
     if (nq < 8 || fits) {
         const bool fits4 = 4 * blocks * nqx <= 256 * S2_UNIT_BLOCKS;
@@ -1700,7 +1703,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         const int64_t all = fits4 ? 4 * blocks : (fits ? 2 * blocks : blocks);
         // (where the second areas do not come from workgroups that run at once, queries of 27 to 36 lists are better off with the
         // planes for them: twelve of 400 000 passages, even lists, K = 33 211 -> 164 us)
-        if (tall && fits && 2 * blocks * nqx > 256 * S2_UNIT_BLOCKS) S2_INVERT(11, unsigned long long, false, true, true, mode, nqx, all, gather_tall);
+        if (tall && fits && 2 * blocks * nqx > 256 * S2_UNIT_BLOCKS)
+            S2_INVERT(11, unsigned long long, false, true, true, mode, nqx, all, gather_tall);
         else if (shift == 11) S2_INVERT(11, unsigned long long, false, true, false, mode, nqx, all, gather);
         else S2_INVERT(13, unsigned long long, false, true, false, mode, nqx, all, gather);
     } else {

@@ -156,11 +156,13 @@ __device__ __forceinline__ void s4_stage_query(const float *__restrict__ Qq, s4_
 // Residual dot products of 32 tokens (packed words rw, this half's) with the 32 query tokens: acc += leading products, acx +=
 // cross terms, scaled by 2^11.  TOKENS_A: rows = tokens, columns = query tokens; else the other way round.  The query
 // operands are read from LDS in every step, through an index the compiler cannot tell from the last call's (kept across
-// calls they would take 64 registers), but for the first H1 of the leading and H2 of the trailing terms, which the caller holds.  AHEAD: they and the table entries are requested one step of 16 dimensions ahead, for
-// which a kernel of four waves per SIMD lacks the registers.
+// calls they would take 64 registers), but for the first H1 of the leading and H2 of the trailing terms, which the caller holds.
+// AHEAD: they and the table entries are requested one step of 16 dimensions ahead, for which a kernel of four waves per SIMD lacks
+// the registers.
 template <int NBITS, bool TOKENS_A, bool AHEAD, int H1, int H2>
 __device__ __forceinline__ void s4_products(const uint32_t (&rw)[2 * NBITS], const typename S4Entry<NBITS>::type *hlut,
-                                            const s4_half8 (&qs)[2][8][64], const s4_half8 *held1, const s4_half8 *held2, int lane, floatx16 &acc, floatx16 &acx)
+                                            const s4_half8 (&qs)[2][8][64], const s4_half8 *held1, const s4_half8 *held2, int lane,
+                                            floatx16 &acc, floatx16 &acx)
 {
     int ql = lane;
     asm volatile("" : "+v"(ql));
@@ -462,12 +464,13 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
 // scored: their keys get score 0.  cand: [q][cand_stride] ascending candidate pids, in_counts[q] of them; out_keys[q][j] =
 // key of cand[q][j].  The candidates of different queries are mostly the same passages: workgroup L takes query
 // L / 8 % nq and a share of the (L % 8)-th eighth of its candidates, so that the queries read a passage at about the same
-// time through the same partition's cache (16 queries: the counter of fetches, which sees half of the bytes, shows 17 GB with a grid column per query, 1.2 GB this way).
-// 16 queries of 400 000 candidates: 8.4 -> 4.9 ms, of which listing the tokens takes 1.9 (scalar and vector instructions) and
-// the products 2.0 (matrix instructions 1.7).  The list holds a token's number itself, unless 32 bits do not hold that (WIDE), and its lanes are taken from the
-// mask as it is: the pruning by coarse scores of 16 queries 3.10 -> 2.84 ms (before: rows within the passage, and its first token per group of eight positions).
-// (Rows of S_cq requested a step ahead: 2.96 -> 3.07 ms, 144 queries of 1024 passages 414 -> 426 us; eight passages at a time: the same; a
-// table entry per half byte in banks of a lane's own, so that look-ups never conflict: 3 to 5 % slower, its reads being twice as many.)
+// time through the same partition's cache (16 queries: the counter of fetches, which sees half of the bytes, shows 17 GB with a
+// grid column per query, 1.2 GB this way).  16 queries of 400 000 candidates: 8.4 -> 4.9 ms, of which listing the tokens takes 1.9
+// (scalar and vector instructions) and the products 2.0 (matrix instructions 1.7).  The list holds a token's number itself, unless
+// 32 bits do not hold that (WIDE), and its lanes are taken from the mask as it is: the pruning by coarse scores of 16 queries 3.10
+// -> 2.84 ms (before: rows within the passage, and its first token per group of eight positions).  (Rows of S_cq requested a step
+// ahead: 2.96 -> 3.07 ms, 144 queries of 1024 passages 414 -> 426 us; eight passages at a time: the same; a table entry per half
+// byte in banks of a lane's own, so that look-ups never conflict: 3 to 5 % slower, its reads being twice as many.)
 #define VP_GROUP 4
 #define VP_CAP 288  // listed positions: what is left of the last list (< 32), one chunk of 64 and its padding always fit
 #define VP_SLOTS 16
@@ -500,8 +503,9 @@ __device__ __forceinline__ void vp_sync()  // orders a wave's LDS accesses
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// RN: as above; WIDE: 2^25 centroids or 2^32 tokens are not enough.  COARSE (with FILTER): the leading products only, a third of the matrix instructions and half of the table
-// look-ups; every score lies within the bound that van_bounds_kernel computes of the full one.
+// RN: as above; WIDE: 2^25 centroids or 2^32 tokens are not enough.  COARSE (with FILTER): the leading products only, a third of
+// the matrix instructions and half of the table look-ups; every score lies within the bound that van_bounds_kernel computes of the
+// full one.
 template <int NBITS, bool FILTER, bool RN, bool WIDE, bool COARSE>
 __device__ __forceinline__ void maxsim_list_body(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
@@ -771,7 +775,8 @@ __device__ __forceinline__ void maxsim_list_body(
                     }
                     const bool listed = __builtin_amdgcn_inverse_ballot_w64(mask);
                     const int n = __popcll(mask);
-                    const int at = FILTER ? (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)have))
+                    const int at = FILTER ? (int)__builtin_amdgcn_mbcnt_hi(
+                                                (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)have))
                                           : have + lane;
                     const uint32_t row0 = WIDE ? (uint32_t)src : (uint32_t)t0[k] + (uint32_t)src;
                     if (listed) A.code[at] = cc, A.row[at] = row0 + (uint32_t)lane;
@@ -839,7 +844,9 @@ __global__ __launch_bounds__(256, 3) void maxsim_list_kernel(
     const int32_t *__restrict__ in_counts, int32_t ncandidates, int nq, int gx, int spread, uint64_t *__restrict__ out_keys,
     int64_t out_stride)
 {
-    maxsim_list_body<NBITS, FILTER, RN, WIDE, false>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits, keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys, out_stride);
+    maxsim_list_body<NBITS, FILTER, RN, WIDE, false>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits,
+                                                      keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys,
+                                                      out_stride);
 }
 template <int NBITS>
 __global__ __launch_bounds__(256, 4) void van_coarse_kernel(
@@ -850,7 +857,9 @@ __global__ __launch_bounds__(256, 4) void van_coarse_kernel(
     const int32_t *__restrict__ in_counts, int32_t ncandidates, int nq, int gx, int spread, uint64_t *__restrict__ out_keys,
     int64_t out_stride)
 {
-    maxsim_list_body<NBITS, true, false, false, true>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits, keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys, out_stride);
+    maxsim_list_body<NBITS, true, false, false, true>(Q, S, C, doc_offsets, codes, residuals, weights, inv_norm, in_keys, in_stride, probebits,
+                                                      keep_words, cand, cand_stride, in_counts, ncandidates, nq, gx, spread, out_keys,
+                                                      out_stride);
 }
 
 // Pruning by coarse scores.  Most candidates lie far from the cut: scores from the leading products decide them, and only

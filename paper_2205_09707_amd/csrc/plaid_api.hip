@@ -919,8 +919,9 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         STAMP();
         // stage 1: S_cq (Eq. 2), pruning map (Eq. 5), probes and candidates (Section 4.1)
         for (int phase = PLAID_STAGE1_PREP; phase <= PLAID_STAGE1_PROBES; phase <<= 1) {
-            plaid_launch_stage1(st, phase, ix->centroids, C, Qc, w.Qd, form, ix->scq_matrix_form != 0, ix->A16, n, t_cs, nprobe, w.S, w.keepbits, w.ambbits,
-                                w.keep_words, w.tilemax, w.groupmax, (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed,
+            plaid_launch_stage1(st, phase, ix->centroids, C, Qc, w.Qd, form, ix->scq_matrix_form != 0, ix->A16, n,
+                                t_cs, nprobe, w.S, w.keepbits, w.ambbits, w.keep_words, w.tilemax, w.groupmax,
+                                (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed,
                                 w.uniq, w.uniq_stride, w.n_uniq, w.s2, w.probe_scratch, w.probe_scratch_bytes,
                                 timing ? ix->score_clocks : nullptr);
             STAMP();
@@ -1111,8 +1112,9 @@ extern "C" int plaid_search_vanilla(plaid_index *ix, const float *Q, int32_t nq,
         const float *Qc = Q + (int64_t)q0 * QLEN * DIM;
         // Eq. 2 and the probes, as in plaid_search (no pruning map is needed: t_cs = +infinity)
         for (int phase = PLAID_STAGE1_PREP; phase <= PLAID_STAGE1_PROBES; phase <<= 1)
-            plaid_launch_stage1(st, phase, ix->centroids, C, Qc, w.Qd, form, ix->scq_matrix_form != 0, ix->A16, n, INFINITY, nprobe, w.S, w.keepbits, w.ambbits,
-                                w.keep_words, w.tilemax, w.groupmax, (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed, w.uniq,
+            plaid_launch_stage1(st, phase, ix->centroids, C, Qc, w.Qd, form, ix->scq_matrix_form != 0, ix->A16, n,
+                                INFINITY, nprobe, w.S, w.keepbits, w.ambbits, w.keep_words, w.tilemax, w.groupmax,
+                                (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed, w.uniq,
                                 w.uniq_stride, w.n_uniq, w.s2, w.probe_scratch, w.probe_scratch_bytes);
         // candidate passages from the embedding lists of the probed centroids (Section 4.1)
         uint32_t *probebits = w.ambbits;       // free once the probes are known
@@ -1270,8 +1272,9 @@ extern "C" int plaid_assign_centroids(const float *centroids, int64_t C, const f
     auto run = [&](const float *src, int64_t ng, int32_t *dst, int64_t cnt) -> int {
         const Workspace w = carve((char *)ws.p, &fake, (int)ng, pl);
         for (int phase = PLAID_STAGE1_PREP; phase <= PLAID_STAGE1_PROBES; phase <<= 1)
-            plaid_launch_stage1(st, phase, centroids, C, src, w.Qd, fake.scq_form, fake.scq_matrix_form != 0, nullptr, (int)ng, INFINITY, 1, w.S, w.keepbits,
-                                w.ambbits, w.keep_words, w.tilemax, nullptr, (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed,
+            plaid_launch_stage1(st, phase, centroids, C, src, w.Qd, fake.scq_form, fake.scq_matrix_form != 0, nullptr, (int)ng,
+                                INFINITY, 1, w.S, w.keepbits, w.ambbits, w.keep_words, w.tilemax, nullptr,
+                                (uint32_t *)w.zero_base, (int64_t)(w.zero_bytes / 4), w.probed,
                                 w.uniq, w.uniq_stride, w.n_uniq, w.s2, w.probe_scratch, w.probe_scratch_bytes);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipMemcpyAsync(dst, w.probed, (size_t)cnt * 4, hipMemcpyDeviceToDevice, st));  // probed is [group][32][1]

@@ -158,9 +158,10 @@ int plaid_scq_matrix_form_ok(hipStream_t st, int *ok);  // returns a hipError_t 
 #define PLAID_SCQ_MATRIX 1
 #define PLAID_SCQ_SPLIT16 2
 void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int64_t C, const float *Q, void *Qx, int form,
-                         bool matrix_ok /* plaid_scq_matrix_form_ok */, const void *A16, int nq, float t_cs, int nprobe, float *S, uint32_t *keepbits, uint32_t *ambbits,
-                         int64_t keep_words, float *tilemax, float *groupmax /* may be null */, uint32_t *zero, int64_t zero_words, int32_t *probed,
-                         int32_t *uniq, int uniq_stride, int32_t *n_uniq, const struct Stage2Buffers &s2, void *probe_scratch,
+                         bool matrix_ok /* plaid_scq_matrix_form_ok */, const void *A16, int nq, float t_cs, int nprobe,
+                         float *S, uint32_t *keepbits, uint32_t *ambbits, int64_t keep_words, float *tilemax,
+                         float *groupmax /* may be null */, uint32_t *zero, int64_t zero_words, int32_t *probed, int32_t *uniq,
+                         int uniq_stride, int32_t *n_uniq, const struct Stage2Buffers &s2, void *probe_scratch,
                          size_t probe_scratch_bytes, unsigned long long *score_clocks = nullptr);
 size_t plaid_stage1_tilemax_bytes(int64_t C, int nq, int nprobe);
 size_t plaid_stage1_groupmax_bytes(int64_t C, int nq);
