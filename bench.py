@@ -54,9 +54,10 @@ def algorithmic_work(pl, idx, w_dev, Q, params, cfg):
     Stage 2 (Eq. 3-5), code-stream figure: per candidate passage 8 bytes of offsets + 4 bytes per token code; for a query
     none of whose centroids passes Eq. 5 every bag is empty whatever the codes hold, and only the candidate bitmap is read
     and written.  Inverted-list figure (what the inverted form of candidate generation + stage 2 must move instead): 4 bytes
-    per entry of the inverted lists of the probed and the surviving centroids (for a query without a surviving centroid,
-    which only needs the candidate set, a list longer than a bitmap over the passages counts as that bitmap), 8 bytes
-    per key written (queries with a surviving centroid) and the candidate and empty-bag words.
+    per entry of the inverted lists of the surviving centroids, a list longer than a bitmap over the passages counting as that
+    bitmap, and 8 bytes per key kept.  (The probed lists of no survivor and the candidate words are left alone once ndocs scores are
+    known.)  A query without a survivor: the same of the probed lists, the candidate and the empty-bag words; one of more than 63
+    survivors: those, the candidates' codes and a 4-byte score word each.
     Stage 3 (Eq. 3-4): per passage kept by stage 2, 8 bytes of offsets and 4 bytes per token code, plus the 128-byte S_cq
     row of every DISTINCT centroid among those tokens (a row shared by several tokens of a query has to be fetched once).
     Stage 4 (Section 4.5, Eq. 1): per surviving passage 8 bytes of offsets and per token its 4-byte code and its packed
@@ -94,19 +95,21 @@ def algorithmic_work(pl, idx, w_dev, Q, params, cfg):
         survivors = keep.sum(dim=1).tolist()
         del b["S_cq"]
         for j in range(keep.shape[0]):
-            lists = keep[j].clone() if survivors[j] <= 63 else torch.zeros_like(keep[j])
-            lists[b["probed"][j].flatten().long()] = True
-            list_bytes = 4 * ivf_len[lists]
-            if survivors[j] == 0:
-                list_bytes = torch.clamp(list_bytes, max=bitmap_bytes)
-            inv += int(list_bytes.sum()) + 2 * bitmap_bytes
+            if 1 <= survivors[j] <= 63:
+                lists = keep[j]
+                inv += 8 * int(b["n2"][j])
+            else:
+                lists = torch.zeros_like(keep[j])
+                lists[b["probed"][j].flatten().long()] = True
+                inv += 2 * bitmap_bytes
+            inv += int(torch.clamp(4 * ivf_len[lists], max=bitmap_bytes).sum())
         for j in range(b["cand"].shape[0]):
             n = int(b["n_cand"][j])
             c = b["cand"][j, :n].long()
             if survivors[j] > 0:
                 s2 += 8 * n + 4 * int(lens[c].sum())
-                # (inverted form: one 4-byte score word per candidate; more than 63 survivors: the candidates' codes too)
-                inv += 4 * n if survivors[j] <= 63 else 4 * n + 4 * int(lens[c].sum())
+                if survivors[j] > 63:
+                    inv += 4 * n + 4 * int(lens[c].sum())
             else:
                 s2 += 8 * ((cfg.P + 31) // 32)
                 n_skipped += 1
