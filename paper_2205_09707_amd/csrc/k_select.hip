@@ -1411,10 +1411,11 @@ __global__ __launch_bounds__(FIN_THREADS, 8) void sel2_finish_kernel(const uint6
 }
 
 // Launches of few queries.  A boundary list longer than what LDS holds goes through a digit pass by all workgroups of the query.  The
-// bin filter, which every query goes through in any case, counts the pass's digits: both that it may be, the score within the bin and
-// the passage id (keys that share their score).  The pass itself, sel2_cut_kernel<1>, takes one or the other, and the last of its workgroups to
-// arrive cuts what is left; a list that is not too long the query's first workgroup cuts at once.  So a selection is two launches, of
-// which each costs 4.6 us when it waits for the one before, however little it does (a search of
+// bin filter, which every query goes through in any case, counts the pass's digits: all that it may be, the score within the bin, the
+// score itself (scores close together) and the passage id (keys that share their score).  The pass itself, sel2_cut_kernel<1>, takes
+// one of them, and the last of its workgroups to arrive cuts what is left; a list that is not too long the query's first workgroup cuts
+// at once.  So a selection is two launches (four with the second pass below), of which each costs 4.6 us when it waits for the one
+// before, however little it does (a search of
 // one query of 10 000 / 200 000 / 400 000 / 8.8 M passages took 71.8 / 81.1 / 104.5 / 279 us with the digits counted, filtered and the
 // rest cut by launches of their own, now 68.1 / 78.4 / 101.7 / 269; 23 queries of 123 457 167.0 / 162.4).  In launches of many queries
 // the other form wins: its workgroups are small, most find nothing to do, and tie groups do not meet in one histogram's word (512 of

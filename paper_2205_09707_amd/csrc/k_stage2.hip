@@ -1640,6 +1640,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     // 70 / 73, of 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 /
     // 129 / 148), of a million 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of
     // 400 000 120 / 120 / 131 / 151.
+    // Between 400 000 and a million (2048 / 1024, k 100): one query of 450 000 93 / 88, of 500 000 94 / 89, of 600 000 90 / 94, of
+    // 700 000 91 / 97, of 900 000 94 / 99; four of 450 000 113 / 116, of 500 000 112 / 118, of 600 000 117 / 126.
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
     int len_log = 11;
     while (len_log > 9 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
