@@ -394,13 +394,17 @@ bool plaid_scq16_takes_queries(int64_t C, int nq, int64_t zero_words)
 }
 // Queries per workgroup, which walks them one after the other: with few workgroups that chain is the launch's time, with many its centroid operands
 // should be loaded for as many queries as leave the chip filled several times over.  Up to 512 workgroups of one query run at once.
-// us of a launch with 1 / 2 / 4 / 8 queries per workgroup: 8 queries of 1024 centroids 7 / 11 / 17 / 27, 200 17 / 15 / 18 / 29; 23 of 10 007
-// 16 / 14 / 17 / 28, 50 28 / 25 / 24 / 31; 4 of 32 768 10 / 12 / 17 / 17, 9 20 / 17 / 19 / 30, 40 64 / 53 / 50 / 55; 8 of 65 536 32
-// / 26 / 25 / 33, 16 58 / 48 / 42 / 43; 6 of 262 144 143 / 105 / 79 / 60; 256 of 16 384 189 / 156 / 141 / 138.
+// us of a search that has little else to do (60 000 passages, ndocs 16), with 1 / 2 / 4 / 6 / 8 queries per workgroup: 8 queries of 1024
+// centroids 49 / 51 / 52 / 56 / 58, 200 100 / 97 / 98 / 100 / 103; 23 of 10 007 58 / 57 / 58 / 63 / 66, 64 96 / 92 / 93 / 91 / 95; 40 of
+// 16 384 94 / 90 / 89 / 88 / 92, 64 113 / 105 / 104 / 103 / 101; 23 of 32 768 85 / 79 / 77 / 75 / 76, 32 111 / 102 / 98 / 99 / 95; 12 of
+// 65 536 89 / 81 / 78 / 75 / 76, 16 102 / 92 / 87 / 85 / 83; of 131 072 and with 2 / 4 / as many as there are: 5 92 / 84 / 74, 8 112 / 92 / 83.
+// (33 of 16 384, whose last workgroups take few: 4 86, 5 86, in a search with more to do 122 and 125.)
 static constexpr int scq16_queries(int64_t nq, int64_t gx)
 {
     const int64_t work = nq * gx, full = (work + 2047) / 2048, half = (work + 1023) / 1024, once = (work + 511) / 512;
-    int64_t qg = once < 4 ? once : half < 4 ? 4 : half < 8 ? half : full < 8 ? 8 : full < 64 ? full : 64;
+    int64_t qg = 1;
+    while (qg <= 8 && (nq + qg - 1) / qg * gx > 512) ++qg;
+    if (qg > 8) qg = once <= 8 ? 8 : half < 8 ? half : full < 8 ? 8 : full < 64 ? full : 64;
     if (qg > nq) qg = nq;
     return (int)(qg < 1 ? 1 : qg);
 }

@@ -11,9 +11,12 @@ from test_build_properties import CSRC, HIPCC, ROOT
 
 # queries and workgroups of one (256 centroids each): queries per workgroup
 CLAIMS = ["scq16_queries(1, 1) == 1", "scq16_queries(1, 4096) == 1", "scq16_queries(512, 1) == 1", "scq16_queries(513, 1) == 2", "scq16_queries(23, 40) == 2",
-          "scq16_queries(9, 128) == 3", "scq16_queries(16, 256) == 4", "scq16_queries(40, 128) == 5", "scq16_queries(6, 1024) == 6",
+          "scq16_queries(9, 128) == 3", "scq16_queries(16, 256) == 8", "scq16_queries(40, 128) == 5", "scq16_queries(6, 1024) == 6",
           "scq16_queries(256, 64) == 8", "scq16_queries(512, 256) == 64", "scq16_queries(512, 1024) == 64", "scq16_queries(144, 1024) == 64",
-          "scq16_queries(100, 180) == 9"]
+          "scq16_queries(100, 180) == 9",
+          # all workgroups of one query at once, up to eight queries each
+          "scq16_queries(5, 512) == 5", "scq16_queries(8, 512) == 8", "scq16_queries(9, 512) == 5", "scq16_queries(12, 256) == 6",
+          "scq16_queries(32, 64) == 4", "scq16_queries(17, 256) == 5"]
 
 
 @pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
