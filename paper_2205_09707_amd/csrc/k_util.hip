@@ -121,15 +121,20 @@ __global__ __launch_bounds__(1024) void bitmap_to_list_kernel(const uint32_t *__
         int all;
         totals(before, all);
         const int at = base + before + incl - mine;  // of this lane's first bit
-        if (o && __any(v != 0u)) {                   // uniform over the wave
+        auto write = [&](int k) {                    // the ids of words k and k + 1 of the wave's
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)v, k), hi = (uint32_t)__builtin_amdgcn_readlane((int)v, k + 1);
+            const int place = __builtin_amdgcn_readlane(at, k);
+            const unsigned long long m = (unsigned long long)hi << 32 | lo;
+            if ((m >> lane) & 1ull)
+                o[place + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)((w0 + 64 * wave + k) * 32 + lane);
+        };
+        const unsigned long long some = __ballot(v != 0u);
+        unsigned long long pairs = o ? (some | some >> 1) & 0x5555555555555555ull : 0ull;
+        if (__popcll(pairs) > 16) {                  // uniform over the wave
 #pragma unroll 4
-            for (int k = 0; k < 64; k += 2) {
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)v, k), hi = (uint32_t)__builtin_amdgcn_readlane((int)v, k + 1);
-                const int place = __builtin_amdgcn_readlane(at, k);
-                const unsigned long long m = (unsigned long long)hi << 32 | lo;
-                if ((m >> lane) & 1ull)
-                    o[place + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)((w0 + 64 * wave + k) * 32 + lane);
-            }
+            for (int k = 0; k < 64; k += 2) write(k);
+        } else {                                     // few of them (the probed centroids of a query)
+            for (; pairs; pairs &= pairs - 1) write((int)__builtin_ctzll(pairs));
         }
         base += all;
     }
