@@ -874,7 +874,9 @@ void plaid_launch_select(hipStream_t st, const uint64_t *keys, int64_t key_strid
                            sc.state, sc.hist);
         hipLaunchKernelGGL(sel_level_kernel<0>, dim3(gx, nseg), dim3(SEL_THREADS), 0, st, keys, key_stride, sc.state,
                            sc.hist, sc.sure, sc.sure_stride, sc.list0, sc.list_stride);
-        const int gx1 = gx > 16 ? 16 : gx;
+        // (the second list is short more often than not: 2048 workgroups for all lists together, if they have no more than the first; 1024
+        // lists of 16 384 keys 26 us with eight each)
+        const int most1 = (2048 + nseg - 1) / nseg, gx1 = gx < most1 ? (gx > 16 ? 16 : gx) : (most1 > 16 ? 16 : most1);
         hipLaunchKernelGGL(sel_level_kernel<1>, dim3(gx1, nseg), dim3(SEL_THREADS), 0, st, sc.list0, sc.list_stride,
                            sc.state, sc.hist, sc.sure, sc.sure_stride, sc.list1, sc.list_stride);
         hipLaunchKernelGGL(sel_finish_kernel<false>, dim3(nseg), dim3(FIN_THREADS), 0, st, keys, key_stride, counts, m,
