@@ -1579,6 +1579,36 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     }
 }
 
+// log2 of the passages per wave and step: 2048, fewer for indexes of so few passages that a wave's own chain of steps is all that counts
+// and the chip has room for more waves.  512 at least and up to 400 ranges of a query: beyond, what they add to one histogram and score
+// before there is a threshold costs more.  us per search with 2048 / 1024 / 512 / 256: one query of 40 000 passages 73 / 70 / 70 / 73, of
+// 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 / 129 / 148), of a million
+// 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of 400 000 120 / 120 / 131 / 151.  Between
+// 400 000 and a million (2048 / 1024, k 100): one query of 450 000 93 / 88, of 500 000 94 / 89, of 600 000 90 / 94, of 700 000 91 / 97, of
+// 900 000 94 / 99; four of 450 000 113 / 116, of 500 000 112 / 118, of 600 000 117 / 126.
+// The smallest collections: down to 128, up to 100 ranges of a query and 1280 waves, beyond 8192 passages only while a wave's share of m is
+// more than 16.  With 512 / 256 / 128: ndocs a twentieth of the passages, one query of 1000 65 / 63 / 63, of 5000 78 / 75 / 75, of 10 000 74 /
+// 72 / 72, of 20 000 78 / 74 / 76; fifteen of 5000 90 / 87 / 86, of 10 000 97 / 98 / 91; a quarter, one of 5000 92 / 85 / 81, of 10 000 93 / 88 /
+// 82, fifteen of 10 000 136 / 129 / 123; a fiftieth, one of 5000 73 / 71 / 70, of 10 000 67 / 68 / 66.  Beyond: one of 10 000, ndocs 256, 65.7 /
+// - / 66.9, of 30 000, ndocs 1024, 76 / 79 / -; 33 of 10 000 147 / 150 / -.
+static constexpr int s2_range_log(int64_t P, int64_t nq, int64_t m)
+{
+    const int64_t ranges = (P + 2047) >> 11, waves = nq * ranges;
+    int len_log = 11;
+    while (len_log > 9 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
+    while (len_log <= 9 && len_log > 7 && (P <= 8192 || (m << len_log) / P > 16) && (ranges << (12 - len_log)) <= 100 &&
+           (waves << (12 - len_log)) <= 1280)
+        --len_log;
+    // An ndocs so large that a wave has several batches to score in any case (one query of 400 000 passages, ndocs 100 000: stage 2 and
+    // selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the
+    // order of the bags' sizes: 115, 58, 695, 529): shorter ranges while the chip has room.
+    while (len_log > 9 && (m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
+    // A collection of which a large share is kept: down to 128, while a wave's share of m is more than 64 and a query has up to 400 ranges
+    // (one query of 40 000, half of them kept, 264 / 252 / 246).
+    while (len_log > 7 && (m << len_log) / P > 64 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
+    return len_log;
+}
+
 // Ranges that a wave takes one after the other (waves: how many there are with one each).  The set-up of a workgroup (10 us when
 // the chip is full) is worth sharing once every SIMD has dozens of waves to run (512 queries of 400 000 passages: 3.12 / 3.11 /
 // 3.16 ms with 1 / 2 / 4 steps, 150 of 8.8 M: 13.3 / 12.6 / 12.4 ms).  A single query of somewhat more ranges than the chip holds
@@ -1634,26 +1664,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_candidates_kernel, dim3((unsigned)((cand_words + 63) / 64), nq), dim3(64 * IV_WAVES), 0, st, uniq, n_uniq,
                            uniq_stride, ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            wide);
-    // Passages per wave and step: 2048, fewer (512 at least, but see below) for indexes of so few passages that a wave's own chain of steps is all
-    // that counts and the chip has room for more waves, up to 400 of a query: beyond, what they add to one histogram and score before there is a
-    // threshold costs more.  us per search with 2048 / 1024 / 512 / 256: one query of 10 000 passages 77 / 69 / 65 / 66, of 40 000 73 / 70 /
-    // 70 / 73, of 100 000 85 / 82 / 84 / 82, of 200 000 76 / 78 / 75 / 80, of 400 000 99 / 94 / 99 / 119 (ndocs 4096 131 / 123 /
-    // 129 / 148), of a million 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of
-    // 400 000 120 / 120 / 131 / 151.
-    // Between 400 000 and a million (2048 / 1024, k 100): one query of 450 000 93 / 88, of 500 000 94 / 89, of 600 000 90 / 94, of
-    // 700 000 91 / 97, of 900 000 94 / 99; four of 450 000 113 / 116, of 500 000 112 / 118, of 600 000 117 / 126.
     const int64_t ranges = (P + 2047) >> 11, waves = (int64_t)nq * ranges;
-    int len_log = 11;
-    while (len_log > 9 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
-    // An ndocs so large that a wave has several batches to score in any case (one query of 400 000 passages, ndocs 100 000:
-    // stage 2 and selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries
-    // 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the order of the bags' sizes: 115, 58, 695, 529): shorter
-    // ranges while the chip has room.
-    while (len_log > 9 && ((int64_t)m << len_log) / P > 128 && (waves << (12 - len_log)) <= 2560) --len_log;
-    // A small collection of which a large share is kept: down to 128, while a wave's share of m is more than 64.  us per search of
-    // 10 000 passages, ndocs 4096, with 512 / this: one query 134 / 105, four 155 / 125, fifteen 207 / 177; of 15 000 112 / 102,
-    // 138 / 126, 194 / 184.
-    while (len_log > 7 && ((int64_t)m << len_log) / P > 64 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
+    const int len_log = s2_range_log(P, nq, m);
     const int steps = s2_steps(nq, waves);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
     // Passages a wave scores before there is a threshold: 24 (and those that tie with the last of them), which mostly fit a batch of 32 in which

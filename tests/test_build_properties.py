@@ -165,7 +165,13 @@ RULES = [
                       # which of 32 (bit 0) to 63 survivors: a list in every range, in most of them, and where few need planes
                       "s2_tall_queries(1.0) == 0xFFE0001Fu", "s2_tall_queries(0.9999) == 0xFFE0001Fu", "s2_tall_queries(0.975) == 0xFFC0001Fu",
                       "s2_tall_queries(0.85) == 0xE00003FFu", "s2_tall_queries(0.71) == 0x0003FFF0u",
-                      "s2_tall_queries(0.65) == 0", "s2_tall_queries(0.0) == 0"]),
+                      "s2_tall_queries(0.65) == 0", "s2_tall_queries(0.0) == 0",
+                      # passages per range: smallest collections, those up to 400 ranges, large ones; many queries; large shares kept
+                      "s2_range_log(1000, 1, 50) == 7", "s2_range_log(8192, 20, 100) == 7", "s2_range_log(8192, 21, 100) == 8", "s2_range_log(8193, 1, 256) == 9",
+                      "s2_range_log(10000, 1, 500) == 8", "s2_range_log(10000, 16, 700) == 7", "s2_range_log(20000, 1, 1000) == 8", "s2_range_log(30000, 1, 2000) == 9", "s2_range_log(200000, 1, 256) == 9",
+                      "s2_range_log(400000, 1, 1024) == 10", "s2_range_log(409601, 1, 1024) == 11", "s2_range_log(10000, 33, 256) == 9",
+                      "s2_range_log(10000, 512, 256) == 11", "s2_range_log(40000, 1, 20000) == 7", "s2_range_log(400000, 1, 100000) == 9",
+                      "s2_range_log(8800000, 1, 4096) == 11"]),
     # long lists in great number only
     ("k_stage4.hip", ["s4_packed(256, 512)", "s4_packed(1024, 36)", "!s4_packed(1024, 35)", "s4_packed(96, 384)", "!s4_packed(72, 512)",
                       "!s4_packed(64, 576)", "!s4_packed(64, 2048)", "!s4_packed(16, 2304)"]),
