@@ -1622,6 +1622,18 @@ static constexpr int s2_steps(int nq, int64_t waves)
     return waves >= 16 * 12288 ? 4 : (waves >= 4 * 12288 || (nq == 1 && waves > 4096 && waves <= 7000) ? 2 : 1);
 }
 
+// Passages a wave scores before there is a threshold, or its share of m, which has to be scored whatever the bounds say: 24 (and those
+// that tie with the last of them), which mostly fit a batch of 32 in which two lanes share a passage, 48 in whole ranges of large searches.
+// us per search with 24 / 32 / 48 / 64, ranges of 2048: 33 queries of 400 000 passages, ndocs 4096, 490 / 486 / 479 / 476, ndocs 256 212 /
+// 211 / 212 / 213; 128 1379 / 1366 / 1361 / 1365; 33 of 600 000 523 / 514 / 506 / 506; one of 3 M, ndocs 16 384, 315 / 309 / 304 / 300, ndocs 4096
+// 172 / 173 / 170 / 170; sixteen of 200 000, ndocs 1024, 128 / 129 / 130 / 133; 32 of 600 000 286 / 287 / 292 / 295.  Shorter ranges: one
+// of 400 000, ndocs 4096, 121 / 122 / 123 / 125; of 200 000 107 / 107 / 110 / 110; of 30 000, ndocs 1024, 77 / 78 / 78 / 84.
+static constexpr int64_t s2_first_batch(int64_t P, int64_t nq, int64_t m, int len_log)
+{
+    const int64_t share = (m << len_log) / P, few = len_log == 11 && (nq > 32 || m >= 4096) ? 48 : 24;
+    return share > few ? share : few;
+}
+
 // The numbers of survivors K (bit K - 32) whose queries the TALL instance takes in launches of many workgroups.  share: how
 // often a surviving centroid needs a plane (plaid_launch_ivf_plane_share): K of them need K share, give or take the root of K share
 // (1 - share).  With 26 planes four workgroups run on a compute unit, with 36 three: the second wins where it goes through whole
@@ -1668,12 +1680,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const int len_log = s2_range_log(P, nq, m);
     const int steps = s2_steps(nq, waves);
     const int64_t per_block = (int64_t)(IV_WAVES * steps) << len_log;
-    // Passages a wave scores before there is a threshold: 24 (and those that tie with the last of them), which mostly fit a batch of 32 in which
-    // two lanes share a passage, or its share of m, which has to be scored whatever the bounds say.  us per search with 16 / 24 / 32 / 48, one
-    // query: of 40 000 passages (512 per wave) 70 / 70 / 73 / 71, of 100 000 (1024) 83 / 82 / 83 / 83, of 400 000 and ndocs 4096 (1024) 124 / 123 /
-    // 124 / 124; eight times the share, up to 64: 73, 86 and 126.
-    const int64_t share = ((int64_t)m << len_log) / P;
-    const int first_batch = (int)(share > 24 ? share : 24);
+    const int first_batch = (int)s2_first_batch(P, nq, m, len_log);
     const int64_t blocks = (P + per_block - 1) / per_block;
     // workgroups of the gather form: no more than there are bitmap words to share, and a multiple of eight
     const int64_t words = (nq * cand_words + 7) & ~7ll;
