@@ -1586,18 +1586,19 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
 // 101 / 112 / 132 / 178; four of 100 000 112 / 106 / 105 / 108, of 200 000 94 / 92 / 93 / 103, of 400 000 120 / 120 / 131 / 151.  Between
 // 400 000 and a million (2048 / 1024, k 100): one query of 450 000 93 / 88, of 500 000 94 / 89, of 600 000 90 / 94, of 700 000 91 / 97, of
 // 900 000 94 / 99; four of 450 000 113 / 116, of 500 000 112 / 118, of 600 000 117 / 126.
-// The smallest collections: down to 128, up to 100 ranges of a query and 1280 waves, beyond 8192 passages only while a wave's share of m is
-// more than 16.  With 512 / 256 / 128: ndocs a twentieth of the passages, one query of 1000 65 / 63 / 63, of 5000 78 / 75 / 75, of 10 000 74 /
-// 72 / 72, of 20 000 78 / 74 / 76; fifteen of 5000 90 / 87 / 86, of 10 000 97 / 98 / 91; a quarter, one of 5000 92 / 85 / 81, of 10 000 93 / 88 /
-// 82, fifteen of 10 000 136 / 129 / 123; a fiftieth, one of 5000 73 / 71 / 70, of 10 000 67 / 68 / 66.  Beyond: one of 10 000, ndocs 256, 65.7 /
-// - / 66.9, of 30 000, ndocs 1024, 76 / 79 / -; 33 of 10 000 147 / 150 / -.
+// The smallest collections: down to 128, up to 100 ranges of a query and while the launch then has at most 2560 waves, beyond 8192
+// passages only while a wave's share of m is more than 16.  With 512 / 256 / 128 and the first batches below: ndocs a tenth of the
+// passages, eight queries of 2000 81 / 77 / 73, of 5000 94 / 89 / 84, of 12 000 95 / 93 / 87, 33 of 5000 121 / 116 / 112, of 8000 140 / 140 /
+// 134; a quarter, eight of 5000 110 / 101 / 90, 33 162 / 154 / 145; a fiftieth, eight of 5000 78 / 76 / 75, of 12 000 78 / 75 / 75, one of
+// 10 000 66 / 68 / 67, 33 of 8000 100 / 98 / 99.  Of 20 000, ndocs a twentieth, one 78 / 74 / 76, fifteen 104 / 102 / 98.  Beyond: one of
+// 30 000, ndocs 1024, 76 / 79 / -; 33 of 10 000 147 / 150 / -; 48 of 12 000 173 / 174 / 179.
 static constexpr int s2_range_log(int64_t P, int64_t nq, int64_t m)
 {
     const int64_t ranges = (P + 2047) >> 11, waves = nq * ranges;
     int len_log = 11;
     while (len_log > 9 && (ranges << (12 - len_log)) <= 400 && (waves << (12 - len_log)) <= 2560) --len_log;
     while (len_log <= 9 && len_log > 7 && (P <= 8192 || (m << len_log) / P > 16) && (ranges << (12 - len_log)) <= 100 &&
-           (waves << (12 - len_log)) <= 1280)
+           (waves << (12 - len_log)) <= (len_log == 9 ? 1280 : 2560))
         --len_log;
     // An ndocs so large that a wave has several batches to score in any case (one query of 400 000 passages, ndocs 100 000: stage 2 and
     // selection 208 -> 158 us, all 400 000 345 -> 87; 64 queries 1129 -> 1030 and 1534 -> 910; scored by four waves per range, in the
@@ -1627,10 +1628,12 @@ static constexpr int s2_steps(int nq, int64_t waves)
 // us per search with 24 / 32 / 48 / 64, ranges of 2048: 33 queries of 400 000 passages, ndocs 4096, 490 / 486 / 479 / 476, ndocs 256 212 /
 // 211 / 212 / 213; 128 1379 / 1366 / 1361 / 1365; 33 of 600 000 523 / 514 / 506 / 506; one of 3 M, ndocs 16 384, 315 / 309 / 304 / 300, ndocs 4096
 // 172 / 173 / 170 / 170; sixteen of 200 000, ndocs 1024, 128 / 129 / 130 / 133; 32 of 600 000 286 / 287 / 292 / 295.  Shorter ranges: one
-// of 400 000, ndocs 4096, 121 / 122 / 123 / 125; of 200 000 107 / 107 / 110 / 110; of 30 000, ndocs 1024, 77 / 78 / 78 / 84.
+// of 400 000, ndocs 4096, 121 / 122 / 123 / 125; of 200 000 107 / 107 / 110 / 110; of 30 000, ndocs 1024, 77 / 78 / 78 / 84.  Of 128, which are
+// chosen where much of a small collection is kept, 64: eight of 5000, ndocs 500, 86 / 87 / - / 84, ndocs 1250 95 / 95 / - / 90, ndocs 100 75 / 75 /
+// - / 75; 33 153 / 153 / - / 145.
 static constexpr int64_t s2_first_batch(int64_t P, int64_t nq, int64_t m, int len_log)
 {
-    const int64_t share = (m << len_log) / P, few = len_log == 11 && (nq > 32 || m >= 4096) ? 48 : 24;
+    const int64_t share = (m << len_log) / P, few = len_log == 7 ? 64 : len_log == 11 && (nq > 32 || m >= 4096) ? 48 : 24;
     return share > few ? share : few;
 }
 

@@ -167,14 +167,14 @@ RULES = [
                       "s2_tall_queries(0.85) == 0xE00003FFu", "s2_tall_queries(0.71) == 0x0003FFF0u",
                       "s2_tall_queries(0.65) == 0", "s2_tall_queries(0.0) == 0",
                       # passages per range: smallest collections, those up to 400 ranges, large ones; many queries; large shares kept
-                      "s2_range_log(1000, 1, 50) == 7", "s2_range_log(8192, 20, 100) == 7", "s2_range_log(8192, 21, 100) == 8", "s2_range_log(8193, 1, 256) == 9",
+                      "s2_range_log(1000, 1, 50) == 7", "s2_range_log(8192, 40, 100) == 7", "s2_range_log(8192, 41, 100) == 9", "s2_range_log(8193, 1, 256) == 9",
                       "s2_range_log(10000, 1, 500) == 8", "s2_range_log(10000, 16, 700) == 7", "s2_range_log(20000, 1, 1000) == 8", "s2_range_log(30000, 1, 2000) == 9", "s2_range_log(200000, 1, 256) == 9",
                       "s2_range_log(400000, 1, 1024) == 10", "s2_range_log(409601, 1, 1024) == 11", "s2_range_log(10000, 33, 256) == 9",
                       "s2_range_log(10000, 512, 256) == 11", "s2_range_log(40000, 1, 20000) == 7", "s2_range_log(400000, 1, 100000) == 9",
                       "s2_range_log(8800000, 1, 4096) == 11",
                       # first batches of whole and of shorter ranges; a share of ndocs that is more
                       "s2_first_batch(400000, 33, 256, 11) == 48", "s2_first_batch(400000, 32, 1024, 11) == 24", "s2_first_batch(8800000, 1, 4096, 11) == 48",
-                      "s2_first_batch(400000, 1, 4096, 10) == 24", "s2_first_batch(30000, 64, 256, 9) == 24", "s2_first_batch(400000, 1, 100000, 9) == 128",
+                      "s2_first_batch(400000, 1, 4096, 10) == 24", "s2_first_batch(30000, 64, 256, 9) == 24", "s2_first_batch(5000, 64, 256, 7) == 64", "s2_first_batch(400000, 1, 100000, 9) == 128",
                       "s2_first_batch(400000, 64, 40000, 11) == 204"]),
     # long lists in great number only
     ("k_stage4.hip", ["s4_packed(256, 512)", "s4_packed(1024, 36)", "!s4_packed(1024, 35)", "s4_packed(96, 384)", "!s4_packed(72, 512)",
