@@ -1557,10 +1557,11 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
         // (the second pass as below; a list of no more than LDS holds has not gone through the first)
         const int second = (nq >= 8 || lists) && P > SEL2_SECOND_MIN_PASSAGES ? 1 : 0;
         const int id_shift = sel2_id_shift(P), cut = gx < 2 ? 1 : gx / 2;
-        // (all workgroups: with 16 a query, as below, counting the digits of long lists was slow.  us per search, hardly a survivor, ndocs 4096,
-        // with 16 / 64: sixteen queries of 200 000 passages 231 / 213, of 400 000 427 / 389, of 3 M 826 / 545, 32 1128 / 844; the other
-        // form 223, 397, 721, 1017; lists that need no digit pass take up to 1 us more)
-        hipLaunchKernelGGL(sel2_bins_kernel, dim3(gx, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P, m,
+        // (more workgroups than below: with 16 a query counting the digits of long lists was slow.  us per search, hardly a survivor, ndocs
+        // 4096, with 16 / 32 / 64: sixteen queries of 200 000 passages 231 / 220 / 213, of 400 000 427 / 403 / 389, of 3 M 826 / 640 / 545,
+        // 32 1128 / 930 / 844; the other form 223, 397, 721, 1017.  Lists that need no digit pass: 24 of 400 000, ndocs 256, 178 / 178 / 180)
+        const int gx_bins = nq > 16 && gx > 32 ? 32 : gx;
+        hipLaunchKernelGGL(sel2_bins_kernel, dim3(gx_bins, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P, m,
                            b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1, b.hist);
         hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.hist, b.meta, lists,
                            id_shift, second, keys2, key_stride, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
