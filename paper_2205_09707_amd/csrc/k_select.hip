@@ -1135,14 +1135,13 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint6
 __global__ __launch_bounds__(SEL_THREADS, 6) void sel2_bins_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                 const uint32_t *__restrict__ candbits, int64_t cand_words, int64_t P,
                                                                 int32_t m, const S2Meta *__restrict__ meta,
-                                                                const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
+                                                                int32_t *hist, Sel2State *state, uint64_t *__restrict__ out,
                                                                 int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride,
-                                                                int lists, int id_shift, int32_t *__restrict__ hist1,
-                                                                int32_t *__restrict__ low)
+                                                                int lists, int id_shift, int32_t *__restrict__ hist1)
 {
     __shared__ int32_t lh[SEL_BINS + SEL2_SUB];
     sel2_filter_body<true>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists,
-                           id_shift, hist1, low, lh);
+                           id_shift, hist1, hist, lh);
 }
 
 template <int LEVEL>
@@ -1562,7 +1561,7 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
         // 32 1128 / 930 / 844; the other form 223, 397, 721, 1017.  Lists that need no digit pass: 24 of 400 000, ndocs 256, 178 / 178 / 180)
         const int gx_bins = nq > 16 && gx > 32 ? 32 : gx;
         hipLaunchKernelGGL(sel2_bins_kernel, dim3(gx_bins, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P, m,
-                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1, b.hist);
+                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1);
         hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.hist, b.meta, lists,
                            id_shift, second, keys2, key_stride, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
         if (second) {
