@@ -1476,8 +1476,11 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                 const int rank = s2_wave_scan(pc);
                 const int total = __builtin_amdgcn_readlane(rank, 63);
                 if (total == 0) break;
-                int base = 0;
-                if (lane == 0) base = atomicAdd(&state[q].n_list, total);  // (its round trip overlaps the first batch)
+                // Its round trip overlaps the first batch: the address is one the compiler takes for a lane's own, since it makes of an
+                // addition to a uniform one a sum over the wave, and waits for the result at once.
+                int base = 0, place = 0;
+                s2_opaque(place);
+                if (lane == 0) base = atomicAdd(&state[q].n_list + place, total);
                 s2_wave_sync();
                 lcnt[lane] = (uint32_t)(rank - pc);
                 lcand[lane] = sel;
