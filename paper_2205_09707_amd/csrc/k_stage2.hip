@@ -1086,7 +1086,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     constexpr int FULL_PLANES = sizeof(SetT) == 4 ? 31 : (SHIFT == 11 ? (TALL ? S2_TALL_PLANES : S2_PLANES) : 24);
     static_assert(4 * FULL_PLANES >= KMAX, "every slot has a plane at a quarter of the length");
     constexpr int SLOTS = KMAX + 1;
-    constexpr int MORE = SHIFT == 11 ? 2 : 4;  // loads in flight per lane of a long list (of a coarse column: four times as long)
+    constexpr int MORE = ALL ? 6 : (SHIFT == 11 ? 2 : 4);  // loads in flight per lane of a long list (of a coarse column: four times as long)
     __shared__ __align__(16) uint32_t area_all[IV_WAVES][FULL_PLANES * 64];
     __shared__ __align__(16) float Tl[KMAX * S2_TSTRIDE];
     __shared__ float rowsum[SLOTS];
@@ -1281,11 +1281,23 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                         }
                 }
             } else {
-                for (int i0 = 0; i0 < n_dense; i0 += groups) {
-                    const int i = i0 + grp, row = __shfl(dense_row, i & 63), g = __shfl(gain_lane, i & 63);
-                    const uint32_t v = i < n_dense && gact ? dense_bits[(int64_t)row * cand_words + w0 + gl] : 0u;
-                    if (i < n_near) area[i * nw + gl] = v;
-                    add(v, i & 63, g);
+                for (int i0 = 0; i0 < n_dense; i0 += 4 * groups) {  // four loads in flight
+                    uint32_t v[4];
+                    int g[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int i = i0 + u * groups + grp, row = __shfl(dense_row, i & 63);
+                        g[u] = __shfl(gain_lane, i & 63);
+                        v[u] = i < n_dense && gact ? dense_bits[(int64_t)row * cand_words + w0 + gl] : 0u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int i = i0 + u * groups + grp;
+                        if (i0 + u * groups < n_dense) {  // uniform
+                            if (i < n_near) area[i * nw + gl] = v[u];
+                            add(v[u], i & 63, g[u]);
+                        }
+                    }
                 }
             }
             // the planes of the survivors' other lists, entry by entry
@@ -1358,9 +1370,20 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                         }
                 }
             } else {
-                for (int i0 = 0; i0 < n_act; i0 += groups) {
-                    const int i = i0 + grp, s = __shfl(plane_slot, i & 63) & 63, g = __shfl(gain_lane, s);
-                    add(i < n_act ? planes[i * nw + gl] : 0u, s, g);
+                const int plane_gain = __shfl(gain_lane, plane_slot & 63);
+                for (int i0 = 0; i0 < n_act; i0 += 2 * groups) {
+                    uint32_t v[2];
+                    int s[2], g[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int i = i0 + u * groups + grp;
+                        s[u] = __shfl(plane_slot, i & 63) & 63;
+                        g[u] = __shfl(plane_gain, i & 63);
+                        v[u] = i < n_act ? planes[i * nw + gl] : 0u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        if (i0 + u * groups < n_act) add(v[u], s[u], g[u]);  // uniform
                 }
                 for (int d = nw; d < 64; d <<= 1) {
                     uint32_t carry = 0u;
@@ -1573,9 +1596,9 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                     if (live) klist[base + at] = plaid_make_key(score, (uint32_t)(p0 + 32 * w + pos));
                 }
                 s2_wave_sync();
+                // (both of a lane's bins in one addition)
                 const uint32_t counts = lstart[lane];
-                if (counts & 0xFFFFu) atomicAdd(&coarse_q[2 * lane], (int32_t)(counts & 0xFFFFu));
-                if (counts >> 16) atomicAdd(&coarse_q[2 * lane + 1], (int32_t)(counts >> 16));
+                if (counts) atomicAdd(reinterpret_cast<unsigned long long *>(coarse_q) + lane, (unsigned long long)(counts >> 16) << 32 | (counts & 0xFFFFu));
             }
             s2_wave_sync();  // the next range's planes overwrite what the last batch read
         }
