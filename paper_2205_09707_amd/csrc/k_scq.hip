@@ -130,6 +130,7 @@ struct SurvivorScratch {
     float colmm[3 * QLEN];
     int32_t ids[S2_MAX_KEPT + 1], rank[S2_MAX_KEPT + 1];
     int32_t misc[2];  // number of survivors, chosen hash trial
+    float gain[S2_MAX_KEPT + 1];
     int32_t amb_n, amb_total;
     uint32_t amb_pass[TAIL_AMB / 32];
 };
@@ -172,23 +173,24 @@ __device__ __forceinline__ void tail_exact_rows(const float *row, int n, const f
 }
 
 // The rows whose bit is set in the query's pruning words, in any order (the table sorts them), and with amb the number of
-// those set there, to amb_total: sixteen words of each per thread in flight, nearly all of them zero.  All threads call this;
+// those set there, to amb_total: FLY words of each per thread in flight, nearly all of them zero.  All threads call this;
 // the counters are zero and published, a barrier has to follow.
+template <int FLY>
 __device__ __forceinline__ void stage1_list_survivors(const uint32_t *__restrict__ kb, const uint32_t *__restrict__ amb, int64_t keep_words,
                                                       SurvivorScratch &sh)
 {
     const int tid = threadIdx.x, nthreads = blockDim.x;
     int open = 0;
-    for (int64_t w0 = tid; w0 < keep_words; w0 += 16ll * nthreads) {
-        uint32_t v[16], a[16];
+    for (int64_t w0 = tid; w0 < keep_words; w0 += (int64_t)FLY * nthreads) {
+        uint32_t v[FLY], a[FLY];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < FLY; ++u) {
             const int64_t w = w0 + (int64_t)u * nthreads;
             v[u] = w < keep_words ? kb[w] : 0u;
             a[u] = amb && w < keep_words ? amb[w] : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < FLY; ++u) {
             open += __popc(a[u]);
             if (v[u]) {
                 int pos = atomicAdd(&sh.misc[0], __popc(v[u]));
@@ -301,14 +303,30 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
             else scq_column_bounds<7>(Tx, K, (K + 6) / 9, tid, colmm);
         }
         __syncthreads();
+        // the slots' gains, eight threads a slot
+        float *gain = sh.gain;
+        for (int e = tid; e < 8 * K; e += nthreads) {  // (whole groups of eight)
+            const int s = e >> 3;
+            float g = 0.f;
+#pragma unroll
+            for (int u = 0; u < QLEN / 8; ++u) {
+                const int i = (e & 7) + 8 * u;
+                g += fmaxf(Tx[s * TX_STRIDE + i] - colmm[2 * QLEN + i], 0.f);
+            }
+            g += __shfl_xor(g, 1);
+            g += __shfl_xor(g, 2);
+            g += __shfl_xor(g, 4);
+            if ((e & 7) == 0) gain[s] = g;
+        }
+        __syncthreads();
         if (tid < 64 && K > 0) {  // one wave, lane = slot (the next one fills in the rest of the record)
-            float g = 0.f, base = 0.f, scale = 0.f;
-#pragma unroll 8
-            for (int i = 0; i < QLEN; ++i) {
-                const float b = colmm[2 * QLEN + i];
-                if (tid < K) g += fmaxf(Tx[tid * TX_STRIDE + i] - b, 0.f);
-                base += b;
-                scale += fmaxf(fabsf(colmm[i]), fabsf(colmm[QLEN + i]));
+            const float g = tid < K ? gain[tid] : 0.f;
+            float base = tid < QLEN ? colmm[2 * QLEN + tid] : 0.f;
+            float scale = tid < QLEN ? fmaxf(fabsf(colmm[tid]), fabsf(colmm[QLEN + tid])) : 0.f;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                base += __shfl_xor(base, d);
+                scale += __shfl_xor(scale, d);
             }
             float total = g;
 #pragma unroll
@@ -371,7 +389,7 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
         sh.misc[1] = -1;
     }
     __syncthreads();
-    stage1_list_survivors(keepbits + (int64_t)q * keep_words, nullptr, keep_words, sh);
+    stage1_list_survivors<8>(keepbits + (int64_t)q * keep_words, nullptr, keep_words, sh);
     __syncthreads();
     stage1_survivor_table<false>(Sq, C,
                                  [&](float *colmm) { if (threadIdx.x < QLEN) colmm[threadIdx.x] = Sq[(int64_t)top1[threadIdx.x] * QLEN + threadIdx.x]; },
@@ -824,21 +842,19 @@ __device__ __forceinline__ float tail_max32(float m)
 // The nprobe-th largest of the values the 32 lanes of a token hold, four each (-infinity where there are fewer).
 __device__ __forceinline__ float tail_nth_largest(float (&v)[4], int nprobe, int l)
 {
-    float T = -INFINITY;
-    for (int r = 0; r < nprobe; ++r) {  // uniform
-        const float mine = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-        T = tail_max32(mine);
-        const unsigned long long who = __ballot(mine == T);
+    // each lane's in descending order, so that it drops the first
+    auto order = [&](int a, int b) {
+        const float x = v[a], y = v[b];
+        v[a] = fmaxf(x, y);
+        v[b] = fminf(x, y);
+    };
+    order(0, 1), order(2, 3), order(0, 2), order(1, 3), order(1, 2);
+    float T = tail_max32(v[0]);
+    for (int r = 1; r < nprobe; ++r) {  // uniform
+        const unsigned long long who = __ballot(v[0] == T);
         const uint32_t half = (threadIdx.x & 32) ? (uint32_t)(who >> 32) : (uint32_t)who;  // this token's 32 lanes
-        if (l == __ffs(half) - 1) {  // the first holder drops it
-            bool gone = false;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool drop = !gone && v[u] == T;
-                gone = gone || drop;
-                v[u] = drop ? -INFINITY : v[u];
-            }
-        }
+        if (l == __ffs(half) - 1) v[0] = v[1], v[1] = v[2], v[2] = v[3], v[3] = -INFINITY;  // the first holder drops it
+        T = tail_max32(v[0]);
     }
     return T;
 }
@@ -948,7 +964,9 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
         for (int j = 0; j < NP; ++j) best[j] = PLAID_KEY_MAX;
         const int n_sel = sh.tile_cnt[i];
         const bool listed = n_sel <= TAIL_SEL;
-        const int chunks = (tile_rows + TAIL_LANES - 1) / TAIL_LANES;  // 32-row pieces of a tile
+        // 32-row pieces of a tile (one with approximate scores, which spares the divisions below)
+        static_assert(SM_WROWS == TAIL_LANES, "a row per lane");
+        const int rows = APPROX ? TAIL_LANES : tile_rows, chunks = (rows + TAIL_LANES - 1) / TAIL_LANES;
         const int n_items = (listed ? n_sel : nblk) * chunks;
         // walk: every listed row with its score; what happens to a row is up to `visit`
         constexpr int FLY = NP <= 2 ? 4 : 8;  // score rows in flight per lane
@@ -964,8 +982,8 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                     const int k = ok[u] ? it / chunks : 0, r = (it % chunks) * TAIL_LANES + l;
                     const int t = listed ? sh.sel_tile[i][k] : k;
                     if (!listed && ok[u]) ok[u] = tmq[(int64_t)t * QLEN + i] >= T;
-                    cc[u] = (int64_t)t * tile_rows + r;
-                    ok[u] = ok[u] && r < tile_rows && cc[u] < C;
+                    cc[u] = (int64_t)t * rows + r;
+                    ok[u] = ok[u] && r < rows && cc[u] < C;
                     sv[u] = ok[u] ? Sq[cc[u] * QLEN + i] : 0.f;
                 }
 #pragma unroll
@@ -1161,7 +1179,9 @@ __device__ __forceinline__ void tail_survivors(TableScratch<APPROX> &ts, int q, 
     if (APPROX) tail_stage_query(x.Q, q, ts.x[0].Qs);
     if (APPROX && tid == 0) ts.x[0].matrix = x.matrix;
     __syncthreads();
-    stage1_list_survivors(kbq, abq, keep_words, sh);
+    // (a thread's instructions take the time here, sixteen waves on one compute unit: no more words than it has)
+    if (keep_words <= 2ll * TAIL_THREADS) stage1_list_survivors<2>(kbq, abq, keep_words, sh);
+    else stage1_list_survivors<8>(kbq, abq, keep_words, sh);
     __syncthreads();
     if (APPROX) {
         // Eq. 5 for the rows the score kernel left open.  Rounds of at most TAIL_AMB rows: the rows of a range of bitmap
