@@ -88,6 +88,7 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     int32_t *qlist;         //   from the end of the last row), appended as their workgroups finish (null: not recorded).
     int qlist_stride;       //   Stage 2 takes its queries from these lists.
     bool need_hash;         // stage 2 will use the streaming form
+    bool probes_apart;      // uniq holds every probe of the query, with duplicates and in no order
 };
 
 // Floats per query row in the probe kernel's LDS.  The survivor table is evaluated with a lane per query token: with rows
@@ -859,25 +860,40 @@ __device__ __forceinline__ float tail_nth_largest(float (&v)[4], int nprobe, int
     return T;
 }
 
-template <int NP, bool APPROX>
-__device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, const float *__restrict__ S, int64_t C,
+// TOK query tokens from t0 on: all of them, or TAIL_TOKENS (APPROX only), by as many waves as they need; the others leave.  Then the
+// probed ids are left as they are, token by token, in the place of their union.
+#define TAIL_TOKENS 8
+template <int NP, bool APPROX, int TOK>
+__device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, int t0, const float *__restrict__ S, int64_t C,
                                             const float *__restrict__ tmq, int nblk, int tile_rows, const float *__restrict__ gmq,
                                             int ng, int gs, int nprobe, const Stage1Out o, const Stage1Exact x)
 {
     static_assert(TAIL_LANES == 32, "32 lanes per query token");
+    static_assert(TOK == QLEN || (APPROX && TOK == TAIL_TOKENS && 16 % TOK == 0), "whole waves, and one tile of sixteen tokens");
+    constexpr int THREADS = TOK * TAIL_LANES, ROWS = TAIL_ROWS * TOK / QLEN;
     const int tid = threadIdx.x;
+    if (TOK < QLEN && tid >= THREADS) return;  // whole waves
     const float *__restrict__ Sq = S + (int64_t)q * C * QLEN;
     const float margin = APPROX ? x.margin : 0.f;
-    if (APPROX) tail_stage_query(x.Q, q, sh.Qs);
+    const int q16 = t0 & ~15;  // a part's sixteen tokens of a tile
+    if constexpr (APPROX && TOK < QLEN) {
+#pragma unroll
+        for (int e = tid; e < 16 * (DIM / 4); e += THREADS)
+            *reinterpret_cast<float4 *>(sh.Qs + (q16 + e / (DIM / 4)) * TAIL_QSTRIDE + 4 * (e % (DIM / 4))) =
+                *reinterpret_cast<const float4 *>(x.Q + ((int64_t)q * QLEN + q16) * DIM + 4 * e);
+    } else if (APPROX) {
+        tail_stage_query(x.Q, q, sh.Qs);
+    }
     // pass 1: the maxima of groups part, part + 128, ... of tokens 4 tk4 .. 4 tk4 + 3, one block of rows per thread
-    const int tk4 = tid % (QLEN / 4), part = tid / (QLEN / 4);
+    const int tk4 = tid % (TOK / 4), part = tid / (TOK / 4);
+    static_assert(THREADS / (TOK / 4) == TAIL_PARTS, "as many threads share four tokens");
     float4 g[TAIL_FLY];  // the first of them stay in registers
     auto load = [&](int b0) {
 #pragma unroll
         for (int u = 0; u < TAIL_FLY; ++u) {
             const int b = b0 + TAIL_PARTS * u;
             g[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (b < ng) g[u] = *reinterpret_cast<const float4 *>(gmq + (int64_t)b * QLEN + 4 * tk4);
+            if (b < ng) g[u] = *reinterpret_cast<const float4 *>(gmq + (int64_t)b * QLEN + t0 + 4 * tk4);
         }
     };
     float4 most = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
@@ -889,7 +905,8 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
     }
     *reinterpret_cast<float4 *>(&sh.block[part][4 * tk4]) = most;
     __syncthreads();
-    const int i = tid / TAIL_LANES, l = tid % TAIL_LANES;  // the token that this lane shares, its number among those that do
+    const int i = tid / TAIL_LANES, l = tid % TAIL_LANES;  // the token (of TOK) that this lane shares, its number among those that do
+    const int tok = t0 + i;
     {
         float v[4];
 #pragma unroll
@@ -934,11 +951,11 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int it = l + TAIL_LANES * u, t = it < n_tiles ? tile_of(it) : nblk;
-            v[u] = kept[u] = t < nblk ? tmq[(int64_t)t * QLEN + i] : -INFINITY;
+            v[u] = kept[u] = t < nblk ? tmq[(int64_t)t * QLEN + tok] : -INFINITY;
         }
         for (int it = l + 4 * TAIL_LANES; it < n_tiles; it += TAIL_LANES) {  // more than that: a lane's share is one block
             const int t = tile_of(it);
-            if (t < nblk) kept[0] = fmaxf(kept[0], tmq[(int64_t)t * QLEN + i]);
+            if (t < nblk) kept[0] = fmaxf(kept[0], tmq[(int64_t)t * QLEN + tok]);
         }
         T = tail_nth_largest(kept, nprobe, l) - margin;
         auto list = [&](float m, int t) {
@@ -954,7 +971,7 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
         }
         for (int it = l + 4 * TAIL_LANES; it < n_tiles; it += TAIL_LANES) {
             const int t = tile_of(it);
-            if (t < nblk) list(tmq[(int64_t)t * QLEN + i], t);
+            if (t < nblk) list(tmq[(int64_t)t * QLEN + tok], t);
         }
     }
     __syncthreads();
@@ -981,10 +998,10 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                     ok[u] = it < n_items;
                     const int k = ok[u] ? it / chunks : 0, r = (it % chunks) * TAIL_LANES + l;
                     const int t = listed ? sh.sel_tile[i][k] : k;
-                    if (!listed && ok[u]) ok[u] = tmq[(int64_t)t * QLEN + i] >= T;
+                    if (!listed && ok[u]) ok[u] = tmq[(int64_t)t * QLEN + tok] >= T;
                     cc[u] = (int64_t)t * rows + r;
                     ok[u] = ok[u] && r < rows && cc[u] < C;
-                    sv[u] = ok[u] ? Sq[cc[u] * QLEN + i] : 0.f;
+                    sv[u] = ok[u] ? Sq[cc[u] * QLEN + tok] : 0.f;
                 }
 #pragma unroll
                 for (int u = 0; u < FLY; ++u)
@@ -1009,20 +1026,20 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
             __syncthreads();
             n_x = sh.xc_cnt[i];
             if (tid < 64) {  // where each token's rows start in the list of all
-                const int n = tid < QLEN && sh.xc_cnt[tid & (QLEN - 1)] <= TAIL_XCAP ? sh.xc_cnt[tid & (QLEN - 1)] : 0;
+                const int n = tid < TOK && sh.xc_cnt[tid & (TOK - 1)] <= TAIL_XCAP ? sh.xc_cnt[tid & (TOK - 1)] : 0;
                 int incl = n;
 #pragma unroll
                 for (int d = 1; d < QLEN; d <<= 1) {
                     const int below = __shfl_up(incl, d);
                     incl += tid >= d ? below : 0;
                 }
-                if (tid < QLEN) sh.xc_first[tid] = incl - n;
-                if (tid == QLEN - 1) sh.xc_first[QLEN] = incl;
+                if (tid < TOK) sh.xc_first[tid] = incl - n;
+                if (tid == TOK - 1) sh.xc_first[QLEN] = incl;
             }
             __syncthreads();
             const int n_all = sh.xc_first[QLEN];  // uniform
             ranked = n_x <= TAIL_XCAP;
-            if (x.matrix && n_all <= TAIL_ROWS) {
+            if (x.matrix && n_all <= ROWS) {
                 // a token's lanes fetch its rows, a 16-byte piece per lane, all of them before the first is used; the lower half
                 // of the dimensions is staged and multiplied, then the upper half (see tail_exact_rows; a wave keeps its tiles'
                 // sums in between)
@@ -1036,8 +1053,9 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                     if (u < mine) piece[u] = *reinterpret_cast<const float4 *>(src + (int64_t)sh.xc_id[i][u] * DIM);
                 }
                 if (ranked && l < n_x) sh.row_of[sh.xc_first[i] + l] = (int16_t)(i * TAIL_XCAP + l);
-                constexpr int TILES = TAIL_ROWS / 16 * (QLEN / 16) / (TAIL_THREADS / 64);  // of a wave
-                static_assert(TILES * (TAIL_THREADS / 64) == TAIL_ROWS / 16 * (QLEN / 16), "every wave has as many tiles");
+                // (tiles of 16 rows and 16 tokens: all the query's, or the one that a part's tokens lie in)
+                constexpr int ACROSS = TOK == QLEN ? QLEN / 16 : 1, TILES = (ROWS / 16 * ACROSS + THREADS / 64 - 1) / (THREADS / 64);  // of a wave
+                static_assert(TOK < QLEN || TILES * (THREADS / 64) == ROWS / 16 * ACROSS, "every wave has as many tiles");
                 const int lane = tid & 63, li = lane & 15, lg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
                 scq_double4 acc[TILES];
 #pragma unroll
@@ -1057,7 +1075,7 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                     __syncthreads();
 #pragma unroll
                     for (int t = 0; t < TILES; ++t) {
-                        const int at = wave + t * (TAIL_THREADS / 64), r0 = 16 * (at / (QLEN / 16)), c0 = 16 * (at % (QLEN / 16));
+                        const int at = wave + t * (THREADS / 64), r0 = 16 * (at / ACROSS), c0 = TOK == QLEN ? 16 * (at % ACROSS) : q16;
                         if (r0 < n_all) {  // uniform
                             const float *a = sh.row + (r0 + li) * TAIL_HSTRIDE + lg, *bq = sh.Qs + (c0 + li) * TAIL_QSTRIDE + half * (DIM / 2) + lg;
 #pragma unroll 8
@@ -1068,7 +1086,7 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                 }
 #pragma unroll
                 for (int t = 0; t < TILES; ++t) {
-                    const int at = wave + t * (TAIL_THREADS / 64), r0 = 16 * (at / (QLEN / 16)), c0 = 16 * (at % (QLEN / 16));
+                    const int at = wave + t * (THREADS / 64), r0 = 16 * (at / ACROSS), c0 = (TOK == QLEN ? 16 * (at % ACROSS) : q16) - t0;
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
                         if (r0 + 4 * r + lg < n_all) {  // (the row's own token is the only one of interest)
@@ -1077,21 +1095,22 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
                         }
                 }
             } else if (ranked && l < n_x) {
-                sh.xscore[i][l] = plaid_exact_dot(x.Cm + (int64_t)sh.xc_id[i][l] * DIM, sh.Qs + i * TAIL_QSTRIDE);
+                sh.xscore[i][l] = plaid_exact_dot(x.Cm + (int64_t)sh.xc_id[i][l] * DIM, sh.Qs + tok * TAIL_QSTRIDE);
             }
             if (!ranked)
                 walk([&](float sv, int64_t cc) {
-                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(plaid_exact_dot(x.Cm + cc * DIM, sh.Qs + i * TAIL_QSTRIDE), (uint32_t)cc));
+                    if (sv >= T) scq_insert_key<NP>(best, plaid_make_key(plaid_exact_dot(x.Cm + cc * DIM, sh.Qs + tok * TAIL_QSTRIDE), (uint32_t)cc));
                 });
             __syncthreads();
         }
         // A list entry can only be missing when the scores are not numbers (a query holding NaN compares false against
         // every threshold): later kernels index the inverted lists with these ids, so such a slot gets centroid j
         // (nprobe <= C), never an id out of range.
-        int32_t *probed_i = o.probed + ((int64_t)q * QLEN + i) * nprobe;
+        int32_t *probed_i = o.probed + ((int64_t)q * QLEN + tok) * nprobe;
         auto put = [&](int j, int32_t id) {
             probed_i[j] = id;
-            sh.idl[i * nprobe + j] = id;
+            if (TOK == QLEN) sh.idl[i * nprobe + j] = id;
+            else o.uniq[(int64_t)q * o.uniq_stride + tok * nprobe + j] = id;
         };
         if (__any(!ranked)) {
             // shuffle tree over the 32 lanes of this token (lanes l and l ^ d exchange lists; both keep the merged list)
@@ -1118,6 +1137,10 @@ __device__ __forceinline__ void tail_probes(ProbeScratch<APPROX> &sh, int q, con
             for (int j = 0; j < NP; ++j)
                 if (j < nprobe) put(j, best[j] == PLAID_KEY_MAX ? j : (int32_t)(best[j] & 0xFFFFFFFFu));
         }
+    }
+    if (TOK < QLEN) {
+        if (t0 == 0 && tid == 0) o.n_uniq[q] = QLEN * nprobe;
+        return;
     }
     __syncthreads();
     // ascending duplicate-free union of the n = 32 * nprobe (<= 256) probed ids: each id's place in sorted order by counting
@@ -1256,9 +1279,29 @@ __global__ __launch_bounds__(TAIL_THREADS) void stage1_tail_kernel(const float *
     const int q = blockIdx.x;
     const float *gmq = gmax + (int64_t)q * ng * QLEN;
     if (blockIdx.y == 0)
-        tail_probes<NP, APPROX>(sh.p, q, S, C, tilemax + (int64_t)q * nblk * QLEN, nblk, tile_rows, gmq, ng, gs, nprobe, o, x);
+        tail_probes<NP, APPROX, QLEN>(sh.p, q, 0, S, C, tilemax + (int64_t)q * nblk * QLEN, nblk, tile_rows, gmq, ng, gs, nprobe, o, x);
     else
         tail_survivors<APPROX>(sh.t, q, S, C, keepbits + (int64_t)q * keep_words, keep_words, gmq, ng, o, x);
+}
+
+// The same with a workgroup per TAIL_TOKENS query tokens (blockIdx.y; the last one: the survivors).
+template <int NP>
+__global__ __launch_bounds__(TAIL_THREADS) void stage1_parts_kernel(const float *__restrict__ S, int64_t C, uint32_t *__restrict__ keepbits,
+                                                                    int64_t keep_words, const float *__restrict__ tilemax, int nblk,
+                                                                    const float *__restrict__ gmax, int ng, int gs, int nprobe, Stage1Out o,
+                                                                    Stage1Exact x)
+{
+    __shared__ __align__(16) union {
+        ProbeScratch<true> p;
+        TableScratch<true> t;
+    } sh;
+    const int q = blockIdx.x;
+    const float *gmq = gmax + (int64_t)q * ng * QLEN;
+    if (blockIdx.y < QLEN / TAIL_TOKENS)
+        tail_probes<NP, true, TAIL_TOKENS>(sh.p, q, TAIL_TOKENS * (int)blockIdx.y, S, C, tilemax + (int64_t)q * nblk * QLEN, nblk, SM_WROWS,
+                                           gmq, ng, gs, nprobe, o, x);
+    else
+        tail_survivors<true>(sh.t, q, S, C, keepbits + (int64_t)q * keep_words, keep_words, gmq, ng, o, x);
 }
 
 // np = capacity of the tail's lists (1, 2, 4 or 8 >= nprobe); np = 0: scores and pruning bits only (large nprobe).
@@ -1311,7 +1354,15 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
 #define TAIL(NP_, AP_)                                                                                                     \
     hipLaunchKernelGGL((stage1_tail_kernel<NP_, AP_>), dim3(nq, 2), dim3(TAIL_THREADS), 0, st, S, C, keepbits, keep_words, \
                        tilemax, n_tiles, tile_rows, gmx, ng, gs, nprobe, o, x)
-        if (form == PLAID_SCQ_SPLIT16) {
+#define PARTS(NP_)                                                                                                              \
+    hipLaunchKernelGGL(stage1_parts_kernel<NP_>, dim3(nq, QLEN / TAIL_TOKENS + 1), dim3(TAIL_THREADS), 0, st, S, C, keepbits, keep_words, \
+                       tilemax, n_tiles, gmx, ng, gs, nprobe, o, x)
+        if (form == PLAID_SCQ_SPLIT16 && o.probes_apart) {
+            if (np == 1) PARTS(1);
+            else if (np == 2) PARTS(2);
+            else if (np == 4) PARTS(4);
+            else PARTS(8);
+        } else if (form == PLAID_SCQ_SPLIT16) {
             if (np == 1) TAIL(1, true);
             else if (np == 2) TAIL(2, true);
             else if (np == 4) TAIL(4, true);
@@ -1323,6 +1374,7 @@ static void launch_fused(hipStream_t st, int phases, int np, const float *centro
             else TAIL(8, false);
         }
 #undef TAIL
+#undef PARTS
     }
 }
 
@@ -1366,6 +1418,7 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
     o.qlist = s2.qlist;
     o.qlist_stride = s2.qlist_stride;
     o.need_hash = s2.need_hash;
+    o.probes_apart = s2.probes_apart;
     const int np = nprobe == 1 ? 1 : (nprobe == 2 ? 2 : (nprobe <= 4 ? 4 : (nprobe <= PLAID_PROBE_FAST_MAX ? 8 : 0)));
     if (np > 0)
         launch_fused(st, phases, np, centroids, C, Q, Qd, form, matrix_ok, A16, nq, t_cs, S, keepbits, ambbits, keep_words, tilemax, groupmax, nprobe,

@@ -1158,6 +1158,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         const int K = K_all;
         const int nu = n_uniq[q];
         __syncthreads();  // the previous query's readers are done
+        if (mode & 512) reinterpret_cast<int2 *>(area_all[0])[tid] = make_int2(-1, -1);
         if (tid < 64) {
             int32_t c = -1, d = -1;
             if (tid < K) {
@@ -1185,7 +1186,16 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         }
         if (!given) {
             static_assert(64 * IV_WAVES >= IV_LISTS, "one thread per probed list");
-            if (tid < nu) {
+            bool first = tid < nu;
+            if ((mode & 512) && first) {  // probes of several tokens may be the same: the first to enter its table of 512 places
+                int32_t *seen = reinterpret_cast<int32_t *>(area_all[0]);
+                for (uint32_t h = (uint32_t)probed_c * 0x9E3779B1u >> 23;; h = (h + 1) & 511u) {
+                    const int32_t was = atomicCAS(&seen[h], -1, probed_c);
+                    first = was == -1;
+                    if (first || was == probed_c) break;  // (at most 256 of the places are taken)
+                }
+            }
+            if (first) {
                 const int32_t c = probed_c;
                 const int32_t d = dense_id[c];
                 int slot = -1;
@@ -1699,7 +1709,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         hipLaunchKernelGGL(s2_union_wide_kernel, dim3((unsigned)nwide, nq), dim3(UW_THREADS), 0, st, uniq, n_uniq, uniq_stride,
                            ivf_offsets, ivf_pids, table, nr, shift, P, b.meta, dense_id, dense_bits, candbits, cand_words,
                            b.emptybits);
-    const int base = wide | (all_candidates ? 256 : 0);
+    const int base = wide | (all_candidates ? 256 : 0) | (b.probes_apart ? 512 : 0);
     const int given = uniq_stride > IV_LISTS ? 16 : 0;
     if (given)
         hipLaunchKernelGGL(s2_candidates_kernel, dim3((unsigned)((cand_words + 63) / 64), nq), dim3(64 * IV_WAVES), 0, st, uniq, n_uniq,

@@ -906,7 +906,8 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
 
     for (int32_t q0 = 0; q0 < nq; q0 += qc) {
         const int n = nq - q0 < qc ? nq - q0 : qc;
-        const Workspace w = carve(ws_base, ix, n, pl);
+        Workspace w = carve(ws_base, ix, n, pl);
+        w.s2.probes_apart = ix->ivr_table && form == PLAID_SCQ_SPLIT16 && plaid_probes_apart(n, C, nprobe);
         const float *Qc = Q + (int64_t)q0 * QLEN * DIM;
         const SelScratch sc3 = plaid_select_scratch_carve2(w.sel3_zero, w.sel3_body, n, pl.nd, pl.m3);
         const SelScratch sc4 = plaid_select_scratch_carve2(w.sel4_zero, w.sel4_body, n, pl.m3, pl.kk);

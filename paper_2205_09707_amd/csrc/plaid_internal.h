@@ -275,9 +275,19 @@ struct Stage2Buffers {   // all device pointers, leading dimension = query of th
     uint32_t *emptybits; // [nq][cand_words] candidates whose bag is empty
     uint64_t *blist;     // [nq][P] boundary list after the bin filter
     bool need_hash;      // the streaming form follows: the survivor table needs its hash
+    bool probes_apart;   // the probes of a query are found by several workgroups (plaid_probes_apart), and the inverted form, which
+                         //   follows, drops the duplicates among them
     // of the index (null when there is none: nearest-centroid assignment)
     const int64_t *ivf_offsets;  // [C + 1]: the probe kernel numbers the surviving centroids by list length
 };
+
+// Whether the probes of a query (nprobe <= PLAID_PROBE_FAST_MAX, split-fp16 scores) are found by a workgroup per eight of its tokens and
+// left with duplicates.  Eight tokens' phases take a third of the time of 32 on one compute unit, whose address units fetch the tiles'
+// rows a line per lane: probe kernel, one query of 16 384 / 65 536 / 262 144 centroids, nprobe 1 / 2 / 4, 11.1 / 17.3 / 26.6 -> 9.9 / 11.4 / 16.9
+// us (the survivors' workgroup), 23 of 10 007 16.6 -> 11.6.  Whole searches, us, before / so, 65 536 centroids, nprobe 4: 1 query 114 / 107, 8 175 /
+// 167, 31 440 / 435.  From 32 queries on the probe kernel has workgroups for half of the chip, and queries without survivors take their
+// candidates from the union (s2_union_wide_kernel).
+static constexpr bool plaid_probes_apart(int nq, int64_t C, int nprobe) { return C >= (int64_t)QLEN * nprobe && nq < 32; }
 
 // Eq. 3-5 over every candidate.  The streaming form (and the inverted one for queries with more than S2_MAX_KEPT surviving
 // centroids) writes dense score words.  The passage id of a stage-2 key is its position, so only the score half is stored:
