@@ -161,7 +161,7 @@ __device__ __forceinline__ void tail_exact_rows(const float *row, int n, const f
             const int r0 = 16 * (t / (QLEN / 16)), c0 = 16 * (t % (QLEN / 16));
             const float *a = row + (r0 + li) * TAIL_QSTRIDE + lg, *b = Qs + (c0 + li) * TAIL_QSTRIDE + lg;
             scq_double4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
+#pragma unroll 16
             for (int s = 0; s < DIM / 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[4 * s], (double)b[4 * s], acc, 0, 0, 0);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -230,7 +230,6 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     // query's gains are the same each time.  Stage 2 needs no particular order.
     if (K > 0 && K <= S2_MAX_KEPT) {
         int32_t my_id = 0;
-        int rank = 0;
         uint32_t *lens = trial;  // its first K words serve as the list lengths; the hash trials start from zeros
         for (int e = tid; need_hash && e < S2_NHASH * (S2_HASH / 32); e += nthreads)
             if (e >= K) trial[e] = 0u;
@@ -240,22 +239,42 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
             lens[tid] = ivf_offsets ? (uint32_t)(ivf_offsets[my_id + 1] - ivf_offsets[my_id]) : 0u;
         }
         if (APPROX)
-            for (int e = tid; e < K * (DIM / 4); e += nthreads)
-                *reinterpret_cast<float4 *>(x->row + e / (DIM / 4) * TAIL_QSTRIDE + 4 * (e % (DIM / 4))) =
-                    *reinterpret_cast<const float4 *>(Cm + (int64_t)ids[e / (DIM / 4)] * DIM + 4 * (e % (DIM / 4)));
-        __syncthreads();
-        if (tid < K) {
-            const uint32_t my_len = lens[tid];
-#pragma unroll 4
-            for (int u = 0; u < K; ++u) {
-                const uint32_t len = lens[u];
-                rank += (len > my_len || (len == my_len && ids[u] < my_id)) ? 1 : 0;
+            for (int e0 = tid; e0 < K * (DIM / 4); e0 += 2 * nthreads) {  // (two pieces in flight: all of them)
+                float4 piece[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int e = e0 + u * nthreads;
+                    piece[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (e < K * (DIM / 4)) piece[u] = *reinterpret_cast<const float4 *>(Cm + (int64_t)ids[e / (DIM / 4)] * DIM + 4 * (e % (DIM / 4)));
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int e = e0 + u * nthreads;
+                    if (e < K * (DIM / 4)) *reinterpret_cast<float4 *>(x->row + e / (DIM / 4) * TAIL_QSTRIDE + 4 * (e % (DIM / 4))) = piece[u];
+                }
             }
-            sh.rank[tid] = rank;
+        __syncthreads();
+        for (int e = tid; e < 16 * K; e += nthreads) {  // a slot's rank by counting, sixteen threads a slot (whole groups of them)
+            const int s = e >> 4;
+            const uint32_t my_len = lens[s];
+            const int32_t id = ids[s];
+            int rank = 0;
+#pragma unroll
+            for (int u0 = 0; u0 <= S2_MAX_KEPT; u0 += 16) {
+                const int u = u0 + (e & 15);
+                const uint32_t len = u < K ? lens[u] : 0u;
+                const int32_t other = u < K ? ids[u] : 0x7FFFFFFF;
+                rank += (len > my_len || (len == my_len && other < id)) ? 1 : 0;
+            }
+            rank += __shfl_xor(rank, 1);
+            rank += __shfl_xor(rank, 2);
+            rank += __shfl_xor(rank, 4);
+            rank += __shfl_xor(rank, 8);
+            if ((e & 15) == 0) sh.rank[s] = rank;
         }
         __syncthreads();
         if (tid < K) {
-            ids[rank] = my_id;
+            ids[sh.rank[tid]] = my_id;
             lens[tid] = 0u;
         }
         __syncthreads();
