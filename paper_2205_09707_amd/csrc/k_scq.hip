@@ -87,6 +87,7 @@ struct Stage1Out {          // per-query outputs of the tail (device pointers, l
     int32_t *qcount;        // [4] / [3][qlist_stride]: the queries by number of surviving centroids (none, 1..31, 32..63; more:
     int32_t *qlist;         //   from the end of the last row), appended as their workgroups finish (null: not recorded).
     int qlist_stride;       //   Stage 2 takes its queries from these lists.
+    int32_t *list_counts;   // stage 2's, to be cleared (null: none)
     bool need_hash;         // stage 2 will use the streaming form
     bool probes_apart;      // uniq holds every probe of the query, with duplicates and in no order
 };
@@ -217,7 +218,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
                                       int32_t *__restrict__ kept_ids_q, float *__restrict__ Tq, SurvivorScratch &sh,
                                       SurvivorRows *x = nullptr, const float *__restrict__ Cm = nullptr,
                                       const int64_t *__restrict__ ivf_offsets = nullptr, int q = 0,
-                                      int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0,
+                                      int32_t *qcount = nullptr, int32_t *qlist = nullptr, int qlist_stride = 0, int32_t *list_counts = nullptr,
                                       bool need_hash = true /* the streaming form looks survivors up */)
 {
     const int tid = threadIdx.x, nthreads = blockDim.x;
@@ -225,6 +226,7 @@ __device__ __forceinline__ void stage1_survivor_table(const float *__restrict__ 
     uint32_t *trial = sh.trial;
     float *colmm = sh.colmm, *Tx = sh.Tx;
     int K = misc[0];
+    if (list_counts && tid < S2_COPIES) list_counts[(int64_t)q * S2_COUNTS_QUERY + tid * S2_COUNT_STRIDE] = 0;
     if (C > (1ll << 26) - 2 && K <= S2_MAX_KEPT) K = S2_MAX_KEPT + 1;  // ids must fit the 26-bit field of a table entry
     // Slots in one order, whatever order the ids were found in: by decreasing inverted-list length, ties by id, so that a
     // query's gains are the same each time.  Stage 2 needs no particular order.
@@ -414,7 +416,7 @@ __global__ __launch_bounds__(512) void stage1_survivor_kernel(const float *__res
     stage1_survivor_table<false>(Sq, C,
                                  [&](float *colmm) { if (threadIdx.x < QLEN) colmm[threadIdx.x] = Sq[(int64_t)top1[threadIdx.x] * QLEN + threadIdx.x]; },
                                  o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT, o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, sh,
-                                 nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.need_hash);
+                                 nullptr, nullptr, o.ivf_offsets, q, o.qcount, o.qlist, o.qlist_stride, o.list_counts, o.need_hash);
 }
 
 // tilemax: [q][tile][32] column maxima of each tile (null: scores and pruning bits only).
@@ -1281,7 +1283,7 @@ __device__ __forceinline__ void tail_survivors(TableScratch<APPROX> &ts, int q, 
     static_assert(TAIL_THREADS <= S2_MAX_KEPT * TX_STRIDE, "the partial maxima take the place of the survivors' entries");
     stage1_survivor_table<APPROX>(Sq, C, col_max, o.meta + q, o.kept_ids + (int64_t)q * S2_MAX_KEPT,
                                   o.T + (int64_t)q * (S2_MAX_KEPT + 1) * QLEN, sh, APPROX ? ts.x : nullptr, x.Cm, o.ivf_offsets, q, o.qcount,
-                                  o.qlist, o.qlist_stride, o.need_hash);
+                                  o.qlist, o.qlist_stride, o.list_counts, o.need_hash);
 }
 
 template <int NP, bool APPROX>
@@ -1436,6 +1438,7 @@ void plaid_launch_stage1(hipStream_t st, int phases, const float *centroids, int
     o.qcount = s2.qcount;
     o.qlist = s2.qlist;
     o.qlist_stride = s2.qlist_stride;
+    o.list_counts = s2.list_counts;
     o.need_hash = s2.need_hash;
     o.probes_apart = s2.probes_apart;
     const int np = nprobe == 1 ? 1 : (nprobe == 2 ? 2 : (nprobe <= 4 ? 4 : (nprobe <= PLAID_PROBE_FAST_MAX ? 8 : 0)));

@@ -1001,7 +1001,7 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
                                                  int64_t cand_words, int64_t P, int32_t m, const S2Meta *__restrict__ meta,
                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
                                                  int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride, int lists,
-                                                 int id_shift, int32_t *__restrict__ hist1, int32_t *__restrict__ low,
+                                                 const int32_t *__restrict__ list_counts, int id_shift, int32_t *__restrict__ hist1, int32_t *__restrict__ low,
                                                  int32_t *lh /* [SEL_BINS + SEL2_SUB] */)
 {
     __shared__ int32_t scan[SEL_THREADS];
@@ -1012,7 +1012,27 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
     const S2Meta mt = meta[seg];
     if (mt.K == 0) return;  // no surviving centroid: no valid key, the state stays zero and the fill takes over
     const bool is_list = lists && mt.K <= S2_MAX_KEPT;
-    const int64_t n_items = is_list ? (int64_t)s->n_list : P;
+    // a list: its keys; in parts (launches of few queries): where they end, one after the other, and the way from there to their places
+    int64_t n_items = P;
+    int32_t part_end[DIGITS ? S2_COPIES : 1], part_at[DIGITS ? S2_COPIES : 1];
+    bool parts = false;
+    if (is_list) {  // uniform
+        const int32_t *counts = list_counts + (int64_t)seg * S2_COUNTS_QUERY;
+        int32_t n = counts[0];
+        if constexpr (DIGITS) {
+            parts = lists == 2;
+            if (parts) {  // uniform
+                n = 0;
+#pragma unroll
+                for (int x = 0; x < S2_COPIES; ++x) {
+                    part_at[x] = counts[x * S2_COUNT_STRIDE + 1] - n;
+                    n += counts[x * S2_COUNT_STRIDE];
+                    part_end[x] = n;
+                }
+            }
+        }
+        n_items = n;
+    }
     // a list is short next to the passages the grid is sized for: most of its workgroups have nothing to read
     if (blockIdx.x > 0 && (int64_t)blockIdx.x * SEL2_STEP >= n_items) return;
     int bstar, before;
@@ -1049,7 +1069,14 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
 #pragma unroll
             for (int u = 0; u < SEL2_GROUPS; ++u) {
                 const int64_t i = i0 + 64 * u + lane;
-                key[u] = i < n_items ? kl[i] : PLAID_KEY_MAX;
+                int32_t at = 0;
+                if constexpr (DIGITS)
+                    if (parts) {  // uniform
+                        at = part_at[0];
+#pragma unroll
+                        for (int x = 1; x < S2_COPIES; ++x) at = (int32_t)i >= part_end[x - 1] ? part_at[x] : at;
+                    }
+                key[u] = i < n_items ? kl[i + at] : PLAID_KEY_MAX;
             }
         } else {
             // word i is meaningful only when passage i is a candidate; it then holds its score word or "no score".  The
@@ -1127,9 +1154,10 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint6
                                                                   int64_t P, int32_t m, const S2Meta *__restrict__ meta,
                                                                   const int32_t *__restrict__ hist, Sel2State *state,
                                                                   uint64_t *__restrict__ out, int64_t out_stride,
-                                                                  uint64_t *__restrict__ blist, int64_t blist_stride, int lists)
+                                                                  uint64_t *__restrict__ blist, int64_t blist_stride, int lists,
+                                                                  const int32_t *__restrict__ list_counts)
 {
-    sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists, 0,
+    sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists, list_counts, 0,
                             nullptr, nullptr, nullptr);
 }
 __global__ __launch_bounds__(SEL_THREADS, 6) void sel2_bins_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
@@ -1137,11 +1165,12 @@ __global__ __launch_bounds__(SEL_THREADS, 6) void sel2_bins_kernel(const uint64_
                                                                 int32_t m, const S2Meta *__restrict__ meta,
                                                                 int32_t *hist, Sel2State *state, uint64_t *__restrict__ out,
                                                                 int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride,
-                                                                int lists, int id_shift, int32_t *__restrict__ hist1)
+                                                                int lists, const int32_t *__restrict__ list_counts, int id_shift,
+                                                                int32_t *__restrict__ hist1)
 {
     __shared__ int32_t lh[SEL_BINS + SEL2_SUB];
     sel2_filter_body<true>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists,
-                           id_shift, hist1, hist, lh);
+                           list_counts, id_shift, hist1, hist, lh);
 }
 
 template <int LEVEL>
@@ -1561,7 +1590,7 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
         // 32 1128 / 930 / 844; the other form 223, 397, 721, 1017.  Lists that need no digit pass: 24 of 400 000, ndocs 256, 178 / 178 / 180)
         const int gx_bins = nq > 16 && gx > 32 ? 32 : gx;
         hipLaunchKernelGGL(sel2_bins_kernel, dim3(gx_bins, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P, m,
-                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, id_shift, b.hist1);
+                           b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, b.list_counts, id_shift, b.hist1);
         hipLaunchKernelGGL(sel2_cut_kernel<1>, dim3(cut, nq), dim3(FIN_THREADS), 0, st, b.blist, P, b.state, b.hist1, b.hist, b.meta, lists,
                            id_shift, second, keys2, key_stride, b.emptybits, cand_words, P, m, out, out_stride, out_counts);
         if (second) {
@@ -1573,7 +1602,7 @@ void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, c
         return;
     }
     hipLaunchKernelGGL(sel2_filter_kernel, dim3(gx_filter, nq), dim3(SEL_THREADS), 0, st, keys2, key_stride, candbits, cand_words, P,
-                       m, b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists);
+                       m, b.meta, b.hist, b.state, out, out_stride, b.blist, P, lists, b.list_counts);
     // Digit filters: only a boundary list longer than SEL2_DIGIT_MIN makes them do anything.  The second pair is worth its
     // two launches for large indexes (a tie group can be as long as the index) in launches of several queries; otherwise
     // the query's finishing workgroup handles a long remainder alone (same result).  keys2 serves as the first

@@ -1072,9 +1072,9 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     int64_t nr, const float *__restrict__ S, int64_t C, const uint32_t *__restrict__ keepbits, int64_t keep_words,
     const int32_t *__restrict__ codes, const int64_t *__restrict__ doc_offsets, int64_t P, const S2Meta *__restrict__ meta,
     const int32_t *__restrict__ kept_ids, const float *__restrict__ T, uint32_t *__restrict__ candbits, int64_t cand_words,
-    uint64_t *__restrict__ keys2, int64_t key_stride, int32_t *__restrict__ hist, Sel2State *__restrict__ state,
-    uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits,
-    int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
+    uint64_t *__restrict__ keys2, int64_t key_stride, int32_t *__restrict__ hist,
+    int32_t *__restrict__ list_counts, uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id,
+    const uint32_t *__restrict__ dense_bits, int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
     int steps, int32_t m, int first_batch, unsigned main_blocks, uint32_t tall)
 {
     constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
@@ -1217,7 +1217,16 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         const int dense_row = lane < n_dense ? drow[lane] : 0;
         const int list_c = lane < n_ss ? kid[n_dense + lane] : -1;
         const bool all_probed = (uint32_t)__popc(pm0) + (uint32_t)__popc(pm1) == (uint32_t)K;
+        // this workgroup's part of the key list (s2_parts), one per XCD
         uint64_t *klist = keys2 + (int64_t)q * key_stride;
+        int32_t *count_q = list_counts + (int64_t)q * S2_COUNTS_QUERY;
+        if (!PLAIN && (mode & 1024)) {  // uniform
+            const int64_t passages = (int64_t)((IV_WAVES >> lend) * steps) << len_log;
+            const int64_t at = s2_list_part(rb & (S2_COPIES - 1), passages, P);
+            klist += at;
+            count_q += (rb & (S2_COPIES - 1)) * S2_COUNT_STRIDE;
+            if (rb < S2_COPIES && tid == 0) count_q[1] = (int32_t)at;
+        }
         uint32_t *cbq = candbits + (int64_t)q * cand_words;
         uint32_t *ebq = emptybits + (int64_t)q * cand_words;
         int32_t *hist_q = hist + (int64_t)q * SEL_BINS;
@@ -1513,7 +1522,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                 // addition to a uniform one a sum over the wave, and waits for the result at once.
                 int base = 0, place = 0;
                 s2_opaque(place);
-                if (lane == 0) base = atomicAdd(&state[q].n_list + place, total);
+                if (lane == 0) base = atomicAdd(count_q + place, total);
                 s2_wave_sync();
                 lcnt[lane] = (uint32_t)(rank - pc);
                 lcand[lane] = sel;
@@ -1673,6 +1682,13 @@ static constexpr int64_t s2_first_batch(int64_t P, int64_t nq, int64_t m, int le
     return share > few ? share : few;
 }
 
+// Whether a query's key list is in parts.  The waves of a single query reserve their first places at about the same time, and some ten
+// nanoseconds after one another where there is one counter: up to 20 us for the last of two thousand.  Parts cost the selection a
+// microsecond or two, which reads their numbers first.  us per search with one list / parts, one query: of 400 000 passages (391 waves, nprobe 2)
+// 78.7 / 78.9, of 800 000 84.4 / 83.0, of 2 M 93 / 87 (nprobe 1), 100 / 97, 133 / 127 (nprobe 4), of 4 M 117 / 108, of 8.8 M 229 / 220; four
+// of 2 M 113 / 110, 133 / 133, 167 / 168, of 4 M 149 / 149; sixteen of 400 000 152 / 155, of 2 M 253 / 260, of 4 M 337 / 352.
+static constexpr bool s2_parts(int nq, int64_t waves) { return nq == 1 && waves > 391; }
+
 // The numbers of survivors K (bit K - 32) whose queries the TALL instance takes in launches of many workgroups.  share: how
 // often a surviving centroid needs a plane (plaid_launch_ivf_plane_share): K of them need K share, give or take the root of K share
 // (1 - share).  With 26 planes four workgroups run on a compute unit, with 36 three: the second wins where it goes through whole
@@ -1693,7 +1709,7 @@ static constexpr uint32_t s2_tall_queries(double share)
     return set;
 }
 
-void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
+bool plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
                                   const int64_t *ivf_offsets, const int32_t *ivf_pids, const uint32_t *table, const float *S,
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
@@ -1730,7 +1746,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     hipLaunchKernelGGL((s2_invert_kernel<SH_, T_, PLAIN_, ALL_, TALL_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (GATHER_)),                    \
                        dim3(64 * IV_WAVES), 0, st, uniq,                                                                      \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \
-                       P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.state,         \
+                       P, b.meta, b.kept_ids, b.T, candbits, cand_words, keys2, key_stride, b.hist, b.list_counts,          \
                         b.emptybits, dense_id, dense_bits, MODE_, b.qcount, b.qlist, b.qlist_stride, NQX_, len_log,  \
                        steps, m, first_batch, (unsigned)((BLOCKS_) * (NQX_)), tall)
     // Updates of one histogram from several XCDs travel between their caches (one query of 8.8 M passages: 0.2 ms for the
@@ -1748,7 +1764,8 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const bool spread = nq <= 32;
     const int nqx = spread ? (nq | 1) : (nq + 7) & ~7;
     const int copies = spread && nq * blocks > 64 ? (4ll * m >= 3 * ((P + (1ll << len_log) - 1) >> len_log) ? 8 | 64 : 8) : 0;
-    const int own = copies | given;
+    const bool parts = copies && s2_parts(nq, (P + (1ll << len_log) - 1) >> len_log);
+    const int own = copies | given | (parts ? 1024 : 0);
     // Few workgroups, at most S2_FITS_BLOCKS: the 64-bit instance alone, taking every query (same sets, same scores, one launch
     // less, and no waiting of one class for the other: eight queries of 400 000 passages, thresholds 0.45 / 0.38 / 0.36: 83 / 138 /
     // 126 -> 73 / 72 / 102 us; 24 of 200 000, 0.5 / 0.36: 71 / 113 -> 65 / 70); with twice the workgroups, so that queries with
@@ -1782,6 +1799,7 @@ void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
         }
     }
 #undef S2_INVERT
+    return parts;
 }
 
 // ------------------------------------------------------------------ host side

@@ -804,6 +804,7 @@ static Workspace carve(char *base, const plaid_index *ix, int qc, const Plan &pl
     w.s2.emptybits = (uint32_t *)take((size_t)qc * w.cand_words * 4);
     w.s2.qlist = (int32_t *)take((size_t)3 * qc * 4);
     w.s2.qlist_stride = qc;
+    w.s2.list_counts = (int32_t *)w.Qd;
     w.s2.need_hash = ix->ivr_table == nullptr;
     w.s2.ivf_offsets = ix->ivf_offsets;
     w.sel2 = (uint64_t *)take((size_t)qc * pl.nd * 8);
@@ -932,8 +933,9 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
                                    w.cand_words);
         STAMP();
         // stage 2: centroid interaction with pruning over every candidate (Eq. 3-5), keep ndocs
+        int lists = 0;  // 2: in parts
         if (ix->ivr_table)
-            plaid_launch_stage2_inverted(st, w.uniq, w.n_uniq, w.uniq_stride, ix->ivf_offsets, ix->ivf_pids, ix->ivr_table, w.S,
+            lists = 1 + plaid_launch_stage2_inverted(st, w.uniq, w.n_uniq, w.uniq_stride, ix->ivf_offsets, ix->ivf_pids, ix->ivr_table, w.S,
                                          C, w.keepbits, w.keep_words, ix->codes, ix->doc_offsets, P, n, w.s2, w.candbits,
                                          w.cand_words, w.keys2, P, ix->dense_id, ix->dense_bits, ix->plane_share, ix->ivr_shift, pl.nd,
                                          dbg && (dbg->cand || dbg->n_cand));
@@ -942,7 +944,7 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
                                 ix->doc_offsets, ix->codes, n, w.s2, w.keys2, P);
         STAMP();
         plaid_launch_select2(st, w.keys2, P, w.candbits, n, P, w.cand_words, pl.nd, w.s2, w.sel2, pl.nd, w.n2,
-                             ix->ivr_table ? 1 : 0);
+                             lists);
         STAMP();
         // stage 3: centroid interaction without pruning (Eq. 3-4), keep ndocs/4
         plaid_launch_ci_list(st, w.S, C, ix->doc_offsets, ix->codes, n, w.sel2, pl.nd, w.n2, pl.nd, w.keys3, pl.nd);

@@ -237,13 +237,29 @@ struct Sel2State {
     int32_t n_b2;                      // ... after the second one (only when it is launched and n_b1 > SEL2_DIGIT_MIN)
     int32_t m_rem2;
     int32_t shift2, width2;
-    int32_t n_list;                    // scored candidates in the key list (inverted form, K <= S2_MAX_KEPT)
     int32_t bin;                       // the boundary bin
     int32_t arrived[2];                // workgroups of each of sel2_cut_kernel's passes that have handed over what they kept
     uint32_t ord_max, ord_nmin;        // extremes of a long boundary list's score words (sel2_bins_kernel); the latter's complement
-    int32_t pad[7];
+    int32_t pad[8];
 };
 static_assert(sizeof(Sel2State) == 128, "Sel2State is a 128-byte record");
+
+// The key list of a single query of the inverted form is in S2_COPIES parts where it has many waves (s2_parts): that of a workgroup is its number among the query's, modulo their number.  A part has room for all passages of its workgroups; the one of the
+// last workgroup, whose passages may be fewer, comes last, so that all of them together have room for P.  First place of the part:
+static constexpr __host__ __device__ __forceinline__ int64_t s2_list_part(int part, int64_t passages, int64_t P)
+{
+    const int64_t blocks = (P + passages - 1) / passages;
+    const int last = (int)((blocks - 1) % S2_COPIES);
+    int64_t before = 0;  // workgroups of the parts that come before
+    for (int i = 1; i <= S2_COPIES; ++i) {
+        const int p = (last + i) % S2_COPIES;
+        if (p == part) break;
+        before += (blocks - p + S2_COPIES - 1) / S2_COPIES;
+    }
+    return before * passages;
+}
+#define S2_COUNT_STRIDE 32                // words from a part's number of keys, which its first place follows, to the next one's: a cache line
+#define S2_COUNTS_QUERY (QLEN * DIM * 2)  // ... and from a query's to the next one's
 
 // Bin of a finite pruned score: 0 for the best scores, SEL_BINS-1 for the worst.  Monotone in the score, so bins
 // never contradict the ranking; producer and selection call this same function on the same inputs.
@@ -268,6 +284,8 @@ struct Stage2Buffers {   // all device pointers, leading dimension = query of th
     int32_t *qlist;      // [3][qlist_stride] those queries, in the order their probe workgroups finished; those with more
                          //   than S2_MAX_KEPT from the end of the last row
     int qlist_stride;
+    int32_t *list_counts;  // [nq][S2_COUNTS_QUERY] keys in the list's parts, S2_COUNT_STRIDE apart (in the place of the query's score operands;
+                         //   the probe kernel clears them; null: no stage 2)
     S2Meta *meta;        // [nq]
     int32_t *kept_ids;   // [nq][S2_MAX_KEPT]
     float *T;            // [nq][S2_MAX_KEPT+1][32] rows of the surviving centroids; in the place of row 0 the gains of the
@@ -303,16 +321,16 @@ void plaid_launch_stage2(hipStream_t st, const float *S, int64_t C, const uint32
 // Inverted form of candidate generation + stage 2 (k_stage2.hip): the outputs of plaid_launch_ivf_union followed by
 // plaid_launch_stage2 (candbits included, which need not be cleared beforehand), computed from the inverted lists of
 // the probed and the surviving centroids.  Queries with 1 .. S2_MAX_KEPT surviving centroids leave a LIST of 64-bit keys in
-// their region of keys2 (Sel2State::n_list of them, any order) instead of dense words; it and the coarse histogram (in the
+// their region of keys2 (any order; s2_list_part, list_counts) instead of dense words; it and the coarse histogram (in the
 // place of the fine one) hold every candidate that can be among the best m (= the m of the selection that follows), not
 // those proven not to be.  table: plaid_ivf_range_table_bytes(C, P, shift) bytes filled once per index
 // by plaid_launch_ivf_range_table.
-// shift: log2 of the passages per table column, 11 or 13.  all_candidates: the candidate words are complete (otherwise they, and the
+// Returns whether the lists are in parts.  shift: log2 of the passages per table column, 11 or 13.  all_candidates: the candidate words are complete (otherwise they, and the
 // empty-bag words, may be missing where m scores were known already: the selection that follows does not read them then).
 size_t plaid_ivf_range_table_bytes(int64_t C, int64_t P, int shift);
 void plaid_launch_ivf_range_table(hipStream_t st, const int64_t *ivf_offsets, const int32_t *ivf_pids, int64_t C, int64_t P,
                                   int shift, uint32_t *table);
-void plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
+bool plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int32_t *n_uniq, int uniq_stride,
                                   const int64_t *ivf_offsets, const int32_t *ivf_pids, const uint32_t *table, const float *S,
                                   int64_t C, const uint32_t *keepbits, int64_t keep_words, const int32_t *codes,
                                   const int64_t *doc_offsets, int64_t P, int nq, const Stage2Buffers &b, uint32_t *candbits,
@@ -360,7 +378,7 @@ void plaid_launch_ivf_build_fill(hipStream_t st, const int32_t *codes, const int
 // boundary bin is over-long), then from the empty candidates in pid order.  keys2 is overwritten (scratch).
 void plaid_launch_select2(hipStream_t st, uint64_t *keys2, int64_t key_stride, const uint32_t *candbits, int nq, int64_t P,
                           int64_t cand_words, int32_t m, const Stage2Buffers &b, uint64_t *out, int64_t out_stride,
-                          int32_t *out_counts, int lists /* 1 after the inverted form */);
+                          int32_t *out_counts, int lists /* after the inverted form: 1, 2 where the lists are in parts */);
 
 // Eq. 3-4 over a key list (stage 3): out_keys[q][j] is the key of the passage of in_keys[q][j].
 void plaid_launch_ci_list(hipStream_t st, const float *S, int64_t C, const int64_t *doc_offsets, const int32_t *codes,
