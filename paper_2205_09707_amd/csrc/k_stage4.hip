@@ -446,6 +446,105 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
     }
 }
 
+// Stage 3's cut and the scores of what it keeps in one launch, for lists of up to CUT_KEYS keys (short launches): a workgroup per key of the
+// list, which counts the keys before its own and leaves if there are m of them; otherwise its passage's score goes to the place of that
+// number in out_keys.  The four waves share the passage as above.  Bound by the round trips to memory that follow one another (keys, code,
+// scores), which a launch's start and a list that goes through memory only add to: one query of 400 000 passages, 1024 keys of which 256
+// stay, 5.2 and 6.9 us as two launches, 6.9 us so; 256 keys of which 64 stay 4.2 and 5.5, 4.8 so.
+#define CUT_KEYS 1024
+template <int NBITS, bool RN, bool WIDE>
+__global__ __launch_bounds__(256, 3) void cut_maxsim_kernel(
+    const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
+    const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
+    const float *__restrict__ inv_norm, const uint64_t *__restrict__ in_keys, int64_t in_stride, const int32_t *__restrict__ in_counts,
+    int32_t m, uint64_t *__restrict__ out_keys, int64_t out_stride, int32_t *__restrict__ out_counts)
+{
+    constexpr int RB = 16 * NBITS, RW = 2 * NBITS, EACH = CUT_KEYS / 256;
+    __shared__ typename S4Entry<NBITS>::type hlut[S4_SECOND + 256];
+    __shared__ float wmax[4][QLEN];
+    __shared__ s4_half8 qs[2][8][64];  // [term][step of 16 dimensions][lane]
+    __shared__ int32_t fewer[4];
+    const int q = blockIdx.y, j = blockIdx.x;
+    const int n = in_counts[q] < CUT_KEYS ? in_counts[q] : CUT_KEYS;
+    if (j == 0 && threadIdx.x == 0) out_counts[q] = m < n ? m : n;
+    if (j >= n) return;  // uniform
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r32 = lane & 31, h = lane >> 5;
+    const uint64_t *keys = in_keys + (int64_t)q * in_stride;
+    uint64_t other[EACH];
+#pragma unroll
+    for (int u = 0; u < EACH; ++u) other[u] = (int)threadIdx.x + 256 * u < n ? keys[threadIdx.x + 256 * u] : PLAID_KEY_MAX;
+    const uint64_t mine = keys[j];
+    const uint32_t pid = (uint32_t)mine;
+    const int64_t t0 = doc_offsets[pid], t1 = doc_offsets[(int64_t)pid + 1];
+    int before = 0;
+#pragma unroll
+    for (int u = 0; u < EACH; ++u) before += __popcll(__ballot(other[u] < mine));
+    if (lane == 0) fewer[wave] = before;
+    __syncthreads();
+    const int rank = fewer[0] + fewer[1] + fewer[2] + fewer[3];
+    if (rank >= m) return;  // uniform
+    const int len = (int)(t1 - t0);
+    int32_t code = 0;
+    float nf = 1.0f;
+    uint32_t rw[RW] = {0};
+    auto request = [&](int b) {
+        const int row = b + r32;  // this lane's passage token
+        const int64_t tok = t0 + (row < len ? row : len - 1);
+        code = codes[tok];
+        if (RN) nf = inv_norm[tok];
+        if (NBITS == 2) {
+            const uint4 v = reinterpret_cast<const uint4 *>(residuals + tok * RB)[h];
+            rw[0] = v.x, rw[1] = v.y, rw[2 % RW] = v.z, rw[3 % RW] = v.w;
+        } else {
+            const uint2 v = reinterpret_cast<const uint2 *>(residuals + tok * RB)[h];
+            rw[0] = v.x, rw[1] = v.y;
+        }
+    };
+    if (32 * wave < len) request(32 * wave);
+    s4_build_tables<NBITS>(hlut, weights, threadIdx.x, 256);
+    s4_stage_query(Q + (int64_t)q * QLEN * DIM, qs);
+    __syncthreads();
+    const char *Sq = reinterpret_cast<const char *>(S + (int64_t)q * C * QLEN);
+    float mx[16];  // running maxima of this lane's column class: query token 8 (v / 4) + 4 h + v % 4
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mx[v] = -INFINITY;
+    for (int base = 32 * wave; base < len; base += 128) {  // uniform for the wave
+        float4 sv[4];
+        {
+            typename std::conditional<WIDE, uint64_t, uint32_t>::type off = (uint32_t)code;
+            off = off * (uint32_t)(QLEN * 4) + 16u * (uint32_t)h;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) sv[g] = *reinterpret_cast<const float4 *>(Sq + off + 32u * g);
+        }
+        uint32_t now[RW];
+#pragma unroll
+        for (int e = 0; e < RW; ++e) now[e] = rw[e];
+        const float f = nf;
+        if (base + 128 < len) request(base + 128);
+        floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        floatx16 acx = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // cross terms, scaled by 2^11
+        s4_products<NBITS, false, true, 0, 0>(now, hlut, qs, nullptr, nullptr, lane, acc, acx);
+        const float svf[16] = {sv[0].x, sv[0].y, sv[0].z, sv[0].w, sv[1].x, sv[1].y, sv[1].z, sv[1].w,
+                               sv[2].x, sv[2].y, sv[2].z, sv[2].w, sv[3].x, sv[3].y, sv[3].z, sv[3].w};
+        if (base + r32 < len) {  // this lane's column is a token of the passage
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float x = fmaf(acx[v], 1.0f / S4_SCALE, acc[v]) + svf[v];
+                if (RN) x *= f;
+                mx[v] = s4_max(mx[v], x);
+            }
+        }
+    }
+    const float cm = s4_column_maxima(mx, lane);  // query token s4_token_of_lane(lane), in even and odd lane alike
+    if (!(lane & 1)) wmax[wave][s4_token_of_lane(lane)] = cm;
+    __syncthreads();
+    const float best = fmaxf(fmaxf(wmax[0][r32], wmax[1][r32]), fmaxf(wmax[2][r32], wmax[3][r32]));
+    const float total = plaid_sum32_in_order(best);
+    if (threadIdx.x == 0) out_keys[(int64_t)q * out_stride + rank] = plaid_make_key(len > 0 ? total : -INFINITY, pid);
+}
+
 // Many passages per wave: the tokens to score are listed in LDS, VP_GROUP passages at a time, each passage's rounded up to
 // eight by repeats of its last one, and the steps of 32 tokens run over the list whatever passage a token belongs to.  Rows
 // of the matrix instruction are list positions, columns query tokens: lane 32 h + n gets, for query token n, positions
@@ -1065,6 +1164,37 @@ void plaid_launch_vanilla_prune(hipStream_t st, const float *Q, const float *S, 
 // 159 / 167, of 128 162 / 157 and 193 / 199, of 192 234 / 224 and 281 / 285; 384 queries: of 96 115 / 108 and 134 / 139, of 128 140 / 119
 // and 162 / 153.
 static constexpr bool s4_packed(int n_upper, int nq) { return n_upper >= 96 && (int64_t)n_upper * nq >= 48ll * VP_RESIDENT_BLOCKS; }
+
+// Whether the cut of lists of up to n_upper keys and the scores of the m best are one launch: the workgroups that only count and leave are
+// three of four, each of which reads its query's whole list, so the launch is bound by them from some 8000 keys on, a few for each place
+// of the chip.  Whole searches in us, as one launch and as two, with 1024 keys a query of 400 000 passages: 4 queries 97 / 102, 8 queries 115 /
+// 120, 12 queries 144 / 138, 31 queries 276 / 244; 40 000 passages: 6 queries 80 / 85, 12 queries 101 / 91, 31 queries 151 / 119; 256 keys a
+// query of 200 000 passages: 12 queries 83 / 88, 31 queries 122 / 129, 40 queries 141 / 135, 96 queries 245 / 224.
+static constexpr bool s4_cuts(int n_upper, int nq) { return n_upper <= CUT_KEYS && (int64_t)n_upper * nq <= 8192; }
+bool plaid_launch_cut_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets, const int32_t *codes,
+                             const uint8_t *residuals, const float *bucket_weights, int nbits, int nq, const uint64_t *in_keys,
+                             int64_t in_stride, const int32_t *in_counts, int n_upper, int32_t m, uint64_t *out_keys, int64_t out_stride,
+                             int32_t *out_counts, const float *inv_norm)
+{
+    if (n_upper <= 0 || nq <= 0 || !s4_cuts(n_upper, nq)) return false;
+    const bool wide = plaid_wide(C, N);
+#define PLAID_S4_CUT(NB, RN, WIDE)                                                                                              \
+    hipLaunchKernelGGL((cut_maxsim_kernel<NB, RN, WIDE>), dim3((unsigned)n_upper, (unsigned)nq), dim3(256), 0, st, Q, S, C,        \
+                       doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, in_counts, m, out_keys,       \
+                       out_stride, out_counts)
+#define PLAID_S4_CUTS(NB)                                  \
+    do {                                                   \
+        if (inv_norm && wide) PLAID_S4_CUT(NB, true, true); \
+        else if (inv_norm) PLAID_S4_CUT(NB, true, false);   \
+        else if (wide) PLAID_S4_CUT(NB, false, true);       \
+        else PLAID_S4_CUT(NB, false, false);                \
+    } while (0)
+    if (nbits == 2) PLAID_S4_CUTS(2);
+    else PLAID_S4_CUTS(1);
+#undef PLAID_S4_CUTS
+#undef PLAID_S4_CUT
+    return true;
+}
 
 void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets,
                                     const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,

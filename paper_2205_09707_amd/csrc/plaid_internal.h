@@ -244,8 +244,9 @@ struct Sel2State {
 };
 static_assert(sizeof(Sel2State) == 128, "Sel2State is a 128-byte record");
 
-// The key list of a single query of the inverted form is in S2_COPIES parts where it has many waves (s2_parts): that of a workgroup is its number among the query's, modulo their number.  A part has room for all passages of its workgroups; the one of the
-// last workgroup, whose passages may be fewer, comes last, so that all of them together have room for P.  First place of the part:
+// The key list of a single query of the inverted form is in S2_COPIES parts where it has many waves (s2_parts).  A workgroup's part is
+// its number among the query's modulo theirs.  A part has room for all passages of its workgroups; that of the last workgroup, whose
+// passages may be fewer, comes last, so that all of them together have room for P.  First place of a part:
 static constexpr __host__ __device__ __forceinline__ int64_t s2_list_part(int part, int64_t passages, int64_t P)
 {
     const int64_t blocks = (P + passages - 1) / passages;
@@ -325,8 +326,9 @@ void plaid_launch_stage2(hipStream_t st, const float *S, int64_t C, const uint32
 // place of the fine one) hold every candidate that can be among the best m (= the m of the selection that follows), not
 // those proven not to be.  table: plaid_ivf_range_table_bytes(C, P, shift) bytes filled once per index
 // by plaid_launch_ivf_range_table.
-// Returns whether the lists are in parts.  shift: log2 of the passages per table column, 11 or 13.  all_candidates: the candidate words are complete (otherwise they, and the
-// empty-bag words, may be missing where m scores were known already: the selection that follows does not read them then).
+// Returns whether the lists are in parts.  shift: log2 of the passages per table column, 11 or 13.  all_candidates: the candidate
+// words are complete (otherwise they, and the empty-bag words, may be missing where m scores were known already: the selection that
+// follows does not read them then).
 size_t plaid_ivf_range_table_bytes(int64_t C, int64_t P, int shift);
 void plaid_launch_ivf_range_table(hipStream_t st, const int64_t *ivf_offsets, const int32_t *ivf_pids, int64_t C, int64_t P,
                                   int shift, uint32_t *table);
@@ -393,6 +395,12 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
                                     int nbits, int nq, const uint64_t *in_keys, int64_t in_stride,
                                     const int32_t *in_counts, int n_upper, uint64_t *out_keys, int64_t out_stride,
                                     const float *inv_norm = nullptr /* [N]: reconstructed vectors scaled to unit length */);
+// The cut of a key list to its m best and their scores as above in one launch, where the lists are short (returns false, and does nothing,
+// where they are not): in any order to out_keys, their number to out_counts.
+bool plaid_launch_cut_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets, const int32_t *codes,
+                             const uint8_t *residuals, const float *bucket_weights, int nbits, int nq, const uint64_t *in_keys,
+                             int64_t in_stride, const int32_t *in_counts, int n_upper, int32_t m, uint64_t *out_keys, int64_t out_stride,
+                             int32_t *out_counts, const float *inv_norm);
 
 // Section 4.5 alone: reconstructed vectors / bucket indices of listed passages.
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,

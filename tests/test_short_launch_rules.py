@@ -1,0 +1,82 @@
+"""Where a single query's key list is in parts, and that the parts' places neither overlap nor leave the list; which lists are cut and scored
+by one launch.  On the GPU, a query whose list is in parts against the same one in a launch of four, where none is."""
+import os
+import shutil
+import subprocess
+
+import pytest
+import torch
+
+from test_build_properties import CSRC, HIPCC, ROOT
+
+PARTS = """
+constexpr bool parts_fit(int64_t passages, int64_t P) {  // a workgroup's passages; at most S2_COPIES parts, each with its workgroups' places
+    const int64_t blocks = (P + passages - 1) / passages;
+    int64_t from[S2_COPIES] = {}, need[S2_COPIES] = {};
+    for (int p = 0; p < S2_COPIES && p < blocks; ++p) {
+        from[p] = s2_list_part(p, passages, P);
+        for (int64_t b = p; b < blocks; b += S2_COPIES) need[p] += b + 1 < blocks ? passages : P - b * passages;
+    }
+    for (int p = 0; p < S2_COPIES && p < blocks; ++p) {
+        if (from[p] < 0 || from[p] + need[p] > P) return false;
+        for (int o = 0; o < p; ++o)
+            if (from[p] < from[o] + need[o] && from[o] < from[p] + need[p]) return false;
+    }
+    return true;
+}
+"""
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+def test_rules_of_parts_and_cuts(tmp_path):
+    claims = ["s2_parts(1, 392)", "!s2_parts(1, 391)", "!s2_parts(2, 4297)"]
+    claims += [f"parts_fit({n}, {P})" for n in (1024, 4096, 8192, 16384) for P in (1, 1023, 400_385, 405_003, 409_600, 800_769, 8 * 16384, 8 * 16384 + 1,
+                                                                                   2_000_001, 8_800_000, (1 << 31) - 1)
+               if P < 1_000_000 or n > 4096]
+    for src, body in (("k_stage2.hip", PARTS + "".join(f'static_assert({c}, "{c}");\n' for c in claims)),
+                      ("k_stage4.hip", "".join(f'static_assert({c}, "{c}");\n' for c in (
+                          "s4_cuts(1024, 8)", "!s4_cuts(1024, 9)", "!s4_cuts(1025, 1)", "s4_cuts(256, 32)", "!s4_cuts(256, 33)", "s4_cuts(1, 8192)")))):
+        unit = tmp_path / ("rules_" + src)
+        unit.write_text(f'#include "{src}"\n' + body)
+        r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-fconstexpr-steps=100000000", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+                            "--cuda-host-only", "-fsyntax-only", str(unit)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P", [400_385, 409_600, 800_769, 1_000_003])
+def test_a_list_in_parts(P):
+    import paper_2205_09707_amd as pl
+    C = 3000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1)
+    offsets = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(torch.randint(0, 5, (P,), generator=g, device="cuda"), 0)
+    N = int(offsets[-1])
+    codes = (torch.rand(N, generator=g, device="cuda") ** 3 * C).int().clamp_(max=C - 1)
+    ivf_offsets, ivf_pids = pl.plaid_build_ivf(codes, offsets, C)
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
+              "residuals": torch.randint(0, 256, (N, 16), generator=g, device="cuda", dtype=torch.uint8),
+              "bucket_weights": torch.tensor([-0.05, 0.06], device="cuda")}
+    Q = torch.nn.functional.normalize(cen[codes[torch.randint(0, N, (4 * 32,), generator=g, device="cuda")].long()]
+                                      + 0.05 * torch.randn(4 * 32, 128, generator=g, device="cuda"), dim=1).reshape(4, 32, 128).contiguous()
+    idx = pl.plaid_index_from_view(arrays, 1, device=0, copy=False)
+    try:
+        for nprobe, t_cs, ndocs in [(1, 0.5, 256), (4, 0.4, 4096), (2, 0.3, 60_000), (2, 0.99, 1024)]:
+            pl.plaid_set_max_chunk(idx, 4)
+            many = pl.plaid_search_debug(idx, Q, nprobe, t_cs, ndocs, 50, want=["n_cand", "n2", "sel3_ids", "n3"])
+            pl.plaid_set_max_chunk(idx, 1)
+            one = pl.plaid_search_debug(idx, Q, nprobe, t_cs, ndocs, 50, want=["n_cand", "n2", "sel3_ids", "n3"])
+            ids, scores = pl.plaid_search(idx, Q, nprobe, t_cs, ndocs, 50)
+            torch.cuda.synchronize()
+            print(P, nprobe, "candidates", many[2]["n_cand"].tolist())
+            for name in ("n_cand", "n2", "n3", "sel3_ids"):
+                a, b = many[2][name], one[2][name]
+                if name == "sel3_ids":  # (a set)
+                    a, b = torch.sort(a, dim=1).values, torch.sort(b, dim=1).values
+                assert torch.equal(a, b), (name, nprobe)
+            for a, b in ((ids, scores), one[:2]):
+                assert torch.equal(a, many[0]) and torch.equal(b, many[1]), nprobe
+    finally:
+        pl.plaid_index_free(idx)
