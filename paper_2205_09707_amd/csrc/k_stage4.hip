@@ -1342,9 +1342,12 @@ void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, in
                        capacity, work, refused, ticket, report);
 }
 
-// Same table, same lookup and same addition as the fused kernel; thread t handles dimensions 4t .. 4t+3.
+// Same table, same lookup and same addition as the fused kernel; a workgroup per passage, of 256 or 512 threads, of which 32 have a
+// token, 4 dimensions each.  Bound by its writes and by the centroid rows, 512 bytes a token each: what is written goes past the caches
+// (nontemporal stores), which then hold more of the rows.  5000 passages of 65 tokens 51.0 -> 41.5 us, 50 000 662 -> 544 us.
+typedef float s4_float4 __attribute__((ext_vector_type(4)));
 template <int NBITS>
-__global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__restrict__ centroids,
+__global__ __launch_bounds__(512) void decompress_dump_kernel(const float *__restrict__ centroids,
                                                               const int64_t *__restrict__ doc_offsets,
                                                               const int32_t *__restrict__ codes,
                                                               const uint8_t *__restrict__ residuals,
@@ -1361,7 +1364,8 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
     __shared__ uint32_t ilut[256 * (NBITS == 2 ? 1 : 2)];
     // (uniform) refused by passage_offsets_kernel; another call that is refused meanwhile leaves another ticket
     if (*refused == ticket) return;
-    build_tables<NBITS>(wlut, ilut, weights, threadIdx.x, 256);
+    const int threads = blockDim.x, rows = threads >> 5;  // uniform
+    build_tables<NBITS>(wlut, ilut, weights, threadIdx.x, threads);
     __syncthreads();
     const int a = blockIdx.x;
     const int32_t pid = pids[a];
@@ -1370,14 +1374,14 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
     const int64_t o0 = out_offsets[a];
     const int quad = threadIdx.x & 31;
     // four rows per thread in flight: code and residual, then the centroid's piece, then the stores
-    for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 32) {
+    for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 4 * rows) {
         int slot[4];
         int32_t code[4];
         float4 c[4];
         float f[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int row = row0 + 8 * u < len ? row0 + 8 * u : row0;  // (a row past the end repeats the first)
+            const int row = row0 + rows * u < len ? row0 + rows * u : row0;  // (a row past the end repeats the first)
             code[u] = codes[t0 + row];
             slot[u] = table_slot<NBITS>(residuals + (t0 + row) * RB, quad);
             f[u] = inv_norm ? inv_norm[t0 + row] : 1.0f;
@@ -1386,30 +1390,36 @@ __global__ __launch_bounds__(256) void decompress_dump_kernel(const float *__res
         for (int u = 0; u < 4; ++u) c[u] = *reinterpret_cast<const float4 *>(centroids + (int64_t)code[u] * DIM + 4 * quad);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int row = row0 + 8 * u;
+            const int row = row0 + rows * u;
             if (row >= len) break;
             const float4 w = wlut[slot[u]];
             if (out_vectors) {
                 float4 d = make_float4(c[u].x + w.x, c[u].y + w.y, c[u].z + w.z, c[u].w + w.w);
                 // scaled to unit length: one fp32 factor per token, one rounding per component
                 if (inv_norm) d = make_float4(d.x * f[u], d.y * f[u], d.z * f[u], d.w * f[u]);
-                *reinterpret_cast<float4 *>(out_vectors + (o0 + row) * DIM + 4 * quad) = d;
+                __builtin_nontemporal_store(s4_float4{d.x, d.y, d.z, d.w}, reinterpret_cast<s4_float4 *>(out_vectors + (o0 + row) * DIM + 4 * quad));
             }
-            if (out_indices) *reinterpret_cast<uint32_t *>(out_indices + (o0 + row) * DIM + 4 * quad) = ilut[slot[u]];
+            if (out_indices) __builtin_nontemporal_store(ilut[slot[u]], reinterpret_cast<uint32_t *>(out_indices + (o0 + row) * DIM + 4 * quad));
         }
     }
 }
-void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
+// Threads of a passage, by the collection's tokens per passage: more have more of a passage's rows in flight at once, fewer leave fewer
+// idle.  us of the kernel with 256 / 512 / 1024, 50 000 passages of 1 to 8 tokens 62 / 87 / 158, of 8 to 24 133 / 157 / 242, of 12 to 36
+// 200 / 195 / 298, of 24 to 40 267 / 260 / 337, of 30 to 100 544 / 536 / 518; 5000 of 1 to 8 7.4 / 8.8 / 14.2, of 8 to 24 16.2 / 18.7 / 27.2, of
+// 12 to 36 23.6 / 23.4 / 33.3, of 30 to 100 41.5 / 39.3 / 41.8; 500 of 200 to 600 46 / 39 / 39; 100 of 2000 to 6000 318 / 192 / 119.
+static constexpr int s4_dump_threads(int64_t P, int64_t N) { return N >= 24 * P ? 512 : 256; }
+void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, int64_t P, int64_t N, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                   int nbits, const int32_t *pids, int n, const int64_t *out_offsets, float *out_vectors,
                                   uint8_t *out_indices, const float *inv_norm, const int64_t *refused, int64_t ticket)
 {
     if (n <= 0) return;
+    const unsigned threads = s4_dump_threads(P, N);
     if (nbits == 2)
-        hipLaunchKernelGGL(decompress_dump_kernel<2>, dim3(n), dim3(256), 0, st, centroids, doc_offsets, codes, residuals,
+        hipLaunchKernelGGL(decompress_dump_kernel<2>, dim3(n), dim3(threads), 0, st, centroids, doc_offsets, codes, residuals,
                            bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm, refused, ticket);
     else
-        hipLaunchKernelGGL(decompress_dump_kernel<1>, dim3(n), dim3(256), 0, st, centroids, doc_offsets, codes, residuals,
+        hipLaunchKernelGGL(decompress_dump_kernel<1>, dim3(n), dim3(threads), 0, st, centroids, doc_offsets, codes, residuals,
                            bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm, refused, ticket);
 }
 

@@ -1,0 +1,50 @@
+"""plaid_decompress_passages with either number of threads per passage (collections of fewer and of 24 or more tokens per passage): passages of
+lengths around the rows that the threads have in flight, lists around the ids of one of the offsets kernel's workgroups (64) and around a
+workgroup per compute unit (16 384), with and without bucket indices and unit lengths."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nbits", [1, 2])
+@pytest.mark.parametrize("lengths", [[0, 1, 7, 8, 9, 31, 32, 33, 65], [0, 1, 15, 16, 17, 63, 64, 65, 130], [24], [23]])
+def test_lists_and_lengths(nbits, lengths):
+    import paper_2205_09707_amd as pl
+    P, C = 1000, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P + nbits)
+    n_tok = torch.tensor(lengths, device="cuda")[torch.arange(P, device="cuda") % len(lengths)]
+    offsets = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(n_tok, 0)
+    N = int(offsets[-1])
+    assert (N >= 24 * P) == (lengths in ([0, 1, 15, 16, 17, 63, 64, 65, 130], [24]))
+    codes = torch.randint(0, C, (N,), generator=g, device="cuda", dtype=torch.int32)
+    io, ip = pl.plaid_build_ivf(codes, offsets, C)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
+    res = torch.randint(0, 256, (N, 16 * nbits), generator=g, device="cuda", dtype=torch.uint8)
+    w = torch.linspace(-0.06, 0.05, 1 << nbits, device="cuda")
+    idx = pl.plaid_index_from_view({"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": io, "ivf_pids": ip, "residuals": res,
+                                    "bucket_weights": w}, nbits, device=0, copy=False)
+    try:
+        shifts = range(8 - nbits, -1, -nbits)
+        all_ind = torch.stack([(res >> s) & ((1 << nbits) - 1) for s in shifts], dim=2).reshape(N, 128)
+        all_vec = cen[codes.long()] + w[all_ind.long()]
+        for n in (1, 64, 65, 129, 16_384, 16_385):
+            pids = (torch.arange(n, device="cuda") * 7 + 5) % P
+            length = offsets[pids + 1] - offsets[pids]
+            want = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+            want[1:] = torch.cumsum(length, 0)
+            total = int(want[-1])
+            tok = torch.repeat_interleave(offsets[pids] - want[:-1], length) + torch.arange(total, device="cuda")
+            for indices in (True, False):
+                offs, vec, ind = pl.plaid_decompress_passages(idx, pids.int(), total, indices=indices)
+                torch.cuda.synchronize()
+                assert torch.equal(offs, want) and torch.equal(vec, all_vec[tok]), n
+                assert not indices or torch.equal(ind, all_ind[tok]), n
+        pl.plaid_index_set_renormalize(idx, True)
+        vec = pl.plaid_decompress_passages(idx, pids.int(), total)[1]
+        # a factor of one rounding of a square root's reciprocal, and one rounding per component
+        assert float((vec - torch.nn.functional.normalize(all_vec.double(), dim=1)[tok]).abs().max()) < 3 * 2.0 ** -24
+    finally:
+        pl.plaid_index_free(idx)
