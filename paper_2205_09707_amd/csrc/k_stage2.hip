@@ -749,13 +749,27 @@ __device__ __forceinline__ int2 s2_coarse_load(const int32_t *coarse_q, int lane
                                                    __HIP_MEMORY_SCOPE_AGENT);
     return make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
 }
+// Probes found by several workgroups (Stage2Buffers::probes_apart) are a query's with duplicates.  Whether this thread is the first to
+// bring c, by a table of S2_SEEN places, -1 at the start, of which the probes of a query (up to IV_LISTS) take at most half.
+#define S2_SEEN (2 * IV_LISTS)
+__device__ __forceinline__ bool s2_first_probe(int32_t *seen, int32_t c)
+{
+    static_assert(S2_SEEN == 512, "nine bits of the hash");
+    for (uint32_t h = (uint32_t)c * 0x9E3779B1u >> 23;; h = (h + 1) & (S2_SEEN - 1)) {
+        const int32_t was = atomicCAS(&seen[h], -1, c);
+        if (was == -1) return true;
+        if (was == c) return false;
+    }
+}
 // The candidates among the passages of the bitmap words [w0, w0 + nw), nw <= 64, all in one column of the range table: the
-// union of the nu probed lists, into lcand[0 .. nw).  All 256 threads of a workgroup call this; a barrier ends it.
+// union of the nu probed lists, probe(e) the e-th's centroid or -1, into lcand[0 .. nw).  All 256 threads of a workgroup call this; thread t
+// asks for probes t, t + 256, ...; a barrier ends it.
 struct S2CandScratch {
     int64_t first[IV_LISTS];
     int32_t count[IV_LISTS];
 };
-__device__ __forceinline__ void s2_block_candidates(const int32_t *__restrict__ uq, int nu, const int64_t *__restrict__ ivf_offsets,
+template <typename F>
+__device__ __forceinline__ void s2_block_candidates(F &&probe, int nu, const int64_t *__restrict__ ivf_offsets,
                                                     const int32_t *__restrict__ ivf_pids, const uint32_t *__restrict__ table,
                                                     int64_t nr, int shift, const int32_t *__restrict__ dense_id,
                                                     const uint32_t *__restrict__ dense_bits, int64_t cand_words, int64_t P,
@@ -770,8 +784,8 @@ __device__ __forceinline__ void s2_block_candidates(const int32_t *__restrict__ 
         __syncthreads();  // the words are zero / the previous lists are done
         if (tid < 2) counts[tid] = 0;
         __syncthreads();
-        if (u0 + tid < nu) {
-            const int32_t c = uq[u0 + tid];
+        const int32_t c = u0 + tid < nu ? probe(u0 + tid) : -1;
+        if (c >= 0) {
             const int32_t d = dense_id[c];
             const uint32_t a = table[(int64_t)c * (nr + 1) + col], b = table[(int64_t)c * (nr + 1) + col + 1];
             if (d >= 0) {
@@ -838,7 +852,8 @@ __global__ __launch_bounds__(64 * IV_WAVES) void s2_candidates_kernel(
     if (skip_none && s2_uniform(meta[q].K) == 0) return;  // uniform
     const int64_t w0 = (int64_t)blockIdx.x * 64;
     const int nw = cand_words - w0 < 64 ? (int)(cand_words - w0) : 64;
-    s2_block_candidates(uniq + (int64_t)q * uniq_stride, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id, dense_bits,
+    const int32_t *uq = uniq + (int64_t)q * uniq_stride;
+    s2_block_candidates([=](int e) { return uq[e]; }, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id, dense_bits,
                         cand_words, P, w0, nw, lcand, cs, rows, counts);
     if (tid < nw) candbits[(int64_t)q * cand_words + w0 + tid] = lcand[tid];
 }
@@ -915,7 +930,7 @@ __device__ __forceinline__ void s2_gather_share(int q, int64_t j, int64_t nj, co
                                 uint32_t *__restrict__ candbits, int64_t cand_words, uint64_t *__restrict__ keys2, int64_t key_stride,
                                 int32_t *__restrict__ hist, uint32_t *__restrict__ emptybits,
                                 const int32_t *__restrict__ dense_id, const uint32_t *__restrict__ dense_bits, S2GatherScratch &gs,
-                                uint32_t *lcand, uint32_t *lempty, int32_t *rows, int32_t *counts, bool given)
+                                uint32_t *lcand, uint32_t *lempty, int32_t *rows, int32_t *counts, bool given, bool apart)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = s2_uniform(tid >> 6);
@@ -925,6 +940,19 @@ __device__ __forceinline__ void s2_gather_share(int q, int64_t j, int64_t nj, co
     const uint32_t *kb = keepbits + (int64_t)q * keep_words;
     uint32_t *keys_out = reinterpret_cast<uint32_t *>(keys2 + (int64_t)q * key_stride);
     for (int e = tid; e < SEL_BINS; e += 64 * IV_WAVES) gs.hist[e] = 0;
+    // This thread's probe, -1 where another thread has the same one: a list walked again costs what it did the first time.  us per search
+    // of 31 queries of 200 000 passages, some 200 survivors and 19 to 29 distinct ones of 128 probes (means of eight sets of queries, whose
+    // order alone makes 4 %): probes united beforehand 2229, every duplicate walked 2257, so 2220; nprobe 8 2239, 2286, 2232.
+    const int nu = given ? 0 : n_uniq[q];
+    int32_t mine = tid < nu ? uniq[(int64_t)q * uniq_stride + tid] : -1;
+    if (apart && !given) {  // uniform
+        static_assert(sizeof(gs.list) >= S2_SEEN * sizeof(int32_t), "the table takes the place of the lists");
+        static_assert(S2_SEEN == 2 * 64 * IV_WAVES, "two places a thread");
+        int32_t *seen = &gs.list[0][0][0];
+        seen[tid] = seen[tid + 64 * IV_WAVES] = -1;
+        __syncthreads();
+        if (mine >= 0 && !s2_first_probe(seen, mine)) mine = -1;
+    }
     for (int64_t w0 = wa; w0 < wb;) {
         const int64_t we = (w0 | 63) + 1 < wb ? (w0 | 63) + 1 : wb;  // within 2048 aligned passages: one column of the table
         const int nw = (int)(we - w0);
@@ -932,8 +960,8 @@ __device__ __forceinline__ void s2_gather_share(int q, int64_t j, int64_t nj, co
         if (given) {  // uniform: s2_candidates_kernel's
             if (tid < nw) lcand[tid] = cbq[tid];
         } else {
-            s2_block_candidates(uniq + (int64_t)q * uniq_stride, n_uniq[q], ivf_offsets, ivf_pids, table, nr, shift, dense_id,
-                                dense_bits, cand_words, P, w0, nw, lcand, gs.cand, rows, counts);
+            s2_block_candidates([=](int) { return mine; }, nu, ivf_offsets, ivf_pids, table, nr, shift, dense_id, dense_bits, cand_words,
+                                P, w0, nw, lcand, gs.cand, rows, counts);
             if (tid < nw) cbq[tid] = lcand[tid];
         }
         if (tid < 64) lempty[tid] = 0u;
@@ -1120,7 +1148,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                 s2_gather_share(q, own_xcd ? g >> 3 : g, own_xcd ? ng >> 3 : ng, uniq, n_uniq, uniq_stride, ivf_offsets, ivf_pids,
                                 table, nr, SHIFT, S, C, keepbits, keep_words, codes, doc_offsets, P, meta[q].bin_hi,
                                 meta[q].bin_scale, candbits, cand_words, keys2, key_stride, hist, emptybits, dense_id, dense_bits, gs,
-                                lcand_all[0], lcnt_all[0], plist, n_front, given);
+                                lcand_all[0], lcnt_all[0], plist, n_front, given, mode & 512);
                 i = !own_xcd ? i + 1 : (i + 8 < by_xcd ? i + 8 : by_xcd);
             }
             return;
@@ -1158,6 +1186,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         const int K = K_all;
         const int nu = n_uniq[q];
         __syncthreads();  // the previous query's readers are done
+        static_assert(S2_SEEN == 2 * 64 * IV_WAVES && sizeof(area_all) >= S2_SEEN * sizeof(int32_t), "two places a thread, where the planes will be");
         if (mode & 512) reinterpret_cast<int2 *>(area_all[0])[tid] = make_int2(-1, -1);
         if (tid < 64) {
             int32_t c = -1, d = -1;
@@ -1186,16 +1215,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         }
         if (!given) {
             static_assert(64 * IV_WAVES >= IV_LISTS, "one thread per probed list");
-            bool first = tid < nu;
-            if ((mode & 512) && first) {  // probes of several tokens may be the same: the first to enter its table of 512 places
-                int32_t *seen = reinterpret_cast<int32_t *>(area_all[0]);
-                for (uint32_t h = (uint32_t)probed_c * 0x9E3779B1u >> 23;; h = (h + 1) & 511u) {
-                    const int32_t was = atomicCAS(&seen[h], -1, probed_c);
-                    first = was == -1;
-                    if (first || was == probed_c) break;  // (at most 256 of the places are taken)
-                }
-            }
-            if (first) {
+            if (tid < nu && (!(mode & 512) || s2_first_probe(reinterpret_cast<int32_t *>(area_all[0]), probed_c))) {
                 const int32_t c = probed_c;
                 const int32_t d = dense_id[c];
                 int slot = -1;

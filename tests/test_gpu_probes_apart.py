@@ -47,3 +47,47 @@ def test_queries_in_one_launch_and_a_few_at_a_time(C, copies, nprobe):
                 assert torch.equal(b[0], y[0]) and torch.equal(b[1], y[1]) and torch.equal(a[0], x[0]) and torch.equal(a[1], x[1]), chunk
     finally:
         pl.plaid_index_free(idx)
+
+
+@pytest.mark.parametrize("P,nprobe,nq", [(900, 1, 34), (70_001, 4, 40), (70_001, 8, 33)])
+def test_queries_of_the_gather_form_in_one_launch_and_a_few_at_a_time(P, nprobe, nq):
+    """Queries with more surviving centroids than there are slots (S2_MAX_KEPT, 63) take their candidates from the probes in workgroups of
+    their own, which drop the duplicates too: all tokens of a query at four centroids, one of them in most passages (its list has a bitmap)."""
+    import paper_2205_09707_amd as pl
+    pl.load_library()
+    C = 3000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P + nprobe)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1)
+    offsets = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(torch.randint(0, 12, (P,), generator=g, device="cuda"), 0)
+    N = int(offsets[-1])
+    codes = (torch.rand(N, generator=g, device="cuda") ** 6 * C).int().clamp_(max=C - 1)
+    ivf_offsets, ivf_pids = pl.plaid_build_ivf(codes, offsets, C)
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
+              "residuals": torch.randint(0, 256, (N, 32), generator=g, device="cuda", dtype=torch.uint8),
+              "bucket_weights": torch.linspace(-0.05, 0.05, 4, device="cuda")}
+    src = torch.randint(0, C, (nq, 4), generator=g, device="cuda")
+    src[:, 0] = 0
+    Q = torch.nn.functional.normalize(cen[src.repeat(1, 8)] + 0.02 * torch.randn(nq, 32, 128, generator=g, device="cuda"), dim=2).contiguous()
+    idx = pl.plaid_index_from_view(arrays, 2, device=0, copy=False)
+    try:
+        got = {}
+        for chunk in (nq, 31, 9, 8, 1):
+            pl.plaid_set_max_chunk(idx, chunk)
+            got[chunk] = (pl.plaid_search_debug(idx, Q, nprobe, 0.15, 400, 50, want=["probed", "cand", "n_cand", "keep"]),
+                          pl.plaid_search(idx, Q, nprobe, 0.15, 400, 50))
+        torch.cuda.synchronize()
+        a, b = got[nq]
+        survivors = sum((a[2]["keep"] >> s & 1).sum(1) for s in range(32))
+        assert int(survivors.min()) > 63
+        assert all(len(torch.unique(a[2]["probed"][q])) < 32 * nprobe for q in range(nq))
+        for chunk in (31, 9, 8, 1):
+            x, y = got[chunk]
+            assert torch.equal(a[2]["probed"], x[2]["probed"]) and torch.equal(a[2]["n_cand"], x[2]["n_cand"]), chunk
+            for q in range(nq):
+                n = int(a[2]["n_cand"][q])
+                assert torch.equal(a[2]["cand"][q, :n], x[2]["cand"][q, :n]), (chunk, q)
+            assert torch.equal(b[0], y[0]) and torch.equal(b[1], y[1]) and torch.equal(a[0], x[0]) and torch.equal(a[1], x[1]), chunk
+    finally:
+        pl.plaid_index_free(idx)
