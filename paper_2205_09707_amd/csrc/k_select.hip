@@ -1012,7 +1012,7 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
     const S2Meta mt = meta[seg];
     if (mt.K == 0) return;  // no surviving centroid: no valid key, the state stays zero and the fill takes over
     const bool is_list = lists && mt.K <= S2_MAX_KEPT;
-    // a list: its keys; in parts (launches of few queries): where they end, one after the other, and the way from there to their places
+    // a list: its keys; in parts (a single query): where they end, one after the other, and the way from there to their places
     int64_t n_items = P;
     int32_t part_end[DIGITS ? S2_COPIES : 1], part_at[DIGITS ? S2_COPIES : 1];
     bool parts = false;

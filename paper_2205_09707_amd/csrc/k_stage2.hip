@@ -1187,7 +1187,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         const int nu = n_uniq[q];
         __syncthreads();  // the previous query's readers are done
         static_assert(S2_SEEN == 2 * 64 * IV_WAVES && sizeof(area_all) >= S2_SEEN * sizeof(int32_t), "two places a thread, where the planes will be");
-        if (mode & 512) reinterpret_cast<int2 *>(area_all[0])[tid] = make_int2(-1, -1);
+        const bool apart = !PLAIN && (mode & 512);  // (launches of fewer than 32 queries)
+        if (apart) reinterpret_cast<int2 *>(area_all[0])[tid] = make_int2(-1, -1);
         if (tid < 64) {
             int32_t c = -1, d = -1;
             if (tid < K) {
@@ -1215,7 +1216,7 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         }
         if (!given) {
             static_assert(64 * IV_WAVES >= IV_LISTS, "one thread per probed list");
-            if (tid < nu && (!(mode & 512) || s2_first_probe(reinterpret_cast<int32_t *>(area_all[0]), probed_c))) {
+            if (tid < nu && (!apart || s2_first_probe(reinterpret_cast<int32_t *>(area_all[0]), probed_c))) {
                 const int32_t c = probed_c;
                 const int32_t d = dense_id[c];
                 int slot = -1;
@@ -1237,10 +1238,10 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
         const int dense_row = lane < n_dense ? drow[lane] : 0;
         const int list_c = lane < n_ss ? kid[n_dense + lane] : -1;
         const bool all_probed = (uint32_t)__popc(pm0) + (uint32_t)__popc(pm1) == (uint32_t)K;
-        // this workgroup's part of the key list (s2_parts), one per XCD
+        // this workgroup's part of the key list (s2_parts: of a single query, which an instance that takes every query serves), one per XCD
         uint64_t *klist = keys2 + (int64_t)q * key_stride;
         int32_t *count_q = list_counts + (int64_t)q * S2_COUNTS_QUERY;
-        if (!PLAIN && (mode & 1024)) {  // uniform
+        if (ALL && (mode & 1024)) {  // uniform
             const int64_t passages = (int64_t)((IV_WAVES >> lend) * steps) << len_log;
             const int64_t at = s2_list_part(rb & (S2_COPIES - 1), passages, P);
             klist += at;

@@ -135,6 +135,16 @@ def test_gather_form_has_the_workgroups_that_run_at_once(tmp_path):
         assert blocks == 256 * min(512 // vgprs, (160 << 10) // m["group_segment_fixed_size"]), (key, blocks, m)
 
 
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+def test_range_kernels_scalar_spills(tmp_path):
+    """What only a single query (a key list in parts) or launches of fewer than 32 queries (duplicates among the probes) need is no state of the
+    instances that never serve them: scalar registers spilled to vector ones, before they left those instances 106, 80, 142, 141."""
+    meta = _metadata(_assembly("k_stage2.hip", str(tmp_path / "k_stage2.s")))
+    for key, most in (("EjLb0ELb0ELb0E", 95), ("EjLb1ELb0ELb0E", 79), ("EyLb0ELb0ELb0E", 130), ("EyLb0ELb0ELb1E", 135), ("EyLb0ELb1E", 150)):
+        spills = {n: m["sgpr_spill_count"] for n, m in meta.items() if "s2_invert_kernelILi" in n and key in n}
+        assert spills and max(spills.values()) <= most, spills
+
+
 # LDS arrays that are accessed in 16-byte pieces: (source file, where the array starts within the record it lies in)
 LDS_PIECES = [
     ("k_scq.hip", ["offsetof(SurvivorRows, Qs)", "offsetof(SurvivorRows, row)", "offsetof(TableScratch<true>, x)",
