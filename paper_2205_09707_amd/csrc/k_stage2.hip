@@ -1705,10 +1705,13 @@ static constexpr int64_t s2_first_batch(int64_t P, int64_t nq, int64_t m, int le
 
 // Whether a query's key list is in parts.  The waves of a single query reserve their first places at about the same time, and some ten
 // nanoseconds after one another where there is one counter: up to 20 us for the last of two thousand.  Parts cost the selection a
-// microsecond or two, which reads their numbers first.  us per search with one list / parts, one query: of 400 000 passages (391 waves, nprobe 2)
-// 78.7 / 78.9, of 800 000 84.4 / 83.0, of 2 M 93 / 87 (nprobe 1), 100 / 97, 133 / 127 (nprobe 4), of 4 M 117 / 108, of 8.8 M 229 / 220; four
-// of 2 M 113 / 110, 133 / 133, 167 / 168, of 4 M 149 / 149; sixteen of 400 000 152 / 155, of 2 M 253 / 260, of 4 M 337 / 352.
-static constexpr bool s2_parts(int nq, int64_t waves) { return nq == 1 && waves > 391; }
+// microsecond or two, which reads their numbers first.  us per search with one list / parts, one query, by its number of waves, nprobe 1 and ndocs 256,
+// 2 and 1024, 4 and 4096: 391 66.6 / 66.6, 71.0 / 72.5, 99.5 / 100.3; 398 71.1 / 71.4, 77.7 / 78.4, 109.7 / 110.1; 416 73.8 / 74.1, 79.3 / 80.1, 111.1 / 111.6;
+// 440 72.2 / 71.6, 78.8 / 79.6, 111.6 / 111.6; 464 75.1 / 75.0, 80.1 / 81.3, 112.5 / 113.1; 489 72.0 / 70.8, 79.1 / 78.9, 113.6 / 113.5; 586 73.9 / 72.2, 79.8 / 79.3,
+// 113.9 / 113.2; 733 77.6 / 75.1, 84.5 / 83.6, 116.6 / 114.8; 977 83.2 / 79.8, 91.1 / 89.4, 121.6 / 118.8; shorter ranges (ndocs 60 000 to 300 000): 450
+// 247.5 / 247.2, 782 308 / 302, 977 623 / 615.  Four queries of 2 M passages 113 / 110, 133 / 133, 167 / 168, of 4 M 149 / 149; sixteen of
+// 400 000 152 / 155, of 2 M 253 / 260, of 4 M 337 / 352.
+static constexpr bool s2_parts(int nq, int64_t waves) { return nq == 1 && waves > 480; }
 
 // The numbers of survivors K (bit K - 32) whose queries the TALL instance takes in launches of many workgroups.  share: how
 // often a surviving centroid needs a plane (plaid_launch_ivf_plane_share): K of them need K share, give or take the root of K share

@@ -29,8 +29,8 @@ constexpr bool parts_fit(int64_t passages, int64_t P) {  // a workgroup's passag
 
 @pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
 def test_rules_of_parts_and_cuts(tmp_path):
-    claims = ["s2_parts(1, 392)", "!s2_parts(1, 391)", "!s2_parts(2, 4297)"]
-    claims += [f"parts_fit({n}, {P})" for n in (1024, 4096, 8192, 16384) for P in (1, 1023, 400_385, 405_003, 409_600, 800_769, 8 * 16384, 8 * 16384 + 1,
+    claims = ["s2_parts(1, 481)", "!s2_parts(1, 480)", "!s2_parts(2, 4297)"]
+    claims += [f"parts_fit({n}, {P})" for n in (128, 256, 512, 1024, 2048, 4096, 8192, 16384) for P in (1, 1023, 400_385, 405_003, 409_600, 800_769, 8 * 16384, 8 * 16384 + 1,
                                                                                    2_000_001, 8_800_000, (1 << 31) - 1)
                if P < 1_000_000 or n > 4096]
     for src, body in (("k_stage2.hip", PARTS + "".join(f'static_assert({c}, "{c}");\n' for c in claims)),
@@ -44,8 +44,9 @@ def test_rules_of_parts_and_cuts(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("P", [400_385, 409_600, 800_769, 1_000_003])
+@pytest.mark.parametrize("P", [300_007, 409_600, 983_040, 983_041, 1_000_003])
 def test_a_list_in_parts(P):
+    """Around the smallest collection whose list is in parts, 481 ranges of 2048 passages; 300 007, with the largest ndocs below, in ranges of 512."""
     import paper_2205_09707_amd as pl
     C = 3000
     g = torch.Generator(device="cuda")
@@ -78,5 +79,52 @@ def test_a_list_in_parts(P):
                 assert torch.equal(a, b), (name, nprobe)
             for a, b in ((ids, scores), one[:2]):
                 assert torch.equal(a, many[0]) and torch.equal(b, many[1]), nprobe
+    finally:
+        pl.plaid_index_free(idx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,ndocs", [(32, 500), (58, 500), (32, 60_000), (58, 60_000)])
+def test_a_list_in_parts_by_waves_with_more_areas(K, ndocs):
+    """More surviving centroids without a bitmap than one wave's planes (26) or two waves' (52): a workgroup's passages are a half or a quarter
+    then, and its part of the list is as much smaller."""
+    import paper_2205_09707_amd as pl
+    P, C = 1_000_003, 60_000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1)
+    offsets = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(torch.randint(0, 5, (P,), generator=g, device="cuda"), 0)
+    N = int(offsets[-1])
+    hot = 200  # centroids, 3000 passages each: in most ranges, and no list long enough for a bitmap
+    codes = torch.randint(0, C, (N,), generator=g, device="cuda").int()
+    some = torch.rand(N, generator=g, device="cuda") < 0.3
+    codes[some] = torch.randint(0, hot, (int(some.sum()),), generator=g, device="cuda").int()
+    ivf_offsets, ivf_pids = pl.plaid_build_ivf(codes, offsets, C)
+    assert int((ivf_offsets[1:] - ivf_offsets[:-1]).max()) < P // 16
+    arrays = {"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": ivf_offsets, "ivf_pids": ivf_pids,
+              "residuals": torch.randint(0, 256, (N, 16), generator=g, device="cuda", dtype=torch.uint8),
+              "bucket_weights": torch.tensor([-0.05, 0.06], device="cuda")}
+    at = torch.stack([torch.randperm(hot, generator=g, device="cuda")[:K] for _ in range(4)])
+    tok = torch.arange(32, device="cuda")  # a token at one centroid, or between two
+    Q = cen[at[:, tok % K]] + (cen[at[:, 32 + tok % (K - 32)]] if K > 32 else 0)
+    Q = torch.nn.functional.normalize(Q, dim=2).contiguous()
+    idx = pl.plaid_index_from_view(arrays, 1, device=0, copy=False)
+    try:
+        pl.plaid_set_max_chunk(idx, 4)
+        many = pl.plaid_search_debug(idx, Q, 2, 0.55, ndocs, 50, want=["n_cand", "n2", "n3", "sel2_ids", "keep"])
+        assert sum((many[2]["keep"] >> s & 1).sum(1) for s in range(32)).tolist() == [K] * 4
+        pl.plaid_set_max_chunk(idx, 1)
+        one = pl.plaid_search_debug(idx, Q, 2, 0.55, ndocs, 50, want=["n_cand", "n2", "n3", "sel2_ids"])
+        ids, scores = pl.plaid_search(idx, Q, 2, 0.55, ndocs, 50)
+        torch.cuda.synchronize()
+        assert int(many[2]["n_cand"].min()) > 4 * 480  # keys from many waves
+        for name in ("n_cand", "n2", "n3"):
+            assert torch.equal(many[2][name], one[2][name]), name
+        for q in range(4):
+            n = int(many[2]["n2"][q])  # (the kept ones are a set)
+            assert torch.equal(torch.sort(many[2]["sel2_ids"][q, :n]).values, torch.sort(one[2]["sel2_ids"][q, :n]).values), q
+        for a, b in ((ids, scores), one[:2]):
+            assert torch.equal(a, many[0]) and torch.equal(b, many[1])
     finally:
         pl.plaid_index_free(idx)
