@@ -1342,30 +1342,34 @@ void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, in
                        capacity, work, refused, ticket, report);
 }
 
-// Same table, same lookup and same addition as the fused kernel; a workgroup per passage, of 256 or 512 threads, of which 32 have a
-// token, 4 dimensions each.  Bound by its writes and by the centroid rows, 512 bytes a token each: what is written goes past the caches
-// (nontemporal stores), which then hold more of the rows.  5000 passages of 65 tokens 51.0 -> 41.5 us, 50 000 662 -> 544 us.
+// Same table, same lookup and same addition as the fused kernel; a workgroup per passage, a token to 32 threads, 4 dimensions each.
+// Bound by its writes and by the centroid rows, 512 bytes a token each: what is written goes past the caches (nontemporal stores), which
+// then hold more of the rows.  5000 passages of 65 tokens 51.0 -> 41.5 us, 50 000 662 -> 544 us.
+// Threads of a workgroup: twice as many fetch twice the rows of a long passage at once, but leave fewer passages in flight on a
+// compute unit, and what a list's passages are like does not follow from the collection's mean.  us per call with 256 / 512, lists of
+// 50 000 passages: of 1 to 8 tokens 96 / 125, of 8 to 24 133 / 196, of 24 to 40 290 / 329, of 30 to 100 610 / 596 (of 262 144 centroids 637 / 653); of
+// 5000: 23 / 23, 23 / 27, 31 / 31, 51 / 54; 1000 of 100 to 300 36 / 38; 100 of 1000 to 3000, which are too few passages to fill the chip, 148 / 94.
+#define DUMP_THREADS 256
 typedef float s4_float4 __attribute__((ext_vector_type(4)));
 template <int NBITS>
-__global__ __launch_bounds__(512) void decompress_dump_kernel(const float *__restrict__ centroids,
-                                                              const int64_t *__restrict__ doc_offsets,
-                                                              const int32_t *__restrict__ codes,
-                                                              const uint8_t *__restrict__ residuals,
-                                                              const float *__restrict__ weights,
-                                                              const int32_t *__restrict__ pids,
-                                                              const int64_t *__restrict__ out_offsets,
-                                                              float *__restrict__ out_vectors,
-                                                              uint8_t *__restrict__ out_indices,
-                                                              const float *__restrict__ inv_norm,
-                                                              const int64_t *refused, int64_t ticket)
+__global__ __launch_bounds__(DUMP_THREADS) void decompress_dump_kernel(const float *__restrict__ centroids,
+                                                                       const int64_t *__restrict__ doc_offsets,
+                                                                       const int32_t *__restrict__ codes,
+                                                                       const uint8_t *__restrict__ residuals,
+                                                                       const float *__restrict__ weights,
+                                                                       const int32_t *__restrict__ pids,
+                                                                       const int64_t *__restrict__ out_offsets,
+                                                                       float *__restrict__ out_vectors,
+                                                                       uint8_t *__restrict__ out_indices,
+                                                                       const float *__restrict__ inv_norm,
+                                                                       const int64_t *refused, int64_t ticket)
 {
-    constexpr int RB = 16 * NBITS;
+    constexpr int RB = 16 * NBITS, ROWS = DUMP_THREADS / 32;
     __shared__ float4 wlut[256 * (NBITS == 2 ? 1 : 2)];
     __shared__ uint32_t ilut[256 * (NBITS == 2 ? 1 : 2)];
     // (uniform) refused by passage_offsets_kernel; another call that is refused meanwhile leaves another ticket
     if (*refused == ticket) return;
-    const int threads = blockDim.x, rows = threads >> 5;  // uniform
-    build_tables<NBITS>(wlut, ilut, weights, threadIdx.x, threads);
+    build_tables<NBITS>(wlut, ilut, weights, threadIdx.x, DUMP_THREADS);
     __syncthreads();
     const int a = blockIdx.x;
     const int32_t pid = pids[a];
@@ -1374,14 +1378,14 @@ __global__ __launch_bounds__(512) void decompress_dump_kernel(const float *__res
     const int64_t o0 = out_offsets[a];
     const int quad = threadIdx.x & 31;
     // four rows per thread in flight: code and residual, then the centroid's piece, then the stores
-    for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 4 * rows) {
+    for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 4 * ROWS) {
         int slot[4];
         int32_t code[4];
         float4 c[4];
         float f[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int row = row0 + rows * u < len ? row0 + rows * u : row0;  // (a row past the end repeats the first)
+            const int row = row0 + ROWS * u < len ? row0 + ROWS * u : row0;  // (a row past the end repeats the first)
             code[u] = codes[t0 + row];
             slot[u] = table_slot<NBITS>(residuals + (t0 + row) * RB, quad);
             f[u] = inv_norm ? inv_norm[t0 + row] : 1.0f;
@@ -1390,7 +1394,7 @@ __global__ __launch_bounds__(512) void decompress_dump_kernel(const float *__res
         for (int u = 0; u < 4; ++u) c[u] = *reinterpret_cast<const float4 *>(centroids + (int64_t)code[u] * DIM + 4 * quad);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int row = row0 + rows * u;
+            const int row = row0 + ROWS * u;
             if (row >= len) break;
             const float4 w = wlut[slot[u]];
             if (out_vectors) {
@@ -1403,23 +1407,17 @@ __global__ __launch_bounds__(512) void decompress_dump_kernel(const float *__res
         }
     }
 }
-// Threads of a passage, by the collection's tokens per passage: more have more of a passage's rows in flight at once, fewer leave fewer
-// idle.  us of the kernel with 256 / 512 / 1024, 50 000 passages of 1 to 8 tokens 62 / 87 / 158, of 8 to 24 133 / 157 / 242, of 12 to 36
-// 200 / 195 / 298, of 24 to 40 267 / 260 / 337, of 30 to 100 544 / 536 / 518; 5000 of 1 to 8 7.4 / 8.8 / 14.2, of 8 to 24 16.2 / 18.7 / 27.2, of
-// 12 to 36 23.6 / 23.4 / 33.3, of 30 to 100 41.5 / 39.3 / 41.8; 500 of 200 to 600 46 / 39 / 39; 100 of 2000 to 6000 318 / 192 / 119.
-static constexpr int s4_dump_threads(int64_t P, int64_t N) { return N >= 24 * P ? 512 : 256; }
-void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, int64_t P, int64_t N, const int64_t *doc_offsets,
+void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                   int nbits, const int32_t *pids, int n, const int64_t *out_offsets, float *out_vectors,
                                   uint8_t *out_indices, const float *inv_norm, const int64_t *refused, int64_t ticket)
 {
     if (n <= 0) return;
-    const unsigned threads = s4_dump_threads(P, N);
     if (nbits == 2)
-        hipLaunchKernelGGL(decompress_dump_kernel<2>, dim3(n), dim3(threads), 0, st, centroids, doc_offsets, codes, residuals,
+        hipLaunchKernelGGL(decompress_dump_kernel<2>, dim3(n), dim3(DUMP_THREADS), 0, st, centroids, doc_offsets, codes, residuals,
                            bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm, refused, ticket);
     else
-        hipLaunchKernelGGL(decompress_dump_kernel<1>, dim3(n), dim3(threads), 0, st, centroids, doc_offsets, codes, residuals,
+        hipLaunchKernelGGL(decompress_dump_kernel<1>, dim3(n), dim3(DUMP_THREADS), 0, st, centroids, doc_offsets, codes, residuals,
                            bucket_weights, pids, out_offsets, out_vectors, out_indices, inv_norm, refused, ticket);
 }
 

@@ -1408,7 +1408,7 @@ extern "C" int plaid_decompress_passages(plaid_index *ix, const int32_t *pids, i
                                  r.tickets, r.words);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && vectors) {
-        plaid_launch_decompress_dump(st, ix->centroids, ix->P, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, pids, n, offs,
+        plaid_launch_decompress_dump(st, ix->centroids, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, pids, n, offs,
                                      out_vectors, out_indices, ix->renormalize ? ix->inv_norm : nullptr, r.refused(), r.tickets);
         e = hipGetLastError();
     }

@@ -403,7 +403,7 @@ bool plaid_launch_cut_maxsim(hipStream_t st, const float *Q, const float *S, int
                              int32_t *out_counts, const float *inv_norm);
 
 // Section 4.5 alone: reconstructed vectors / bucket indices of listed passages.
-void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, int64_t P, int64_t N, const int64_t *doc_offsets,
+void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,
                                   int nbits, const int32_t *pids, int n, const int64_t *out_offsets, float *out_vectors,
                                   uint8_t *out_indices, const float *inv_norm, const int64_t *refused, int64_t ticket);

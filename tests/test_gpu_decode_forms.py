@@ -1,6 +1,6 @@
-"""plaid_decompress_passages with either number of threads per passage (collections of fewer and of 24 or more tokens per passage): passages of
-lengths around the rows that the threads have in flight, lists around the ids of one of the offsets kernel's workgroups (64) and around a
-workgroup per compute unit (16 384), with and without bucket indices and unit lengths."""
+"""plaid_decompress_passages on collections of short and of longer passages: passages of lengths around the rows that a workgroup's threads have in
+flight, lists around the ids of one of the offsets kernel's workgroups (64) and around a workgroup per compute unit (16 384), with and without
+bucket indices and unit lengths."""
 import pytest
 import torch
 
@@ -48,3 +48,44 @@ def test_lists_and_lengths(nbits, lengths):
         assert float((vec - torch.nn.functional.normalize(all_vec.double(), dim=1)[tok]).abs().max()) < 3 * 2.0 ** -24
     finally:
         pl.plaid_index_free(idx)
+
+
+def test_short_passages_of_a_long_collection_take_no_longer():
+    """What a list costs depends on its passages, not on the others of the collection: the same 50 000 of 8 to 24 tokens, alone and beside as many of
+    60 to 100.  (With workgroups by the collection's mean the second took 1.5 times as long.)"""
+    import paper_2205_09707_amd as pl
+    C, half = 4096, 100_000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    short = torch.randint(8, 25, (half,), generator=g, device="cuda")
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
+    pids = torch.randint(0, half, (50_000,), generator=g, device="cuda").int()
+    total = int(short[pids.long()].sum())
+    indices = []
+    for lengths in (short, torch.cat([short, torch.randint(60, 101, (half,), generator=g, device="cuda")])):
+        offsets = torch.zeros(lengths.numel() + 1, dtype=torch.int64, device="cuda")
+        offsets[1:] = torch.cumsum(lengths, 0)
+        N = int(offsets[-1])
+        codes = torch.randint(0, C, (N,), generator=g, device="cuda", dtype=torch.int32)
+        io, ip = pl.plaid_build_ivf(codes, offsets, C)
+        indices.append(pl.plaid_index_from_view({"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": io, "ivf_pids": ip,
+                                                 "residuals": torch.randint(0, 256, (N, 32), generator=g, device="cuda", dtype=torch.uint8),
+                                                 "bucket_weights": torch.linspace(-0.06, 0.05, 4, device="cuda")}, 2, device=0, copy=False))
+    try:
+        times = [[], []]
+        for _ in range(15):
+            for idx, t in zip(indices, times):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                pl.plaid_decompress_passages(idx, pids, total)
+                a.record()
+                for _ in range(8):
+                    pl.plaid_decompress_passages(idx, pids, total)
+                b.record()
+                torch.cuda.synchronize()
+                t.append(a.elapsed_time(b))
+        alone, beside = (sorted(t)[7] for t in times)
+        print(f"50 000 short passages: {1000 * alone / 8:.0f} us a call, of a longer collection {1000 * beside / 8:.0f}")
+        assert beside < 1.2 * alone
+    finally:
+        for idx in indices:
+            pl.plaid_index_free(idx)
