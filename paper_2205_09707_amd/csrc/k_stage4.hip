@@ -1343,14 +1343,29 @@ void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, in
 }
 
 // Same table, same lookup and same addition as the fused kernel; a workgroup per passage, a token to 32 threads, 4 dimensions each.
-// Bound by its writes and by the centroid rows, 512 bytes a token each: what is written goes past the caches (nontemporal stores), which
-// then hold more of the rows.  5000 passages of 65 tokens 51.0 -> 41.5 us, 50 000 662 -> 544 us.
+// Bound by its writes and by the centroid rows, 512 bytes a token each.
 // Threads of a workgroup: twice as many fetch twice the rows of a long passage at once, but leave fewer passages in flight on a
 // compute unit, and what a list's passages are like does not follow from the collection's mean.  us per call with 256 / 512, lists of
 // 50 000 passages: of 1 to 8 tokens 96 / 125, of 8 to 24 133 / 196, of 24 to 40 290 / 329, of 30 to 100 610 / 596 (of 262 144 centroids 637 / 653); of
 // 5000: 23 / 23, 23 / 27, 31 / 31, 51 / 54; 1000 of 100 to 300 36 / 38; 100 of 1000 to 3000, which are too few passages to fill the chip, 148 / 94.
 #define DUMP_THREADS 256
+// Whether what is written goes past the caches (nontemporal stores).  Then they hold more of the rows and codes, but whoever reads the
+// vectors next finds none of them there; where they do not fit the 256 MB of the last cache, he would not in any case.  Passages of 65
+// tokens, vectors and indices, us of a call alone / of the call and a sum over the vectors / of the call and their product with 32 columns, through the
+// caches and past them, lists that are not seen again soon: 1000 (42 MB) 23.1, 38.5, 45.2 and 21.3, 41.2, 48.1; 2000 34.7, 54.7, 61.1 and 33.4, 60.6, 66.0;
+// 5000 (208 MB) 70.4, 106, 123 and 70.3, 123, 130; 6000 (250 MB) 82.8, 133, 151 and 82.1, 144, 153; 8000 (333 MB) 118, 197, 210 and 106, 185, 199;
+// 50 000 656, 1084, 1140 and 610, 1054, 1113.  Eight lists of 5000 in turn, whose codes and rows the caches can hold: 71.7, 111, 129 and 50.6, 124, 134.
+static constexpr __host__ __device__ bool s4_past_caches(int64_t tokens, bool vectors, bool indices)
+{
+    return tokens * ((vectors ? DIM * 4 : 0) + (indices ? DIM : 0)) > (256ll << 20);
+}
 typedef float s4_float4 __attribute__((ext_vector_type(4)));
+template <bool PAST, typename T, typename U>
+__device__ __forceinline__ void s4_store(T value, U *to)
+{
+    if (PAST) __builtin_nontemporal_store(value, reinterpret_cast<T *>(to));
+    else *reinterpret_cast<T *>(to) = value;
+}
 template <int NBITS>
 __global__ __launch_bounds__(DUMP_THREADS) void decompress_dump_kernel(const float *__restrict__ centroids,
                                                                        const int64_t *__restrict__ doc_offsets,
@@ -1377,35 +1392,40 @@ __global__ __launch_bounds__(DUMP_THREADS) void decompress_dump_kernel(const flo
     const int len = (int)(doc_offsets[pid + 1] - t0);
     const int64_t o0 = out_offsets[a];
     const int quad = threadIdx.x & 31;
-    // four rows per thread in flight: code and residual, then the centroid's piece, then the stores
-    for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 4 * ROWS) {
-        int slot[4];
-        int32_t code[4];
-        float4 c[4];
-        float f[4];
+    // Four rows per thread in flight: code and residual, then the centroid's piece, then the stores.  (A loop for either kind of store: of
+    // two that differ in nothing else, on two sides of a branch, the compiler makes one of the plain kind.)
+    auto decode = [&](auto past) {
+        for (int row0 = threadIdx.x >> 5; row0 < len; row0 += 4 * ROWS) {
+            int slot[4];
+            int32_t code[4];
+            float4 c[4];
+            float f[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int row = row0 + ROWS * u < len ? row0 + ROWS * u : row0;  // (a row past the end repeats the first)
-            code[u] = codes[t0 + row];
-            slot[u] = table_slot<NBITS>(residuals + (t0 + row) * RB, quad);
-            f[u] = inv_norm ? inv_norm[t0 + row] : 1.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = *reinterpret_cast<const float4 *>(centroids + (int64_t)code[u] * DIM + 4 * quad);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int row = row0 + ROWS * u;
-            if (row >= len) break;
-            const float4 w = wlut[slot[u]];
-            if (out_vectors) {
-                float4 d = make_float4(c[u].x + w.x, c[u].y + w.y, c[u].z + w.z, c[u].w + w.w);
-                // scaled to unit length: one fp32 factor per token, one rounding per component
-                if (inv_norm) d = make_float4(d.x * f[u], d.y * f[u], d.z * f[u], d.w * f[u]);
-                __builtin_nontemporal_store(s4_float4{d.x, d.y, d.z, d.w}, reinterpret_cast<s4_float4 *>(out_vectors + (o0 + row) * DIM + 4 * quad));
+            for (int u = 0; u < 4; ++u) {
+                const int row = row0 + ROWS * u < len ? row0 + ROWS * u : row0;  // (a row past the end repeats the first)
+                code[u] = codes[t0 + row];
+                slot[u] = table_slot<NBITS>(residuals + (t0 + row) * RB, quad);
+                f[u] = inv_norm ? inv_norm[t0 + row] : 1.0f;
             }
-            if (out_indices) __builtin_nontemporal_store(ilut[slot[u]], reinterpret_cast<uint32_t *>(out_indices + (o0 + row) * DIM + 4 * quad));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = *reinterpret_cast<const float4 *>(centroids + (int64_t)code[u] * DIM + 4 * quad);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int row = row0 + ROWS * u;
+                if (row >= len) break;
+                const float4 w = wlut[slot[u]];
+                if (out_vectors) {
+                    float4 d = make_float4(c[u].x + w.x, c[u].y + w.y, c[u].z + w.z, c[u].w + w.w);
+                    // scaled to unit length: one fp32 factor per token, one rounding per component
+                    if (inv_norm) d = make_float4(d.x * f[u], d.y * f[u], d.z * f[u], d.w * f[u]);
+                    s4_store<decltype(past)::value>(s4_float4{d.x, d.y, d.z, d.w}, out_vectors + (o0 + row) * DIM + 4 * quad);
+                }
+                if (out_indices) s4_store<decltype(past)::value>(ilut[slot[u]], out_indices + (o0 + row) * DIM + 4 * quad);
+            }
         }
-    }
+    };
+    if (s4_past_caches(out_offsets[gridDim.x], out_vectors, out_indices)) decode(std::true_type{});  // uniform
+    else decode(std::false_type{});
 }
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
                                   const int32_t *codes, const uint8_t *residuals, const float *bucket_weights,

@@ -136,6 +136,17 @@ def test_gather_form_has_the_workgroups_that_run_at_once(tmp_path):
 
 
 @pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
+def test_decompression_has_both_kinds_of_stores(tmp_path):
+    """Vectors and indices are stored past the caches or through them, by a condition that is no part of the store: four rows a thread of each."""
+    text = _assembly("k_stage4.hip", str(tmp_path / "k_stage4.s"))
+    for nbits in (1, 2):
+        body = re.search(r"^_Z22decompress_dump_kernelILi%dE.*?\.end_amdhsa_kernel" % nbits, text, re.M | re.S).group(0)
+        for width in ("dwordx4", "dword"):
+            stores = re.findall(r"global_store_%s (.*)" % width, body)
+            assert len(stores) == 8 and sum(l.endswith(" nt") for l in stores) == 4, stores
+
+
+@pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
 def test_range_kernels_scalar_spills(tmp_path):
     """What only a single query (a key list in parts) or launches of fewer than 32 queries (duplicates among the probes) need is no state of the
     instances that never serve them: scalar registers spilled to vector ones, before they left those instances 106, 80, 142, 141."""

@@ -89,3 +89,42 @@ def test_short_passages_of_a_long_collection_take_no_longer():
     finally:
         for idx in indices:
             pl.plaid_index_free(idx)
+
+
+@pytest.mark.parametrize("nbits", [1, 2])
+@pytest.mark.parametrize("vectors,indices,tokens", [(True, True, 419_430), (True, True, 419_431), (True, False, 524_288), (True, False, 524_289),
+                                                    (False, True, 2_097_152), (False, True, 2_097_153)])
+def test_outputs_through_the_caches_and_past_them(nbits, vectors, indices, tokens):
+    """256 MB and a token more: what the list's passages hold decides, not the caller's capacity, which is twice that here."""
+    import paper_2205_09707_amd as pl
+    C = 512
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tokens)
+    lengths = torch.cat([torch.full((2000,), 64, device="cuda"), torch.ones(64, dtype=torch.int64, device="cuda")])
+    offsets = torch.zeros(lengths.numel() + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(lengths, 0)
+    N = int(offsets[-1])
+    codes = torch.randint(0, C, (N,), generator=g, device="cuda", dtype=torch.int32)
+    io, ip = pl.plaid_build_ivf(codes, offsets, C)
+    cen = torch.nn.functional.normalize(torch.randn(C, 128, generator=g, device="cuda"), dim=1).contiguous()
+    res = torch.randint(0, 256, (N, 16 * nbits), generator=g, device="cuda", dtype=torch.uint8)
+    w = torch.linspace(-0.06, 0.05, 1 << nbits, device="cuda")
+    idx = pl.plaid_index_from_view({"centroids": cen, "doc_offsets": offsets, "codes": codes, "ivf_offsets": io, "ivf_pids": ip, "residuals": res,
+                                    "bucket_weights": w}, nbits, device=0, copy=False)
+    try:
+        pids = torch.cat([torch.arange(tokens // 64, device="cuda") * 7 % 2000, 2000 + torch.arange(tokens % 64, device="cuda")])
+        length = offsets[pids + 1] - offsets[pids]
+        want = torch.zeros(pids.numel() + 1, dtype=torch.int64, device="cuda")
+        want[1:] = torch.cumsum(length, 0)
+        assert int(want[-1]) == tokens
+        tok = torch.repeat_interleave(offsets[pids] - want[:-1], length) + torch.arange(tokens, device="cuda")
+        offs, vec, ind = pl.plaid_decompress_passages(idx, pids.int(), 2 * tokens, vectors=vectors, indices=indices)
+        torch.cuda.synchronize()
+        assert torch.equal(offs, want)
+        all_ind = torch.stack([(res >> s) & ((1 << nbits) - 1) for s in range(8 - nbits, -1, -nbits)], dim=2).reshape(N, 128)
+        if vectors:
+            assert torch.equal(vec[:tokens], (cen[codes.long()] + w[all_ind.long()])[tok])
+        if indices:
+            assert torch.equal(ind[:tokens], all_ind[tok])
+    finally:
+        pl.plaid_index_free(idx)

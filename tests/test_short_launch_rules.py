@@ -1,5 +1,5 @@
 """Where a single query's key list is in parts, and that the parts' places neither overlap nor leave the list; which lists are cut and scored
-by one launch.  On the GPU, a query whose list is in parts against the same one in a launch of four, where none is."""
+by one launch; which vectors are written past the caches.  On the GPU, a query whose list is in parts against the same one in a launch of four, where none is."""
 import os
 import shutil
 import subprocess
@@ -35,7 +35,11 @@ def test_rules_of_parts_and_cuts(tmp_path):
                if P < 1_000_000 or n > 4096]
     for src, body in (("k_stage2.hip", PARTS + "".join(f'static_assert({c}, "{c}");\n' for c in claims)),
                       ("k_stage4.hip", "".join(f'static_assert({c}, "{c}");\n' for c in (
-                          "s4_cuts(1024, 8)", "!s4_cuts(1024, 9)", "!s4_cuts(1025, 1)", "s4_cuts(256, 32)", "!s4_cuts(256, 33)", "s4_cuts(1, 8192)")))):
+                          "s4_cuts(1024, 8)", "!s4_cuts(1024, 9)", "!s4_cuts(1025, 1)", "s4_cuts(256, 32)", "!s4_cuts(256, 33)", "s4_cuts(1, 8192)",
+                          # what is written past the caches: more than the last of them holds, 256 MB
+                          "!s4_past_caches(419430, true, true)", "s4_past_caches(419431, true, true)", "!s4_past_caches(524288, true, false)",
+                          "s4_past_caches(524289, true, false)", "!s4_past_caches(2097152, false, true)", "s4_past_caches(2097153, false, true)",
+                          "s4_past_caches(1ll << 40, true, true)", "!s4_past_caches(0, true, true)")))):
         unit = tmp_path / ("rules_" + src)
         unit.write_text(f'#include "{src}"\n' + body)
         r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-fconstexpr-steps=100000000", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
