@@ -214,7 +214,9 @@ int plaid_get_stage2_kernel(const plaid_index *idx, int32_t *form);
 #define PLAID_NUM_STAGES 10
 /* stage order: 0 workspace clearing + query layout, 1 S_cq + pruning map (Eq. 2, 5), 2 top-nprobe, probe union and
  * table of surviving centroids, 3 candidate union (Section 4.1), 4 stage-2 interaction (Eq. 3-5), 5 select ndocs,
- * 6 stage-3 interaction (Eq. 3-4), 7 select ndocs/4, 8 stage-4 decompress + MaxSim (Section 4.5, Eq. 1), 9 top-k */
+ * 6 stage-3 interaction (Eq. 3-4), 7 select ndocs/4, 8 stage-4 decompress + MaxSim (Section 4.5, Eq. 1), 9 top-k.  What
+ * one kernel does of two stages counts for the later one: with the inverted form 3 is in 4, in short launches the probe union of 2
+ * too, and with short lists, few in all, 7 is in 8. */
 int plaid_set_stage_timing(plaid_index *idx, int32_t on);
 int plaid_get_stage_ms(const plaid_index *idx, float *out_ms);
 

@@ -949,18 +949,18 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         // stage 3: centroid interaction without pruning (Eq. 3-4), keep ndocs/4
         plaid_launch_ci_list(st, w.S, C, ix->doc_offsets, ix->codes, n, w.sel2, pl.nd, w.n2, pl.nd, w.keys3, pl.nd);
         STAMP();
-        // (both at once where there is little to do and nobody asks for the cut or its time)
-        const bool ask = timing || (dbg && (dbg->sel3_ids || dbg->sel3_scores || dbg->n3));
-        const bool cut = !ask && plaid_launch_cut_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, n,
-                                                         w.keys3, pl.nd, w.n2, pl.nd, pl.m3, w.keys4, pl.m3, w.n3,
-                                                         ix->renormalize ? ix->inv_norm : nullptr);
+        // (where there is little to do, by one launch: stage 4's)
+        const bool cut = plaid_cut_with_scores(pl.nd, n);
         if (!cut) plaid_launch_select(st, w.keys3, pl.nd, w.n2, n, pl.nd, pl.m3, w.sel3, pl.m3, w.n3, 0, sc3, 0);
         STAMP();
         // stage 4: decompression (Section 4.5) + exact MaxSim (Eq. 1), best k
-        if (!cut)
+        const float *inv_norm = ix->renormalize ? ix->inv_norm : nullptr;
+        if (cut)
+            plaid_launch_cut_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, n, w.keys3, pl.nd,
+                                    w.n2, pl.nd, pl.m3, w.keys4, pl.m3, w.n3, dbg && (dbg->sel3_ids || dbg->sel3_scores) ? w.sel3 : nullptr, inv_norm);
+        else
             plaid_launch_decompress_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights,
-                                           ix->nbits, n, w.sel3, pl.m3, w.n3, pl.m3, w.keys4, pl.m3,
-                                           ix->renormalize ? ix->inv_norm : nullptr);
+                                           ix->nbits, n, w.sel3, pl.m3, w.n3, pl.m3, w.keys4, pl.m3, inv_norm);
         STAMP();
         if (pl.m3 <= SEL_SORT_CAP) {
             plaid_launch_rank_output(st, w.keys4, pl.m3, w.n3, n, pl.m3, k, out_ids + (int64_t)q0 * k,
