@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256, COOP ? 3 : 4) void decompress_maxsim_kernel(
 
 // Stage 3's cut and the scores of what it keeps in one launch, for lists of up to CUT_KEYS keys (short launches): a workgroup per key of the
 // list, which counts the keys before its own and leaves if there are m of them; otherwise its passage's score goes to the place of that
-// number in out_keys (and its key of stage 3 to that place in kept, unless null).  The four waves share the passage as above.  Bound by the round trips to memory that follow one another (keys, code,
+// number in out_keys.  The four waves share the passage as above.  Bound by the round trips to memory that follow one another (keys, code,
 // scores), which a launch's start and a list that goes through memory only add to: one query of 400 000 passages, 1024 keys of which 256
 // stay, 5.2 and 6.9 us as two launches, 6.9 us so; 256 keys of which 64 stay 4.2 and 5.5, 4.8 so.
 #define CUT_KEYS 1024
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256, 3) void cut_maxsim_kernel(
     const float *__restrict__ Q, const float *__restrict__ S, int64_t C, const int64_t *__restrict__ doc_offsets,
     const int32_t *__restrict__ codes, const uint8_t *__restrict__ residuals, const float *__restrict__ weights,
     const float *__restrict__ inv_norm, const uint64_t *__restrict__ in_keys, int64_t in_stride, const int32_t *__restrict__ in_counts,
-    int32_t m, uint64_t *__restrict__ out_keys, int64_t out_stride, int32_t *__restrict__ out_counts, uint64_t *__restrict__ kept)
+    int32_t m, uint64_t *__restrict__ out_keys, int64_t out_stride, int32_t *__restrict__ out_counts)
 {
     constexpr int RB = 16 * NBITS, RW = 2 * NBITS, EACH = CUT_KEYS / 256;
     __shared__ typename S4Entry<NBITS>::type hlut[S4_SECOND + 256];
@@ -485,7 +485,6 @@ __global__ __launch_bounds__(256, 3) void cut_maxsim_kernel(
     __syncthreads();
     const int rank = fewer[0] + fewer[1] + fewer[2] + fewer[3];
     if (rank >= m) return;  // uniform
-    if (kept && threadIdx.x == 0) kept[(int64_t)q * out_stride + rank] = mine;
     const int len = (int)(t1 - t0);
     int32_t code = 0;
     float nf = 1.0f;
@@ -1176,13 +1175,13 @@ bool plaid_cut_with_scores(int n_upper, int nq) { return n_upper > 0 && nq > 0 &
 void plaid_launch_cut_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets, const int32_t *codes,
                              const uint8_t *residuals, const float *bucket_weights, int nbits, int nq, const uint64_t *in_keys,
                              int64_t in_stride, const int32_t *in_counts, int n_upper, int32_t m, uint64_t *out_keys, int64_t out_stride,
-                             int32_t *out_counts, uint64_t *kept, const float *inv_norm)
+                             int32_t *out_counts, const float *inv_norm)
 {
     const bool wide = plaid_wide(C, N);
 #define PLAID_S4_CUT(NB, RN, WIDE)                                                                                              \
     hipLaunchKernelGGL((cut_maxsim_kernel<NB, RN, WIDE>), dim3((unsigned)n_upper, (unsigned)nq), dim3(256), 0, st, Q, S, C,        \
                        doc_offsets, codes, residuals, bucket_weights, inv_norm, in_keys, in_stride, in_counts, m, out_keys,       \
-                       out_stride, out_counts, kept)
+                       out_stride, out_counts)
 #define PLAID_S4_CUTS(NB)                                  \
     do {                                                   \
         if (inv_norm && wide) PLAID_S4_CUT(NB, true, true); \

@@ -67,6 +67,28 @@ void plaid_launch_keys_to_pairs(hipStream_t st, const uint64_t *keys, int64_t ke
                        out_scores, out_counts);
 }
 
+// A workgroup per query; the lists have up to some thousand keys, each passage once.
+__global__ __launch_bounds__(256) void keys_of_passages_kernel(const uint64_t *__restrict__ in_keys, int64_t in_stride,
+                                                               const int32_t *__restrict__ in_counts, const uint64_t *__restrict__ keys,
+                                                               const int32_t *__restrict__ counts, int64_t stride, uint64_t *__restrict__ out)
+{
+    const int q = blockIdx.x, n = in_counts[q], m = counts[q];
+    for (int j = threadIdx.x; j < m; j += 256) {
+        const uint32_t pid = (uint32_t)keys[(int64_t)q * stride + j];
+        uint64_t found = PLAID_KEY_MAX;
+        for (int i = 0; i < n; ++i) {
+            const uint64_t key = in_keys[(int64_t)q * in_stride + i];
+            found = (uint32_t)key == pid ? key : found;
+        }
+        out[(int64_t)q * stride + j] = found;
+    }
+}
+void plaid_launch_keys_of_passages(hipStream_t st, const uint64_t *in_keys, int64_t in_stride, const int32_t *in_counts, const uint64_t *keys,
+                                   const int32_t *counts, int64_t stride, int nq, uint64_t *out)
+{
+    hipLaunchKernelGGL(keys_of_passages_kernel, dim3(nq), dim3(256), 0, st, in_keys, in_stride, in_counts, keys, counts, stride, out);
+}
+
 // Ascending list of the set bits of bits[q][0..words).  A workgroup lists `chunk` words (a multiple of 1024) and counts the bits of all
 // words before them itself, a few loads per thread and no waiting for another workgroup.  A wave writes the ids of 64 passages at a
 // time, side by side.  Sixteen queries of 400 000 candidates: 12 us, with one workgroup per query, a scan through LDS and a thread

@@ -957,7 +957,7 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
         const float *inv_norm = ix->renormalize ? ix->inv_norm : nullptr;
         if (cut)
             plaid_launch_cut_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights, ix->nbits, n, w.keys3, pl.nd,
-                                    w.n2, pl.nd, pl.m3, w.keys4, pl.m3, w.n3, dbg && (dbg->sel3_ids || dbg->sel3_scores) ? w.sel3 : nullptr, inv_norm);
+                                    w.n2, pl.nd, pl.m3, w.keys4, pl.m3, w.n3, inv_norm);
         else
             plaid_launch_decompress_maxsim(st, Qc, w.S, C, ix->N, ix->doc_offsets, ix->codes, ix->residuals, ix->weights,
                                            ix->nbits, n, w.sel3, pl.m3, w.n3, pl.m3, w.keys4, pl.m3, inv_norm);
@@ -992,6 +992,8 @@ static int search_impl(plaid_index *ix, const float *Q, int32_t nq, int32_t npro
                                            dbg->sel2_ids ? dbg->sel2_ids + (int64_t)q0 * ndocs : nullptr,
                                            dbg->sel2_scores ? dbg->sel2_scores + (int64_t)q0 * ndocs : nullptr,
                                            dbg->n2 ? dbg->n2 + q0 : nullptr);
+            if (cut && (dbg->sel3_ids || dbg->sel3_scores))
+                plaid_launch_keys_of_passages(st, w.keys3, pl.nd, w.n2, w.keys4, w.n3, pl.m3, n, w.sel3);
             if (dbg->sel3_ids || dbg->sel3_scores || dbg->n3)
                 plaid_launch_keys_to_pairs(st, w.sel3, pl.m3, w.n3, n, m3,
                                            dbg->sel3_ids ? dbg->sel3_ids + (int64_t)q0 * m3 : nullptr,

@@ -396,12 +396,15 @@ void plaid_launch_decompress_maxsim(hipStream_t st, const float *Q, const float 
                                     const int32_t *in_counts, int n_upper, uint64_t *out_keys, int64_t out_stride,
                                     const float *inv_norm = nullptr /* [N]: reconstructed vectors scaled to unit length */);
 // The cut of a key list to its m best and their scores as above in one launch, for short lists (plaid_cut_with_scores): in any order
-// to out_keys, their number to out_counts; with kept (null: not asked for) also the keys that stay, leading dimension out_stride.
+// to out_keys, their number to out_counts.
 bool plaid_cut_with_scores(int n_upper, int nq);
 void plaid_launch_cut_maxsim(hipStream_t st, const float *Q, const float *S, int64_t C, int64_t N, const int64_t *doc_offsets, const int32_t *codes,
                              const uint8_t *residuals, const float *bucket_weights, int nbits, int nq, const uint64_t *in_keys,
                              int64_t in_stride, const int32_t *in_counts, int n_upper, int32_t m, uint64_t *out_keys, int64_t out_stride,
-                             int32_t *out_counts, uint64_t *kept, const float *inv_norm);
+                             int32_t *out_counts, const float *inv_norm);
+// The keys of in_keys that belong to the passages of keys[q][0 .. counts[q]) (debug output of what such a cut keeps).
+void plaid_launch_keys_of_passages(hipStream_t st, const uint64_t *in_keys, int64_t in_stride, const int32_t *in_counts, const uint64_t *keys,
+                                   const int32_t *counts, int64_t stride, int nq, uint64_t *out);
 
 // Section 4.5 alone: reconstructed vectors / bucket indices of listed passages.
 void plaid_launch_decompress_dump(hipStream_t st, const float *centroids, const int64_t *doc_offsets,
