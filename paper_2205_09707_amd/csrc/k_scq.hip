@@ -77,7 +77,7 @@ __device__ __forceinline__ void scq_insert_key(uint64_t (&best)[NP], uint64_t ke
 
 struct Stage1Out {          // per-query outputs of the tail (device pointers, leading dimension = query)
     int32_t *probed;        // [nq][32][nprobe] best first
-    int32_t *uniq;          // [nq][uniq_stride] ascending distinct probed centroids
+    int32_t *uniq;          // [nq][uniq_stride] ascending distinct probed centroids (see probes_apart)
     int32_t *n_uniq;        // [nq]
     int uniq_stride;
     S2Meta *meta;           // [nq]

@@ -20,6 +20,10 @@ KERNELS = {
     "stage1_tail_kernelILi8ELb0E": ("k_scq.hip", 128, 64 << 10),
     "stage1_tail_kernelILi2ELb1E": ("k_scq.hip", 128, 64 << 10),   # ... also with the re-evaluations in double
     "stage1_tail_kernelILi8ELb1E": ("k_scq.hip", 128, 64 << 10),
+    "stage1_parts_kernelILi1E": ("k_scq.hip", 128, 64 << 10),      # the survivors' workgroup has 1024 threads
+    "stage1_parts_kernelILi2E": ("k_scq.hip", 128, 64 << 10),
+    "stage1_parts_kernelILi4E": ("k_scq.hip", 128, 64 << 10),
+    "stage1_parts_kernelILi8E": ("k_scq.hip", 128, 64 << 10),
     "scq16_kernelILi2ELb1E": ("k_scq16.hip", 256, 40 << 10),   # two waves per SIMD, two to four workgroups per CU
     "scq16_kernelILi2ELb0E": ("k_scq16.hip", 256, 32 << 10),   # without group maxima: the two operand buffers and nothing else
     # a wave per 2048 passages, 256 threads: what the workgroups per compute unit that its launch bounds name can have
@@ -42,6 +46,14 @@ KERNELS = {
     "decompress_maxsim_kernelILi1ELb0ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
     "decompress_maxsim_kernelILi2ELb0ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),   # ... with 64-bit offsets of rows
     "decompress_maxsim_kernelILi2ELb0ELb1ELb0E": ("k_stage4.hip", 128, 32 << 10),   # ... with unit-length reconstruction
+    "cut_maxsim_kernelILi2ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),   # a workgroup per key: four waves per SIMD
+    "cut_maxsim_kernelILi1ELb0ELb0E": ("k_stage4.hip", 128, 32 << 10),
+    "cut_maxsim_kernelILi2ELb1ELb0E": ("k_stage4.hip", 128, 32 << 10),   # ... with unit-length reconstruction
+    "cut_maxsim_kernelILi1ELb1ELb0E": ("k_stage4.hip", 128, 32 << 10),
+    "cut_maxsim_kernelILi2ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),   # ... with 64-bit offsets of rows
+    "cut_maxsim_kernelILi1ELb0ELb1E": ("k_stage4.hip", 128, 32 << 10),
+    "cut_maxsim_kernelILi2ELb1ELb1E": ("k_stage4.hip", 128, 32 << 10),
+    "cut_maxsim_kernelILi1ELb1ELb1E": ("k_stage4.hip", 128, 32 << 10),
     # three waves per SIMD, three workgroups per CU (the pruning instances add 8 KB of dynamic LDS)
     "maxsim_list_kernelILi2ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
     "maxsim_list_kernelILi1ELb1ELb0ELb0E": ("k_stage4.hip", 168, 45 << 10),
@@ -52,7 +64,8 @@ KERNELS = {
     "van_coarse_kernelILi1E": ("k_stage4.hip", 128, 32 << 10),
     "van_bounds_kernel": ("k_stage4.hip", 64, 1 << 10),
     "van_band_kernel": ("k_stage4.hip", 64, 1 << 10),
-    "decompress_dump_kernelILi2E": ("k_stage4.hip", 64, 8 << 10),
+    "decompress_dump_kernelILi2E": ("k_stage4.hip", 64, 8 << 10),        # eight workgroups of 256 threads per CU
+    "decompress_dump_kernelILi1E": ("k_stage4.hip", 64, 16 << 10),
     "passage_offsets_kernel": ("k_stage4.hip", 64, 1 << 10),
     "van_codes_kernel": ("k_vanilla.hip", 64, 1 << 10),
     "van_union_kernel": ("k_vanilla.hip", 64, 8 << 10),
@@ -68,7 +81,7 @@ KERNELS = {
     "bitmap_to_list_kernel": ("k_util.hip", 64, 1 << 10),          # 1024 threads, two workgroups per CU
     "encode_residuals_kernelILi2E": ("k_build.hip", 64, 0),
     "ivb_rank_kernel": ("k_build.hip", 64, 0),
-    "ivb_sort_short_kernel": ("k_build.hip", 64, 32 << 10),      # a 2048-entry LDS area per wave
+    "ivb_sort_short_kernel": ("k_build.hip", 64, 0),             # up to 32 entries per lane in registers: eight waves per SIMD
     "ivb_sort_long_kernel": ("k_build.hip", 128, 130 << 10),     # a bitmap of 2^20 passage ids: one workgroup (16 waves) per CU
 }
 
