@@ -231,10 +231,11 @@ __global__ __launch_bounds__(ASG_THREADS, 2) void asg_screen_kernel(const asg_ha
 // centroids twice in a row: 62.9 ms that way, 1.6 with the products dealt to the threads (bound by the rows, which a lane
 // each reads 16 bytes of at a time), 0.79 now.  Five waves per SIMD: with four (the products unrolled further) vectors whose
 // winner is clear, most of them, wait longer for their block maxima (740 000 against 4096 centroids 97 us, 88 with five).
-// The block maxima, 256 bytes a group and block of rows, are read once, and by the open vectors, each its own, once more.  The first time past
-// the caches (nontemporal loads): 585 000 vectors against 32 768 centroids, six launches, 316 -> 253 us.  Where all vectors are open, whose
-// second reading then goes to memory, the products take the time: ms per call with loads through the caches / past them, every centroid with a
-// near one in another block 7.59 / 7.58, with seven of them 7.90 / 7.97 (runs of one side differ by 2 %), 200 000 vectors against 1024 centroids each twice 0.82 / 0.83.
+// The block maxima, 256 bytes a group and block of rows, are read once, and by the open vectors, each its own, once more.  The first time
+// past the caches (nontemporal loads): 585 000 vectors against 32 768 centroids, six launches, 316 -> 253 us.  Where all vectors are open,
+// whose second reading then goes to memory, the products take the time: ms per call with loads through the caches / past them, every
+// centroid with a near one in another block 7.59 / 7.58, with seven of them 7.90 / 7.97 (runs of one side differ by 2 %), 200 000 vectors
+// against 1024 centroids each twice 0.82 / 0.83.
 typedef float asg_float2 __attribute__((ext_vector_type(2)));
 __global__ __launch_bounds__(256, 5) void asg_pick_kernel(const float *__restrict__ centroids, int64_t C, const float *__restrict__ x,
                                                        int64_t n, const float2 *__restrict__ best2, int64_t n_blk,

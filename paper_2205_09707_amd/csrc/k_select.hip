@@ -1001,7 +1001,8 @@ __device__ __forceinline__ void sel2_filter_body(const uint64_t *__restrict__ ke
                                                  int64_t cand_words, int64_t P, int32_t m, const S2Meta *__restrict__ meta,
                                                  const int32_t *__restrict__ hist, Sel2State *state, uint64_t *__restrict__ out,
                                                  int64_t out_stride, uint64_t *__restrict__ blist, int64_t blist_stride, int lists,
-                                                 const int32_t *__restrict__ list_counts, int id_shift, int32_t *__restrict__ hist1, int32_t *__restrict__ low,
+                                                 const int32_t *__restrict__ list_counts, int id_shift, int32_t *__restrict__ hist1,
+                                                 int32_t *__restrict__ low,
                                                  int32_t *lh /* [SEL_BINS + SEL2_SUB] */)
 {
     __shared__ int32_t scan[SEL_THREADS];
@@ -1157,8 +1158,8 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void sel2_filter_kernel(const uint6
                                                                   uint64_t *__restrict__ blist, int64_t blist_stride, int lists,
                                                                   const int32_t *__restrict__ list_counts)
 {
-    sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists, list_counts, 0,
-                            nullptr, nullptr, nullptr);
+    sel2_filter_body<false>(keys, key_stride, candbits, cand_words, P, m, meta, hist, state, out, out_stride, blist, blist_stride, lists,
+                            list_counts, 0, nullptr, nullptr, nullptr);
 }
 __global__ __launch_bounds__(SEL_THREADS, 6) void sel2_bins_kernel(const uint64_t *__restrict__ keys, int64_t key_stride,
                                                                 const uint32_t *__restrict__ candbits, int64_t cand_words, int64_t P,

@@ -1102,8 +1102,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
     const int32_t *__restrict__ kept_ids, const float *__restrict__ T, uint32_t *__restrict__ candbits, int64_t cand_words,
     uint64_t *__restrict__ keys2, int64_t key_stride, int32_t *__restrict__ hist,
     int32_t *__restrict__ list_counts, uint32_t *__restrict__ emptybits, const int32_t *__restrict__ dense_id,
-    const uint32_t *__restrict__ dense_bits, int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride, int nqx, int len_log,
-    int steps, int32_t m, int first_batch, unsigned main_blocks, uint32_t tall)
+    const uint32_t *__restrict__ dense_bits, int mode, const int32_t *__restrict__ qcount, const int32_t *__restrict__ qlist, int qlist_stride,
+    int nqx, int len_log, int steps, int32_t m, int first_batch, unsigned main_blocks, uint32_t tall)
 {
     constexpr int KMAX = sizeof(SetT) == 4 ? 31 : S2_MAX_KEPT;
     // Planes of 64 words that fit a wave's area: what lets four workgroups share a compute unit.  Only lists with an entry in
@@ -1638,7 +1638,8 @@ __global__ __launch_bounds__(64 * IV_WAVES, TALL ? S2_TALL_UNIT_BLOCKS : S2_UNIT
                 s2_wave_sync();
                 // (both of a lane's bins in one addition)
                 const uint32_t counts = lstart[lane];
-                if (counts) atomicAdd(reinterpret_cast<unsigned long long *>(coarse_q) + lane, (unsigned long long)(counts >> 16) << 32 | (counts & 0xFFFFu));
+                if (counts)
+                    atomicAdd(reinterpret_cast<unsigned long long *>(coarse_q) + lane, (unsigned long long)(counts >> 16) << 32 | (counts & 0xFFFFu));
             }
             s2_wave_sync();  // the next range's planes overwrite what the last batch read
         }
@@ -1705,12 +1706,13 @@ static constexpr int64_t s2_first_batch(int64_t P, int64_t nq, int64_t m, int le
 
 // Whether a query's key list is in parts.  The waves of a single query reserve their first places at about the same time, and some ten
 // nanoseconds after one another where there is one counter: up to 20 us for the last of two thousand.  Parts cost the selection a
-// microsecond or two, which reads their numbers first.  us per search with one list / parts, one query, by its number of waves, nprobe 1 and ndocs 256,
-// 2 and 1024, 4 and 4096: 391 66.6 / 66.6, 71.0 / 72.5, 99.5 / 100.3; 398 71.1 / 71.4, 77.7 / 78.4, 109.7 / 110.1; 416 73.8 / 74.1, 79.3 / 80.1, 111.1 / 111.6;
-// 440 72.2 / 71.6, 78.8 / 79.6, 111.6 / 111.6; 464 75.1 / 75.0, 80.1 / 81.3, 112.5 / 113.1; 489 72.0 / 70.8, 79.1 / 78.9, 113.6 / 113.5; 586 73.9 / 72.2, 79.8 / 79.3,
-// 113.9 / 113.2; 733 77.6 / 75.1, 84.5 / 83.6, 116.6 / 114.8; 977 83.2 / 79.8, 91.1 / 89.4, 121.6 / 118.8; shorter ranges (ndocs 60 000 to 300 000): 450
-// 247.5 / 247.2, 782 308 / 302, 977 623 / 615.  Four queries of 2 M passages 113 / 110, 133 / 133, 167 / 168, of 4 M 149 / 149; sixteen of
-// 400 000 152 / 155, of 2 M 253 / 260, of 4 M 337 / 352.
+// microsecond or two, which reads their numbers first.  us per search with one list / parts, one query, by its number of waves, nprobe 1
+// and ndocs 256, 2 and 1024, 4 and 4096: 391 66.6 / 66.6, 71.0 / 72.5, 99.5 / 100.3; 398 71.1 / 71.4, 77.7 / 78.4, 109.7 / 110.1; 416 73.8
+// / 74.1, 79.3 / 80.1, 111.1 / 111.6; 440 72.2 / 71.6, 78.8 / 79.6, 111.6 / 111.6; 464 75.1 / 75.0, 80.1 / 81.3, 112.5 / 113.1; 489 72.0 /
+// 70.8, 79.1 / 78.9, 113.6 / 113.5; 586 73.9 / 72.2, 79.8 / 79.3, 113.9 / 113.2; 733 77.6 / 75.1, 84.5 / 83.6, 116.6 / 114.8; 977 83.2 /
+// 79.8, 91.1 / 89.4, 121.6 / 118.8; shorter ranges (ndocs 60 000 to 300 000): 450 247.5 / 247.2, 782 308 / 302, 977 623 / 615.  Four
+// queries of 2 M passages 113 / 110, 133 / 133, 167 / 168, of 4 M 149 / 149; sixteen of 400 000 152 / 155, of 2 M 253 / 260, of 4 M 337 /
+// 352.
 static constexpr bool s2_parts(int nq, int64_t waves) { return nq == 1 && waves > 480; }
 
 // The numbers of survivors K (bit K - 32) whose queries the TALL instance takes in launches of many workgroups.  share: how
@@ -1766,7 +1768,7 @@ bool plaid_launch_stage2_inverted(hipStream_t st, const int32_t *uniq, const int
     const unsigned gather = words < S2_GATHER_BLOCKS ? (unsigned)words : S2_GATHER_BLOCKS;
     const unsigned gather_tall = words < 256 * S2_TALL_UNIT_BLOCKS ? (unsigned)words : 256 * S2_TALL_UNIT_BLOCKS;
     const uint32_t tall = shift == 11 ? s2_tall_queries(plane_share) : 0u;
-#define S2_INVERT(SH_, T_, PLAIN_, ALL_, TALL_, MODE_, NQX_, BLOCKS_, GATHER_)                                                                            \
+#define S2_INVERT(SH_, T_, PLAIN_, ALL_, TALL_, MODE_, NQX_, BLOCKS_, GATHER_)                                                   \
     hipLaunchKernelGGL((s2_invert_kernel<SH_, T_, PLAIN_, ALL_, TALL_>), dim3((unsigned)((BLOCKS_) * (NQX_)) + (GATHER_)),                    \
                        dim3(64 * IV_WAVES), 0, st, uniq,                                                                      \
                        n_uniq, uniq_stride, ivf_offsets, ivf_pids, table, nr, S, C, keepbits, keep_words, codes, doc_offsets, \

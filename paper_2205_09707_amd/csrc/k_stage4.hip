@@ -1343,17 +1343,19 @@ void plaid_launch_passage_offsets(hipStream_t st, const int64_t *doc_offsets, in
 
 // Same table, same lookup and same addition as the fused kernel; a workgroup per passage, a token to 32 threads, 4 dimensions each.
 // Bound by its writes and by the centroid rows, 512 bytes a token each.
-// Threads of a workgroup: twice as many fetch twice the rows of a long passage at once, but leave fewer passages in flight on a
-// compute unit, and what a list's passages are like does not follow from the collection's mean.  us per call with 256 / 512, lists of
-// 50 000 passages: of 1 to 8 tokens 96 / 125, of 8 to 24 133 / 196, of 24 to 40 290 / 329, of 30 to 100 610 / 596 (of 262 144 centroids 637 / 653); of
-// 5000: 23 / 23, 23 / 27, 31 / 31, 51 / 54; 1000 of 100 to 300 36 / 38; 100 of 1000 to 3000, which are too few passages to fill the chip, 148 / 94.
+// Threads of a workgroup: twice as many fetch twice the rows of a long passage at once, but leave fewer passages in flight on a compute
+// unit, and what a list's passages are like does not follow from the collection's mean.  us per call with 256 / 512, lists of 50 000
+// passages: of 1 to 8 tokens 96 / 125, of 8 to 24 133 / 196, of 24 to 40 290 / 329, of 30 to 100 610 / 596 (of 262 144 centroids 637 /
+// 653); of 5000: 23 / 23, 23 / 27, 31 / 31, 51 / 54; 1000 of 100 to 300 36 / 38; 100 of 1000 to 3000, which are too few passages to fill
+// the chip, 148 / 94.
 #define DUMP_THREADS 256
 // Whether what is written goes past the caches (nontemporal stores).  Then they hold more of the rows and codes, but whoever reads the
-// vectors next finds none of them there; where they do not fit the 256 MB of the last cache, he would not in any case.  Passages of 65
-// tokens, vectors and indices, us of a call alone / of the call and a sum over the vectors / of the call and their product with 32 columns, through the
-// caches and past them, lists that are not seen again soon: 1000 (42 MB) 23.1, 38.5, 45.2 and 21.3, 41.2, 48.1; 2000 34.7, 54.7, 61.1 and 33.4, 60.6, 66.0;
-// 5000 (208 MB) 70.4, 106, 123 and 70.3, 123, 130; 6000 (250 MB) 82.8, 133, 151 and 82.1, 144, 153; 8000 (333 MB) 118, 197, 210 and 106, 185, 199;
-// 50 000 656, 1084, 1140 and 610, 1054, 1113.  Eight lists of 5000 in turn, whose codes and rows the caches can hold: 71.7, 111, 129 and 50.6, 124, 134.
+// vectors next finds none of them there; where they do not fit the 256 MB of the last cache, most would be gone anyway.  Passages of 65
+// tokens, vectors and indices, us of a call alone / of the call and a sum over the vectors / of the call and their product with 32 columns,
+// through the caches and past them, lists that are not seen again soon: 1000 (42 MB) 23.1, 38.5, 45.2 and 21.3, 41.2, 48.1; 2000 34.7,
+// 54.7, 61.1 and 33.4, 60.6, 66.0; 5000 (208 MB) 70.4, 106, 123 and 70.3, 123, 130; 6000 (250 MB) 82.8, 133, 151 and 82.1, 144, 153; 8000
+// (333 MB) 118, 197, 210 and 106, 185, 199; 50 000 656, 1084, 1140 and 610, 1054, 1113.  Eight lists of 5000 in turn, whose codes and rows
+// the caches can hold: 71.7, 111, 129 and 50.6, 124, 134.
 static constexpr __host__ __device__ bool s4_past_caches(int64_t tokens, bool vectors, bool indices)
 {
     return tokens * ((vectors ? DIM * 4 : 0) + (indices ? DIM : 0)) > (256ll << 20);

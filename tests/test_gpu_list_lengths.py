@@ -5,7 +5,8 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-LENGTHS = [0, 1, 2, 3, 4, 5, 8, 9, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 1500, 2047, 2048, 2049, 3000]
+LENGTHS = [0, 1, 2, 3, 4, 5, 8, 9, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025,
+           1500, 2047, 2048, 2049, 3000]
 
 
 @pytest.mark.parametrize("P", [3000, 70_001])

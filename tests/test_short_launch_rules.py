@@ -1,5 +1,6 @@
 """Where a single query's key list is in parts, and that the parts' places neither overlap nor leave the list; which lists are cut and scored
-by one launch; which vectors are written past the caches.  On the GPU, a query whose list is in parts against the same one in a launch of four, where none is."""
+by one launch; which vectors are written past the caches.  On the GPU, a query whose list is in parts against the same one in a launch of
+four, where none is."""
 import os
 import shutil
 import subprocess
@@ -30,8 +31,8 @@ constexpr bool parts_fit(int64_t passages, int64_t P) {  // a workgroup's passag
 @pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not installed")
 def test_rules_of_parts_and_cuts(tmp_path):
     claims = ["s2_parts(1, 481)", "!s2_parts(1, 480)", "!s2_parts(2, 4297)"]
-    claims += [f"parts_fit({n}, {P})" for n in (128, 256, 512, 1024, 2048, 4096, 8192, 16384) for P in (1, 1023, 400_385, 405_003, 409_600, 800_769, 8 * 16384, 8 * 16384 + 1,
-                                                                                   2_000_001, 8_800_000, (1 << 31) - 1)
+    claims += [f"parts_fit({n}, {P})" for n in (128, 256, 512, 1024, 2048, 4096, 8192, 16384)
+               for P in (1, 1023, 400_385, 405_003, 409_600, 800_769, 8 * 16384, 8 * 16384 + 1, 2_000_001, 8_800_000, (1 << 31) - 1)
                if P < 1_000_000 or n > 4096]
     for src, body in (("k_stage2.hip", PARTS + "".join(f'static_assert({c}, "{c}");\n' for c in claims)),
                       ("k_stage4.hip", "".join(f'static_assert({c}, "{c}");\n' for c in (
@@ -42,8 +43,9 @@ def test_rules_of_parts_and_cuts(tmp_path):
                           "s4_past_caches(1ll << 40, true, true)", "!s4_past_caches(0, true, true)")))):
         unit = tmp_path / ("rules_" + src)
         unit.write_text(f'#include "{src}"\n' + body)
-        r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-fconstexpr-steps=100000000", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
-                            "--cuda-host-only", "-fsyntax-only", str(unit)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-fconstexpr-steps=100000000", "-I" + os.path.join(ROOT, "include"),
+                            "-I" + CSRC, "--cuda-host-only", "-fsyntax-only", str(unit)],
+                           stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert r.returncode == 0, r.stdout
 
 
